@@ -2771,8 +2771,26 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
         if (knn_search_lds_bytes(c->d, c->k) > (size_t)lds_max) return SC_EDOMAIN;  // d and k_nn too large together
         DevBuf<double> xp;
         xp.alloc((size_t)c->n * (knn_padded_dim(c->d) + 1));  // padded rows, then one squared norm per row
-        HIP_TRY(launch_knn_search(c->x, c->ldx, c->n, c->d, c->k, xp.p, c->idx, c->dist, c->st));
+        HIP_TRY(launch_knn_pad(c->x, c->ldx, c->n, c->d, xp.p, c->st));
+        const size_t wb = knn_screen_workspace(c->n, c->d, c->k);
+        if (wb == 0) {
+          HIP_TRY(launch_knn_search(c->n, c->d, c->k, xp.p, nullptr, 0, nullptr, c->idx, c->dist, c->st));
+          HIP_TRY(hipStreamSynchronize(c->st));
+          return SC_OK;
+        }
+        DevBuf<char> work;
+        PinnedBuf<int32_t> left;
+        work.alloc(wb);
+        left.alloc(1);
+        int32_t *tiles = nullptr, *ntiles = nullptr;
+        double* bound = nullptr;
+        HIP_TRY(launch_knn_screen(xp.p, c->n, c->d, c->k, work.p, left.p, &tiles, &ntiles, &bound, c->idx, c->dist, c->st));
+        HIP_TRY(hipMemcpyAsync(left.p, ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
+        if (*left.p > 0) {
+          HIP_TRY(launch_knn_search(c->n, c->d, c->k, xp.p, tiles, *left.p, bound, c->idx, c->dist, c->st));
+          HIP_TRY(hipStreamSynchronize(c->st));
+        }
         return SC_OK;
       },
       &ctx);

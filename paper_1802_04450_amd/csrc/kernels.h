@@ -268,12 +268,21 @@ hipError_t launch_edge_similarity(const double* x, int64_t ldx, int d, const int
 // ---- k-nearest-neighbour graph (Section III-A; knn.hip) -------------------------------------------------------
 // Exact Euclidean k nearest neighbours of every row of x (n x d, leading dimension ldx) other than the row itself:
 // idx_out[i*k + a] / dist_out[i*k + a] = index / distance of the a-th nearest, nearest first, equal distances by
-// index.  xp: device scratch of n * (knn_padded_dim(d) + 1) doubles.  2 <= n <= INT32_MAX, 1 <= k <= n - 1, and
-// knn_search_lds_bytes(d, k) must not exceed the LDS a workgroup may have (else hipErrorInvalidValue).
+// index.  xp: device scratch of n * (knn_padded_dim(d) + 1) doubles, which launch_knn_pad fills with the rows, zero
+// padded.  2 <= n <= INT32_MAX, 1 <= k <= n - 1, and knn_search_lds_bytes(d, k) must not exceed the LDS a workgroup may
+// have (else hipErrorInvalidValue).
 int knn_padded_dim(int d);
 size_t knn_search_lds_bytes(int d, int k);
-hipError_t launch_knn_search(const double* x, int64_t ldx, int64_t n, int d, int k, double* xp, int32_t* idx_out,
-                             double* dist_out, hipStream_t st);
+hipError_t launch_knn_pad(const double* x, int64_t ldx, int64_t n, int d, double* xp, hipStream_t st);
+// The bf16 screen: bytes of scratch it needs, 0 where it is not used.  It leaves device pointers to a list of tiles of
+// 64 queries that it could not settle, to their number and to an upper bound of every query's k-th squared distance;
+// launch_knn_search does those (tiles, ntiles, bound), or every query when tiles is null (all that there is to do without
+// the screen; bound may be null then).  host: pinned int32; the call waits for the stream (once per round of queries).
+size_t knn_screen_workspace(int64_t n, int d, int k);
+hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* work, int32_t* host, int32_t** tiles,
+                             int32_t** ntiles, double** bound, int32_t* idx_out, double* dist_out, hipStream_t st);
+hipError_t launch_knn_search(int64_t n, int d, int k, double* xp, const int32_t* tiles, int64_t ntiles,
+                             const double* bound, int32_t* idx_out, double* dist_out, hipStream_t st);
 // The undirected edges {i, j} (j in i's list or i in j's) once each as eu < ev, in row order of the emitting list;
 // val = the listed distance, or exp(-dist^2 / (2 sigma^2)) if sigma > 0.  eu, ev, val have room for n * k entries;
 // last_two (device int32[2]) receives two numbers whose sum is the pair count.  work: knn_pairs_workspace(n) bytes.

@@ -5,7 +5,8 @@
 // Search.  The distance that ranks the neighbours is the plain sum of squared coordinate differences in coordinate
 // order (the |x|^2 + |y|^2 - 2xy expansion loses digits to cancellation), and equal distances are ranked by index,
 // so the result is unique.  Up to 128 coordinates the expansion is still used, on the matrix cores, but only to screen
-// the candidates (knn_mfma_kernel); beyond, a vector kernel computes every distance directly (knn_search_kernel: one
+// the candidates: in bf16 parts with a bound of the error (screen_kernel), in fp64 for what that cannot settle and for
+// small sets (knn_mfma_kernel); beyond, a vector kernel computes every distance directly (knn_search_kernel: one
 // thread per query, the query's coordinates in LDS, the candidates' read with wave-uniform addresses from a
 // zero-padded copy, four candidates in flight).  Either way a query keeps its k best so far in LDS together with the
 // worst of them; a candidate that beats the worst replaces it and the worst is found again by a scan of the k slots,
@@ -156,8 +157,8 @@ constexpr int kMt = 256;     // threads
 constexpr int kRound = 2;    // steps of 64 candidates between two walks of the masks
 template <int DP>
 __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 3 : 2))) void knn_mfma_kernel(
-    const double* __restrict__ xp, const double* __restrict__ xn, int64_t n, int k, int32_t* __restrict__ idx_out,
-    double* __restrict__ dist_out) {
+    const double* __restrict__ xp, const double* __restrict__ xn, int64_t n, int k, const int32_t* __restrict__ tiles,
+    const double* __restrict__ bound, int32_t* __restrict__ idx_out, double* __restrict__ dist_out) {
   constexpr int NS = DP / 4;            // MFMAs per 16 x 16 block
   // coordinates per piece of a step (the B operands of one piece are in flight).  Up to 32 coordinates the pieces are
   // 16 wide, which fits three waves per SIMD without spills (28 instead of 30 ms on 100,000 points of 32 coordinates:
@@ -174,7 +175,7 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 
   int32_t* bi = reinterpret_cast<int32_t*>(mask + kRound * kMq);                 // [k][kMq]
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
-  const int64_t q0 = (int64_t)blockIdx.x * kMq;
+  const int64_t q0 = (int64_t)(tiles ? tiles[blockIdx.x] : (int32_t)blockIdx.x) * kMq;
   const double2* __restrict__ xp2 = reinterpret_cast<const double2*>(xp);
 
   // setup: lists, thresholds, masks
@@ -183,7 +184,9 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 
     bi[e] = INT32_MAX;
   }
   for (int e = tid; e < kRound * kMq; e += kMt) mask[e] = 0ull;
-  if (tid < kMq) thrq[tid] = q0 + tid < n ? INFINITY : -INFINITY;  // a query past the end lets nothing through
+  // bound (may be null): per query a squared distance that at least k others do not exceed; a query past the end lets
+  // nothing through
+  if (tid < kMq) thrq[tid] = q0 + tid < n ? (bound ? bound[q0 + tid] : INFINITY) : -INFINITY;
   // this lane's part of the A operand: query 16 wave + i, coordinates 8m + 2g, 8m + 2g + 1
   double a[NS];
   {
@@ -205,11 +208,12 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 
   }
   // the walking lanes' state: lanes 0..15 of every wave, one of the wave's queries each.  A wave screens and walks
   // on its own: after the setup no barrier joins the four waves, so one wave's walk does not hold up the others.
-  double thr = INFINITY;
-  int32_t thr_idx = INT32_MAX;
-  int thr_slot = 0;
   const int myql = 16 * wave + lane;  // meaningful for lane < 16
   const int64_t myq = q0 + myql;
+  const double cut = bound && lane < 16 && myq < n ? bound[myq] : INFINITY;
+  double thr = cut;
+  int32_t thr_idx = INT32_MAX;
+  int thr_slot = 0;
   __syncthreads();
 
   const int64_t nstep = (n + 63) / 64;
@@ -314,8 +318,8 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 
                   ws = s;
                 }
               }
-              thr = w;
-              thr_idx = wid;
+              thr = w < cut ? w : cut;
+              thr_idx = w < cut ? wid : INT32_MAX;
               thr_slot = ws;
             }
           }
@@ -361,6 +365,444 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 
     bi[aidx * kMq + tidq] = bid;
     idx_out[myq * k + aidx] = bid == INT32_MAX ? -1 : bid;
     dist_out[myq * k + aidx] = sqrt(bv);
+  }
+}
+
+// ---- the bf16 screen ---------------------------------------------------------------------------------------------
+// Up to 128 coordinates and from kScreenMinN points on, the candidates are screened twice on the bf16 matrix cores,
+// which are 32 times as fast as the fp64 ones, and only what survives is looked at in fp64.  With
+//   v(q, y) = q.y - |y|^2 / 2      ( |q - y|^2 = |q|^2 - 2 v, so the nearest are the candidates of largest v )
+// the first pass (screen_kernel<., ., false>) leaves for every query the largest v of each of `groups` classes of
+// candidates (class = index mod 16 and number of the candidate's tile mod `slices`, so that neighbours that follow one
+// another in memory fall into different classes).  The (k+1)-th largest of these maxima, v*, is reached by at least k
+// candidates besides the query itself, so the k nearest all have v >= v* up to rounding.  The second pass forms the
+// same v again and lists the candidates with v >= v* - 2 e (screen_threshold_kernel), about 1.1 to 1.7 k of them, and
+// screen_rank_kernel ranks those by (distance, index) with the distances of the other kernels: the same sums in the
+// same order, so the result is the same to the last bit.  A query whose list overflows or comes out short (data with
+// many equal points, a spread so large that e exceeds the distances, non-finite coordinates) goes to knn_mfma_kernel
+// with the 64 queries around it.
+//
+// e bounds the error of v.  Points are centred and scaled by a power of two (M = the largest norm, in [1, 2)); a
+// coordinate is split into two bf16 parts, x = h + m + r with |m| <= 2^-9 |x| and |r| <= 1.02 * 2^-18 |x|, and
+// q.y ~ h.h + (h.m + m.h): what is left out is at most 3.1 * 2^-18 |q||y| (Cauchy-Schwarz).  The cross terms are summed
+// first, then the DP terms of h.h: taking every one of those additions to be off by 2^-23 of the sum of the moduli gives
+// DP 2^-23 (1 + 2^-6) |q||y|, the subtraction of |y|^2 / 2, rounded to float, 2^-23 M^2 more.  The rounding of the
+// centred coordinates (2^-52 of the largest original one, A) moves v by less than 3 M sqrt(DP) 2^-52 A, and 2^-40 M^2
+// covers the rounding of the fp64 distances that decide in the end.
+//
+// 100,000 points of 32 coordinates, k = 20: 28.2 ms for the fp64 screen alone (22.7 TFLOP/s), 3.75 ms with
+// this one (two passes of 1.5 and 2.1 ms; 64 coordinates, k = 32: 61 -> 7.2 ms).  Bound by the matrix cores and, up to 32 coordinates, the vector work on the 16 results that a lane gets from
+// each tile (subtract, running maximum).
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+
+constexpr int kScreenMinN = 512;
+constexpr int kMomentBlocks = 256;
+constexpr int kQueue = 256;        // survivors a wave gathers in LDS before it hands them on
+constexpr float kNoValue = -3.0e38f;
+
+struct ScreenScale {  // device: what the passes need to know of the whole point set
+  double max_abs;            // A, of the original coordinates
+  unsigned long long m2;     // bits of the largest centred squared norm
+};
+
+// part[b][c] = sum, part[b][DP + c] = largest modulus of coordinate c over the rows of block b
+__global__ __launch_bounds__(kT) void screen_moments_kernel(const double* __restrict__ xp, int64_t n, int dp,
+                                                            double* __restrict__ part) {
+  __shared__ double sums[kT], tops[kT];
+  const int c = threadIdx.x % dp, r = threadIdx.x / dp, nr = kT / dp;
+  double sum = 0.0, top = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * nr + r; i < n; i += (int64_t)gridDim.x * nr) {
+    const double v = xp[i * dp + c];
+    sum += v;
+    top = fmax(top, fabs(v));
+  }
+  sums[threadIdx.x] = sum;
+  tops[threadIdx.x] = top;
+  __syncthreads();
+  if (r) return;
+  for (int q = 1; q < nr; ++q) {
+    sum += sums[q * dp + c];
+    top = fmax(top, tops[q * dp + c]);
+  }
+  part[(int64_t)blockIdx.x * 2 * dp + c] = sum;
+  part[(int64_t)blockIdx.x * 2 * dp + dp + c] = top;
+}
+
+// 8 threads per coordinate take every 8th block's part; their sums are added in thread order
+__global__ __launch_bounds__(1024) void screen_mean_kernel(const double* __restrict__ part, int nparts, int64_t n, int dp,
+                                                           double* __restrict__ mean, ScreenScale* __restrict__ scale) {
+  __shared__ double sums[8][128], tops[8][128];
+  const int c = threadIdx.x & 127, r = threadIdx.x >> 7;
+  double sum = 0.0, top = 0.0;
+  if (c < dp) {
+#pragma unroll 4
+    for (int b = r; b < nparts; b += 8) {
+      sum += part[(int64_t)b * 2 * dp + c];
+      top = fmax(top, part[(int64_t)b * 2 * dp + dp + c]);
+    }
+  }
+  sums[r][c] = sum;
+  tops[r][c] = top;
+  __syncthreads();
+  if (r == 0) {
+    for (int q = 1; q < 8; ++q) {
+      sum += sums[q][c];
+      top = fmax(top, tops[q][c]);
+    }
+    if (c < dp) mean[c] = sum / (double)n;
+    tops[0][c] = top;
+  }
+  __syncthreads();
+  if (threadIdx.x) return;
+  for (int q = 1; q < 128; ++q) top = fmax(top, tops[0][q]);
+  scale->max_abs = top;
+  scale->m2 = 0ull;
+}
+
+// nrm2[i] = |x_i - mean|^2, scale->m2 = the largest (as bits: a NaN counts as larger than everything)
+__global__ __launch_bounds__(kT) void screen_norms_kernel(const double* __restrict__ xp, const double* __restrict__ mean,
+                                                          int64_t n, int dp, double* __restrict__ nrm2,
+                                                          ScreenScale* __restrict__ scale) {
+  const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
+  double acc = 0.0;
+  if (i < n) {
+    for (int t = 0; t < dp; ++t) {
+      const double v = xp[i * dp + t] - mean[t];
+      acc = fma(v, v, acc);
+    }
+    nrm2[i] = acc;
+  }
+  unsigned long long bits = (unsigned long long)__double_as_longlong(acc);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(bits, o, 64);
+    bits = other > bits ? other : bits;
+  }
+  if ((threadIdx.x & 63) == 0 && bits > scale->m2) atomicMax(&scale->m2, bits);
+}
+
+__device__ __forceinline__ bool screen_usable(const ScreenScale& s) {
+  const double m2 = __longlong_as_double((long long)s.m2);
+  return m2 > 1e-200 && m2 < 1e200 && s.max_abs < 1e100;
+}
+__device__ __forceinline__ double screen_factor(const ScreenScale& s) {  // power of two that takes M into [1, 2)
+  return screen_usable(s) ? ldexp(1.0, -ilogb(sqrt(__longlong_as_double((long long)s.m2)))) : 0.0;
+}
+
+// The operands in the order in which a wave reads them.  Tile t = points 32 t .. 32 t + 31; piece (t, s, part) = 64
+// lanes x 8 bf16, lane l = coordinates 16 s + 8 (l / 32) + 0..7 of point 32 t + l % 32, part 0 = h, part 1 = m.  Points
+// past the end are zeros with half[.] = +3e38, which no query ever prefers.  One thread per lane of a piece pair.
+__global__ __launch_bounds__(kT) void screen_split_kernel(const double* __restrict__ xp, const double* __restrict__ mean,
+                                                          const double* __restrict__ nrm2, int64_t n, int dp, int ks,
+                                                          const ScreenScale* __restrict__ scale, int64_t tiles,
+                                                          u4* __restrict__ xb, float* __restrict__ half,
+                                                          float* __restrict__ norm) {
+  const int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
+  if (e >= tiles * ks * 64) return;
+  const int l = (int)(e & 63);
+  const int64_t ts = e >> 6;
+  const int s = (int)(ts % ks);
+  const int64_t t = ts / ks, i = 32 * t + (l & 31);
+  const double f = screen_factor(*scale);
+  union { __bf16 b[8]; u4 v; } h, m;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int c = 16 * s + 8 * (l >> 5) + q;
+    const float x = i < n && c < dp ? (float)((xp[i * dp + c] - mean[c]) * f) : 0.0f;
+    h.b[q] = (__bf16)x;
+    m.b[q] = (__bf16)(x - (float)h.b[q]);
+  }
+  xb[(ts * 2) * 64 + l] = h.v;
+  xb[(ts * 2 + 1) * 64 + l] = m.v;
+  if (s == 0 && l < 32) {
+    const double q = i < n ? nrm2[i] * f * f : 0.0;
+    half[i] = i < n ? (float)(0.5 * q) : 3.0e38f;
+    norm[i] = (float)(sqrt(q) * 1.000001);  // rounded up
+  }
+}
+
+// One pass over all candidates for the queries of tiles qtile0 ...  A workgroup's four waves own NQ tiles of 32 queries
+// each (B operands, in registers) and go through the candidate tiles slice, slice + slices, ... (A operands), staged
+// through LDS in 16 KB chunks that all four read; the next chunk is in flight while this one is multiplied.  A lane
+// then holds 16 candidates of one query: register r = candidate 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile.
+//   COLLECT false: maxima[(query - first query) * groups + slice * 16 + 8 (lane / 32) + r % 8]
+//   COLLECT true:  candidates with v >= tau[query - first query] are appended to the query's list (count, list)
+template <int DP, int NQ, bool COLLECT>
+__global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(2))) void screen_kernel(
+    const u4* __restrict__ xb, const float* __restrict__ half, int64_t n, int64_t tiles, int64_t qtile0, int64_t qtiles,
+    int slices, float* __restrict__ maxima, const float* __restrict__ tau, int cap, int32_t* __restrict__ count,
+    int32_t* __restrict__ list) {
+  constexpr int KS = DP / 16;
+  constexpr int CT = 8 / KS;             // candidate tiles per chunk: 16 KB
+  constexpr int PT = KS * 2 * 64;        // 16-byte pieces per tile
+  constexpr int NL = CT * PT / kMt;      // pieces a thread stages: 4
+  __shared__ u4 stage[2][CT * PT];
+  __shared__ float hstage[2][CT * 32];
+  __shared__ int2 queue[COLLECT ? 4 : 1][COLLECT ? kQueue : 1];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int slice = (int)blockIdx.y;
+  const int64_t qt0 = ((int64_t)blockIdx.x * 4 + wave) * NQ;  // relative to qtile0
+  const int64_t nj = (tiles - slice + slices - 1) / slices;  // at least one: slices <= tiles
+  const int64_t nchunk = (nj + CT - 1) / CT;
+
+  bf16x8 bh[NQ][KS], bm[NQ][KS];
+  float thr[NQ];
+  float best[COLLECT ? 1 : NQ][8];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    int64_t t = qtile0 + qt0 + q;
+    t = t < tiles ? t : tiles - 1;  // past the end: computed, never stored
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      bh[q][s] = __builtin_bit_cast(bf16x8, xb[((t * KS + s) * 2) * 64 + lane]);
+      bm[q][s] = __builtin_bit_cast(bf16x8, xb[((t * KS + s) * 2 + 1) * 64 + lane]);
+    }
+    if constexpr (COLLECT)
+      thr[q] = qt0 + q < qtiles && t * 32 + (lane & 31) < n ? tau[(qt0 + q) * 32 + (lane & 31)] : INFINITY;
+    else
+#pragma unroll
+      for (int r = 0; r < 8; ++r) best[q][r] = kNoValue;
+  }
+
+  u4 next[NL];
+  float hnext = 0.0f;
+  auto request = [&](int64_t chunk) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) {
+      const int p = tid + u * kMt;
+      int64_t j = chunk * CT + p / PT;
+      j = j < nj ? j : nj - 1;  // the last tile again: skipped below
+      next[u] = xb[(slice + j * slices) * PT + p % PT];
+    }
+    if (tid < CT * 32) {
+      int64_t j = chunk * CT + tid / 32;
+      j = j < nj ? j : nj - 1;
+      hnext = half[(slice + j * slices) * 32 + tid % 32];
+    }
+  };
+  auto park = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NL; ++u) stage[buf][tid + u * kMt] = next[u];
+    if (tid < CT * 32) hstage[buf][tid] = hnext;
+  };
+
+  int queued = 0;  // wave-uniform
+  auto hand_on = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the wave's own LDS operations complete in order
+    __builtin_amdgcn_wave_barrier();
+    for (int e = lane; e < queued; e += 64) {
+      const int2 entry = queue[wave][e];
+      const int slot = atomicAdd(&count[entry.x], 1);
+      if (slot < cap) list[(int64_t)entry.x * cap + slot] = entry.y;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    queued = 0;
+  };
+
+  request(0);
+  park(0);
+  __syncthreads();
+  for (int64_t chunk = 0; chunk < nchunk; ++chunk) {
+    const int buf = (int)(chunk & 1);
+    if (chunk + 1 < nchunk) request(chunk + 1);
+#pragma unroll 1
+    for (int ct = 0; ct < CT; ++ct) {
+      const int64_t j = chunk * CT + ct;
+      if (j >= nj) break;  // uniform
+      const u4* __restrict__ a = &stage[buf][ct * PT];
+      f16v acc[NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[q][r] = 0.0f;
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {  // the small cross terms first
+        const bf16x8 ah = __builtin_bit_cast(bf16x8, a[(s * 2) * 64 + lane]);
+        const bf16x8 am = __builtin_bit_cast(bf16x8, a[(s * 2 + 1) * 64 + lane]);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bh[q][s], acc[q], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bm[q][s], acc[q], 0, 0, 0);
+      }
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const bf16x8 ah = __builtin_bit_cast(bf16x8, a[(s * 2) * 64 + lane]);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[q][s], acc[q], 0, 0, 0);
+      }
+      float y[16];
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f4 v = *reinterpret_cast<const f4*>(&hstage[buf][ct * 32 + 8 * r4 + 4 * (lane >> 5)]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[4 * r4 + r] = v[r];
+      }
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        float v[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r] = acc[q][r] - y[r];
+        if constexpr (!COLLECT) {
+#pragma unroll
+          for (int r = 0; r < 8; ++r) best[q][r] = fmaxf(fmaxf(best[q][r], v[r]), v[r + 8]);
+        } else {
+          float top[4];
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) top[r4] = fmaxf(fmaxf(fmaxf(v[4 * r4], v[4 * r4 + 1]), v[4 * r4 + 2]), v[4 * r4 + 3]);
+          if (__any(fmaxf(fmaxf(fmaxf(top[0], top[1]), top[2]), top[3]) >= thr[q])) {  // uniform
+            const int64_t c0 = (slice + j * slices) * 32 + 4 * (lane >> 5);
+            const int64_t ql = (qt0 + q) * 32 + (lane & 31);  // relative to the first query
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+              if (!__any(top[r4] >= thr[q])) continue;  // uniform
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const int64_t c = c0 + 8 * r4 + r;
+                const bool hit = v[4 * r4 + r] >= thr[q] && c < n && c != qtile0 * 32 + ql;
+                const unsigned long long mask = __ballot(hit);
+                if (mask) {  // uniform
+                  if (hit) queue[wave][queued + __popcll(mask & ((1ull << lane) - 1ull))] = make_int2((int)ql, (int)c);
+                  queued += __popcll(mask);
+                  if (queued > kQueue - 64) hand_on();
+                }
+              }
+            }
+          }
+        }
+      }
+    }
+    if (chunk + 1 < nchunk) park(buf ^ 1);  // nobody reads that buffer before the barrier
+    __syncthreads();
+  }
+  if constexpr (COLLECT) {
+    hand_on();
+  } else {
+    const int groups = slices * 16;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      if (qt0 + q >= qtiles) continue;
+      float* __restrict__ out = maxima + ((qt0 + q) * 32 + (lane & 31)) * groups + slice * 16 + 8 * (lane >> 5);
+#pragma unroll
+      for (int r = 0; r < 8; r += 4) *reinterpret_cast<f4*>(out + r) = (f4){best[q][r], best[q][r + 1], best[q][r + 2], best[q][r + 3]};
+    }
+  }
+}
+
+// tau[q] = v* - 2 e, v* = the (k+1)-th largest of the query's maxima, found bit by bit; clears the query's list.  A wave
+// per query.  bound[first query + q] = a squared distance that at least k others do not exceed: what the fp64 kernel
+// starts from if it comes to that.  tau = +inf (nothing is listed, the query falls back) where the point set has no
+// usable scale or far too many would be listed; *hopeless counts those.
+template <int NP>  // keys per lane: groups <= 64 NP
+__global__ __launch_bounds__(kT) void screen_threshold_kernel(const float* __restrict__ maxima, int groups, int k, int dp,
+                                                              const float* __restrict__ norm, int64_t q0, int64_t nq,
+                                                              const double* __restrict__ nrm2, int cap,
+                                                              const ScreenScale* __restrict__ scale,
+                                                              float* __restrict__ tau, int32_t* __restrict__ count,
+                                                              double* __restrict__ bound,
+                                                              int32_t* __restrict__ hopeless) {
+  const int lane = threadIdx.x & 63;
+  const int64_t q = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
+  if (q >= nq) return;
+  uint32_t key[NP];  // order-preserving image of the floats
+#pragma unroll
+  for (int u = 0; u < NP; ++u) {
+    key[u] = 0u;
+    if (64 * u + lane < groups) {
+      const uint32_t b = __float_as_uint(maxima[q * groups + 64 * u + lane]);
+      key[u] = b & 0x80000000u ? ~b : b | 0x80000000u;
+    }
+  }
+  uint32_t low = 0u;  // the largest value that at least k + 1 keys reach
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t probe = low | (1u << bit);
+    int reach = 0;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) reach += __popcll(__ballot(key[u] >= probe));
+    if (reach > k) low = probe;
+  }
+  const float vstar = __uint_as_float(low & 0x80000000u ? low & 0x7fffffffu : ~low);
+  const ScreenScale s = *scale;
+  if (!screen_usable(s) || !(vstar > -1.0e38f)) {  // uniform
+    if (lane == 0) {
+      count[q] = 0;
+      tau[q] = INFINITY;
+      bound[q0 + q] = INFINITY;
+      atomicAdd(hopeless, 1);
+    }
+    return;
+  }
+  const double f = screen_factor(s), m = sqrt(__longlong_as_double((long long)s.m2)) * f * 1.000001;
+  const double u23 = 1.1920928955078125e-07;  // 2^-23
+  const double e = (double)norm[q0 + q] * m * (3.1 / 262144.0 + 1.02 * dp * u23) + u23 * m * m +
+                   3.0 * m * sqrt((double)dp) * 2.220446049250313e-16 * s.max_abs * f + 9.1e-13 * m * m;
+  const double t = (double)vstar - 2.0 * e;
+  const float cut = (float)(t - 1.2e-7 * fabs(t));  // rounded down
+  // how many will be listed: the classes that reach the cut say so, were they filled at random
+  const uint32_t cb = __float_as_uint(cut), ck = cb & 0x80000000u ? ~cb : cb | 0x80000000u;
+  int reach = 0;
+#pragma unroll
+  for (int u = 0; u < NP; ++u) reach += __popcll(__ballot(key[u] >= ck));
+  if (lane) return;
+  const bool lost = reach >= groups || -log1p(-(double)reach / groups) * groups > 1.5 * cap;
+  count[q] = 0;
+  tau[q] = lost ? INFINITY : cut;
+  if (lost) atomicAdd(hopeless, 1);
+  const double d2 = nrm2[q0 + q] * f * f - 2.0 * ((double)vstar - e);
+  bound[q0 + q] = (d2 + 1e-6 * fabs(d2)) / (f * f);
+}
+
+// The k nearest of the listed candidates, by (exact squared distance, index).  A wave per query: a lane computes a
+// candidate's distance as the other kernels do, its rank is the number of listed candidates before it.
+__global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restrict__ xp, int dp, int64_t q0, int64_t nq,
+                                                         int k, int cap, const int32_t* __restrict__ count,
+                                                         const int32_t* __restrict__ list,
+                                                         int32_t* __restrict__ tile_flag, int32_t* __restrict__ tiles,
+                                                         int32_t* __restrict__ ntiles, int32_t* __restrict__ idx_out,
+                                                         double* __restrict__ dist_out) {
+  extern __shared__ double lds[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double* dist = lds + (size_t)wave * cap;
+  int32_t* idx = reinterpret_cast<int32_t*>(lds + (size_t)(kT / 64) * cap) + (size_t)wave * cap;
+  const int64_t q = (int64_t)blockIdx.x * (kT / 64) + wave;
+  if (q >= nq) return;
+  const int64_t i = q0 + q;
+  const int found = count[q];
+  if (found > cap || found < k) {
+    if (lane == 0 && atomicExch(&tile_flag[i / kMq], 1) == 0) tiles[atomicAdd(ntiles, 1)] = (int32_t)(i / kMq);
+    return;
+  }
+  const double2* __restrict__ xp2 = reinterpret_cast<const double2*>(xp);
+  const double2* __restrict__ qr = xp2 + i * (dp / 2);
+  for (int c = lane; c < found; c += 64) {
+    const int32_t j = list[q * cap + c];
+    const double2* __restrict__ yr = xp2 + (int64_t)j * (dp / 2);
+    double ex = 0.0;
+#pragma unroll 8
+    for (int t = 0; t < dp / 2; ++t) {
+      const double2 qv = qr[t], yv = yr[t];
+      const double d0 = qv.x - yv.x;
+      ex = fma(d0, d0, ex);
+      const double d1 = qv.y - yv.y;
+      ex = fma(d1, d1, ex);
+    }
+    dist[c] = ex;
+    idx[c] = j;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the wave's own LDS operations complete in order
+  __builtin_amdgcn_wave_barrier();
+  for (int c = lane; c < found; c += 64) {
+    const double v = dist[c];
+    const int32_t id = idx[c];
+    int rank = 0;
+    for (int o = 0; o < found; ++o) rank += (dist[o] < v || (dist[o] == v && idx[o] < id)) ? 1 : 0;
+    if (rank < k) {
+      idx_out[i * k + rank] = id;
+      dist_out[i * k + rank] = sqrt(v);
+    }
   }
 }
 
@@ -417,8 +859,181 @@ size_t knn_search_lds_bytes(int d, int k) {
   return (size_t)kQ * ((size_t)dp * sizeof(double) + (size_t)k * (sizeof(double) + sizeof(int32_t)));
 }
 
-hipError_t launch_knn_search(const double* x, int64_t ldx, int64_t n, int d, int k, double* xp, int32_t* idx_out,
-                             double* dist_out, hipStream_t st) {
+namespace {
+
+hipError_t launch_knn_mfma(const double* xp, const double* xn, int64_t n, int k, int dp, const int32_t* tiles,
+                           const double* bound, unsigned grid, size_t lds, int32_t* idx_out, double* dist_out, hipStream_t st) {
+#define SC_KNN_MFMA(DPV)                                                                                       \
+  do {                                                                                                         \
+    if (lds > 64 * 1024) {                                                                                     \
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&knn_mfma_kernel<DPV>),           \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);          \
+      if (e != hipSuccess) return e;                                                                           \
+    }                                                                                                          \
+    hipLaunchKernelGGL(knn_mfma_kernel<DPV>, dim3(grid), dim3(kMt), lds, st, xp, xn, n, k, tiles, bound,       \
+                       idx_out, dist_out);                                                                     \
+  } while (0)
+  if (dp == 8) SC_KNN_MFMA(8);
+  else if (dp == 16) SC_KNN_MFMA(16);
+  else if (dp == 32) SC_KNN_MFMA(32);
+  else if (dp == 64) SC_KNN_MFMA(64);
+  else SC_KNN_MFMA(128);
+#undef SC_KNN_MFMA
+  return hipGetLastError();
+}
+
+// How the bf16 screen goes about n points of d coordinates and k neighbours.
+struct ScreenPlan {
+  bool use = false;
+  int dpb = 0, nq = 0;          // padded coordinates (a multiple of 16) and query tiles per wave
+  int slices = 0, cap = 0;
+  int64_t tiles = 0, chunk = 0; // tiles of 32 points; query tiles per round of launches
+  size_t off_bound = 0, off_half = 0, off_norm = 0, off_nrm2 = 0, off_mean = 0, off_part = 0, off_scale = 0, off_maxima = 0, off_tau = 0,
+         off_count = 0, off_list = 0, off_flag = 0, off_tiles = 0, off_ntiles = 0, bytes = 0;
+};
+
+ScreenPlan plan_screen(int64_t n, int d, int k) {
+  ScreenPlan p;
+  const int dp = knn_padded_dim(d);
+  // more than 128 coordinates: the operands of a query tile do not fit the registers; fewer points than 512 or than 16
+  // per neighbour: too few classes for a threshold (512 points of 3 coordinates, k = 5: 140 us with the fp64 kernel
+  // alone, 80 us with the screen's eight launches; 700 points of 128: 1,043 and 109 us)
+  if (dp > 128 || n < kScreenMinN || (int64_t)16 * (k + 1) > n) return p;
+  p.use = true;
+  p.dpb = dp < 16 ? 16 : dp;
+  p.nq = p.dpb <= 32 ? 4 : 2;
+  p.tiles = (n + 31) / 32;
+  p.cap = 3 * k + 64;
+  // classes: 16 per slice, 2.5 (k + 1) of them make the threshold almost that of the k-th neighbour itself; more slices
+  // where the queries alone do not fill the 512 workgroups that are resident at a time
+  int need = (5 * (k + 1) + 31) / 32;
+  need = need > 64 ? 64 : need;
+  const int64_t qblocks = (p.tiles + 4 * p.nq - 1) / (4 * p.nq);
+  int best = need;
+  double best_eff = 0.0;
+  const int64_t most = p.tiles < 64 ? p.tiles : 64;
+  for (int s = need; s <= most; ++s) {
+    const double rounds = (double)(qblocks * s) / 512.0;
+    const double eff = rounds / (double)((qblocks * s + 511) / 512);
+    if (eff > best_eff + 0.03) {
+      best = s;
+      best_eff = eff;
+    }
+    if (rounds > 8.0) break;
+  }
+  p.slices = best;
+  // scratch per query: maxima and list; rounds of at most 256 MB
+  const size_t per_tile = 32 * ((size_t)p.slices * 16 + p.cap) * 4;
+  int64_t chunk = (int64_t)(((size_t)256 << 20) / per_tile);
+  chunk = chunk / (4 * p.nq) * (4 * p.nq);
+  p.chunk = chunk < 4 * p.nq ? 4 * p.nq : (chunk > p.tiles ? p.tiles : chunk);
+  size_t off = (size_t)p.tiles * (p.dpb / 16) * 2 * 1024;
+  auto place = [&](size_t bytes) {
+    const size_t at = off;
+    off += (bytes + 255) / 256 * 256;
+    return at;
+  };
+  p.off_half = place((size_t)p.tiles * 32 * 4);
+  p.off_norm = place((size_t)p.tiles * 32 * 4);
+  p.off_nrm2 = place((size_t)n * 8);
+  p.off_bound = place((size_t)n * 8);
+  p.off_mean = place(128 * 8);
+  p.off_part = place((size_t)kMomentBlocks * 2 * 128 * 8);
+  p.off_scale = place(sizeof(ScreenScale));
+  p.off_maxima = place((size_t)p.chunk * 32 * p.slices * 16 * 4);
+  p.off_tau = place((size_t)p.chunk * 32 * 4);
+  p.off_count = place((size_t)p.chunk * 32 * 4);
+  p.off_list = place((size_t)p.chunk * 32 * p.cap * 4);
+  p.off_flag = place((size_t)((n + kMq - 1) / kMq) * 4 + 8);
+  p.off_tiles = place((size_t)((n + kMq - 1) / kMq) * 4);
+  p.off_ntiles = p.off_flag + (size_t)((n + kMq - 1) / kMq) * 4;
+  p.bytes = off;
+  return p;
+}
+
+}  // namespace
+
+size_t knn_screen_workspace(int64_t n, int d, int k) { return plan_screen(n, d, k).bytes; }
+
+hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* work, int32_t* host, int32_t** tiles,
+                             int32_t** ntiles, double** bound, int32_t* idx_out, double* dist_out, hipStream_t st) {
+  const ScreenPlan p = plan_screen(n, d, k);
+  if (!p.use) return hipErrorInvalidValue;
+  const int dp = knn_padded_dim(d), ks = p.dpb / 16;
+  char* w = static_cast<char*>(work);
+  u4* xb = reinterpret_cast<u4*>(w);
+  float* half = reinterpret_cast<float*>(w + p.off_half);
+  float* norm = reinterpret_cast<float*>(w + p.off_norm);
+  double* nrm2 = reinterpret_cast<double*>(w + p.off_nrm2);
+  double* mean = reinterpret_cast<double*>(w + p.off_mean);
+  double* part = reinterpret_cast<double*>(w + p.off_part);
+  ScreenScale* scale = reinterpret_cast<ScreenScale*>(w + p.off_scale);
+  float* maxima = reinterpret_cast<float*>(w + p.off_maxima);
+  float* tau = reinterpret_cast<float*>(w + p.off_tau);
+  int32_t* count = reinterpret_cast<int32_t*>(w + p.off_count);
+  int32_t* list = reinterpret_cast<int32_t*>(w + p.off_list);
+  int32_t* flag = reinterpret_cast<int32_t*>(w + p.off_flag);
+  *tiles = reinterpret_cast<int32_t*>(w + p.off_tiles);
+  *ntiles = reinterpret_cast<int32_t*>(w + p.off_ntiles);
+  int32_t* hopeless = *ntiles + 1;
+  *bound = reinterpret_cast<double*>(w + p.off_bound);
+  int32_t lost_before = 0;
+  const size_t rank_lds = (size_t)(kT / 64) * p.cap * 12;
+  hipError_t e = launch_fill_int32(flag, (n + kMq - 1) / kMq + 2, 0, 0, st);  // the flags and, behind them, the two counts
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(screen_moments_kernel, dim3(kMomentBlocks), dim3(kT), 0, st, xp, n, dp, part);
+  hipLaunchKernelGGL(screen_mean_kernel, dim3(1), dim3(1024), 0, st, part, kMomentBlocks, n, dp, mean, scale);
+  hipLaunchKernelGGL(screen_norms_kernel, dim3(blocks(n)), dim3(kT), 0, st, xp, mean, n, dp, nrm2, scale);
+  hipLaunchKernelGGL(screen_split_kernel, dim3(blocks(p.tiles * ks * 64)), dim3(kT), 0, st, xp, mean, nrm2, n, dp, ks, scale,
+                     p.tiles, xb, half, norm);
+  for (int64_t t0 = 0; t0 < p.tiles; t0 += p.chunk) {
+    const int64_t nt = p.tiles - t0 < p.chunk ? p.tiles - t0 : p.chunk;
+    const int64_t q0 = 32 * t0, nq = n - q0 < 32 * nt ? n - q0 : 32 * nt;
+    const dim3 grid((unsigned)((nt + 4 * p.nq - 1) / (4 * p.nq)), (unsigned)p.slices);
+#define SC_SCREEN(DPV, NQV, COL)                                                                                      \
+  hipLaunchKernelGGL((screen_kernel<DPV, NQV, COL>), grid, dim3(kMt), 0, st, xb, half, n, p.tiles, t0, nt, p.slices, \
+                     maxima, tau, p.cap, count, list)
+#define SC_SCREEN_DIM(COL)                                       \
+  do {                                                           \
+    if (p.dpb == 16) SC_SCREEN(16, 4, COL);                      \
+    else if (p.dpb == 32) SC_SCREEN(32, 4, COL);                 \
+    else if (p.dpb == 64) SC_SCREEN(64, 2, COL);                 \
+    else SC_SCREEN(128, 2, COL);                                 \
+  } while (0)
+    SC_SCREEN_DIM(false);
+#define SC_THRESHOLD(NPV)                                                                                              \
+  hipLaunchKernelGGL((screen_threshold_kernel<NPV>), dim3(blocks(nq * 64)), dim3(kT), 0, st, maxima, p.slices * 16, k, \
+                     p.dpb, norm, q0, nq, nrm2, p.cap, scale, tau, count, *bound, hopeless)
+    if (p.slices <= 4) SC_THRESHOLD(1);
+    else if (p.slices <= 8) SC_THRESHOLD(2);
+    else if (p.slices <= 16) SC_THRESHOLD(4);
+    else if (p.slices <= 32) SC_THRESHOLD(8);
+    else SC_THRESHOLD(16);
+#undef SC_THRESHOLD
+    // most queries lost: the second pass would be for nothing, an empty list sends them all to the fp64 kernel
+    e = hipMemcpyAsync(host, hopeless, sizeof(int32_t), hipMemcpyDeviceToHost, st);
+    if (e != hipSuccess) return e;
+    e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+    const int32_t lost = *host - lost_before;
+    lost_before = *host;
+    if (lost <= nq / 2) SC_SCREEN_DIM(true);
+#undef SC_SCREEN_DIM
+#undef SC_SCREEN
+    hipLaunchKernelGGL(screen_rank_kernel, dim3(blocks(nq * 64)), dim3(kT), rank_lds, st, xp, dp, q0, nq, k, p.cap, count,
+                       list, flag, *tiles, *ntiles, idx_out, dist_out);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_knn_pad(const double* x, int64_t ldx, int64_t n, int d, double* xp, hipStream_t st) {
+  const int dp = knn_padded_dim(d);
+  hipLaunchKernelGGL(pad_rows_kernel, dim3(blocks(n * dp)), dim3(kT), 0, st, x, ldx, n, d, dp, xp);
+  return hipGetLastError();
+}
+
+hipError_t launch_knn_search(int64_t n, int d, int k, double* xp, const int32_t* tiles, int64_t ntiles,
+                             const double* bound, int32_t* idx_out, double* dist_out, hipStream_t st) {
   if (n < 2 || d < 1 || k < 1 || k > n - 1 || n > INT32_MAX) return hipErrorInvalidValue;
   const int dp = knn_padded_dim(d);
   const size_t lds = knn_search_lds_bytes(d, k);
@@ -428,29 +1043,13 @@ hipError_t launch_knn_search(const double* x, int64_t ldx, int64_t n, int d, int
   e = hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev);
   if (e != hipSuccess) return e;
   if (lds > (size_t)lds_max) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(pad_rows_kernel, dim3(blocks(n * dp)), dim3(kT), 0, st, x, ldx, n, d, dp, xp);
   if (dp <= 128) {
     double* xn = xp + (size_t)n * dp;
     hipLaunchKernelGGL(row_norms_kernel, dim3(blocks(n)), dim3(kT), 0, st, xp, n, dp, xn);
-    const size_t l = lds;
-    const dim3 grid((unsigned)((n + kMq - 1) / kMq));
-#define SC_KNN_MFMA(DPV)                                                                                       \
-  do {                                                                                                         \
-    if (l > 64 * 1024) {                                                                                       \
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&knn_mfma_kernel<DPV>),                            \
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)l);                             \
-      if (e != hipSuccess) return e;                                                                           \
-    }                                                                                                          \
-    hipLaunchKernelGGL(knn_mfma_kernel<DPV>, grid, dim3(kMt), l, st, xp, xn, n, k, idx_out, dist_out);         \
-  } while (0)
-    if (dp == 8) SC_KNN_MFMA(8);
-    else if (dp == 16) SC_KNN_MFMA(16);
-    else if (dp == 32) SC_KNN_MFMA(32);
-    else if (dp == 64) SC_KNN_MFMA(64);
-    else SC_KNN_MFMA(128);
-#undef SC_KNN_MFMA
-    return hipGetLastError();
+    const int64_t grid = tiles ? ntiles : (n + kMq - 1) / kMq;
+    return launch_knn_mfma(xp, xn, n, k, dp, tiles, bound, (unsigned)grid, lds, idx_out, dist_out, st);
   }
+  if (tiles) return hipErrorInvalidValue;
   if (lds > 64 * 1024) {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&knn_search_kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

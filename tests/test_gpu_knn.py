@@ -53,6 +53,38 @@ def test_search_matches_oracle(B, n, d, k):
     assert np.all(idx != np.arange(n)[:, None]) and np.all(np.diff(dist, axis=1) >= 0)
 
 
+# the bf16 screen: its smallest sizes, ragged tiles of 32 points and of 512 queries, every padded dimension, k up to the
+# most that fits; neighbours that follow one another in memory; a common offset; points that the screen cannot tell apart
+@pytest.mark.parametrize("n,d,k,kind", [(512, 3, 31, "random"), (513, 70, 7, "random"), (2048, 16, 10, "random"), (2049, 1, 1, "random"), (2111, 128, 20, "random"),
+                                        (4097, 17, 32, "random"), (3600, 64, 200, "random"), (6000, 33, 20, "sorted"),
+                                        (5003, 32, 15, "offset"), (2500, 12, 8, "copies"), (4000, 3, 10, "far"),
+                                        (2600, 8, 5, "equal"), (2300, 10, 6, "tiny")])
+def test_screened_search_matches_oracle(B, n, d, k, kind):
+    rng = np.random.default_rng(7 * n + d)
+    x = rng.standard_normal((n, d))
+    if kind == "sorted":          # clusters, each contiguous
+        x += 30.0 * rng.standard_normal((12, d))[np.arange(n) * 12 // n]
+    elif kind == "offset":
+        x += 1e6
+    elif kind == "copies":        # more equal points than a list holds, beside ordinary ones
+        x[::3] = x[0]
+    elif kind == "far":           # spread 1e6, distances 1e-3: below the resolution of the screen
+        x = 1e6 * rng.standard_normal((40, d))[rng.integers(0, 40, n)] + 1e-3 * x
+    elif kind == "equal":
+        x[:] = x[0]
+    elif kind == "tiny":
+        x *= 1e-150
+    ref_i, ref_d = oknn.knn_bruteforce(x, k)
+    idx, dist = B.sc_knn_search(_dev(x, torch.float64), k)
+    idx, dist = idx.cpu().numpy(), dist.cpu().numpy()
+    # candidates are ranked by the fp64 sum of squared differences on both sides, in coordinate order here and in the
+    # oracle's own order there: two whose sums agree to the rounding of d + 2 additions may change places
+    bad = idx != ref_i
+    assert np.all(np.abs(dist - ref_d)[bad] <= (d + 2) * 2.3e-16 * ref_d[bad])
+    np.testing.assert_allclose(dist, ref_d, rtol=1e-13, atol=0)
+    assert np.all(idx != np.arange(n)[:, None])
+
+
 def test_search_orders_equal_distances_by_index(B):
     # integer points on a line and on a small grid: many exactly equal distances, all sums exact in fp64
     x = np.arange(37, dtype=np.float64)[:, None]
