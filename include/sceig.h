@@ -360,9 +360,9 @@ typedef struct sc_kmeans_stats {
                            at max_iter (the centres moved after the last labelling) */
   double t_total;       /* seconds, host clock, whole call */
   double t_seed;        /* seconds spent in the seeding */
-  double t_distance;    /* seconds, device clock, all distance-product launches (V C^T); 0 unless timing was set */
+  double t_distance;    /* seconds, device clock, all labelling launches (V C^T and its arg-min); 0 unless timing was set */
   int64_t distance_launches;
-  double distance_bytes; /* algorithmic bytes of those launches: points read + product block written + centres */
+  double distance_bytes; /* algorithmic bytes of those launches: points and centres read, labels read and written */
   double distance_flops; /* 2 n k d per labelling step */
 } sc_kmeans_stats;
 

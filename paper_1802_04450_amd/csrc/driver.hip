@@ -1850,7 +1850,7 @@ struct KMeans {
   void seed(uint64_t seed_value, int32_t* chosen, double* c) {
     std::vector<double> u((size_t)k);
     for (int i = 0; i < k; ++i) u[i] = km_uniform01(seed_value, (uint64_t)i);
-    const size_t wb = kmeans_seed_workspace(n);
+    const size_t wb = kmeans_seed_workspace(n, ldx, d, k);
     DevBuf<char> work;
     work.alloc(wb);
     HIP_TRY(launch_kmeanspp(x.p, ldx, d, n, k, u.data(), work.p, wb, chosen, st));
@@ -1861,21 +1861,17 @@ struct KMeans {
   // Algorithm 4 step 3 from the centres in c (device k x ldx, updated in place)
   int lloyd(double* c, int max_iter, int32_t* labels, sc_kmeans_stats* stats) {
     const int64_t ldc = ((int64_t)k + 15) / 16 * 16;
-    int64_t chunk = ((int64_t)1 << 27) / ldc / 128 * 128;  // distance block of at most 1 GiB
-    if (chunk < 128) chunk = 128;
-    if (chunk > n) chunk = n;
-    DevBuf<double> ct, cnorm, sblock, part;
+    DevBuf<double> ct, cnorm, part;
     DevBuf<int32_t> start;
     DevBuf<int> changes;
     DevBuf<char> work;
     PinnedBuf<int> hchanges;
     ct.alloc((size_t)ldx * ldc);
     cnorm.alloc((size_t)k);
-    sblock.alloc((size_t)chunk * ldc);
     start.alloc((size_t)k + 1);
-    changes.alloc(1);
-    hchanges.alloc(1);
-    const size_t wb = kmeans_update_workspace(n);
+    changes.alloc(kChangeInts);
+    hchanges.alloc(kChangeInts);
+    const size_t wb = kmeans_update_workspace(n, ldx, k);
     work.alloc(wb);
     HIP_TRY(launch_fill_int32(labels, n, -1, 0, st));
     int iters = 0, converged = 0, last_changes = 0;
@@ -1893,32 +1889,28 @@ struct KMeans {
       }
     } events;
     double dist_bytes = 0.0, dist_flops = 0.0;
+    HIP_TRY(launch_centroid_operand(c, ldx, k, d, (int)ldx, ct.p, ldc, cnorm.p, changes.p, st));
     for (int it = 0; it < max_iter; ++it) {
-      HIP_TRY(launch_fill_int32(changes.p, 1, 0, 0, st));
-      HIP_TRY(launch_centroid_operand(c, ldx, k, d, (int)ldx, ct.p, ldc, cnorm.p, st));
-      for (int64_t r0 = 0; r0 < n; r0 += chunk) {
-        const int64_t rows = std::min<int64_t>(chunk, n - r0);
-        if (timing) {
-          events.v.push_back(EventPair{nullptr, nullptr});
-          HIP_TRY(hipEventCreate(&events.v.back().a));
-          HIP_TRY(hipEventCreate(&events.v.back().b));
-          HIP_TRY(hipEventRecord(events.v.back().a, st));
-        }
-        HIP_TRY(launch_row_gemm(x.p + r0 * ldx, rows, ldx, 0, d, ct.p, (int)ldc, k, 1, 0, sblock.p, ldc, nullptr, st));
-        if (timing) HIP_TRY(hipEventRecord(events.v.back().b, st));
-        dist_bytes += 8.0 * ((double)rows * d + (double)rows * k + (double)k * d);
-        dist_flops += 2.0 * (double)rows * k * d;
-        HIP_TRY(launch_argmin(sblock.p, ldc, rows, k, cnorm.p, labels + r0, changes.p, st));
+      if (timing) {
+        events.v.push_back(EventPair{nullptr, nullptr});
+        HIP_TRY(hipEventCreate(&events.v.back().a));
+        HIP_TRY(hipEventCreate(&events.v.back().b));
+        HIP_TRY(hipEventRecord(events.v.back().a, st));
       }
-      HIP_TRY(hipMemcpyAsync(hchanges.p, changes.p, sizeof(int), hipMemcpyDeviceToHost, st));
+      HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, labels, changes.p, st));
+      if (timing) HIP_TRY(hipEventRecord(events.v.back().b, st));
+      dist_bytes += 8.0 * ((double)n * d + (double)k * d) + 8.0 * (double)n;
+      dist_flops += 2.0 * (double)n * k * d;
+      HIP_TRY(hipMemcpyAsync(hchanges.p, changes.p, sizeof(int) * kChangeInts, hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
       ++iters;
-      last_changes = *hchanges.p;
+      last_changes = 0;
+      for (int s = 0; s < kChangeSlots; ++s) last_changes += hchanges.p[s * kChangeStride];
       if (last_changes == 0) {
         converged = 1;
         break;
       }
-      HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, work.p, wb, start.p, c, st));
+      HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, work.p, wb, start.p, c, ct.p, ldc, cnorm.p, changes.p, st));
     }
     if (stats) {
       // objective of the final labelling against the centres it was computed from (after a converged run these are

@@ -1,6 +1,6 @@
 // k-means on the rows of the eigenvector matrix (paper Section II Step 4, Section IV-C, Algorithms 4 and 5): device
 // kernels.  The distance step is the paper's expanded form S = |v|^2 + |c|^2 - 2 V C^T with the product on the fp64
-// matrix cores (row_gemm_kernel, kernels.hip); |v|^2 does not change the arg-min and is left out.  The centre update
+// matrix cores and the arg-min in the same launch (label_kernel, kernels.hip); |v|^2 does not change the arg-min and is left out.  The centre update
 // is sort based as in the paper (points ordered by label, every cluster a contiguous run), with a fixed summation
 // order so that results are reproducible.  The seeding follows Algorithm 5 with the uniform numbers supplied by the
 // host (a counter-based generator); a draw is one distance pass that also leaves block sums and one single-workgroup
@@ -49,73 +49,162 @@ __global__ __launch_bounds__(kT) void points_to_rowmajor_kernel(const double* __
   }
 }
 
-// ct[t * ldc + j] = c[j * ldx + t] (the right-hand operand of V C^T, zero padded to ldc columns and dpad rows) and
-// cnorm[j] = |c_j|^2.  One workgroup per centre.
-__global__ __launch_bounds__(kT) void centroid_operand_kernel(const double* __restrict__ c, int64_t ldx, int k, int d,
-                                                              int dpad, double* __restrict__ ct, int64_t ldc,
-                                                              double* __restrict__ cnorm) {
-  __shared__ double part[kT / 64];
+// *out = the sum of one value per thread of the workgroup, in a fixed order
+__device__ __forceinline__ void block_norm(double ss, double* __restrict__ out) {
+  __shared__ double wsum[kT / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if (threadIdx.x % 64 == 0) wsum[threadIdx.x / 64] = ss;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double tot = 0.0;
+    for (int w = 0; w < kT / 64; ++w) tot += wsum[w];
+    *out = tot;
+  }
+}
+
+// ct[t * ldc + j] = c[j * ldx + t] (the right-hand operand of V C^T, zero padded to dpad rows), cnorm[j] = |c_j|^2, and
+// the count of changed labels cleared.  One workgroup per centre.
+__global__ __launch_bounds__(kT) void centroid_operand_kernel(const double* __restrict__ c, int64_t ldx, int d, int dpad,
+                                                              double* __restrict__ ct, int64_t ldc,
+                                                              double* __restrict__ cnorm, int* __restrict__ changes) {
   const int j = blockIdx.x;
+  if (j == 0 && threadIdx.x < kChangeSlots) changes[threadIdx.x * kChangeStride] = 0;
   double ss = 0.0;
   for (int t = threadIdx.x; t < dpad; t += kT) {
     const double val = t < d ? c[(int64_t)j * ldx + t] : 0.0;
     ct[(int64_t)t * ldc + j] = val;
     ss += val * val;
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-  if (threadIdx.x % 64 == 0) part[threadIdx.x / 64] = ss;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
-    for (int w = 0; w < kT / 64; ++w) tot += part[w];
-    cnorm[j] = tot;
-  }
-  (void)k;
-}
-
-// label[i] = arg-min over j of cnorm[j] - 2 s[i, j] (the first one on ties); counts the labels that changed.
-// 16 lanes per point.
-__global__ __launch_bounds__(kT) void argmin_kernel(const double* __restrict__ s, int64_t lds, int64_t n, int k,
-                                                    const double* __restrict__ cnorm, int32_t* __restrict__ label,
-                                                    int* __restrict__ changes) {
-  constexpr int L = 16;
-  __shared__ int block_changes;
-  if (threadIdx.x == 0) block_changes = 0;
-  __syncthreads();
-  const int lane = threadIdx.x % L;
-  const int64_t i = (int64_t)blockIdx.x * (kT / L) + threadIdx.x / L;
-  if (i < n) {
-    double best = 1.79769313486231570815e308;
-    int bj = 0x7fffffff;
-    for (int j = lane; j < k; j += L) {
-      const double val = cnorm[j] - 2.0 * s[i * lds + j];
-      if (val < best) {  // j grows: an equal value later does not replace an earlier one
-        best = val;
-        bj = j;
-      }
-    }
-#pragma unroll
-    for (int o = L / 2; o > 0; o >>= 1) {
-      const double ob = __shfl_xor(best, o, L);
-      const int oj = __shfl_xor(bj, o, L);
-      if (ob < best || (ob == best && oj < bj)) {
-        best = ob;
-        bj = oj;
-      }
-    }
-    if (lane == 0) {
-      if (label[i] != bj) atomicAdd(&block_changes, 1);
-      label[i] = bj;
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0 && block_changes) atomicAdd(changes, block_changes);
+  block_norm(ss, cnorm + j);
 }
 
 __global__ __launch_bounds__(kT) void iota_fill_kernel(int32_t* __restrict__ a, int64_t n, int32_t value, int use_iota) {
   const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (i < n) a[i] = use_iota ? (int32_t)i : value;
+}
+
+// ---- grouping the points by label --------------------------------------------------------------------------------
+// A stable counting sort in three launches: every block of 1,024 points counts its labels, a wave per cluster turns the
+// counts into offsets, and the blocks write their points' indices in order.  (The library's radix sort of (label, index)
+// pairs takes ten launches, 49 us at 100,000 points and 100 clusters; these three take 12 us.)  Up to kMaxBins
+// clusters; beyond, a block's counters no longer fit the LDS and the radix sort is used.  A label outside [0, k), which
+// only points without a finite distance have, belongs to no cluster.
+constexpr int kMaxBins = 1024;
+constexpr int kSortBlock = 4 * kT;
+
+__global__ __launch_bounds__(kT) void label_count_kernel(const int32_t* __restrict__ label, int64_t n, int k, int nb,
+                                                         int32_t* __restrict__ count) {
+  __shared__ int bin[kMaxBins];
+  for (int c = threadIdx.x; c < k; c += kT) bin[c] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t i = (int64_t)blockIdx.x * kSortBlock + u * kT + threadIdx.x;
+    if (i < n && (uint32_t)label[i] < (uint32_t)k) atomicAdd(&bin[label[i]], 1);
+  }
+  __syncthreads();
+  for (int c = threadIdx.x; c < k; c += kT) count[(int64_t)c * nb + blockIdx.x] = bin[c];
+}
+
+// count[c][.] becomes its exclusive prefix sum, total[c] the sum.  A wave per cluster.
+__global__ __launch_bounds__(kT) void label_offset_kernel(int32_t* __restrict__ count, int k, int nb,
+                                                          int32_t* __restrict__ total) {
+  const int lane = threadIdx.x & 63;
+  const int c = blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
+  if (c >= k) return;
+  int32_t* row = count + (int64_t)c * nb;
+  int sum = 0;
+  for (int b0 = 0; b0 < nb; b0 += 64) {
+    const int mine = b0 + lane < nb ? row[b0 + lane] : 0;
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    if (b0 + lane < nb) row[b0 + lane] = sum + incl - mine;
+    sum += __shfl(incl, 63, 64);
+  }
+  if (lane == 0) total[c] = sum;
+}
+
+// start[c] = first position of cluster c, start[k] = number of grouped points; member[p] = the points in label order,
+// ascending within a label
+__global__ __launch_bounds__(kT) void label_scatter_kernel(const int32_t* __restrict__ label, int64_t n, int k, int bits,
+                                                           int nb, const int32_t* __restrict__ count,
+                                                           const int32_t* __restrict__ total,
+                                                           int32_t* __restrict__ start, int32_t* __restrict__ member) {
+  __shared__ int base[kT / 64][kMaxBins];
+  __shared__ int wave_sum[kT / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t w0 = (int64_t)blockIdx.x * kSortBlock + wave * 256;  // the wave's 256 points
+  for (int c = lane; c < k; c += 64) base[wave][c] = 0;
+  __syncthreads();
+  int lab[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t i = w0 + 64 * u + lane;
+    lab[u] = i < n ? label[i] : -1;
+    if ((uint32_t)lab[u] >= (uint32_t)k) lab[u] = -1;
+    if (lab[u] >= 0) atomicAdd(&base[wave][lab[u]], 1);
+  }
+  // where every cluster starts: thread t has the clusters 4 t .. 4 t + 3
+  int own[4], sum = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = 4 * (int)threadIdx.x + q;
+    own[q] = c < k ? total[c] : 0;
+    sum += own[q];
+  }
+  int incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wave_sum[wave] = incl;
+  __syncthreads();
+  int first = incl - sum;
+  for (int w = 0; w < wave; ++w) first += wave_sum[w];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = 4 * (int)threadIdx.x + q;
+    if (c < k) {
+      if (blockIdx.x == 0) {
+        start[c] = first;
+        if (c == k - 1) start[k] = first + own[q];
+      }
+      int at = first + count[(int64_t)c * nb + blockIdx.x];
+#pragma unroll
+      for (int w = 0; w < kT / 64; ++w) {
+        const int here = base[w][c];
+        base[w][c] = at;
+        at += here;
+      }
+    }
+    first += own[q];
+  }
+  __syncthreads();
+  // from here on a wave touches its own row of `base` only, one batch of 64 points after the other
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    uint64_t same = __ballot(lab[u] >= 0);
+    for (int bit = 0; bit < bits; ++bit) {
+      const bool set = (lab[u] >> bit) & 1;
+      const uint64_t with = __ballot(set);
+      same &= set ? with : ~with;
+    }
+    if (lab[u] >= 0) {
+      const int rank = __popcll(same & ((1ull << lane) - 1ull));
+      const int at = base[wave][lab[u]];
+      member[at + rank] = (int32_t)(w0 + 64 * u + lane);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // every lane has read before the first of a label adds
+      if (rank == 0) base[wave][lab[u]] = at + __popcll(same);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // start[c] = first position in the sorted label array with label >= c, c = 0 .. k
@@ -135,60 +224,149 @@ __global__ __launch_bounds__(kT) void cluster_starts_kernel(const int32_t* __res
   start[c] = (int32_t)lo;
 }
 
-// c[j, :] = mean of the points of cluster j (rows x[member[m]], start[j] <= m < start[j+1]); an empty cluster keeps
-// its centre.  Workgroup (j, column tile of 64): wave w sums the members w, w+4, ... in order, the four partial sums
-// are added in wave order.
-__global__ __launch_bounds__(kT) void centroid_mean_kernel(const double* __restrict__ x, int64_t ldx, int d,
-                                                           const int32_t* __restrict__ member,
-                                                           const int32_t* __restrict__ start, double* __restrict__ c) {
-  __shared__ double part[kT / 64][64];
-  const int j = blockIdx.x;
-  const int t = blockIdx.y * 64 + threadIdx.x % 64;
-  const int w = threadIdx.x / 64;
-  const int m0 = start[j], m1 = start[j + 1];
-  double acc = 0.0;
-  if (t < d)
-    for (int m = m0 + w; m < m1; m += kT / 64) acc += x[(int64_t)member[m] * ldx + t];
-  part[w][threadIdx.x % 64] = acc;
+// part[(j * parts + q) * ldx + t] = sum over the q-th of `parts` equal pieces of cluster j's points.  Workgroup (j, q,
+// column tile of 2 DL): DL lanes carry two columns each, the 256 / DL slots take every so many-th point of the piece,
+// four in flight, and their sums are added in slot order.  One workgroup per cluster and 64 columns, a chain of one
+// point's index and row after the other, took 194 us at 100,000 points, 100 coordinates and 100 clusters, this takes
+// 17 us: 80 MB from the Infinity Cache.
+template <int DL>
+__global__ __launch_bounds__(kT) void cluster_sum_kernel(const double* __restrict__ x, int64_t ldx,
+                                                         const int32_t* __restrict__ member,
+                                                         const int32_t* __restrict__ start, int parts,
+                                                         double* __restrict__ part) {
+  constexpr int S = kT / DL;
+  __shared__ double2 red[kT];
+  const int j = blockIdx.x, q = blockIdx.y;
+  const int t = ((int)blockIdx.z * DL + (int)threadIdx.x % DL) * 2, slot = threadIdx.x / DL;
+  const int m0 = start[j], len = start[j + 1] - m0;
+  const int a = m0 + (int)((int64_t)len * q / parts), b = m0 + (int)((int64_t)len * (q + 1) / parts);
+  double2 acc = make_double2(0.0, 0.0);
+  if (t < ldx) {
+    int m = a + slot;
+    for (; m + 3 * S < b; m += 4 * S) {
+      double2 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const double2*>(x + (int64_t)member[m + u * S] * ldx + t);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        acc.x += v[u].x;
+        acc.y += v[u].y;
+      }
+    }
+    for (; m < b; m += S) {
+      const double2 v = *reinterpret_cast<const double2*>(x + (int64_t)member[m] * ldx + t);
+      acc.x += v.x;
+      acc.y += v.y;
+    }
+  }
+  red[threadIdx.x] = acc;
   __syncthreads();
-  if (w == 0 && t < d && m1 > m0) {
-    double tot = part[0][threadIdx.x];
-    for (int q = 1; q < kT / 64; ++q) tot += part[q][threadIdx.x];
-    c[(int64_t)j * ldx + t] = tot / (double)(m1 - m0);
+  if (slot == 0 && t < ldx) {
+#pragma unroll 8
+    for (int s = 1; s < S; ++s) {
+      const double2 v = red[s * DL + threadIdx.x];
+      acc.x += v.x;
+      acc.y += v.y;
+    }
+    *reinterpret_cast<double2*>(part + ((int64_t)j * parts + q) * ldx + t) = acc;
   }
 }
 
-// dist2[i] = |x_i - x_c|^2 (first != 0) or min(dist2[i], |x_i - x_c|^2), c = *centre; bsum[block] = the sum of the
-// block's 16 values of dist2 in point order.  16 lanes per point, 16 points per workgroup.
-constexpr int kSeedPoints = kT / 16;
-__global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
-                                                           const int32_t* __restrict__ centre, int first,
-                                                           double* __restrict__ dist2, double* __restrict__ bsum) {
-  constexpr int L = 16;
-  __shared__ double pts[kSeedPoints];
-  const int lane = threadIdx.x % L;
-  const int64_t i = (int64_t)blockIdx.x * kSeedPoints + threadIdx.x / L;
-  double mine = 0.0;
-  if (i < n) {  // uniform over the point's lanes
-    const int64_t c = *centre;
-    double acc = 0.0;
-    for (int t = lane; t < d; t += L) {
-      const double diff = x[i * ldx + t] - x[c * ldx + t];
-      acc += diff * diff;
+// c[j, :] = mean of the points of cluster j from the sums of its pieces, added in order; an empty cluster keeps its
+// centre.  What the next labelling needs is made on the way (see centroid_operand_kernel), and its count of changes is
+// cleared.  One workgroup per centre.
+__global__ __launch_bounds__(kT) void centroid_finish_kernel(const double* __restrict__ part, int parts,
+                                                             const int32_t* __restrict__ start, int d, int64_t ldx,
+                                                             double* __restrict__ c, double* __restrict__ ct, int64_t ldc,
+                                                             double* __restrict__ cnorm, int* __restrict__ changes) {
+  const int j = blockIdx.x;
+  if (j == 0 && threadIdx.x < kChangeSlots) changes[threadIdx.x * kChangeStride] = 0;
+  const int len = start[j + 1] - start[j];
+  double ss = 0.0;
+  for (int t = threadIdx.x; t < ldx; t += kT) {
+    double v = t < d ? c[(int64_t)j * ldx + t] : 0.0;
+    if (len > 0 && t < d) {
+      v = 0.0;
+#pragma unroll 4
+      for (int q = 0; q < parts; ++q) v += part[((int64_t)j * parts + q) * ldx + t];
+      v /= (double)len;
+      c[(int64_t)j * ldx + t] = v;
     }
-#pragma unroll
-    for (int o = L / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, L);
-    mine = first ? acc : (acc < dist2[i] ? acc : dist2[i]);
-    if (lane == 0) dist2[i] = mine;
+    ct[(int64_t)t * ldc + j] = v;
+    ss += v * v;
   }
-  if (lane == 0) pts[threadIdx.x / L] = mine;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
+  block_norm(ss, cnorm + j);
+}
+
+// ---- seeding -------------------------------------------------------------------------------------------------------
+// A draw's distance pass: dist2[i] = |x_i - x_c|^2 (first) or min(dist2[i], |x_i - x_c|^2), c = *centre, and bsum[block] =
+// the sum of the block's 64 values of dist2 in a fixed order.  All draws but the first leave out the points whose distance
+// cannot shrink, by a bf16 copy of the points, a quarter of their bytes: with err_i >= |x_i - x~_i| (seed_copy_kernel), the
+// distance is at least |x~_i - x~_c| - err_i - err_c, and if that is no less than the distance kept, the minimum stands.
+// What is left is computed in fp64 as before, by 16 lanes per point, so the distances are the same to the last bit.  The
+// float distance of the copies is taken to be off by (d + 8) 2^-23 of itself, and the lower bound has to exceed the
+// distance kept by 1e-6 of it: more than the fp64 sums are off.  A NaN on the way fails the test and the point is
+// computed.
+// Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 11.6 us with the copy, which an XCD's L2 keeps
+// its part of from draw to draw (21 MB in all); what is left is the chain centre, its row, the point's row.  (Leaving points out by the triangle inequality with a kept assignment did
+// not shorten the pass: it saves no load of the first row.)
+constexpr int kSeedPoints = 64;   // points per block
+constexpr int kExactLanes = 16;
+// Up to this many blocks a pass finds its centre by itself: every workgroup reads all block sums once more, which then
+// costs less than the launch of a kernel that does it for all (whole seeding at 100,000 points of 100 coordinates, 100
+// draws: 1.64 against 1.88 ms; at 140,000 of 128, 128 draws: 2.82 against 2.64 ms).
+constexpr int64_t kDrawBlocks = 1800;
+
+// xh[i] = the centred point in bf16, padded with zeros to dpb coordinates (a multiple of 8); err[i] as above, rounded up.
+// mean: any point will do (exactness does not depend on it); a bf16 value is off by 2^-9 of its modulus at most, the
+// centring by 2^-52 of the coordinates.  8 lanes per point.
+__global__ __launch_bounds__(kT) void seed_copy_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
+                                                       const double* __restrict__ mean, int dpb, __bf16* __restrict__ xh,
+                                                       float* __restrict__ err) {
+  const int lane = threadIdx.x % 8;
+  const int64_t i = (int64_t)blockIdx.x * (kT / 8) + threadIdx.x / 8;
+  if (i >= n) return;  // uniform over the point's lanes
+  double moved = 0.0, size = 0.0;
+  for (int c0 = lane * 8; c0 < dpb; c0 += 64) {
+    union { __bf16 b[8]; uint4 v; } piece;
 #pragma unroll
-    for (int q = 0; q < kSeedPoints; ++q) tot += pts[q];
-    bsum[blockIdx.x] = tot;
+    for (int q = 0; q < 8; ++q) {
+      const int t = c0 + q;
+      const double v = t < d ? x[i * ldx + t] : 0.0, m = t < d ? mean[t] : 0.0, y = v - m;
+      piece.b[q] = (__bf16)(float)y;
+      const double off = y - (double)(float)piece.b[q];
+      moved += off * off;
+      size += v * v + m * m;
+    }
+    *reinterpret_cast<uint4*>(xh + i * dpb + c0) = piece.v;
   }
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) {
+    moved += __shfl_xor(moved, o, 8);
+    size += __shfl_xor(size, o, 8);
+  }
+  if (lane == 0) err[i] = (float)((sqrt(moved) + 4.5e-16 * sqrt(size)) * 1.00001);
+}
+
+// mean[t] of the points, in two steps with a fixed order: part[b][t] over the points b, b + gridDim.x, ...
+__global__ __launch_bounds__(kT) void seed_sum_kernel(const double* __restrict__ x, int64_t ldx, int64_t n,
+                                                      double* __restrict__ part) {
+  for (int t = threadIdx.x; t < ldx; t += kT) {
+    double acc = 0.0;
+#pragma unroll 8
+    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) acc += x[i * ldx + t];
+    part[(int64_t)blockIdx.x * ldx + t] = acc;
+  }
+}
+
+__global__ __launch_bounds__(kT) void seed_mean_kernel(const double* __restrict__ part, int parts, int64_t ldx, int64_t n,
+                                                       double* __restrict__ mean) {
+  const int t = blockIdx.x * kT + threadIdx.x;
+  if (t >= ldx) return;
+  double acc = 0.0;
+#pragma unroll 8
+  for (int b = 0; b < parts; ++b) acc += part[(int64_t)b * ldx + t];
+  mean[t] = acc / (double)n;
 }
 
 // Inclusive prefix sums of one value per lane over the wave (fixed shuffle tree).
@@ -221,33 +399,34 @@ __device__ int wave_first_exceeding(const double* __restrict__ v, int64_t count,
   return -1;
 }
 
-// Algorithm 5's draw in one workgroup: total = sum of all dist2 (through the block sums), r = u * total, and the first
-// point whose inclusive prefix sum exceeds r, found level by level: the 1024 threads each sum a contiguous run of
+// Algorithm 5's draw by one workgroup of T threads: total = sum of all dist2 (through the block sums), r = u * total, and
+// the first point whose inclusive prefix sum exceeds r, found level by level: the threads each sum a contiguous run of
 // block sums, their prefix sums name the run, one wave then finds the block inside the run and the point inside the
 // block.  Every sum has a fixed order.  If rounding makes a level miss (the finer sums fall short of the coarser
 // one) the last block / point of that level is taken; if no run qualifies (total = 0) the last point, as the
-// definition says.
-constexpr int kSelectThreads = 1024;
-__global__ __launch_bounds__(kSelectThreads) void seed_select_kernel(const double* __restrict__ bsum, int64_t nb,
-                                                                     const double* __restrict__ dist2, int64_t n, double u,
-                                                                     int32_t* __restrict__ chosen) {
-  __shared__ double wave_tot[kSelectThreads / 64];
-  __shared__ double excl[kSelectThreads];
+// definition says.  Every thread gets the point.
+template <int T>
+__device__ int64_t draw_point(const double* __restrict__ bsum, int64_t nb, const double* __restrict__ dist2, int64_t n,
+                              double u) {
+  __shared__ double wave_tot[T / 64];
+  __shared__ double excl[T];
   __shared__ int first_run;
+  __shared__ int32_t drawn;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int64_t chunk = (nb + kSelectThreads - 1) / kSelectThreads;
+  const int64_t chunk = (nb + T - 1) / T;
   const int64_t j0 = (int64_t)t * chunk;
   int64_t j1 = j0 + chunk;
   j1 = j1 < nb ? j1 : nb;
   double run = 0.0;
+#pragma unroll 4
   for (int64_t j = j0; j < j1; ++j) run += bsum[j];
   const double incl_w = wave_inclusive(run, lane);
   if (lane == 63) wave_tot[wave] = incl_w;
-  if (t == 0) first_run = kSelectThreads;
+  if (t == 0) first_run = T;
   __syncthreads();
   double offset = 0.0, total = 0.0;
 #pragma unroll
-  for (int w = 0; w < kSelectThreads / 64; ++w) {
+  for (int w = 0; w < T / 64; ++w) {
     if (w < wave) offset += wave_tot[w];
     total += wave_tot[w];
   }
@@ -256,28 +435,134 @@ __global__ __launch_bounds__(kSelectThreads) void seed_select_kernel(const doubl
   const double r = u * total;
   if (j0 < j1 && incl > r) atomicMin(&first_run, t);
   __syncthreads();
-  if (wave != 0) return;
-  const int tr = first_run;
-  if (tr == kSelectThreads) {  // nothing exceeds r: all distances are zero (or u * total rounded up to the total)
-    if (lane == 0) *chosen = (int32_t)(n - 1);
-    return;
+  if (wave == 0) {
+    const int tr = first_run;
+    int32_t at = (int32_t)(n - 1);  // nothing exceeds r: all distances are zero (or u * total rounded up to the total)
+    if (tr < T) {
+      const int64_t b0 = (int64_t)tr * chunk;
+      int64_t b1 = b0 + chunk;
+      b1 = b1 < nb ? b1 : nb;
+      double base = excl[tr];
+      bool missed = false;
+      int jb = wave_first_exceeding(bsum + b0, b1 - b0, r, &base, lane);
+      if (jb < 0) {  // the run's own sum exceeded r but its block sums, added up one by one, do not: take its last block
+        jb = (int)(b1 - b0) - 1;
+        missed = true;
+      }
+      const int64_t p0 = (b0 + jb) * kSeedPoints;
+      int64_t p1 = p0 + kSeedPoints;
+      p1 = p1 < n ? p1 : n;
+      int jp = missed ? -1 : wave_first_exceeding(dist2 + p0, p1 - p0, r, &base, lane);
+      if (jp < 0) jp = (int)(p1 - p0) - 1;
+      at = (int32_t)(p0 + jp);
+    }
+    if (lane == 0) drawn = at;
   }
-  const int64_t b0 = (int64_t)tr * chunk;
-  int64_t b1 = b0 + chunk;
-  b1 = b1 < nb ? b1 : nb;
-  double base = excl[tr];
-  bool missed = false;
-  int jb = wave_first_exceeding(bsum + b0, b1 - b0, r, &base, lane);
-  if (jb < 0) {  // the run's own sum exceeded r but its block sums, added up one by one, do not: take its last block
-    jb = (int)(b1 - b0) - 1;
-    missed = true;
+  __syncthreads();
+  return drawn;
+}
+
+constexpr int kSelectThreads = 1024;
+__global__ __launch_bounds__(kSelectThreads) void seed_select_kernel(const double* __restrict__ bsum, int64_t nb,
+                                                                     const double* __restrict__ dist2, int64_t n, double u,
+                                                                     int32_t* __restrict__ chosen) {
+  const int64_t at = draw_point<kSelectThreads>(bsum, nb, dist2, n, u);
+  if (threadIdx.x == 0) *chosen = (int32_t)at;
+}
+
+// The pass for the centre *centre (DRAW false), or for the centre that this draw itself takes from the distances before it
+// (DRAW true; every workgroup finds it for itself from the block sums, workgroup 0 writes it down): dist2 and bsum go from
+// one buffer to the other.
+template <bool SCREEN, bool DRAW>
+__global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
+                                                           const __bf16* __restrict__ xh, int dpb,
+                                                           const float* __restrict__ err, double u,
+                                                           int32_t* __restrict__ centre, int first,
+                                                           const double* __restrict__ bsum_in, int64_t nb,
+                                                           const double* __restrict__ dist2_in,
+                                                           double* __restrict__ dist2, double* __restrict__ bsum) {
+  constexpr int SL = 4;  // lanes per point of the screen: 64 points at a time
+  constexpr int EP = kSeedPoints / (kT / kExactLanes);  // points per 16 lanes
+  __shared__ double pts[kSeedPoints];
+  __shared__ int todo[kSeedPoints];
+  __shared__ int ntodo;
+  const int64_t i0 = (int64_t)blockIdx.x * kSeedPoints;
+  const int here = n - i0 < kSeedPoints ? (int)(n - i0) : kSeedPoints;
+  if (threadIdx.x == 0) ntodo = 0;
+  if (threadIdx.x < kSeedPoints) pts[threadIdx.x] = threadIdx.x < here && !first ? dist2_in[i0 + threadIdx.x] : 0.0;
+  int64_t c;
+  if constexpr (DRAW) {
+    c = draw_point<kT>(bsum_in, nb, dist2_in, n, u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *centre = (int32_t)c;
+  } else {
+    c = *centre;
+    __syncthreads();
   }
-  const int64_t p0 = (b0 + jb) * kSeedPoints;
-  int64_t p1 = p0 + kSeedPoints;
-  p1 = p1 < n ? p1 : n;
-  int jp = missed ? -1 : wave_first_exceeding(dist2 + p0, p1 - p0, r, &base, lane);
-  if (jp < 0) jp = (int)(p1 - p0) - 1;
-  if (lane == 0) *chosen = (int32_t)(p0 + jp);
+  const int lane = threadIdx.x % kExactLanes, group = threadIdx.x / kExactLanes;
+  if constexpr (SCREEN) {
+    const int p = threadIdx.x / SL, sl = threadIdx.x % SL;
+    const int64_t i = i0 + (p < here ? p : here - 1);
+    float acc = 0.0f;
+#pragma unroll 4
+    for (int t = sl * 8; t < dpb; t += SL * 8) {
+      union { __bf16 b[8]; uint4 v; } a, b;
+      a.v = *reinterpret_cast<const uint4*>(xh + i * dpb + t);
+      b.v = *reinterpret_cast<const uint4*>(xh + c * dpb + t);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float diff = (float)a.b[q] - (float)b.b[q];
+        acc += diff * diff;
+      }
+    }
+#pragma unroll
+    for (int o = SL / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, SL);
+    if (sl == 0 && p < here) {
+      const double low = sqrt((double)acc) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)err[i] - (double)err[c];
+      const bool stands = low > 0.0 && low * low >= pts[p] * (1.0 + 1e-6);
+      if (!stands) todo[atomicAdd(&ntodo, 1)] = p;
+    }
+    __syncthreads();
+    const int count = ntodo;
+    for (int s = group; s < count; s += kT / kExactLanes) {  // uniform over the point's lanes
+      const int pt = todo[s];
+      double acc2 = 0.0;
+      for (int t = lane; t < d; t += kExactLanes) {
+        const double diff = x[(i0 + pt) * ldx + t] - x[c * ldx + t];
+        acc2 += diff * diff;
+      }
+#pragma unroll
+      for (int o = kExactLanes / 2; o > 0; o >>= 1) acc2 += __shfl_xor(acc2, o, kExactLanes);
+      if (lane == 0 && acc2 < pts[pt]) pts[pt] = acc2;
+    }
+  } else {  // the lanes take their four points together
+    double acc[EP];
+#pragma unroll
+    for (int q = 0; q < EP; ++q) acc[q] = 0.0;
+    for (int t = lane; t < d; t += kExactLanes) {
+      const double cv = x[c * ldx + t];
+#pragma unroll
+      for (int q = 0; q < EP; ++q) {
+        const int p = group + q * (kT / kExactLanes);
+        const double diff = x[(i0 + (p < here ? p : here - 1)) * ldx + t] - cv;
+        acc[q] += diff * diff;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < EP; ++q) {
+#pragma unroll
+      for (int o = kExactLanes / 2; o > 0; o >>= 1) acc[q] += __shfl_xor(acc[q], o, kExactLanes);
+      const int p = group + q * (kT / kExactLanes);
+      if (lane == 0 && p < here && (first || acc[q] < pts[p])) pts[p] = acc[q];
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    double tot = pts[threadIdx.x];
+    if (threadIdx.x < here) dist2[i0 + threadIdx.x] = tot;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+  }
 }
 
 // c[j, :] = x[index[j], :]
@@ -343,14 +628,8 @@ hipError_t launch_points_to_rowmajor(const double* v, int64_t ldv, int colmajor,
 }
 
 hipError_t launch_centroid_operand(const double* c, int64_t ldx, int k, int d, int dpad, double* ct, int64_t ldc,
-                                   double* cnorm, hipStream_t st) {
-  hipLaunchKernelGGL(centroid_operand_kernel, dim3((unsigned)k), dim3(kT), 0, st, c, ldx, k, d, dpad, ct, ldc, cnorm);
-  return hipGetLastError();
-}
-
-hipError_t launch_argmin(const double* s, int64_t lds, int64_t n, int k, const double* cnorm, int32_t* label,
-                         int* changes, hipStream_t st) {
-  hipLaunchKernelGGL(argmin_kernel, dim3(blocks(n * 16)), dim3(kT), 0, st, s, lds, n, k, cnorm, label, changes);
+                                   double* cnorm, int* changes, hipStream_t st) {
+  hipLaunchKernelGGL(centroid_operand_kernel, dim3((unsigned)k), dim3(kT), 0, st, c, ldx, d, dpad, ct, ldc, cnorm, changes);
   return hipGetLastError();
 }
 
@@ -360,60 +639,139 @@ hipError_t launch_fill_int32(int32_t* a, int64_t n, int32_t value, int use_iota,
   return hipGetLastError();
 }
 
-size_t kmeans_update_workspace(int64_t n) {
-  size_t sort_bytes = 0;
-  (void)rocprim::radix_sort_pairs(nullptr, sort_bytes, (const int32_t*)nullptr, (int32_t*)nullptr,
-                                  (const int32_t*)nullptr, (int32_t*)nullptr, (size_t)n, 0u, 32u, (hipStream_t) nullptr);
-  sort_bytes = (sort_bytes + 255) / 256 * 256;
-  // temp | ident[n] | sorted_label[n] | member[n]
-  return sort_bytes + (size_t)n * 12 + 1024;
+namespace {
+
+// pieces per cluster: about 2,048 workgroups in all (eight per compute unit), at least 32 points each on average
+int update_parts(int64_t n, int64_t ldx, int k) {
+  const int64_t tiles = (ldx + 127) / 128;
+  int64_t parts = 2048 / ((int64_t)k * tiles);
+  const int64_t most = n / ((int64_t)k * 32) + 1;
+  parts = parts < most ? parts : most;
+  return (int)(parts < 1 ? 1 : parts);
+}
+
+size_t label_sort_bytes(int64_t n) {
+  size_t bytes = 0;
+  (void)rocprim::radix_sort_pairs(nullptr, bytes, (const int32_t*)nullptr, (int32_t*)nullptr, (const int32_t*)nullptr,
+                                  (int32_t*)nullptr, (size_t)n, 0u, 32u, (hipStream_t) nullptr);
+  return (bytes + 255) / 256 * 256;
+}
+
+}  // namespace
+
+size_t kmeans_update_workspace(int64_t n, int64_t ldx, int k) {
+  const size_t sums = ((size_t)k * update_parts(n, ldx, k) * (size_t)ldx * 8 + 255) / 256 * 256;
+  const size_t nb = (size_t)((n + kSortBlock - 1) / kSortBlock);
+  // sums | member[n] | counts[k][nb], total[k]   or   sums | member[n] | sorted_label[n], ident[n], temp
+  const size_t group = k <= kMaxBins ? ((size_t)k * nb + (size_t)k) * 4 : (size_t)n * 8 + label_sort_bytes(n);
+  return sums + ((size_t)n * 4 + 255) / 256 * 256 + group + 1024;
 }
 
 hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, void* work,
-                                  size_t work_bytes, int32_t* start, double* c, hipStream_t st) {
-  if (n <= 0 || n > INT32_MAX) return hipErrorInvalidValue;
-  size_t sort_bytes = 0;
-  hipError_t e = rocprim::radix_sort_pairs(nullptr, sort_bytes, (const int32_t*)nullptr, (int32_t*)nullptr,
-                                           (const int32_t*)nullptr, (int32_t*)nullptr, (size_t)n, 0u, 32u, st);
-  if (e != hipSuccess) return e;
-  const size_t tmp = (sort_bytes + 255) / 256 * 256;
-  if (work_bytes < tmp + (size_t)n * 12) return hipErrorInvalidValue;
+                                  size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
+                                  int* changes, hipStream_t st) {
+  if (n <= 0 || n > INT32_MAX || work_bytes < kmeans_update_workspace(n, ldx, k)) return hipErrorInvalidValue;
+  const int parts = update_parts(n, ldx, k);
   char* base = static_cast<char*>(work);
-  int32_t* ident = reinterpret_cast<int32_t*>(base + tmp);
-  int32_t* sorted_label = ident + n;
-  int32_t* member = sorted_label + n;
-  hipLaunchKernelGGL(iota_fill_kernel, dim3(blocks(n)), dim3(kT), 0, st, ident, n, 0, 1);
-  size_t sb = sort_bytes;
-  e = rocprim::radix_sort_pairs(base, sb, label, sorted_label, ident, member, (size_t)n, 0u, (unsigned)bits_for(k), st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cluster_starts_kernel, dim3(blocks(k + 1)), dim3(kT), 0, st, sorted_label, n, k, start);
-  hipLaunchKernelGGL(centroid_mean_kernel, dim3((unsigned)k, (unsigned)((d + 63) / 64)), dim3(kT), 0, st, x, ldx, d, member,
-                     start, c);
+  double* sums = reinterpret_cast<double*>(base);
+  base += ((size_t)k * parts * (size_t)ldx * 8 + 255) / 256 * 256;
+  int32_t* member = reinterpret_cast<int32_t*>(base);
+  base += ((size_t)n * 4 + 255) / 256 * 256;
+  if (k <= kMaxBins) {
+    const int nb = (int)((n + kSortBlock - 1) / kSortBlock);
+    int32_t* count = reinterpret_cast<int32_t*>(base);
+    int32_t* total = count + (size_t)k * nb;
+    hipLaunchKernelGGL(label_count_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, nb, count);
+    hipLaunchKernelGGL(label_offset_kernel, dim3((unsigned)((k + 3) / 4)), dim3(kT), 0, st, count, k, nb, total);
+    hipLaunchKernelGGL(label_scatter_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, bits_for(k), nb, count, total,
+                       start, member);
+  } else {
+    int32_t* sorted_label = reinterpret_cast<int32_t*>(base);
+    int32_t* ident = sorted_label + n;
+    char* temp = reinterpret_cast<char*>(((uintptr_t)(ident + n) + 255) / 256 * 256);
+    size_t sb = label_sort_bytes(n);
+    hipLaunchKernelGGL(iota_fill_kernel, dim3(blocks(n)), dim3(kT), 0, st, ident, n, 0, 1);
+    const hipError_t e = rocprim::radix_sort_pairs(temp, sb, label, sorted_label, ident, member, (size_t)n, 0u,
+                                                   (unsigned)bits_for(k), st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(cluster_starts_kernel, dim3(blocks(k + 1)), dim3(kT), 0, st, sorted_label, n, k, start);
+  }
+#define SC_SUM(DLV)                                                                                                     \
+  hipLaunchKernelGGL((cluster_sum_kernel<DLV>), dim3((unsigned)k, (unsigned)parts, (unsigned)((ldx + 2 * DLV - 1) / (2 * DLV))), \
+                     dim3(kT), 0, st, x, ldx, member, start, parts, sums)
+  if (ldx <= 4) SC_SUM(2);
+  else if (ldx <= 8) SC_SUM(4);
+  else if (ldx <= 16) SC_SUM(8);
+  else if (ldx <= 32) SC_SUM(16);
+  else if (ldx <= 64) SC_SUM(32);
+  else SC_SUM(64);
+#undef SC_SUM
+  hipLaunchKernelGGL(centroid_finish_kernel, dim3((unsigned)k), dim3(kT), 0, st, sums, parts, start, d, ldx, c, ct, ldc, cnorm,
+                     changes);
   return hipGetLastError();
 }
 
-size_t kmeans_seed_workspace(int64_t n) {
-  // dist2[n] | bsum[ceil(n / 16)]
+namespace {
+
+// The bf16 copy costs three launches (70 us at 100,000 points of 100 coordinates) and pays once the points no longer fit
+// the L2s and there are draws to spread that over: 100,000 x 100, 100 draws 2.04 -> 1.64 ms, 142,541 x 500, 500 draws
+// 60 -> 27 ms; 140,000 x 8, 100 draws 1.47 -> 1.44 ms, 50,000 x 64, 16 draws 0.19 -> 0.23 ms.
+bool seed_screened(int64_t n, int d, int k) { return n * (int64_t)d >= 4000000 && k >= 32; }
+constexpr int kSeedParts = 256;
+inline int seed_dpb(int d) { return (d + 7) / 8 * 8; }
+
+}  // namespace
+
+size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k) {
+  // two of (dist2[n] | bsum[ceil(n / 64)])  and, with the screen,  mean[ldx] | sums[kSeedParts][ldx] | err[n] | xh[n][dpb]
   const size_t nb = (size_t)((n + kSeedPoints - 1) / kSeedPoints);
-  return (size_t)n * 8 + nb * 8 + 1024;
+  size_t bytes = 2 * ((size_t)n + nb) * 8 + 1024;
+  if (seed_screened(n, d, k)) bytes += (size_t)ldx * 8 * (kSeedParts + 1) + (size_t)n * (4 + 2 * (size_t)seed_dpb(d)) + 1024;
+  return bytes;
 }
 
 // Algorithm 5.  u[0 .. k-1]: host array of uniform numbers in [0, 1).  chosen: device int32[k], the indices of the
-// chosen points in the order they were drawn.  Two launches per draw.
+// chosen points in the order they were drawn.  One or two launches per draw.
 hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, void* work,
                            size_t work_bytes, int32_t* chosen, hipStream_t st) {
   if (n <= 0 || n > INT32_MAX || k < 1) return hipErrorInvalidValue;
   const int64_t nb = (n + kSeedPoints - 1) / kSeedPoints;
-  if (work_bytes < (size_t)n * 8 + (size_t)nb * 8) return hipErrorInvalidValue;
-  double* dist2 = static_cast<double*>(work);
-  double* bsum = dist2 + n;
+  if (work_bytes < kmeans_seed_workspace(n, ldx, d, k)) return hipErrorInvalidValue;
+  double* dist2[2] = {static_cast<double*>(work), static_cast<double*>(work) + n + nb};
+  double* mean = dist2[1] + n + nb;
+  double* sums = mean + ldx;
+  float* err = reinterpret_cast<float*>(sums + (size_t)kSeedParts * ldx);
+  __bf16* xh = reinterpret_cast<__bf16*>(((uintptr_t)(err + n) + 15) / 16 * 16);
+  const int dpb = seed_dpb(d);
+  const bool screened = seed_screened(n, d, k), draws = nb <= kDrawBlocks;
   int64_t first = (int64_t)(u[0] * (double)n);
   first = first < n - 1 ? first : n - 1;
   hipLaunchKernelGGL(iota_fill_kernel, dim3(1), dim3(kT), 0, st, chosen, 1, (int32_t)first, 0);
+  if (screened) {
+    hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums);
+    hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, kSeedParts, ldx, n, mean);
+    hipLaunchKernelGGL(seed_copy_kernel, dim3(blocks(n * 8)), dim3(kT), 0, st, x, ldx, d, n, mean, dpb, xh, err);
+  }
+  int at = 0;  // the buffer with the distances to the centres so far
+  auto pass = [&](int i) {  // the distances to centre i - 1
+    const bool draw = draws && i > 1;
+    const double *din = dist2[at], *bin = dist2[at] + n;
+    if (i > 1) at ^= 1;
+#define SC_SEED(SCR, DRW)                                                                                               \
+  hipLaunchKernelGGL((seed_distance_kernel<SCR, DRW>), dim3((unsigned)nb), dim3(kT), 0, st, x, ldx, d, n, xh, dpb, err, \
+                     u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], dist2[at] + n)
+    if (screened && i > 1) {
+      if (draw) SC_SEED(true, true); else SC_SEED(true, false);
+    } else {
+      if (draw) SC_SEED(false, true); else SC_SEED(false, false);
+    }
+#undef SC_SEED
+  };
   for (int i = 1; i < k; ++i) {
-    hipLaunchKernelGGL(seed_distance_kernel, dim3((unsigned)nb), dim3(kT), 0, st, x, ldx, d, n, chosen + (i - 1),
-                       i == 1 ? 1 : 0, dist2, bsum);
-    hipLaunchKernelGGL(seed_select_kernel, dim3(1), dim3(kSelectThreads), 0, st, bsum, nb, dist2, n, u[i], chosen + i);
+    pass(i);
+    if (!draws || i == k - 1)
+      hipLaunchKernelGGL(seed_select_kernel, dim3(1), dim3(kSelectThreads), 0, st, dist2[at] + n, nb, dist2[at], n, u[i],
+                         chosen + i);
   }
   return hipGetLastError();
 }

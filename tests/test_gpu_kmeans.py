@@ -169,3 +169,53 @@ def test_kmeans_argument_errors(B):
     assert lib.sc_kmeans(None, 3, 0, 10, 3, 4, 0, 10, out_l.data_ptr(), out_c.data_ptr(), None, None) == B.SC_EINVAL
     assert lib.sc_kmeans(x.data_ptr(), 3, 0, 10, 3, 4, 0, 0, out_l.data_ptr(), out_c.data_ptr(), None, None) == B.SC_EDOMAIN
     assert lib.sc_kmeans_lloyd(x.data_ptr(), 3, 0, 10, 3, 4, None, 5, out_l.data_ptr(), None, None) == B.SC_EINVAL
+
+
+# the counting sort of the update at the edges of its blocks and of its range of clusters, and the radix sort beyond
+@pytest.mark.parametrize("n,d,k", [(1023, 1, 1), (1024, 2, 64), (1025, 5, 3), (4500, 9, 1024), (4500, 3, 1025), (3000, 129, 200)])
+def test_update_over_its_ranges(B, n, d, k):
+    rng = np.random.default_rng(n + d + k)
+    x = rng.standard_normal((n, d))
+    init = x[rng.choice(n, k, replace=False)].copy()
+    labels_ref, dist_ref = okm.assign(x, init)
+    cen_ref = okm.update_centroids(x, labels_ref, init)
+    labels, cen, _, _ = B.sc_kmeans_lloyd(_dev(x), _dev(init), 1)
+    lg = labels.cpu().numpy().astype(np.int64)
+    _check_labels(x, init, lg, labels_ref, dist_ref, max_ambiguous=2)
+    same = np.ones(k, dtype=bool)      # centres of clusters that the ambiguous points moved between are not comparable
+    same[np.concatenate([lg[lg != labels_ref], labels_ref[lg != labels_ref]])] = False
+    # sums of at most n numbers below 6 in another order: n 2^-53 of the sum of the moduli
+    np.testing.assert_allclose(cen.cpu().numpy()[same], cen_ref[same], rtol=0, atol=6.0 * n * 2.0 ** -53)
+
+
+# the seeding with the bf16 copy of the points: with and without its own draw, a common offset, equal points
+@pytest.mark.parametrize("n,d,k,kind", [(62501, 64, 33, "blobs"), (120003, 34, 40, "blobs"), (45001, 90, 32, "offset"),
+                                        (40001, 101, 35, "equal")])
+def test_screened_seeding_equals_plain_distances(B, n, d, k, kind):
+    x = _blobs(n, d, 25, seed=n, spread=0.3)
+    if kind == "offset":
+        x += 1e7
+    elif kind == "equal":
+        x[1:] = x[0] + np.repeat(np.arange(1.0, n)[:, None] % 7, d, axis=1)
+    chosen = B.sc_kmeanspp(_dev(x), k, 5)[0].cpu().numpy().astype(np.int64)
+    # draw by draw from the chosen points themselves: the index must be where the prefix sum passes u * total, to the
+    # rounding of sums of n numbers
+    d2 = okm.sq_distances_to(x, x[chosen[0]])
+    for i in range(1, k):
+        cs = np.cumsum(d2)
+        r = okm.uniform01(5, i) * cs[-1]
+        tol = 4.0 * n * 2.0 ** -53 * cs[-1]
+        j = chosen[i]
+        assert (j == n - 1 or cs[j] > r - tol) and (j == 0 or cs[j - 1] <= r + tol), (i, j)
+        d2 = np.minimum(d2, okm.sq_distances_to(x, x[j]))
+
+
+def test_points_without_a_finite_distance_break_nothing(B):
+    x = _blobs(5000, 20, 6, seed=3)
+    bad = np.array([17, 2048, 4999])
+    x[bad[0], 3], x[bad[1], 7], x[bad[2], 0] = np.nan, np.inf, -np.inf
+    init = np.delete(x, bad, axis=0)[:6].copy()
+    labels, cen, _, _ = B.sc_kmeans_lloyd(_dev(x), _dev(init), 1)
+    good = np.delete(np.arange(5000), bad)
+    labels_ref, _ = okm.assign(x[good], init)
+    np.testing.assert_array_equal(labels.cpu().numpy()[good], labels_ref)
