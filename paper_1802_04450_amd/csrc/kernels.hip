@@ -15,7 +15,9 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 #define MFMA_F64(a, b, c) __builtin_amdgcn_mfma_f64_16x16x4f64((a), (b), (c), 0, 0, 0)
 // Two waves per SIMD and more: the compiler then keeps the accumulators of the matrix instructions in the vector
 // registers.  With one wave allowed it prefers the accumulation registers and copies every accumulator over and back
-// around each trip of the loop.
+// around each trip of a loop: a loop of nothing but v_mfma_f64_16x16x4 ran at 49 instead of 73 to 78 TFLOP/s for that.
+// The kernels below, which wait for memory as well, gain 1 to 3 % (a block of 32 columns against 120, 500,000 rows, both
+// passes: 701 -> 676 us; against 992: 3.51 -> 3.43 ms).
 #define SC_MFMA_IN_VGPRS __attribute__((amdgpu_waves_per_eu(2)))
 
 namespace {
@@ -553,7 +555,7 @@ hipError_t launch_spmm_nz(const int64_t* rowptr, const int32_t* col, const doubl
 // A[row+g][c0 + 4i .. 4i+3] (32 contiguous bytes) and B[row+g][i (+16)].  MFMA q multiplies the q-th
 // of the four A values, so its output row M stands for A column c0 + 4M + q.
 template <int NT>
-__global__ __launch_bounds__(kThreads) void project_kernel(const double* __restrict__ basis, int64_t n, int64_t ld,
+__global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void project_kernel(const double* __restrict__ basis, int64_t n, int64_t ld,
                                                            int acol0, int ja, int bcol0, int b, int rows_per_panel,
                                                            int nwc, int vec_ok, double* __restrict__ part,
                                                            const int* __restrict__ skip) {
@@ -785,19 +787,35 @@ __device__ __forceinline__ void stage_coefficients(double* __restrict__ lds, con
 // chunk sits in LDS permuted so that the 64 lanes of one MFMA read 64 consecutive doubles.
 // PIPE: loads one trip ahead of the MFMAs, for long contractions only (see update_gram_kernel).
 template <int NT, int MT, bool PIPE>
-__global__ __launch_bounds__(kThreads) void row_gemm_kernel(double* __restrict__ basis, int64_t n, int64_t ld,
+__global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(double* __restrict__ basis, int64_t n, int64_t ld,
                                                             int acol0, int kdim, const double* __restrict__ bmat,
                                                             int ldb, int ncols, int mode, int ccol0,
                                                             double* __restrict__ out, int64_t ldo, int vec_ok,
                                                             const int32_t* __restrict__ rowmap,
                                                             const int* __restrict__ skip) {
   if (skip && *skip) return;  // uniform over the grid
-  constexpr int KC = 4096 / (NT * 16);  // contraction indices per LDS chunk (32 KB)
+  // contraction indices per LDS chunk: 32 KB, or 64 KB where the matrix instructions are the bound (half as many waits
+  // for a chunk: 1,000 x 500 coefficients and 500,000 rows 9.0 -> 8.6 ms)
+  constexpr int KC = (NT == 4 && PIPE ? 8192 : 4096) / (NT * 16);
   __shared__ double lds[KC * NT * 16];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
-  const int n0 = (int)blockIdx.y * NT * 16;
-  const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * (16 * MT);
+  // More than 64 output columns: the column groups of one panel of rows follow one another on the same XCD, so that the
+  // panel comes from memory once and from that XCD's L2 for the other groups (one group after the other over all rows
+  // read everything once per group).  300,000 rows, 400 coefficients: 192 columns 1,130 -> 950 us, 200 columns 1,390 ->
+  // 1,150 us; 500,000 rows, 1,000 x 500: 9.7 -> 8.6 ms = 58 of the 78 TFLOP/s of the fp64 matrix cores.  Groups of 80
+  // columns where that makes fewer of them were no better (950 and 1,170 us; 10.2 ms).
+  int group = 0;
+  int64_t panel = blockIdx.x;
+  if constexpr (NT == 4) {
+    const int groups = (ncols + 63) / 64;
+    const unsigned t = blockIdx.x / 8;
+    group = (int)(t % groups);
+    panel = (int64_t)(t / groups) * 8 + blockIdx.x % 8;
+    if (panel * (64 * MT) >= n) return;  // uniform over the workgroup
+  }
+  const int n0 = group * NT * 16;
+  const int64_t row0 = (panel * 4 + wave) * (16 * MT);
 
   d4 acc[MT][NT];
 #pragma unroll
@@ -831,19 +849,24 @@ __global__ __launch_bounds__(kThreads) void row_gemm_kernel(double* __restrict__
             av[h][mt] = *reinterpret_cast<const d4*>(abase + (int64_t)mt * 16 * ld + kcol);
         }
       };
+      const int tiles = (ncols - n0 + 15) / 16;  // of the last group of columns fewer than NT may hold any
       auto mult = [&](const d4 (&av)[2][MT], int kb) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           if (kb + 16 * h < kc16) {  // uniform; the LDS slots beyond kc16 were not filled
             const int kt = (kb >> 4) + h;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < 4; ++q) {
+              double bq[NT];
+#pragma unroll
+              for (int nt = 0; nt < NT; ++nt) bq[nt] = lds[((((kt * 4 + q) * NT + nt) * 4 + g) << 4) + i];
 #pragma unroll
               for (int nt = 0; nt < NT; ++nt) {
-                const double bq = lds[((((kt * 4 + q) * NT + nt) * 4 + g) << 4) + i];
+                if (NT == 4 && nt >= tiles) break;  // uniform
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = MFMA_F64(av[h][mt][q], bq, acc[mt][nt]);
+                for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = MFMA_F64(av[h][mt][q], bq[nt], acc[mt][nt]);
               }
+            }
           }
         }
       };
@@ -1313,7 +1336,7 @@ __global__ __launch_bounds__(kThreads) void cheb_combine_kernel(const double* __
 // PIPE: the variant for long contractions, see the note at its loop.  It needs more registers (fewer resident waves),
 // which costs more than it gains when the contraction has only a trip or two, so it is a kernel of its own.
 template <int NT, bool PIPE>
-__global__ __launch_bounds__(kThreads) void update_gram_kernel(double* __restrict__ basis, int64_t n, int64_t ld,
+__global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void update_gram_kernel(double* __restrict__ basis, int64_t n, int64_t ld,
                                                                int acol0, int kdim, const double* __restrict__ bmat, int b,
                                                                int ccol0, int vec_ok, int overwrite,
                                                                double* __restrict__ gpart,
@@ -1846,17 +1869,18 @@ hipError_t launch_row_gemm(double* basis, int64_t n, int64_t ld, int acol0, int 
   constexpr int MT = 2;
   const unsigned gx = (unsigned)ceil_div64(n, 4 * 16 * MT);
   const bool pipe = kdim >= 128;  // loads one trip ahead pay from a few trips on
-#define SC_LAUNCH_RG(NTV, PV, GY)                                                                                  \
-  hipLaunchKernelGGL((row_gemm_kernel<NTV, MT, PV>), dim3(gx, (GY)), dim3(kThreads), 0, st, basis, n, ld, acol0,   \
+#define SC_LAUNCH_RG(NTV, PV, GRID)                                                                                \
+  hipLaunchKernelGGL((row_gemm_kernel<NTV, MT, PV>), dim3(GRID), dim3(kThreads), 0, st, basis, n, ld, acol0,       \
                      kdim, bmat, ldb, ncols, mode, ccol0, out, ldo, vec_ok, rowmap, skip)
   if (ncols <= 16) {
-    if (pipe) SC_LAUNCH_RG(1, true, 1); else SC_LAUNCH_RG(1, false, 1);
+    if (pipe) SC_LAUNCH_RG(1, true, gx); else SC_LAUNCH_RG(1, false, gx);
   } else if (ncols <= 32) {
-    if (pipe) SC_LAUNCH_RG(2, true, 1); else SC_LAUNCH_RG(2, false, 1);
+    if (pipe) SC_LAUNCH_RG(2, true, gx); else SC_LAUNCH_RG(2, false, gx);
   } else {
     if (mode == 0 || (mode == 3 && ncols > 64)) return hipErrorInvalidValue;
-    const unsigned gy = (unsigned)((ncols + 63) / 64);
-    if (pipe) SC_LAUNCH_RG(4, true, gy); else SC_LAUNCH_RG(4, false, gy);
+    const int64_t grid = ceil_div64(gx, 8) * 8 * ((ncols + 63) / 64);
+    if (grid > INT32_MAX) return hipErrorInvalidValue;
+    if (pipe) SC_LAUNCH_RG(4, true, (unsigned)grid); else SC_LAUNCH_RG(4, false, (unsigned)grid);
   }
 #undef SC_LAUNCH_RG
   return hipGetLastError();
@@ -1930,10 +1954,10 @@ __global__ __launch_bounds__(kTestThreads) void second_pass_test_kernel(const do
 // Measurement aid: nothing but fp64 matrix-core instructions, eight independent accumulators per wave, no memory
 // traffic inside the loop, in either form of the instruction: 16x16x4 (2,048 flops, what the contraction kernels above
 // use: one operand value per lane feeds a 16 x 16 block) or 4x4x4 (four independent 4 x 4 blocks, 512 flops).  What
-// this reaches is the practical ceiling of the fp64 MFMA rate on the device (the published peak assumes the highest
-// clock and the better form).
+// this reaches is the practical ceiling of the fp64 MFMA rate on the device: 73 and 70 TFLOP/s at 2,048 workgroups, 78
+// in either form with operands that stay the same.
 template <int SHAPE>
-__global__ __launch_bounds__(kThreads) void mfma_rate_kernel(double* __restrict__ sink, int iters, double a0, double b0) {
+__global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void mfma_rate_kernel(double* __restrict__ sink, int iters, double a0, double b0) {
   d4 acc[8];
   double acc1[8];
 #pragma unroll
