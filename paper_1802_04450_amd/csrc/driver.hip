@@ -2675,15 +2675,25 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
       [](void* p) {
         Ctx* c = static_cast<Ctx*>(p);
         DevBuf<double> mean, norm;
+        DevBuf<char> work;
         DevBuf<int> bad;
         PinnedBuf<int> hbad;
-        bad.alloc(1);
-        hbad.alloc(1);
-        HIP_TRY(launch_fill_int32(bad.p, 1, 0, 0, c->st));
+        bad.alloc(2);
+        hbad.alloc(2);
+        HIP_TRY(launch_fill_int32(bad.p, 2, 0, 0, c->st));
         if (c->measure != 2) {
           mean.alloc((size_t)c->n);
           norm.alloc((size_t)c->n);
           HIP_TRY(launch_row_stats(c->x, c->ldx, c->n, c->d, c->measure == 0 ? 1 : 0, mean.p, norm.p, c->st));
+        }
+        const size_t wb = edge_buckets_workspace(c->n, c->d, c->ne);
+        if (wb) {
+          work.alloc(wb);
+          HIP_TRY(launch_edge_similarity_buckets(c->x, c->ldx, c->d, c->u, c->v, c->ne, c->measure, c->sigma, mean.p,
+                                                 norm.p, c->n, work.p, wb, bad.p, bad.p + 1, c->val, c->st));
+          HIP_TRY(hipMemcpyAsync(hbad.p, bad.p, 2 * sizeof(int), hipMemcpyDeviceToHost, c->st));
+          HIP_TRY(hipStreamSynchronize(c->st));
+          if (!hbad.p[1]) return hbad.p[0] ? SC_ECSR : SC_OK;
         }
         HIP_TRY(launch_edge_similarity(c->x, c->ldx, c->d, c->u, c->v, c->ne, c->measure, c->sigma, mean.p, norm.p,
                                        c->n, bad.p, c->val, c->st));
@@ -2722,20 +2732,25 @@ int sc_coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int
           return SC_OK;
         }
         const int64_t total = c->nnz * (c->sym ? 2 : 1);
-        const size_t wb = coo_to_csr_workspace(total);
         DevBuf<char> work;
         DevBuf<int> bad;
-        PinnedBuf<int64_t> host;
-        work.alloc(wb);
-        bad.alloc(1);
+        PinnedBuf<int64_t> host;  // rowptr[n], then the two flags
+        bad.alloc(2);
         host.alloc(2);
-        HIP_TRY(launch_fill_int32(bad.p, 1, 0, 0, c->st));
-        HIP_TRY(coo_to_csr(c->row, c->col, c->val, c->nnz, c->n, c->sym, work.p, wb, c->rp, c->co, c->vo, bad.p, c->st));
-        HIP_TRY(hipMemcpyAsync(host.p, c->rp + c->n, sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
-        int hbad = 0;
-        HIP_TRY(hipMemcpyAsync(&hbad, bad.p, sizeof(int), hipMemcpyDeviceToHost, c->st));
-        HIP_TRY(hipStreamSynchronize(c->st));
-        if (hbad) return SC_ECSR;
+        for (int radix = 0; radix < 2; ++radix) {
+          const size_t wb = coo_to_csr_workspace(total, c->n, radix);
+          work.alloc(wb);
+          HIP_TRY(launch_fill_int32(bad.p, 2, 0, 0, c->st));
+          HIP_TRY(coo_to_csr(c->row, c->col, c->val, c->nnz, c->n, c->sym, radix, work.p, wb, c->rp, c->co, c->vo, bad.p,
+                             c->st));
+          HIP_TRY(hipMemcpyAsync(host.p, c->rp + c->n, sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
+          HIP_TRY(hipMemcpyAsync(host.p + 1, bad.p, 2 * sizeof(int), hipMemcpyDeviceToHost, c->st));
+          HIP_TRY(hipStreamSynchronize(c->st));
+          int flags[2];
+          std::memcpy(flags, host.p + 1, sizeof flags);
+          if (flags[0]) return SC_ECSR;
+          if (!flags[1]) break;  // else a bucket overflowed: the radix sort
+        }
         if (c->nnz_out) *c->nnz_out = host.p[0];
         return SC_OK;
       },

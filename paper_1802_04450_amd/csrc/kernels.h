@@ -270,6 +270,13 @@ hipError_t launch_row_stats(const double* x, int64_t ldx, int64_t n, int d, int 
 hipError_t launch_edge_similarity(const double* x, int64_t ldx, int d, const int32_t* eu, const int32_t* ev,
                                   int64_t nedges, int measure, double sigma, const double* mean, const double* norm,
                                   int64_t n, int* bad, double* val, hipStream_t st);
+// The same through buckets of rows: 0 bytes where that does not pay.  over: device int, set to 1 if a bucket overflowed
+// (some values are then missing: call launch_edge_similarity).
+size_t edge_buckets_workspace(int64_t n, int d, int64_t nedges);
+hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, const int32_t* eu, const int32_t* ev,
+                                          int64_t nedges, int measure, double sigma, const double* mean,
+                                          const double* norm, int64_t n, void* work, size_t work_bytes, int* bad,
+                                          int* over, double* val, hipStream_t st);
 // ---- k-nearest-neighbour graph (Section III-A; knn.hip) -------------------------------------------------------
 // Exact Euclidean k nearest neighbours of every row of x (n x d, leading dimension ldx) other than the row itself:
 // idx_out[i*k + a] / dist_out[i*k + a] = index / distance of the a-th nearest, nearest first, equal distances by
@@ -295,9 +302,9 @@ size_t knn_pairs_workspace(int64_t n);
 hipError_t launch_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int k, double sigma, void* work,
                                   size_t work_bytes, int32_t* eu, int32_t* ev, double* val, int32_t* last_two,
                                   hipStream_t st);
-size_t coo_to_csr_workspace(int64_t total);
+size_t coo_to_csr_workspace(int64_t total, int64_t n, int radix);
 hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int64_t nnz_in, int64_t n,
-                      int symmetrize, void* work, size_t work_bytes, int64_t* rowptr_out, int32_t* col_out,
+                      int symmetrize, int radix, void* work, size_t work_bytes, int64_t* rowptr_out, int32_t* col_out,
                       double* val_out, int* bad, hipStream_t st);
 
 // Measurement aid: `workgroups` workgroups of four waves, each wave issuing iters * 8 fp64 matrix instructions and

@@ -4,8 +4,10 @@
 // Algorithm 1 centres the data in place and gives one thread a row / an edge.  Here the data are read only: a first
 // kernel stores the mean and the norm of every row (of the centred row for the cross correlation), and the edge
 // kernel forms sum_t (x_it - m_i)(x_jt - m_j) directly, 16 lanes per edge with 16-byte loads, so a row of the paper's
-// 90 doubles is read as a few full cache lines.  The conversion sorts (row, col) keys with rocPRIM's radix sort (a
-// library primitive, the counterpart of the paper's library call) and finds the row pointers by binary search.
+// 90 doubles is read as a few full cache lines.  Larger data are read bucket by bucket of rows, so that a row comes out of
+// memory a few times instead of once per pair.  The conversion puts the entries into buckets of rows and sorts each in
+// LDS; matrices that this does not suit go through rocPRIM's radix sort of (row, col) keys (a library primitive, the
+// counterpart of the paper's library call) with row pointers by binary search.
 #include <hip/hip_runtime.h>
 #include <cstring>
 
@@ -30,6 +32,184 @@ __device__ __forceinline__ double group_sum(double v) {
 #pragma unroll
   for (int o = kL / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kL);
   return v;
+}
+
+// ---- entries into buckets of rows ----------------------------------------------------------------------------------
+// Bucket b takes the entries of the rows [b << shift, (b + 1) << shift) into slots b * kBucketRoom .. of `slots`, in no
+// particular order: a workgroup counts its kPartEntries entries per bucket in LDS, reserves that many slots of every
+// bucket with one atomic addition and writes.  fill[b] ends up as the bucket's number of entries, more than kBucketRoom if
+// they did not fit (what does not fit is dropped: the caller looks at the counts).
+constexpr int kBucketRoom = 4096;
+constexpr int kMaxBuckets = 16384;
+constexpr int kPartThreads = 1024;
+constexpr int kPartTrips = 16;
+constexpr int kPartEntries = kPartThreads * kPartTrips;
+
+// The e-th entry is (row[e], col[e]) with payload e; with MIRROR the same again as (col[e], row[e]) with payload
+// nnz_in + e unless the two are equal.  An index outside [0, n) sets *bad; such an entry is left out.
+template <bool MIRROR>
+__global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* __restrict__ row,
+                                                                 const int32_t* __restrict__ col, int64_t nnz_in, int64_t n,
+                                                                 int shift, int nbuckets, int32_t* __restrict__ fill,
+                                                                 uint2* __restrict__ slots, uint32_t* __restrict__ slot_row,
+                                                                 int* __restrict__ bad) {
+  __shared__ int32_t count[kMaxBuckets];
+  const int64_t e0 = (int64_t)blockIdx.x * (MIRROR ? kPartEntries / 2 : kPartEntries);
+  constexpr int TR = MIRROR ? kPartTrips / 2 : kPartTrips;
+  for (int b = threadIdx.x; b < nbuckets; b += kPartThreads) count[b] = 0;
+  __syncthreads();
+  int32_t r[TR], c[TR];
+#pragma unroll
+  for (int u = 0; u < TR; ++u) {
+    const int64_t e = e0 + u * kPartThreads + threadIdx.x;
+    r[u] = e < nnz_in ? row[e] : -1;
+    c[u] = e < nnz_in ? col[e] : -1;
+  }
+  bool wrong = false;
+#pragma unroll
+  for (int u = 0; u < TR; ++u) {
+    const int64_t e = e0 + u * kPartThreads + threadIdx.x;
+    if (e >= nnz_in) continue;
+    if (r[u] < 0 || r[u] >= n || c[u] < 0 || c[u] >= n) {
+      wrong = true;
+      r[u] = -1;
+      continue;
+    }
+    atomicAdd(&count[r[u] >> shift], 1);
+    if (MIRROR && r[u] != c[u]) atomicAdd(&count[c[u] >> shift], 1);
+  }
+  if (wrong) atomicOr(bad, 1);
+  __syncthreads();
+  for (int b = threadIdx.x; b < nbuckets; b += kPartThreads) {
+    const int mine = count[b];
+    if (mine) count[b] = atomicAdd(&fill[b], mine);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < TR; ++u) {
+    const int64_t e = e0 + u * kPartThreads + threadIdx.x;
+    if (e >= nnz_in || r[u] < 0) continue;
+    const int at = atomicAdd(&count[r[u] >> shift], 1);
+    if (at < kBucketRoom) {
+      slots[(int64_t)(r[u] >> shift) * kBucketRoom + at] = make_uint2((uint32_t)c[u], (uint32_t)e);
+      slot_row[(int64_t)(r[u] >> shift) * kBucketRoom + at] = (uint32_t)r[u];
+    }
+    if (MIRROR && r[u] != c[u]) {
+      const int am = atomicAdd(&count[c[u] >> shift], 1);
+      if (am < kBucketRoom) {
+        slots[(int64_t)(c[u] >> shift) * kBucketRoom + am] = make_uint2((uint32_t)r[u], (uint32_t)(nnz_in + e));
+        slot_row[(int64_t)(c[u] >> shift) * kBucketRoom + am] = (uint32_t)c[u];
+      }
+    }
+  }
+}
+
+// base[b] = exclusive prefix sums of fill, *over |= 1 if a bucket overflowed.  One workgroup.
+__global__ __launch_bounds__(kPartThreads) void bucket_scan_kernel(const int32_t* __restrict__ fill, int nbuckets,
+                                                                   int32_t* __restrict__ base, int* __restrict__ over) {
+  __shared__ int32_t wave_sum[kPartThreads / 64];
+  constexpr int PER = kMaxBuckets / kPartThreads;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int32_t v[PER], sum = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int b = (int)threadIdx.x * PER + q;
+    v[q] = b < nbuckets ? fill[b] : 0;
+    if (v[q] > kBucketRoom) atomicOr(over, 1);
+    sum += v[q];
+  }
+  int32_t incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += up;
+  }
+  if (lane == 63) wave_sum[wave] = incl;
+  __syncthreads();
+  int32_t at = incl - sum;
+  for (int w = 0; w < wave; ++w) at += wave_sum[w];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int b = (int)threadIdx.x * PER + q;
+    if (b < nbuckets) base[b] = at;
+    at += v[q];
+  }
+}
+
+// The rows of a bucket, each sorted by (column, payload), to their place in the CSR.  One workgroup per bucket: the
+// entries are grouped by row in LDS, then an entry's place is the number of entries of its row that come before it.
+constexpr int kMaxBucketRows = 1024;
+__global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restrict__ fill, const int32_t* __restrict__ base,
+                                                         const int* __restrict__ over, int shift, int64_t n, int64_t nnz_in,
+                                                         const uint2* __restrict__ slots,
+                                                         const uint32_t* __restrict__ slot_row,
+                                                         const double* __restrict__ val, int64_t* __restrict__ rowptr,
+                                                         int32_t* __restrict__ col_out, double* __restrict__ val_out) {
+  __shared__ uint64_t key[kBucketRoom];
+  __shared__ uint16_t krow[kBucketRoom];
+  __shared__ int32_t first[kMaxBucketRows + 1], next[kMaxBucketRows];
+  __shared__ int32_t wave_sum[kT / 64];
+  if (*over) return;  // uniform over the grid
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int len = fill[b], rows = 1 << shift;
+  const int64_t row0 = (int64_t)b << shift, at0 = base[b];
+  for (int r = threadIdx.x; r < rows; r += kT) next[r] = 0;
+  __syncthreads();
+  const uint2* __restrict__ mine = slots + (int64_t)b * kBucketRoom;
+  const uint32_t* __restrict__ mrow = slot_row + (int64_t)b * kBucketRoom;
+  for (int p = threadIdx.x; p < len; p += kT) atomicAdd(&next[mrow[p] - (uint32_t)row0], 1);
+  __syncthreads();
+  {  // exclusive prefix sums over the rows: thread t has the rows 4 t .. 4 t + 3
+    int32_t v[kMaxBucketRows / kT], sum = 0;
+#pragma unroll
+    for (int q = 0; q < kMaxBucketRows / kT; ++q) {
+      const int r = (int)threadIdx.x * (kMaxBucketRows / kT) + q;
+      v[q] = r < rows ? next[r] : 0;
+      sum += v[q];
+    }
+    int32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int32_t at = incl - sum;
+    for (int w = 0; w < wave; ++w) at += wave_sum[w];
+#pragma unroll
+    for (int q = 0; q < kMaxBucketRows / kT; ++q) {
+      const int r = (int)threadIdx.x * (kMaxBucketRows / kT) + q;
+      if (r < rows) {
+        first[r] = at;
+        next[r] = at;
+        if (row0 + r < n) rowptr[row0 + r] = at0 + at;
+        if (row0 + r == n - 1) rowptr[n] = at0 + at + v[q];
+        if (r == rows - 1) first[rows] = at + v[q];
+      }
+      at += v[q];
+    }
+  }
+  __syncthreads();
+  for (int p = threadIdx.x; p < len; p += kT) {
+    const uint2 e = mine[p];
+    const int r = (int)(mrow[p] - (uint32_t)row0);
+    const int at = atomicAdd(&next[r], 1);
+    key[at] = ((uint64_t)e.x << 32) | e.y;
+    krow[at] = (uint16_t)r;
+  }
+  __syncthreads();
+  for (int p = threadIdx.x; p < len; p += kT) {
+    const uint64_t k = key[p];
+    const int r = krow[p], lo = first[r], hi = first[r + 1];
+    int before = 0;
+#pragma unroll 4
+    for (int q = lo; q < hi; ++q) before += key[q] < k ? 1 : 0;
+    const int64_t out = at0 + lo + before;
+    const int64_t e = (int64_t)(uint32_t)k;
+    col_out[out] = (int32_t)(k >> 32);
+    val_out[out] = val[e < nnz_in ? e : e - nnz_in];
+  }
 }
 
 // mean[i] = (1/d) sum_t x_it (0 when centre == 0), norm[i] = |x_i - mean[i]|_2
@@ -117,43 +297,158 @@ __global__ __launch_bounds__(kT) void edge_similarity_kernel(const double* __res
   if (lane == 0) val[e] = measure == 2 ? exp(-acc * inv_two_sigma2) : acc / (norm[u] * norm[v]);
 }
 
-// key[p] = row << 32 | col of output entry p, src[p] = the listed entry it copies.  Entry e gives output e; with
-// symmetrize its mirror (col, row) is output nnz_in + e, or a key of all ones (sorted past the end, then dropped) when
+// The same for data that do not fit the L2s, bucket by bucket of first rows: a workgroup keeps the rows of its bucket in
+// LDS and reads the second rows from memory; the buckets of an XCD are neighbours, so that where pairs join rows that are
+// near one another (a voxel grid, a neighbour list after a renumbering) the second rows come from its L2.  A pair's value
+// is formed by the same lanes in the same order as above.  3.8 M pairs of 142,541 rows of 90 doubles, listed offset by
+// offset: 683 us with every row read from the Infinity Cache once per pair (7.4 TB/s), 430 us here with the 34 us of the
+// partition.
+__global__ __launch_bounds__(kT) void edge_bucket_kernel(const double* __restrict__ x, int64_t ldx, int d, int shift,
+                                                         int nbuckets, const int32_t* __restrict__ fill,
+                                                         const uint2* __restrict__ slots,
+                                                         const uint32_t* __restrict__ slot_row, int measure,
+                                                         double inv_two_sigma2, const double* __restrict__ mean,
+                                                         const double* __restrict__ norm, int vec_ok, int64_t n,
+                                                         int* __restrict__ over, double* __restrict__ val) {
+  extern __shared__ double rows[];  // (1 << shift) x dl, then means and norms
+  const int per = (nbuckets + 7) / 8;
+  const int b = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+  if ((int)(blockIdx.x / 8) >= per || b >= nbuckets) return;  // uniform
+  const int count = fill[b];
+  if (count > kBucketRoom) {  // uniform
+    if (threadIdx.x == 0) *over = 1;
+    return;
+  }
+  if (count == 0) return;
+  const int dl = (d + 1) & ~1, nr = 1 << shift;
+  const int64_t row0 = (int64_t)b << shift;
+  double* mrow = rows + (size_t)nr * dl;
+  double* nrow = mrow + nr;
+  for (int e = threadIdx.x; e < nr * d; e += kT) {
+    const int r = e / d, t = e - r * d;
+    if (row0 + r < n) rows[r * dl + t] = x[(row0 + r) * ldx + t];
+  }
+  if (measure != 2 && (int)threadIdx.x < nr && row0 + threadIdx.x < n) {
+    mrow[threadIdx.x] = mean[row0 + threadIdx.x];
+    nrow[threadIdx.x] = norm[row0 + threadIdx.x];
+  }
+  __syncthreads();
+  const int lane = threadIdx.x % kL;
+  const uint2* __restrict__ mine = slots + (int64_t)b * kBucketRoom;
+  const uint32_t* __restrict__ urow = slot_row + (int64_t)b * kBucketRoom;
+  constexpr int E = 4;  // pairs in flight per 16 lanes (one: 670 us, eight: 510 us for the case above)
+  for (int p0 = threadIdx.x / kL; p0 < count; p0 += E * (kT / kL)) {  // uniform over the pairs' lanes
+    const double *xu[E], *xv[E];
+    double mu[E], mv[E], acc[E];
+    uint32_t out[E];
+    int ru[E];
+    int64_t vi[E];
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      const int p = p0 + q * (kT / kL) < count ? p0 + q * (kT / kL) : p0;  // past the end: the first again, not stored
+      const uint2 e = mine[p];
+      vi[q] = e.x;
+      out[q] = e.y;
+      ru[q] = (int)((int64_t)urow[p] - row0);
+      xu[q] = rows + ru[q] * dl;
+      xv[q] = x + vi[q] * ldx;
+      acc[q] = 0.0;
+      mu[q] = 0.0;
+      mv[q] = 0.0;
+    }
+    if (measure != 2) {
+#pragma unroll
+      for (int q = 0; q < E; ++q) {
+        mu[q] = mrow[ru[q]];
+        mv[q] = mean[vi[q]];
+      }
+    }
+    int t0 = 0;
+    if (vec_ok) {  // rows start 16-byte aligned: pairs of coordinates per load
+      const int d2 = d / 2;
+#pragma unroll 2
+      for (int t = lane; t < d2; t += kL) {
+        double2 bb[E];
+#pragma unroll
+        for (int q = 0; q < E; ++q) bb[q] = reinterpret_cast<const double2*>(xv[q])[t];
+#pragma unroll
+        for (int q = 0; q < E; ++q) {
+          const double2 a = reinterpret_cast<const double2*>(xu[q])[t];
+          if (measure == 2) {
+            const double f = a.x - bb[q].x, g = a.y - bb[q].y;
+            acc[q] += f * f;
+            acc[q] += g * g;
+          } else {
+            acc[q] += (a.x - mu[q]) * (bb[q].x - mv[q]);
+            acc[q] += (a.y - mu[q]) * (bb[q].y - mv[q]);
+          }
+        }
+      }
+      t0 = 2 * d2;
+    }
+    for (int t = t0 + lane; t < d; t += kL) {
+#pragma unroll
+      for (int q = 0; q < E; ++q) {
+        if (measure == 2) {
+          const double f = xu[q][t] - xv[q][t];
+          acc[q] += f * f;
+        } else {
+          acc[q] += (xu[q][t] - mu[q]) * (xv[q][t] - mv[q]);
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < E; ++q) {
+      const double tot = group_sum(acc[q]);
+      if (lane == 0 && p0 + q * (kT / kL) < count)
+        val[out[q]] = measure == 2 ? exp(-tot * inv_two_sigma2) : tot / (nrow[ru[q]] * norm[vi[q]]);
+    }
+  }
+}
+
+// the pairs with an index out of range: NaN
+__global__ __launch_bounds__(kT) void edge_invalid_kernel(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
+                                                          int64_t nedges, int64_t n, const int* __restrict__ bad,
+                                                          double* __restrict__ val) {
+  if (*bad == 0) return;  // uniform over the grid
+  for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nedges; e += (int64_t)gridDim.x * kT) {
+    const int64_t u = eu[e], v = ev[e];
+    if (u < 0 || u >= n || v < 0 || v >= n) val[e] = __longlong_as_double(0x7ff8000000000000ll);
+  }
+}
+
+// key[p] = row << bits | col of output entry p, src[p] = the listed entry it copies.  Entry e gives output e; with
+// symmetrize its mirror (col, row) is output nnz_in + e, or a key of row n (sorted past the end, then dropped) when
 // row == col.
 __global__ __launch_bounds__(kT) void coo_keys_kernel(const int32_t* __restrict__ row, const int32_t* __restrict__ col,
-                                                      int64_t nnz_in, int symmetrize, int64_t n,
+                                                      int64_t nnz_in, int symmetrize, int64_t n, int bits,
                                                       uint64_t* __restrict__ key, uint32_t* __restrict__ src,
                                                       int* __restrict__ bad) {
   const int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (e >= nnz_in) return;
   const int64_t r = row[e], c = col[e];
+  const uint64_t none = (uint64_t)n << bits;
+  src[e] = (uint32_t)e;
+  if (symmetrize) src[nnz_in + e] = (uint32_t)e;
   if (r < 0 || r >= n || c < 0 || c >= n) {
     atomicOr(bad, 1);
-    key[e] = ~0ull;
-    src[e] = (uint32_t)e;
-    if (symmetrize) {
-      key[nnz_in + e] = ~0ull;
-      src[nnz_in + e] = (uint32_t)e;
-    }
+    key[e] = none;
+    if (symmetrize) key[nnz_in + e] = none;
     return;
   }
-  key[e] = ((uint64_t)r << 32) | (uint64_t)c;
-  src[e] = (uint32_t)e;
-  if (symmetrize) {
-    key[nnz_in + e] = r == c ? ~0ull : (((uint64_t)c << 32) | (uint64_t)r);
-    src[nnz_in + e] = (uint32_t)e;
-  }
+  key[e] = ((uint64_t)r << bits) | (uint64_t)c;
+  if (symmetrize) key[nnz_in + e] = r == c ? none : (((uint64_t)c << bits) | (uint64_t)r);
 }
 
-// rowptr[i] = first sorted position whose row is >= i, i = 0 .. n (keys of all ones count as row 2^32 - 1 >= n)
-__global__ __launch_bounds__(kT) void coo_rowptr_kernel(const uint64_t* __restrict__ key, int64_t total, int64_t n,
+// rowptr[i] = first sorted position whose row is >= i, i = 0 .. n
+__global__ __launch_bounds__(kT) void coo_rowptr_kernel(const uint64_t* __restrict__ key, int64_t total, int64_t n, int bits,
                                                         int64_t* __restrict__ rowptr) {
   const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (i > n) return;
   int64_t lo = 0, hi = total;
   while (lo < hi) {
     const int64_t mid = (lo + hi) / 2;
-    if ((int64_t)(key[mid] >> 32) < i) {
+    if ((int64_t)(key[mid] >> bits) < i) {
       lo = mid + 1;
     } else {
       hi = mid;
@@ -163,11 +458,11 @@ __global__ __launch_bounds__(kT) void coo_rowptr_kernel(const uint64_t* __restri
 }
 
 __global__ __launch_bounds__(kT) void coo_emit_kernel(const uint64_t* __restrict__ key, const uint32_t* __restrict__ src,
-                                                      const double* __restrict__ val, int64_t nnz_out,
+                                                      const double* __restrict__ val, int64_t nnz_out, int bits,
                                                       int32_t* __restrict__ col_out, double* __restrict__ val_out) {
   const int64_t p = (int64_t)blockIdx.x * kT + threadIdx.x;
   if (p >= nnz_out) return;
-  col_out[p] = (int32_t)(key[p] & 0xffffffffull);
+  col_out[p] = (int32_t)(key[p] & ((1ull << bits) - 1ull));
   val_out[p] = val[src[p]];
 }
 
@@ -197,47 +492,150 @@ hipError_t launch_edge_similarity(const double* x, int64_t ldx, int d, const int
   return hipGetLastError();
 }
 
-size_t coo_to_csr_workspace(int64_t total) {
+namespace {
+
+struct BucketPlan {
+  bool use = false;
+  int shift = 0, buckets = 0;
+};
+
+// Rows per bucket: about 2,048 entries in a bucket that holds 4,096, fewer where that leaves the chip without work.
+BucketPlan plan_buckets(int64_t total, int64_t n) {
+  BucketPlan p;
+  if (n < 1) return p;
+  int64_t target = total / 1024;
+  target = target < 256 ? 256 : (target > kBucketRoom / 2 ? kBucketRoom / 2 : target);
+  while (p.shift < 10 && ((int64_t)2 << p.shift) * total <= target * n) ++p.shift;
+  const int64_t nb = ((n - 1) >> p.shift) + 1;
+  // more buckets than a workgroup has counters, or rows so long that ranking their entries (quadratic in the length) costs
+  // more than the sort: 2,000 rows of 2,000 entries take 1,124 us in buckets and 390 us in the radix sort
+  p.use = nb <= kMaxBuckets && total <= nb * (kBucketRoom / 2) && total <= 256 * n;
+  p.buckets = (int)nb;
+  return p;
+}
+
+size_t up256(size_t bytes) { return (bytes + 255) / 256 * 256; }
+
+size_t radix_workspace(int64_t total) {
   size_t sort_bytes = 0;
   (void)rocprim::radix_sort_pairs(nullptr, sort_bytes, (const uint64_t*)nullptr, (uint64_t*)nullptr,
                                   (const uint32_t*)nullptr, (uint32_t*)nullptr, (size_t)total, 0u, 64u,
                                   (hipStream_t) nullptr);
-  sort_bytes = (sort_bytes + 255) / 256 * 256;
   // temp | key[total] | key_sorted[total] | src[total] | src_sorted[total]
-  return sort_bytes + (size_t)total * 24 + 1024;
+  return up256(sort_bytes) + (size_t)total * 24 + 1024;
 }
 
-// Entries sorted by (row, col); listed duplicates stay separate entries in listing order (the sort is stable).
-// rowptr_out[n] is the number of entries emitted; col_out / val_out need room for `total` entries,
-// total = nnz_in * (symmetrize ? 2 : 1) < 2^31.  bad: device int, |= 1 if an index is out of range.
+}  // namespace
+
+size_t coo_to_csr_workspace(int64_t total, int64_t n, int radix) {
+  const BucketPlan p = plan_buckets(total, n);
+  // over, fill[buckets] | base[buckets] | slots | slot_row
+  if (p.use && !radix) return 2 * up256((size_t)p.buckets * 4 + 8) + (size_t)p.buckets * kBucketRoom * 12 + 1024;
+  return radix_workspace(total);
+}
+
+// Entries sorted by (row, col); listed duplicates stay separate entries in listing order.  rowptr_out[n] is the number
+// of entries emitted; col_out / val_out need room for `total` entries, total = nnz_in * (symmetrize ? 2 : 1) < 2^31.
+// bad: device int[2]; bad[0] |= 1 if an index is out of range; bad[1] = 1 if a bucket overflowed and nothing was done: the
+// caller then calls again with radix = 1.
+//
+// 3.8 M pairs of 142,541 rows (7.6 M entries): radix sort of 64-bit keys 640 us, with the keys, row pointers and gather
+// round it 730 us; buckets 180 us (partition 50, sort 126).  Bound by the scattered writes of the partition and the gather of the values.
 hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int64_t nnz_in, int64_t n,
-                      int symmetrize, void* work, size_t work_bytes, int64_t* rowptr_out, int32_t* col_out,
+                      int symmetrize, int radix, void* work, size_t work_bytes, int64_t* rowptr_out, int32_t* col_out,
                       double* val_out, int* bad, hipStream_t st) {
   const int64_t total = nnz_in * (symmetrize ? 2 : 1);
-  if (total <= 0 || total > INT32_MAX) return hipErrorInvalidValue;
+  if (total <= 0 || total > INT32_MAX || work_bytes < coo_to_csr_workspace(total, n, radix)) return hipErrorInvalidValue;
+  char* base = static_cast<char*>(work);
+  const BucketPlan p = plan_buckets(total, n);
+  if (p.use && !radix) {
+    int32_t* fill = reinterpret_cast<int32_t*>(base);
+    int32_t* first = reinterpret_cast<int32_t*>(base + up256((size_t)p.buckets * 4 + 8));
+    uint2* slots = reinterpret_cast<uint2*>(base + 2 * up256((size_t)p.buckets * 4 + 8));
+    uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + (size_t)p.buckets * kBucketRoom);
+    hipError_t e = launch_fill_int32(fill, p.buckets, 0, 0, st);
+    if (e != hipSuccess) return e;
+    const int64_t per = symmetrize ? kPartEntries / 2 : kPartEntries;
+    const dim3 grid((unsigned)((nnz_in + per - 1) / per));
+    if (symmetrize)
+      hipLaunchKernelGGL((partition_kernel<true>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
+                         fill, slots, slot_row, bad);
+    else
+      hipLaunchKernelGGL((partition_kernel<false>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
+                         fill, slots, slot_row, bad);
+    hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(kPartThreads), 0, st, fill, p.buckets, first, bad + 1);
+    hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)p.buckets), dim3(kT), 0, st, fill, first, bad + 1, p.shift, n,
+                       nnz_in, slots, slot_row, val, rowptr_out, col_out, val_out);
+    return hipGetLastError();
+  }
   size_t sort_bytes = 0;
   hipError_t e = rocprim::radix_sort_pairs(nullptr, sort_bytes, (const uint64_t*)nullptr, (uint64_t*)nullptr,
                                            (const uint32_t*)nullptr, (uint32_t*)nullptr, (size_t)total, 0u, 64u, st);
   if (e != hipSuccess) return e;
-  const size_t tmp = (sort_bytes + 255) / 256 * 256;
-  if (work_bytes < tmp + (size_t)total * 24) return hipErrorInvalidValue;
-  char* base = static_cast<char*>(work);
-  uint64_t* key = reinterpret_cast<uint64_t*>(base + tmp);
+  uint64_t* key = reinterpret_cast<uint64_t*>(base + up256(sort_bytes));
   uint64_t* key_sorted = key + total;
   uint32_t* src = reinterpret_cast<uint32_t*>(key_sorted + total);
   uint32_t* src_sorted = src + total;
-  hipLaunchKernelGGL(coo_keys_kernel, dim3(blocks(nnz_in)), dim3(kT), 0, st, row, col, nnz_in, symmetrize, n, key, src,
-                     bad);
+  const int bits = key_bits(n + 1);  // row n stands for dropped entries
+  hipLaunchKernelGGL(coo_keys_kernel, dim3(blocks(nnz_in)), dim3(kT), 0, st, row, col, nnz_in, symmetrize, n, bits, key,
+                     src, bad);
   size_t sb = sort_bytes;
-  // all 64 bits when dropped entries (keys of all ones) may be present, else only the bits that indices use
-  const int end_bit = symmetrize ? 64 : 32 + key_bits(n);
-  e = rocprim::radix_sort_pairs(base, sb, key, key_sorted, src, src_sorted, (size_t)total, 0u, (unsigned)end_bit, st);
+  e = rocprim::radix_sort_pairs(base, sb, key, key_sorted, src, src_sorted, (size_t)total, 0u, (unsigned)(2 * bits), st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(coo_rowptr_kernel, dim3(blocks(n + 1)), dim3(kT), 0, st, key_sorted, total, n, rowptr_out);
-  // entries past rowptr[n] are the dropped ones; emitting them too is harmless (col = 2^32 - 1 truncated) but the
-  // caller's arrays hold exactly `total` slots, so emit everything and let rowptr[n] say how many count
-  hipLaunchKernelGGL(coo_emit_kernel, dim3(blocks(total)), dim3(kT), 0, st, key_sorted, src_sorted, val, total, col_out,
-                     val_out);
+  hipLaunchKernelGGL(coo_rowptr_kernel, dim3(blocks(n + 1)), dim3(kT), 0, st, key_sorted, total, n, bits, rowptr_out);
+  // entries past rowptr[n] are the dropped ones; emitting them too is harmless but the caller's arrays hold exactly
+  // `total` slots, so emit everything and let rowptr[n] say how many count
+  hipLaunchKernelGGL(coo_emit_kernel, dim3(blocks(total)), dim3(kT), 0, st, key_sorted, src_sorted, val, total, bits,
+                     col_out, val_out);
+  return hipGetLastError();
+}
+
+namespace {
+
+// Rows of a bucket: a power of two that fits 24 KB (six workgroups per compute unit; 48 KB was 3 % slower), about half a
+// bucket's room of pairs.  Used where the data exceed what the L2s hold between them and a row occurs in several pairs:
+// 142,541 x 90 with 27 pairs a row 726 -> 478 us, 60,000 x 90 with 26 322 -> 226 us, 142,541 x 128 with 38 1,382 -> 535 us;
+// 142,541 x 33 with 27 448 -> 436 us, 30,000 x 64 with 26 115 -> 148 us, 142,541 x 90 with 3 111 -> 151 us.
+BucketPlan plan_edge_buckets(int64_t n, int d, int64_t nedges) {
+  BucketPlan p;
+  if (n * (int64_t)d < 5000000 || nedges < 8 * n) return p;
+  const int64_t row_bytes = (int64_t)((d + 1) & ~1) * 8 + 16;
+  while (p.shift < 8 && ((int64_t)2 << p.shift) * row_bytes <= 24 * 1024 &&
+         ((int64_t)2 << p.shift) * nedges <= kBucketRoom / 2 * n)
+    ++p.shift;
+  const int64_t nb = ((n - 1) >> p.shift) + 1;
+  if (p.shift < 3 || nb > kMaxBuckets || nedges > nb * (kBucketRoom / 2)) return p;
+  p.use = true;
+  p.buckets = (int)nb;
+  return p;
+}
+
+}  // namespace
+
+size_t edge_buckets_workspace(int64_t n, int d, int64_t nedges) {
+  const BucketPlan p = plan_edge_buckets(n, d, nedges);
+  return p.use ? up256((size_t)p.buckets * 4) + (size_t)p.buckets * kBucketRoom * 12 + 1024 : 0;
+}
+
+hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, const int32_t* eu, const int32_t* ev,
+                                          int64_t nedges, int measure, double sigma, const double* mean,
+                                          const double* norm, int64_t n, void* work, size_t work_bytes, int* bad,
+                                          int* over, double* val, hipStream_t st) {
+  const BucketPlan p = plan_edge_buckets(n, d, nedges);
+  if (!p.use || work_bytes < edge_buckets_workspace(n, d, nedges)) return hipErrorInvalidValue;
+  int32_t* fill = static_cast<int32_t*>(work);
+  uint2* slots = reinterpret_cast<uint2*>(static_cast<char*>(work) + up256((size_t)p.buckets * 4));
+  uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + (size_t)p.buckets * kBucketRoom);
+  const hipError_t e = launch_fill_int32(fill, p.buckets, 0, 0, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((partition_kernel<false>), dim3((unsigned)((nedges + kPartEntries - 1) / kPartEntries)),
+                     dim3(kPartThreads), 0, st, eu, ev, nedges, n, p.shift, p.buckets, fill, slots, slot_row, bad);
+  const int vec_ok = (ldx % 2 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
+  const double inv = measure == 2 ? 1.0 / (2.0 * sigma * sigma) : 0.0;
+  const size_t lds = ((size_t)1 << p.shift) * (size_t)(((d + 1) & ~1) + 2) * 8;
+  hipLaunchKernelGGL(edge_bucket_kernel, dim3((unsigned)((p.buckets + 7) / 8 * 8)), dim3(kT), lds, st, x, ldx, d, p.shift,
+                     p.buckets, fill, slots, slot_row, measure, inv, mean, norm, vec_ok, n, over, val);
+  hipLaunchKernelGGL(edge_invalid_kernel, dim3(512), dim3(kT), 0, st, eu, ev, nedges, n, bad, val);
   return hipGetLastError();
 }
 

@@ -107,6 +107,62 @@ def test_coo_to_csr_matches_oracle(B, n, ne, symmetrize):
                 assert sorted(mine.tolist()) == sorted(listed)
 
 
+def _csr_by_sorting(r, c, w, n, symmetrize):
+    """Rows sorted by column, equal entries in listing order (all listed entries before all mirrored ones)."""
+    m = r != c
+    if symmetrize:
+        r, c, w = np.concatenate([r, c[m]]), np.concatenate([c, r[m]]), np.concatenate([w, w[m]])
+    at = np.lexsort((np.arange(r.size), c, r))
+    return np.concatenate([[0], np.cumsum(np.bincount(r, minlength=n))]), c[at], w[at]
+
+
+# buckets of one row and of many, a last bucket that is not full, rows at the limit of a bucket and beyond (radix sort),
+# rows too long for the ranking, more rows than there are buckets
+@pytest.mark.parametrize("n,ne,hub", [(1, 3, 0), (1024, 260, 0), (1025, 5000, 0), (4099, 200_000, 4000), (4099, 200_000, 5000),
+                                      (300, 90_000, 0), (70_001, 1_200_000, 0), (20_000_000, 3000, 0)])
+@pytest.mark.parametrize("symmetrize", [False, True])
+def test_coo_to_csr_over_its_ranges(B, n, ne, hub, symmetrize):
+    rng = np.random.default_rng(n + ne + hub)
+    r, c = _edges(n, ne, 5)
+    if hub:
+        r[:hub] = n // 2                      # one row with `hub` entries more
+    w = rng.uniform(0.1, 1.0, size=ne)
+    rp, co, vo = B.sc_coo_to_csr(_dev(r, torch.int32), _dev(c, torch.int32), _dev(w, torch.float64), n, symmetrize)
+    rp0, co0, vo0 = _csr_by_sorting(r, c, w, n, symmetrize)
+    np.testing.assert_array_equal(rp.cpu().numpy(), rp0)
+    np.testing.assert_array_equal(co.cpu().numpy(), co0)
+    np.testing.assert_array_equal(vo.cpu().numpy(), vo0)
+
+
+# the bucketed pair kernel (data of 40 MB and more, eight pairs a row): against the oracle, with a ragged last bucket, odd
+# dimensions and strides (scalar loads), an index out of range, and one row in more pairs than a bucket holds
+@pytest.mark.parametrize("d,ldx,measure,twist", [(90, 90, 0, ""), (85, 85, 1, ""), (128, 129, 2, ""), (380, 380, 0, ""),
+                                                 (90, 90, 0, "bad"), (100, 100, 1, "hub")])
+def test_bucketed_edge_similarity_matches_oracle(B, d, ldx, measure, twist):
+    n = 5_000_000 // d + 37
+    rng = np.random.default_rng(d)
+    big = rng.normal(size=(n, ldx)) + 1.5
+    u, v = _edges(n, 8 * n + 11, 9)
+    if twist == "hub":
+        u[::8] = 12
+    if twist == "bad":
+        u[1234], v[99] = n, -1
+    x = _dev(big, torch.float64)
+    val = torch.zeros(u.size, dtype=torch.float64, device="cuda:0")
+    st = torch.cuda.current_stream().cuda_stream
+    du, dv = _dev(u, torch.int32), _dev(v, torch.int32)
+    code = B.lib().sc_edge_similarity(x.data_ptr(), ldx, n, d, du.data_ptr(), dv.data_ptr(), u.size, measure, float(np.sqrt(d)),
+                                      val.data_ptr(), st)
+    got, ok = val.cpu().numpy(), np.ones(u.size, dtype=bool)
+    assert code == (B.SC_ECSR if twist == "bad" else 0)
+    if twist == "bad":
+        ok[[1234, 99]] = False
+        assert np.isnan(got[~ok]).all()
+    ref = osim.edge_similarity(big[:, :d], u[ok], v[ok], measure, float(np.sqrt(d)))
+    # sums of d products: 2 d 2^-53 of the product of the norms, which is 1 in the value
+    np.testing.assert_allclose(got[ok], ref, rtol=1e-12, atol=4.0 * d * 2.0 ** -53)
+
+
 def test_coo_to_csr_edge_cases(B):
     z32 = torch.empty(0, dtype=torch.int32, device="cuda:0")
     z64 = torch.empty(0, dtype=torch.float64, device="cuda:0")
