@@ -441,18 +441,26 @@ void enqueue_block_qr(double* basis, int64_t n, int64_t ld, int col, int b, doub
   if (!tm) tm = &none;
   const double blk = 8.0 * (double)n * b;
   tm->begin(kFamQr);
+  // from the partial Gram blocks to the factor: one launch where there are few of them
+  auto factor = [&](const double* parts, int np, double* gcopy, double* rout, const double* rprev, double abs_tol2,
+                    double rel_tol) {
+    if (gram_cholesky_takes_parts(np, b)) {
+      HIP_TRY(launch_gram_cholesky_parts(parts, np, b, gcopy, rinv, rout, rprev, abs_tol2, rel_tol, st));
+    } else {
+      HIP_TRY(launch_reduce_partials(parts, np, b, b, gram, nullptr, 0, nullptr, 0, st));
+      HIP_TRY(launch_gram_cholesky(gram, b, gcopy, rinv, rout, rprev, abs_tol2, rel_tol, st));
+    }
+  };
   if (ngram > 0) {
-    HIP_TRY(launch_reduce_partials(gpart, ngram, b, b, gram, nullptr, 0, nullptr, 0, st));
+    factor(gpart, ngram, g_out, r1, nullptr, kAbsDrop2, kRelDrop);
   } else {
     const ProjectPlan plan = plan_project(n, b, kMaxPartials);
     HIP_TRY(launch_project(basis, n, ld, col, b, col, b, plan, part, st));
-    HIP_TRY(launch_reduce_partials(part, plan.npart, b, b, gram, nullptr, 0, nullptr, 0, st));
+    factor(part, plan.npart, g_out, r1, nullptr, kAbsDrop2, kRelDrop);
   }
-  HIP_TRY(launch_gram_cholesky(gram, b, g_out, rinv, r1, nullptr, kAbsDrop2, kRelDrop, st));
   HIP_TRY(launch_update_gram(basis, n, ld, col, b, rinv, b, col, 1, gpart, st));
-  HIP_TRY(launch_reduce_partials(gpart, plan_update_gram(n), b, b, gram, nullptr, 0, nullptr, 0, st));
   // second pass: a column that survived the first pass has unit norm, so only exact zeros are dropped
-  HIP_TRY(launch_gram_cholesky(gram, b, nullptr, rinv, r_out, r1, 0.25, 1e-8, st));
+  factor(gpart, plan_update_gram(n), nullptr, r_out, r1, 0.25, 1e-8);
   HIP_TRY(launch_apply_rinv(basis, n, ld, col, b, rinv, z, s, st));
   tm->end(kFamQr, (ngram > 0 ? 4.0 : 5.0) * blk + (z ? blk : 0.0), 4.0 * (double)n * b * b);
 }
@@ -1697,6 +1705,7 @@ struct Solver {
     int nfound = std::min(nx, k_out);
     if (nx < k_out) HIP_TRY(hipMemsetAsync(evecs_out, 0, (size_t)n * k_out * sizeof(double), st));
     std::vector<int32_t> order;
+    bool rows_done = false;  // the output's rows have unit length already
     if (nx > 0 && !final_rr) {
       order.resize(nx);
       std::iota(order.begin(), order.end(), 0);
@@ -1706,7 +1715,12 @@ struct Solver {
       std::vector<int32_t> outpos((size_t)nx, -1);  // output column of every locked basis column
       for (int t = 0; t < nfound; ++t) outpos[order[t]] = t;
       HIP_TRY(hipMemcpyAsync(perm_d.p, outpos.data(), (size_t)nx * sizeof(int32_t), hipMemcpyHostToDevice, st));
-      HIP_TRY(launch_gather_cols_colmajor(basis.p, n, ld, perm_d.p, nx, evecs_out, rowinv, st));
+      // rows of unit length are made on the way out (the packed block is free: it takes the factors), unless the rows
+      // are to be scaled by D^-1/2 first
+      const bool unit_rows = (flags & SC_FLAG_ROW_NORMALIZE) && !(flags & SC_FLAG_RANDOM_WALK_VECTORS);
+      if (unit_rows) HIP_TRY(launch_row_factor(basis.p, n, ld, perm_d.p, nx, z.p, st));
+      HIP_TRY(launch_gather_cols_colmajor(basis.p, n, ld, perm_d.p, nx, evecs_out, rowinv, unit_rows ? z.p : nullptr, st));
+      rows_done = unit_rows;
       HIP_TRY(hipStreamSynchronize(st));  // `outpos` is pageable host memory
     } else if (nx > 0) {
       std::vector<double> G((size_t)nx * nx, 0.0), hbuf((size_t)nx * kPP);
@@ -1747,7 +1761,8 @@ struct Solver {
     if ((flags & SC_FLAG_RANDOM_WALK_VECTORS) && nfound > 0)
       HIP_TRY(launch_scale_rows_colmajor(evecs_out, n, nfound, s.p, rowinv, st));
     // the embedding handed to k-means (Section II Step 4) with every point on the unit sphere
-    if ((flags & SC_FLAG_ROW_NORMALIZE) && nfound > 0) HIP_TRY(launch_normalize_rows_colmajor(evecs_out, n, nfound, st));
+    if ((flags & SC_FLAG_ROW_NORMALIZE) && !rows_done && nfound > 0)
+      HIP_TRY(launch_normalize_rows_colmajor(evecs_out, n, nfound, st));
     HIP_TRY(hipMemcpyAsync(evals_out, evals_host.data(), (size_t)k_out * sizeof(double), hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (debug_on()) std::fprintf(stderr, "[sceig] t=%.4fs outputs written\n", now_s() - t_begin);

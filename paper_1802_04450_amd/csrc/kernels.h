@@ -83,6 +83,11 @@ hipError_t launch_row_gemm(double* basis, int64_t n, int64_t ld, int acol0, int 
 //   If rprev != null: rout = r * rprev (composition of two passes) else rout = r.  Any output may be null.
 hipError_t launch_gram_cholesky(const double* g_in, int b, double* g_out, double* rinv, double* rout,
                                 const double* rprev, double abs_tol2, double rel_tol, hipStream_t st);
+// The same on the sum of npart partial Gram blocks (as launch_project and launch_update_gram leave them), where
+// gram_cholesky_takes_parts says that one launch is the cheaper way.
+bool gram_cholesky_takes_parts(int npart, int b);
+hipError_t launch_gram_cholesky_parts(const double* gpart, int npart, int b, double* g_out, double* rinv, double* rout,
+                                      const double* rprev, double abs_tol2, double rel_tol, hipStream_t st);
 // basis[:, col0 : col0+b] = basis[:, col0 : col0+b] * rinv  (rinv b x b row-major stride kPartialPad);
 // if z != null also z[i*b + t] = s[i] * new value.
 hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const double* rinv, double* z,
@@ -197,9 +202,13 @@ hipError_t launch_random_block(double* basis, int64_t n, int64_t ld, int col0, i
                                uint64_t stream_id, hipStream_t st);
 // dst[i*ldd + dcol0 + t] = src[i*lds + scol0 + t], t < w (regions must not overlap)
 // out[pos[c]*n + o] = basis[r(o)*ld + c] for c < ncols with pos[c] >= 0 (pos: device int32[ncols], the output column
-// of basis column c or -1; r(o) = inv[o], the internal row of original row o, if inv is given, else o)
+// of basis column c or -1; r(o) = inv[o], the internal row of original row o, if inv is given, else o); factor (may be
+// null): row r of the basis is multiplied by factor[r] on the way
 hipError_t launch_gather_cols_colmajor(const double* basis, int64_t n, int64_t ld, const int32_t* pos, int ncols,
-                                       double* out, const int32_t* inv, hipStream_t st);
+                                       double* out, const int32_t* inv, const double* factor, hipStream_t st);
+// factor[i] = 1 / 2-norm of the entries of row i that the gather copies (1 if they are all zero)
+hipError_t launch_row_factor(const double* basis, int64_t n, int64_t ld, const int32_t* pos, int ncols, double* factor,
+                             hipStream_t st);
 // The solver's own operator copy for wide blocks (b = 8, 16, 32) holds S_ij = s_i W_ij s_j multiplied out:
 // val_out[e] = s_i * val[e] * s_j (val_out may be val).
 hipError_t launch_scale_values(const int64_t* rowptr, const int32_t* col, const double* val, const double* s,

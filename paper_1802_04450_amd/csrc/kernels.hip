@@ -1162,9 +1162,14 @@ __global__ __launch_bounds__(kCholThreads) void gram_cholesky_kernel(const doubl
   }
 }
 
-constexpr int kRinvTrips = 16;  // row groups per workgroup: the staging of R^-1 is paid once for all of them
+// Row groups per workgroup: the staging of R^-1 is paid once for all of them, but only once the chip has its workgroups
+// (always 16 groups: 12.4 us for 4,040 rows of 8 columns, in eight workgroups, now 3.5; 100,000 x 16: 19 -> 12 us).
+inline int rinv_trips(int64_t n, int b) {
+  const int64_t groups = ceil_div64(n, kThreads / b), trips = groups / 1024;
+  return (int)(trips < 1 ? 1 : (trips > 16 ? 16 : trips));
+}
 __global__ __launch_bounds__(kThreads) void apply_rinv_kernel(double* __restrict__ basis, int64_t n, int64_t ld,
-                                                              int col0, int b, const double* __restrict__ rinv,
+                                                              int col0, int b, int trips, const double* __restrict__ rinv,
                                                               double* __restrict__ z, const double* __restrict__ s) {
   __shared__ double Ri[kMaxBlock][kMaxBlock + 1];
   __shared__ double Wt[2 * kThreads];  // rows_per_block rows of b + 1 doubles (b >= 1)
@@ -1172,15 +1177,15 @@ __global__ __launch_bounds__(kThreads) void apply_rinv_kernel(double* __restrict
   const int rows_per_block = kThreads / b;
   const int t = threadIdx.x % b, rl = threadIdx.x / b;
   // the entry of the next trip is requested before this trip's sums, so its latency hides behind them
-  const int64_t first = (int64_t)blockIdx.x * kRinvTrips * rows_per_block + rl;
+  const int64_t first = (int64_t)blockIdx.x * trips * rows_per_block + rl;
   double ahead = first < n ? basis[first * ld + col0 + t] : 0.0;
-  for (int trip = 0; trip < kRinvTrips; ++trip) {
-    const int64_t row = ((int64_t)blockIdx.x * kRinvTrips + trip) * rows_per_block + rl;
+  for (int trip = 0; trip < trips; ++trip) {
+    const int64_t row = ((int64_t)blockIdx.x * trips + trip) * rows_per_block + rl;
     __syncthreads();  // the tile of the trip before has been read (and, first time round, R^-1 is staged)
     Wt[rl * (b + 1) + t] = ahead;
     __syncthreads();
     const int64_t nrow = row + rows_per_block;
-    ahead = (trip + 1 < kRinvTrips && nrow < n) ? basis[nrow * ld + col0 + t] : 0.0;
+    ahead = (trip + 1 < trips && nrow < n) ? basis[nrow * ld + col0 + t] : 0.0;
     double acc = 0.0;
     for (int q = 0; q <= t; ++q) acc += Wt[rl * (b + 1) + q] * Ri[q][t];
     if (row < n) {
@@ -1250,7 +1255,8 @@ __global__ __launch_bounds__(kThreads) void copy_cols_kernel(const double* __res
 __global__ __launch_bounds__(kThreads) void gather_cols_colmajor_kernel(const double* __restrict__ basis, int64_t n,
                                                                         int64_t ld, const int32_t* __restrict__ pos,
                                                                         int ncols, double* __restrict__ out,
-                                                                        const int32_t* __restrict__ inv) {
+                                                                        const int32_t* __restrict__ inv,
+                                                                        const double* __restrict__ factor) {
   __shared__ double tile[64][65];
   const int64_t i0 = (int64_t)blockIdx.x * 64;
   const int c0 = blockIdx.y * 64;
@@ -1268,7 +1274,7 @@ __global__ __launch_bounds__(kThreads) void gather_cols_colmajor_kernel(const do
   }
   double v[16];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) v[u] = basis[src[u] * ld + cc];
+  for (int u = 0; u < 16; ++u) v[u] = basis[src[u] * ld + cc] * (factor ? factor[src[u]] : 1.0);
 #pragma unroll
   for (int u = 0; u < 16; ++u) tile[c][rq + 4 * u] = v[u];
   __syncthreads();
@@ -1279,6 +1285,27 @@ __global__ __launch_bounds__(kThreads) void gather_cols_colmajor_kernel(const do
       if (p >= 0) out[(int64_t)p * n + i0 + r] = tile[oc][r];
     }
   }
+}
+
+// factor[i] = 1 / |row i of the output columns| (1 for a row of zeros): with it the gather above writes rows of unit
+// length.  A wave per row.  Normalising the column-major output afterwards read it twice and wrote it once more: 500,000 x
+// 2,000 4.5 ms, this 1.8 (and 0.7 more in the gather).
+__global__ __launch_bounds__(kThreads) void row_factor_kernel(const double* __restrict__ basis, int64_t n, int64_t ld,
+                                                              const int32_t* __restrict__ pos, int ncols,
+                                                              double* __restrict__ factor) {
+  const int lane = threadIdx.x & 63;
+  const int64_t i = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (i >= n) return;
+  const double* __restrict__ row = basis + i * ld;
+  double ss = 0.0;
+#pragma unroll 4
+  for (int c = lane; c < ncols; c += 64) {
+    const double v = pos[c] >= 0 ? row[c] : 0.0;
+    ss += v * v;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if (lane == 0) factor[i] = ss > 0.0 ? 1.0 / sqrt(ss) : 1.0;
 }
 
 // out[t * n + o] *= s[r(o)] for t < k: column-major vectors in the caller's numbering times the scaling vector held in
@@ -1536,6 +1563,88 @@ __device__ __forceinline__ double bcast_lane(double v, int l) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// Cholesky with column drop, inverse and product with the factor before it, by one wave, lane t = column t (see
+// launch_gram_cholesky): b <= 16.  g: b x b, row stride gs.  A finished row of R is taken out of all remaining rows at
+// once, a finished entry of the inverse's column goes into all sums that wait for it, so that the multiply-adds of a step
+// do not wait for one another.
+template <int B>
+__device__ __forceinline__ void chol_wave(const double* g, int gs, double* __restrict__ g_out,
+                                          double* __restrict__ rinv_out, double* __restrict__ r_out,
+                                          const double* __restrict__ rprev, double abs_tol2, double rel_tol) {
+  const int t = threadIdx.x & 63;
+  const bool act = t < B;
+  const int tc = act ? t : 0;
+  double gcol[B], rcol[B], ricol[B];
+  double gdiag = 0.0;  // own diagonal entry of g
+#pragma unroll
+  for (int q = 0; q < B; ++q) {
+    const int lo = q < tc ? q : tc, hi = q < tc ? tc : q;
+    gcol[q] = g[lo * gs + hi];  // upper triangle, mirrored
+    gdiag = q == tc ? gcol[q] : gdiag;
+    ricol[q] = 0.0;
+  }
+  if (g_out && act) {
+#pragma unroll
+    for (int q = 0; q < B; ++q) g_out[q * kPartialPad + t] = gcol[q];
+  }
+#pragma unroll
+  for (int k = 0; k < B; ++k) {
+    const double gkk = bcast_lane(gdiag, k), pk = bcast_lane(gcol[k], k);
+    const bool drop = !(gkk > abs_tol2) || !(pk > rel_tol * gkk);
+    const double rkk = drop ? 0.0 : sqrt(pk);
+    rcol[k] = (t == k) ? rkk : ((t > k && !drop) ? gcol[k] / rkk : 0.0);
+#pragma unroll
+    for (int q = k + 1; q < B; ++q) gcol[q] -= bcast_lane(rcol[k], q) * rcol[k];
+  }
+  double rcc = 0.0;  // own diagonal entry
+#pragma unroll
+  for (int q = 0; q < B; ++q) rcc = (q == t) ? rcol[q] : rcc;
+  // ricol[r] holds the sum over the finished entries x > r of R[r][x] Rinv[x][t] until it is its turn
+#pragma unroll
+  for (int r = B - 1; r >= 0; --r) {
+    const double rrr = bcast_lane(rcol[r], r);
+    double v = 0.0;
+    if (rrr != 0.0 && rcc != 0.0) v = (t == r) ? 1.0 / rrr : (t > r ? -ricol[r] / rrr : 0.0);
+    ricol[r] = v;
+#pragma unroll
+    for (int x = 0; x < r; ++x) ricol[x] += bcast_lane(rcol[x], r) * v;
+  }
+  if (rinv_out && act) {
+#pragma unroll
+    for (int q = 0; q < B; ++q) rinv_out[q * kPartialPad + t] = ricol[q];
+  }
+  if (r_out) {
+    if (rprev) {
+      double v[B];
+#pragma unroll
+      for (int q = 0; q < B; ++q) v[q] = 0.0;
+#pragma unroll
+      for (int x = 0; x < B; ++x) {
+        const double p = rprev[x * kPartialPad + tc];
+#pragma unroll
+        for (int q = 0; q <= x; ++q) v[q] += bcast_lane(rcol[q], x) * p;
+      }
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (act) r_out[q * kPartialPad + t] = v[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (act) r_out[q * kPartialPad + t] = rcol[q];
+    }
+  }
+}
+
+template <int B>
+__global__ __launch_bounds__(64) void chol_wave_kernel(const double* __restrict__ g_in, double* __restrict__ g_out,
+                                                       double* __restrict__ rinv_out, double* __restrict__ r_out,
+                                                       const double* __restrict__ rprev, double abs_tol2, double rel_tol) {
+  chol_wave<B>(g_in, kPartialPad, g_out, rinv_out, r_out, rprev, abs_tol2, rel_tol);
+}
+
+// The same for b = 32 with every entry as one chain of multiply-adds: 38.6 us, where the form above takes 54 (its code is
+// longer, and what bounds straight-line code of 40 KB that runs once is the instruction fetch), and rolled loops over LDS
+// by a workgroup 45 (two barriers a step).
 template <int B>
 __global__ __launch_bounds__(64) void chol_reg_kernel(const double* __restrict__ g_in, double* __restrict__ g_out,
                                                       double* __restrict__ rinv_out, double* __restrict__ r_out,
@@ -1603,6 +1712,39 @@ __global__ __launch_bounds__(64) void chol_reg_kernel(const double* __restrict__
       if (act) r_out[q * kPartialPad + t] = v;
     }
   }
+}
+
+
+// From npart partial Gram blocks to the factor in one launch instead of two, where there are few of them: the workgroup
+// adds them up in a fixed order first.
+constexpr int kPartsThreads = 256;
+template <int B>
+__global__ __launch_bounds__(kPartsThreads) void chol_parts_kernel(const double* __restrict__ gpart, int npart,
+                                                                   double* __restrict__ g_out,
+                                                                   double* __restrict__ rinv_out,
+                                                                   double* __restrict__ r_out,
+                                                                   const double* __restrict__ rprev, double abs_tol2,
+                                                                   double rel_tol) {
+  constexpr int SPLIT = kPartsThreads / (B * B);
+  __shared__ double sub[SPLIT][B * B];
+  const int e = threadIdx.x % (B * B), r = threadIdx.x / (B * B);
+  const double* p = gpart + (e / B) * kPartialPad + e % B;
+  double acc = 0.0;
+#pragma unroll 8
+  for (int q = r; q < npart; q += SPLIT) acc += p[(int64_t)q * B * kPartialPad];
+  sub[r][e] = acc;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;  // a wave: the others are done
+#pragma unroll
+  for (int f = 0; f < B * B; f += 64) {
+    double tot = sub[0][f + threadIdx.x];
+#pragma unroll
+    for (int q = 1; q < SPLIT; ++q) tot += sub[q][f + threadIdx.x];
+    sub[0][f + threadIdx.x] = tot;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own LDS operations complete in order
+  __builtin_amdgcn_wave_barrier();
+  chol_wave<B>(sub[0], B, g_out, rinv_out, r_out, rprev, abs_tol2, rel_tol);
 }
 
 
@@ -1902,8 +2044,8 @@ hipError_t launch_label(const double* x, int64_t ldx, int64_t n, const double* c
 
 hipError_t launch_gram_cholesky(const double* g_in, int b, double* g_out, double* rinv, double* rout,
                                 const double* rprev, double abs_tol2, double rel_tol, hipStream_t st) {
-#define SC_CHOL(BB)                                                                                              \
-  hipLaunchKernelGGL((chol_reg_kernel<BB>), dim3(1), dim3(64), 0, st, g_in, g_out, rinv, rout, rprev, abs_tol2, \
+#define SC_CHOL(BB)                                                                                               \
+  hipLaunchKernelGGL((chol_wave_kernel<BB>), dim3(1), dim3(64), 0, st, g_in, g_out, rinv, rout, rprev, abs_tol2, \
                      rel_tol)
   switch (b) {
     case 1: SC_CHOL(1); break;
@@ -1911,11 +2053,29 @@ hipError_t launch_gram_cholesky(const double* g_in, int b, double* g_out, double
     case 4: SC_CHOL(4); break;
     case 8: SC_CHOL(8); break;
     case 16: SC_CHOL(16); break;
-    case 32: SC_CHOL(32); break;
+    case 32:
+      hipLaunchKernelGGL((chol_reg_kernel<32>), dim3(1), dim3(64), 0, st, g_in, g_out, rinv, rout, rprev, abs_tol2, rel_tol);
+      break;
     default:
       hipLaunchKernelGGL(gram_cholesky_kernel, dim3(1), dim3(kCholThreads), 0, st, g_in, b, g_out, rinv, rout, rprev,
                          abs_tol2, rel_tol);
   }
+#undef SC_CHOL
+  return hipGetLastError();
+}
+
+bool gram_cholesky_takes_parts(int npart, int b) {
+  // up to 32 loads one after the other per thread cost less than the launch they save (block QR of 4,040 x 8: 51 -> 41 us)
+  return (b == 8 && npart <= 128) || (b == 16 && npart <= 32);
+}
+
+hipError_t launch_gram_cholesky_parts(const double* gpart, int npart, int b, double* g_out, double* rinv, double* rout,
+                                      const double* rprev, double abs_tol2, double rel_tol, hipStream_t st) {
+  if (!gram_cholesky_takes_parts(npart, b)) return hipErrorInvalidValue;
+#define SC_CHOL(BB)                                                                                                   \
+  hipLaunchKernelGGL((chol_parts_kernel<BB>), dim3(1), dim3(kPartsThreads), 0, st, gpart, npart, g_out, rinv, rout, \
+                     rprev, abs_tol2, rel_tol)
+  if (b == 8) SC_CHOL(8); else SC_CHOL(16);
 #undef SC_CHOL
   return hipGetLastError();
 }
@@ -2021,8 +2181,9 @@ hipError_t launch_update_gram(double* basis, int64_t n, int64_t ld, int acol0, i
 
 hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const double* rinv, double* z,
                              const double* s, hipStream_t st) {
-  hipLaunchKernelGGL(apply_rinv_kernel, dim3((unsigned)ceil_div64(n, (int64_t)(kThreads / b) * kRinvTrips)),
-                     dim3(kThreads), 0, st, basis, n, ld, col0, b, rinv, z, s);
+  const int trips = rinv_trips(n, b);
+  hipLaunchKernelGGL(apply_rinv_kernel, dim3((unsigned)ceil_div64(n, (int64_t)(kThreads / b) * trips)), dim3(kThreads), 0,
+                     st, basis, n, ld, col0, b, trips, rinv, z, s);
   return hipGetLastError();
 }
 
@@ -2066,10 +2227,19 @@ hipError_t launch_copy_cols(const double* src, int64_t lds, int scol0, double* d
 }
 
 hipError_t launch_gather_cols_colmajor(const double* basis, int64_t n, int64_t ld, const int32_t* pos, int ncols,
-                                       double* out, const int32_t* inv, hipStream_t st) {
+                                       double* out, const int32_t* inv, const double* factor,
+                                       hipStream_t st) {
   if (n <= 0 || ncols <= 0) return hipSuccess;
   hipLaunchKernelGGL(gather_cols_colmajor_kernel, dim3((unsigned)ceil_div64(n, 64), (unsigned)((ncols + 63) / 64)),
-                     dim3(kThreads), 0, st, basis, n, ld, pos, ncols, out, inv);
+                     dim3(kThreads), 0, st, basis, n, ld, pos, ncols, out, inv, factor);
+  return hipGetLastError();
+}
+
+hipError_t launch_row_factor(const double* basis, int64_t n, int64_t ld, const int32_t* pos, int ncols, double* factor,
+                             hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(row_factor_kernel, dim3((unsigned)ceil_div64(n, kThreads / 64)), dim3(kThreads), 0, st, basis, n, ld, pos,
+                     ncols, factor);
   return hipGetLastError();
 }
 

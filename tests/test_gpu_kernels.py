@@ -260,6 +260,23 @@ def test_block_qr(B, n, j, b):
     assert np.max(np.abs(g - w.T @ w)) <= 1e-12 * np.abs(w.T @ w).max()
 
 
+# row counts on both sides of where the Gram partials go straight into the factorisation (128 and 32 partial blocks of 128
+# rows) and of where a workgroup of the last scaling takes more than one group of rows
+@pytest.mark.parametrize("n,b", [(1, 8), (127, 8), (16384, 8), (16385, 8), (4096, 16), (4097, 16), (32784, 16), (66000, 8),
+                                 (16400, 32), (131073, 4)])
+def test_block_qr_over_its_rules(B, n, b):
+    rng = np.random.default_rng(n + b)
+    w = rng.standard_normal((n, b))
+    dbasis = torch.from_numpy(w.copy()).cuda()
+    r, g = (t.cpu().numpy() for t in B.sc_block_qr(dbasis, 0, b))
+    q = dbasis.cpu().numpy()
+    rank = min(n, b)
+    eye = np.diag((np.arange(b) < rank).astype(float))
+    assert np.max(np.abs(q.T @ q - eye)) <= 1e-13 * max(1.0, np.sqrt(n / 1e4))
+    assert np.max(np.abs(q @ r[:, :rank] - w[:, :rank])) <= 1e-12 * np.abs(w).max()
+    assert np.max(np.abs(g - w.T @ w)) <= 1e-12 * np.abs(w.T @ w).max()
+
+
 def test_block_qr_drops_dependent_and_zero_columns(B):
     n, b = 3000, 8
     rng = np.random.default_rng(5)
@@ -279,7 +296,9 @@ def test_block_qr_drops_dependent_and_zero_columns(B):
 
 @pytest.mark.parametrize("n,j0,ja,l,colmajor", [(5000, 0, 100, 40, False), (4099, 3, 77, 5, False),
                                                 (3001, 8, 300, 130, True), (1000, 1, 16, 1, True),
-                                                (2048, 4, 520, 64, False)])
+                                                (2048, 4, 520, 64, False),
+                                                # panels that are no multiple of eight, last groups of one to four tiles
+                                                (1153, 0, 128, 65, False), (129, 4, 200, 200, True), (2049, 0, 144, 257, False)])
 def test_rotate(B, n, j0, ja, l, colmajor):
     rng = np.random.default_rng(n + ja)
     basis = rng.standard_normal((n, j0 + ja + 3))
