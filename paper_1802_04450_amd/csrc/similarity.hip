@@ -509,7 +509,8 @@ BucketPlan plan_buckets(int64_t total, int64_t n) {
   const int64_t nb = ((n - 1) >> p.shift) + 1;
   // more buckets than a workgroup has counters, or rows so long that ranking their entries (quadratic in the length) costs
   // more than the sort: 2,000 rows of 2,000 entries take 1,124 us in buckets and 390 us in the radix sort
-  p.use = nb <= kMaxBuckets && total <= nb * (kBucketRoom / 2) && total <= 256 * n;
+  // or so few entries that the room of the buckets (48 KB each) is out of proportion
+  p.use = nb <= kMaxBuckets && total <= nb * (kBucketRoom / 2) && total <= 256 * n && (nb <= 1024 || nb * 128 <= total);
   p.buckets = (int)nb;
   return p;
 }

@@ -119,7 +119,7 @@ def _csr_by_sorting(r, c, w, n, symmetrize):
 # buckets of one row and of many, a last bucket that is not full, rows at the limit of a bucket and beyond (radix sort),
 # rows too long for the ranking, more rows than there are buckets
 @pytest.mark.parametrize("n,ne,hub", [(1, 3, 0), (1024, 260, 0), (1025, 5000, 0), (4099, 200_000, 4000), (4099, 200_000, 5000),
-                                      (300, 90_000, 0), (70_001, 1_200_000, 0), (20_000_000, 3000, 0)])
+                                      (300, 90_000, 0), (70_001, 1_200_000, 0), (1_048_577, 3000, 0), (20_000_000, 3000, 0)])
 @pytest.mark.parametrize("symmetrize", [False, True])
 def test_coo_to_csr_over_its_ranges(B, n, ne, hub, symmetrize):
     rng = np.random.default_rng(n + ne + hub)
