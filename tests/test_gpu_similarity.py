@@ -191,3 +191,26 @@ def test_points_to_eigenpairs_chain(B):
     evals, evecs, code, _ = B.sc_laplacian_eigsh(rp2, c2, v2, 5, 1e-10)
     lam_full, _ = dense.full_spectrum(rp, c, v)
     assert code == 0 and np.max(np.abs(evals.cpu().numpy() - lam_full[:5])) <= 1e-8
+
+
+def test_a_full_block_cache_gives_way(B):
+    """Blocks of 0.7 to 0.8 GB fill the cache (4 GiB); a later call's 0.5 GB block then takes the place of the oldest, so
+    that more device memory is free after the call than before it (were it turned away, as much as before)."""
+    B.sc_release_cache()
+    gen = torch.Generator(device="cuda:0").manual_seed(1)
+
+    def free_after_call(ne):                   # 24 bytes of scratch an entry, and the sort's
+        r = torch.randint(0, 4000, (ne,), generator=gen, device="cuda:0", dtype=torch.int32)
+        rp, co, vo = B.sc_coo_to_csr(r, r.flip(0).contiguous(), torch.ones(ne, dtype=torch.float64, device="cuda:0"), 4000,
+                                     False)
+        assert int(rp[-1]) == ne
+        del r, co, vo
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        return torch.cuda.mem_get_info()[0]
+
+    for ne in (30_000_000, 31_000_000, 32_000_000, 33_000_000, 34_000_000):
+        before = free_after_call(ne)
+    after = free_after_call(20_000_000)
+    B.sc_release_cache()
+    assert after - before > 100 << 20
