@@ -357,7 +357,7 @@ typedef struct sc_kmeans_stats {
   int32_t timing;       /* INPUT: nonzero = bracket every distance-product launch with events on the stream and
                            report their summed duration below (the only field read on entry; all others are outputs) */
   double objective;     /* sum of squared distances of the points to the centres of their labels; -1 if the run stopped
-                           at max_iter (the centres moved after the last labelling) */
+                           at max_iter (the centres moved after the last labelling); NaN if a point has no label */
   double t_total;       /* seconds, host clock, whole call */
   double t_seed;        /* seconds spent in the seeding */
   double t_distance;    /* seconds, device clock, all labelling launches (V C^T and its arg-min); 0 unless timing was set */
@@ -384,7 +384,8 @@ int sc_kmeanspp(const double* points, int64_t ld, int32_t colmajor, int64_t n, i
  * One iteration: label of every point = the nearest centre, decided on |c_j|^2 - 2 <v_i, c_j> (the expanded form of
  * Section IV-C with the product V C^T on the fp64 matrix cores; the lowest index wins a tie); stop if no label
  * changed; else every centre becomes the mean of its points (points grouped by a sort on the labels; a centre without
- * points stays where it is).  At most max_iter (>= 1) labelling steps.
+ * points stays where it is).  At most max_iter (>= 1) labelling steps.  A point without a finite distance to any centre
+ * (a NaN coordinate) gets the label 2^31 - 1, which is no centre's, and moves none.
  * Returns SC_OK, or SC_NOT_CONVERGED if labels still changed in the last step (outputs hold the last labels and the
  * centres computed from them).
  */

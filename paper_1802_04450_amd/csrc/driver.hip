@@ -1961,7 +1961,7 @@ struct KMeans {
       part.alloc((size_t)np);
       std::vector<double> hp((size_t)np);
       if (converged || max_iter == 0 || iters == 0) {
-        HIP_TRY(launch_objective(x.p, ldx, d, n, labels, c, part.p, st));
+        HIP_TRY(launch_objective(x.p, ldx, d, n, labels, k, c, part.p, st));
         HIP_TRY(hipMemcpyAsync(hp.data(), part.p, sizeof(double) * np, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         double tot = 0.0;

@@ -264,9 +264,10 @@ size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k);
 hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, void* work,
                            size_t work_bytes, int32_t* chosen, hipStream_t st);
 hipError_t launch_gather_rows(const double* x, int64_t ldx, const int32_t* index, int k, double* c, hipStream_t st);
-// part[p], p < kmeans_objective_parts(): partial sums of |x_i - c_label(i)|^2 (add them in order on the host)
+// part[p], p < kmeans_objective_parts(): partial sums of |x_i - c_label(i)|^2 (add them in order on the host); NaN for a
+// point whose label is not in [0, k)
 int kmeans_objective_parts();
-hipError_t launch_objective(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, const double* c,
+hipError_t launch_objective(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, const double* c,
                             double* part, hipStream_t st);
 hipError_t launch_copy_rows(const double* src, int64_t lds, double* dst, int64_t ldd, int rows, int cols, hipStream_t st);
 

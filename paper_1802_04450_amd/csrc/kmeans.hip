@@ -576,15 +576,21 @@ __global__ __launch_bounds__(kT) void gather_rows_kernel(const double* __restric
 }
 
 // part[block] = sum over the block's points of |x_i - c_label(i)|^2; fixed assignment of points to threads and a
-// fixed tree, so the partial sums are reproducible.  Grid-stride over points, one thread per point and trip.
+// fixed tree, so the partial sums are reproducible.  Grid-stride over points, one thread per point and trip.  A label
+// outside [0, k), which a point without a finite distance has, names no row of c: that point's distance is NaN.
 __global__ __launch_bounds__(kT) void objective_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
-                                                       const int32_t* __restrict__ label, const double* __restrict__ c,
-                                                       double* __restrict__ part) {
+                                                       const int32_t* __restrict__ label, int k,
+                                                       const double* __restrict__ c, double* __restrict__ part) {
   __shared__ double red[kT];
   double acc = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT) {
     const double* xi = x + i * ldx;
-    const double* cj = c + (int64_t)label[i] * ldx;
+    const int32_t lab = label[i];
+    if ((uint32_t)lab >= (uint32_t)k) {
+      acc = __longlong_as_double(0x7ff8000000000000ll);
+      continue;
+    }
+    const double* cj = c + (int64_t)lab * ldx;
     double s2 = 0.0;
     for (int t = 0; t < d; ++t) {
       const double diff = xi[t] - cj[t];
@@ -783,10 +789,10 @@ hipError_t launch_gather_rows(const double* x, int64_t ldx, const int32_t* index
 
 int kmeans_objective_parts() { return 1024; }
 
-hipError_t launch_objective(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, const double* c,
+hipError_t launch_objective(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, const double* c,
                             double* part, hipStream_t st) {
-  hipLaunchKernelGGL(objective_kernel, dim3((unsigned)kmeans_objective_parts()), dim3(kT), 0, st, x, ldx, d, n, label, c,
-                     part);
+  hipLaunchKernelGGL(objective_kernel, dim3((unsigned)kmeans_objective_parts()), dim3(kT), 0, st, x, ldx, d, n, label, k,
+                     c, part);
   return hipGetLastError();
 }
 

@@ -219,3 +219,21 @@ def test_points_without_a_finite_distance_break_nothing(B):
     good = np.delete(np.arange(5000), bad)
     labels_ref, _ = okm.assign(x[good], init)
     np.testing.assert_array_equal(labels.cpu().numpy()[good], labels_ref)
+
+
+def test_a_converging_run_with_points_without_a_finite_distance(B):
+    """Points with a NaN coordinate have no label, move no centre and leave no objective; the rest is clustered as if they
+    were not there."""
+    x = _blobs(5000, 20, 6, seed=3)
+    bad = np.array([0, 17, 2048, 4999])
+    x[bad, [0, 3, 7, 19]] = np.nan
+    good = np.delete(np.arange(5000), bad)
+    init = x[good][okm.kmeanspp_indices(x[good], 6, 1)].copy()
+    labels_ref, cen_ref, iters_ref, _, conv_ref = okm.lloyd(x[good], init, 60)
+    assert conv_ref
+    labels, cen, code, st = B.sc_kmeans_lloyd(_dev(x), _dev(init), 60)
+    assert code == 0 and st["converged"] == 1 and st["iterations"] == iters_ref and np.isnan(st["objective"])
+    lg = labels.cpu().numpy()
+    np.testing.assert_array_equal(lg[good], labels_ref)
+    assert np.all(lg[bad] == 2 ** 31 - 1)
+    np.testing.assert_allclose(cen.cpu().numpy(), cen_ref, rtol=1e-11, atol=1e-12)
