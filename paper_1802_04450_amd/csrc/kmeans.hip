@@ -304,9 +304,11 @@ __global__ __launch_bounds__(kT) void centroid_finish_kernel(const double* __res
 // cannot shrink, by a bf16 copy of the points, a quarter of their bytes: with err_i >= |x_i - x~_i| (seed_copy_kernel), the
 // distance is at least |x~_i - x~_c| - err_i - err_c, and if that is no less than the distance kept, the minimum stands.
 // What is left is computed in fp64 as before, by 16 lanes per point, so the distances are the same to the last bit.  The
-// float distance of the copies is taken to be off by (d + 8) 2^-23 of itself, and the lower bound has to exceed the
-// distance kept by 1e-6 of it: more than the fp64 sums are off.  A NaN on the way fails the test and the point is
-// computed.
+// copies are scaled by a power of two that takes the largest coordinate into [1, 2) (seed_mean_kernel), so that their
+// float distance cannot overflow; it is taken to be off by (d + 8) 2^-23 of itself, which holds down to a square of
+// kScreenFloor (below, what single squares lose to the denormal numbers is no longer negligible), and the lower bound has
+// to exceed the distance kept by 1e-6 of it: more than the fp64 sums are off.  A NaN on the way fails the test and the
+// point is computed; so is every point of data that have no such scale (scale 0: copies of zeros).
 // Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 11.6 us with the copy, which an XCD's L2 keeps
 // its part of from draw to draw (21 MB in all); what is left is the chain centre, its row, the point's row.  (Leaving points out by the triangle inequality with a kept assignment did
 // not shorten the pass: it saves no load of the first row.)
@@ -317,22 +319,25 @@ constexpr int kExactLanes = 16;
 // draws: 1.64 against 1.88 ms; at 140,000 of 128, 128 draws: 2.82 against 2.64 ms).
 constexpr int64_t kDrawBlocks = 1800;
 
-// xh[i] = the centred point in bf16, padded with zeros to dpb coordinates (a multiple of 8); err[i] as above, rounded up.
-// mean: any point will do (exactness does not depend on it); a bf16 value is off by 2^-9 of its modulus at most, the
-// centring by 2^-52 of the coordinates.  8 lanes per point.
+constexpr float kScreenFloor = 1e-30f;
+
+// xh[i] = the centred and scaled point in bf16, padded with zeros to dpb coordinates (a multiple of 8); err[i] as above,
+// rounded up.  mean: any point will do (exactness does not depend on it); a bf16 value is off by 2^-9 of its modulus at
+// most, the centring by 2^-52 of the coordinates.  8 lanes per point.
 __global__ __launch_bounds__(kT) void seed_copy_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
-                                                       const double* __restrict__ mean, int dpb, __bf16* __restrict__ xh,
-                                                       float* __restrict__ err) {
+                                                       const double* __restrict__ mean, const double* __restrict__ scale,
+                                                       int dpb, __bf16* __restrict__ xh, float* __restrict__ err) {
   const int lane = threadIdx.x % 8;
   const int64_t i = (int64_t)blockIdx.x * (kT / 8) + threadIdx.x / 8;
   if (i >= n) return;  // uniform over the point's lanes
+  const double f = *scale;
   double moved = 0.0, size = 0.0;
   for (int c0 = lane * 8; c0 < dpb; c0 += 64) {
     union { __bf16 b[8]; uint4 v; } piece;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int t = c0 + q;
-      const double v = t < d ? x[i * ldx + t] : 0.0, m = t < d ? mean[t] : 0.0, y = v - m;
+      const double v = t < d ? x[i * ldx + t] * f : 0.0, m = t < d ? mean[t] * f : 0.0, y = v - m;
       piece.b[q] = (__bf16)(float)y;
       const double off = y - (double)(float)piece.b[q];
       moved += off * off;
@@ -345,22 +350,50 @@ __global__ __launch_bounds__(kT) void seed_copy_kernel(const double* __restrict_
     moved += __shfl_xor(moved, o, 8);
     size += __shfl_xor(size, o, 8);
   }
-  if (lane == 0) err[i] = (float)((sqrt(moved) + 4.5e-16 * sqrt(size)) * 1.00001);
+  if (lane == 0) err[i] = (float)((sqrt(moved) + 4.5e-16 * sqrt(size)) * 1.00001) + 1e-37f;
 }
 
-// mean[t] of the points, in two steps with a fixed order: part[b][t] over the points b, b + gridDim.x, ...
+// mean[t] of the points, in two steps with a fixed order: part[b][t] over the points b, b + gridDim.x, ..., top[b] = their
+// largest modulus of a coordinate
+constexpr int kSeedParts = kT;
 __global__ __launch_bounds__(kT) void seed_sum_kernel(const double* __restrict__ x, int64_t ldx, int64_t n,
-                                                      double* __restrict__ part) {
+                                                      double* __restrict__ part, double* __restrict__ top) {
+  __shared__ double tops[kT];
+  double most = 0.0;
   for (int t = threadIdx.x; t < ldx; t += kT) {
     double acc = 0.0;
 #pragma unroll 8
-    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) acc += x[i * ldx + t];
+    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+      const double v = x[i * ldx + t];
+      acc += v;
+      most = fmax(most, fabs(v));
+    }
     part[(int64_t)blockIdx.x * ldx + t] = acc;
   }
+  tops[threadIdx.x] = most;
+  __syncthreads();
+  for (int o = kT / 2; o > 0; o >>= 1) {
+    if (threadIdx.x < o) tops[threadIdx.x] = fmax(tops[threadIdx.x], tops[threadIdx.x + o]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) top[blockIdx.x] = tops[0];
 }
 
-__global__ __launch_bounds__(kT) void seed_mean_kernel(const double* __restrict__ part, int parts, int64_t ldx, int64_t n,
-                                                       double* __restrict__ mean) {
+// the second step; *scale = the power of two that takes the largest modulus into [1, 2), 0 where the squares of such
+// numbers leave the range of a double
+__global__ __launch_bounds__(kT) void seed_mean_kernel(const double* __restrict__ part, const double* __restrict__ top,
+                                                       int parts, int64_t ldx, int64_t n, double* __restrict__ mean,
+                                                       double* __restrict__ scale) {
+  if (blockIdx.x == 0) {
+    __shared__ double tops[kT];
+    tops[threadIdx.x] = top[threadIdx.x];
+    __syncthreads();
+    for (int o = kT / 2; o > 0; o >>= 1) {
+      if (threadIdx.x < o) tops[threadIdx.x] = fmax(tops[threadIdx.x], tops[threadIdx.x + o]);
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) *scale = tops[0] > 1e-100 && tops[0] < 1e100 ? ldexp(1.0, -ilogb(tops[0])) : 0.0;
+  }
   const int t = blockIdx.x * kT + threadIdx.x;
   if (t >= ldx) return;
   double acc = 0.0;
@@ -476,7 +509,8 @@ __global__ __launch_bounds__(kSelectThreads) void seed_select_kernel(const doubl
 template <bool SCREEN, bool DRAW>
 __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
                                                            const __bf16* __restrict__ xh, int dpb,
-                                                           const float* __restrict__ err, double u,
+                                                           const float* __restrict__ err,
+                                                           const double* __restrict__ scale, double u,
                                                            int32_t* __restrict__ centre, int first,
                                                            const double* __restrict__ bsum_in, int64_t nb,
                                                            const double* __restrict__ dist2_in,
@@ -518,7 +552,8 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
     for (int o = SL / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, SL);
     if (sl == 0 && p < here) {
       const double low = sqrt((double)acc) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)err[i] - (double)err[c];
-      const bool stands = low > 0.0 && low * low >= pts[p] * (1.0 + 1e-6);
+      const double f = *scale;
+      const bool stands = acc >= kScreenFloor && low > 0.0 && low * low >= pts[p] * (f * f) * (1.0 + 1e-6);
       if (!stands) todo[atomicAdd(&ntodo, 1)] = p;
     }
     __syncthreads();
@@ -723,16 +758,16 @@ namespace {
 // the L2s and there are draws to spread that over: 100,000 x 100, 100 draws 2.04 -> 1.64 ms, 142,541 x 500, 500 draws
 // 60 -> 27 ms; 140,000 x 8, 100 draws 1.47 -> 1.44 ms, 50,000 x 64, 16 draws 0.19 -> 0.23 ms.
 bool seed_screened(int64_t n, int d, int k) { return n * (int64_t)d >= 4000000 && k >= 32; }
-constexpr int kSeedParts = 256;
 inline int seed_dpb(int d) { return (d + 7) / 8 * 8; }
 
 }  // namespace
 
 size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k) {
-  // two of (dist2[n] | bsum[ceil(n / 64)])  and, with the screen,  mean[ldx] | sums[kSeedParts][ldx] | err[n] | xh[n][dpb]
+  // two of (dist2[n] | bsum[ceil(n / 64)])  and, with the screen,
+  // mean[ldx] | sums[kSeedParts][ldx] | tops[kSeedParts] | scale | err[n] | xh[n][dpb]
   const size_t nb = (size_t)((n + kSeedPoints - 1) / kSeedPoints);
   size_t bytes = 2 * ((size_t)n + nb) * 8 + 1024;
-  if (seed_screened(n, d, k)) bytes += (size_t)ldx * 8 * (kSeedParts + 1) + (size_t)n * (4 + 2 * (size_t)seed_dpb(d)) + 1024;
+  if (seed_screened(n, d, k)) bytes += (size_t)(ldx + 1) * 8 * (kSeedParts + 1) + (size_t)n * (4 + 2 * (size_t)seed_dpb(d)) + 1024;
   return bytes;
 }
 
@@ -746,7 +781,9 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
   double* dist2[2] = {static_cast<double*>(work), static_cast<double*>(work) + n + nb};
   double* mean = dist2[1] + n + nb;
   double* sums = mean + ldx;
-  float* err = reinterpret_cast<float*>(sums + (size_t)kSeedParts * ldx);
+  double* tops = sums + (size_t)kSeedParts * ldx;
+  double* scale = tops + kSeedParts;
+  float* err = reinterpret_cast<float*>(scale + 1);
   __bf16* xh = reinterpret_cast<__bf16*>(((uintptr_t)(err + n) + 15) / 16 * 16);
   const int dpb = seed_dpb(d);
   const bool screened = seed_screened(n, d, k), draws = nb <= kDrawBlocks;
@@ -754,9 +791,11 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
   first = first < n - 1 ? first : n - 1;
   hipLaunchKernelGGL(iota_fill_kernel, dim3(1), dim3(kT), 0, st, chosen, 1, (int32_t)first, 0);
   if (screened) {
-    hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums);
-    hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, kSeedParts, ldx, n, mean);
-    hipLaunchKernelGGL(seed_copy_kernel, dim3(blocks(n * 8)), dim3(kT), 0, st, x, ldx, d, n, mean, dpb, xh, err);
+    hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums, tops);
+    hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, tops, kSeedParts, ldx, n, mean,
+                       scale);
+    hipLaunchKernelGGL(seed_copy_kernel, dim3(blocks(n * 8)), dim3(kT), 0, st, x, ldx, d, n, mean, scale, dpb, xh,
+                       err);
   }
   int at = 0;  // the buffer with the distances to the centres so far
   auto pass = [&](int i) {  // the distances to centre i - 1
@@ -765,7 +804,7 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
     if (i > 1) at ^= 1;
 #define SC_SEED(SCR, DRW)                                                                                               \
   hipLaunchKernelGGL((seed_distance_kernel<SCR, DRW>), dim3((unsigned)nb), dim3(kT), 0, st, x, ldx, d, n, xh, dpb, err, \
-                     u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], dist2[at] + n)
+                     scale, u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], dist2[at] + n)
     if (screened && i > 1) {
       if (draw) SC_SEED(true, true); else SC_SEED(true, false);
     } else {

@@ -188,15 +188,22 @@ def test_update_over_its_ranges(B, n, d, k):
     np.testing.assert_allclose(cen.cpu().numpy()[same], cen_ref[same], rtol=0, atol=6.0 * n * 2.0 ** -53)
 
 
-# the seeding with the bf16 copy of the points: with and without its own draw, a common offset, equal points
+# the seeding with the bf16 copy of the points: with and without its own draw, a common offset, equal points, coordinates
+# whose squares leave the range of a float at either end, or of which no scale is made
 @pytest.mark.parametrize("n,d,k,kind", [(62501, 64, 33, "blobs"), (120003, 34, 40, "blobs"), (45001, 90, 32, "offset"),
-                                        (40001, 101, 35, "equal")])
+                                        (40001, 101, 35, "equal"), (62501, 64, 40, 1e20), (62501, 64, 40, 1e19),
+                                        (120003, 34, 40, 1e25), (62501, 64, 40, 3e-23), (62501, 64, 40, 1e-21),
+                                        (62501, 64, 40, 1e-30), (62501, 64, 33, 1e120), (62501, 64, 33, "two scales")])
 def test_screened_seeding_equals_plain_distances(B, n, d, k, kind):
     x = _blobs(n, d, 25, seed=n, spread=0.3)
     if kind == "offset":
         x += 1e7
     elif kind == "equal":
         x[1:] = x[0] + np.repeat(np.arange(1.0, n)[:, None] % 7, d, axis=1)
+    elif kind == "two scales":       # one point far away: the others' squares are near the smallest float after scaling
+        x[1:] *= 1e-20
+    elif isinstance(kind, float):
+        x *= kind
     chosen = B.sc_kmeanspp(_dev(x), k, 5)[0].cpu().numpy().astype(np.int64)
     # draw by draw from the chosen points themselves: the index must be where the prefix sum passes u * total, to the
     # rounding of sums of n numbers
