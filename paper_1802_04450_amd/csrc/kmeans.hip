@@ -732,8 +732,9 @@ hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n
     char* temp = reinterpret_cast<char*>(((uintptr_t)(ident + n) + 255) / 256 * 256);
     size_t sb = label_sort_bytes(n);
     hipLaunchKernelGGL(iota_fill_kernel, dim3(blocks(n)), dim3(kT), 0, st, ident, n, 0, 1);
+    // one value more than there are clusters: a label outside [0, k), all ones in these bits, comes after them all
     const hipError_t e = rocprim::radix_sort_pairs(temp, sb, label, sorted_label, ident, member, (size_t)n, 0u,
-                                                   (unsigned)bits_for(k), st);
+                                                   (unsigned)bits_for((int64_t)k + 1), st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(cluster_starts_kernel, dim3(blocks(k + 1)), dim3(kT), 0, st, sorted_label, n, k, start);
   }

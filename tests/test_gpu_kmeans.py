@@ -244,3 +244,21 @@ def test_a_converging_run_with_points_without_a_finite_distance(B):
     np.testing.assert_array_equal(lg[good], labels_ref)
     assert np.all(lg[bad] == 2 ** 31 - 1)
     np.testing.assert_allclose(cen.cpu().numpy(), cen_ref, rtol=1e-11, atol=1e-12)
+
+
+# both ways of grouping the points, with numbers of clusters on both sides of a power of two
+@pytest.mark.parametrize("k", [512, 1023, 1024, 1025, 2047, 2048, 2049, 4096])
+def test_points_without_a_label_belong_to_no_cluster(B, k):
+    n, d = 9000, 5
+    x = _blobs(n, d, 30, seed=k, spread=0.5)
+    bad = np.array([0, 17, 2048, 4095, 8999])
+    good = np.delete(np.arange(n), bad)
+    init = x[good][np.random.default_rng(k).choice(good.size, k, replace=False)].copy()
+    x[bad, 2] = np.nan
+    labels_ref, _ = okm.assign(x[good], init)
+    cen_ref = okm.update_centroids(x[good], labels_ref, init)
+    labels, cen, _, _ = B.sc_kmeans_lloyd(_dev(x), _dev(init), 1)
+    lg = labels.cpu().numpy()
+    assert np.all(lg[bad] == 2 ** 31 - 1)
+    np.testing.assert_array_equal(lg[good], labels_ref)
+    np.testing.assert_allclose(cen.cpu().numpy(), cen_ref, rtol=0, atol=6.0 * n * 2.0 ** -53)
