@@ -2721,7 +2721,7 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
         DevBuf<int> bad;
         PinnedBuf<int> hbad;
         bad.alloc(2);
-        hbad.alloc(2);
+        hbad.alloc(1);
         HIP_TRY(launch_fill_int32(bad.p, 2, 0, 0, c->st));
         if (c->measure != 2) {
           mean.alloc((size_t)c->n);
@@ -2733,12 +2733,10 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
           work.alloc(wb);
           HIP_TRY(launch_edge_similarity_buckets(c->x, c->ldx, c->d, c->u, c->v, c->ne, c->measure, c->sigma, mean.p,
                                                  norm.p, c->n, work.p, wb, bad.p, bad.p + 1, c->val, c->st));
-          HIP_TRY(hipMemcpyAsync(hbad.p, bad.p, 2 * sizeof(int), hipMemcpyDeviceToHost, c->st));
-          HIP_TRY(hipStreamSynchronize(c->st));
-          if (!hbad.p[1]) return hbad.p[0] ? SC_ECSR : SC_OK;
+        } else {
+          HIP_TRY(launch_edge_similarity(c->x, c->ldx, c->d, c->u, c->v, c->ne, c->measure, c->sigma, mean.p, norm.p,
+                                         c->n, bad.p, c->val, c->st));
         }
-        HIP_TRY(launch_edge_similarity(c->x, c->ldx, c->d, c->u, c->v, c->ne, c->measure, c->sigma, mean.p, norm.p,
-                                       c->n, bad.p, c->val, c->st));
         HIP_TRY(hipMemcpyAsync(hbad.p, bad.p, sizeof(int), hipMemcpyDeviceToHost, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
         return *hbad.p ? SC_ECSR : SC_OK;

@@ -280,13 +280,13 @@ hipError_t launch_row_stats(const double* x, int64_t ldx, int64_t n, int d, int 
 hipError_t launch_edge_similarity(const double* x, int64_t ldx, int d, const int32_t* eu, const int32_t* ev,
                                   int64_t nedges, int measure, double sigma, const double* mean, const double* norm,
                                   int64_t n, int* bad, double* val, hipStream_t st);
-// The same through buckets of rows: 0 bytes where that does not pay.  over: device int, set to 1 if a bucket overflowed
-// (some values are then missing: call launch_edge_similarity).
+// The same through buckets of rows: 0 bytes of work where that does not pay.  nrest: device int, 0 on entry, the number of
+// pairs that had no room in their bucket or an index out of range afterwards (they are done like the others).
 size_t edge_buckets_workspace(int64_t n, int d, int64_t nedges);
 hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, const int32_t* eu, const int32_t* ev,
                                           int64_t nedges, int measure, double sigma, const double* mean,
                                           const double* norm, int64_t n, void* work, size_t work_bytes, int* bad,
-                                          int* over, double* val, hipStream_t st);
+                                          int32_t* nrest, double* val, hipStream_t st);
 // ---- k-nearest-neighbour graph (Section III-A; knn.hip) -------------------------------------------------------
 // Exact Euclidean k nearest neighbours of every row of x (n x d, leading dimension ldx) other than the row itself:
 // idx_out[i*k + a] / dist_out[i*k + a] = index / distance of the a-th nearest, nearest first, equal distances by

@@ -38,7 +38,8 @@ __device__ __forceinline__ double group_sum(double v) {
 // Bucket b takes the entries of the rows [b << shift, (b + 1) << shift) into slots b * kBucketRoom .. of `slots`, in no
 // particular order: a workgroup counts its kPartEntries entries per bucket in LDS, reserves that many slots of every
 // bucket with one atomic addition and writes.  fill[b] ends up as the bucket's number of entries, more than kBucketRoom if
-// they did not fit (what does not fit is dropped: the caller looks at the counts).
+// they did not fit: what does not fit, and entries with an index out of range, go to the list `rest` (room for all of
+// them, *nrest of them) or, where that is null, are dropped and the caller looks at the counts.
 constexpr int kBucketRoom = 4096;
 constexpr int kMaxBuckets = 16384;
 constexpr int kPartThreads = 1024;
@@ -46,17 +47,20 @@ constexpr int kPartTrips = 16;
 constexpr int kPartEntries = kPartThreads * kPartTrips;
 
 // The e-th entry is (row[e], col[e]) with payload e; with MIRROR the same again as (col[e], row[e]) with payload
-// nnz_in + e unless the two are equal.  An index outside [0, n) sets *bad; such an entry is left out.
+// nnz_in + e unless the two are equal (rest is null then).  An index outside [0, n) sets *bad.
 template <bool MIRROR>
 __global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* __restrict__ row,
                                                                  const int32_t* __restrict__ col, int64_t nnz_in, int64_t n,
                                                                  int shift, int nbuckets, int32_t* __restrict__ fill,
                                                                  uint2* __restrict__ slots, uint32_t* __restrict__ slot_row,
+                                                                 uint32_t* __restrict__ rest, int32_t* __restrict__ nrest,
                                                                  int* __restrict__ bad) {
   __shared__ int32_t count[kMaxBuckets];
+  __shared__ int32_t left, left0;
   const int64_t e0 = (int64_t)blockIdx.x * (MIRROR ? kPartEntries / 2 : kPartEntries);
   constexpr int TR = MIRROR ? kPartTrips / 2 : kPartTrips;
   for (int b = threadIdx.x; b < nbuckets; b += kPartThreads) count[b] = 0;
+  if (threadIdx.x == 0) left = 0;
   __syncthreads();
   int32_t r[TR], c[TR];
 #pragma unroll
@@ -88,19 +92,32 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* 
 #pragma unroll
   for (int u = 0; u < TR; ++u) {
     const int64_t e = e0 + u * kPartThreads + threadIdx.x;
-    if (e >= nnz_in || r[u] < 0) continue;
-    const int at = atomicAdd(&count[r[u] >> shift], 1);
+    if (e >= nnz_in) continue;
+    const int at = r[u] < 0 ? kBucketRoom : atomicAdd(&count[r[u] >> shift], 1);
     if (at < kBucketRoom) {
       slots[(int64_t)(r[u] >> shift) * kBucketRoom + at] = make_uint2((uint32_t)c[u], (uint32_t)e);
       slot_row[(int64_t)(r[u] >> shift) * kBucketRoom + at] = (uint32_t)r[u];
+    } else if (rest) {
+      c[u] = -2 - atomicAdd(&left, 1);  // its place among the workgroup's
     }
-    if (MIRROR && r[u] != c[u]) {
+    if (MIRROR && r[u] >= 0 && r[u] != c[u]) {
       const int am = atomicAdd(&count[c[u] >> shift], 1);
       if (am < kBucketRoom) {
         slots[(int64_t)(c[u] >> shift) * kBucketRoom + am] = make_uint2((uint32_t)r[u], (uint32_t)(nnz_in + e));
         slot_row[(int64_t)(c[u] >> shift) * kBucketRoom + am] = (uint32_t)c[u];
       }
     }
+  }
+  if (!rest) return;  // uniform
+  // one addition to *nrest per workgroup (one per wave, 60,000 of them, took 600 us)
+  __syncthreads();
+  if (left == 0) return;  // uniform
+  if (threadIdx.x == 0) left0 = atomicAdd(nrest, left);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < TR; ++u) {
+    const int64_t e = e0 + u * kPartThreads + threadIdx.x;
+    if (e < nnz_in && c[u] <= -2) rest[left0 + (-2 - c[u])] = (uint32_t)e;
   }
 }
 
@@ -240,17 +257,12 @@ __global__ __launch_bounds__(kT) void row_stats_kernel(const double* __restrict_
 
 // measure 0 / 1: val[e] = <x_u - m_u, x_v - m_v> / (norm_u norm_v)  (m = 0 for the cosine measure)
 // measure 2:     val[e] = exp(-|x_u - x_v|^2 / (2 sigma^2))
-__global__ __launch_bounds__(kT) void edge_similarity_kernel(const double* __restrict__ x, int64_t ldx, int d,
-                                                             const int32_t* __restrict__ eu,
-                                                             const int32_t* __restrict__ ev, int64_t nedges,
-                                                             int measure, double inv_two_sigma2,
-                                                             const double* __restrict__ mean,
-                                                             const double* __restrict__ norm, int vec_ok,
-                                                             int64_t n, int* __restrict__ bad,
-                                                             double* __restrict__ val) {
-  const int lane = threadIdx.x % kL;
-  const int64_t e = (int64_t)blockIdx.x * (kT / kL) + threadIdx.x / kL;
-  if (e >= nedges) return;
+// By the 16 lanes of one pair.
+__device__ __forceinline__ void edge_pair(const double* __restrict__ x, int64_t ldx, int d, const int32_t* __restrict__ eu,
+                                          const int32_t* __restrict__ ev, int64_t e, int lane, int measure,
+                                          double inv_two_sigma2, const double* __restrict__ mean,
+                                          const double* __restrict__ norm, int vec_ok, int64_t n, int* __restrict__ bad,
+                                          double* __restrict__ val) {
   const int64_t u = eu[e], v = ev[e];
   if (u < 0 || u >= n || v < 0 || v >= n) {  // uniform over the edge's lanes; no row is touched
     if (lane == 0) {
@@ -297,29 +309,59 @@ __global__ __launch_bounds__(kT) void edge_similarity_kernel(const double* __res
   if (lane == 0) val[e] = measure == 2 ? exp(-acc * inv_two_sigma2) : acc / (norm[u] * norm[v]);
 }
 
+// every pair; an index out of range gives NaN and sets *bad
+__global__ __launch_bounds__(kT) void edge_similarity_kernel(const double* __restrict__ x, int64_t ldx, int d,
+                                                             const int32_t* __restrict__ eu,
+                                                             const int32_t* __restrict__ ev, int64_t nedges,
+                                                             int measure, double inv_two_sigma2,
+                                                             const double* __restrict__ mean,
+                                                             const double* __restrict__ norm, int vec_ok,
+                                                             int64_t n, int* __restrict__ bad,
+                                                             double* __restrict__ val) {
+  const int64_t e = (int64_t)blockIdx.x * (kT / kL) + threadIdx.x / kL;
+  if (e >= nedges) return;
+  edge_pair(x, ldx, d, eu, ev, e, threadIdx.x % kL, measure, inv_two_sigma2, mean, norm, vec_ok, n, bad, val);
+}
+
+// the pairs list[0 .. *count - 1]: those that the buckets below have no room for, and those with an index out of range
+__global__ __launch_bounds__(kT) void edge_list_kernel(const double* __restrict__ x, int64_t ldx, int d,
+                                                       const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
+                                                       const uint32_t* __restrict__ list,
+                                                       const int32_t* __restrict__ count, int measure,
+                                                       double inv_two_sigma2, const double* __restrict__ mean,
+                                                       const double* __restrict__ norm, int vec_ok, int64_t n,
+                                                       int* __restrict__ bad, double* __restrict__ val) {
+  const int64_t here = *count;
+  for (int64_t p = (int64_t)blockIdx.x * (kT / kL) + threadIdx.x / kL; p < here; p += (int64_t)gridDim.x * (kT / kL))
+    edge_pair(x, ldx, d, eu, ev, list[p], threadIdx.x % kL, measure, inv_two_sigma2, mean, norm, vec_ok, n, bad, val);
+}
+
 // The same for data that do not fit the L2s, bucket by bucket of first rows: a workgroup keeps the rows of its bucket in
 // LDS and reads the second rows from memory; the buckets of an XCD are neighbours, so that where pairs join rows that are
 // near one another (a voxel grid, a neighbour list after a renumbering) the second rows come from its L2.  A pair's value
 // is formed by the same lanes in the same order as above.  3.8 M pairs of 142,541 rows of 90 doubles, listed offset by
 // offset: 683 us with every row read from the Infinity Cache once per pair (7.4 TB/s), 430 us here with the 34 us of the
 // partition.
+// An XCD gets kRuns runs of neighbours from all over the rows, because first rows need not be spread evenly: with first
+// rows drawn by a power law (half of the pairs in an eighth of the rows) one run per XCD took 1,880 us for the same number
+// of pairs, 4 runs 1,000, 8 runs 865, 16 runs 775, and no buckets 945.  Runs cost reuse where they end: 16 of them 480 us
+// on the case above as with one, 100,000 rows 380 for 365 us (without buckets 565).  One counter of taken buckets per XCD,
+// so that idle XCDs take over what is left, cost 200 us.
+constexpr int kRuns = 16;
+__host__ __device__ inline int edge_run(int nbuckets) { return (nbuckets + 8 * kRuns - 1) / (8 * kRuns); }
 __global__ __launch_bounds__(kT) void edge_bucket_kernel(const double* __restrict__ x, int64_t ldx, int d, int shift,
                                                          int nbuckets, const int32_t* __restrict__ fill,
                                                          const uint2* __restrict__ slots,
                                                          const uint32_t* __restrict__ slot_row, int measure,
                                                          double inv_two_sigma2, const double* __restrict__ mean,
                                                          const double* __restrict__ norm, int vec_ok, int64_t n,
-                                                         int* __restrict__ over, double* __restrict__ val) {
+                                                         double* __restrict__ val) {
   extern __shared__ double rows[];  // (1 << shift) x dl, then means and norms
-  const int per = (nbuckets + 7) / 8;
-  const int b = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-  if ((int)(blockIdx.x / 8) >= per || b >= nbuckets) return;  // uniform
-  const int count = fill[b];
-  if (count > kBucketRoom) {  // uniform
-    if (threadIdx.x == 0) *over = 1;
-    return;
-  }
-  if (count == 0) return;
+  const int t = (int)(blockIdx.x / 8), run = edge_run(nbuckets);
+  const int b = (t / run * 8 + (int)(blockIdx.x % 8)) * run + t % run;
+  if (b >= nbuckets) return;  // uniform
+  const int count = fill[b] < kBucketRoom ? fill[b] : kBucketRoom;
+  if (count == 0) return;  // uniform
   const int dl = (d + 1) & ~1, nr = 1 << shift;
   const int64_t row0 = (int64_t)b << shift;
   double* mrow = rows + (size_t)nr * dl;
@@ -403,17 +445,6 @@ __global__ __launch_bounds__(kT) void edge_bucket_kernel(const double* __restric
       if (lane == 0 && p0 + q * (kT / kL) < count)
         val[out[q]] = measure == 2 ? exp(-tot * inv_two_sigma2) : tot / (nrow[ru[q]] * norm[vi[q]]);
     }
-  }
-}
-
-// the pairs with an index out of range: NaN
-__global__ __launch_bounds__(kT) void edge_invalid_kernel(const int32_t* __restrict__ eu, const int32_t* __restrict__ ev,
-                                                          int64_t nedges, int64_t n, const int* __restrict__ bad,
-                                                          double* __restrict__ val) {
-  if (*bad == 0) return;  // uniform over the grid
-  for (int64_t e = (int64_t)blockIdx.x * kT + threadIdx.x; e < nedges; e += (int64_t)gridDim.x * kT) {
-    const int64_t u = eu[e], v = ev[e];
-    if (u < 0 || u >= n || v < 0 || v >= n) val[e] = __longlong_as_double(0x7ff8000000000000ll);
   }
 }
 
@@ -560,10 +591,10 @@ hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val,
     const dim3 grid((unsigned)((nnz_in + per - 1) / per));
     if (symmetrize)
       hipLaunchKernelGGL((partition_kernel<true>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
-                         fill, slots, slot_row, bad);
+                         fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
     else
       hipLaunchKernelGGL((partition_kernel<false>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
-                         fill, slots, slot_row, bad);
+                         fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
     hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(kPartThreads), 0, st, fill, p.buckets, first, bad + 1);
     hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)p.buckets), dim3(kT), 0, st, fill, first, bad + 1, p.shift, n,
                        nnz_in, slots, slot_row, val, rowptr_out, col_out, val_out);
@@ -615,28 +646,32 @@ BucketPlan plan_edge_buckets(int64_t n, int d, int64_t nedges) {
 
 size_t edge_buckets_workspace(int64_t n, int d, int64_t nedges) {
   const BucketPlan p = plan_edge_buckets(n, d, nedges);
-  return p.use ? up256((size_t)p.buckets * 4) + (size_t)p.buckets * kBucketRoom * 12 + 1024 : 0;
+  // fill[buckets] | slots | slot_row | rest[nedges]
+  return p.use ? up256((size_t)p.buckets * 4) + (size_t)p.buckets * kBucketRoom * 12 + (size_t)nedges * 4 + 1024 : 0;
 }
 
 hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, const int32_t* eu, const int32_t* ev,
                                           int64_t nedges, int measure, double sigma, const double* mean,
                                           const double* norm, int64_t n, void* work, size_t work_bytes, int* bad,
-                                          int* over, double* val, hipStream_t st) {
+                                          int32_t* nrest, double* val, hipStream_t st) {
   const BucketPlan p = plan_edge_buckets(n, d, nedges);
   if (!p.use || work_bytes < edge_buckets_workspace(n, d, nedges)) return hipErrorInvalidValue;
   int32_t* fill = static_cast<int32_t*>(work);
   uint2* slots = reinterpret_cast<uint2*>(static_cast<char*>(work) + up256((size_t)p.buckets * 4));
   uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + (size_t)p.buckets * kBucketRoom);
+  uint32_t* rest = slot_row + (size_t)p.buckets * kBucketRoom;
   const hipError_t e = launch_fill_int32(fill, p.buckets, 0, 0, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((partition_kernel<false>), dim3((unsigned)((nedges + kPartEntries - 1) / kPartEntries)),
-                     dim3(kPartThreads), 0, st, eu, ev, nedges, n, p.shift, p.buckets, fill, slots, slot_row, bad);
+                     dim3(kPartThreads), 0, st, eu, ev, nedges, n, p.shift, p.buckets, fill, slots, slot_row, rest, nrest,
+                     bad);
   const int vec_ok = (ldx % 2 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   const double inv = measure == 2 ? 1.0 / (2.0 * sigma * sigma) : 0.0;
   const size_t lds = ((size_t)1 << p.shift) * (size_t)(((d + 1) & ~1) + 2) * 8;
-  hipLaunchKernelGGL(edge_bucket_kernel, dim3((unsigned)((p.buckets + 7) / 8 * 8)), dim3(kT), lds, st, x, ldx, d, p.shift,
-                     p.buckets, fill, slots, slot_row, measure, inv, mean, norm, vec_ok, n, over, val);
-  hipLaunchKernelGGL(edge_invalid_kernel, dim3(512), dim3(kT), 0, st, eu, ev, nedges, n, bad, val);
+  hipLaunchKernelGGL(edge_bucket_kernel, dim3((unsigned)(8 * kRuns * edge_run(p.buckets))), dim3(kT), lds, st, x, ldx, d,
+                     p.shift, p.buckets, fill, slots, slot_row, measure, inv, mean, norm, vec_ok, n, val);
+  hipLaunchKernelGGL(edge_list_kernel, dim3(2048), dim3(kT), 0, st, x, ldx, d, eu, ev, rest, nrest, measure, inv, mean, norm,
+                     vec_ok, n, bad, val);
   return hipGetLastError();
 }
 

@@ -135,17 +135,21 @@ def test_coo_to_csr_over_its_ranges(B, n, ne, hub, symmetrize):
 
 
 # the bucketed pair kernel (data of 40 MB and more, eight pairs a row): against the oracle, with a ragged last bucket, odd
-# dimensions and strides (scalar loads), an index out of range, and one row in more pairs than a bucket holds
+# dimensions and strides (scalar loads), an index out of range, one row in more pairs than a bucket holds, first rows by a
+# power law (many buckets that are too small beside many that are empty), and both with indices out of range
 @pytest.mark.parametrize("d,ldx,measure,twist", [(90, 90, 0, ""), (85, 85, 1, ""), (128, 129, 2, ""), (380, 380, 0, ""),
-                                                 (90, 90, 0, "bad"), (100, 100, 1, "hub")])
+                                                 (90, 90, 0, "bad"), (100, 100, 1, "hub"), (90, 90, 2, "power"),
+                                                 (101, 102, 0, "power bad"), (100, 100, 1, "hub bad")])
 def test_bucketed_edge_similarity_matches_oracle(B, d, ldx, measure, twist):
     n = 5_000_000 // d + 37
     rng = np.random.default_rng(d)
     big = rng.normal(size=(n, ldx)) + 1.5
     u, v = _edges(n, 8 * n + 11, 9)
-    if twist == "hub":
+    if "hub" in twist:
         u[::8] = 12
-    if twist == "bad":
+    if "power" in twist:
+        u[:] = np.minimum((rng.random(u.size) ** 4 * n).astype(u.dtype), n - 1)
+    if "bad" in twist:
         u[1234], v[99] = n, -1
     x = _dev(big, torch.float64)
     val = torch.zeros(u.size, dtype=torch.float64, device="cuda:0")
@@ -154,8 +158,8 @@ def test_bucketed_edge_similarity_matches_oracle(B, d, ldx, measure, twist):
     code = B.lib().sc_edge_similarity(x.data_ptr(), ldx, n, d, du.data_ptr(), dv.data_ptr(), u.size, measure, float(np.sqrt(d)),
                                       val.data_ptr(), st)
     got, ok = val.cpu().numpy(), np.ones(u.size, dtype=bool)
-    assert code == (B.SC_ECSR if twist == "bad" else 0)
-    if twist == "bad":
+    assert code == (B.SC_ECSR if "bad" in twist else 0)
+    if "bad" in twist:
         ok[[1234, 99]] = False
         assert np.isnan(got[~ok]).all()
     ref = osim.edge_similarity(big[:, :d], u[ok], v[ok], measure, float(np.sqrt(d)))
