@@ -408,6 +408,8 @@ int sc_kmeans(const double* points, int64_t ld, int32_t colmajor, int64_t n, int
  *   val_out  device fp64[nedges]; a constant row gives NaN under the first two measures (0/0), as the definition does
  * Returns SC_ECSR if an index is outside [0, n) (that edge's value is NaN, no row was read for it), SC_EDOMAIN for
  * d < 1, ldx < d, an unknown measure or sigma <= 0.
+ * Device scratch of the call: 16 n bytes (none for the third measure), and for n d >= 5,000,000 with eight pairs a row or
+ * more up to 100 * nedges + 2^26 + 2^17 bytes more; where these cannot be had the call does without them, at less speed.
  */
 #define SC_SIM_CROSS_CORRELATION 0
 #define SC_SIM_COSINE 1

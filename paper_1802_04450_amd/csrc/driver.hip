@@ -239,18 +239,28 @@ struct DevBuf {
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
   void alloc(size_t count) {
+    if (!try_alloc(count)) SC_THROW(SC_ENOMEM);
+  }
+  // false: there is no such memory (a caller with a way that needs less then takes that)
+  bool try_alloc(size_t count) {
     release();
     if (count == 0) count = 1;
     void* q = nullptr;
     if (tl_arena) {
       q = tl_arena->get(count * sizeof(T));
-      if (!q) SC_THROW(SC_ENOMEM);  // the caller's workspace is too small
+      if (!q) return false;  // the caller's workspace is too small
       arena = tl_arena;
     } else {
-      HIP_TRY(device_cache().get(count * sizeof(T), &q));
+      const hipError_t e = device_cache().get(count * sizeof(T), &q);
+      if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        return false;
+      }
+      HIP_TRY(e);
     }
     p = static_cast<T*>(q);
     bytes = count * sizeof(T);
+    return true;
   }
   void release() {
     if (p) {
@@ -2729,8 +2739,7 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
           HIP_TRY(launch_row_stats(c->x, c->ldx, c->n, c->d, c->measure == 0 ? 1 : 0, mean.p, norm.p, c->st));
         }
         const size_t wb = edge_buckets_workspace(c->n, c->d, c->ne);
-        if (wb) {
-          work.alloc(wb);
+        if (wb && work.try_alloc(wb)) {
           HIP_TRY(launch_edge_similarity_buckets(c->x, c->ldx, c->d, c->u, c->v, c->ne, c->measure, c->sigma, mean.p,
                                                  norm.p, c->n, work.p, wb, bad.p, bad.p + 1, c->val, c->st));
         } else {

@@ -35,10 +35,10 @@ __device__ __forceinline__ double group_sum(double v) {
 }
 
 // ---- entries into buckets of rows ----------------------------------------------------------------------------------
-// Bucket b takes the entries of the rows [b << shift, (b + 1) << shift) into slots b * kBucketRoom .. of `slots`, in no
-// particular order: a workgroup counts its kPartEntries entries per bucket in LDS, reserves that many slots of every
-// bucket with one atomic addition and writes.  fill[b] ends up as the bucket's number of entries, more than kBucketRoom if
-// they did not fit: what does not fit, and entries with an index out of range, go to the list `rest` (room for all of
+// Bucket b takes the entries of the rows [b << shift, (b + 1) << shift) into slots b * room .. of `slots` (room <=
+// kBucketRoom), in no particular order: a workgroup counts its kPartEntries entries per bucket in LDS, reserves that many
+// slots of every bucket with one atomic addition and writes.  fill[b] ends up as the bucket's number of entries, more than
+// `room` if they did not fit: what does not fit, and entries with an index out of range, go to the list `rest` (room for all of
 // them, *nrest of them) or, where that is null, are dropped and the caller looks at the counts.
 constexpr int kBucketRoom = 4096;
 constexpr int kMaxBuckets = 16384;
@@ -51,8 +51,9 @@ constexpr int kPartEntries = kPartThreads * kPartTrips;
 template <bool MIRROR>
 __global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* __restrict__ row,
                                                                  const int32_t* __restrict__ col, int64_t nnz_in, int64_t n,
-                                                                 int shift, int nbuckets, int32_t* __restrict__ fill,
-                                                                 uint2* __restrict__ slots, uint32_t* __restrict__ slot_row,
+                                                                 int shift, int nbuckets, int room,
+                                                                 int32_t* __restrict__ fill, uint2* __restrict__ slots,
+                                                                 uint32_t* __restrict__ slot_row,
                                                                  uint32_t* __restrict__ rest, int32_t* __restrict__ nrest,
                                                                  int* __restrict__ bad) {
   __shared__ int32_t count[kMaxBuckets];
@@ -93,18 +94,18 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* 
   for (int u = 0; u < TR; ++u) {
     const int64_t e = e0 + u * kPartThreads + threadIdx.x;
     if (e >= nnz_in) continue;
-    const int at = r[u] < 0 ? kBucketRoom : atomicAdd(&count[r[u] >> shift], 1);
-    if (at < kBucketRoom) {
-      slots[(int64_t)(r[u] >> shift) * kBucketRoom + at] = make_uint2((uint32_t)c[u], (uint32_t)e);
-      slot_row[(int64_t)(r[u] >> shift) * kBucketRoom + at] = (uint32_t)r[u];
+    const int at = r[u] < 0 ? room : atomicAdd(&count[r[u] >> shift], 1);
+    if (at < room) {
+      slots[(int64_t)(r[u] >> shift) * room + at] = make_uint2((uint32_t)c[u], (uint32_t)e);
+      slot_row[(int64_t)(r[u] >> shift) * room + at] = (uint32_t)r[u];
     } else if (rest) {
       c[u] = -2 - atomicAdd(&left, 1);  // its place among the workgroup's
     }
     if (MIRROR && r[u] >= 0 && r[u] != c[u]) {
       const int am = atomicAdd(&count[c[u] >> shift], 1);
-      if (am < kBucketRoom) {
-        slots[(int64_t)(c[u] >> shift) * kBucketRoom + am] = make_uint2((uint32_t)r[u], (uint32_t)(nnz_in + e));
-        slot_row[(int64_t)(c[u] >> shift) * kBucketRoom + am] = (uint32_t)c[u];
+      if (am < room) {
+        slots[(int64_t)(c[u] >> shift) * room + am] = make_uint2((uint32_t)r[u], (uint32_t)(nnz_in + e));
+        slot_row[(int64_t)(c[u] >> shift) * room + am] = (uint32_t)c[u];
       }
     }
   }
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* 
 
 // base[b] = exclusive prefix sums of fill, *over |= 1 if a bucket overflowed.  One workgroup.
 __global__ __launch_bounds__(kPartThreads) void bucket_scan_kernel(const int32_t* __restrict__ fill, int nbuckets,
-                                                                   int32_t* __restrict__ base, int* __restrict__ over) {
+                                                                   int room, int32_t* __restrict__ base, int* __restrict__ over) {
   __shared__ int32_t wave_sum[kPartThreads / 64];
   constexpr int PER = kMaxBuckets / kPartThreads;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(kPartThreads) void bucket_scan_kernel(const int32_t
   for (int q = 0; q < PER; ++q) {
     const int b = (int)threadIdx.x * PER + q;
     v[q] = b < nbuckets ? fill[b] : 0;
-    if (v[q] > kBucketRoom) atomicOr(over, 1);
+    if (v[q] > room) atomicOr(over, 1);
     sum += v[q];
   }
   int32_t incl = sum;
@@ -157,7 +158,8 @@ __global__ __launch_bounds__(kPartThreads) void bucket_scan_kernel(const int32_t
 // entries are grouped by row in LDS, then an entry's place is the number of entries of its row that come before it.
 constexpr int kMaxBucketRows = 1024;
 __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restrict__ fill, const int32_t* __restrict__ base,
-                                                         const int* __restrict__ over, int shift, int64_t n, int64_t nnz_in,
+                                                         const int* __restrict__ over, int shift, int room, int64_t n,
+                                                         int64_t nnz_in,
                                                          const uint2* __restrict__ slots,
                                                          const uint32_t* __restrict__ slot_row,
                                                          const double* __restrict__ val, int64_t* __restrict__ rowptr,
@@ -172,8 +174,8 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
   const int64_t row0 = (int64_t)b << shift, at0 = base[b];
   for (int r = threadIdx.x; r < rows; r += kT) next[r] = 0;
   __syncthreads();
-  const uint2* __restrict__ mine = slots + (int64_t)b * kBucketRoom;
-  const uint32_t* __restrict__ mrow = slot_row + (int64_t)b * kBucketRoom;
+  const uint2* __restrict__ mine = slots + (int64_t)b * room;
+  const uint32_t* __restrict__ mrow = slot_row + (int64_t)b * room;
   for (int p = threadIdx.x; p < len; p += kT) atomicAdd(&next[mrow[p] - (uint32_t)row0], 1);
   __syncthreads();
   {  // exclusive prefix sums over the rows: thread t has the rows 4 t .. 4 t + 3
@@ -350,7 +352,7 @@ __global__ __launch_bounds__(kT) void edge_list_kernel(const double* __restrict_
 constexpr int kRuns = 16;
 __host__ __device__ inline int edge_run(int nbuckets) { return (nbuckets + 8 * kRuns - 1) / (8 * kRuns); }
 __global__ __launch_bounds__(kT) void edge_bucket_kernel(const double* __restrict__ x, int64_t ldx, int d, int shift,
-                                                         int nbuckets, const int32_t* __restrict__ fill,
+                                                         int nbuckets, int room, const int32_t* __restrict__ fill,
                                                          const uint2* __restrict__ slots,
                                                          const uint32_t* __restrict__ slot_row, int measure,
                                                          double inv_two_sigma2, const double* __restrict__ mean,
@@ -360,7 +362,7 @@ __global__ __launch_bounds__(kT) void edge_bucket_kernel(const double* __restric
   const int t = (int)(blockIdx.x / 8), run = edge_run(nbuckets);
   const int b = (t / run * 8 + (int)(blockIdx.x % 8)) * run + t % run;
   if (b >= nbuckets) return;  // uniform
-  const int count = fill[b] < kBucketRoom ? fill[b] : kBucketRoom;
+  const int count = fill[b] < room ? fill[b] : room;
   if (count == 0) return;  // uniform
   const int dl = (d + 1) & ~1, nr = 1 << shift;
   const int64_t row0 = (int64_t)b << shift;
@@ -376,8 +378,8 @@ __global__ __launch_bounds__(kT) void edge_bucket_kernel(const double* __restric
   }
   __syncthreads();
   const int lane = threadIdx.x % kL;
-  const uint2* __restrict__ mine = slots + (int64_t)b * kBucketRoom;
-  const uint32_t* __restrict__ urow = slot_row + (int64_t)b * kBucketRoom;
+  const uint2* __restrict__ mine = slots + (int64_t)b * room;
+  const uint32_t* __restrict__ urow = slot_row + (int64_t)b * room;
   constexpr int E = 4;  // pairs in flight per 16 lanes (one: 670 us, eight: 510 us for the case above)
   for (int p0 = threadIdx.x / kL; p0 < count; p0 += E * (kT / kL)) {  // uniform over the pairs' lanes
     const double *xu[E], *xv[E];
@@ -527,8 +529,18 @@ namespace {
 
 struct BucketPlan {
   bool use = false;
-  int shift = 0, buckets = 0;
+  int shift = 0, buckets = 0, room = 0;
+  size_t slot_count() const { return (size_t)buckets * room; }  // 12 bytes each
 };
+
+// Slots per bucket: as many as the LDS takes, but no more than `most` per entry in all unless that is little anyway
+// (64 MB).  Entries that find no room cost more than unused slots do: 131,072 rows of 380 coordinates with 8 pairs a row
+// get 512 slots for 64 pairs a bucket on average.
+int bucket_room(int64_t buckets, int64_t entries, int64_t most) {
+  int room = kBucketRoom;
+  while (room > 64 && buckets * room > most * entries && buckets * room * 12 > (int64_t)64 << 20) room /= 2;
+  return room;
+}
 
 // Rows per bucket: about 2,048 entries in a bucket that holds 4,096, fewer where that leaves the chip without work.
 BucketPlan plan_buckets(int64_t total, int64_t n) {
@@ -540,9 +552,10 @@ BucketPlan plan_buckets(int64_t total, int64_t n) {
   const int64_t nb = ((n - 1) >> p.shift) + 1;
   // more buckets than a workgroup has counters, or rows so long that ranking their entries (quadratic in the length) costs
   // more than the sort: 2,000 rows of 2,000 entries take 1,124 us in buckets and 390 us in the radix sort
-  // or so few entries that the room of the buckets (48 KB each) is out of proportion
+  // or so few entries that most buckets are next to empty
   p.use = nb <= kMaxBuckets && total <= nb * (kBucketRoom / 2) && total <= 256 * n && (nb <= 1024 || nb * 128 <= total);
   p.buckets = (int)nb;
+  p.room = bucket_room(nb, total, 8);
   return p;
 }
 
@@ -562,14 +575,14 @@ size_t radix_workspace(int64_t total) {
 size_t coo_to_csr_workspace(int64_t total, int64_t n, int radix) {
   const BucketPlan p = plan_buckets(total, n);
   // over, fill[buckets] | base[buckets] | slots | slot_row
-  if (p.use && !radix) return 2 * up256((size_t)p.buckets * 4 + 8) + (size_t)p.buckets * kBucketRoom * 12 + 1024;
+  if (p.use && !radix) return 2 * up256((size_t)p.buckets * 4 + 8) + p.slot_count() * 12 + 1024;
   return radix_workspace(total);
 }
 
 // Entries sorted by (row, col); listed duplicates stay separate entries in listing order.  rowptr_out[n] is the number
 // of entries emitted; col_out / val_out need room for `total` entries, total = nnz_in * (symmetrize ? 2 : 1) < 2^31.
 // bad: device int[2]; bad[0] |= 1 if an index is out of range; bad[1] = 1 if a bucket overflowed and nothing was done: the
-// caller then calls again with radix = 1.
+// caller then calls again with radix = 1, as it does where the scratch of the buckets cannot be had.
 //
 // 3.8 M pairs of 142,541 rows (7.6 M entries): radix sort of 64-bit keys 640 us, with the keys, row pointers and gather
 // round it 730 us; buckets 180 us (partition 50, sort 126).  Bound by the scattered writes of the partition and the gather of the values.
@@ -584,20 +597,20 @@ hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val,
     int32_t* fill = reinterpret_cast<int32_t*>(base);
     int32_t* first = reinterpret_cast<int32_t*>(base + up256((size_t)p.buckets * 4 + 8));
     uint2* slots = reinterpret_cast<uint2*>(base + 2 * up256((size_t)p.buckets * 4 + 8));
-    uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + (size_t)p.buckets * kBucketRoom);
+    uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + p.slot_count());
     hipError_t e = launch_fill_int32(fill, p.buckets, 0, 0, st);
     if (e != hipSuccess) return e;
     const int64_t per = symmetrize ? kPartEntries / 2 : kPartEntries;
     const dim3 grid((unsigned)((nnz_in + per - 1) / per));
     if (symmetrize)
       hipLaunchKernelGGL((partition_kernel<true>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
-                         fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
+                         p.room, fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
     else
       hipLaunchKernelGGL((partition_kernel<false>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
-                         fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
-    hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(kPartThreads), 0, st, fill, p.buckets, first, bad + 1);
-    hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)p.buckets), dim3(kT), 0, st, fill, first, bad + 1, p.shift, n,
-                       nnz_in, slots, slot_row, val, rowptr_out, col_out, val_out);
+                         p.room, fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
+    hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(kPartThreads), 0, st, fill, p.buckets, p.room, first, bad + 1);
+    hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)p.buckets), dim3(kT), 0, st, fill, first, bad + 1, p.shift, p.room,
+                       n, nnz_in, slots, slot_row, val, rowptr_out, col_out, val_out);
     return hipGetLastError();
   }
   size_t sort_bytes = 0;
@@ -639,6 +652,7 @@ BucketPlan plan_edge_buckets(int64_t n, int d, int64_t nedges) {
   if (p.shift < 3 || nb > kMaxBuckets || nedges > nb * (kBucketRoom / 2)) return p;
   p.use = true;
   p.buckets = (int)nb;
+  p.room = bucket_room(nb, nedges, 8);
   return p;
 }
 
@@ -647,7 +661,7 @@ BucketPlan plan_edge_buckets(int64_t n, int d, int64_t nedges) {
 size_t edge_buckets_workspace(int64_t n, int d, int64_t nedges) {
   const BucketPlan p = plan_edge_buckets(n, d, nedges);
   // fill[buckets] | slots | slot_row | rest[nedges]
-  return p.use ? up256((size_t)p.buckets * 4) + (size_t)p.buckets * kBucketRoom * 12 + (size_t)nedges * 4 + 1024 : 0;
+  return p.use ? up256((size_t)p.buckets * 4) + p.slot_count() * 12 + (size_t)nedges * 4 + 1024 : 0;
 }
 
 hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, const int32_t* eu, const int32_t* ev,
@@ -658,18 +672,18 @@ hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, c
   if (!p.use || work_bytes < edge_buckets_workspace(n, d, nedges)) return hipErrorInvalidValue;
   int32_t* fill = static_cast<int32_t*>(work);
   uint2* slots = reinterpret_cast<uint2*>(static_cast<char*>(work) + up256((size_t)p.buckets * 4));
-  uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + (size_t)p.buckets * kBucketRoom);
-  uint32_t* rest = slot_row + (size_t)p.buckets * kBucketRoom;
+  uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + p.slot_count());
+  uint32_t* rest = slot_row + p.slot_count();
   const hipError_t e = launch_fill_int32(fill, p.buckets, 0, 0, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((partition_kernel<false>), dim3((unsigned)((nedges + kPartEntries - 1) / kPartEntries)),
-                     dim3(kPartThreads), 0, st, eu, ev, nedges, n, p.shift, p.buckets, fill, slots, slot_row, rest, nrest,
-                     bad);
+                     dim3(kPartThreads), 0, st, eu, ev, nedges, n, p.shift, p.buckets, p.room, fill, slots, slot_row, rest,
+                     nrest, bad);
   const int vec_ok = (ldx % 2 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   const double inv = measure == 2 ? 1.0 / (2.0 * sigma * sigma) : 0.0;
   const size_t lds = ((size_t)1 << p.shift) * (size_t)(((d + 1) & ~1) + 2) * 8;
   hipLaunchKernelGGL(edge_bucket_kernel, dim3((unsigned)(8 * kRuns * edge_run(p.buckets))), dim3(kT), lds, st, x, ldx, d,
-                     p.shift, p.buckets, fill, slots, slot_row, measure, inv, mean, norm, vec_ok, n, val);
+                     p.shift, p.buckets, p.room, fill, slots, slot_row, measure, inv, mean, norm, vec_ok, n, val);
   hipLaunchKernelGGL(edge_list_kernel, dim3(2048), dim3(kT), 0, st, x, ldx, d, eu, ev, rest, nrest, measure, inv, mean, norm,
                      vec_ok, n, bad, val);
   return hipGetLastError();

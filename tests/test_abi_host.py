@@ -152,3 +152,23 @@ def test_workspace_bytes_query():
             B.sc_workspace_bytes(**bad)
         assert e.value.code == B.SC_EDOMAIN
     assert B.lib().sc_workspace_bytes(100, 500, 5, None, None) == B.SC_EINVAL
+
+
+def _size_query(name, *types):
+    """A host-only scratch-size function of the library's kernels.h (C++ name)."""
+    f = getattr(binding.lib(), name)
+    f.restype, f.argtypes = ctypes.c_size_t, list(types)
+    return f
+
+
+def test_edge_similarity_scratch_is_in_proportion_to_the_pairs():
+    f = _size_query("_ZN5sceig22edge_buckets_workspaceElil", ctypes.c_int64, ctypes.c_int32, ctypes.c_int64)
+    used = 0
+    for n in (13_158, 60_000, 142_541, 500_000, 1_000_003, 4_000_000):
+        for d in (2, 5, 17, 90, 128, 380, 381):
+            for per_row in (8, 9, 27, 40, 200):
+                ne = n * per_row + 1
+                need = f(n, d, ne)
+                used += need > 0
+                assert need <= 100 * ne + 2 ** 26 + 2 ** 17, (n, d, ne, need)
+    assert used > 20

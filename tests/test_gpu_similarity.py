@@ -218,3 +218,34 @@ def test_a_full_block_cache_gives_way(B):
     after = free_after_call(20_000_000)
     B.sc_release_cache()
     assert after - before > 100 << 20
+
+
+def _all_but(nbytes, B):
+    """Tensors that leave about `nbytes` of the device's memory free."""
+    B.sc_release_cache()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(8):                      # what is reported as free comes down in steps
+        more = torch.cuda.mem_get_info()[0] - nbytes
+        if more < 8 << 20:
+            break
+        held.append(torch.empty(more, dtype=torch.uint8, device="cuda:0"))
+    assert torch.cuda.mem_get_info()[0] <= nbytes + (8 << 20)
+    return held
+
+
+def test_edge_similarity_without_room_for_buckets(B):
+    """235 MB of scratch for the buckets, 96 MB there: the values are formed pair by pair, the same as with buckets."""
+    n, d, ne = 131_072, 48, 8_000_000
+    gen = torch.Generator(device="cuda:0").manual_seed(4)
+    x = torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    u, v = (torch.randint(0, n, (ne,), device="cuda:0", generator=gen, dtype=torch.int32) for _ in range(2))
+    ref = B.sc_edge_similarity(x, u, v, 0)
+    got = torch.empty_like(ref)
+    held = _all_but(96 << 20, B)
+    code = B.lib().sc_edge_similarity(x.data_ptr(), d, n, d, u.data_ptr(), v.data_ptr(), ne, 0, 1.0, got.data_ptr(),
+                                      torch.cuda.current_stream().cuda_stream)
+    del held
+    torch.cuda.empty_cache()
+    assert code == B.SC_OK and torch.equal(got, ref)
