@@ -463,6 +463,8 @@ int sc_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int32_
  *                   listing order; what lies beyond rowptr_out[n] is unspecified
  *   nnz_out         host, = rowptr_out[n]; may be NULL
  * n <= 2^31 - 1 and at most 2^31 - 1 output entries (else SC_EDOMAIN); SC_ECSR if an index is outside [0, n).
+ * Device scratch of the call: up to 100 bytes an output entry + 2^26 + 2^18; where these cannot be had, the call does with
+ * the 24 bytes an entry (and those of a radix sort) that it takes where rows are very long or very many, at less speed.
  */
 int sc_coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int64_t nnz_in, int64_t n,
                   int32_t symmetrize, int64_t* rowptr_out, int32_t* col_out, double* val_out, int64_t* nnz_out,

@@ -2787,8 +2787,12 @@ int sc_coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int
         bad.alloc(2);
         host.alloc(2);
         for (int radix = 0; radix < 2; ++radix) {
-          const size_t wb = coo_to_csr_workspace(total, c->n, radix);
-          work.alloc(wb);
+          size_t wb = coo_to_csr_workspace(total, c->n, radix);
+          if (radix == 0 && !work.try_alloc(wb)) {  // no room for the buckets: the sort needs less
+            radix = 1;
+            wb = coo_to_csr_workspace(total, c->n, radix);
+          }
+          if (radix) work.alloc(wb);
           HIP_TRY(launch_fill_int32(bad.p, 2, 0, 0, c->st));
           HIP_TRY(coo_to_csr(c->row, c->col, c->val, c->nnz, c->n, c->sym, radix, work.p, wb, c->rp, c->co, c->vo, bad.p,
                              c->st));

@@ -36,19 +36,21 @@ __device__ __forceinline__ double group_sum(double v) {
 
 // ---- entries into buckets of rows ----------------------------------------------------------------------------------
 // Bucket b takes the entries of the rows [b << shift, (b + 1) << shift) into slots b * room .. of `slots` (room <=
-// kBucketRoom), in no particular order: a workgroup counts its kPartEntries entries per bucket in LDS, reserves that many
+// kBucketRoom), in no particular order: a workgroup counts its entries per bucket in LDS, reserves that many
 // slots of every bucket with one atomic addition and writes.  fill[b] ends up as the bucket's number of entries, more than
 // `room` if they did not fit: what does not fit, and entries with an index out of range, go to the list `rest` (room for all of
 // them, *nrest of them) or, where that is null, are dropped and the caller looks at the counts.
 constexpr int kBucketRoom = 4096;
 constexpr int kMaxBuckets = 16384;
 constexpr int kPartThreads = 1024;
-constexpr int kPartTrips = 16;
-constexpr int kPartEntries = kPartThreads * kPartTrips;
+// Entries per thread: 16, so that few additions reserve many slots, or 2 where 16 would leave the chip without workgroups
+// (up to kPartFew entries; 200,000: 31 us with 16, 9 us with 2).
+constexpr int kPartTrips = 16, kPartTripsFew = 2;
+constexpr int64_t kPartFew = 256 * kPartThreads * kPartTripsFew;
 
 // The e-th entry is (row[e], col[e]) with payload e; with MIRROR the same again as (col[e], row[e]) with payload
 // nnz_in + e unless the two are equal (rest is null then).  An index outside [0, n) sets *bad.
-template <bool MIRROR>
+template <bool MIRROR, int TRIPS>
 __global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* __restrict__ row,
                                                                  const int32_t* __restrict__ col, int64_t nnz_in, int64_t n,
                                                                  int shift, int nbuckets, int room,
@@ -58,8 +60,8 @@ __global__ __launch_bounds__(kPartThreads) void partition_kernel(const int32_t* 
                                                                  int* __restrict__ bad) {
   __shared__ int32_t count[kMaxBuckets];
   __shared__ int32_t left, left0;
-  const int64_t e0 = (int64_t)blockIdx.x * (MIRROR ? kPartEntries / 2 : kPartEntries);
-  constexpr int TR = MIRROR ? kPartTrips / 2 : kPartTrips;
+  constexpr int TR = MIRROR ? TRIPS / 2 : TRIPS;
+  const int64_t e0 = (int64_t)blockIdx.x * (TR * kPartThreads);
   for (int b = threadIdx.x; b < nbuckets; b += kPartThreads) count[b] = 0;
   if (threadIdx.x == 0) left = 0;
   __syncthreads();
@@ -154,9 +156,45 @@ __global__ __launch_bounds__(kPartThreads) void bucket_scan_kernel(const int32_t
   }
 }
 
+// key[lo .. lo + len - 1] into ascending order by the whole workgroup: a bitonic network whose comparators all point
+// upwards, so that those with a partner past the end can be left out.
+__device__ __forceinline__ void sort_run(uint64_t* __restrict__ key, int lo, int len) {
+  for (int k = 2; k < 2 * len; k *= 2) {
+    for (int j = k / 2; j > 0; j /= 2) {
+      __syncthreads();
+      const int flip = j == k / 2 ? k - 1 : j;  // the first stage of a merge pairs an entry with its mirror image
+      for (int q0 = threadIdx.x; 2 * (q0 & ~(j - 1)) < len; q0 += 4 * kT) {  // pair q: entries with bit j clear and set
+        uint64_t a[4], b[4];
+        int t[4], o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = q0 + u * kT;
+          t[u] = 2 * (q & ~(j - 1)) | (q & (j - 1));
+          o[u] = t[u] ^ flip;
+          if (o[u] >= len) o[u] = t[u] = 0;  // left out
+          a[u] = key[lo + t[u]];
+          b[u] = key[lo + o[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (a[u] > b[u]) {
+            key[lo + t[u]] = b[u];
+            key[lo + o[u]] = a[u];
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+}
+
 // The rows of a bucket, each sorted by (column, payload), to their place in the CSR.  One workgroup per bucket: the
-// entries are grouped by row in LDS, then an entry's place is the number of entries of its row that come before it.
+// entries are grouped by row in LDS, then an entry's place is the number of entries of its row that come before it, or,
+// in a row of more than kLongRow entries, where a sort leaves it.  The count is quadratic in the length: 200,000 entries, one
+// row with 3,000 of them, took 757 us with it and take 119 us (145 in the radix sort); 128 entries as the limit were slower
+// on rows of 200, 256 and 1,024 made no difference.
 constexpr int kMaxBucketRows = 1024;
+constexpr int kLongRow = 512;
 __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restrict__ fill, const int32_t* __restrict__ base,
                                                          const int* __restrict__ over, int shift, int room, int64_t n,
                                                          int64_t nnz_in,
@@ -168,11 +206,13 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
   __shared__ uint16_t krow[kBucketRoom];
   __shared__ int32_t first[kMaxBucketRows + 1], next[kMaxBucketRows];
   __shared__ int32_t wave_sum[kT / 64];
+  __shared__ int32_t long_row[kBucketRoom / kLongRow], nlong;
   if (*over) return;  // uniform over the grid
   const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int len = fill[b], rows = 1 << shift;
   const int64_t row0 = (int64_t)b << shift, at0 = base[b];
   for (int r = threadIdx.x; r < rows; r += kT) next[r] = 0;
+  if (threadIdx.x == 0) nlong = 0;
   __syncthreads();
   const uint2* __restrict__ mine = slots + (int64_t)b * room;
   const uint32_t* __restrict__ mrow = slot_row + (int64_t)b * room;
@@ -205,6 +245,7 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
         if (row0 + r < n) rowptr[row0 + r] = at0 + at;
         if (row0 + r == n - 1) rowptr[n] = at0 + at + v[q];
         if (r == rows - 1) first[rows] = at + v[q];
+        if (v[q] > kLongRow) long_row[atomicAdd(&nlong, 1)] = r;
       }
       at += v[q];
     }
@@ -218,12 +259,17 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
     krow[at] = (uint16_t)r;
   }
   __syncthreads();
+  for (int q = 0; q < nlong; ++q) sort_run(key, first[long_row[q]], first[long_row[q] + 1] - first[long_row[q]]);
   for (int p = threadIdx.x; p < len; p += kT) {
     const uint64_t k = key[p];
     const int r = krow[p], lo = first[r], hi = first[r + 1];
     int before = 0;
+    if (hi - lo > kLongRow) {
+      before = p - lo;
+    } else {
 #pragma unroll 4
-    for (int q = lo; q < hi; ++q) before += key[q] < k ? 1 : 0;
+      for (int q = lo; q < hi; ++q) before += key[q] < k ? 1 : 0;
+    }
     const int64_t out = at0 + lo + before;
     const int64_t e = (int64_t)(uint32_t)k;
     col_out[out] = (int32_t)(k >> 32);
@@ -559,6 +605,22 @@ BucketPlan plan_buckets(int64_t total, int64_t n) {
   return p;
 }
 
+void launch_partition(const int32_t* row, const int32_t* col, int64_t nnz_in, int64_t n, bool mirror, const BucketPlan& p,
+                      int32_t* fill, uint2* slots, uint32_t* slot_row, uint32_t* rest, int32_t* nrest, int* bad,
+                      hipStream_t st) {
+  const int64_t total = mirror ? 2 * nnz_in : nnz_in;
+  const int64_t per = (int64_t)kPartThreads * (total <= kPartFew ? kPartTripsFew : kPartTrips);
+#define SC_PARTITION(MIR, TRIPS)                                                                                       \
+  hipLaunchKernelGGL((partition_kernel<MIR, TRIPS>), dim3((unsigned)((total + per - 1) / per)), dim3(kPartThreads), 0, \
+                     st, row, col, nnz_in, n, p.shift, p.buckets, p.room, fill, slots, slot_row, rest, nrest, bad)
+  if (total <= kPartFew) {
+    if (mirror) SC_PARTITION(true, kPartTripsFew); else SC_PARTITION(false, kPartTripsFew);
+  } else {
+    if (mirror) SC_PARTITION(true, kPartTrips); else SC_PARTITION(false, kPartTrips);
+  }
+#undef SC_PARTITION
+}
+
 size_t up256(size_t bytes) { return (bytes + 255) / 256 * 256; }
 
 size_t radix_workspace(int64_t total) {
@@ -582,7 +644,8 @@ size_t coo_to_csr_workspace(int64_t total, int64_t n, int radix) {
 // Entries sorted by (row, col); listed duplicates stay separate entries in listing order.  rowptr_out[n] is the number
 // of entries emitted; col_out / val_out need room for `total` entries, total = nnz_in * (symmetrize ? 2 : 1) < 2^31.
 // bad: device int[2]; bad[0] |= 1 if an index is out of range; bad[1] = 1 if a bucket overflowed and nothing was done: the
-// caller then calls again with radix = 1, as it does where the scratch of the buckets cannot be had.
+// caller then calls again with radix = 1, as it does where the scratch of the buckets cannot be had.  A row that is longer
+// than a bucket thus costs the partition on top of the sort: 200,000 entries 152 -> 159 us, 3.8 M 535 -> 559 us.
 //
 // 3.8 M pairs of 142,541 rows (7.6 M entries): radix sort of 64-bit keys 640 us, with the keys, row pointers and gather
 // round it 730 us; buckets 180 us (partition 50, sort 126).  Bound by the scattered writes of the partition and the gather of the values.
@@ -600,14 +663,7 @@ hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val,
     uint32_t* slot_row = reinterpret_cast<uint32_t*>(slots + p.slot_count());
     hipError_t e = launch_fill_int32(fill, p.buckets, 0, 0, st);
     if (e != hipSuccess) return e;
-    const int64_t per = symmetrize ? kPartEntries / 2 : kPartEntries;
-    const dim3 grid((unsigned)((nnz_in + per - 1) / per));
-    if (symmetrize)
-      hipLaunchKernelGGL((partition_kernel<true>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
-                         p.room, fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
-    else
-      hipLaunchKernelGGL((partition_kernel<false>), grid, dim3(kPartThreads), 0, st, row, col, nnz_in, n, p.shift, p.buckets,
-                         p.room, fill, slots, slot_row, (uint32_t*)nullptr, (int32_t*)nullptr, bad);
+    launch_partition(row, col, nnz_in, n, symmetrize != 0, p, fill, slots, slot_row, nullptr, nullptr, bad, st);
     hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(kPartThreads), 0, st, fill, p.buckets, p.room, first, bad + 1);
     hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)p.buckets), dim3(kT), 0, st, fill, first, bad + 1, p.shift, p.room,
                        n, nnz_in, slots, slot_row, val, rowptr_out, col_out, val_out);
@@ -676,9 +732,7 @@ hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, c
   uint32_t* rest = slot_row + p.slot_count();
   const hipError_t e = launch_fill_int32(fill, p.buckets, 0, 0, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((partition_kernel<false>), dim3((unsigned)((nedges + kPartEntries - 1) / kPartEntries)),
-                     dim3(kPartThreads), 0, st, eu, ev, nedges, n, p.shift, p.buckets, p.room, fill, slots, slot_row, rest,
-                     nrest, bad);
+  launch_partition(eu, ev, nedges, n, false, p, fill, slots, slot_row, rest, nrest, bad, st);
   const int vec_ok = (ldx % 2 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   const double inv = measure == 2 ? 1.0 / (2.0 * sigma * sigma) : 0.0;
   const size_t lds = ((size_t)1 << p.shift) * (size_t)(((d + 1) & ~1) + 2) * 8;

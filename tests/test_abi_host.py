@@ -172,3 +172,12 @@ def test_edge_similarity_scratch_is_in_proportion_to_the_pairs():
                 used += need > 0
                 assert need <= 100 * ne + 2 ** 26 + 2 ** 17, (n, d, ne, need)
     assert used > 20
+
+
+def test_coo_to_csr_scratch_is_in_proportion_to_the_entries():
+    f = _size_query("_ZN5sceig20coo_to_csr_workspaceElli", ctypes.c_int64, ctypes.c_int64, ctypes.c_int32)
+    for n in (1, 300, 4099, 70_001, 1_000_000, 8_000_000, 16_000_000):
+        for total in (1, 1000, 100_000, 500_000, 2_200_000, 8_000_000, 33_000_000):
+            if total > 256 * n or (n > 1_000_000 and total < 2_000_000):
+                continue                        # the radix sort, whose own scratch takes a device to ask for
+            assert f(total, n, 0) <= 100 * total + 2 ** 26 + 2 ** 18, (n, total)

@@ -1,5 +1,7 @@
 """GPU parity of the similarity-graph step (Section IV-A, Algorithm 1; Algorithm 2 step 4) against the oracle,
 through the C ABI, and the chain points -> similarity -> CSR -> eigensolver input."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -117,8 +119,11 @@ def _csr_by_sorting(r, c, w, n, symmetrize):
 
 
 # buckets of one row and of many, a last bucket that is not full, rows at the limit of a bucket and beyond (radix sort),
-# rows too long for the ranking, more rows than there are buckets
+# rows too long for the ranking, rows at the limit of the ranking, several of them in a bucket, more rows than there are
+# buckets
 @pytest.mark.parametrize("n,ne,hub", [(1, 3, 0), (1024, 260, 0), (1025, 5000, 0), (4099, 200_000, 4000), (4099, 200_000, 5000),
+                                      (20_000, 20_000, 511), (20_000, 20_000, 513), (20_000, 20_000, 2049),
+                                      (4, 700, 0), (7, 4000, 2000), (20_000, 520_000, 700), (20_000, 530_000, 700),
                                       (300, 90_000, 0), (70_001, 1_200_000, 0), (1_048_577, 3000, 0), (20_000_000, 3000, 0)])
 @pytest.mark.parametrize("symmetrize", [False, True])
 def test_coo_to_csr_over_its_ranges(B, n, ne, hub, symmetrize):
@@ -249,3 +254,20 @@ def test_edge_similarity_without_room_for_buckets(B):
     del held
     torch.cuda.empty_cache()
     assert code == B.SC_OK and torch.equal(got, ref)
+
+
+def test_coo_to_csr_without_room_for_buckets(B):
+    """184 MB of scratch for the buckets, 128 MB there: the sort does with less, and the result is the same."""
+    n, ne = 16_000_000, 2_200_000
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    r, c = (torch.randint(0, n, (ne,), device="cuda:0", generator=gen, dtype=torch.int32) for _ in range(2))
+    w = torch.rand(ne, dtype=torch.float64, device="cuda:0", generator=gen)
+    ref = B.sc_coo_to_csr(r, c, w, n, False)
+    got = [torch.empty_like(t) for t in ref]
+    nnz = ctypes.c_int64(0)
+    held = _all_but(128 << 20, B)
+    code = B.lib().sc_coo_to_csr(r.data_ptr(), c.data_ptr(), w.data_ptr(), ne, n, 0, *(t.data_ptr() for t in got),
+                                 ctypes.byref(nnz), torch.cuda.current_stream().cuda_stream)
+    del held
+    torch.cuda.empty_cache()
+    assert code == B.SC_OK and nnz.value == ne and all(torch.equal(a, b) for a, b in zip(got, ref))
