@@ -429,9 +429,9 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
  * SC_EDOMAIN: 768 * k_nn + 1536 bytes for d <= 128 (any k_nn up to 200), 128 * (8 * dp + 12 * k_nn) bytes for d > 128
  * (dp = d rounded up to a multiple of 8).  The library allocates n * (dp + 1) * 8 bytes of scratch for the call, dp = d
  * rounded up to 8, 16, 32, 64 or 128 (to a multiple of 8 beyond), and for d <= 128 and n >= 512 up to
- * n * (4 * dp + 32) + 2^28 bytes more (a reduced-precision copy of the points that only screens the candidates, and
- * their lists; every distance that is compared or returned is the fp64 sum).  Returns after the work on `stream` is
- * done.
+ * n * (4 * max(dp, 16) + 34) + 2^28 + 2^20 bytes more (a reduced-precision copy of the points that only screens the
+ * candidates, and their lists; every distance that is compared or returned is the fp64 sum); where the latter cannot be
+ * had, the call does without the screen, at a fraction of the speed.  Returns after the work on `stream` is done.
  */
 int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_nn, int32_t* idx_out, double* dist_out,
                   void* stream);

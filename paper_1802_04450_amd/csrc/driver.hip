@@ -2833,14 +2833,13 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
         xp.alloc((size_t)c->n * (knn_padded_dim(c->d) + 1));  // padded rows, then one squared norm per row
         HIP_TRY(launch_knn_pad(c->x, c->ldx, c->n, c->d, xp.p, c->st));
         const size_t wb = knn_screen_workspace(c->n, c->d, c->k);
-        if (wb == 0) {
+        DevBuf<char> work;
+        if (wb == 0 || !work.try_alloc(wb)) {  // no screen, or no room for it
           HIP_TRY(launch_knn_search(c->n, c->d, c->k, xp.p, nullptr, 0, nullptr, c->idx, c->dist, c->st));
           HIP_TRY(hipStreamSynchronize(c->st));
           return SC_OK;
         }
-        DevBuf<char> work;
         PinnedBuf<int32_t> left;
-        work.alloc(wb);
         left.alloc(1);
         int32_t *tiles = nullptr, *ntiles = nullptr;
         double* bound = nullptr;

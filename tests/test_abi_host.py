@@ -181,3 +181,14 @@ def test_coo_to_csr_scratch_is_in_proportion_to_the_entries():
             if total > 256 * n or (n > 1_000_000 and total < 2_000_000):
                 continue                        # the radix sort, whose own scratch takes a device to ask for
             assert f(total, n, 0) <= 100 * total + 2 ** 26 + 2 ** 18, (n, total)
+
+
+def test_knn_screen_scratch_is_what_the_header_says():
+    f = _size_query("_ZN5sceig20knn_screen_workspaceElii", ctypes.c_int64, ctypes.c_int32, ctypes.c_int32)
+    for n in (100, 512, 5000, 60_000, 100_000, 2_000_000, 20_000_000, 400_000_000):
+        for d in (1, 3, 8, 9, 16, 17, 32, 64, 100, 128, 129):
+            dp = next((p for p in (8, 16, 32, 64, 128) if d <= p), (d + 7) // 8 * 8)
+            for k in (1, 10, 60, 200):
+                need = f(n, d, k)
+                assert need <= n * (4 * max(dp, 16) + 34) + 2 ** 28 + 2 ** 20, (n, d, k, need)
+                assert need == 0 or (d <= 128 and n >= 512)

@@ -188,3 +188,58 @@ def test_search_at_benchmark_size_on_sampled_queries(B):
         np.testing.assert_array_equal(idx[i], order)
         np.testing.assert_allclose(dist[i], np.sqrt(d2[order]), rtol=1e-13)
     assert np.all(np.diff(dist, axis=1) >= 0) and idx.min() >= 0 and idx.max() < x.shape[0]
+
+
+def _sampled(x, k, rows, idx, dist):
+    """The lists of `rows` against the oracle's distances of those rows alone."""
+    for i in rows:
+        d2 = ((x - x[i]) ** 2).sum(axis=1)
+        d2[i] = np.inf
+        ref = np.lexsort((np.arange(x.shape[0]), d2))[:k]
+        same = idx[i] == ref
+        # two whose sums agree to the rounding of d + 2 additions may change places
+        tol = (x.shape[1] + 2) * 2.3e-16
+        assert np.all(np.abs(d2[idx[i]][~same] - d2[ref][~same]) <= 2 * tol * d2[ref][~same]), i
+        np.testing.assert_allclose(dist[i], np.sqrt(d2[ref]), rtol=1e-13, atol=0)
+
+
+# more queries than one round of the screen takes, the last round ragged; and with so many equal points among the rows of
+# either round that the screen gives up on them
+@pytest.mark.parametrize("kind", ["random", "equal at the start", "equal at the end"])
+def test_screened_search_in_two_rounds(B, kind):
+    n, d, k = 60_001, 8, 200                    # rounds of 55,296 queries: 256 MB of maxima and lists
+    rng = np.random.default_rng(n)
+    x = rng.standard_normal((n, d))
+    if kind == "equal at the start":
+        x[:900] = x[0]
+    elif kind == "equal at the end":
+        x[-900:] = x[-1]
+    idx, dist = B.sc_knn_search(_dev(x, torch.float64), k)
+    idx, dist = idx.cpu().numpy(), dist.cpu().numpy()
+    assert np.all(idx != np.arange(n)[:, None]) and np.all(np.diff(dist, axis=1) >= 0)
+    cut = 55_296
+    rows = np.concatenate([[0, 1, 898, 901, n - 1, n - 2, n - 901], np.arange(cut - 70, cut + 70, 7), rng.integers(0, n, 40)])
+    _sampled(x, k, rows, idx, dist)
+
+
+def test_search_without_room_for_the_screen(B):
+    """290 MB of scratch for the screen, 160 MB there: the fp64 kernel alone gives the same lists."""
+    n, d, k = 400_000, 4, 8
+    gen = torch.Generator(device="cuda:0").manual_seed(6)
+    x = torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    idx, dist = B.sc_knn_search(x, k)
+    got = [torch.empty_like(idx), torch.empty_like(dist)]
+    B.sc_release_cache()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(8):                          # what is reported as free comes down in steps
+        more = torch.cuda.mem_get_info()[0] - (160 << 20)
+        if more < 8 << 20:
+            break
+        held.append(torch.empty(more, dtype=torch.uint8, device="cuda:0"))
+    code = B.lib().sc_knn_search(x.data_ptr(), d, n, d, k, got[0].data_ptr(), got[1].data_ptr(),
+                                 torch.cuda.current_stream().cuda_stream)
+    del held
+    torch.cuda.empty_cache()
+    assert code == B.SC_OK and torch.equal(got[0], idx) and torch.equal(got[1], dist)
