@@ -2840,7 +2840,7 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
           return SC_OK;
         }
         PinnedBuf<int32_t> left;
-        left.alloc(1);
+        left.alloc(kLostInts);
         int32_t *tiles = nullptr, *ntiles = nullptr;
         double* bound = nullptr;
         HIP_TRY(launch_knn_screen(xp.p, c->n, c->d, c->k, work.p, left.p, &tiles, &ntiles, &bound, c->idx, c->dist, c->st));

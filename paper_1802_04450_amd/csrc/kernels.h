@@ -299,7 +299,9 @@ hipError_t launch_knn_pad(const double* x, int64_t ldx, int64_t n, int d, double
 // The bf16 screen: bytes of scratch it needs, 0 where it is not used.  It leaves device pointers to a list of tiles of
 // 64 queries that it could not settle, to their number and to an upper bound of every query's k-th squared distance;
 // launch_knn_search does those (tiles, ntiles, bound), or every query when tiles is null (all that there is to do without
-// the screen; bound may be null then).  host: pinned int32; the call waits for the stream (once per round of queries).
+// the screen; bound may be null then).  host: kLostInts pinned ints; the call waits for the stream (once per round of
+// queries).
+constexpr int kLostSlots = 64, kLostStride = 32, kLostInts = kLostSlots * kLostStride;
 size_t knn_screen_workspace(int64_t n, int d, int k);
 hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* work, int32_t* host, int32_t** tiles,
                              int32_t** ntiles, double** bound, int32_t* idx_out, double* dist_out, hipStream_t st);

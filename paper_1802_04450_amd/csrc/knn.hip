@@ -391,7 +391,9 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 
 // covers the rounding of the fp64 distances that decide in the end.
 //
 // 100,000 points of 32 coordinates, k = 20: 28.2 ms for the fp64 screen alone (22.7 TFLOP/s), 3.75 ms with
-// this one (two passes of 1.5 and 2.1 ms; 64 coordinates, k = 32: 61 -> 7.2 ms).  Bound by the matrix cores and, up to 32 coordinates, the vector work on the 16 results that a lane gets from
+// this one (two passes of 1.5 and 2.1 ms; 64 coordinates, k = 32: 61 -> 7.2 ms).  Data that it cannot settle pay for what
+// it did before that showed: 28.0 -> 29.1 ms for tight clusters far apart, 48.5 -> 53.2 ms with every 20th point the same
+// one, which leaves each tile of 64 queries to the fp64 kernel.  Bound by the matrix cores and, up to 32 coordinates, the vector work on the 16 results that a lane gets from
 // each tile (subtract, running maximum).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
@@ -530,11 +532,13 @@ __global__ __launch_bounds__(kT) void screen_split_kernel(const double* __restri
 // then holds 16 candidates of one query: register r = candidate 8 (r / 4) + 4 (lane / 32) + r % 4 of the tile.
 //   COLLECT false: maxima[(query - first query) * groups + slice * 16 + 8 (lane / 32) + r % 8]
 //   COLLECT true:  candidates with v >= tau[query - first query] are appended to the query's list (count, list)
+// Where the point set has no usable scale (a NaN among the coordinates, all points equal) there is nothing to screen.
 template <int DP, int NQ, bool COLLECT>
 __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(2))) void screen_kernel(
     const u4* __restrict__ xb, const float* __restrict__ half, int64_t n, int64_t tiles, int64_t qtile0, int64_t qtiles,
-    int slices, float* __restrict__ maxima, const float* __restrict__ tau, int cap, int32_t* __restrict__ count,
-    int32_t* __restrict__ list) {
+    int slices, const ScreenScale* __restrict__ scale, float* __restrict__ maxima, const float* __restrict__ tau, int cap,
+    int32_t* __restrict__ count, int32_t* __restrict__ list) {
+  if (!screen_usable(*scale)) return;  // uniform over the grid
   constexpr int KS = DP / 16;
   constexpr int CT = 8 / KS;             // candidate tiles per chunk: 16 KB
   constexpr int PT = KS * 2 * 64;        // 16-byte pieces per tile
@@ -695,7 +699,8 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(2))) void s
 // tau[q] = v* - 2 e, v* = the (k+1)-th largest of the query's maxima, found bit by bit; clears the query's list.  A wave
 // per query.  bound[first query + q] = a squared distance that at least k others do not exceed: what the fp64 kernel
 // starts from if it comes to that.  tau = +inf (nothing is listed, the query falls back) where the point set has no
-// usable scale or far too many would be listed; *hopeless counts those.
+// usable scale or far too many would be listed; the kLostSlots counters at `lost_count` count those between them (one counter for
+// all of 100,000 such queries took 1 ms).
 template <int NP>  // keys per lane: groups <= 64 NP
 __global__ __launch_bounds__(kT) void screen_threshold_kernel(const float* __restrict__ maxima, int groups, int k, int dp,
                                                               const float* __restrict__ norm, int64_t q0, int64_t nq,
@@ -703,7 +708,7 @@ __global__ __launch_bounds__(kT) void screen_threshold_kernel(const float* __res
                                                               const ScreenScale* __restrict__ scale,
                                                               float* __restrict__ tau, int32_t* __restrict__ count,
                                                               double* __restrict__ bound,
-                                                              int32_t* __restrict__ hopeless) {
+                                                              int32_t* __restrict__ lost_count) {
   const int lane = threadIdx.x & 63;
   const int64_t q = (int64_t)blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
   if (q >= nq) return;
@@ -731,7 +736,7 @@ __global__ __launch_bounds__(kT) void screen_threshold_kernel(const float* __res
       count[q] = 0;
       tau[q] = INFINITY;
       bound[q0 + q] = INFINITY;
-      atomicAdd(hopeless, 1);
+      atomicAdd(&lost_count[blockIdx.x % kLostSlots * kLostStride], 1);
     }
     return;
   }
@@ -750,7 +755,7 @@ __global__ __launch_bounds__(kT) void screen_threshold_kernel(const float* __res
   const bool lost = reach >= groups || -log1p(-(double)reach / groups) * groups > 1.5 * cap;
   count[q] = 0;
   tau[q] = lost ? INFINITY : cut;
-  if (lost) atomicAdd(hopeless, 1);
+  if (lost) atomicAdd(&lost_count[blockIdx.x % kLostSlots * kLostStride], 1);
   const double d2 = nrm2[q0 + q] * f * f - 2.0 * ((double)vstar - e);
   bound[q0 + q] = (d2 + 1e-6 * fabs(d2)) / (f * f);
 }
@@ -944,7 +949,7 @@ ScreenPlan plan_screen(int64_t n, int d, int k) {
   p.off_tau = place((size_t)p.chunk * 32 * 4);
   p.off_count = place((size_t)p.chunk * 32 * 4);
   p.off_list = place((size_t)p.chunk * 32 * p.cap * 4);
-  p.off_flag = place((size_t)((n + kMq - 1) / kMq) * 4 + 8);
+  p.off_flag = place(((size_t)((n + kMq - 1) / kMq) + 1 + kLostInts) * 4);
   p.off_tiles = place((size_t)((n + kMq - 1) / kMq) * 4);
   p.off_ntiles = p.off_flag + (size_t)((n + kMq - 1) / kMq) * 4;
   p.bytes = off;
@@ -975,11 +980,11 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
   int32_t* flag = reinterpret_cast<int32_t*>(w + p.off_flag);
   *tiles = reinterpret_cast<int32_t*>(w + p.off_tiles);
   *ntiles = reinterpret_cast<int32_t*>(w + p.off_ntiles);
-  int32_t* hopeless = *ntiles + 1;
+  int32_t* lost_count = *ntiles + 1;
   *bound = reinterpret_cast<double*>(w + p.off_bound);
-  int32_t lost_before = 0;
+  int64_t lost_before = 0;
   const size_t rank_lds = (size_t)(kT / 64) * p.cap * 12;
-  hipError_t e = launch_fill_int32(flag, (n + kMq - 1) / kMq + 2, 0, 0, st);  // the flags and, behind them, the two counts
+  hipError_t e = launch_fill_int32(flag, (n + kMq - 1) / kMq + 1 + kLostInts, 0, 0, st);  // the flags and the counts behind
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(screen_moments_kernel, dim3(kMomentBlocks), dim3(kT), 0, st, xp, n, dp, part);
   hipLaunchKernelGGL(screen_mean_kernel, dim3(1), dim3(1024), 0, st, part, kMomentBlocks, n, dp, mean, scale);
@@ -992,7 +997,7 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     const dim3 grid((unsigned)((nt + 4 * p.nq - 1) / (4 * p.nq)), (unsigned)p.slices);
 #define SC_SCREEN(DPV, NQV, COL)                                                                                      \
   hipLaunchKernelGGL((screen_kernel<DPV, NQV, COL>), grid, dim3(kMt), 0, st, xb, half, n, p.tiles, t0, nt, p.slices, \
-                     maxima, tau, p.cap, count, list)
+                     scale, maxima, tau, p.cap, count, list)
 #define SC_SCREEN_DIM(COL)                                       \
   do {                                                           \
     if (p.dpb == 16) SC_SCREEN(16, 4, COL);                      \
@@ -1003,7 +1008,7 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     SC_SCREEN_DIM(false);
 #define SC_THRESHOLD(NPV)                                                                                              \
   hipLaunchKernelGGL((screen_threshold_kernel<NPV>), dim3(blocks(nq * 64)), dim3(kT), 0, st, maxima, p.slices * 16, k, \
-                     p.dpb, norm, q0, nq, nrm2, p.cap, scale, tau, count, *bound, hopeless)
+                     p.dpb, norm, q0, nq, nrm2, p.cap, scale, tau, count, *bound, lost_count)
     if (p.slices <= 4) SC_THRESHOLD(1);
     else if (p.slices <= 8) SC_THRESHOLD(2);
     else if (p.slices <= 16) SC_THRESHOLD(4);
@@ -1011,12 +1016,13 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     else SC_THRESHOLD(16);
 #undef SC_THRESHOLD
     // most queries lost: the second pass would be for nothing, an empty list sends them all to the fp64 kernel
-    e = hipMemcpyAsync(host, hopeless, sizeof(int32_t), hipMemcpyDeviceToHost, st);
+    e = hipMemcpyAsync(host, lost_count, sizeof(int32_t) * kLostInts, hipMemcpyDeviceToHost, st);
     if (e != hipSuccess) return e;
     e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
-    const int32_t lost = *host - lost_before;
-    lost_before = *host;
+    int64_t lost = -lost_before;
+    for (int q = 0; q < kLostSlots; ++q) lost += host[q * kLostStride];
+    lost_before += lost;
     if (lost <= nq / 2) SC_SCREEN_DIM(true);
 #undef SC_SCREEN_DIM
 #undef SC_SCREEN
