@@ -348,7 +348,9 @@ int sc_sym_eig_top(const double* a, int32_t n, int32_t count, double* w, double*
  * points[t*ld + i], ld >= n (the evecs_out layout of sc_laplacian_eigsh, so its output can be passed on as it is);
  * colmajor == 0: points[i*ld + t], ld >= d.  Centres: device fp64[k*d], row-major k x d.  Labels: device int32[n].
  * 1 <= k <= n <= 2^27, d >= 1 (else SC_EDOMAIN).  All work is enqueued on `stream`; the calls return after it is done.
- * The library stages its own row-major copy of the points and never keeps a caller's pointer.
+ * The library stages its own row-major copy of the points and never keeps a caller's pointer.  Device scratch beside that
+ * copy: about 17 n bytes for the seeding, which takes 2 n d bytes more where it can have them; after that about
+ * 4 n + 4 n k / 1,024 bytes (12 n and those of a radix sort beyond 1,024 clusters) and 16 k d + 2^22 for the iterations.
  */
 typedef struct sc_kmeans_stats {
   int32_t iterations;   /* labelling steps done */

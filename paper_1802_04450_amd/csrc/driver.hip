@@ -1902,10 +1902,15 @@ struct KMeans {
   void seed(uint64_t seed_value, int32_t* chosen, double* c) {
     std::vector<double> u((size_t)k);
     for (int i = 0; i < k; ++i) u[i] = km_uniform01(seed_value, (uint64_t)i);
-    const size_t wb = kmeans_seed_workspace(n, ldx, d, k);
+    int screen = 1;
+    size_t wb = kmeans_seed_workspace(n, ldx, d, k, screen);
     DevBuf<char> work;
-    work.alloc(wb);
-    HIP_TRY(launch_kmeanspp(x.p, ldx, d, n, k, u.data(), work.p, wb, chosen, st));
+    if (!work.try_alloc(wb)) {
+      screen = 0;
+      wb = kmeans_seed_workspace(n, ldx, d, k, screen);
+      work.alloc(wb);
+    }
+    HIP_TRY(launch_kmeanspp(x.p, ldx, d, n, k, u.data(), screen, work.p, wb, chosen, st));
     HIP_TRY(launch_gather_rows(x.p, ldx, chosen, k, c, st));
     HIP_TRY(hipStreamSynchronize(st));  // u and work are released on return
   }

@@ -259,9 +259,10 @@ size_t kmeans_update_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, void* work,
                                   size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
                                   int* changes, hipStream_t st);
-// Algorithm 5 with the uniform numbers u[0..k-1] supplied by the host; chosen: device int32[k]
-size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k);
-hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, void* work,
+// Algorithm 5 with the uniform numbers u[0..k-1] supplied by the host; chosen: device int32[k].  screen = 0: without the
+// reduced copy of the points, which makes the draws faster and takes a quarter of their bytes
+size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen);
+hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, int screen, void* work,
                            size_t work_bytes, int32_t* chosen, hipStream_t st);
 hipError_t launch_gather_rows(const double* x, int64_t ldx, const int32_t* index, int k, double* c, hipStream_t st);
 // part[p], p < kmeans_objective_parts(): partial sums of |x_i - c_label(i)|^2 (add them in order on the host); NaN for a

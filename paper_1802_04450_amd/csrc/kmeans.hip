@@ -763,22 +763,22 @@ inline int seed_dpb(int d) { return (d + 7) / 8 * 8; }
 
 }  // namespace
 
-size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k) {
+size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen) {
   // two of (dist2[n] | bsum[ceil(n / 64)])  and, with the screen,
   // mean[ldx] | sums[kSeedParts][ldx] | tops[kSeedParts] | scale | err[n] | xh[n][dpb]
   const size_t nb = (size_t)((n + kSeedPoints - 1) / kSeedPoints);
   size_t bytes = 2 * ((size_t)n + nb) * 8 + 1024;
-  if (seed_screened(n, d, k)) bytes += (size_t)(ldx + 1) * 8 * (kSeedParts + 1) + (size_t)n * (4 + 2 * (size_t)seed_dpb(d)) + 1024;
+  if (screen && seed_screened(n, d, k)) bytes += (size_t)(ldx + 1) * 8 * (kSeedParts + 1) + (size_t)n * (4 + 2 * (size_t)seed_dpb(d)) + 1024;
   return bytes;
 }
 
 // Algorithm 5.  u[0 .. k-1]: host array of uniform numbers in [0, 1).  chosen: device int32[k], the indices of the
 // chosen points in the order they were drawn.  One or two launches per draw.
-hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, void* work,
+hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, int screen, void* work,
                            size_t work_bytes, int32_t* chosen, hipStream_t st) {
   if (n <= 0 || n > INT32_MAX || k < 1) return hipErrorInvalidValue;
   const int64_t nb = (n + kSeedPoints - 1) / kSeedPoints;
-  if (work_bytes < kmeans_seed_workspace(n, ldx, d, k)) return hipErrorInvalidValue;
+  if (work_bytes < kmeans_seed_workspace(n, ldx, d, k, screen)) return hipErrorInvalidValue;
   double* dist2[2] = {static_cast<double*>(work), static_cast<double*>(work) + n + nb};
   double* mean = dist2[1] + n + nb;
   double* sums = mean + ldx;
@@ -787,7 +787,7 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
   float* err = reinterpret_cast<float*>(scale + 1);
   __bf16* xh = reinterpret_cast<__bf16*>(((uintptr_t)(err + n) + 15) / 16 * 16);
   const int dpb = seed_dpb(d);
-  const bool screened = seed_screened(n, d, k), draws = nb <= kDrawBlocks;
+  const bool screened = screen && seed_screened(n, d, k), draws = nb <= kDrawBlocks;
   int64_t first = (int64_t)(u[0] * (double)n);
   first = first < n - 1 ? first : n - 1;
   hipLaunchKernelGGL(iota_fill_kernel, dim3(1), dim3(kT), 0, st, chosen, 1, (int32_t)first, 0);

@@ -262,3 +262,26 @@ def test_points_without_a_label_belong_to_no_cluster(B, k):
     assert np.all(lg[bad] == 2 ** 31 - 1)
     np.testing.assert_array_equal(lg[good], labels_ref)
     np.testing.assert_allclose(cen.cpu().numpy(), cen_ref, rtol=0, atol=6.0 * n * 2.0 ** -53)
+
+
+def test_seeding_without_room_for_its_copy(B):
+    """512 MB of points are staged, and of the 150 MB that the seeding would like 88 MB are there."""
+    n, d, k = 1_000_000, 64, 40
+    gen = torch.Generator(device="cuda:0").manual_seed(7)
+    x = torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    chosen, cen = B.sc_kmeanspp(x, k, 3)
+    got = [torch.empty_like(chosen), torch.empty_like(cen)]
+    B.sc_release_cache()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for _ in range(8):                          # what is reported as free comes down in steps
+        more = torch.cuda.mem_get_info()[0] - n * d * 8 - (88 << 20)
+        if more < 8 << 20:
+            break
+        held.append(torch.empty(more, dtype=torch.uint8, device="cuda:0"))
+    code = B.lib().sc_kmeanspp(x.data_ptr(), d, 0, n, d, k, 3, got[0].data_ptr(), got[1].data_ptr(),
+                               torch.cuda.current_stream().cuda_stream)
+    del held
+    torch.cuda.empty_cache()
+    assert code == B.SC_OK and torch.equal(got[0], chosen) and torch.equal(got[1], cen)
