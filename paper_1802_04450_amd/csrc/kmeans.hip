@@ -322,11 +322,11 @@ constexpr int64_t kDrawBlocks = 1800;
 constexpr float kScreenFloor = 1e-30f;
 
 // xh[i] = the centred and scaled point in bf16, padded with zeros to dpb coordinates (a multiple of 8); err[i] as above,
-// rounded up.  mean: any point will do (exactness does not depend on it); a bf16 value is off by 2^-9 of its modulus at
-// most, the centring by 2^-52 of the coordinates.  8 lanes per point.
+// rounded up, and beside it the exponent of the scale.  mean: any point will do (exactness does not depend on it); a bf16
+// value is off by 2^-9 of its modulus at most, the centring by 2^-52 of the coordinates.  8 lanes per point.
 __global__ __launch_bounds__(kT) void seed_copy_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
                                                        const double* __restrict__ mean, const double* __restrict__ scale,
-                                                       int dpb, __bf16* __restrict__ xh, float* __restrict__ err) {
+                                                       int dpb, __bf16* __restrict__ xh, float2* __restrict__ err) {
   const int lane = threadIdx.x % 8;
   const int64_t i = (int64_t)blockIdx.x * (kT / 8) + threadIdx.x / 8;
   if (i >= n) return;  // uniform over the point's lanes
@@ -337,7 +337,8 @@ __global__ __launch_bounds__(kT) void seed_copy_kernel(const double* __restrict_
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int t = c0 + q;
-      const double v = t < d ? x[i * ldx + t] * f : 0.0, m = t < d ? mean[t] * f : 0.0, y = v - m;
+      const double xv = t < d ? x[i * ldx + t] : 0.0, mv = t < d ? mean[t] : 0.0;
+      const double v = xv * f, m = mv * f, y = v - m;
       piece.b[q] = (__bf16)(float)y;
       const double off = y - (double)(float)piece.b[q];
       moved += off * off;
@@ -350,49 +351,48 @@ __global__ __launch_bounds__(kT) void seed_copy_kernel(const double* __restrict_
     moved += __shfl_xor(moved, o, 8);
     size += __shfl_xor(size, o, 8);
   }
-  if (lane == 0) err[i] = (float)((sqrt(moved) + 4.5e-16 * sqrt(size)) * 1.00001) + 1e-37f;
+  if (lane == 0)
+    err[i] = make_float2((float)((sqrt(moved) + 4.5e-16 * sqrt(size)) * 1.00001) + 1e-37f, f > 0.0 ? (float)ilogb(f) : 0.0f);
 }
 
-// mean[t] of the points, in two steps with a fixed order: part[b][t] over the points b, b + gridDim.x, ..., top[b] = their
-// largest modulus of a coordinate
+// mean[t] of the points, in two steps with a fixed order: part[b][t] over the points b, b + gridDim.x, ..., top[b] = the
+// upper word of their largest modulus of a coordinate (the exponent is all that is needed)
 constexpr int kSeedParts = kT;
 __global__ __launch_bounds__(kT) void seed_sum_kernel(const double* __restrict__ x, int64_t ldx, int64_t n,
-                                                      double* __restrict__ part, double* __restrict__ top) {
-  __shared__ double tops[kT];
-  double most = 0.0;
+                                                      double* __restrict__ part, uint32_t* __restrict__ top) {
+  __shared__ uint32_t most_of_all;
+  uint32_t most = 0u;
+  if (threadIdx.x == 0) most_of_all = 0u;
+  __syncthreads();
   for (int t = threadIdx.x; t < ldx; t += kT) {
     double acc = 0.0;
 #pragma unroll 8
     for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
       const double v = x[i * ldx + t];
+      const uint32_t m = (uint32_t)__double2hiint(v) & 0x7fffffffu;
       acc += v;
-      most = fmax(most, fabs(v));
+      most = m > most ? m : most;
     }
     part[(int64_t)blockIdx.x * ldx + t] = acc;
   }
-  tops[threadIdx.x] = most;
+  atomicMax(&most_of_all, most);
   __syncthreads();
-  for (int o = kT / 2; o > 0; o >>= 1) {
-    if (threadIdx.x < o) tops[threadIdx.x] = fmax(tops[threadIdx.x], tops[threadIdx.x + o]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) top[blockIdx.x] = tops[0];
+  if (threadIdx.x == 0) top[blockIdx.x] = most_of_all;
 }
 
 // the second step; *scale = the power of two that takes the largest modulus into [1, 2), 0 where the squares of such
-// numbers leave the range of a double
-__global__ __launch_bounds__(kT) void seed_mean_kernel(const double* __restrict__ part, const double* __restrict__ top,
+// numbers leave the range of a double (or one of them is no number)
+__global__ __launch_bounds__(kT) void seed_mean_kernel(const double* __restrict__ part, const uint32_t* __restrict__ top,
                                                        int parts, int64_t ldx, int64_t n, double* __restrict__ mean,
                                                        double* __restrict__ scale) {
   if (blockIdx.x == 0) {
-    __shared__ double tops[kT];
-    tops[threadIdx.x] = top[threadIdx.x];
+    __shared__ uint32_t most_of_all;
+    if (threadIdx.x == 0) most_of_all = 0u;
     __syncthreads();
-    for (int o = kT / 2; o > 0; o >>= 1) {
-      if (threadIdx.x < o) tops[threadIdx.x] = fmax(tops[threadIdx.x], tops[threadIdx.x + o]);
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) *scale = tops[0] > 1e-100 && tops[0] < 1e100 ? ldexp(1.0, -ilogb(tops[0])) : 0.0;
+    atomicMax(&most_of_all, top[threadIdx.x]);
+    __syncthreads();
+    const int e = (int)(most_of_all >> 20) - 1023;
+    if (threadIdx.x == 0) *scale = e > -330 && e < 330 ? ldexp(1.0, -e) : 0.0;
   }
   const int t = blockIdx.x * kT + threadIdx.x;
   if (t >= ldx) return;
@@ -509,8 +509,7 @@ __global__ __launch_bounds__(kSelectThreads) void seed_select_kernel(const doubl
 template <bool SCREEN, bool DRAW>
 __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
                                                            const __bf16* __restrict__ xh, int dpb,
-                                                           const float* __restrict__ err,
-                                                           const double* __restrict__ scale, double u,
+                                                           const float2* __restrict__ err, double u,
                                                            int32_t* __restrict__ centre, int first,
                                                            const double* __restrict__ bsum_in, int64_t nb,
                                                            const double* __restrict__ dist2_in,
@@ -551,9 +550,10 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
 #pragma unroll
     for (int o = SL / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, SL);
     if (sl == 0 && p < here) {
-      const double low = sqrt((double)acc) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)err[i] - (double)err[c];
-      const double f = *scale;
-      const bool stands = acc >= kScreenFloor && low > 0.0 && low * low >= pts[p] * (f * f) * (1.0 + 1e-6);
+      const float2 mine = err[i];
+      const double low = sqrt((double)acc) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)mine.x - (double)err[c].x;
+      const double l = ldexp(low, -(int)mine.y);
+      const bool stands = acc >= kScreenFloor && low > 0.0 && l * l >= pts[p] * (1.0 + 1e-6);
       if (!stands) todo[atomicAdd(&ntodo, 1)] = p;
     }
     __syncthreads();
@@ -768,7 +768,7 @@ size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen) {
   // mean[ldx] | sums[kSeedParts][ldx] | tops[kSeedParts] | scale | err[n] | xh[n][dpb]
   const size_t nb = (size_t)((n + kSeedPoints - 1) / kSeedPoints);
   size_t bytes = 2 * ((size_t)n + nb) * 8 + 1024;
-  if (screen && seed_screened(n, d, k)) bytes += (size_t)(ldx + 1) * 8 * (kSeedParts + 1) + (size_t)n * (4 + 2 * (size_t)seed_dpb(d)) + 1024;
+  if (screen && seed_screened(n, d, k)) bytes += (size_t)(ldx + 1) * 8 * (kSeedParts + 1) + (size_t)n * (8 + 2 * (size_t)seed_dpb(d)) + 1024;
   return bytes;
 }
 
@@ -782,9 +782,9 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
   double* dist2[2] = {static_cast<double*>(work), static_cast<double*>(work) + n + nb};
   double* mean = dist2[1] + n + nb;
   double* sums = mean + ldx;
-  double* tops = sums + (size_t)kSeedParts * ldx;
-  double* scale = tops + kSeedParts;
-  float* err = reinterpret_cast<float*>(scale + 1);
+  uint32_t* tops = reinterpret_cast<uint32_t*>(sums + (size_t)kSeedParts * ldx);
+  double* scale = reinterpret_cast<double*>(tops + kSeedParts);
+  float2* err = reinterpret_cast<float2*>(scale + 1);
   __bf16* xh = reinterpret_cast<__bf16*>(((uintptr_t)(err + n) + 15) / 16 * 16);
   const int dpb = seed_dpb(d);
   const bool screened = screen && seed_screened(n, d, k), draws = nb <= kDrawBlocks;
@@ -805,7 +805,7 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
     if (i > 1) at ^= 1;
 #define SC_SEED(SCR, DRW)                                                                                               \
   hipLaunchKernelGGL((seed_distance_kernel<SCR, DRW>), dim3((unsigned)nb), dim3(kT), 0, st, x, ldx, d, n, xh, dpb, err, \
-                     scale, u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], dist2[at] + n)
+                     u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], dist2[at] + n)
     if (screened && i > 1) {
       if (draw) SC_SEED(true, true); else SC_SEED(true, false);
     } else {
