@@ -1921,15 +1921,16 @@ struct KMeans {
     DevBuf<double> ct, cnorm, part;
     DevBuf<int32_t> start;
     DevBuf<int> changes;
-    DevBuf<char> work;
+    DevBuf<char> work, lwork;
     PinnedBuf<int> hchanges;
     ct.alloc((size_t)ldx * ldc);
     cnorm.alloc((size_t)k);
     start.alloc((size_t)k + 1);
     changes.alloc(kChangeInts);
     hchanges.alloc(kChangeInts);
-    const size_t wb = kmeans_update_workspace(n, ldx, k);
+    const size_t wb = kmeans_update_workspace(n, ldx, k), lwb = label_workspace(n, ldx, k);
     work.alloc(wb);
+    if (lwb) lwork.alloc(lwb);
     HIP_TRY(launch_fill_int32(labels, n, -1, 0, st));
     int iters = 0, converged = 0, last_changes = 0;
     const bool timing = stats && stats->timing;
@@ -1954,7 +1955,7 @@ struct KMeans {
         HIP_TRY(hipEventCreate(&events.v.back().b));
         HIP_TRY(hipEventRecord(events.v.back().a, st));
       }
-      HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, labels, changes.p, st));
+      HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, lwork.p, lwb, labels, changes.p, st));
       if (timing) HIP_TRY(hipEventRecord(events.v.back().b, st));
       dist_bytes += 8.0 * ((double)n * d + (double)k * d) + 8.0 * (double)n;
       dist_flops += 2.0 * (double)n * k * d;

@@ -248,9 +248,10 @@ constexpr int kChangeSlots = 64, kChangeStride = 32, kChangeInts = kChangeSlots 
 hipError_t launch_centroid_operand(const double* c, int64_t ldx, int k, int d, int dpad, double* ct, int64_t ldc,
                                    double* cnorm, int* changes, hipStream_t st);
 // label[i] = arg-min_j cnorm[j] - 2 (x ct)[i, j] (first on ties); changes += number of labels that changed.  x: 32-byte
-// aligned, ldx % 4 == 0, zero padded; ct: ldx rows
+// aligned, ldx % 4 == 0, zero padded; ct: ldx rows; work: label_workspace bytes
+size_t label_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_label(const double* x, int64_t ldx, int64_t n, const double* ct, int64_t ldc, int k, const double* cnorm,
-                        int32_t* label, int* changes, hipStream_t st);
+                        void* work, size_t work_bytes, int32_t* label, int* changes, hipStream_t st);
 hipError_t launch_fill_int32(int32_t* a, int64_t n, int32_t value, int use_iota, hipStream_t st);
 // centres = means of their points (grouped by label, fixed summation order); empty clusters keep their centre.  ct, cnorm
 // and changes as launch_centroid_operand would then make them.  work: kmeans_update_workspace(n, ldx, k) bytes; start:

@@ -991,24 +991,31 @@ struct LabelBest {
         }
     }
   }
+  // the best of the 16 lanes that look at a point together, on all of them
+  __device__ __forceinline__ void meet() {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr)
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+          const double ob = __shfl_xor(v[mt][rr], o, 16);
+          const int oc = __shfl_xor(j[mt][rr], o, 16);
+          if (ob < v[mt][rr] || (ob == v[mt][rr] && oc < j[mt][rr])) {
+            v[mt][rr] = ob;
+            j[mt][rr] = oc;
+          }
+        }
+  }
   // labels of the points row0 .. row0 + 16 MT - 1; returns how many changed (the same on every lane)
   __device__ __forceinline__ int store(int64_t row0, int64_t n, int i, int g, int32_t* __restrict__ label) {
     int moved = 0;
+    meet();
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
-        double b = v[mt][rr];
-        int c = j[mt][rr];
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-          const double ob = __shfl_xor(b, o, 16);
-          const int oc = __shfl_xor(c, o, 16);
-          if (ob < b || (ob == b && oc < c)) {
-            b = ob;
-            c = oc;
-          }
-        }
+        const int c = j[mt][rr];
         const int64_t row = row0 + mt * 16 + 4 * rr + g;
         const bool mine = i == 0 && row < n;
         const bool differs = mine && label[row] != c;
@@ -1016,6 +1023,21 @@ struct LabelBest {
         moved += __popcll(__ballot(differs));
       }
     return moved;
+  }
+  // the same for a part of the centres: to be compared with the other parts'
+  __device__ __forceinline__ void park(int64_t row0, int64_t n, int i, int g, double* __restrict__ pv,
+                                       int32_t* __restrict__ pj) {
+    meet();
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int rr = 0; rr < 4; ++rr) {
+        const int64_t row = row0 + mt * 16 + 4 * rr + g;
+        if (i == 0 && row < n) {
+          pv[row] = v[mt][rr];
+          pj[row] = j[mt][rr];
+        }
+      }
   }
 };
 
@@ -1061,13 +1083,17 @@ __device__ __forceinline__ void label_mult_tiles(d4 (&acc)[1][4], const d4 (&a)[
   else label_mult<KG, 1>(acc, a, lds, kc16, i, g);
 }
 
-template <int KG>
+// PARTS: workgroup (., y) looks at the `per` centres from y * per on only (a multiple of 64) and leaves value and index of
+// the best at pv, pj [y][n].
+template <int KG, bool PARTS>
 __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const double* __restrict__ x, int64_t ldx,
                                                                           int64_t n, const double* __restrict__ ct,
                                                                           int64_t ldc, int k,
                                                                           const double* __restrict__ cnorm,
                                                                           int32_t* __restrict__ label,
-                                                                          int* __restrict__ changes) {
+                                                                          int* __restrict__ changes, int per,
+                                                                          double* __restrict__ pv,
+                                                                          int32_t* __restrict__ pj) {
   constexpr int KC = 16 * KG;
   __shared__ double lds[KC * 64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1077,14 +1103,16 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const 
   d4 a[KG];
   LabelBest<1> best;
   best.clear();
-  for (int n0 = 0; n0 < k; n0 += 64) {
+  const int j0 = PARTS ? (int)blockIdx.y * per : 0;
+  const int j1 = PARTS && j0 + per < k ? j0 + per : k;
+  for (int n0 = j0; n0 < j1; n0 += 64) {
     d4 acc[1][4];
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) acc[0][nt] = (d4){0.0, 0.0, 0.0, 0.0};
     for (int k0 = 0; k0 < kdim; k0 += KC) {
       const int kc = kdim - k0 < KC ? kdim - k0 : KC;
       const int kc16 = (kc + 15) & ~15;
-      if (n0 == 0 || kdim > KC) label_points<KG>(a, x, ldx, n, row0, k0, i, g);
+      if (n0 == j0 || kdim > KC) label_points<KG>(a, x, ldx, n, row0, k0, i, g);
       __syncthreads();
       stage_coefficients<4>(lds, ct, ldc, k0, kc, kc16, n0, k);
       __syncthreads();
@@ -1092,9 +1120,38 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const 
     }
     best.look(acc, n0, i, k, cnorm);
   }
-  const int moved = best.store(row0, n, i, g, label);
-  // one counter for everybody is 10 ns per wave, 87 us at 140,000 points
-  if (lane == 0 && moved) atomicAdd(&changes[(blockIdx.x % kChangeSlots) * kChangeStride], moved);
+  if constexpr (PARTS) {
+    best.park(row0, n, i, g, pv + blockIdx.y * n, pj + blockIdx.y * n);
+  } else {
+    const int moved = best.store(row0, n, i, g, label);
+    // one counter for everybody is 10 ns per wave, 87 us at 140,000 points
+    if (lane == 0 && moved) atomicAdd(&changes[(blockIdx.x % kChangeSlots) * kChangeStride], moved);
+  }
+}
+
+// labels from the best of every part of the centres, the lowest index on ties
+__global__ __launch_bounds__(kThreads) void label_join_kernel(const double* __restrict__ pv, const int32_t* __restrict__ pj,
+                                                              int64_t n, int parts, int32_t* __restrict__ label,
+                                                              int* __restrict__ changes) {
+  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  bool differs = false;
+  if (i < n) {
+    double v = pv[i];
+    int c = pj[i];
+#pragma unroll 4
+    for (int q = 1; q < parts; ++q) {
+      const double ov = pv[q * n + i];
+      const int oc = pj[q * n + i];
+      if (ov < v) {  // the parts come in the order of the centres
+        v = ov;
+        c = oc;
+      }
+    }
+    differs = label[i] != c;
+    label[i] = c;
+  }
+  const int moved = __popcll(__ballot(differs));
+  if ((threadIdx.x & 63) == 0 && moved) atomicAdd(&changes[(blockIdx.x % kChangeSlots) * kChangeStride], moved);
 }
 
 // --------------------------------------------------------------------------------------------
@@ -2035,17 +2092,56 @@ hipError_t launch_row_gemm(double* basis, int64_t n, int64_t ld, int acol0, int 
   return hipGetLastError();
 }
 
+namespace {
+
+// coordinates of a point that a wave keeps in registers, in groups of 16
+int label_groups16(int64_t ldx) { return ldx <= 16 ? 1 : (ldx <= 32 ? 2 : (ldx <= 64 ? 4 : 8)); }
+
+// Parts of the centres: few points leave most of the chip without a workgroup while each goes through all centres, 64 of
+// them and up to 128 coordinates at a time.  Three iterations on 5,000 points of 50 coordinates, 4,000 centres: 746 -> 363
+// us; 5,000 of 400, 300 centres: 555 -> 333 us; 20,000 of 300, 1,000 centres: 1,632 -> 1,207 us.  Below eight trips the
+// second launch costs what the parts gain (2,000 of 20, 300 centres), from 512 workgroups on the chip is full.
+int label_parts(int64_t n, int64_t ldx, int k) {
+  const int64_t blocks = ceil_div64(n, 64), groups = (k + 63) / 64, kc = 16 * label_groups16(ldx);
+  if (blocks >= 512 || groups * ceil_div64(ldx, kc) < 8) return 1;
+  const int64_t parts = 1024 / blocks < groups ? 1024 / blocks : groups;
+  const int64_t per = ceil_div64(groups, parts);
+  return (int)ceil_div64(groups, per);
+}
+
+}  // namespace
+
+size_t label_workspace(int64_t n, int64_t ldx, int k) {
+  const int parts = label_parts(n, ldx, k);
+  return parts > 1 ? (size_t)parts * (size_t)n * 12 : 0;
+}
+
 hipError_t launch_label(const double* x, int64_t ldx, int64_t n, const double* ct, int64_t ldc, int k, const double* cnorm,
-                        int32_t* label, int* changes, hipStream_t st) {
+                        void* work, size_t work_bytes, int32_t* label, int* changes, hipStream_t st) {
   if (n <= 0 || k <= 0 || ldx % 4 != 0 || reinterpret_cast<uintptr_t>(x) % 32 != 0) return hipErrorInvalidValue;
-#define SC_LABEL(KGV)                                                                                              \
-  hipLaunchKernelGGL((label_kernel<KGV>), dim3((unsigned)ceil_div64(n, 64)), dim3(kThreads), 0, st, x, ldx, n, ct, \
-                     ldc, k, cnorm, label, changes)
-  if (ldx <= 16) SC_LABEL(1);
-  else if (ldx <= 32) SC_LABEL(2);
-  else if (ldx <= 64) SC_LABEL(4);
-  else SC_LABEL(8);
+  const int parts = label_parts(n, ldx, k);
+  if (parts > 1 && work_bytes < label_workspace(n, ldx, k)) return hipErrorInvalidValue;
+  const int per = (int)ceil_div64((k + 63) / 64, parts) * 64;
+  double* pv = static_cast<double*>(work);
+  int32_t* pj = reinterpret_cast<int32_t*>(pv + (size_t)parts * n);
+#define SC_LABEL_P(KGV, PV)                                                                                            \
+  hipLaunchKernelGGL((label_kernel<KGV, PV>), dim3((unsigned)ceil_div64(n, 64), (unsigned)parts), dim3(kThreads), 0, st, \
+                     x, ldx, n, ct, ldc, k, cnorm, label, changes, per, pv, pj)
+#define SC_LABEL(KGV)                                                            \
+  do {                                                                           \
+    if (parts > 1) SC_LABEL_P(KGV, true); else SC_LABEL_P(KGV, false);           \
+  } while (0)
+  switch (label_groups16(ldx)) {
+    case 1: SC_LABEL(1); break;
+    case 2: SC_LABEL(2); break;
+    case 4: SC_LABEL(4); break;
+    default: SC_LABEL(8); break;
+  }
 #undef SC_LABEL
+#undef SC_LABEL_P
+  if (parts > 1)
+    hipLaunchKernelGGL(label_join_kernel, dim3((unsigned)ceil_div64(n, kThreads)), dim3(kThreads), 0, st, pv, pj, n, parts,
+                       label, changes);
   return hipGetLastError();
 }
 

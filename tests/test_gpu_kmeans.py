@@ -172,7 +172,9 @@ def test_kmeans_argument_errors(B):
 
 
 # the counting sort of the update at the edges of its blocks and of its range of clusters, and the radix sort beyond
-@pytest.mark.parametrize("n,d,k", [(1023, 1, 1), (1024, 2, 64), (1025, 5, 3), (4500, 9, 1024), (4500, 3, 1025), (3000, 129, 200)])
+# and the labelling in parts of the centres on both sides of where it begins, with a last part that is not full
+@pytest.mark.parametrize("n,d,k", [(2000, 10, 448), (2000, 10, 449), (5000, 130, 257), (1000, 300, 161), (32704, 20, 520),
+                                   (32705, 20, 520), (520, 7, 513), (70, 2, 70), (1023, 1, 1), (1024, 2, 64), (1025, 5, 3), (4500, 9, 1024), (4500, 3, 1025), (3000, 129, 200)])
 def test_update_over_its_ranges(B, n, d, k):
     rng = np.random.default_rng(n + d + k)
     x = rng.standard_normal((n, d))
@@ -285,3 +287,16 @@ def test_seeding_without_room_for_its_copy(B):
     del held
     torch.cuda.empty_cache()
     assert code == B.SC_OK and torch.equal(got[0], chosen) and torch.equal(got[1], cen)
+
+
+def test_labelling_in_parts_takes_the_lowest_index_on_ties(B):
+    """Equal centres in different parts of the centres: the first of them gets the points."""
+    rng = np.random.default_rng(8)
+    n, d, k = 700, 12, 700
+    x = rng.integers(-4, 5, size=(n, d)).astype(np.float64)       # all products exact
+    init = x[rng.permutation(n)].copy()
+    init[600:] = init[:100]
+    init[64:128] = init[:64]
+    labels_ref, _ = okm.assign(x, init)
+    labels, _, _, _ = B.sc_kmeans_lloyd(_dev(x), _dev(init), 1)
+    np.testing.assert_array_equal(labels.cpu().numpy(), labels_ref)
