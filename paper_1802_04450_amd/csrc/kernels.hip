@@ -494,7 +494,8 @@ __global__ __launch_bounds__(kThreads) void spmv_tile_kernel(const int64_t* __re
   }
 }
 
-// Tile shape by the average row length: the register buffer (U*64 entries) should hold an average tile with some room.
+// Tile shape by the average row length and the number of rows: the register buffer (U*64 entries) should hold an average
+// tile with some room.
 static hipError_t launch_spmv_tile(const int64_t* rowptr, const int32_t* col, const double* val, const double* s,
                                    int64_t n, const double* z, double* y, int64_t ldy, double avg_deg,
                                    hipStream_t st, double* zout = nullptr) {
@@ -504,19 +505,32 @@ static hipError_t launch_spmv_tile(const int64_t* rowptr, const int32_t* col, co
     hipLaunchKernelGGL((spmv_tile_kernel<RW_, U_>), dim3((unsigned)ceil_div64(ntiles, kThreads / 64)),              \
                        dim3(kThreads), 0, st, rowptr, col, val, s, z, y, ldy, n, ntiles, zout);                    \
   } while (0)
-  // register slots per lane and row of the tile.  The slots that a tile does not fill cost loads and LDS: with 22 slots
-  // for 13.5 a product with 50 entries a row (2,000,000 rows) ran at 4.05 TB/s, with 14 at 4.75; 127 entries a row, 18 for
-  // 17.2 slots: 4.55 -> 4.92 TB/s.
+  // Register slots per lane and row of the tile.  Slots that a tile does not fill cost loads and LDS, so tiles of 16 rows
+  // (of 8 beyond 81 entries a row) take 14, 18 or 22 of them: 200,000 rows of 50 entries, columns near the diagonal, 258 us
+  // with 22 for 13.5, 206 with 14.  But the smaller the tiles and the more of them are resident, the less of the gathered
+  // lines they share: where columns are far apart and there are rows enough for several rounds of workgroups, 14 and 18
+  // slots lose 5 to 15 % against 22.  Twice the rows in 28 or 36 slots (512 workgroups resident) loses on neither side.
+  // 2,000,000 rows of 50 entries, 22 slots, 14, 32 rows in 28: near the diagonal 280, 234, 228 us; anywhere in communities
+  // of 2,000 rows 297, 300, 256; within 20,000 rows 569, 644, 531.  100 entries, 22, 14, 16 rows in 28: 541, 439, 427; 567,
+  // 572, 471; 1,116, 1,272, 1,041 us.  It wants about 6 rounds (28 slots) or 8 (36) to spread evenly: 205,000 rows of 116
+  // entries within 20,000 rows 243, 256, 248 us.  At 60 to 67 and 119 to 133 entries 36 slots lose up to 9 % where columns
+  // are far apart, so 18 slots give way to 22 there, after 5 rounds of theirs (1,024 resident).
   const double need = avg_deg * 1.08 / 64.0;
+  constexpr int64_t kWaves = kThreads / 64;
+  auto rounds = [&](int rows, int64_t resident) { return (double)n / (double)(rows * kWaves * resident); };
   if (need * 32 <= 8) SC_LAUNCH_TILE(32, 8);
   else if (need * 32 <= 12) SC_LAUNCH_TILE(32, 12);
   else if (need * 32 <= 16) SC_LAUNCH_TILE(32, 16);
   else if (need * 32 <= 22) SC_LAUNCH_TILE(32, 22);
+  else if (need * 32 <= 28 && rounds(32, 512) >= 6) SC_LAUNCH_TILE(32, 28);
   else if (need * 16 <= 14) SC_LAUNCH_TILE(16, 14);
-  else if (need * 16 <= 18) SC_LAUNCH_TILE(16, 18);
+  else if (need * 32 <= 32 && rounds(32, 512) >= 8) SC_LAUNCH_TILE(32, 36);
+  else if (need * 16 <= 18 && rounds(16, 1024) < 5) SC_LAUNCH_TILE(16, 18);
   else if (need * 16 <= 22) SC_LAUNCH_TILE(16, 22);
+  else if (need * 16 <= 28 && rounds(16, 512) >= 6) SC_LAUNCH_TILE(16, 28);
   else if (need * 8 <= 14) SC_LAUNCH_TILE(8, 14);
-  else if (need * 8 <= 18) SC_LAUNCH_TILE(8, 18);
+  else if (need * 16 <= 32 && rounds(16, 512) >= 8) SC_LAUNCH_TILE(16, 36);
+  else if (need * 8 <= 18 && rounds(8, 1024) < 5) SC_LAUNCH_TILE(8, 18);
   else SC_LAUNCH_TILE(8, 22);
 #undef SC_LAUNCH_TILE
   return hipGetLastError();

@@ -111,11 +111,12 @@ def _regular_with_hub(n, deg, seed):
     return wl.symmetric_from_edges(u, v, rng.uniform(0.5, 2.0, size=u.size), n)
 
 
-@pytest.mark.parametrize("deg", [8, 18, 26, 36, 60, 100])
+@pytest.mark.parametrize("deg", [8, 18, 26, 36, 46, 60, 72, 100, 120, 150])
 def test_single_vector_product_over_average_degrees(B, deg):
-    """The single-vector product picks its tile height and register buffer from the average row length (six
-    combinations, boundaries at about 14.8, 22.2, 29.6, 40.7 and 81.5 entries per row): one graph per combination,
-    each with a hub row, with and without the scaling vector (the materialised operator), ragged last tile."""
+    """The single-vector product picks its tile height and register buffer from the average row length and the number of
+    rows (for few rows ten combinations, boundaries at about 14.8, 22.2, 29.6, 40.7, 51.9, 66.7, 81.5, 103.7 and 133.3
+    entries per row): one graph per combination, each with a hub row, with and without the scaling vector (the materialised
+    operator), ragged last tile."""
     n = 4099
     rp, c, v, _ = _regular_with_hub(n, deg, deg)
     avg = rp[-1] / n
@@ -131,6 +132,30 @@ def test_single_vector_product_over_average_degrees(B, deg):
     y2 = B.sc_spmm_normalized(drp, dc, vs, None, dx)
     torch.cuda.synchronize()
     assert np.max(np.abs(y2.cpu().numpy() - y0)) <= 1e-13 * np.abs(y0).max(), deg
+
+
+# the combinations for many rows, on both sides of where they begin, and a row longer than any register buffer
+@pytest.mark.parametrize("n,deg", [(393_215, 50), (393_217, 44), (393_249, 51), (524_287, 58), (524_301, 58), (327_679, 63),
+                                   (327_703, 63), (196_607, 100), (196_611, 84), (196_627, 103), (262_143, 117),
+                                   (262_147, 117), (163_839, 126), (163_849, 126)])
+def test_single_vector_product_of_many_rows(B, n, deg):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + deg)
+    lens = torch.randint(deg - 12, deg + 13, (n,), device="cuda:0", generator=gen)
+    lens[n // 3] = 30_000
+    lens[n - 1] = 0
+    rp = torch.zeros(n + 1, dtype=torch.int64, device="cuda:0")
+    rp[1:] = torch.cumsum(lens, 0)
+    nnz = int(rp[-1])
+    assert abs(nnz / n - deg) < 0.4
+    c = torch.randint(0, n, (nnz,), device="cuda:0", generator=gen, dtype=torch.int32)
+    v = torch.rand(nnz, dtype=torch.float64, device="cuda:0", generator=gen) + 0.5
+    x = torch.rand(n, dtype=torch.float64, device="cuda:0", generator=gen) + 0.5
+    row = torch.repeat_interleave(torch.arange(n, device="cuda:0"), lens)
+    ref = torch.zeros(n, dtype=torch.float64, device="cuda:0").index_add_(0, row, v * x[c.long()])
+    y = B.sc_spmm_normalized(rp, c, v, None, x)
+    torch.cuda.synchronize()
+    # sums of positive terms: len 2^-53 of the sum in either order
+    assert torch.all((y - ref).abs() <= 2.0 * lens.clamp(min=1) * 2.0 ** -53 * ref)
 
 
 @pytest.mark.parametrize("deg", [4, 8, 26, 60])
