@@ -75,11 +75,13 @@ double now_s() {
 // the releasing call can still be using a block when it is handed out again.  The cache holds at most
 // `limit` bytes per kind (default 4 GiB, SCEIG_CACHE_LIMIT_MB overrides, 0 switches caching off); sc_release_cache()
 // empties it.  A block that finds the cache full takes the place of the blocks that have lain there longest, of calls
-// before the one that releases it: a program that goes on to another problem shape would otherwise allocate on every call
-// for good (a 0.7 ms call on 200 MB blocks took 12 ms after a solve had filled the cache).  Blocks of the same call never
-// push one another out, so a repeated call finds what the one before left.
-std::atomic<uint64_t> call_count{0};
-thread_local uint64_t tl_call = 0;  // number of the entry point's call that this thread is in
+// at least kKeepCalls before the one that releases it (calls that release blocks at all are counted): a program that goes
+// on to another problem shape would otherwise allocate on every call for good (a 0.7 ms call on 200 MB blocks took 12 ms
+// after a solve had filled the cache).  Blocks of later calls stay, so that of up to three calls that take turns and are too
+// large for the cache together the first ones find theirs; were each to push out the others, all would allocate every time.
+constexpr uint64_t kKeepCalls = 3;
+std::atomic<uint64_t> releasing_calls{0};
+thread_local uint64_t tl_call = 0;  // number of the call that this thread is in, 0 until it releases its first block
 
 class BlockCache {
  public:
@@ -107,18 +109,20 @@ class BlockCache {
   void put(void* p, size_t bytes) {
     int dev = 0;
     (void)hipGetDevice(&dev);
+    if (tl_call == 0) tl_call = ++releasing_calls;
+    auto old = [&](const Block& b) { return b.call + kKeepCalls <= tl_call; };
     std::vector<Block> out;
     bool kept = false;
     {
       std::lock_guard<std::mutex> lock(mu_);
       if (bytes <= limit_) {
         size_t older = 0;
-        for (auto& kv : blocks_) older += kv.second.call != tl_call ? kv.first : 0;
+        for (auto& kv : blocks_) older += old(kv.second) ? kv.first : 0;
         if (held_ - older + bytes <= limit_) {
           while (held_ + bytes > limit_) {
             auto oldest = blocks_.end();
             for (auto it = blocks_.begin(); it != blocks_.end(); ++it)
-              if (it->second.call != tl_call && (oldest == blocks_.end() || it->second.call < oldest->second.call)) oldest = it;
+              if (old(it->second) && (oldest == blocks_.end() || it->second.call < oldest->second.call)) oldest = it;
             out.push_back(oldest->second);
             held_ -= oldest->first;
             blocks_.erase(oldest);
@@ -1827,7 +1831,7 @@ struct Solver {
 };
 
 int guarded(int (*fn)(void*), void* ctx) {
-  tl_call = ++call_count;
+  tl_call = 0;
   try {
     return fn(ctx);
   } catch (const ScError& e) {

@@ -271,3 +271,25 @@ def test_coo_to_csr_without_room_for_buckets(B):
     del held
     torch.cuda.empty_cache()
     assert code == B.SC_OK and nnz.value == ne and all(torch.equal(a, b) for a, b in zip(got, ref))
+
+
+def test_calls_that_take_turns_keep_their_blocks(B):
+    """Two calls of 2.5 and 2.2 GB of scratch do not fit the cache (4 GiB) together: the first one's block stays, so that
+    neither call changes what is free, however often they take turns (were they to push one another out, the second would
+    leave the difference)."""
+    B.sc_release_cache()
+    gen = torch.Generator(device="cuda:0").manual_seed(2)
+    rows = {ne: torch.randint(0, 4000, (ne,), generator=gen, device="cuda:0", dtype=torch.int32)
+            for ne in (70_000_000, 60_000_000)}
+    free = []
+    for ne in (70_000_000, 60_000_000) * 3:
+        r = rows[ne]
+        out = B.sc_coo_to_csr(r, r, torch.ones(ne, dtype=torch.float64, device="cuda:0"), 4000, False)
+        assert int(out[0][-1]) == ne
+        del out
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        free.append(torch.cuda.mem_get_info()[0])
+    B.sc_release_cache()
+    free.sort()                             # one reading may still see the test's own tensors
+    assert free[-2] - free[1] < 64 << 20, [f >> 20 for f in free]
