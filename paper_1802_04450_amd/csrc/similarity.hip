@@ -157,11 +157,11 @@ __global__ __launch_bounds__(kPartThreads) void bucket_scan_kernel(const int32_t
 }
 
 // key[lo .. lo + len - 1] into ascending order by the whole workgroup: a bitonic network whose comparators all point
-// upwards, so that those with a partner past the end can be left out.
-__device__ __forceinline__ void sort_run(uint64_t* __restrict__ key, int lo, int len) {
+// upwards, so that those with a partner past the end can be left out.  The entries are there for every wave on entry, and
+// again on return.
+__device__ __forceinline__ void sort_run(uint64_t* key, int lo, int len) {
   for (int k = 2; k < 2 * len; k *= 2) {
     for (int j = k / 2; j > 0; j /= 2) {
-      __syncthreads();
       const int flip = j == k / 2 ? k - 1 : j;  // the first stage of a merge pairs an entry with its mirror image
       for (int q0 = threadIdx.x; 2 * (q0 & ~(j - 1)) < len; q0 += 4 * kT) {  // pair q: entries with bit j clear and set
         uint64_t a[4], b[4];
@@ -171,21 +171,24 @@ __device__ __forceinline__ void sort_run(uint64_t* __restrict__ key, int lo, int
           const int q = q0 + u * kT;
           t[u] = 2 * (q & ~(j - 1)) | (q & (j - 1));
           o[u] = t[u] ^ flip;
-          if (o[u] >= len) o[u] = t[u] = 0;  // left out
+          if (o[u] >= len) o[u] = t[u] = 0;  // left out: a partner is never entry 0
           a[u] = key[lo + t[u]];
           b[u] = key[lo + o[u]];
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          if (a[u] > b[u]) {
+          if (o[u] > 0 && a[u] > b[u]) {  // what was read for a pair left out may just be changing
             key[lo + t[u]] = b[u];
             key[lo + o[u]] = a[u];
           }
         }
       }
+      // the wait is spelled out: with the barrier at the head of this loop the generated code (ROCm 7.2) had none for the LDS
+      // writes of the stage before
+      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+      __syncthreads();
     }
   }
-  __syncthreads();
 }
 
 // The rows of a bucket, each sorted by (column, payload), to their place in the CSR.  One workgroup per bucket: the

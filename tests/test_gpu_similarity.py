@@ -282,7 +282,7 @@ def test_calls_that_take_turns_keep_their_blocks(B):
     rows = {ne: torch.randint(0, 4000, (ne,), generator=gen, device="cuda:0", dtype=torch.int32)
             for ne in (70_000_000, 60_000_000)}
     free = []
-    for ne in (70_000_000, 60_000_000) * 3:
+    for ne in (70_000_000, 60_000_000) * 5:
         r = rows[ne]
         out = B.sc_coo_to_csr(r, r, torch.ones(ne, dtype=torch.float64, device="cuda:0"), 4000, False)
         assert int(out[0][-1]) == ne
@@ -291,5 +291,23 @@ def test_calls_that_take_turns_keep_their_blocks(B):
         torch.cuda.empty_cache()
         free.append(torch.cuda.mem_get_info()[0])
     B.sc_release_cache()
-    free.sort()                             # one reading may still see the test's own tensors
-    assert free[-2] - free[1] < 64 << 20, [f >> 20 for f in free]
+    # medians: a reading now and then still sees the test's own tensors
+    assert abs(np.median(free[0::2]) - np.median(free[1::2])) < 64 << 20, [f >> 20 for f in free]
+
+
+def test_coo_to_csr_sorts_many_long_rows_every_time(B):
+    """400 rows of 600 to 1,800 entries among short ones, thirty times: the slots come in another order each time, the result
+    may not."""
+    rng = np.random.default_rng(11)
+    n = 20_000
+    lens = rng.integers(600, 1800, size=400)
+    r = np.concatenate([np.repeat(np.arange(400) * 50, lens), rng.integers(0, n, size=200_000)]).astype(np.int64)
+    r = r[rng.permutation(r.size)]
+    c = rng.integers(0, n, size=r.size)
+    w = rng.uniform(0.1, 1.0, size=r.size)
+    rp0, co0, vo0 = _csr_by_sorting(r, c, w, n, False)
+    ref = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (rp0.astype(np.int64), co0.astype(np.int32), vo0)]
+    dr, dc, dw = _dev(r, torch.int32), _dev(c, torch.int32), _dev(w, torch.float64)
+    for _ in range(30):
+        got = B.sc_coo_to_csr(dr, dc, dw, n, False)
+        assert all(torch.equal(a, b) for a, b in zip(got, ref))
