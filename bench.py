@@ -260,7 +260,7 @@ def bench_kmeans(B, torch, args):
         # per launch: points read once, product block written once (8 n (d + k) bytes), 2 n k d flops: 0.25 k d / (d + k)
         # flop per byte = 12.5 at d = k = 100, above the fp64 ridge of 9.8 flop/B: the matrix cores bound it
         tf = st["distance_flops"] / st["t_distance"] / 1e12
-        out["roofline"] = {"bound": "mfma", "kernel": "row_gemm_kernel mode 1 (distance product V C^T, fp64 MFMA)",
+        out["roofline"] = {"bound": "mfma", "kernel": "label_kernel (distance product V C^T with its arg-min, fp64 MFMA)",
                            "achieved": tf, "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                            "frac": tf / FP64_MFMA_PEAK_TFLOPS, "traffic": None,
                            "launches_per_step": st["distance_launches"],
@@ -325,7 +325,7 @@ def bench_similarity(B, torch, args):
            "unit": "s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": sec * 1e3,
            "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "f64", "data": "synthetic",
            "config": {"workload": f"dti_like: n={n}, d={d}, pairs={ne}, nnz={int(rp[-1])}"},
-           "roofline": {"bound": "hbm", "kernel": "row_stats_kernel + edge_similarity_kernel (one sc_edge_similarity call)",
+           "roofline": {"bound": "hbm", "kernel": "row_stats_kernel, partition_kernel, edge_bucket_kernel, edge_list_kernel (one sc_edge_similarity call)",
                         "achieved": alg / t_sim / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                         "frac": alg / t_sim / 1e9 / HBM_PEAK_GBS, "traffic": None, "call_us": t_sim * 1e6,
                         "gathered_gbps": gathered / t_sim / 1e9}}
@@ -382,7 +382,7 @@ def bench_knn(B, torch, args):
            "value": sec, "unit": "s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": sec * 1e3,
            "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "f64", "data": "synthetic",
            "config": {"workload": f"{cfg.name} points: n={n}, d={d}, k_nn={k}, nnz={int(rp[-1])}"},
-           "roofline": {"bound": "mfma", "kernel": "knn_mfma_kernel (one sc_knn_search call, with row padding and norms)",
+           "roofline": {"bound": "mfma", "kernel": "screen_kernel in two passes and screen_rank_kernel (one sc_knn_search call, priced as the fp64 brute force)",
                         "achieved": flops / t_knn / 1e12, "peak": 78.6, "unit": "TFLOP/s",
                         "frac": flops / t_knn / 1e12 / 78.6, "traffic": None, "call_ms": t_knn * 1e3}}
     if not args.no_cpu_baseline:
