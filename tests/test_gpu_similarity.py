@@ -1,6 +1,7 @@
 """GPU parity of the similarity-graph step (Section IV-A, Algorithm 1; Algorithm 2 step 4) against the oracle,
 through the C ABI, and the chain points -> similarity -> CSR -> eigensolver input."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -289,9 +290,12 @@ def test_calls_that_take_turns_keep_their_blocks(B):
         del out
         torch.cuda.synchronize()
         torch.cuda.empty_cache()
-        free.append(torch.cuda.mem_get_info()[0])
+        readings = []
+        for _ in range(12):                 # what has just been given back is not always free at once
+            readings.append(torch.cuda.mem_get_info()[0])
+            time.sleep(0.05)
+        free.append(max(readings))
     B.sc_release_cache()
-    # medians: a reading now and then still sees the test's own tensors
     assert abs(np.median(free[0::2]) - np.median(free[1::2])) < 64 << 20, [f >> 20 for f in free]
 
 
