@@ -433,7 +433,10 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
  * rounded up to 8, 16, 32, 64 or 128 (to a multiple of 8 beyond), and for d <= 128 and n >= 512 up to
  * n * (4 * max(dp, 16) + 34) + 2^28 + 2^20 bytes more (a reduced-precision copy of the points that only screens the
  * candidates, and their lists; every distance that is compared or returned is the fp64 sum); where the latter cannot be
- * had, the call does without the screen, at a fraction of the speed.  Returns after the work on `stream` is done.
+ * had, the call does without the screen, at a fraction of the speed.  From n^2 max(dp, 16) of 6e10 on, up to
+ * n * (7 * max(dp, 16) + 40) + 2^30 + 2^28 + 2^21 bytes more (the points grouped by place, and for every group of queries the
+ * groups of points that can hold a neighbour); where these cannot be had, every pair is looked at.  Returns after the work on
+ * `stream` is done.
  */
 int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_nn, int32_t* idx_out, double* dist_out,
                   void* stream);

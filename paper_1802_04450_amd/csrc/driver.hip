@@ -2853,7 +2853,11 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
         left.alloc(kLostInts);
         int32_t *tiles = nullptr, *ntiles = nullptr;
         double* bound = nullptr;
-        HIP_TRY(launch_knn_screen(xp.p, c->n, c->d, c->k, work.p, left.p, &tiles, &ntiles, &bound, c->idx, c->dist, c->st));
+        const size_t gb = knn_group_workspace(c->n, c->d, c->k);
+        DevBuf<char> group;
+        const bool grouped = gb > 0 && group.try_alloc(gb);
+        HIP_TRY(launch_knn_screen(xp.p, c->n, c->d, c->k, work.p, grouped ? group.p : nullptr, left.p, &tiles, &ntiles,
+                                  &bound, c->idx, c->dist, c->st));
         HIP_TRY(hipMemcpyAsync(left.p, ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
         if (*left.p > 0) {

@@ -192,3 +192,15 @@ def test_knn_screen_scratch_is_what_the_header_says():
                 need = f(n, d, k)
                 assert need <= n * (4 * max(dp, 16) + 34) + 2 ** 28 + 2 ** 20, (n, d, k, need)
                 assert need == 0 or (d <= 128 and n >= 512)
+
+
+def test_knn_group_scratch_is_what_the_header_says():
+    f = _size_query("_ZN5sceig19knn_group_workspaceElii", ctypes.c_int64, ctypes.c_int32, ctypes.c_int32)
+    for n in (512, 20_000, 45_000, 62_000, 100_000, 2_000_000, 20_000_000, 400_000_000):
+        for d in (1, 8, 9, 17, 32, 100, 128, 129):
+            dp = next((p for p in (8, 16, 32, 64, 128) if d <= p), (d + 7) // 8 * 8)
+            for k in (1, 10, 60, 200):
+                need = f(n, d, k)
+                assert need <= n * (7 * max(dp, 16) + 40) + 2 ** 30 + 2 ** 28 + 2 ** 21, (n, d, k, need)
+                assert need == 0 or (d <= 128 and n * n * max(dp, 16) >= 6e10)
+    assert f(100_000, 32, 20) > 0

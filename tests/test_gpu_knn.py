@@ -243,3 +243,29 @@ def test_search_without_room_for_the_screen(B):
     del held
     torch.cuda.empty_cache()
     assert code == B.SC_OK and torch.equal(got[0], idx) and torch.equal(got[1], dist)
+
+
+# grouped points: cells with ragged last tiles, every padded dimension, clusters and none (then every pair is looked at),
+# outliers in the cells, a common offset, equal points, more neighbours than a cell has points, two rounds of queries
+@pytest.mark.parametrize("n,d,k,kind", [(62_000, 3, 10, "clusters"), (61_300, 16, 7, "clusters"), (45_001, 32, 20, "clusters"),
+                                        (43_400, 17, 5, "random"), (31_007, 64, 32, "clusters"), (22_000, 100, 12, "clusters"),
+                                        (63_000, 8, 200, "clusters"), (62_003, 2, 20, "outliers"), (45_000, 32, 6, "offset"),
+                                        (62_500, 5, 9, "equal"), (61_999, 12, 3, "line")])
+def test_grouped_search(B, n, d, k, kind):
+    rng = np.random.default_rng(3 * n + d)
+    x = rng.standard_normal((n, d))
+    if kind == "line":            # along a curve, in order
+        t = np.linspace(0.0, 30.0, n)[:, None]
+        x = np.sin(t * np.arange(1, d + 1) / d) * 5.0 + 1e-3 * x
+    elif kind != "random":
+        x += 15.0 * rng.standard_normal((90, d))[rng.integers(0, 90, n)]
+    if kind == "outliers":
+        x[::37] = 300.0 * rng.standard_normal((x[::37].shape[0], d))
+    elif kind == "offset":
+        x += 1e5
+    elif kind == "equal":
+        x[100:1100] = x[100]
+    idx, dist = B.sc_knn_search(_dev(x, torch.float64), k)
+    idx, dist = idx.cpu().numpy(), dist.cpu().numpy()
+    assert np.all(idx != np.arange(n)[:, None]) and np.all(np.diff(dist, axis=1) >= 0) and idx.min() >= 0
+    _sampled(x, k, np.concatenate([[0, 99, 100, 600, n - 1], rng.integers(0, n, 120)]), idx, dist)
