@@ -2890,7 +2890,7 @@ int sc_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int32_
   return guarded(
       [](void* p) {
         Ctx* c = static_cast<Ctx*>(p);
-        const size_t wb = knn_pairs_workspace(c->n);
+        const size_t wb = knn_pairs_workspace(c->n, c->k);
         DevBuf<char> work;
         DevBuf<int32_t> two;
         PinnedBuf<int32_t> host;

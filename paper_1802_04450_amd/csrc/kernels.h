@@ -315,8 +315,8 @@ hipError_t launch_knn_search(int64_t n, int d, int k, double* xp, const int32_t*
                              const double* bound, int32_t* idx_out, double* dist_out, hipStream_t st);
 // The undirected edges {i, j} (j in i's list or i in j's) once each as eu < ev, in row order of the emitting list;
 // val = the listed distance, or exp(-dist^2 / (2 sigma^2)) if sigma > 0.  eu, ev, val have room for n * k entries;
-// last_two (device int32[2]) receives two numbers whose sum is the pair count.  work: knn_pairs_workspace(n) bytes.
-size_t knn_pairs_workspace(int64_t n);
+// last_two (device int32[2]) receives two numbers whose sum is the pair count.  work: knn_pairs_workspace(n, k) bytes.
+size_t knn_pairs_workspace(int64_t n, int k);
 hipError_t launch_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int k, double sigma, void* work,
                                   size_t work_bytes, int32_t* eu, int32_t* ev, double* val, int32_t* last_two,
                                   hipStream_t st);
