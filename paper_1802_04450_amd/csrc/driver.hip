@@ -1925,7 +1925,7 @@ struct KMeans {
     DevBuf<double> ct, cnorm, part;
     DevBuf<int32_t> start;
     DevBuf<int> changes;
-    DevBuf<char> work, lwork;
+    DevBuf<char> work, lwork, swork;
     PinnedBuf<int> hchanges;
     ct.alloc((size_t)ldx * ldc);
     cnorm.alloc((size_t)k);
@@ -1935,6 +1935,10 @@ struct KMeans {
     const size_t wb = kmeans_update_workspace(n, ldx, k), lwb = label_workspace(n, ldx, k);
     work.alloc(wb);
     if (lwb) lwork.alloc(lwb);
+    // the reduced copy of the points is worth its three launches from the third step on
+    const size_t sb = max_iter >= 3 ? label_screen_workspace(n, ldx, k) : 0;
+    bool screen = sb > 0 && swork.try_alloc(sb);
+    if (screen) HIP_TRY(launch_label_copy(x.p, ldx, d, n, k, swork.p, st));
     HIP_TRY(launch_fill_int32(labels, n, -1, 0, st));
     int iters = 0, converged = 0, last_changes = 0;
     const bool timing = stats && stats->timing;
@@ -1959,7 +1963,10 @@ struct KMeans {
         HIP_TRY(hipEventCreate(&events.v.back().b));
         HIP_TRY(hipEventRecord(events.v.back().a, st));
       }
-      HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, lwork.p, lwb, labels, changes.p, st));
+      if (screen)
+        HIP_TRY(launch_label_screened(x.p, ldx, d, n, c, ct.p, ldc, k, cnorm.p, swork.p, labels, changes.p, st));
+      else
+        HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, lwork.p, lwb, labels, changes.p, st));
       if (timing) HIP_TRY(hipEventRecord(events.v.back().b, st));
       dist_bytes += 8.0 * ((double)n * d + (double)k * d) + 8.0 * (double)n;
       dist_flops += 2.0 * (double)n * k * d;
@@ -1968,6 +1975,8 @@ struct KMeans {
       ++iters;
       last_changes = 0;
       for (int s = 0; s < kChangeSlots; ++s) last_changes += hchanges.p[s * kChangeStride];
+      // where the screen leaves much to the fp64 labelling it only comes on top
+      if (screen && hchanges.p[kChangeUndecided] > n / 4) screen = false;
       if (last_changes == 0) {
         converged = 1;
         break;

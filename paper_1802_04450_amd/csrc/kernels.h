@@ -252,6 +252,19 @@ hipError_t launch_centroid_operand(const double* c, int64_t ldx, int k, int d, i
 size_t label_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_label(const double* x, int64_t ldx, int64_t n, const double* ct, int64_t ldc, int k, const double* cnorm,
                         void* work, size_t work_bytes, int32_t* label, int* changes, hipStream_t st);
+// the same for the points rows[0 .. *listed) (device) alone, *listed <= n
+hipError_t launch_label_listed(const double* x, int64_t ldx, int64_t n, const int32_t* rows, const int* listed,
+                               const double* ct, int64_t ldc, int k, const double* cnorm, int32_t* label, int* changes,
+                               hipStream_t st);
+// Labelling screened in bf16 (kmeans.hip): the same labels.  0 bytes where it does not pay.  launch_label_copy makes the
+// reduced copy of the points, once; launch_label_screened does a labelling step and leaves the number of points that the
+// screen could not decide, which were labelled in fp64, at changes[kChangeUndecided].
+constexpr int kChangeUndecided = 1;
+size_t label_screen_workspace(int64_t n, int64_t ldx, int k);
+hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, hipStream_t st);
+hipError_t launch_label_screened(const double* x, int64_t ldx, int d, int64_t n, const double* c, const double* ct,
+                                 int64_t ldc, int k, const double* cnorm, void* work, int32_t* label, int* changes,
+                                 hipStream_t st);
 hipError_t launch_fill_int32(int32_t* a, int64_t n, int32_t value, int use_iota, hipStream_t st);
 // centres = means of their points (grouped by label, fixed summation order); empty clusters keep their centre.  ct, cnorm
 // and changes as launch_centroid_operand would then make them.  work: kmeans_update_workspace(n, ldx, k) bytes; start:

@@ -1022,7 +1022,8 @@ struct LabelBest {
         }
   }
   // labels of the points row0 .. row0 + 16 MT - 1; returns how many changed (the same on every lane)
-  __device__ __forceinline__ int store(int64_t row0, int64_t n, int i, int g, int32_t* __restrict__ label) {
+  __device__ __forceinline__ int store(int64_t row0, int64_t n, const int32_t* __restrict__ rows, int i, int g,
+                                       int32_t* __restrict__ label) {
     int moved = 0;
     meet();
 #pragma unroll
@@ -1030,8 +1031,9 @@ struct LabelBest {
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
         const int c = j[mt][rr];
-        const int64_t row = row0 + mt * 16 + 4 * rr + g;
+        int64_t row = row0 + mt * 16 + 4 * rr + g;
         const bool mine = i == 0 && row < n;
+        if (rows && mine) row = rows[row];
         const bool differs = mine && label[row] != c;
         if (mine) label[row] = c;
         moved += __popcll(__ballot(differs));
@@ -1058,11 +1060,13 @@ struct LabelBest {
 // coordinates k0 .. k0 + 16 KG - 1 of the points row0 + i.  Columns past the end are read from the last four and set to
 // zero (an infinite coordinate must not meet a zero coefficient there), rows past the end are the last one again: their
 // results are dropped.
+// rows (may be null): the points' rows.
 template <int KG>
 __device__ __forceinline__ void label_points(d4 (&a)[KG], const double* __restrict__ x, int64_t ldx, int64_t n,
-                                             int64_t row0, int k0, int i, int g) {
+                                             const int32_t* __restrict__ rows, int64_t row0, int k0, int i, int g) {
   int64_t row = row0 + i;
   row = row < n ? row : n - 1;
+  if (rows) row = rows[row];
 #pragma unroll
   for (int h = 0; h < KG; ++h) {
     const int kcol = k0 + 16 * h + 4 * g;
@@ -1097,11 +1101,14 @@ __device__ __forceinline__ void label_mult_tiles(d4 (&acc)[1][4], const d4 (&a)[
   else label_mult<KG, 1>(acc, a, lds, kc16, i, g);
 }
 
+// LISTED: only the points rows[0 .. *listed), by any number of workgroups.
 // PARTS: workgroup (., y) looks at the `per` centres from y * per on only (a multiple of 64) and leaves value and index of
 // the best at pv, pj [y][n].
-template <int KG, bool PARTS>
+template <int KG, bool PARTS, bool LISTED>
 __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const double* __restrict__ x, int64_t ldx,
-                                                                          int64_t n, const double* __restrict__ ct,
+                                                                          int64_t n, const int32_t* __restrict__ rows,
+                                                                          const int* __restrict__ listed,
+                                                                          const double* __restrict__ ct,
                                                                           int64_t ldc, int k,
                                                                           const double* __restrict__ cnorm,
                                                                           int32_t* __restrict__ label,
@@ -1112,34 +1119,38 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const 
   __shared__ double lds[KC * 64];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int i = lane & 15, g = lane >> 4;
-  const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * 16;
+  if constexpr (LISTED) n = *listed;
+  const int32_t* __restrict__ at = LISTED ? rows : nullptr;
   const int kdim = (int)ldx;
-  d4 a[KG];
-  LabelBest<1> best;
-  best.clear();
   const int j0 = PARTS ? (int)blockIdx.y * per : 0;
   const int j1 = PARTS && j0 + per < k ? j0 + per : k;
-  for (int n0 = j0; n0 < j1; n0 += 64) {
-    d4 acc[1][4];
+  for (int64_t block = blockIdx.x; block * 64 < n; block += gridDim.x) {  // uniform over the workgroup; one trip without a list
+    const int64_t row0 = (block * 4 + wave) * 16;
+    d4 a[KG];
+    LabelBest<1> best;
+    best.clear();
+    for (int n0 = j0; n0 < j1; n0 += 64) {
+      d4 acc[1][4];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[0][nt] = (d4){0.0, 0.0, 0.0, 0.0};
-    for (int k0 = 0; k0 < kdim; k0 += KC) {
-      const int kc = kdim - k0 < KC ? kdim - k0 : KC;
-      const int kc16 = (kc + 15) & ~15;
-      if (n0 == j0 || kdim > KC) label_points<KG>(a, x, ldx, n, row0, k0, i, g);
-      __syncthreads();
-      stage_coefficients<4>(lds, ct, ldc, k0, kc, kc16, n0, k);
-      __syncthreads();
-      label_mult_tiles<KG>(acc, a, lds, kc16, i, g, (k - n0 + 15) / 16);
+      for (int nt = 0; nt < 4; ++nt) acc[0][nt] = (d4){0.0, 0.0, 0.0, 0.0};
+      for (int k0 = 0; k0 < kdim; k0 += KC) {
+        const int kc = kdim - k0 < KC ? kdim - k0 : KC;
+        const int kc16 = (kc + 15) & ~15;
+        if (n0 == j0 || kdim > KC) label_points<KG>(a, x, ldx, n, at, row0, k0, i, g);
+        __syncthreads();
+        stage_coefficients<4>(lds, ct, ldc, k0, kc, kc16, n0, k);
+        __syncthreads();
+        label_mult_tiles<KG>(acc, a, lds, kc16, i, g, (k - n0 + 15) / 16);
+      }
+      best.look(acc, n0, i, k, cnorm);
     }
-    best.look(acc, n0, i, k, cnorm);
-  }
-  if constexpr (PARTS) {
-    best.park(row0, n, i, g, pv + blockIdx.y * n, pj + blockIdx.y * n);
-  } else {
-    const int moved = best.store(row0, n, i, g, label);
-    // one counter for everybody is 10 ns per wave, 87 us at 140,000 points
-    if (lane == 0 && moved) atomicAdd(&changes[(blockIdx.x % kChangeSlots) * kChangeStride], moved);
+    if constexpr (PARTS) {
+      best.park(row0, n, i, g, pv + blockIdx.y * n, pj + blockIdx.y * n);
+    } else {
+      const int moved = best.store(row0, n, at, i, g, label);
+      // one counter for everybody is 10 ns per wave, 87 us at 140,000 points
+      if (lane == 0 && moved) atomicAdd(&changes[(block % kChangeSlots) * kChangeStride], moved);
+    }
   }
 }
 
@@ -2139,8 +2150,8 @@ hipError_t launch_label(const double* x, int64_t ldx, int64_t n, const double* c
   double* pv = static_cast<double*>(work);
   int32_t* pj = reinterpret_cast<int32_t*>(pv + (size_t)parts * n);
 #define SC_LABEL_P(KGV, PV)                                                                                            \
-  hipLaunchKernelGGL((label_kernel<KGV, PV>), dim3((unsigned)ceil_div64(n, 64), (unsigned)parts), dim3(kThreads), 0, st, \
-                     x, ldx, n, ct, ldc, k, cnorm, label, changes, per, pv, pj)
+  hipLaunchKernelGGL((label_kernel<KGV, PV, false>), dim3((unsigned)ceil_div64(n, 64), (unsigned)parts), dim3(kThreads), \
+                     0, st, x, ldx, n, nullptr, nullptr, ct, ldc, k, cnorm, label, changes, per, pv, pj)
 #define SC_LABEL(KGV)                                                            \
   do {                                                                           \
     if (parts > 1) SC_LABEL_P(KGV, true); else SC_LABEL_P(KGV, false);           \
@@ -2156,6 +2167,24 @@ hipError_t launch_label(const double* x, int64_t ldx, int64_t n, const double* c
   if (parts > 1)
     hipLaunchKernelGGL(label_join_kernel, dim3((unsigned)ceil_div64(n, kThreads)), dim3(kThreads), 0, st, pv, pj, n, parts,
                        label, changes);
+  return hipGetLastError();
+}
+
+hipError_t launch_label_listed(const double* x, int64_t ldx, int64_t n, const int32_t* rows, const int* listed,
+                               const double* ct, int64_t ldc, int k, const double* cnorm, int32_t* label, int* changes,
+                               hipStream_t st) {
+  if (n <= 0 || k <= 0 || ldx % 4 != 0 || reinterpret_cast<uintptr_t>(x) % 32 != 0) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)std::min<int64_t>(ceil_div64(n, 64), 512);
+#define SC_LABEL(KGV)                                                                                               \
+  hipLaunchKernelGGL((label_kernel<KGV, false, true>), dim3(grid), dim3(kThreads), 0, st, x, ldx, n, rows, listed, ct, \
+                     ldc, k, cnorm, label, changes, 0, nullptr, nullptr)
+  switch (label_groups16(ldx)) {
+    case 1: SC_LABEL(1); break;
+    case 2: SC_LABEL(2); break;
+    case 4: SC_LABEL(4); break;
+    default: SC_LABEL(8); break;
+  }
+#undef SC_LABEL
   return hipGetLastError();
 }
 

@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kT) void centroid_finish_kernel(const double* __res
 // kScreenFloor (below, what single squares lose to the denormal numbers is no longer negligible), and the lower bound has
 // to exceed the distance kept by 1e-6 of it: more than the fp64 sums are off.  A NaN on the way fails the test and the
 // point is computed; so is every point of data that have no such scale (scale 0: copies of zeros).
-// Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 11.6 us with the copy, which an XCD's L2 keeps
+// Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 14.2 us with the copy, which an XCD's L2 keeps
 // its part of from draw to draw (21 MB in all); what is left is the chain centre, its row, the point's row.  (Leaving points out by the triangle inequality with a kept assignment did
 // not shorten the pass: it saves no load of the first row.)
 constexpr int kSeedPoints = 64;   // points per block
@@ -319,6 +319,7 @@ constexpr int kExactLanes = 16;
 // draws: 1.64 against 1.88 ms; at 140,000 of 128, 128 draws: 2.82 against 2.64 ms).
 constexpr int64_t kDrawBlocks = 1800;
 
+constexpr int64_t kSeedWide = 768;
 constexpr float kScreenFloor = 1e-30f;
 
 // xh[i] = the centred and scaled point in bf16, padded with zeros to dpb coordinates (a multiple of 8); err[i] as above,
@@ -506,7 +507,9 @@ __global__ __launch_bounds__(kSelectThreads) void seed_select_kernel(const doubl
 // The pass for the centre *centre (DRAW false), or for the centre that this draw itself takes from the distances before it
 // (DRAW true; every workgroup finds it for itself from the block sums, workgroup 0 writes it down): dist2 and bsum go from
 // one buffer to the other.
-template <bool SCREEN, bool DRAW>
+// SUB blocks per workgroup.  AHEAD (up to 128 coordinates): a thread requests its points' copies before the draw, which does
+// not concern them.
+template <bool SCREEN, bool DRAW, int SUB, bool AHEAD>
 __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restrict__ x, int64_t ldx, int d, int64_t n,
                                                            const __bf16* __restrict__ xh, int dpb,
                                                            const float2* __restrict__ err, double u,
@@ -516,13 +519,33 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
                                                            double* __restrict__ dist2, double* __restrict__ bsum) {
   constexpr int SL = 4;  // lanes per point of the screen: 64 points at a time
   constexpr int EP = kSeedPoints / (kT / kExactLanes);  // points per 16 lanes
-  __shared__ double pts[kSeedPoints];
-  __shared__ int todo[kSeedPoints];
+  constexpr int P = SUB * kSeedPoints;
+  static_assert(SUB <= kT / 64, "a wave per block sum");
+  static_assert(SCREEN || SUB == 1, "the unscreened pass takes one block");
+  __shared__ double pts[P];
+  __shared__ int todo[P];
   __shared__ int ntodo;
-  const int64_t i0 = (int64_t)blockIdx.x * kSeedPoints;
-  const int here = n - i0 < kSeedPoints ? (int)(n - i0) : kSeedPoints;
+  const int64_t i0 = (int64_t)blockIdx.x * P;
+  const int here = n - i0 < P ? (int)(n - i0) : P;
   if (threadIdx.x == 0) ntodo = 0;
-  if (threadIdx.x < kSeedPoints) pts[threadIdx.x] = threadIdx.x < here && !first ? dist2_in[i0 + threadIdx.x] : 0.0;
+  if (threadIdx.x < P) pts[threadIdx.x] = threadIdx.x < here && !first ? dist2_in[i0 + threadIdx.x] : 0.0;
+  const int sp = threadIdx.x / SL, sl = threadIdx.x % SL;
+  union Piece { __bf16 b[8]; uint4 v; };
+  Piece ahead[AHEAD ? SUB : 1][4];
+  float2 own_err[SUB];
+  if constexpr (AHEAD) {
+#pragma unroll
+    for (int r = 0; r < SUB; ++r) {
+      const int p = sp + r * kSeedPoints;
+      const int64_t i = i0 + (p < here ? p : here - 1);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int t = sl * 8 + v * SL * 8;
+        ahead[r][v].v = *reinterpret_cast<const uint4*>(xh + i * dpb + (t < dpb ? t : 0));
+      }
+      own_err[r] = err[i];
+    }
+  }
   int64_t c;
   if constexpr (DRAW) {
     c = draw_point<kT>(bsum_in, nb, dist2_in, n, u);
@@ -533,28 +556,62 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
   }
   const int lane = threadIdx.x % kExactLanes, group = threadIdx.x / kExactLanes;
   if constexpr (SCREEN) {
-    const int p = threadIdx.x / SL, sl = threadIdx.x % SL;
-    const int64_t i = i0 + (p < here ? p : here - 1);
-    float acc = 0.0f;
-#pragma unroll 4
-    for (int t = sl * 8; t < dpb; t += SL * 8) {
-      union { __bf16 b[8]; uint4 v; } a, b;
-      a.v = *reinterpret_cast<const uint4*>(xh + i * dpb + t);
-      b.v = *reinterpret_cast<const uint4*>(xh + c * dpb + t);
+    float acc[SUB];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float diff = (float)a.b[q] - (float)b.b[q];
-        acc += diff * diff;
+    for (int r = 0; r < SUB; ++r) acc[r] = 0.0f;
+    if constexpr (AHEAD) {
+      Piece b[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int t = sl * 8 + v * SL * 8;
+        b[v].v = *reinterpret_cast<const uint4*>(xh + c * dpb + (t < dpb ? t : 0));
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if (v * SL * 8 >= dpb) break;  // uniform
+        const bool in = sl * 8 + v * SL * 8 < dpb;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const float bq = (float)b[v].b[q];
+#pragma unroll
+          for (int r = 0; r < SUB; ++r) {
+            const float diff = in ? (float)ahead[r][v].b[q] - bq : 0.0f;
+            acc[r] += diff * diff;
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < SUB; ++r) {
+        const int p = sp + r * kSeedPoints;
+        const int64_t i = i0 + (p < here ? p : here - 1);
+        own_err[r] = err[i];
+#pragma unroll 4
+        for (int t = sl * 8; t < dpb; t += SL * 8) {
+          Piece a, b;
+          a.v = *reinterpret_cast<const uint4*>(xh + i * dpb + t);
+          b.v = *reinterpret_cast<const uint4*>(xh + c * dpb + t);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            const float diff = (float)a.b[q] - (float)b.b[q];
+            acc[r] += diff * diff;
+          }
+        }
       }
     }
+    const double centre_err = (double)err[c].x;
 #pragma unroll
-    for (int o = SL / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, SL);
-    if (sl == 0 && p < here) {
-      const float2 mine = err[i];
-      const double low = sqrt((double)acc) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)mine.x - (double)err[c].x;
-      const double l = ldexp(low, -(int)mine.y);
-      const bool stands = acc >= kScreenFloor && low > 0.0 && l * l >= pts[p] * (1.0 + 1e-6);
-      if (!stands) todo[atomicAdd(&ntodo, 1)] = p;
+    for (int r = 0; r < SUB; ++r) {
+      const int p = sp + r * kSeedPoints;
+#pragma unroll
+      for (int o = SL / 2; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, SL);
+      if (sl == 0 && p < here) {
+        const float2 mine = own_err[r];
+        const double low = sqrt((double)acc[r]) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)mine.x - centre_err;
+        const double l = ldexp(low, -(int)mine.y);
+        const bool stands = acc[r] >= kScreenFloor && low > 0.0 && l * l >= pts[p] * (1.0 + 1e-6);
+        if (!stands) todo[atomicAdd(&ntodo, 1)] = p;
+      }
     }
     __syncthreads();
     const int count = ntodo;
@@ -591,13 +648,395 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
     }
   }
   __syncthreads();
-  if (threadIdx.x < 64) {
+  if (threadIdx.x < P) {  // whole waves: one per block
     double tot = pts[threadIdx.x];
     if (threadIdx.x < here) dist2[i0 + threadIdx.x] = tot;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+    const int64_t block = (int64_t)blockIdx.x * SUB + (threadIdx.x >> 6);
+    if ((threadIdx.x & 63) == 0 && block < nb) bsum[block] = tot;
   }
+}
+
+// ---- labelling, screened -------------------------------------------------------------------------------------------
+// Most points are clearly nearer to one centre than to all others, and a product of bf16 numbers shows which: with the
+// centred points and centres, scaled by a power of two (seed_mean_kernel's mean and scale), in two bf16 parts each,
+// x = h + m + r,
+//   v~(x, c) = h.h' + (h.m' + m.h') - |c|^2 / 2      ( |x - c|^2 = |x|^2 - 2 v )
+// is formed on the bf16 matrix cores, and a point whose largest v~ exceeds the second largest by more than twice the bound
+// E of the error of any of its v~ gets that centre's label: the fp64 labelling would give the same, E including what that
+// itself is off by.  Between two centres alone fp64 distances decide (screen_store); the other points are listed and labelled
+// by label_kernel.  With the norms ex, ec of what the parts leave
+// out and the largest norms C of a centre and Cu of an uncentred one (all measured when the parts are made),
+//   E = |x| ec + ex (C + ec) + 1.05 2^-18 |x| C    the parts, and m.m' (|m| <= 2^-9 |x|)
+//     + 1.05 (D + 8) 2^-23 |x| C                   D products summed in single precision, and the subtraction
+//     + C^2 2^-24                                  |c|^2 / 2 rounded
+//     + (2 d + 16) 2^-53 ((|x| + |mean|) Cu + Cu^2)   the fp64 sums of the uncentred labelling.
+// A NaN fails the comparison, and without a usable scale every point is listed.  Per step at 100,000 points,
+// 100 coordinates and 100 centres 29 us with the fp64 distances of the points between two centres (a tenth of them) and 5 us
+// for the rest, instead of 84 us all in fp64: 45 MB of the copy, the products (4 us) and the search (5 us) one after another.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+struct CentreBound {  // of one tile of 32 centres
+  float norm, err, uncentred, pad;
+};
+
+// The rows of x as the matrix instruction takes them: piece (t, s, part) = 64 lanes x 8 bf16, lane l = coordinates 16 s +
+// 8 (l / 32) + 0 .. 7 of row 32 t + l % 32, part 0 = h, part 1 = m; rows past the end are zeros.  bound[i] = (|y|, |y - h - m|)
+// rounded up, y the scaled row.  A wave per tile, or (CENTRES: few rows) a workgroup, which leaves half[i] = |y|^2 / 2 (3e38
+// past the end), most[t] = the largest norms of the tile, and *undecided = 0.
+template <bool CENTRES>
+__global__ __launch_bounds__(CENTRES ? 512 : kT) void label_copy_kernel(const double* __restrict__ x, int64_t ldx, int d,
+                                                        int64_t n, int64_t tiles, int ks, const double* __restrict__ mean,
+                                                        const double* __restrict__ scale, uint4* __restrict__ out,
+                                                        float2* __restrict__ bound, float* __restrict__ half,
+                                                        CentreBound* __restrict__ most, int* __restrict__ undecided) {
+  constexpr int W = CENTRES ? 8 : 1;  // waves per tile
+  __shared__ double parts[W][4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t = CENTRES ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * (kT / 64) + wave;
+  if (CENTRES && blockIdx.x == 0 && threadIdx.x == 0) *undecided = 0;
+  if (t >= tiles) return;  // uniform over the workgroup where it meets below
+  const int64_t i = 32 * t + (lane & 31);
+  const double f = *scale;
+  double moved = 0.0, size = 0.0, sum = 0.0, raw = 0.0;
+  for (int s = CENTRES ? wave : 0; s < ks; s += W) {
+    union { __bf16 b[8]; uint4 v; } h, m;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int c = 16 * s + 8 * (lane >> 5) + q;
+      const double xv = i < n && c < d ? x[i * ldx + c] : 0.0, mv = i < n && c < d ? mean[c] : 0.0;
+      const double v = xv * f, mu = mv * f, y = v - mu;
+      h.b[q] = (__bf16)(float)y;
+      const double rest = y - (double)(float)h.b[q];
+      m.b[q] = (__bf16)(float)rest;
+      const double off = rest - (double)(float)m.b[q];
+      moved += off * off;
+      size += v * v + mu * mu;
+      sum += y * y;
+      raw += v * v;
+    }
+    out[((t * ks + s) * 2) * 64 + lane] = h.v;
+    out[((t * ks + s) * 2 + 1) * 64 + lane] = m.v;
+  }
+  if constexpr (CENTRES) {
+    parts[wave][0][lane] = moved;
+    parts[wave][1][lane] = size;
+    parts[wave][2][lane] = sum;
+    parts[wave][3][lane] = raw;
+    __syncthreads();
+    if (wave) return;
+    for (int w = 1; w < W; ++w) {
+      moved += parts[w][0][lane];
+      size += parts[w][1][lane];
+      sum += parts[w][2][lane];
+      raw += parts[w][3][lane];
+    }
+  }
+  moved += __shfl_xor(moved, 32, 64);
+  size += __shfl_xor(size, 32, 64);
+  sum += __shfl_xor(sum, 32, 64);
+  float err = (float)((sqrt(moved) + 4.5e-16 * sqrt(size)) * 1.00001) + 1e-37f;
+  float norm = (float)(sqrt(sum) * 1.00001) + 1e-37f;
+  if constexpr (!CENTRES) {
+    if (lane < 32 && i < n) bound[i] = make_float2(norm, err);
+  } else {
+    raw += __shfl_xor(raw, 32, 64);
+    float unc = (float)(sqrt(raw) * 1.00001) + 1e-37f;
+    if (lane < 32) half[i] = i < n ? (float)(0.5 * sum) : 3.0e38f;
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) {  // a NaN stays
+      const float on = __shfl_xor(norm, o, 64), oe = __shfl_xor(err, o, 64), ou = __shfl_xor(unc, o, 64);
+      norm = on > norm || on != on ? on : norm;
+      err = oe > err || oe != oe ? oe : err;
+      unc = ou > unc || ou != ou ? ou : unc;
+    }
+    if (lane == 0) most[t] = CentreBound{norm, err, unc, 0.0f};
+  }
+}
+
+// What a lane knows of one point: the best two of the centres it has seen, and the value of the third.
+struct ScreenBest {
+  float best, second, third;
+  int at, at2;
+  __device__ __forceinline__ void clear() {
+    best = second = third = -INFINITY;
+    at = at2 = 0;
+  }
+  __device__ __forceinline__ void take(float v, int j) {
+    third = fmaxf(third, fminf(second, v));
+    at2 = v > best ? at : v > second ? j : at2;
+    second = fmaxf(second, fminf(best, v));
+    at = v > best ? j : at;
+    best = fmaxf(best, v);
+  }
+  // the products with the centres j0 + 8 r4 + r; their halved squared norms at chalf + j0
+  __device__ __forceinline__ void look(const f16v& acc, const float* __restrict__ chalf, int j0) {
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) {
+      const f4 h = *reinterpret_cast<const f4*>(chalf + j0 + 8 * r4);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) take(acc[4 * r4 + r] - h[r], j0 + 8 * r4 + r);
+    }
+  }
+  // what the lane's other half has seen of the same point
+  __device__ __forceinline__ void meet() {
+    const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64), ot = __shfl_xor(third, 32, 64);
+    const int oa = __shfl_xor(at, 32, 64), oa2 = __shfl_xor(at2, 32, 64);
+    take(ob, oa);
+    take(os, oa2);
+    third = fmaxf(third, ot);
+  }
+};
+
+// The largest norms of all centres (every lane alike); a NaN stays.
+__device__ __forceinline__ CentreBound centre_bound(const CentreBound* __restrict__ most, int ctiles, int lane) {
+  float n = 0.0f, e = 0.0f, u = 0.0f;
+  for (int t = lane; t < ctiles; t += 64) {
+    const CentreBound m = most[t];
+    n = m.norm > n || m.norm != m.norm ? m.norm : n;
+    e = m.err > e || m.err != m.err ? m.err : e;
+    u = m.uncentred > u || m.uncentred != m.uncentred ? m.uncentred : u;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float on = __shfl_xor(n, o, 64), oe = __shfl_xor(e, o, 64), ou = __shfl_xor(u, o, 64);
+    n = on > n || on != on ? on : n;
+    e = oe > e || oe != oe ? oe : e;
+    u = ou > u || ou != ou ? ou : u;
+  }
+  return CentreBound{n, e, u, 0.0f};
+}
+
+// |mean| in the screen's scale, rounded up (every lane alike)
+__device__ __forceinline__ float scaled_norm(const double* __restrict__ mean, int d, double f, int lane) {
+  double sum = 0.0;
+  for (int c = lane; c < d; c += 64) sum += mean[c] * f * (mean[c] * f);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  return (float)(sqrt(sum) * 1.00001);
+}
+
+// The labels of tile t's points.  Where only two centres are within 2 E, their distances are formed in fp64, 16 lanes per
+// point and four points at a time, and decide if they differ by more than they and the fp64 labelling can be off,
+// (8 d + 64) 2^-53 ((|x| + |mean|) + Cu)^2; what is left is listed.
+__device__ __forceinline__ void screen_store(ScreenBest mine, int64_t t, int64_t n, const double* __restrict__ x, int64_t ldx,
+                                             const double* __restrict__ centres, const float2* __restrict__ bound,
+                                             const CentreBound& c, float mnorm, int ks, int d, double f, int k, int lane,
+                                             int32_t* __restrict__ label, int32_t* __restrict__ rows,
+                                             int* __restrict__ changes, int slot) {
+  mine.meet();
+  const int64_t i = t * 32 + lane;
+  const bool live = lane < 32 && i < n;
+  bool clear = false, pair = false;
+  float norm = 0.0f;
+  const int before = live ? label[i] : 0;
+  if (live && f > 0.0) {
+    const float2 b = bound[i];
+    norm = b.x + mnorm;
+    const float e = b.x * c.err + b.y * (c.norm + c.err) +
+                    b.x * c.norm * (1.05f * 3.8146973e-06f + 1.05f * (float)(16 * ks + 8) * 1.1920929e-07f) +
+                    c.norm * c.norm * 5.9604645e-08f +
+                    (float)(2 * d + 16) * 1.1102230e-16f * (norm * c.uncentred + c.uncentred * c.uncentred);
+    clear = mine.best - mine.second > 2.0002f * e;
+    pair = !clear && mine.best - mine.third > 2.0002f * e && mine.at < k && mine.at2 < k;
+  }
+  unsigned long long pairs = __ballot(pair);
+  while (pairs) {  // uniform
+    const int sub = lane >> 4;
+    unsigned long long rest = pairs;
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (q < sub) rest &= rest - 1ull;
+    const bool have = rest != 0ull;  // uniform over the 16 lanes
+    const int from = have ? __ffsll((long long)rest) - 1 : 0;
+    const int j1 = __shfl(mine.at, from, 64), j2 = __shfl(mine.at2, from, 64);
+    const float pn = __shfl(norm, from, 64);
+    double d1 = 0.0, d2 = 0.0;
+    if (have) {
+      const double* __restrict__ xi = x + (t * 32 + from) * ldx;
+      const double *__restrict__ c1 = centres + (int64_t)j1 * ldx, *__restrict__ c2 = centres + (int64_t)j2 * ldx;
+#pragma unroll 4
+      for (int q = lane & 15; q < d; q += 16) {
+        const double v = xi[q], a = v - c1[q], b = v - c2[q];
+        d1 += a * a;
+        d2 += b * b;
+      }
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+      d1 += __shfl_xor(d1, o, 16);
+      d2 += __shfl_xor(d2, o, 16);
+    }
+    const double off = (8.0 * d + 64.0) * 1.1102230246251565e-16 * (double)(pn + c.uncentred) * (double)(pn + c.uncentred);
+    const bool first = (d2 - d1) * f * f > off, other = (d1 - d2) * f * f > off;
+    // to the point's own lane
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (!pairs) break;  // uniform
+      const int to = __ffsll((long long)pairs) - 1;
+      pairs &= pairs - 1ull;
+      const int qf = __shfl((int)first, 16 * q, 64), qo = __shfl((int)other, 16 * q, 64);
+      if (lane == to) {
+        clear = qf || qo;
+        if (qo) mine.at = mine.at2;
+      }
+    }
+  }
+  const bool differs = clear && before != mine.at;
+  if (differs) label[i] = mine.at;
+  const unsigned long long open = __ballot(live && !clear);
+  const int moved = __popcll(__ballot(differs));
+  int place = 0;
+  if (lane == 0) {
+    if (moved) atomicAdd(&changes[slot % kChangeSlots * kChangeStride], moved);
+    if (open) place = atomicAdd(&changes[kChangeUndecided], __popcll(open));
+  }
+  place = __builtin_amdgcn_readfirstlane(place);
+  if (live && !clear) rows[place + __popcll(open & ((1ull << lane) - 1ull))] = (int32_t)i;
+}
+
+#define MFMA_BF16(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
+
+// Up to 128 coordinates.  A wave keeps a tile of points in registers (B operands) and requests the next one while it goes
+// through the centres (A operands, two tiles at a time), which the workgroup holds in LDS: all of them where they fit
+// `chunk` tiles, else chunk by chunk.  A lane gets 16 centres of one point from every product.  Two waves per SIMD: eight
+// waves a workgroup and four per SIMD, without the request ahead, spill and took 43 instead of 29 us (100,000 points, 100
+// coordinates, 100 centres).
+template <int KS>
+__global__ __launch_bounds__(kT) __attribute__((amdgpu_waves_per_eu(2))) void label_screen_kernel(
+    const double* __restrict__ x, int64_t ldx,
+    const double* __restrict__ centres, int k, const bf16x8* __restrict__ xb, const float2* __restrict__ bound, int64_t n, int64_t tiles, int d,
+    const bf16x8* __restrict__ cb, const float* __restrict__ chalf, const CentreBound* __restrict__ most, int ctiles,
+    int chunk, const double* __restrict__ mean, const double* __restrict__ scale, int32_t* __restrict__ label,
+    int32_t* __restrict__ rows, int* __restrict__ changes) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  bf16x8* stage = reinterpret_cast<bf16x8*>(smem);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double f = *scale;
+  const float mnorm = scaled_norm(mean, d, f, lane);
+  const CentreBound cbound = centre_bound(most, ctiles, lane);
+  const int64_t stride = (int64_t)gridDim.x * (kT / 64);
+  bf16x8 bh[KS], bm[KS], nh[KS], nm[KS];
+  auto request = [&](int64_t t) __attribute__((always_inline)) {
+    t = t < tiles ? t : tiles - 1;  // past the end: computed, never stored
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      nh[s] = xb[((t * KS + s) * 2) * 64 + lane];
+      nm[s] = xb[((t * KS + s) * 2 + 1) * 64 + lane];
+    }
+  };
+  int64_t t = (int64_t)blockIdx.x * (kT / 64) + wave;
+  request(t);
+  bool staged = false;
+  for (int64_t g = (int64_t)blockIdx.x * (kT / 64); g < tiles; g += stride, t += stride) {  // uniform over the workgroup
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      bh[s] = nh[s];
+      bm[s] = nm[s];
+    }
+    if (g + stride < tiles) request(t + stride);
+    ScreenBest mine;
+    mine.clear();
+    for (int c0 = 0; c0 < ctiles; c0 += chunk) {
+      const int nc = ctiles - c0 < chunk ? ctiles - c0 : chunk;  // even
+      if (!staged || ctiles > chunk) {  // uniform
+        if (staged) __syncthreads();    // the chunk before has been read
+        for (int e = threadIdx.x; e < nc * KS * 128; e += kT) stage[e] = cb[(int64_t)c0 * KS * 128 + e];
+        __syncthreads();
+        staged = true;
+      }
+      for (int c = 0; c < nc; c += 2) {
+        f16v acc[2];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[a][r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s)  // the small cross terms first
+#pragma unroll
+          for (int a = 0; a < 2; ++a) {
+            const bf16x8 ah = stage[(((c + a) * KS + s) * 2) * 64 + lane], am = stage[(((c + a) * KS + s) * 2 + 1) * 64 + lane];
+            acc[a] = MFMA_BF16(am, bh[s], acc[a]);
+            acc[a] = MFMA_BF16(ah, bm[s], acc[a]);
+          }
+#pragma unroll
+        for (int s = 0; s < KS; ++s)
+#pragma unroll
+          for (int a = 0; a < 2; ++a) {
+            const bf16x8 ah = stage[(((c + a) * KS + s) * 2) * 64 + lane];
+            acc[a] = MFMA_BF16(ah, bh[s], acc[a]);
+          }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) mine.look(acc[a], chalf, 32 * (c0 + c + a) + 4 * (lane >> 5));
+      }
+    }
+    if (t < tiles)
+      screen_store(mine, t, n, x, ldx, centres, bound, cbound, mnorm, KS, d, f, k, lane, label, rows, changes,
+                   (int)blockIdx.x * (kT / 64) + wave);
+  }
+}
+
+// More coordinates: a wave takes two tiles of points against two tiles of centres at a time, all pieces from the L2.
+__global__ __launch_bounds__(kT) void label_screen_wide_kernel(
+    const double* __restrict__ x, int64_t ldx,
+    const double* __restrict__ centres, int k, const bf16x8* __restrict__ xb, const float2* __restrict__ bound, int64_t n, int64_t tiles, int ks, int d,
+    const bf16x8* __restrict__ cb, const float* __restrict__ chalf, const CentreBound* __restrict__ most, int ctiles,
+    const double* __restrict__ mean, const double* __restrict__ scale, int32_t* __restrict__ label,
+    int32_t* __restrict__ rows, int* __restrict__ changes) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t0 = ((int64_t)blockIdx.x * (kT / 64) + wave) * 2;
+  if (t0 >= tiles) return;
+  const int64_t t1 = t0 + 1 < tiles ? t0 + 1 : t0;
+  const double f = *scale;
+  const float mnorm = scaled_norm(mean, d, f, lane);
+  const CentreBound cbound = centre_bound(most, ctiles, lane);
+  ScreenBest mine[2];
+  mine[0].clear();
+  mine[1].clear();
+  for (int c0 = 0; c0 < ctiles; c0 += 2) {
+    f16v low[2][2], acc[2][2];  // [centre tile][point tile]: the cross terms apart, they are added last
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) low[a][q][r] = acc[a][q][r] = 0.0f;
+    for (int s = 0; s < ks; ++s) {
+      bf16x8 xh[2], xm[2], ch[2], cm[2];
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int64_t t = q ? t1 : t0;
+        xh[q] = xb[((t * ks + s) * 2) * 64 + lane];
+        xm[q] = xb[((t * ks + s) * 2 + 1) * 64 + lane];
+        ch[q] = cb[(((int64_t)(c0 + q) * ks + s) * 2) * 64 + lane];
+        cm[q] = cb[(((int64_t)(c0 + q) * ks + s) * 2 + 1) * 64 + lane];
+      }
+#pragma unroll
+      for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          low[a][q] = MFMA_BF16(cm[a], xh[q], low[a][q]);
+          low[a][q] = MFMA_BF16(ch[a], xm[q], low[a][q]);
+          acc[a][q] = MFMA_BF16(ch[a], xh[q], acc[a][q]);
+        }
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][q][r] += low[a][q][r];
+        mine[q].look(acc[a][q], chalf, 32 * (c0 + a) + 4 * (lane >> 5));
+      }
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (t0 + q < tiles)
+      screen_store(mine[q], t0 + q, n, x, ldx, centres, bound, cbound, mnorm, ks, d, f, k, lane, label, rows, changes,
+                   (int)blockIdx.x * (kT / 64) + wave);
 }
 
 // c[j, :] = x[index[j], :]
@@ -803,13 +1242,21 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
     const bool draw = draws && i > 1;
     const double *din = dist2[at], *bin = dist2[at] + n;
     if (i > 1) at ^= 1;
-#define SC_SEED(SCR, DRW)                                                                                               \
-  hipLaunchKernelGGL((seed_distance_kernel<SCR, DRW>), dim3((unsigned)nb), dim3(kT), 0, st, x, ldx, d, n, xh, dpb, err, \
-                     u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], dist2[at] + n)
+#define SC_SEED(SCR, DRW, SUBV, AHD)                                                                                     \
+  hipLaunchKernelGGL((seed_distance_kernel<SCR, DRW, SUBV, AHD>), dim3((unsigned)((nb + SUBV - 1) / SUBV)), dim3(kT), 0, \
+                     st, x, ldx, d, n, xh, dpb, err, u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], \
+                     dist2[at] + n)
     if (screened && i > 1) {
-      if (draw) SC_SEED(true, true); else SC_SEED(true, false);
+      // four blocks a workgroup: a quarter as many that read all block sums for the draw (15.6 -> 14.2 us a
+      // draw at 100,000 x 100), and fewer launches'
+      // worth of workgroups where there are few coordinates (300,000 x 20, no draw inside: 20.9 -> 17.5 us a pass;
+      // 140,000 x 128: 21.0 against 23.2 us, so not there)
+      if (draw && dpb <= 128 && nb >= kSeedWide) SC_SEED(true, true, 4, true);
+      else if (draw) SC_SEED(true, true, 1, false);
+      else if (dpb <= 64 && nb >= kSeedWide) SC_SEED(true, false, 4, true);
+      else SC_SEED(true, false, 1, false);
     } else {
-      if (draw) SC_SEED(false, true); else SC_SEED(false, false);
+      if (draw) SC_SEED(false, true, 1, false); else SC_SEED(false, false, 1, false);
     }
 #undef SC_SEED
   };
@@ -820,6 +1267,109 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
                          chosen + i);
   }
   return hipGetLastError();
+}
+
+namespace {
+
+// Where the fp64 product takes clearly more than the two launches of the screened form (n d k of 4e8: 33 us;
+// 50,000 x 64, 128 centres, 20 steps 2.63 -> 2.50 ms, 100,000 x 100, 100 centres 4.19 -> 3.25 ms).
+bool label_screened(int64_t n, int64_t ldx, int k) { return (double)n * (double)ldx * (double)k >= 4.0e8; }
+
+struct LabelScreen {
+  int ks = 0, ctiles = 0;
+  int64_t tiles = 0;
+  size_t off_cb = 0, off_bound = 0, off_half = 0, off_most = 0, off_mean = 0, off_sums = 0, off_tops = 0, off_scale = 0,
+         off_rows = 0, bytes = 0;
+};
+
+LabelScreen plan_label_screen(int64_t n, int64_t ldx, int k) {
+  LabelScreen p;
+  p.ks = (int)((ldx + 15) / 16);
+  p.tiles = (n + 31) / 32;
+  p.ctiles = (k + 63) / 64 * 2;
+  size_t off = (size_t)p.tiles * p.ks * 2048;
+  auto place = [&](size_t bytes) {
+    const size_t at = off;
+    off += (bytes + 255) / 256 * 256;
+    return at;
+  };
+  p.off_cb = place((size_t)p.ctiles * p.ks * 2048);
+  p.off_bound = place((size_t)n * sizeof(float2));
+  p.off_half = place((size_t)p.ctiles * 32 * 4);
+  p.off_most = place((size_t)p.ctiles * sizeof(CentreBound));
+  p.off_mean = place((size_t)ldx * 8);
+  p.off_sums = place((size_t)kSeedParts * ldx * 8);
+  p.off_tops = place((size_t)kSeedParts * 4);
+  p.off_scale = place(8);
+  p.off_rows = place((size_t)n * 4);
+  p.bytes = off;
+  return p;
+}
+
+}  // namespace
+
+size_t label_screen_workspace(int64_t n, int64_t ldx, int k) {
+  return label_screened(n, ldx, k) ? plan_label_screen(n, ldx, k).bytes : 0;
+}
+
+hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, hipStream_t st) {
+  const LabelScreen p = plan_label_screen(n, ldx, k);
+  char* w = static_cast<char*>(work);
+  double* mean = reinterpret_cast<double*>(w + p.off_mean);
+  double* sums = reinterpret_cast<double*>(w + p.off_sums);
+  uint32_t* tops = reinterpret_cast<uint32_t*>(w + p.off_tops);
+  double* scale = reinterpret_cast<double*>(w + p.off_scale);
+  hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums, tops);
+  hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, tops, kSeedParts, ldx, n, mean, scale);
+  hipLaunchKernelGGL(label_copy_kernel<false>, dim3((unsigned)((p.tiles + kT / 64 - 1) / (kT / 64))), dim3(kT), 0, st, x, ldx,
+                     d, n, p.tiles, p.ks, mean, scale, reinterpret_cast<uint4*>(w),
+                     reinterpret_cast<float2*>(w + p.off_bound), nullptr, nullptr, nullptr);
+  return hipGetLastError();
+}
+
+hipError_t launch_label_screened(const double* x, int64_t ldx, int d, int64_t n, const double* c, const double* ct,
+                                 int64_t ldc, int k, const double* cnorm, void* work, int32_t* label, int* changes,
+                                 hipStream_t st) {
+  const LabelScreen p = plan_label_screen(n, ldx, k);
+  char* w = static_cast<char*>(work);
+  const double* mean = reinterpret_cast<const double*>(w + p.off_mean);
+  const double* scale = reinterpret_cast<const double*>(w + p.off_scale);
+  float* half = reinterpret_cast<float*>(w + p.off_half);
+  CentreBound* most = reinterpret_cast<CentreBound*>(w + p.off_most);
+  int32_t* rows = reinterpret_cast<int32_t*>(w + p.off_rows);
+  const bf16x8* xb = reinterpret_cast<const bf16x8*>(w);
+  const float2* bound = reinterpret_cast<const float2*>(w + p.off_bound);
+  const bf16x8* cb = reinterpret_cast<const bf16x8*>(w + p.off_cb);
+  hipLaunchKernelGGL(label_copy_kernel<true>, dim3((unsigned)p.ctiles), dim3(512), 0, st, c, ldx, d, (int64_t)k,
+                     (int64_t)p.ctiles, p.ks, mean, scale, reinterpret_cast<uint4*>(w + p.off_cb), nullptr, half, most,
+                     changes + kChangeUndecided);
+  if (p.ks <= 8) {
+    // 64 KB of centres: two workgroups per compute unit, which take equally many tiles of points each
+    int chunk = 32 / p.ks / 2 * 2;
+    chunk = chunk < p.ctiles ? chunk : p.ctiles;
+    const int64_t groups = (p.tiles + kT / 64 - 1) / (kT / 64), rounds = (groups + 511) / 512;
+    const unsigned grid = (unsigned)((groups + rounds - 1) / rounds);
+#define SC_LABEL_SCREEN(KSV)                                                                                             \
+  hipLaunchKernelGGL(label_screen_kernel<KSV>, dim3(grid), dim3(kT), (size_t)chunk * KSV * 2048, st, x, ldx, c, k, xb, bound, n, \
+                     p.tiles, d, cb, half, most, p.ctiles, chunk, mean, scale, label, rows, changes)
+    switch (p.ks) {
+      case 1: SC_LABEL_SCREEN(1); break;
+      case 2: SC_LABEL_SCREEN(2); break;
+      case 3: SC_LABEL_SCREEN(3); break;
+      case 4: SC_LABEL_SCREEN(4); break;
+      case 5: SC_LABEL_SCREEN(5); break;
+      case 6: SC_LABEL_SCREEN(6); break;
+      case 7: SC_LABEL_SCREEN(7); break;
+      default: SC_LABEL_SCREEN(8); break;
+    }
+#undef SC_LABEL_SCREEN
+  } else {
+    hipLaunchKernelGGL(label_screen_wide_kernel, dim3((unsigned)((p.tiles + 2 * (kT / 64) - 1) / (2 * (kT / 64)))), dim3(kT),
+                       0, st, x, ldx, c, k, xb, bound, n, p.tiles, p.ks, d, cb, half, most, p.ctiles, mean, scale, label, rows, changes);
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_label_listed(x, ldx, n, rows, changes + kChangeUndecided, ct, ldc, k, cnorm, label, changes, st);
 }
 
 hipError_t launch_gather_rows(const double* x, int64_t ldx, const int32_t* index, int k, double* c, hipStream_t st) {

@@ -204,3 +204,17 @@ def test_knn_group_scratch_is_what_the_header_says():
                 assert need <= n * (7 * max(dp, 16) + 40) + 2 ** 30 + 2 ** 28 + 2 ** 21, (n, d, k, need)
                 assert need == 0 or (d <= 128 and n * n * max(dp, 16) >= 6e10)
     assert f(100_000, 32, 20) > 0
+
+
+def test_label_screen_scratch_is_what_the_header_says():
+    f = _size_query("_ZN5sceig22label_screen_workspaceElli", ctypes.c_int64, ctypes.c_int64, ctypes.c_int32)
+    used = 0
+    for n in (2_000, 50_000, 100_000, 500_000, 8_000_000):
+        for d in (1, 4, 31, 32, 100, 128, 129, 500, 2000):
+            for k in (1, 2, 64, 65, 100, 2000):
+                ldx = (d + 3) // 4 * 4
+                need = f(n, ldx, k)
+                used += need > 0
+                assert need <= 4 * (n + k + 64) * (d + 16) + 12 * n + 2100 * (d + 4) + 2 ** 20, (n, d, k, need)
+                assert need == 0 or n * ldx * k >= 4e8
+    assert used > 20

@@ -300,3 +300,41 @@ def test_labelling_in_parts_takes_the_lowest_index_on_ties(B):
     labels_ref, _ = okm.assign(x, init)
     labels, _, _, _ = B.sc_kmeans_lloyd(_dev(x), _dev(init), 1)
     np.testing.assert_array_equal(labels.cpu().numpy(), labels_ref)
+
+
+# the screened labelling: ragged tiles of points and of centres, one to all pieces of 16 coordinates, the wide form, centres in
+# more than one chunk of LDS, blobs with several centres each, data far from the origin, equal points, a NaN
+@pytest.mark.parametrize("n,d,k,kind", [(500_003, 5, 161, "blobs"), (262_147, 16, 97, "blobs"), (100_001, 33, 130, "blobs"),
+                                        (40_010, 100, 100, "split"), (33_333, 128, 101, "blobs"), (30_001, 129, 104, "blobs"),
+                                        (13_007, 300, 110, "split"), (200_001, 20, 100, "offset"), (60_000, 70, 96, "equal"),
+                                        (60_001, 70, 96, "nan"), (2_100, 130, 1500, "blobs")])
+def test_screened_labelling_is_the_nearest_centre(B, n, d, k, kind):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + d)
+    blobs = k // 4 if kind == "split" else k
+    cen = torch.randn((blobs, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    x = cen[torch.randint(0, blobs, (n,), device="cuda:0", generator=gen)]
+    x = x + 0.2 * torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    if kind == "offset":
+        x += 1e5
+    elif kind == "equal":
+        x[: n // 2] = x[0]
+    elif kind == "nan":
+        x[17, 3] = float("nan")
+    init = x[torch.randperm(n - 100, device="cuda:0", generator=gen)[:k] + 100].clone()
+    if kind == "equal":
+        init[1] = init[0]
+    labels, centres, code, stats = B.sc_kmeans_lloyd(x, init, 3)
+    # the labels are those of the last labelling step: its centres come out of a run one update shorter
+    _, before, _, st2 = B.sc_kmeans_lloyd(x, init, 2)
+    assert stats["iterations"] == 3 or stats["converged"]
+    cen_used = before if stats["iterations"] == 3 else centres
+    for r0 in range(0, n, 8192):
+        xr = x[r0:r0 + 8192]
+        v = (cen_used * cen_used).sum(1)[None, :] - 2.0 * (xr @ cen_used.T)
+        lab = labels[r0:r0 + 8192].long()
+        fine = torch.isfinite(v).all(1)
+        got = torch.gather(v, 1, lab.clamp(0, k - 1)[:, None])[:, 0]
+        # the label's value is the smallest, up to what the fp64 sums of either side are off by
+        size = (xr.norm(dim=1) + cen_used.norm(dim=1).max()) ** 2
+        assert bool((got - v.min(1)[0] <= (4 * d + 16) * 1.2e-16 * size)[fine].all()), r0
+        assert bool(((lab >= 0) & (lab < k))[fine].all())
