@@ -28,6 +28,7 @@
 #include <mutex>
 #include <new>
 #include <numeric>
+#include <queue>
 #include <vector>
 
 #include "../../include/sceig.h"
@@ -515,12 +516,13 @@ struct ResidentPlan {
   size_t lds_bytes = 0;
   bool usable = false;
   double est_step_s = 0.0;  // modelled time of one recurrence step
+  bool single = false;      // one step alone is worth the form's launch, too
   int64_t rest_row0 = 0;    // rows [rest_row0, n): blocks that fit no item, left to the product-per-step kernel
   // sliced copy of the blocks that are worked on in the sliced form (null if there are none)
   DevBuf<uint16_t> scol;
   DevBuf<double> sval;
   DevBuf<int64_t> slice_base;
-  DevBuf<int32_t> slice_len;
+  DevBuf<int32_t> slice_len, slice_first, row_extra;
 };
 
 int device_lds_limit() {
@@ -530,14 +532,28 @@ int device_lds_limit() {
   return lds;
 }
 
+// Blocks of more rows (whose two iterates of 8 columns exceed the LDS) have to be the matrix's last ones, so that they can
+// be left to the product-per-step kernel where that is the faster way for them.
+constexpr int kLargeBlock = 1272;
+
+// Modelled time that a compute unit takes for one entry of a sliced item of `cols` columns and one step: its LDS bytes at
+// 85 a clock (measured per step, beside the model with 1.5 us for a step's barriers: 100,000 rows in 100 components 12.5 us in
+// items of 4 columns, 19.5 in 8 or 16; 500,000 in 500 38 us in 8 and in 16; 212,000 in 234 13.8 us in 8).
+double sliced_entry_s(int cols) { return 8.0 * cols / 204e9; }
+constexpr double kSlicedStepS = 1.5e-6;
+// Making the sliced copy takes about 150 us, which a hundred filter steps have to bring in.
+constexpr double kSlicedCopyS = 1.5e-6;
+
 // Finds the diagonal blocks and their chunk counts on the device, sizes the items on the host.  A block goes, in this
 // order of preference, as items of 32 or 16 columns with its entries in registers (at most two chunks per lane
-// group), or as 8-column items in the sliced form (entries streamed from a sliced copy made here from `val`).  The
+// group), or in the sliced form (entries streamed from a sliced copy made here from `val`) with as many of 16, 8 or 4 columns
+// as LDS holds - or as the model prefers: narrower items read the entries more often and fill the chip better.  The
 // plan is usable when b is 16 or 32, every block fits LDS one way or the other, the sliced copy's padding stays below
-// a half, and the modelled step time beats the general product's: an item costs the LDS bytes its step reads (entries
-// times 8 bytes per column; the sliced form's streamed entries are charged as 48 more bytes each) at about half a
-// compute unit's LDS rate, the items spread over the 256 compute units, largest first; the general product gathers
-// 8 b bytes per entry from the L2 caches at the 12.5 TB/s measured for it, and no launch is shorter than about 4 us.
+// a half, and the modelled step time beats the general product's: an item with its entries in registers costs the LDS bytes
+// its step reads (entries times 8 bytes per column) at about half a compute unit's LDS rate, a sliced one
+// sliced_entry_s per entry and kSlicedStepS, the items spread over the 256 compute units, largest first; the general product gathers
+// 8 b bytes per entry from the L2 caches at the 14.5 TB/s measured for it (3.2 M entries, 16 columns: 28 us; 0.73 M: 11.5 us),
+// and a launch takes 3 us more.
 void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val, int64_t n, int64_t nnz, int b,
                    hipStream_t st, ResidentPlan* plan) {
   plan->usable = false;
@@ -557,124 +573,157 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   HIP_TRY(hipMemcpyAsync(&nblk, count.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (nblk <= 0 || (int64_t)nblk > (int64_t)1 << 22) return;  // the item table stays small
-  extra.alloc((size_t)2 * nblk);
+  extra.alloc((size_t)3 * nblk);
   HIP_TRY(launch_block_extra_chunks(rowptr, starts.p, nblk, n, extra.p, st));
-  std::vector<int32_t> hs((size_t)nblk + 1), hx((size_t)2 * nblk);
+  std::vector<int32_t> hs((size_t)nblk + 1), hx((size_t)3 * nblk);
   HIP_TRY(hipMemcpyAsync(hs.data(), starts.p, (size_t)nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(hx.data(), extra.p, (size_t)2 * nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipMemcpyAsync(hx.data(), extra.p, (size_t)3 * nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   hs[nblk] = (int32_t)n;
   struct Item {
-    int32_t row0, nrows, col0, shape;
+    int32_t row0, nrows, col0, shape, extra;
+    double cost;  // seconds per step
   };
-  std::vector<Item> items;
-  std::vector<int32_t> srow0, srows, sblk0, sblkrows;  // the slices of the blocks that go in the sliced form
-  std::vector<int> sliced_blocks;
-  const int srows_max = resident_slice_rows();
-  size_t lds_max = 0;
   const double avg_deg = (double)nnz / (double)n;
-  double sum_cost = 0.0, max_cost = 0.0;
-  int64_t rest_row0 = n;
-  for (int t = 0; t < nblk; ++t) {
-    const int nr = hs[t + 1] - hs[t];
-    int cl = 0, nx = 0;
-    for (int c = b == 32 ? 4 : 2; c >= 2; c /= 2) {  // widest lane group first
-      const int x = c == 4 ? hx[2 * t] : hx[2 * t + 1];
-      if (x >= (1 << 26) || nr + x > resident_max_chunks(c)) continue;
-      if (resident_item_lds_bytes(nr, c, x) > (size_t)lds_limit) continue;
-      cl = c;
-      nx = x;
-      break;
-    }
-    if (cl == 0 && (no_sliced || nr > 65535 || resident_sliced_lds_bytes(nr) > (size_t)lds_limit)) {
-      // fits no item: acceptable only as part of a run of such blocks at the end of the matrix (the solver's
-      // renumbering puts the large components there), which the product-per-step kernel then takes
-      if (rest_row0 == n) rest_row0 = hs[t];
-      continue;
-    }
-    if (rest_row0 < n) return;  // an item after a block without one: the blocks without items are not a suffix
-    if (cl == 0) {
-      // the sliced form: column indices inside the block take 16 bits, the item's first slice 27
-      if (srow0.size() + (size_t)nr / srows_max + 1 >= ((size_t)1 << 27)) return;
-      cl = 1;
-      nx = (int)srow0.size();
-      for (int r = 0; r < nr; r += srows_max) {
-        srow0.push_back(hs[t] + r);
-        srows.push_back(std::min(srows_max, nr - r));
-        sblk0.push_back(hs[t]);
-        sblkrows.push_back(nr);
+  // What the blocks make of items, the sliced ones of at most `widest` columns; the large ones (kLargeBlock) may be left to
+  // the product-per-step kernel.  False: the large blocks are not the matrix's last rows.
+  struct Split {
+    std::vector<Item> items;
+    std::vector<int32_t> blocks;  // the blocks that go in the sliced form
+    int64_t sliced_rows = 0, rest_row0 = 0, extra = 0, nslots = 0;
+    size_t lds = 0, sliced_blocks = 0;
+    double step_s = 0.0;
+  };
+  auto split = [&](int widest, bool leave_large, Split* out) -> bool {
+    out->rest_row0 = n;
+    bool large_seen = false;
+    for (int t = 0; t < nblk; ++t) {
+      const int nr = hs[t + 1] - hs[t];
+      const bool large = nr > kLargeBlock;
+      if (large_seen && !large) return false;
+      large_seen = large;
+      int cl = 0, nx = 0, bs = 0, x = 0;
+      size_t lds = 0;
+      for (int c = b == 32 ? 4 : 2; c >= 2 && cl == 0; c /= 2) {  // widest lane group first
+        const int chunks = c == 4 ? hx[3 * t] : hx[3 * t + 1];
+        if (chunks >= (1 << 26) || nr + chunks > resident_max_chunks(c)) continue;
+        lds = resident_item_lds_bytes(nr, c, chunks);
+        if (lds > (size_t)lds_limit) continue;
+        cl = c;
+        nx = chunks;
+        bs = 8 * c;
       }
-      sliced_blocks.push_back(t);
+      double cost = (double)nr * avg_deg * 8.0 * bs / 150e9;
+      for (int c = std::min(widest, b); c >= 4 && cl == 0 && !no_sliced && !(large && leave_large); c /= 2) {
+        x = hx[3 * t + 2];
+        lds = resident_sliced_lds_bytes(nr, x, c);
+        if (lds > (size_t)lds_limit) continue;
+        const int64_t first = out->nslots;
+        const int count = sliced_block_slots(nr, x, c);
+        // the item's word has 27 bits for the first slot
+        if (first + count >= ((int64_t)1 << 27) || out->extra + x > INT32_MAX) return false;
+        cl = sliced_shape(c);
+        nx = (int)first;
+        bs = c;
+        out->nslots += count;
+        out->blocks.insert(out->blocks.end(), {hs[t], nr, (int32_t)out->extra, x, c, (int32_t)first});
+        out->extra += x;
+        out->sliced_rows += nr;
+        out->sliced_blocks += 1;
+        cost = (double)nr * avg_deg * sliced_entry_s(c);
+      }
+      if (cl == 0) {
+        // without an item: acceptable only as part of a run of such blocks at the end of the matrix (the solver's
+        // renumbering puts the large components there), which the product-per-step kernel then takes
+        if (out->rest_row0 == n) out->rest_row0 = hs[t];
+        continue;
+      }
+      if (out->rest_row0 < n) return false;
+      for (int c0 = 0; c0 < b; c0 += bs) out->items.push_back(Item{hs[t], nr, c0, (int32_t)(cl | (nx << 4)), x, cost});
+      out->lds = std::max(out->lds, lds);
     }
-    const int bs = 8 * cl;
-    const double cost = (double)nr * avg_deg * (8.0 * bs + (cl == 1 ? 48.0 : 0.0));
-    for (int c0 = 0; c0 < b; c0 += bs) {
-      items.push_back(Item{hs[t], nr, c0, (int32_t)(cl | (nx << 4))});
-      sum_cost += cost;
+    std::stable_sort(out->items.begin(), out->items.end(), [](const Item& x, const Item& y) { return x.cost > y.cost; });
+    // the longest first on 256 compute units
+    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+    for (int q = 0; q < 256; ++q) busy.push(0.0);
+    for (const Item& it : out->items) {
+      const double at = busy.top() + it.cost;
+      busy.pop();
+      busy.push(at);
+      out->step_s = std::max(out->step_s, at);
     }
-    max_cost = std::max(max_cost, cost);
-    lds_max = std::max(lds_max, cl == 1 ? resident_sliced_lds_bytes(nr) : resident_item_lds_bytes(nr, cl, nx));
-  }
-  const double cu_rate = 150e9;  // bytes per second out of one compute unit's LDS, about half of its peak
-  if (items.empty()) return;
-  const double general_step_s = std::max(4e-6, (double)nnz * 8.0 * b / 12.5e12);
-  // the rows without items still take the general product, step by step, after the one launch of the items
-  const double rest_share = (double)(n - rest_row0) / (double)n;
-  plan->est_step_s = std::max(max_cost, sum_cost / 256.0) / cu_rate + 1e-6 +
-                     (rest_share > 0.0 ? std::max(4e-6, rest_share * general_step_s) : 0.0);
-  if (debug_on())
-    std::fprintf(stderr, "[sceig] resident filter plan: %d blocks (%zu sliced), %zu items, LDS %zu, modelled step %.1f us "
-                 "against %.1f us\n", nblk, sliced_blocks.size(), items.size(), lds_max, plan->est_step_s * 1e6,
-                 general_step_s * 1e6);
+    return true;
+  };
+  const double general_step_s = 3e-6 + (double)nnz * 8.0 * b / 14.5e12;
+  Split best;
+  bool have = false;
+  const char* forced = std::getenv("SCEIG_SLICED_COLUMNS");  // for tests of every width
+  for (int widest = 16; widest >= 4; widest /= 2)
+    for (int leave = 0; leave < 2; ++leave) {
+      if (forced && (std::atoi(forced) != widest || leave)) continue;
+      Split s;
+      if (!split(widest, leave != 0, &s) || s.items.empty()) continue;
+      // the rows without items still take the general product, step by step, after the one launch of the items
+      const double rest_share = (double)(n - s.rest_row0) / (double)n;
+      s.step_s += (s.sliced_blocks > 0 ? kSlicedStepS + kSlicedCopyS : 1e-6) +
+                  (rest_share > 0.0 ? std::max(4e-6, rest_share * general_step_s) : 0.0);
+      if (debug_on())
+        std::fprintf(stderr, "[sceig] resident filter plan: %d blocks (%zu sliced, at most %d columns), %zu items, LDS %zu, "
+                     "rest %.3f, modelled step %.1f us against %.1f us\n", nblk, s.sliced_blocks, widest, s.items.size(),
+                     s.lds, rest_share, s.step_s * 1e6, general_step_s * 1e6);
+      if (!have || s.step_s < best.step_s) best = std::move(s);
+      have = true;
+    }
+  if (!have) return;
+  std::vector<Item>& items = best.items;
+  const int64_t rest_row0 = best.rest_row0;
+  const size_t lds_max = best.lds;
+  plan->est_step_s = best.step_s;
+  // loading and storing the iterates takes about ten more microseconds, which d steps share and a single product does not
+  // (100,000 rows in 100 components: 25 us against 28 us by the general product; 30,000 in 20: 18 against 11.5)
+  plan->single = best.step_s + 10e-6 < general_step_s;
   if (!(plan->est_step_s < general_step_s) && !std::getenv("SCEIG_FORCE_RESIDENT")) return;
-  const int nslices = (int)srow0.size();
-  if (nslices > 0) {
-    DevBuf<int32_t> d_row0, d_rows, d_blk0, d_blkrows;
+  const int nslots = (int)best.nslots;
+  if (nslots > 0) {
+    DevBuf<int32_t> d_blocks, d_list;
     DevBuf<int64_t> d_entries;
-    DevBuf<char> swork;
-    d_row0.alloc((size_t)nslices);
-    d_rows.alloc((size_t)nslices);
-    d_blk0.alloc((size_t)nslices);
-    d_blkrows.alloc((size_t)nslices);
-    d_entries.alloc((size_t)nslices + 1);
-    plan->slice_base.alloc((size_t)nslices + 1);
-    plan->slice_len.alloc((size_t)nslices);
-    const size_t sw = sliced_scan_workspace(nslices);
+    DevBuf<char> swork, d_desc;
+    d_desc.alloc(sliced_desc_bytes(nslots));
+    d_blocks.alloc(best.blocks.size());
+    d_list.alloc((size_t)std::max<int64_t>(best.extra, 1));
+    d_entries.alloc((size_t)nslots + 1);
+    plan->row_extra.alloc((size_t)n);
+    plan->slice_base.alloc((size_t)nslots + 1);
+    plan->slice_len.alloc((size_t)nslots);
+    plan->slice_first.alloc((size_t)nslots);
+    const size_t sw = sliced_scan_workspace(nslots);
     swork.alloc(sw);
-    const size_t ib = (size_t)nslices * sizeof(int32_t);
-    HIP_TRY(hipMemcpyAsync(d_row0.p, srow0.data(), ib, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(d_rows.p, srows.data(), ib, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(d_blk0.p, sblk0.data(), ib, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(d_blkrows.p, sblkrows.data(), ib, hipMemcpyHostToDevice, st));
-    HIP_TRY(sliced_copy_layout(rowptr, d_row0.p, d_rows.p, nslices, plan->slice_len.p, d_entries.p, plan->slice_base.p,
-                               swork.p, sw, st));
+    const int nsliced = (int)best.sliced_blocks;
+    HIP_TRY(hipMemcpyAsync(d_blocks.p, best.blocks.data(), best.blocks.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    HIP_TRY(sliced_extra_rows(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, st));
+    HIP_TRY(sliced_copy_layout(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, nslots, d_desc.p, plan->slice_len.p,
+                               plan->slice_first.p, d_entries.p, plan->slice_base.p, swork.p, sw, st));
     int64_t total = 0;
-    HIP_TRY(hipMemcpyAsync(&total, plan->slice_base.p + nslices, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));  // also: the host vectors above have been read
+    HIP_TRY(hipMemcpyAsync(&total, plan->slice_base.p + nslots, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));  // also: the host vector above has been read
     // padding: against the sliced blocks' share of the matrix entries, estimated by their share of the rows
-    int64_t sliced_rows = 0;
-    for (int t : sliced_blocks) sliced_rows += hs[t + 1] - hs[t];
-    const double basis_entries = (double)nnz * (double)sliced_rows / (double)n;
+    const double basis_entries = (double)nnz * (double)best.sliced_rows / (double)n;
     if (debug_on())
-      std::fprintf(stderr, "[sceig] sliced copy: %d slices, %lld entries for %.0f of the matrix\n", nslices,
+      std::fprintf(stderr, "[sceig] sliced copy: %d slots, %lld entries for %.0f of the matrix\n", nslots,
                    (long long)total, basis_entries);
     if ((double)total > 1.5 * basis_entries && !std::getenv("SCEIG_FORCE_RESIDENT")) {
       plan->slice_base.release();
       plan->slice_len.release();
+      plan->slice_first.release();
+      plan->row_extra.release();
       return;
     }
-    const size_t tail = (size_t)sliced_copy_tail_entries();
-    plan->scol.alloc((size_t)total + tail);
-    plan->sval.alloc((size_t)total + tail);
-    HIP_TRY(hipMemsetAsync(plan->scol.p + total, 0, tail * sizeof(uint16_t), st));
-    HIP_TRY(hipMemsetAsync(plan->sval.p + total, 0, tail * sizeof(double), st));
-    HIP_TRY(sliced_copy_fill(rowptr, col, val, d_row0.p, d_rows.p, d_blk0.p, d_blkrows.p, nslices, plan->slice_base.p,
-                             d_entries.p, plan->scol.p, plan->sval.p, st));
+    plan->scol.alloc((size_t)total);
+    plan->sval.alloc((size_t)total);
+    HIP_TRY(sliced_copy_fill(rowptr, col, val, d_desc.p, d_list.p, plan->row_extra.p, nslots, plan->slice_base.p, d_entries.p, plan->scol.p, plan->sval.p,
+                             st));
     HIP_TRY(hipStreamSynchronize(st));  // the temporaries above are released on return
   }
-  std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& c) {
-    return (int64_t)a.nrows * (a.shape & 15) > (int64_t)c.nrows * (c.shape & 15);
-  });
   {
     // Workgroups go to the eight XCDs in turn (workgroup i to XCD i mod 8), each XCD with an L2 of its own.  The items
     // of one block (its column slices) read the same matrix entries, so they are placed eight apart: they run on the
@@ -695,9 +744,12 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
         if (r < queue[x].size()) placed.push_back(queue[x][r]);
     items.swap(placed);
   }
-  plan->items.alloc(items.size() * 4);
-  HIP_TRY(hipMemcpyAsync(plan->items.p, items.data(), items.size() * sizeof(Item), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipStreamSynchronize(st));  // `items` is pageable host memory
+  std::vector<int32_t> words;
+  words.reserve(items.size() * kItemInts);
+  for (const Item& it : items) words.insert(words.end(), {it.row0, it.nrows, it.col0, it.shape, it.extra});
+  plan->items.alloc(words.size());
+  HIP_TRY(hipMemcpyAsync(plan->items.p, words.data(), words.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+  HIP_TRY(hipStreamSynchronize(st));  // `words` is pageable host memory
   plan->nitems = (int)items.size();
   plan->lds_bytes = lds_max;
   plan->rest_row0 = rest_row0;
@@ -732,7 +784,8 @@ double* enqueue_cheb_filter(const int64_t* rowptr, const int32_t* col, const dou
     tm->begin(kFamSpmm);
     HIP_TRY(launch_cheb_resident(rowptr, col, val_scaled, z, out, ldo, b, d, 1.0 / e, 2.0 / e, c, resident->items.p,
                                  resident->nitems, resident->lds_bytes, resident->scol.p, resident->sval.p,
-                                 resident->slice_base.p, resident->slice_len.p, st, d32, rnd_key, use_rnd));
+                                 resident->slice_base.p, resident->slice_len.p, resident->slice_first.p,
+                                 resident->row_extra.p, st, d32, rnd_key, use_rnd));
     const int64_t r0 = resident->rest_row0;
     if (r0 < n) {
       // the blocks without an item: the recurrence step by step on their rows alone (their iterates rotate through the
@@ -950,12 +1003,13 @@ struct Solver {
   }
   // y (row-major, leading dimension ldy) = S x for the block whose packed operand is in z
   void spmm_from_z(double* y, int64_t ldy) {
-    if (val_s.p && resident.usable && resident.rest_row0 >= n && !no_resident_product) {
+    if (val_s.p && resident.usable && resident.single && resident.rest_row0 >= n && !no_resident_product) {
       // every diagonal block has work items of the LDS-resident form: a single product is that form's recurrence
       // with one step (u+ = 1 * (S u - 0 * u) - 0), read from LDS instead of gathered out of L2
       HIP_TRY(launch_cheb_resident(rowptr, col, val_s.p, z.p, y, ldy, b, 1, 1.0, 1.0, 0.0, resident.items.p,
                                    resident.nitems, resident.lds_bytes, resident.scol.p, resident.sval.p,
-                                   resident.slice_base.p, resident.slice_len.p, st));
+                                   resident.slice_base.p, resident.slice_len.p, resident.slice_first.p,
+                                   resident.row_extra.p, st));
     } else if (val_s.p) {
       HIP_TRY(launch_spmm_vals(rowptr, col, val_s.p, n, z.p, b, y, ldy, avg_deg, longrows.p, nlong, st));
     } else {
@@ -970,10 +1024,10 @@ struct Solver {
     val_p.alloc((size_t)nnz);
     old_of_new_d.alloc((size_t)n);
     new_of_old_d.alloc((size_t)n);
-    // components too large for any item of the LDS-resident filter go last, as one run of rows that the filter leaves
-    // to the product-per-step kernel (8-column items with two iterates: 128 bytes of LDS per row)
+    // components too large for most items of the LDS-resident filter go last, as one run of rows that it can leave
+    // to the product-per-step kernel
     int big_rows = 0;
-    if ((b == 16 || b == 32) && !(flags & SC_FLAG_NO_START_FILTER)) big_rows = (device_lds_limit() - 1024) / 128;
+    if ((b == 16 || b == 32) && !(flags & SC_FLAG_NO_START_FILTER)) big_rows = kLargeBlock;
     ncomp = reorder_csr(rowptr, col, val, n, nnz, rowptr_p.p, col_p.p, val_p.p, old_of_new_d.p, new_of_old_d.p,
                         (flags & SC_FLAG_COMPONENT_NULLSPACE) ? &comp_host : nullptr, b >= 8 ? 1 : 0, st, big_rows);
     rowptr = rowptr_p.p;
@@ -2298,8 +2352,8 @@ int sc_workspace_bytes(int64_t n, int64_t nnz, int32_t k, const sc_options* opt,
   total += up(N * 8);                       // scaling vector
   if (b >= 8) total += up(Z * 8) + up(N * 4) + up(long_row_list_workspace(n)) + 256;  // scaled values, long-row list
   if (b >= 8 && !(o.flags & SC_FLAG_NO_START_FILTER))  // diagonal-block search and the work items of the resident filter
-    total += up(diagonal_blocks_workspace(n)) + up(N * 4) + 256 + up(N * 8) + up(N * 18) +
-             up(Z * 15 + N * 2) + up(Z * 3 + N / 4) + 5 * up(N / 8 + 64) + up(sliced_scan_workspace((int)std::min<int64_t>(n, INT32_MAX)));  // + sliced copy (at most 1.5 x the entries plus look-ahead rounds) and its slice tables
+    total += up(diagonal_blocks_workspace(n)) + up(N * 4) + 256 + up(N * 8) + up(N * 18) + up(N * 4) +
+             up(Z * 15 + N * 2) + up(Z * 3 + N / 4) + 5 * up(N / 8 + 64) + up(sliced_scan_workspace((int)std::min<int64_t>(n, INT32_MAX)));  // + sliced copy (at most 1.5 x the entries, 10 bytes each) and its tables (56 bytes a slot for a slice; at most one per 16 rows and 16 more per block, of 124 rows and more)
   total += up(N * ld * 8) + up(N * (size_t)b * 8) + up(N * rot_cols * 8);  // basis, packed block, rotation workspace
   total += up((size_t)kMaxPartials * jmax * kPP * 8) + up((size_t)kGramPartials * kPP * kPP * 8) + 2 * up(jmax * kPP * 8);
   total += up((size_t)(m / b + 4) * kSlotDoubles * 8) + up(jmax * std::max<size_t>(rot_cols, (size_t)k) * 8);

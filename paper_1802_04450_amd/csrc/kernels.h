@@ -108,6 +108,7 @@ hipError_t launch_update_gram(double* basis, int64_t n, int64_t ld, int acol0, i
 // A work item is a diagonal block (or a 16-column slice of it) worked on by lane groups of cl = 4 lanes (32 columns)
 // or cl = 2 lanes (16 columns).  Its rows are cut into chunks of 8 cl entries; `extra` = chunks beyond the first,
 // summed over its rows.  LDS bytes of an item, and the largest number of chunks (rows + extra) one may have:
+constexpr int kItemInts = 5;
 size_t resident_item_lds_bytes(int nrows, int cl, int extra);
 int resident_max_chunks(int cl);
 // Diagonal blocks of a CSR matrix with a symmetric pattern: starts[0 .. *count) = the rows p (ascending) such that no
@@ -116,18 +117,19 @@ int resident_max_chunks(int cl);
 size_t diagonal_blocks_workspace(int64_t n);
 hipError_t diagonal_blocks(const int64_t* rowptr, const int32_t* col, int64_t n, void* work, size_t work_bytes,
                            int32_t* starts, int32_t* count, hipStream_t st);
-// extra[2 t], extra[2 t + 1] (device int32) = extra chunks of block t for chunks of 32 and of 16 entries
+// extra[3 t], extra[3 t + 1], extra[3 t + 2] (device int32) = extra chunks of block t for chunks of 32 and of 16 entries, and
+// the extra rows of the sliced form
 hipError_t launch_block_extra_chunks(const int64_t* rowptr, const int32_t* starts, int nblk, int64_t n, int32_t* extra,
                                      hipStream_t st);
 // y (n x b, leading dimension ldy >= b) = the recurrence applied to x (packed n x b): u_0 = x, u_1 = alpha_first (A u_0 - shift u_0),
 // u_{i+1} = alpha_rest (A u_i - shift u_i) - u_{i-1}; y = u_d.  A = the CSR matrix, whose rows [row0, row0 + nrows) of
-// every item form a diagonal block.  items: device int32[4 * nitems] = (row0, nrows, col0, cl | extra << 4) per
+// every item form a diagonal block.  items: device int32[kItemInts * nitems] = (row0, nrows, col0, cl | extra << 4, 0) per
 // workgroup, covering columns [col0, col0 + 8 cl); every (block, column) pair must be covered exactly once, extra must
 // be the block's extra-chunk count for chunks of 8 cl entries and nrows + extra <= resident_max_chunks(cl).
 // lds_bytes = the largest resident_item_lds_bytes over the items.  y must not alias x.
-// A sliced item (cl = 1; the word's upper bits carry the item's first slice, not a chunk count) covers 8 columns of a
-// block of up to 65,535 rows and reads its entries from the sliced copy (scol, sval, slice_base, slice_len; null when
-// no item is sliced).
+// A sliced item (cl = sliced_shape(cols); the word's upper bits carry the item's first slot, the last word the block's extra rows) covers `cols`
+// = 16, 8 or 4 columns of a block for which resident_sliced_lds_bytes is within the limit, and reads its entries from the
+// sliced copy (scol, sval, slice_base, slice_len, slice_first, row_extra; null when no item is sliced) made for that many columns.
 // d32 (0 <= d32 < d): the first d32 steps of the items with cl = 2 or 4 run in single precision (iterates and entries
 // rounded to float), the rest in double; sliced items take all steps in double.  0 gives the recurrence in double.
 // use_rnd != 0: x is not read; the operand is the random block of key rnd_key (random_block_key), entry by entry as
@@ -135,28 +137,32 @@ hipError_t launch_block_extra_chunks(const int64_t* rowptr, const int32_t* start
 hipError_t launch_cheb_resident(const int64_t* rowptr, const int32_t* col, const double* val, const double* x, double* y,
                                 int64_t ldy, int b, int d, double alpha_first, double alpha_rest, double shift, const int32_t* items,
                                 int nitems, size_t lds_bytes, const uint16_t* scol, const double* sval,
-                                const int64_t* slice_base, const int32_t* slice_len, hipStream_t st, int d32 = 0,
-                                uint64_t rnd_key = 0, int use_rnd = 0);
+                                const int64_t* slice_base, const int32_t* slice_len, const int32_t* slice_first,
+                                const int32_t* row_extra, hipStream_t st, int d32 = 0, uint64_t rnd_key = 0, int use_rnd = 0);
 // key of random block number `stream_id` under `seed`: entry i * b + t of the block launch_random_block writes is
 // 2 u - 1 with u the top 53 bits of mix(key + i * b + t)
 uint64_t random_block_key(uint64_t seed, uint64_t stream_id);
-// Sliced copy of diagonal blocks for the sliced form.  A slice is up to resident_slice_rows() consecutive rows of one
-// block: slice_row0 / slice_rows (device int32[nslices]) name its rows, slice_blk0 / slice_blk_rows its block.
-// sliced_copy_layout fills slice_len (longest row), slice_entries (int64[nslices + 1]: entries the slice takes in the
-// copy, padding included; last slot 0) and slice_base (int64[nslices + 1]: exclusive prefix sums; the last one is the
-// size of the copy).  sliced_copy_fill writes the copy: scol / sval with room for slice_base[nslices] +
-// sliced_copy_tail_entries() entries (the kernel's requests run that far past the last slice; initialise the tail).
-int resident_slice_rows();
-int64_t sliced_copy_tail_entries();
-size_t resident_sliced_lds_bytes(int nrows);
-size_t sliced_scan_workspace(int nslices);
-hipError_t sliced_copy_layout(const int64_t* rowptr, const int32_t* slice_row0, const int32_t* slice_rows, int nslices,
-                              int32_t* slice_len, int64_t* slice_entries, int64_t* slice_base, void* work,
-                              size_t work_bytes, hipStream_t st);
-hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const double* val, const int32_t* slice_row0,
-                            const int32_t* slice_rows, const int32_t* slice_blk0, const int32_t* slice_blk_rows,
-                            int nslices, const int64_t* slice_base, const int64_t* slice_entries, uint16_t* scol,
-                            double* sval, hipStream_t st);
+// Sliced copy of diagonal blocks for the sliced form.  A block with `extra` extra rows (the third count of
+// launch_block_extra_chunks) has sliced_block_slots slots for slices; blocks: device, for every sliced block (first row, rows,
+// place of its first extra row in a list for all blocks, extra rows, columns of its items, first slot).  sliced_extra_rows
+// makes that list and row_extra (int32[n]).  sliced_copy_layout fills, per slot, desc (sliced_desc_bytes of scratch),
+// slice_len, slice_first, slice_entries (int64[nslots + 1]: entries the slice takes in the copy, padding included) and
+// slice_base (int64[nslots + 1]: exclusive prefix sums; the last one is the size of the copy).  sliced_copy_fill writes the
+// copy: scol (8-byte aligned) and sval (16-byte aligned) with room for slice_base[nslots] entries.
+constexpr int kSliceBlockInts = 6;
+int sliced_shape(int cols);
+size_t resident_sliced_lds_bytes(int nrows, int extra, int cols);
+int sliced_block_slots(int nrows, int extra, int cols);
+size_t sliced_desc_bytes(int nslots);
+size_t sliced_scan_workspace(int nslots);
+hipError_t sliced_extra_rows(const int64_t* rowptr, const int32_t* blocks, int nblocks, int32_t* list, int32_t* row_extra,
+                             hipStream_t st);
+hipError_t sliced_copy_layout(const int64_t* rowptr, const int32_t* blocks, int nblocks, const int32_t* list,
+                              const int32_t* row_extra, int nslots, void* desc, int32_t* slice_len, int32_t* slice_first,
+                              int64_t* slice_entries, int64_t* slice_base, void* work, size_t work_bytes, hipStream_t st);
+hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const double* val, const void* desc,
+                            const int32_t* list, const int32_t* row_extra, int nslots, const int64_t* slice_base,
+                            const int64_t* slice_entries, uint16_t* scol, double* sval, hipStream_t st);
 
 // ---- connected components and locality reordering (setup) --------------------------------------
 // Renumbering from the component labels (label[i] = smallest node index of i's component), on the device:

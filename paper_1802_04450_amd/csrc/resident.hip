@@ -53,6 +53,7 @@ namespace {
 constexpr int kRT = 1024;  // threads per workgroup
 constexpr int kRK = 8;     // entries per lane and chunk
 constexpr int kRS = 2;     // chunks per lane group
+constexpr int kShape16 = 8, kShape8 = 9, kShape4 = 10;  // shape words of the sliced items
 
 __host__ __device__ inline size_t resident_lds_bytes(int nrows, int cl, int extra) {
   const size_t bs = (size_t)8 * cl;
@@ -378,161 +379,223 @@ __device__ __forceinline__ void resident_item(const int64_t* __restrict__ rowptr
   }
 }
 
-// The sliced form, for diagonal blocks whose entries do not fit the registers (up to about 1,250 rows): items of 8
-// columns, the iterates in LDS as above, the entries read again in every step - from a copy of the block made for
-// that (build_sliced_copy below): the block's rows in slices of 64, the k-th entries of a slice's rows next to each
-// other, rows padded to the slice's longest with zero entries, columns as 16-bit indices inside the block.  A wave
-// takes a slice, a lane a row: a round is one coalesced read of 64 (column, value) pairs, a 64-byte read of an operand
-// row from LDS per lane (the four 16-byte pieces in an order rotated by the lane index, which spreads the banks) and 8
-// multiply-adds; the row's sum never leaves the lane, so there are no partial sums to exchange.  The solver's
-// renumbering orders the rows of a component by length, which keeps the padding of kNN graphs at a few per cent; a
-// matrix whose padding exceeds a half is left to the product-per-step kernel by the planner.
-constexpr int kSliceRows = 64;
-constexpr int kSliceGroup = 8;  // rounds per register buffer of entries
-constexpr int kSliceOwn = 2;    // slices a wave may own: items of up to 16 * 2 * 64 = 2,048 rows
+// The sliced form, for diagonal blocks whose entries do not fit the registers: items of C = 16, 8 or 4 columns, one iterate u
+// in LDS (up to 1,270, 2,540 or 5,080 rows), the other one, u-, in the registers of the lanes that own its rows (only its
+// own row's recurrence reads it), and the entries read again in every step from a copy of the block made for that:
+//   * The block's rows in slices of RS = 64 / LPR rows, LPR = C / 4 lanes per row, four columns a lane; rows padded to the
+//     slice's longest with zero entries, in groups of four rounds: a lane gets a group's four column numbers with one 8-byte
+//     load and its values with two 16-byte loads, kSliceAhead groups before they are multiplied.  Columns are stored in units of 32 bytes of the iterate (16 bits).
+//   * A row's entries beyond kSliceLong are extra rows of their own (hubs of several hundred entries beside rows of thirty
+//     would be what a step waits for): extra rows have slices like others, a lane parks its sum in LDS, and the row's owner
+//     adds the sums in order once the step's reads are over.
+//   * The slices are dealt to the sixteen waves one by one, extra rows first, each to the wave with the least to do (a step
+//     lasts as long as its slowest wave); a wave's slices lie one behind the other in the copy, so that it reads its entries as
+//     one stream over slice and step boundaries.
+//   * A round is two 16-byte LDS reads of the operand row and four multiply-adds per lane; row sums never leave the lane.  An
+//     item is bound by these reads and by the entry stream out of the L2 / Infinity Cache; 16 columns read the stream once
+//     per step for all of a 16-column block, 4 columns make enough items where the blocks are few.
+//   * When a wave is through its slices its new rows wait in registers (where u- was) for a barrier, then change places with
+//     the old ones in LDS: what was u becomes u-.  (With both iterates in LDS, 8 columns and half as many rows, a lane per row
+//     and a fixed pair of slices per wave, a filter step of 500,000 rows in 500 components took 58 us for the 60 % of the
+//     rows that fitted and 53 us by the general product for the others; now 38 us for all of them.  100,000 rows in 100
+//     components: 12.5 us in items of 4 columns, 28 us by the general product.)
+constexpr int kSliceWaves = kRT / 64;
+constexpr int kSliceOwn = 5;    // slices of rows a wave may own
+constexpr int kSliceExtra = 5;  // slices of extra rows
+constexpr int kSliceLong = 64;  // entries of a row before its extra rows
+constexpr int kSliceAhead = 1;  // groups requested ahead of the one that is multiplied (2 and 3: 2 to 5 % slower, spills)
 
+__host__ __device__ inline int sliced_slices(int rows, int cols) { return (rows + 256 / cols - 1) / (256 / cols); }
+// places for slices that a wave has: its share, and one more up to three (more of them cost registers)
+__host__ __device__ inline int sliced_places(int slices, int most) {
+  const int share = (slices + kSliceWaves - 1) / kSliceWaves;
+  return share == 0 || share >= 3 || share >= most ? share : share + 1;
+}
+__host__ __device__ inline int sliced_slots(int rows, int cols) { return sliced_places(sliced_slices(rows, cols), kSliceOwn); }
+__host__ __device__ inline int sliced_extra_slots(int extra, int cols) {
+  return sliced_places(sliced_slices(extra, cols), kSliceExtra);
+}
+
+template <int C, int MAXS>
 __device__ __forceinline__ void resident_item_sliced(const uint16_t* __restrict__ scol, const double* __restrict__ sval,
                                                      const int64_t* __restrict__ slice_base,
                                                      const int32_t* __restrict__ slice_len,
                                                      const double* __restrict__ x, double* __restrict__ y, int64_t ldy, int b,
                                                      int d, double alpha_first, double alpha_rest, double shift,
-                                                     int row0, int nr, int col0, int slice0, unsigned char* smem,
-                                                     uint64_t rnd_key, int use_rnd) {
-  constexpr int BS = 8;  // columns of the item
-  constexpr int RW = BS / 2;
-  double* bufa = reinterpret_cast<double*>(smem);
-  double* bufb = bufa + (size_t)nr * BS;
+                                                     const int32_t* __restrict__ slice_first,
+                                                     const int32_t* __restrict__ row_extra, int row0, int nr, int col0,
+                                                     int slice0, int nx, unsigned char* smem, uint64_t rnd_key,
+                                                     int use_rnd) {
+  constexpr int LPR = C / 4, RS = 64 / LPR, NB = kSliceAhead + 1, MAXT = kSliceOwn + kSliceExtra;
+  double* u = reinterpret_cast<double*>(smem);
+  const int parked = nr * C * 8;  // byte offset of the extra rows' sums
+  int32_t* groups = reinterpret_cast<int32_t*>(u + (size_t)(nr + nx) * C);  // [wave][MAXT]
+  int32_t* places = groups + kSliceWaves * MAXT;                            // [wave][MAXT]: the slices' first rows
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int pc0 = (lane + 0) & 3, pc1 = (lane + 1) & 3, pc2 = (lane + 2) & 3, pc3 = (lane + 3) & 3;
-  const int pcs[4] = {pc0, pc1, pc2, pc3};
-  for (int idx = tid; idx < nr * BS; idx += kRT) {
-    const int r = idx / BS, t = idx - r * BS;
+  const int j = lane / LPR, h = lane % LPR;
+  for (int idx = tid; idx < nr * C; idx += kRT) {
+    const int r = idx / C, t = idx - r * C;
     const int64_t gi = (int64_t)(row0 + r) * b + col0 + t;
-    bufa[idx] = use_rnd ? random_entry(rnd_key, gi) : x[gi];
-    bufb[idx] = 0.0;
+    u[idx] = use_rnd ? random_entry(rnd_key, gi) : x[gi];
+  }
+  const int xslots = sliced_extra_slots(nx, C), slots = xslots + sliced_slots(nr, C), first = slice0 + wave * slots;
+  // the wave's groups, slices of extra rows and slices of rows (in this order; a place without a slice has no groups)
+  int total = 0, xown = 0, own = 0;
+  {
+    const int g = lane < slots ? (slice_len[first + lane] + 3) / 4 : 0;
+    const unsigned long long some = __ballot(g > 0);
+    if (g > 0) {
+      const int at = wave * MAXT + __popcll(some & ((1ull << lane) - 1ull));
+      groups[at] = g;
+      places[at] = slice_first[first + lane];
+    }
+    xown = __popcll(some & ((1ull << xslots) - 1ull));
+    own = __popcll(some) - xown;
+    int sum = g;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    total = __builtin_amdgcn_readfirstlane(sum);
   }
   __syncthreads();
-  const int nsl = (nr + kSliceRows - 1) / kSliceRows;
-  // the wave's slices (wave, wave + 16, ...: at most kSliceOwn, which the planner guarantees): where their entries
-  // start and how many rounds they take, fetched once
-  const uint16_t* cps[kSliceOwn];
-  const double* vps[kSliceOwn];
-  int lens[kSliceOwn];
-  int nown = 0;
-#pragma unroll
-  for (int j = 0; j < kSliceOwn; ++j) {
-    const int sl = wave + j * (kRT / 64);
-    const bool have = sl < nsl;
-    const int64_t base = have ? slice_base[slice0 + sl] : 0;
-    lens[j] = have ? __builtin_amdgcn_readfirstlane(slice_len[slice0 + sl]) : 0;
-    cps[j] = scol + base + lane;
-    vps[j] = sval + base + lane;
-    nown += have ? 1 : 0;
-  }
-  // Rounds in groups of kSliceGroup, two register buffers: while one group is multiplied the entries of the next
-  // are on their way, and the first group of the slice the wave turns to next (in this step or the one after) is
-  // requested before the recurrence update and the step's barrier.  Whole groups run without a branch, so the LDS
-  // reads of a round are issued ahead of the multiply-adds of the round before.  Requests past a slice's end read
-  // the next slice's entries (the copy ends with room for the last slice's) and are not multiplied.
-  int ca[kSliceGroup], cb[kSliceGroup];
-  double aa[kSliceGroup], ab[kSliceGroup];
-  auto load_group = [&](int (&c)[kSliceGroup], double (&a)[kSliceGroup], const uint16_t* cp, const double* vp, int k0)
-                        __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < kSliceGroup; ++u) {
-      c[u] = cp[(int64_t)(k0 + u) * kSliceRows];
-      a[u] = vp[(int64_t)(k0 + u) * kSliceRows];
+  if (total == 0) {  // a wave without rows keeps the barriers company
+    for (int step = 0; step < d; ++step) {
+      __syncthreads();
+      __syncthreads();
     }
-  };
-  if (nown > 0) load_group(ca, aa, cps[0], vps[0], 0);
-  double* cur = bufa;
-  double* prev = bufb;
-  for (int step = 0; step < d; ++step) {
-    const double alpha = step == 0 ? alpha_first : alpha_rest;
-    const double beta = step == 0 ? 0.0 : 1.0;
-    const double2* __restrict__ cur2 = reinterpret_cast<const double2*>(cur);
-    double2* prev2 = reinterpret_cast<double2*>(prev);
+  } else {
+    // a lane's 32 bytes of a row are two pieces; lanes of even and odd rows read them in opposite order, and a row's entries
+    // are ordered so that the rows of a 16-lane pass fall on different banks (slice_fill_kernel)
+    const int swap = (j & 1) * 16;
+    char* ub = reinterpret_cast<char*>(u);
+    const int part = h * 32 + swap;
+    const int64_t base = slice_base[first];
+    const uint16_t* cp0 = scol + base + 4 * j;
+    const double* vp0 = sval + base + 2 * j;
+    struct Group {
+      uint2 c;
+      double2 v0, v1;
+    };
+    Group buf[NB];
+    int ahead = 0;  // the next group to request
+    auto request = [&](Group& g) __attribute__((always_inline)) {
+      const int64_t off = (int64_t)ahead * (4 * RS);
+      g.c = *reinterpret_cast<const uint2*>(cp0 + off);
+      g.v0 = *reinterpret_cast<const double2*>(vp0 + off);
+      g.v1 = *reinterpret_cast<const double2*>(vp0 + off + 2 * RS);
+      ahead = ahead + 1 < total ? ahead + 1 : 0;
+    };
+    double keep[MAXS][4];  // the rows' u-; a queue: slot s is at the front when its turn comes
+    int extra[MAXS];       // the rows' extra rows: first << 16 | number
 #pragma unroll
-    for (int j = 0; j < kSliceOwn; ++j) {
-      if (j >= nown) break;  // uniform over the wave
-      const int sl = wave + j * (kRT / 64);
-      const int len = lens[j];
-      const uint16_t* cp = cps[j];
-      const double* vp = vps[j];
-      double acc[8];
+    for (int s = 0; s < MAXS; ++s) {
+      const int r = s < own ? places[wave * MAXT + xown + s] + j : nr;
+      extra[s] = nx > 0 && r < nr ? row_extra[row0 + r] : 0;
+    }
+    double acc[4];
 #pragma unroll
-      for (int t = 0; t < 8; ++t) acc[t] = 0.0;
-      auto round = [&](int c, double a) __attribute__((always_inline)) {
-        const double2* zp = cur2 + c * RW;
-        const double2 z0 = zp[pc0], z1 = zp[pc1], z2 = zp[pc2], z3 = zp[pc3];
-        acc[0] += a * z0.x;
-        acc[1] += a * z0.y;
-        acc[2] += a * z1.x;
-        acc[3] += a * z1.y;
-        acc[4] += a * z2.x;
-        acc[5] += a * z2.y;
-        acc[6] += a * z3.x;
-        acc[7] += a * z3.y;
-      };
-      auto mul_group = [&](const int (&c)[kSliceGroup], const double (&a)[kSliceGroup]) __attribute__((always_inline)) {
+    for (int t = 0; t < 4; ++t) acc[t] = 0.0;
 #pragma unroll
-        for (int u = 0; u < kSliceGroup; ++u) round(c[u], a[u]);
-      };
-      auto mul_part = [&](const int (&c)[kSliceGroup], const double (&a)[kSliceGroup], int cnt)
-                          __attribute__((always_inline)) {
+    for (int s = 0; s < MAXS; ++s)
 #pragma unroll
-        for (int u = 0; u < kSliceGroup; ++u)
-          if (u < cnt) round(c[u], a[u]);  // uniform over the wave
-      };
-      // the slice the wave turns to after this one
-      const int jn = (j + 1 < kSliceOwn && j + 1 < nown) ? j + 1 : 0;
-      int k = 0;
-      while (k + 2 * kSliceGroup <= len) {
-        load_group(cb, ab, cp, vp, k + kSliceGroup);
-        mul_group(ca, aa);
-        load_group(ca, aa, cp, vp, k + 2 * kSliceGroup);
-        mul_group(cb, ab);
-        k += 2 * kSliceGroup;
-      }
-      if (len - k >= kSliceGroup) {
-        load_group(cb, ab, cp, vp, k + kSliceGroup);
-        mul_group(ca, aa);
-        load_group(ca, aa, cps[jn], vps[jn], 0);
-        mul_part(cb, ab, len - k - kSliceGroup);
-      } else {
-        int ct[kSliceGroup];
-        double at[kSliceGroup];
+      for (int t = 0; t < 4; ++t) keep[s][t] = 0.0;
+    auto round = [&](uint32_t c, double a) __attribute__((always_inline)) {
+      const int at = (int)(c * 32u) + part;
+      const double2 z0 = *reinterpret_cast<const double2*>(ub + at);
+      const double2 z1 = *reinterpret_cast<const double2*>(ub + (at ^ 16));
+      acc[0] += a * z0.x;
+      acc[1] += a * z0.y;
+      acc[2] += a * z1.x;
+      acc[3] += a * z1.y;
+    };
+    auto push = [&](const double (&last)[4]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < kSliceGroup; ++u) {
-          ct[u] = ca[u];
-          at[u] = aa[u];
+      for (int s = 0; s + 1 < MAXS; ++s)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) keep[s][t] = keep[s + 1][t];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) keep[MAXS - 1][t] = last[t];
+    };
+    int step = 0, slot = 0;
+    int left = __builtin_amdgcn_readfirstlane(groups[wave * MAXT]);
+#pragma unroll
+    for (int q = 0; q < kSliceAhead; ++q) request(buf[q]);
+    for (bool more = true; more;) {
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        request(buf[(q + kSliceAhead) % NB]);
+        round(buf[q].c.x & 0xffffu, buf[q].v0.x);
+        round(buf[q].c.x >> 16, buf[q].v0.y);
+        round(buf[q].c.y & 0xffffu, buf[q].v1.x);
+        round(buf[q].c.y >> 16, buf[q].v1.y);
+        if (--left > 0) continue;  // uniform over the wave, as all that follows
+        if (slot < xown) {  // a slice of extra rows is done
+          const int e = places[wave * MAXT + slot] + j;
+          if (e < nx) {
+            const int at = parked + e * (C * 8) + part;
+            *reinterpret_cast<double2*>(ub + at) = make_double2(acc[0], acc[1]);
+            *reinterpret_cast<double2*>(ub + (at ^ 16)) = make_double2(acc[2], acc[3]);
+          }
+        } else {  // a slice of rows is done: the new iterate without the extra rows' sums
+          const int r = places[wave * MAXT + slot] + j;
+          const int at = (r < nr ? r : nr - 1) * (C * 8) + part;
+          const double2 o0 = *reinterpret_cast<const double2*>(ub + at);
+          const double2 o1 = *reinterpret_cast<const double2*>(ub + (at ^ 16));
+          const double alpha = step == 0 ? alpha_first : alpha_rest, beta = step == 0 ? 0.0 : 1.0;
+          const double next[4] = {alpha * (acc[0] - shift * o0.x) - beta * keep[0][0],
+                                  alpha * (acc[1] - shift * o0.y) - beta * keep[0][1],
+                                  alpha * (acc[2] - shift * o1.x) - beta * keep[0][2],
+                                  alpha * (acc[3] - shift * o1.y) - beta * keep[0][3]};
+          push(next);
         }
-        load_group(ca, aa, cps[jn], vps[jn], 0);
-        mul_part(ct, at, len - k);
-      }
-      const int r = sl * kSliceRows + lane;
-      if (r < nr) {  // the recurrence with the row's sum, stored over u- (only this lane reads or writes that row of it)
-        const double2* own = cur2 + r * RW;
-        double2* out = prev2 + r * RW;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int at = pcs[t];
-          const double2 o = own[at], pv = out[at];
-          double2 w;
-          w.x = alpha * (acc[2 * t] - shift * o.x) - beta * pv.x;
-          w.y = alpha * (acc[2 * t + 1] - shift * o.y) - beta * pv.y;
-          out[at] = w;
+        for (int t = 0; t < 4; ++t) acc[t] = 0.0;
+        ++slot;
+        if (slot == xown + own) {  // the step is done
+          for (int s = own; s < MAXS; ++s) {
+            const double front[4] = {keep[0][0], keep[0][1], keep[0][2], keep[0][3]};
+            push(front);
+          }
+          __syncthreads();  // nobody reads this step's operand any more, and the extra rows' sums are there
+          const double alpha = step == 0 ? alpha_first : alpha_rest;
+#pragma unroll
+          for (int s = 0; s < MAXS; ++s) {
+            const int r = s < own ? places[wave * MAXT + xown + s] + j : nr;
+            if (r < nr) {
+              for (int q = 0; q < (extra[s] & 0xffff); ++q) {
+                const int from = parked + ((extra[s] >> 16) + q) * (C * 8) + part;
+                const double2 e0 = *reinterpret_cast<const double2*>(ub + from);
+                const double2 e1 = *reinterpret_cast<const double2*>(ub + (from ^ 16));
+                keep[s][0] += alpha * e0.x;
+                keep[s][1] += alpha * e0.y;
+                keep[s][2] += alpha * e1.x;
+                keep[s][3] += alpha * e1.y;
+              }
+              const int at = r * (C * 8) + part;
+              double2* p0 = reinterpret_cast<double2*>(ub + at);
+              double2* p1 = reinterpret_cast<double2*>(ub + (at ^ 16));
+              const double2 o0 = *p0, o1 = *p1;
+              *p0 = make_double2(keep[s][0], keep[s][1]);
+              *p1 = make_double2(keep[s][2], keep[s][3]);
+              keep[s][0] = o0.x;
+              keep[s][1] = o0.y;
+              keep[s][2] = o1.x;
+              keep[s][3] = o1.y;
+            }
+          }
+          __syncthreads();  // every row of the new iterate is in place
+          slot = 0;
+          if (++step == d) {
+            more = false;
+            break;
+          }
         }
+        left = __builtin_amdgcn_readfirstlane(groups[wave * MAXT + slot]);
       }
     }
-    __syncthreads();  // every row of the new iterate is in place; nobody reads the old u- any more
-    double* t = cur;
-    cur = prev;
-    prev = t;
   }
-  for (int idx = tid; idx < nr * BS; idx += kRT) {
-    const int r = idx / BS, t = idx - r * BS;
-    y[(int64_t)(row0 + r) * ldy + col0 + t] = cur[idx];
+  for (int idx = tid; idx < nr * C; idx += kRT) {
+    const int r = idx / C, t = idx - r * C;
+    y[(int64_t)(row0 + r) * ldy + col0 + t] = u[idx];
   }
 }
 
@@ -546,111 +609,265 @@ __global__ __launch_bounds__(kRT) void cheb_resident_kernel(const int64_t* __res
                                                             const uint16_t* __restrict__ scol,
                                                             const double* __restrict__ sval,
                                                             const int64_t* __restrict__ slice_base,
-                                                            const int32_t* __restrict__ slice_len, int d32,
+                                                            const int32_t* __restrict__ slice_len,
+                                                            const int32_t* __restrict__ slice_first,
+                                                            const int32_t* __restrict__ row_extra, int d32,
                                                             uint64_t rnd_key, int use_rnd) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int32_t* it = items + 4 * (int64_t)blockIdx.x;
+  const int32_t* it = items + kItemInts * (int64_t)blockIdx.x;
   const int row0 = it[0], nr = it[1], col0 = it[2], cl = it[3] & 15, nx = it[3] >> 4;  // uniform over the workgroup
   if (cl == 4)
     resident_item<4>(rowptr, col, val, x, y, ldy, b, d, alpha_first, alpha_rest, shift, row0, nr, col0, nx, smem, d32, rnd_key, use_rnd);
   else if (cl == 2)
     resident_item<2>(rowptr, col, val, x, y, ldy, b, d, alpha_first, alpha_rest, shift, row0, nr, col0, nx, smem, d32, rnd_key, use_rnd);
-  else if (cl == 1)  // sliced form: the item's last word carries its first slice instead of a chunk count
-    resident_item_sliced(scol, sval, slice_base, slice_len, x, y, ldy, b, d, alpha_first, alpha_rest, shift, row0, nr, col0,
-                         nx, smem, rnd_key, use_rnd);
+  else {  // sliced form: the item's last word carries its first slice instead of a chunk count
+#define SC_SLICED(CV, MAXSV)                                                                                             \
+  resident_item_sliced<CV, MAXSV>(scol, sval, slice_base, slice_len, x, y, ldy, b, d, alpha_first, alpha_rest, shift,    \
+                                  slice_first, row_extra, row0, nr, col0, nx, it[4], smem, rnd_key, use_rnd)
+    const int cols = cl == kShape16 ? 16 : cl == kShape8 ? 8 : 4;
+    const int slots = sliced_slots(nr, cols);
+#define SC_SLICED_SLOTS(CV)                                                                                        \
+  do {                                                                                                             \
+    if (slots <= 3) SC_SLICED(CV, 3); else if (slots == 4) SC_SLICED(CV, 4); else SC_SLICED(CV, kSliceOwn);        \
+  } while (0)
+    if (cl == kShape16) SC_SLICED_SLOTS(16);
+    else if (cl == kShape8) SC_SLICED_SLOTS(8);
+    else if (cl == kShape4) SC_SLICED_SLOTS(4);
+#undef SC_SLICED_SLOTS
+#undef SC_SLICED
+  }
 }
 
 // ---- sliced copy of diagonal blocks ------------------------------------------------------------------------------------
-// One wave per slice (64 consecutive rows of one block, fewer at the block's end).  slice_len = the longest row;
-// slice_entries = 64 * slice_len: what the slice takes in the copy.
-__global__ __launch_bounds__(256) void slice_len_kernel(const int64_t* __restrict__ rowptr,
-                                                        const int32_t* __restrict__ slice_row0,
-                                                        const int32_t* __restrict__ slice_rows, int nslices,
-                                                        int32_t* __restrict__ slice_len,
-                                                        int64_t* __restrict__ slice_entries) {
-  const int sidx = (int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
-  const int lane = threadIdx.x & 63;
-  if (sidx >= nslices) return;
-  const int64_t r = (int64_t)slice_row0[sidx] + lane;
-  int len = lane < slice_rows[sidx] ? (int)(rowptr[r + 1] - rowptr[r]) : 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const int other = __shfl_xor(len, o, 64);
-    len = len > other ? len : other;
+// What a slice of the copy holds: `rows` consecutive rows of the matrix from `first` on (none: a place without a slice), or as
+// many extra rows of the list, of a block of blk_rows rows from blk0 on whose extra rows begin at extra0 of the list (extra
+// = 1), for items of `cols` columns.
+struct SliceDesc {
+  int32_t first, rows, blk0, blk_rows, cols, extra, extra0;
+};
+
+// Entries [*from, *from + return value) of row `*row` of the matrix: what place j of the slice holds.
+__device__ __forceinline__ int slice_row(const SliceDesc& sd, int j, const int64_t* __restrict__ rowptr,
+                                         const int32_t* __restrict__ list, const int32_t* __restrict__ row_extra,
+                                         int64_t* from) {
+  if (j >= sd.rows) {
+    *from = 0;
+    return 0;
   }
-  if (lane == 0) {
-    slice_len[sidx] = len;
-    slice_entries[sidx] = (int64_t)kSliceRows * len;
+  const int64_t r = sd.extra ? (int64_t)list[sd.first + j] : (int64_t)sd.first + j;
+  // the extra row's number within its row
+  const int chunk = sd.extra ? sd.first + j - sd.extra0 - (row_extra[r] >> 16) + 1 : 0;
+  const int64_t e0 = rowptr[r];
+  const int len = (int)(rowptr[r + 1] - e0) - chunk * kSliceLong;
+  *from = e0 + (int64_t)chunk * kSliceLong;
+  return len < kSliceLong ? len : kSliceLong;
+}
+
+// The extra rows of the sliced blocks, blocks[kSliceBlockInts t ..] = (first row, rows, place of its first extra row in the
+// list, extra rows, columns, first slot): list[.] = the row each belongs to, row_extra[r] = place of row r's first one within the block << 16 | their number.  A wave per
+// block.
+__global__ __launch_bounds__(256) void slice_extra_kernel(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ blocks,
+                                                          int nblocks, int32_t* __restrict__ list,
+                                                          int32_t* __restrict__ row_extra) {
+  const int t = (int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
+  const int lane = threadIdx.x & 63;
+  if (t >= nblocks) return;
+  const int32_t* blk = blocks + (int64_t)kSliceBlockInts * t;
+  const int64_t row0 = blk[0];
+  const int rows = blk[1], base = blk[2];
+  int at = 0;
+  for (int r0 = 0; r0 < rows; r0 += 64) {
+    const int r = r0 + lane;
+    const int len = r < rows ? (int)(rowptr[row0 + r + 1] - rowptr[row0 + r]) : 0;
+    const int x = len > kSliceLong ? (len + kSliceLong - 1) / kSliceLong - 1 : 0;
+    int incl = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += up;
+    }
+    const int mine = at + incl - x;
+    if (r < rows) row_extra[row0 + r] = mine << 16 | x;
+    for (int q = 0; q < x; ++q) list[base + mine + q] = (int32_t)(row0 + r);
+    at += __shfl(incl, 63, 64);
   }
 }
 
-// Fills slice sidx of the copy: round k of lane l sits at slice_base + 64 k + l.  Columns are stored relative to the
-// block's first row (slice_blk0); the padding (rounds past a row's end, lanes past the block's end) has value 0.
+// Deals a sliced block's slices to the waves: a workgroup per block, blocks[kSliceBlockInts t ..].  For every slot (wave, place)
+// of the block, from slot0 on: desc = the slice in it (or none), slice_len = its longest row (at least 1), slice_first = its
+// first row within the block / its first extra row, slice_entries = what it takes in the copy, whole groups of four rounds.
+// slice_entries[nslots] = 0: the scan's last output is the copy's size.
+__global__ __launch_bounds__(256) void slice_layout_kernel(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ blocks,
+                                                           const int32_t* __restrict__ list,
+                                                           const int32_t* __restrict__ row_extra, int nslots,
+                                                           SliceDesc* __restrict__ desc, int32_t* __restrict__ slice_len,
+                                                           int32_t* __restrict__ slice_first,
+                                                           int64_t* __restrict__ slice_entries) {
+  constexpr int MAXN = (kSliceOwn + kSliceExtra) * kSliceWaves;
+  __shared__ int length[MAXN], slot_of[MAXN];
+  const int32_t* blk = blocks + (int64_t)kSliceBlockInts * blockIdx.x;
+  const int row0 = blk[0], nr = blk[1], extra0 = blk[2], nx = blk[3], cols = blk[4], slot0 = blk[5];
+  const int rs = 256 / cols, xs = sliced_slices(nx, cols), rsl = sliced_slices(nr, cols);
+  const int xslots = sliced_extra_slots(nx, cols), rslots = sliced_slots(nr, cols), slots = xslots + rslots;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (blockIdx.x == 0 && threadIdx.x == 0) slice_entries[nslots] = 0;
+  auto describe = [&](int q) __attribute__((always_inline)) -> SliceDesc {  // slice q: the extra rows' first
+    const bool x = q < xs;
+    const int at = rs * (x ? q : q - xs), left = (x ? nx : nr) - at;
+    return SliceDesc{(x ? extra0 : row0) + at, left < rs ? left : rs, row0, nr, cols, x ? 1 : 0, extra0};
+  };
+  for (int q = wave; q < xs + rsl; q += 4) {
+    const SliceDesc sd = describe(q);
+    int64_t from;
+    int len = slice_row(sd, lane, rowptr, list, row_extra, &from);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const int other = __shfl_xor(len, o, 64);
+      len = len > other ? len : other;
+    }
+    if (lane == 0) length[q] = len < 1 ? 1 : len;
+  }
+  for (int q = threadIdx.x; q < slots * kSliceWaves; q += 256) {  // no slice, unless one is dealt
+    desc[slot0 + q] = SliceDesc{0, 0, row0, nr, cols, 0, extra0};
+    slice_len[slot0 + q] = 0;
+    slice_first[slot0 + q] = 0;
+    slice_entries[slot0 + q] = 0;
+  }
+  __syncthreads();
+  if (wave == 0) {
+    int busy = 0, taken = 0;  // of wave `lane`, lane < 16: rounds, slices of the kind that is being dealt
+    for (int q = 0; q < xs + rsl; ++q) {
+      if (q == xs) taken = 0;
+      const int len = (length[q] + 3) / 4 * 4;
+      int key = lane < kSliceWaves && taken < (q < xs ? xslots : rslots) ? busy << 4 | lane : INT32_MAX;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) {
+        const int other = __shfl_xor(key, o, 16);
+        key = other < key ? other : key;
+      }
+      if (lane == (key & 15)) {
+        slot_of[q] = lane * slots + (q < xs ? 0 : xslots) + taken;
+        busy += len;
+        ++taken;
+      }
+    }
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < xs + rsl; q += 256) {
+    const int at = slot0 + slot_of[q];
+    desc[at] = describe(q);
+    slice_len[at] = length[q];
+    slice_first[at] = rs * (q < xs ? q : q - xs);
+    slice_entries[at] = (int64_t)rs * ((length[q] + 3) / 4 * 4);
+  }
+}
+
+// Fills the copy; a workgroup per slice, half a wave per row, RS = 256 / cols rows.  Round k of row j sits in group k / 4: column number
+// at group * 4 RS + 4 j + k % 4, value at group * 4 RS + (k % 4) / 2 * 2 RS + 2 j + k % 2.  Column numbers count the operand's
+// 32-byte pieces inside the block; rounds past a row's end, and rows past the block's end, have value 0.
 //
-// The order of a row's entries is chosen for the LDS banks.  In a round the 16 lanes of a pass read 16 bytes each from
-// an operand row of 64 bytes: piece (t + lane) mod 4 of row c sits at bank quad 4 (c mod 4) + piece, so the four lanes
-// of a pass that share a piece number must read rows that differ mod 4, or the pass is served in several turns.
-// Lane l therefore puts into round k, while it has one, an entry whose column is ((l >> 2) + k) mod 4 modulo 4 (four
-// cursors walk the row, one per residue class, each in the row's own order), else an entry of the next class that has
-// any left; padding entries name a row of the wanted class.  The order depends on the matrix alone, so the sums stay
-// reproducible.
-__global__ __launch_bounds__(256) void slice_fill_kernel(const int64_t* __restrict__ rowptr,
-                                                         const int32_t* __restrict__ col,
-                                                         const double* __restrict__ val,
-                                                         const int32_t* __restrict__ slice_row0,
-                                                         const int32_t* __restrict__ slice_rows,
-                                                         const int32_t* __restrict__ slice_blk0,
-                                                         const int32_t* __restrict__ slice_blk_rows, int nslices,
-                                                         const int64_t* __restrict__ slice_base,
+// The order of a row's entries is chosen for the LDS banks.  In a round the 16 lanes of a pass read 16 bytes each of
+// 256 / (8 cols) = NC different operand rows at a time without a conflict if these rows differ mod NC (cols 4, 8, 16: NC 8, 4,
+// 2), half of the pass's rows one piece and half the other (rows j of the same parity).  Row j therefore wants in round k an
+// entry whose column is (j / 2 + k) mod NC; the r-th entry of a class goes into the r-th such round.  Entries for which a
+// row has too few such rounds take, in order, the rounds that other classes leave free.  The order depends on the matrix
+// alone, so the sums stay reproducible.
+__global__ __launch_bounds__(256) void slice_fill_kernel(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                                         const double* __restrict__ val, const SliceDesc* __restrict__ desc,
+                                                         const int32_t* __restrict__ list,
+                                                         const int32_t* __restrict__ row_extra, const int64_t* __restrict__ slice_base,
                                                          const int64_t* __restrict__ slice_entries,
                                                          uint16_t* __restrict__ scol, double* __restrict__ sval) {
-  const int sidx = (int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
-  const int lane = threadIdx.x & 63;
-  if (sidx >= nslices) return;
-  const int rounds = (int)(slice_entries[sidx] / kSliceRows);
+  const int lane = threadIdx.x & 31, half = (threadIdx.x & 32);
+  const int64_t sidx = blockIdx.x;
+  const SliceDesc sd = desc[sidx];
+  const int rs = 256 / sd.cols, lpr = sd.cols / 4, lognc = sd.cols == 16 ? 1 : sd.cols == 8 ? 2 : 3, nc = 1 << lognc;
+  if (sd.rows == 0) return;
+  const int rounds = (int)(slice_entries[sidx] / rs);
   const int64_t base = slice_base[sidx];
-  const bool live = lane < slice_rows[sidx];
-  const int64_t r = (int64_t)slice_row0[sidx] + lane;
-  const int64_t e0 = live ? rowptr[r] : 0, e1 = live ? rowptr[r + 1] : 0;
-  const int blk0 = slice_blk0[sidx];
-  const unsigned last = (unsigned)(slice_blk_rows[sidx] - 1);
-  auto local = [&](int64_t e) -> unsigned {
-    const unsigned lc = (unsigned)(col[e] - blk0);
+  const unsigned last = (unsigned)(sd.blk_rows - 1);
+  for (int j = threadIdx.x >> 5; j < rs; j += 8) {  // uniform over the wave: rs is a multiple of 16
+  int64_t e0;
+  const int len = slice_row(sd, j, rowptr, list, row_extra, &e0);
+  const int turn = j >> 1;
+  auto local = [&](int e) __attribute__((always_inline)) -> unsigned {
+    const unsigned lc = (unsigned)(col[e0 + e] - sd.blk0);
     return lc < last ? lc : last;  // a column outside the block (there is none in a diagonal block) stays inside LDS
   };
-  auto next_of_class = [&](int64_t from, unsigned cls) -> int64_t {
-    int64_t e = from;
-    while (e < e1 && (local(e) & 3u) != cls) ++e;
-    return e;
+  auto first_round = [&](int cls) __attribute__((always_inline)) -> int { return (cls - turn) & (nc - 1); };
+  auto rounds_of = [&](int cls) __attribute__((always_inline)) -> int {
+    const int f = first_round(cls);
+    return f < len ? (len - f + nc - 1) >> lognc : 0;
   };
-  int64_t cur[4];
+  auto put = [&](int k, unsigned lc, double av) __attribute__((always_inline)) {
+    const int64_t at = base + (int64_t)(k >> 2) * (4 * rs);
+    scol[at + 4 * j + (k & 3)] = (uint16_t)(lc * (unsigned)lpr);
+    sval[at + ((k >> 1) & 1) * 2 * rs + 2 * j + (k & 1)] = av;
+  };
+  const int longest = max(len, __shfl_xor(len, 32, 64));  // of the wave's two rows: they go through the loops together
+  // entries of every class, and how many before them have no round of their own / how many rounds are free before
+  int count[8], over[8], gap[8];
 #pragma unroll
-  for (unsigned cls = 0; cls < 4; ++cls) cur[cls] = next_of_class(e0, cls);
-  for (int k = 0; k < rounds; ++k) {
-    const unsigned want = (unsigned)((lane >> 2) + k) & 3u;
-    unsigned lc = want <= last ? want : 0;  // padding: a row of the wanted class
-    double av = 0.0;
+  for (int c = 0; c < 8; ++c) count[c] = 0;
+  for (int b0 = 0; b0 < longest; b0 += 32) {
+    const bool in = b0 + lane < len;
+    const int cls = in ? (int)(local(b0 + lane) & (unsigned)(nc - 1)) : -1;
 #pragma unroll
-    for (unsigned o = 0; o < 4; ++o) {
-      const unsigned cls = (want + o) & 3u;
-      bool took = false;
+    for (int c = 0; c < 8; ++c) count[c] += __popc((unsigned)(__ballot(cls == c) >> half));
+  }
+  int so = 0, sg = 0;
 #pragma unroll
-      for (unsigned q = 0; q < 4; ++q)  // cur[] is indexed with constants only (it lives in registers)
-        if (q == cls && cur[q] < e1 && !took) {
-          lc = local(cur[q]);
-          av = val[cur[q]];
-          cur[q] = next_of_class(cur[q] + 1, q);
-          took = true;
-        }
-      if (took) break;
+  for (int c = 0; c < 8; ++c) {
+    const int m = c < nc ? rounds_of(c) : 0;
+    over[c] = so;
+    gap[c] = sg;
+    so += count[c] > m ? count[c] - m : 0;
+    sg += m > count[c] ? m - count[c] : 0;
+  }
+  int seen[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) seen[c] = 0;
+  for (int b0 = 0; b0 < longest; b0 += 32) {
+    const bool in = b0 + lane < len;
+    const unsigned lc = in ? local(b0 + lane) : 0u;
+    const int cls = in ? (int)(lc & (unsigned)(nc - 1)) : -1;
+    int rank = 0, before = 0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const unsigned m = (unsigned)(__ballot(cls == c) >> half);
+      if (cls == c) {
+        rank = seen[c] + __popc(m & ((1u << lane) - 1u));
+        before = over[c];
+      }
+      seen[c] += __popc(m);
     }
-    scol[base + (int64_t)k * kSliceRows + lane] = (uint16_t)lc;
-    sval[base + (int64_t)k * kSliceRows + lane] = av;
+    if (in) {
+      const int own = rounds_of(cls);
+      int k;
+      if (rank < own) {
+        k = first_round(cls) + (rank << lognc);
+      } else {  // the (before + rank - own)-th free round
+        int want = before + rank - own;
+        k = 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const int m = c < nc ? rounds_of(c) : 0, free_here = m > count[c] ? m - count[c] : 0;
+          const int at = want - gap[c];
+          if (at >= 0 && at < free_here) k = first_round(c) + ((count[c] + at) << lognc);
+        }
+      }
+      put(k, lc, val[e0 + b0 + lane]);
+    }
+  }
+  for (int k = len + lane; k < rounds; k += 32) {  // padding: a row of the wanted class
+    const unsigned want = (unsigned)((turn + k) & (nc - 1));
+    put(k, want <= last ? want : 0u, 0.0);
+  }
   }
 }
 
-// extra[2 t] / extra[2 t + 1] = chunks beyond the first, summed over the rows of diagonal block t, for chunks of 32 /
-// of 16 entries.  One wave per block.
+// extra[3 t], extra[3 t + 1], extra[3 t + 2] = chunks beyond the first, summed over the rows of diagonal block t, for chunks of
+// 32, 16 and kSliceLong entries.  One wave per block.
 __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* __restrict__ rowptr,
                                                                  const int32_t* __restrict__ starts, int nblk, int64_t n,
                                                                  int32_t* __restrict__ extra) {
@@ -658,20 +875,23 @@ __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* 
   const int lane = threadIdx.x & 63;
   if (t >= nblk) return;
   const int64_t r0 = starts[t], r1 = t + 1 < nblk ? (int64_t)starts[t + 1] : n;
-  int x32 = 0, x16 = 0;
+  int x32 = 0, x16 = 0, xl = 0;
   for (int64_t r = r0 + lane; r < r1; r += 64) {
     const int len = (int)(rowptr[r + 1] - rowptr[r]);
     if (len > 32) x32 += (len + 31) / 32 - 1;
     if (len > 16) x16 += (len + 15) / 16 - 1;
+    if (len > kSliceLong) xl += (len + kSliceLong - 1) / kSliceLong - 1;
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     x32 += __shfl_xor(x32, o, 64);
     x16 += __shfl_xor(x16, o, 64);
+    xl += __shfl_xor(xl, o, 64);
   }
   if (lane == 0) {
-    extra[2 * t] = x32;
-    extra[2 * t + 1] = x16;
+    extra[3 * t] = x32;
+    extra[3 * t + 1] = x16;
+    extra[3 * t + 2] = xl;
   }
 }
 
@@ -710,14 +930,22 @@ size_t resident_item_lds_bytes(int nrows, int cl, int extra) { return resident_l
 
 int resident_max_chunks(int cl) { return kRS * (kRT / cl); }
 
-int resident_slice_rows() { return kSliceRows; }
+int sliced_shape(int cols) { return cols == 16 ? kShape16 : cols == 8 ? kShape8 : kShape4; }
 
-int64_t sliced_copy_tail_entries() { return (int64_t)3 * kSliceGroup * kSliceRows; }
-
-size_t resident_sliced_lds_bytes(int nrows) {
-  if (nrows > kSliceOwn * (kRT / 64) * kSliceRows) return ~(size_t)0;  // more slices than the waves own: no item
-  return ((size_t)2 * nrows * 8 * sizeof(double) + 15) / 16 * 16;
+size_t resident_sliced_lds_bytes(int nrows, int extra, int cols) {
+  // more slices than the waves own, or more extra rows than their numbers hold: no item
+  if (nrows > 65535 || extra > 32767 || sliced_slices(nrows, cols) > kSliceOwn * kSliceWaves ||
+      sliced_slices(extra, cols) > kSliceExtra * kSliceWaves)
+    return ~(size_t)0;
+  return (size_t)(nrows + extra) * cols * sizeof(double) +
+         (size_t)2 * kSliceWaves * (kSliceOwn + kSliceExtra) * sizeof(int32_t);
 }
+
+int sliced_block_slots(int nrows, int extra, int cols) {
+  return (sliced_slots(nrows, cols) + sliced_extra_slots(extra, cols)) * kSliceWaves;
+}
+
+size_t sliced_desc_bytes(int nslots) { return (size_t)nslots * sizeof(SliceDesc); }
 
 size_t sliced_scan_workspace(int nslices) {
   size_t t = 0;
@@ -726,29 +954,32 @@ size_t sliced_scan_workspace(int nslices) {
   return up256(t) + 256;
 }
 
-hipError_t sliced_copy_layout(const int64_t* rowptr, const int32_t* slice_row0, const int32_t* slice_rows, int nslices,
-                              int32_t* slice_len, int64_t* slice_entries, int64_t* slice_base, void* work,
-                              size_t work_bytes, hipStream_t st) {
-  if (nslices <= 0) return hipSuccess;
-  hipLaunchKernelGGL(slice_len_kernel, dim3((unsigned)(((int64_t)nslices * 64 + 255) / 256)), dim3(256), 0, st, rowptr,
-                     slice_row0, slice_rows, nslices, slice_len, slice_entries);
-  // slice_entries has nslices + 1 slots, the last one zero: the scan's last output is the copy's size
-  hipError_t e = hipMemsetAsync(slice_entries + nslices, 0, sizeof(int64_t), st);
-  if (e != hipSuccess) return e;
-  e = rocprim::exclusive_scan(work, work_bytes, slice_entries, slice_base, (int64_t)0, (size_t)nslices + 1,
-                              rocprim::plus<int64_t>(), st);
+hipError_t sliced_extra_rows(const int64_t* rowptr, const int32_t* blocks, int nblocks, int32_t* list, int32_t* row_extra,
+                             hipStream_t st) {
+  if (nblocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(slice_extra_kernel, dim3((unsigned)(((int64_t)nblocks * 64 + 255) / 256)), dim3(256), 0, st, rowptr, blocks,
+                     nblocks, list, row_extra);
+  return hipGetLastError();
+}
+
+hipError_t sliced_copy_layout(const int64_t* rowptr, const int32_t* blocks, int nblocks, const int32_t* list,
+                              const int32_t* row_extra, int nslots, void* desc, int32_t* slice_len, int32_t* slice_first,
+                              int64_t* slice_entries, int64_t* slice_base, void* work, size_t work_bytes, hipStream_t st) {
+  if (nslots <= 0 || nblocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL(slice_layout_kernel, dim3((unsigned)nblocks), dim3(256), 0, st, rowptr, blocks, list, row_extra, nslots,
+                     static_cast<SliceDesc*>(desc), slice_len, slice_first, slice_entries);
+  const hipError_t e = rocprim::exclusive_scan(work, work_bytes, slice_entries, slice_base, (int64_t)0, (size_t)nslots + 1,
+                                               rocprim::plus<int64_t>(), st);
   if (e != hipSuccess) return e;
   return hipGetLastError();
 }
 
-hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const double* val, const int32_t* slice_row0,
-                            const int32_t* slice_rows, const int32_t* slice_blk0, const int32_t* slice_blk_rows,
-                            int nslices, const int64_t* slice_base, const int64_t* slice_entries, uint16_t* scol,
-                            double* sval, hipStream_t st) {
-  if (nslices <= 0) return hipSuccess;
-  hipLaunchKernelGGL(slice_fill_kernel, dim3((unsigned)(((int64_t)nslices * 64 + 255) / 256)), dim3(256), 0, st, rowptr,
-                     col, val, slice_row0, slice_rows, slice_blk0, slice_blk_rows, nslices, slice_base, slice_entries,
-                     scol, sval);
+hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const double* val, const void* desc,
+                            const int32_t* list, const int32_t* row_extra, int nslots, const int64_t* slice_base,
+                            const int64_t* slice_entries, uint16_t* scol, double* sval, hipStream_t st) {
+  if (nslots <= 0) return hipSuccess;
+  hipLaunchKernelGGL(slice_fill_kernel, dim3((unsigned)nslots), dim3(256), 0, st, rowptr, col, val,
+                     static_cast<const SliceDesc*>(desc), list, row_extra, slice_base, slice_entries, scol, sval);
   return hipGetLastError();
 }
 
@@ -789,15 +1020,15 @@ hipError_t diagonal_blocks(const int64_t* rowptr, const int32_t* col, int64_t n,
 hipError_t launch_cheb_resident(const int64_t* rowptr, const int32_t* col, const double* val, const double* x, double* y,
                                 int64_t ldy, int b, int d, double alpha_first, double alpha_rest, double shift, const int32_t* items,
                                 int nitems, size_t lds_bytes, const uint16_t* scol, const double* sval,
-                                const int64_t* slice_base, const int32_t* slice_len, hipStream_t st, int d32,
-                                uint64_t rnd_key, int use_rnd) {
+                                const int64_t* slice_base, const int32_t* slice_len, const int32_t* slice_first,
+                                const int32_t* row_extra, hipStream_t st, int d32, uint64_t rnd_key, int use_rnd) {
   if (nitems <= 0 || d <= 0) return hipSuccess;
   if (d32 < 0 || d32 >= d) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&cheb_resident_kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(cheb_resident_kernel, dim3((unsigned)nitems), dim3(kRT), lds_bytes, st, rowptr, col, val, x, y, ldy, b, d,
-                     alpha_first, alpha_rest, shift, items, scol, sval, slice_base, slice_len, d32, rnd_key, use_rnd);
+                     alpha_first, alpha_rest, shift, items, scol, sval, slice_base, slice_len, slice_first, row_extra, d32, rnd_key, use_rnd);
   return hipGetLastError();
 }
 

@@ -533,3 +533,35 @@ def test_fp64_matrix_rate_probe(B):
     assert B.lib().sc_probe_fp64_matrix_rate(16, 8, 0, ctypes.byref(out), 0) == B.SC_EDOMAIN
     assert B.lib().sc_probe_fp64_matrix_rate(8, 8, 8, ctypes.byref(out), 0) == B.SC_EDOMAIN
     assert B.lib().sc_probe_fp64_matrix_rate(16, 8, 8, None, 0) == B.SC_EINVAL
+
+
+# items of every width: rows around one and two slices of 16, 32 and 64, more rows than a narrower width is needed for, rows of
+# 64, 65, 128 and 500 entries (their extra rows), more extra rows than a slice holds, one step and many
+@pytest.mark.parametrize("widest", [16, 8, 4])
+@pytest.mark.parametrize("ncols,degree", [(16, 1), (16, 9), (32, 4)])
+def test_chebyshev_filter_sliced_widths(B, widest, ncols, degree, monkeypatch):
+    from oracle import blockops
+    monkeypatch.setenv("SCEIG_FORCE_RESIDENT", "1")
+    monkeypatch.setenv("SCEIG_SLICED_COLUMNS", str(widest))
+
+    def star(leaves):
+        return wl.symmetric_from_edges(np.zeros(leaves, dtype=np.int64), np.arange(1, leaves + 1),
+                                       np.linspace(0.5, 1.5, leaves), leaves + 1)
+
+    rp, c, v, n = wl.disjoint_union(wl.complete(129), wl.complete(130), wl.complete(200), star(64), star(65), star(500), star(1023),
+                                    star(1024), wl.random_weighted_connected(257, 9000, 1),
+                                    wl.random_weighted_connected(1023, 18000, 2), wl.random_weighted_connected(1025, 3000, 3),
+                                    wl.random_weighted_connected(1270, 15000, 4))
+    rp, c, v, n = wl.disjoint_union((rp, c, v, n), wl.random_weighted_connected(1273, 20000, 5), star(2400),
+                                    wl.random_weighted_connected(2530, 20000, 6), wl.random_weighted_connected(4900, 50000, 7))
+    rng = np.random.default_rng(ncols + degree)
+    x = rng.standard_normal((n, ncols))
+    want = blockops.chebyshev_filter(rp, c, v, x, 0.3, degree)
+    drp, dc, dv = B.csr_to_device(rp, c, v)
+    dx = torch.from_numpy(x).cuda()
+    before = B.sc_counter(B.SC_COUNTER_RESIDENT_FILTERS)
+    got = B.sc_chebyshev_filter(drp, dc, dv, dx, 0.3, degree)
+    assert B.sc_counter(B.SC_COUNTER_RESIDENT_FILTERS) == before + 1
+    # a row's sum of up to 2,400 products, and `degree` steps of at most twice the growth of the recurrence
+    assert np.max(np.abs(got.cpu().numpy() - want)) <= 1e-11 * max(1.0, np.max(np.abs(want)))
+    assert torch.equal(got, B.sc_chebyshev_filter(drp, dc, dv, dx, 0.3, degree))
