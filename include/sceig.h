@@ -148,7 +148,8 @@ typedef struct sc_stats {
  * locked and active basis vectors, second pass against the active Krylov vectors; a phase's random start
  * block gets both passes against everything), thick restart, locking, and re-injection of a fresh random
  * block after every lock so that multiple eigenvalues are found with their multiplicity; once k pairs
- * are locked one further deflated phase must find nothing better (skipped under SC_FLAG_NO_VERIFY, and when
+ * are locked one further deflated phase must find nothing better: it ends when a larger eigenvalue would, but for a
+ * chance of 1e-20, have shown in its random block, or when its largest Ritz pair has converged (skipped under SC_FLAG_NO_VERIFY, and when
  * the k-th locked theta is already within tol of 1, the largest value the spectrum of S can reach for W >= 0);
  * the outputs are the locked Ritz pairs in ascending order of lambda (after a Rayleigh-Ritz step over them when
  * some pair did not meet tol, or under SC_FLAG_FINAL_RR).  Only the projected

@@ -977,6 +977,7 @@ struct Solver {
   double filt_ref = 2.0;    // the Ritz value the planned filter is made large at
   double filt_rate = 0.0;   // growth exponent per degree of the planned filter at filt_ref
   double filt_lo = -1.0;    // lower end of the planned filter's damped interval
+  double next_theta = -2.0;  // largest unlocked Ritz value of the phase that locked last: a lower estimate of what follows
   // Estimate of the bottom of the spectrum of S, from below: the damped interval of the start-block filters is
   // [spec_lo, a] instead of [-1, a], which shortens the polynomial by a seventh to a fifth on kNN graphs (their
   // spectra end near -0.3 ... -0.5).  -1 until the first unfiltered steps have shown the smallest Ritz value (an upper
@@ -1268,6 +1269,7 @@ struct Solver {
     if (rot_cols < (size_t)3 * b) return;
     if (nlead < 1 || ja - nghost < nlead) return;
     const int nu = ja - nlead - nghost;  // Ritz values of real directions below the leading ones
+    if (locked) next_theta = nu >= 1 ? theta[ja - 1 - nlead] : -2.0;
     const double th_ref = locked ? theta[ja - nlead] : theta[ja - 1];
     if (filt_best >= th_ref - 1e-6) filt_best = -2.0;  // the wanted values have moved below the old estimate
     double a = filt_best;
@@ -1299,6 +1301,66 @@ struct Solver {
     filt_lo = lo;
     filt_ref = th_ref;
     filt_rate = rate;
+  }
+
+  // The check phase's question is whether S has an eigenvalue above kappa (the k-th locked one plus tol) outside the
+  // locked vectors.  It is answered from below: the phase's basis spans all T(S) F(S) q, F the start filter (Chebyshev of
+  // degree d on [lo, a]), T any polynomial of degree steps - 1, q a random column.  Take T = the Chebyshev polynomial of
+  // [-1, t] for some t between the largest Ritz value theta and kappa.  If such an eigenvalue existed, P = T F would be at
+  // least P(kappa) on it and at most max|F| on the spectrum below t (none lies below -1), and were its share of q larger
+  // than sqrt(M) max|F| / P(kappa), M = (t + 1) / (t - theta) - 1, the Rayleigh quotient of P(S) q alone, hence the
+  // largest Ritz value, would exceed theta.  A share below x has probability at most x sqrt(n) in one random column (the
+  // entries are uniform; a unit combination of them has density at most 1/sqrt(2), Ball 1986) and that to the power b in
+  // all of them.  Returns the block steps after which this probability is below 1e-20, with the best t of a few.
+  // Waiting for the largest Ritz value itself to converge says no more and costs far more: the spectrum is dense there
+  // (4,040 nodes in one component, 10 values: 85 steps against 1).
+  int check_steps_needed(double theta, double kappa, int d, double lo, double a) const {
+    auto lncosh = [](double v) { return v + std::log1p(std::exp(-2.0 * v)) - std::log(2.0); };
+    auto lnf = [&](double y) {  // ln |F(y)| outside the damped interval, 0 inside (where |F| <= 1)
+      const double x = std::fabs((2.0 * y - a - lo) / (a - lo));
+      return d > 0 && x > 1.0 ? lncosh(d * std::acosh(x)) : 0.0;
+    };
+    if (!(kappa > theta)) return 1 << 30;
+    double best = 1e9;
+    for (int i = 1; i <= 9; ++i) {
+      const double t = theta + 0.1 * i * (kappa - theta);
+      if (!(t > theta) || !(t < kappa) || !(t > -1.0)) continue;
+      const double share = 0.5 * std::log(std::max((t + 1.0) / (t - theta) - 1.0, 1e-3));
+      const double need = share + 0.5 * std::log((double)n) + 20.0 * std::log(10.0) / b;
+      const double have = (d > 0 && kappa <= a ? 0.0 : lnf(kappa)) - std::max({0.0, lnf(t), lnf(-1.0)});
+      const double rate = std::acosh((2.0 * kappa - t + 1.0) / (t + 1.0));
+      const double steps = need <= have ? 1.0 : 1.0 + std::ceil((need - have + std::log(2.0)) / std::max(rate, 1e-9));
+      best = std::min(best, steps);
+    }
+    return (int)best;
+  }
+
+  // Filter of the check phase's block: the degree that answers the question above with one block step, where the
+  // amplification of the locked vectors above kappa (they are projected out before and after) leaves room for it.
+  void plan_check_filter() {
+    if ((flags & SC_FLAG_NO_START_FILTER) || rot_cols < (size_t)3 * b) return;
+    const double kappa = kth_locked_theta() + tol, theta = std::max(filt_best, next_theta);
+    if (theta <= -1.0 || !(kappa - theta > 1e-6)) return;
+    const double top = *std::max_element(theta_locked.begin(), theta_locked.end());
+    int best = 0;
+    for (int i = 2; i <= 6; ++i) {
+      const double a = theta + 0.1 * i * (kappa - theta);
+      const double room = std::log(2.0 * std::min(1e10, 1e-2 / std::max(tol, 1e-300)));
+      const double rate = std::acosh((2.0 * top - a + 1.0) / (a + 1.0));
+      const int dmax = (int)std::min(120.0, std::floor(room / std::max(rate, 1e-9)));
+      // the Ritz value of the filtered block will be somewhat above the estimate
+      const double seen = theta + 0.05 * (kappa - theta);
+      for (int d = 2; d <= dmax && (best == 0 || d < best); ++d) {
+        if (check_steps_needed(seen, kappa, d, -1.0, a) > 1) continue;
+        best = d;
+        filt_a = a;
+      }
+    }
+    if (best == 0) return;  // the filter planned for any phase and more block steps
+    filt_d = best;
+    filt_lo = -1.0;
+    filt_ref = kappa;
+    filt_rate = std::acosh((2.0 * kappa - filt_a + 1.0) / (filt_a + 1.0));
   }
 
   // basis[:, dst : dst+l] = basis[:, nl : nl+ja] * Y[:, sel] (through the rotation workspace when l > 64)
@@ -1387,9 +1449,14 @@ struct Solver {
       stats.phases += 1;
 
       // ---- start block
+      if (verifying) plan_check_filter();
       bool filtered = filt_d > 0;
+      // the check phase's test (check_steps_needed) holds as long as the basis is the Krylov space of a random block
+      bool check_open = verifying && !last_cycle_phase;
+      const int check_d = filt_d;
+      const double check_lo = filt_lo, check_a = filt_a;
       // exponent of the filter this phase starts from (0: none, or not a random block), for the degree feedback
-      double phase_rate = filtered ? filt_rate : 0.0;
+      double phase_rate = filtered && !verifying ? filt_rate : 0.0;
       // The locked vectors' eigenvalues lie above the damped interval too, so the filter amplifies what a block holds
       // along them.  When none of them lies above the value the filter is aimed at (the usual case here: further
       // copies of one multiple eigenvalue), they are amplified no more than the wanted directions, the filtered block
@@ -1484,6 +1551,7 @@ struct Solver {
       // feedback only.
       const bool tight_target =
           tentative_allowed && ncomp > 0 && (double)(k - b) > 4.0 * std::max(ncomp - (k - b), 1);
+      if (check_open && filtered) next_check = 1;
       if (tentative_allowed) next_check = 1;  // a look after the cheap first step costs far less than a full second step
       while (!phase_over) {
         if (next_slot >= max_slots) SC_THROW(SC_EDOMAIN);  // cannot happen: a cycle has at most m/b steps
@@ -1615,6 +1683,17 @@ struct Solver {
                        theta[ja - 1], rho[0], wi >= 0 ? theta[ja - 1 - wi] : 0.0, wi >= 0 ? rho[wi] : 0.0);
         }
 
+        int check_more = 0;  // block steps that the check phase's test still needs, 0 = unknown or out of reach
+        if (check_open && nreal == ja) {
+          const int need = check_steps_needed(theta[ja - 1], kth_locked_theta() + tol, check_d, check_lo, check_a);
+          if (debug_on())
+            std::fprintf(stderr, "[sceig] check phase: %d of %d steps\n", steps_in_phase, need);
+          if (need <= steps_in_phase) {
+            finished = true;
+            break;
+          }
+          if (ja + (need - steps_in_phase) * (int64_t)b <= cap) check_more = need - steps_in_phase;
+        }
         if (tentative && !(lead >= want || exhausted)) {
           // the upper bounds did not pass: the step again, this time with the projection against the locked vectors
           if (debug_on())
@@ -1639,7 +1718,8 @@ struct Solver {
           if (nl < k) not_converged = true;
           break;
         }
-        if (!filtered && !full && !last_cycle_phase && !exhausted && lead < want && steps_in_phase >= 4 && nsel >= b) {
+        if (check_more == 0 && !filtered && !full && !last_cycle_phase && !exhausted && lead < want && steps_in_phase >= 4 &&
+            nsel >= b) {
           // A phase that began from a plain random block (no spectrum estimate was available then): once its Ritz
           // values give one, filter the leading Ritz vectors - a far better start than a random block - and begin
           // the phase anew from the filtered block.
@@ -1655,6 +1735,7 @@ struct Solver {
           }
           plan_start_filter(theta, ja, std::min(want, nreal), ja - nreal, false);
           if (filt_d > 0) {
+            check_open = false;
             if (debug_on())
               std::fprintf(stderr, "[sceig] t=%.4fs phase %d restarts from its %d leading Ritz vectors filtered: degree %d, "
                            "damped interval [%.4f, %.6f]\n", now_s() - t_begin, stats.phases, b, filt_d, filt_lo, filt_a);
@@ -1735,6 +1816,7 @@ struct Solver {
           // ---- thick restart: keep the leading Ritz vectors and the residual block
           cycles += 1;
           stats.restarts += 1;
+          check_open = false;
           const int l = l_restart;
           if (l < 1) SC_THROW(SC_EDOMAIN);
           if (l > ycols) ritz_vectors(l);
@@ -1779,6 +1861,7 @@ struct Solver {
           }
           ja += b;
           next_check = schedule_check(rho[std::min({want, nreal, nsel}) - 1], (cap - ja) / b + 1);
+          if (check_more > 0) next_check = check_more;
         }
         (void)assembled;
       }

@@ -488,3 +488,19 @@ def test_workspace_estimate_covers_what_a_solve_allocates(B):
     assert code == B.SC_OK
     assert 0.8 * taken <= est <= 1.5 * taken + (32 << 20), (taken, est)
     B.sc_release_cache()
+
+
+@pytest.mark.parametrize("k,block,no_filter,most", [(10, 8, False, 30), (10, 8, True, 60), (10, 2, False, None),
+                                                    (7, 8, False, None), (1, 1, False, None), (12, 4, False, None)])
+def test_check_phase(B, k, block, no_filter, most):
+    """The check phase answers whether something larger is left: where the wanted values stand clear of the rest it does so
+    in a few steps (the locking phases take the others; 80 and more until the rest's largest pair converges), where k cuts
+    close values it goes on, and the answer is the oracle's either way."""
+    g, _ = wl.stochastic_block_model(1200, 10, 0.33, 0.002, 3)
+    rp, c, v, n = g
+    lam0, vec0 = dense.smallest_eigenpairs(rp, c, v, k + 1)
+    lam, vec, code, stats = solve(B, g, k, 1e-10, block=block, m=120 if no_filter else 80,
+                                  flags=B.SC_FLAG_NO_START_FILTER if no_filter else 0)
+    assert code == B.SC_OK
+    check_against_oracle(g, k, lam, vec, lam0, vec0)
+    assert most is None or stats["block_steps"] <= most, stats
