@@ -1684,6 +1684,7 @@ struct Solver {
         }
 
         int check_more = 0;  // block steps that the check phase's test still needs, 0 = unknown or out of reach
+        if (theta[0] < -1.0 - 1e-9 && nreal == ja) check_open = false;  // weights below zero: the test takes [-1, t]
         if (check_open && nreal == ja) {
           const int need = check_steps_needed(theta[ja - 1], kth_locked_theta() + tol, check_d, check_lo, check_a);
           if (debug_on())
