@@ -826,16 +826,23 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
   // read everything once per group).  300,000 rows, 400 coefficients: 192 columns 1,130 -> 950 us, 200 columns 1,390 ->
   // 1,150 us; 500,000 rows, 1,000 x 500: 9.7 -> 8.6 ms = 58 of the 78 TFLOP/s of the fp64 matrix cores.  Groups of 80
   // columns where that makes fewer of them were no better (950 and 1,170 us; 10.2 ms).
-  int group = 0;
+  // The tiles of 16 columns are dealt evenly (a last group of one tile reads the panel for a quarter of a group's matrix
+  // instructions: 80 columns 597 -> 502 us), and the groups of the panels come in turning order: workgroups are placed on
+  // an XCD's four shader engines in turn, and with four groups one engine got all the larger ones (200 columns 1,219 ->
+  // 1,126 us by both).
+  int n0 = 0, n1 = ncols;  // columns of this workgroup
   int64_t panel = blockIdx.x;
   if constexpr (NT == 4) {
-    const int groups = (ncols + 63) / 64;
+    const int groups = (ncols + 63) / 64, all = (ncols + 15) / 16;
     const unsigned t = blockIdx.x / 8;
-    group = (int)(t % groups);
+    const int group = (int)((t + t / groups) % groups);
     panel = (int64_t)(t / groups) * 8 + blockIdx.x % 8;
     if (panel * (64 * MT) >= n) return;  // uniform over the workgroup
+    const int each = all / groups, more = all % groups;
+    n0 = 16 * (group * each + (group < more ? group : more));
+    n1 = n0 + 16 * (each + (group < more ? 1 : 0));
+    n1 = n1 < ncols ? n1 : ncols;
   }
-  const int n0 = group * NT * 16;
   const int64_t row0 = (panel * 4 + wave) * (16 * MT);
 
   d4 acc[MT][NT];
@@ -849,7 +856,7 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
     const int kc = (kdim - k0) < KC ? (kdim - k0) : KC;
     const int kc16 = (kc + 15) & ~15;
     __syncthreads();
-    stage_coefficients<NT>(lds, bmat, ldb, k0, kc, kc16, n0, ncols);
+    stage_coefficients<NT>(lds, bmat, ldb, k0, kc, kc16, n0, n1);
     __syncthreads();
     int kk0 = 0;
     // A wave whose rows all exist runs the trips of the chunk without a branch round any load: the operands of the
@@ -870,7 +877,7 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
             av[h][mt] = *reinterpret_cast<const d4*>(abase + (int64_t)mt * 16 * ld + kcol);
         }
       };
-      const int tiles = (ncols - n0 + 15) / 16;  // of the last group of columns fewer than NT may hold any
+      const int tiles = (n1 - n0 + 15) / 16;  // of a group of columns fewer than NT may hold any
       auto mult = [&](const d4 (&av)[2][MT], int kb) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -950,7 +957,7 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
       for (int rr = 0; rr < 4; ++rr) {
         const int64_t row = row0 + mt * 16 + 4 * rr + g;
         const int t = n0 + nt * 16 + i;
-        if (row < n && t < ncols) {
+        if (row < n && t < n1) {
           const double v = acc[mt][nt][rr];
           if (mode == 0) {
             basis[row * ld + ccol0 + t] -= v;
