@@ -28,9 +28,23 @@ constexpr int kT = 256;
 constexpr int kL = 16;  // lanes per row / per edge
 inline unsigned blocks(int64_t n) { return (unsigned)((n + kT - 1) / kT); }
 
+// v of another lane of the 16, by a DPP control word
+template <int CTRL>
+__device__ __forceinline__ double row_dpp(double v) {
+  const uint64_t u = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// The sum over the 16 lanes of a DPP row, in the order of a butterfly over 8, 4, 2, 1: row_ror:8, row_ror:4 (the values
+// repeat every 8 lanes by then), quad_perm [2,3,0,1], quad_perm [1,0,3,2].  All lanes of the row must be active.
 __device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-  for (int o = kL / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kL);
+  static_assert(kL == 16, "a DPP row");
+  v += row_dpp<0x128>(v);
+  v += row_dpp<0x124>(v);
+  v += row_dpp<0x4e>(v);
+  v += row_dpp<0xb1>(v);
   return v;
 }
 
@@ -156,6 +170,9 @@ __global__ __launch_bounds__(kPartThreads) void bucket_scan_kernel(const int32_t
   }
 }
 
+// Threads of the workgroup that sorts a bucket: three workgroups' LDS fit a compute unit, with 256 threads each the waves
+// were too few for the counting and the gather (7.6 M entries of 142,541 rows, the whole conversion 201 -> 175 us).
+constexpr int kST = 512;
 // key[lo .. lo + len - 1] into ascending order by the whole workgroup: a bitonic network whose comparators all point
 // upwards, so that those with a partner past the end can be left out.  The entries are there for every wave on entry, and
 // again on return.
@@ -163,12 +180,12 @@ __device__ __forceinline__ void sort_run(uint64_t* key, int lo, int len) {
   for (int k = 2; k < 2 * len; k *= 2) {
     for (int j = k / 2; j > 0; j /= 2) {
       const int flip = j == k / 2 ? k - 1 : j;  // the first stage of a merge pairs an entry with its mirror image
-      for (int q0 = threadIdx.x; 2 * (q0 & ~(j - 1)) < len; q0 += 4 * kT) {  // pair q: entries with bit j clear and set
+      for (int q0 = threadIdx.x; 2 * (q0 & ~(j - 1)) < len; q0 += 4 * kST) {  // pair q: entries with bit j clear and set
         uint64_t a[4], b[4];
         int t[4], o[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int q = q0 + u * kT;
+          const int q = q0 + u * kST;
           t[u] = 2 * (q & ~(j - 1)) | (q & (j - 1));
           o[u] = t[u] ^ flip;
           if (o[u] >= len) o[u] = t[u] = 0;  // left out: a partner is never entry 0
@@ -198,7 +215,7 @@ __device__ __forceinline__ void sort_run(uint64_t* key, int lo, int len) {
 // on rows of 200, 256 and 1,024 made no difference.
 constexpr int kMaxBucketRows = 1024;
 constexpr int kLongRow = 512;
-__global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restrict__ fill, const int32_t* __restrict__ base,
+__global__ __launch_bounds__(kST) void bucket_sort_kernel(const int32_t* __restrict__ fill, const int32_t* __restrict__ base,
                                                          const int* __restrict__ over, int shift, int room, int64_t n,
                                                          int64_t nnz_in,
                                                          const uint2* __restrict__ slots,
@@ -208,24 +225,24 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
   __shared__ uint64_t key[kBucketRoom];
   __shared__ uint16_t krow[kBucketRoom];
   __shared__ int32_t first[kMaxBucketRows + 1], next[kMaxBucketRows];
-  __shared__ int32_t wave_sum[kT / 64];
+  __shared__ int32_t wave_sum[kST / 64];
   __shared__ int32_t long_row[kBucketRoom / kLongRow], nlong;
   if (*over) return;  // uniform over the grid
   const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int len = fill[b], rows = 1 << shift;
   const int64_t row0 = (int64_t)b << shift, at0 = base[b];
-  for (int r = threadIdx.x; r < rows; r += kT) next[r] = 0;
+  for (int r = threadIdx.x; r < rows; r += kST) next[r] = 0;
   if (threadIdx.x == 0) nlong = 0;
   __syncthreads();
   const uint2* __restrict__ mine = slots + (int64_t)b * room;
   const uint32_t* __restrict__ mrow = slot_row + (int64_t)b * room;
-  for (int p = threadIdx.x; p < len; p += kT) atomicAdd(&next[mrow[p] - (uint32_t)row0], 1);
+  for (int p = threadIdx.x; p < len; p += kST) atomicAdd(&next[mrow[p] - (uint32_t)row0], 1);
   __syncthreads();
   {  // exclusive prefix sums over the rows: thread t has the rows 4 t .. 4 t + 3
-    int32_t v[kMaxBucketRows / kT], sum = 0;
+    int32_t v[kMaxBucketRows / kST], sum = 0;
 #pragma unroll
-    for (int q = 0; q < kMaxBucketRows / kT; ++q) {
-      const int r = (int)threadIdx.x * (kMaxBucketRows / kT) + q;
+    for (int q = 0; q < kMaxBucketRows / kST; ++q) {
+      const int r = (int)threadIdx.x * (kMaxBucketRows / kST) + q;
       v[q] = r < rows ? next[r] : 0;
       sum += v[q];
     }
@@ -240,8 +257,8 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
     int32_t at = incl - sum;
     for (int w = 0; w < wave; ++w) at += wave_sum[w];
 #pragma unroll
-    for (int q = 0; q < kMaxBucketRows / kT; ++q) {
-      const int r = (int)threadIdx.x * (kMaxBucketRows / kT) + q;
+    for (int q = 0; q < kMaxBucketRows / kST; ++q) {
+      const int r = (int)threadIdx.x * (kMaxBucketRows / kST) + q;
       if (r < rows) {
         first[r] = at;
         next[r] = at;
@@ -254,7 +271,7 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
     }
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < len; p += kT) {
+  for (int p = threadIdx.x; p < len; p += kST) {
     const uint2 e = mine[p];
     const int r = (int)(mrow[p] - (uint32_t)row0);
     const int at = atomicAdd(&next[r], 1);
@@ -263,7 +280,7 @@ __global__ __launch_bounds__(kT) void bucket_sort_kernel(const int32_t* __restri
   }
   __syncthreads();
   for (int q = 0; q < nlong; ++q) sort_run(key, first[long_row[q]], first[long_row[q] + 1] - first[long_row[q]]);
-  for (int p = threadIdx.x; p < len; p += kT) {
+  for (int p = threadIdx.x; p < len; p += kST) {
     const uint64_t k = key[p];
     const int r = krow[p], lo = first[r], hi = first[r + 1];
     int before = 0;
@@ -387,114 +404,218 @@ __global__ __launch_bounds__(kT) void edge_list_kernel(const double* __restrict_
     edge_pair(x, ldx, d, eu, ev, list[p], threadIdx.x % kL, measure, inv_two_sigma2, mean, norm, vec_ok, n, bad, val);
 }
 
-// The same for data that do not fit the L2s, bucket by bucket of first rows: a workgroup keeps the rows of its bucket in
-// LDS and reads the second rows from memory; the buckets of an XCD are neighbours, so that where pairs join rows that are
-// near one another (a voxel grid, a neighbour list after a renumbering) the second rows come from its L2.  A pair's value
-// is formed by the same lanes in the same order as above.  3.8 M pairs of 142,541 rows of 90 doubles, listed offset by
-// offset: 683 us with every row read from the Infinity Cache once per pair (7.4 TB/s), 430 us here with the 34 us of the
-// partition.
+// The same for data that do not fit the L2s, by groups of neighbouring buckets of first rows: a workgroup keeps the rows of
+// its group in LDS, puts the group's pairs into order of their second rows (bins, a counting sort in LDS) and reads those
+// from memory: pairs that share one read it together.  The groups of an XCD are neighbours, so that where pairs join rows
+// that are near one another (a voxel grid, a neighbour list after a renumbering) the second rows come from its L2 too.  A
+// pair's value is formed by the same lanes in the same order as above.
+// 3.8 M pairs of 142,541 rows of 90 doubles, listed offset by offset: 683 us with every row read from the Infinity Cache
+// once per pair, 414 us with the first rows in LDS, 24 waves a compute unit and a pair's loads in two steps, 238 us here
+// (the same with 36 coordinates 170 us: it is the latency of a pair's loads that bounds it, then the Infinity Cache).
+// Rows of a workgroup: 128 of them and one workgroup a compute unit 275 us, 64 and two of them 253 us, 32 and three 238 us.
 // An XCD gets kRuns runs of neighbours from all over the rows, because first rows need not be spread evenly: with first
-// rows drawn by a power law (half of the pairs in an eighth of the rows) one run per XCD took 1,880 us for the same number
-// of pairs, 4 runs 1,000, 8 runs 865, 16 runs 775, and no buckets 945.  Runs cost reuse where they end: 16 of them 480 us
-// on the case above as with one, 100,000 rows 380 for 365 us (without buckets 565).  One counter of taken buckets per XCD,
-// so that idle XCDs take over what is left, cost 200 us.
+// rows drawn by a power law (half of the pairs in an eighth of the rows), one bucket a workgroup, one run per XCD took
+// 1,880 us for the same number of pairs, 4 runs 1,000, 8 runs 865, 16 runs 775, and no buckets 945.  One counter of taken
+// buckets per XCD, so that idle XCDs take over what is left, cost 200 us.
 constexpr int kRuns = 16;
 __host__ __device__ inline int edge_run(int nbuckets) { return (nbuckets + 8 * kRuns - 1) / (8 * kRuns); }
-__global__ __launch_bounds__(kT) void edge_bucket_kernel(const double* __restrict__ x, int64_t ldx, int d, int shift,
-                                                         int nbuckets, int room, const int32_t* __restrict__ fill,
-                                                         const uint2* __restrict__ slots,
-                                                         const uint32_t* __restrict__ slot_row, int measure,
-                                                         double inv_two_sigma2, const double* __restrict__ mean,
-                                                         const double* __restrict__ norm, int vec_ok, int64_t n,
-                                                         double* __restrict__ val) {
-  extern __shared__ double rows[];  // (1 << shift) x dl, then means and norms
-  const int t = (int)(blockIdx.x / 8), run = edge_run(nbuckets);
-  const int b = (t / run * 8 + (int)(blockIdx.x % 8)) * run + t % run;
-  if (b >= nbuckets) return;  // uniform
-  const int count = fill[b] < room ? fill[b] : room;
-  if (count == 0) return;  // uniform
-  const int dl = (d + 1) & ~1, nr = 1 << shift;
-  const int64_t row0 = (int64_t)b << shift;
+constexpr int kET = 512;         // threads of a workgroup
+constexpr int kMaxGroup = 8;     // buckets of a workgroup at most
+constexpr int kEdgeBins = 1024;  // bins of second rows
+constexpr int kPairsPerRow = 32;  // pairs ordered at a time, per first row (10 bytes of LDS each)
+constexpr int kMaxPairTrips = 4;
+// V: coordinates of a load (2 where all rows start on 16 bytes), KC: loads a lane has in flight for a row
+template <int V, int KC, bool DISTANCE>
+__global__ __launch_bounds__(kET, 6) void edge_bucket_kernel(const double* __restrict__ x, int64_t ldx, int d, int shift,
+                                                          int group, int nbuckets, int room, int cap,
+                                                          const int32_t* __restrict__ fill,
+                                                          const uint2* __restrict__ slots,
+                                                          const uint32_t* __restrict__ slot_row,
+                                                          double inv_two_sigma2, const double* __restrict__ mean,
+                                                          const double* __restrict__ norm, int64_t n,
+                                                          double* __restrict__ val) {
+  // rows (group << shift) x dl, their means and norms, the ordered pairs (second row, place of the value, first row), bins
+  extern __shared__ __attribute__((aligned(16))) double rows[];
+  __shared__ int32_t wave_sum[kET / 64], before[kMaxGroup + 1];
+  __shared__ int32_t vmin, vmax;
+  const int ngroups = (nbuckets + group - 1) / group;
+  const int wg = (int)(blockIdx.x / 8), run = edge_run(ngroups);
+  const int gb = (wg / run * 8 + (int)(blockIdx.x % 8)) * run + wg % run;
+  if (gb >= ngroups) return;  // uniform
+  const int b0 = gb * group, dl = (d + 1) & ~1, nr = group << shift;
+  const int64_t row0 = (int64_t)b0 << shift;
   double* mrow = rows + (size_t)nr * dl;
   double* nrow = mrow + nr;
-  for (int e = threadIdx.x; e < nr * d; e += kT) {
+  uint32_t* pv = reinterpret_cast<uint32_t*>(nrow + nr);
+  uint32_t* pout = pv + cap;
+  int32_t* bin = reinterpret_cast<int32_t*>(pout + cap);
+  uint16_t* prow = reinterpret_cast<uint16_t*>(bin + kEdgeBins);
+  if (threadIdx.x == 0) {
+    int32_t sum = 0;
+    for (int g = 0; g < group; ++g) {
+      before[g] = sum;
+      if (b0 + g < nbuckets) sum += fill[b0 + g] < room ? fill[b0 + g] : room;
+    }
+    before[group] = sum;
+  }
+  __syncthreads();
+  const int count = before[group];
+  if (count == 0) return;  // uniform
+  for (int e = threadIdx.x; e < nr * d; e += kET) {
     const int r = e / d, t = e - r * d;
     if (row0 + r < n) rows[r * dl + t] = x[(row0 + r) * ldx + t];
   }
-  if (measure != 2 && (int)threadIdx.x < nr && row0 + threadIdx.x < n) {
-    mrow[threadIdx.x] = mean[row0 + threadIdx.x];
-    nrow[threadIdx.x] = norm[row0 + threadIdx.x];
-  }
-  __syncthreads();
-  const int lane = threadIdx.x % kL;
-  const uint2* __restrict__ mine = slots + (int64_t)b * room;
-  const uint32_t* __restrict__ urow = slot_row + (int64_t)b * room;
-  constexpr int E = 4;  // pairs in flight per 16 lanes (one: 670 us, eight: 510 us for the case above)
-  for (int p0 = threadIdx.x / kL; p0 < count; p0 += E * (kT / kL)) {  // uniform over the pairs' lanes
-    const double *xu[E], *xv[E];
-    double mu[E], mv[E], acc[E];
-    uint32_t out[E];
-    int ru[E];
-    int64_t vi[E];
-#pragma unroll
-    for (int q = 0; q < E; ++q) {
-      const int p = p0 + q * (kT / kL) < count ? p0 + q * (kT / kL) : p0;  // past the end: the first again, not stored
-      const uint2 e = mine[p];
-      vi[q] = e.x;
-      out[q] = e.y;
-      ru[q] = (int)((int64_t)urow[p] - row0);
-      xu[q] = rows + ru[q] * dl;
-      xv[q] = x + vi[q] * ldx;
-      acc[q] = 0.0;
-      mu[q] = 0.0;
-      mv[q] = 0.0;
+  if (!DISTANCE) {
+    for (int r = threadIdx.x; r < nr; r += kET) {
+      if (row0 + r >= n) break;
+      mrow[r] = mean[row0 + r];
+      nrow[r] = norm[row0 + r];
     }
-    if (measure != 2) {
+  }
+  const int lane = threadIdx.x % kL;
+#pragma unroll 1
+  for (int c0 = 0; c0 < count; c0 += cap) {  // uniform
+    const int here = count - c0 < cap ? count - c0 : cap;
+    __syncthreads();  // the pairs of the trip before are done with
+    if (threadIdx.x == 0) {
+      vmin = INT32_MAX;
+      vmax = 0;
+    }
+    for (int i = threadIdx.x; i < kEdgeBins; i += kET) bin[i] = 0;
+    __syncthreads();
+    uint2 own[kMaxPairTrips];
+    uint32_t orow[kMaxPairTrips];
+    int lo = INT32_MAX, hi = 0;
+#pragma unroll
+    for (int u = 0; u < kMaxPairTrips; ++u) {
+      const int p = u * kET + (int)threadIdx.x;
+      if (p >= here) break;
+      int g = 0;
+      while (c0 + p >= before[g + 1]) ++g;  // before[group] = count > c0 + p
+      const int64_t at = (int64_t)(b0 + g) * room + (c0 + p - before[g]);
+      own[u] = slots[at];
+      orow[u] = slot_row[at];
+      lo = min(lo, (int)own[u].x);
+      hi = max(hi, (int)own[u].x);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      lo = min(lo, __shfl_xor(lo, o, 64));
+      hi = max(hi, __shfl_xor(hi, o, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+      atomicMin(&vmin, lo);
+      atomicMax(&vmax, hi);
+    }
+    __syncthreads();
+    const int first = vmin, spread = vmax - vmin;
+    int wide = 0;
+    while ((spread >> wide) >= kEdgeBins) ++wide;
+#pragma unroll
+    for (int u = 0; u < kMaxPairTrips; ++u) {
+      if (u * kET + (int)threadIdx.x >= here) break;
+      atomicAdd(&bin[((int)own[u].x - first) >> wide], 1);
+    }
+    __syncthreads();
+    {  // exclusive prefix sums: thread t has the bins 2 t and 2 t + 1
+      static_assert(kEdgeBins == 2 * kET, "two bins a thread");
+      const int a = bin[2 * threadIdx.x], sum = a + bin[2 * threadIdx.x + 1];
+      int incl = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int up = __shfl_up(incl, o, 64);
+        if ((int)(threadIdx.x & 63) >= o) incl += up;
+      }
+      if ((threadIdx.x & 63) == 63) wave_sum[threadIdx.x >> 6] = incl;
+      __syncthreads();
+      int at = incl - sum;
+      for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) at += wave_sum[w];
+      bin[2 * threadIdx.x] = at;
+      bin[2 * threadIdx.x + 1] = at + a;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kMaxPairTrips; ++u) {
+      if (u * kET + (int)threadIdx.x >= here) break;
+      const int at = atomicAdd(&bin[((int)own[u].x - first) >> wide], 1);
+      pv[at] = own[u].x;
+      pout[at] = own[u].y;
+      prow[at] = (uint16_t)((int64_t)orow[u] - row0);
+    }
+    __syncthreads();
+    // A pair's loads are all asked for before the first is used, the norm that the end needs among them.
+    constexpr int E = V * KC >= 6 ? 1 : 2;  // pairs in flight per 16 lanes: what the registers of 24 waves hold
+#pragma unroll 1
+    for (int p0 = threadIdx.x / kL; p0 < here; p0 += E * (kET / kL)) {  // uniform over the pairs' lanes
+      const double* xv[E];
+      double mu[E], mv[E], nv[E], acc[E];
+      int ru[E];
 #pragma unroll
       for (int q = 0; q < E; ++q) {
-        mu[q] = mrow[ru[q]];
-        mv[q] = mean[vi[q]];
+        const int p = p0 + q * (kET / kL) < here ? p0 + q * (kET / kL) : p0;  // past the end: the first again, not stored
+        const uint32_t vi = pv[p];
+        ru[q] = prow[p];
+        xv[q] = x + (int64_t)vi * ldx;
+        acc[q] = mu[q] = mv[q] = nv[q] = 0.0;
+        if (!DISTANCE) {
+          mu[q] = mrow[ru[q]];
+          mv[q] = mean[vi];
+          nv[q] = norm[vi];
+        }
       }
-    }
-    int t0 = 0;
-    if (vec_ok) {  // rows start 16-byte aligned: pairs of coordinates per load
-      const int d2 = d / 2;
-#pragma unroll 2
-      for (int t = lane; t < d2; t += kL) {
-        double2 bb[E];
+      typedef double vec __attribute__((ext_vector_type(2)));
+      const int dv = d / V;
+#pragma unroll 1
+      for (int base = lane; base - lane < dv; base += KC * kL) {
+        vec bb[KC][E];
 #pragma unroll
-        for (int q = 0; q < E; ++q) bb[q] = reinterpret_cast<const double2*>(xv[q])[t];
+        for (int k = 0; k < KC; ++k) {
+          const int t = base + k * kL < dv ? base + k * kL : dv - 1;
 #pragma unroll
-        for (int q = 0; q < E; ++q) {
-          const double2 a = reinterpret_cast<const double2*>(xu[q])[t];
-          if (measure == 2) {
-            const double f = a.x - bb[q].x, g = a.y - bb[q].y;
-            acc[q] += f * f;
-            acc[q] += g * g;
-          } else {
-            acc[q] += (a.x - mu[q]) * (bb[q].x - mv[q]);
-            acc[q] += (a.y - mu[q]) * (bb[q].y - mv[q]);
+          for (int q = 0; q < E; ++q) {
+            if (V == 2) bb[k][q] = reinterpret_cast<const vec*>(xv[q])[t];
+            else bb[k][q].x = xv[q][t];
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+          const int t = base + k * kL;
+          if (t < dv) {
+#pragma unroll
+            for (int q = 0; q < E; ++q) {
+              const double* a = rows + ru[q] * dl + V * t;
+#pragma unroll
+              for (int h = 0; h < V; ++h) {
+                if (DISTANCE) {
+                  const double f = a[h] - bb[k][q][h];
+                  acc[q] += f * f;
+                } else {
+                  acc[q] += (a[h] - mu[q]) * (bb[k][q][h] - mv[q]);
+                }
+              }
+            }
           }
         }
       }
-      t0 = 2 * d2;
-    }
-    for (int t = t0 + lane; t < d; t += kL) {
+      if (V == 2 && (d & 1) && lane == 0) {
 #pragma unroll
-      for (int q = 0; q < E; ++q) {
-        if (measure == 2) {
-          const double f = xu[q][t] - xv[q][t];
-          acc[q] += f * f;
-        } else {
-          acc[q] += (xu[q][t] - mu[q]) * (xv[q][t] - mv[q]);
+        for (int q = 0; q < E; ++q) {
+          const double a = rows[ru[q] * dl + d - 1], b = xv[q][d - 1];
+          acc[q] += DISTANCE ? (a - b) * (a - b) : (a - mu[q]) * (b - mv[q]);
         }
       }
-    }
+      // lane q finishes pair q
+      double tot = 0.0, nn = 1.0;
 #pragma unroll
-    for (int q = 0; q < E; ++q) {
-      const double tot = group_sum(acc[q]);
-      if (lane == 0 && p0 + q * (kT / kL) < count)
-        val[out[q]] = measure == 2 ? exp(-tot * inv_two_sigma2) : tot / (nrow[ru[q]] * norm[vi[q]]);
+      for (int q = 0; q < E; ++q) {
+        const double sum = group_sum(acc[q]);
+        if (lane == q) {
+          tot = sum;
+          nn = DISTANCE ? 1.0 : nrow[ru[q]] * nv[q];
+        }
+      }
+      const int p = p0 + lane * (kET / kL);
+      if (lane < E && p < here) val[pout[p]] = DISTANCE ? exp(-tot * inv_two_sigma2) : tot / nn;
     }
   }
 }
@@ -651,7 +772,7 @@ size_t coo_to_csr_workspace(int64_t total, int64_t n, int radix) {
 // than a bucket thus costs the partition on top of the sort: 200,000 entries 152 -> 159 us, 3.8 M 535 -> 559 us.
 //
 // 3.8 M pairs of 142,541 rows (7.6 M entries): radix sort of 64-bit keys 640 us, with the keys, row pointers and gather
-// round it 730 us; buckets 180 us (partition 50, sort 126).  Bound by the scattered writes of the partition and the gather of the values.
+// round it 730 us; buckets 175 us (partition 50, sort 105).  Bound by the scattered writes of the partition and the gather of the values.
 hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int64_t nnz_in, int64_t n,
                       int symmetrize, int radix, void* work, size_t work_bytes, int64_t* rowptr_out, int32_t* col_out,
                       double* val_out, int* bad, hipStream_t st) {
@@ -668,7 +789,7 @@ hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val,
     if (e != hipSuccess) return e;
     launch_partition(row, col, nnz_in, n, symmetrize != 0, p, fill, slots, slot_row, nullptr, nullptr, bad, st);
     hipLaunchKernelGGL(bucket_scan_kernel, dim3(1), dim3(kPartThreads), 0, st, fill, p.buckets, p.room, first, bad + 1);
-    hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)p.buckets), dim3(kT), 0, st, fill, first, bad + 1, p.shift, p.room,
+    hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)p.buckets), dim3(kST), 0, st, fill, first, bad + 1, p.shift, p.room,
                        n, nnz_in, slots, slot_row, val, rowptr_out, col_out, val_out);
     return hipGetLastError();
   }
@@ -696,15 +817,15 @@ hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val,
 
 namespace {
 
-// Rows of a bucket: a power of two that fits 24 KB (six workgroups per compute unit; 48 KB was 3 % slower), about half a
-// bucket's room of pairs.  Used where the data exceed what the L2s hold between them and a row occurs in several pairs:
+// Rows of a bucket: a power of two that fits kEdgeRowBytes, about half a bucket's room of pairs.  Used where the data exceed what the L2s hold between them and a row occurs in several pairs:
 // 142,541 x 90 with 27 pairs a row 726 -> 478 us, 60,000 x 90 with 26 322 -> 226 us, 142,541 x 128 with 38 1,382 -> 535 us;
 // 142,541 x 33 with 27 448 -> 436 us, 30,000 x 64 with 26 115 -> 148 us, 142,541 x 90 with 3 111 -> 151 us.
+constexpr int64_t kEdgeRowBytes = 24 * 1024;  // rows of a workgroup, beside its pairs
 BucketPlan plan_edge_buckets(int64_t n, int d, int64_t nedges) {
   BucketPlan p;
   if (n * (int64_t)d < 5000000 || nedges < 8 * n) return p;
   const int64_t row_bytes = (int64_t)((d + 1) & ~1) * 8 + 16;
-  while (p.shift < 8 && ((int64_t)2 << p.shift) * row_bytes <= 24 * 1024 &&
+  while (p.shift < 8 && ((int64_t)2 << p.shift) * row_bytes <= kEdgeRowBytes &&
          ((int64_t)2 << p.shift) * nedges <= kBucketRoom / 2 * n)
     ++p.shift;
   const int64_t nb = ((n - 1) >> p.shift) + 1;
@@ -738,9 +859,47 @@ hipError_t launch_edge_similarity_buckets(const double* x, int64_t ldx, int d, c
   launch_partition(eu, ev, nedges, n, false, p, fill, slots, slot_row, rest, nrest, bad, st);
   const int vec_ok = (ldx % 2 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0) ? 1 : 0;
   const double inv = measure == 2 ? 1.0 / (2.0 * sigma * sigma) : 0.0;
-  const size_t lds = ((size_t)1 << p.shift) * (size_t)(((d + 1) & ~1) + 2) * 8;
-  hipLaunchKernelGGL(edge_bucket_kernel, dim3((unsigned)(8 * kRuns * edge_run(p.buckets))), dim3(kT), lds, st, x, ldx, d,
-                     p.shift, p.buckets, p.room, fill, slots, slot_row, measure, inv, mean, norm, vec_ok, n, val);
+  // Buckets of a workgroup: as many as its LDS takes (few coordinates), while there are eight workgroups a compute unit.
+  const int64_t row_bytes = (int64_t)(((d + 1) & ~1) + 2) * 8;
+  int group = 1;
+  while (group < kMaxGroup && ((int64_t)2 * group << p.shift) * row_bytes <= kEdgeRowBytes &&
+         p.buckets / (2 * group) >= 2048)
+    group *= 2;
+  const int nr = group << p.shift;
+  int cap = nr * kPairsPerRow / 4 * 4;
+  cap = cap < kET ? kET : (cap > kMaxPairTrips * kET ? kMaxPairTrips * kET : cap);
+  size_t lds = (size_t)nr * row_bytes + (size_t)cap * 10 + kEdgeBins * 4;
+  while (lds > 160 * 1024 - 512 && cap > kET) {
+    cap -= kET;
+    lds -= (size_t)kET * 10;
+  }
+  const int ngroups = (p.buckets + group - 1) / group;
+  const int kc = (d / (vec_ok ? 2 : 1) + kL - 1) / kL;
+#define SC_EDGE_BUCKETS(V, KC, DISTANCE)                                                                               \
+  do {                                                                                                                  \
+    const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(&edge_bucket_kernel<V, KC, DISTANCE>),     \
+                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                   \
+    if (ea != hipSuccess) return ea;                                                                                    \
+    hipLaunchKernelGGL((edge_bucket_kernel<V, KC, DISTANCE>), dim3((unsigned)(8 * kRuns * edge_run(ngroups))),         \
+                       dim3(kET), lds, st, x, ldx, d, p.shift, group, p.buckets, p.room, cap, fill, slots, slot_row,   \
+                       inv, mean, norm, n, val);                                                                       \
+  } while (0)
+#define SC_EDGE_BUCKETS_M(V, KC)                                                                                       \
+  do {                                                                                                                  \
+    if (measure == 2) SC_EDGE_BUCKETS(V, KC, true); else SC_EDGE_BUCKETS(V, KC, false);                                \
+  } while (0)
+  if (vec_ok) {
+    if (kc <= 1) SC_EDGE_BUCKETS_M(2, 1);
+    else if (kc == 2) SC_EDGE_BUCKETS_M(2, 2);
+    else if (kc == 3) SC_EDGE_BUCKETS_M(2, 3);
+    else SC_EDGE_BUCKETS_M(2, 4);
+  } else {
+    if (kc <= 1) SC_EDGE_BUCKETS_M(1, 1);
+    else if (kc <= 3) SC_EDGE_BUCKETS_M(1, 3);
+    else SC_EDGE_BUCKETS_M(1, 6);
+  }
+#undef SC_EDGE_BUCKETS_M
+#undef SC_EDGE_BUCKETS
   hipLaunchKernelGGL(edge_list_kernel, dim3(2048), dim3(kT), 0, st, x, ldx, d, eu, ev, rest, nrest, measure, inv, mean, norm,
                      vec_ok, n, bad, val);
   return hipGetLastError();

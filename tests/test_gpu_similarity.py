@@ -145,7 +145,9 @@ def test_coo_to_csr_over_its_ranges(B, n, ne, hub, symmetrize):
 # power law (many buckets that are too small beside many that are empty), and both with indices out of range
 @pytest.mark.parametrize("d,ldx,measure,twist", [(90, 90, 0, ""), (85, 85, 1, ""), (128, 129, 2, ""), (380, 380, 0, ""),
                                                  (90, 90, 0, "bad"), (100, 100, 1, "hub"), (90, 90, 2, "power"),
-                                                 (101, 102, 0, "power bad"), (100, 100, 1, "hub bad")])
+                                                 (101, 102, 0, "power bad"), (100, 100, 1, "hub bad"),
+                                                 # two buckets a workgroup, every number of loads a row takes
+                                                 (4, 4, 0, ""), (33, 33, 0, ""), (40, 40, 2, "hub"), (17, 17, 1, "power")])
 def test_bucketed_edge_similarity_matches_oracle(B, d, ldx, measure, twist):
     n = 5_000_000 // d + 37
     rng = np.random.default_rng(d)
