@@ -482,27 +482,36 @@ void enqueue_block_qr(double* basis, int64_t n, int64_t ld, int col, int b, doub
   if (!tm) tm = &none;
   const double blk = 8.0 * (double)n * b;
   tm->begin(kFamQr);
-  // from the partial Gram blocks to the factor: one launch where there are few of them
-  auto factor = [&](const double* parts, int np, double* gcopy, double* rout, const double* rprev, double abs_tol2,
-                    double rel_tol) {
-    if (gram_cholesky_takes_parts(np, b)) {
-      HIP_TRY(launch_gram_cholesky_parts(parts, np, b, gcopy, rinv, rout, rprev, abs_tol2, rel_tol, st));
-    } else {
-      HIP_TRY(launch_reduce_partials(parts, np, b, b, gram, nullptr, 0, nullptr, 0, st));
-      HIP_TRY(launch_gram_cholesky(gram, b, gcopy, rinv, rout, rprev, abs_tol2, rel_tol, st));
-    }
-  };
-  if (ngram > 0) {
-    factor(gpart, ngram, g_out, r1, nullptr, kAbsDrop2, kRelDrop);
-  } else {
+  const double* parts = gpart;  // the partial Gram blocks to factorize next
+  int np = ngram;
+  if (ngram <= 0) {
     const ProjectPlan plan = plan_project(n, b, kMaxPartials);
     HIP_TRY(launch_project(basis, n, ld, col, b, col, b, plan, part, st));
-    factor(part, plan.npart, g_out, r1, nullptr, kAbsDrop2, kRelDrop);
+    parts = part;
+    np = plan.npart;
   }
-  HIP_TRY(launch_update_gram(basis, n, ld, col, b, rinv, b, col, 1, gpart, st));
+  // where the partial blocks are few the launch that applies the inverse factor makes it, too
+  auto factor = [&](double* gcopy, double* rout, const double* rprev, double abs_tol2, double rel_tol) {
+    HIP_TRY(launch_reduce_partials(parts, np, b, b, gram, nullptr, 0, nullptr, 0, st));
+    HIP_TRY(launch_gram_cholesky(gram, b, gcopy, rinv, rout, rprev, abs_tol2, rel_tol, st));
+  };
+  if (gram_cholesky_takes_parts(np, b)) {
+    double* next = parts == gpart ? part : gpart;  // read by every workgroup while the first ones write
+    HIP_TRY(launch_factor_update_gram(basis, n, ld, col, b, {parts, np, g_out, r1, nullptr, kAbsDrop2, kRelDrop}, next, st));
+    parts = next;
+  } else {
+    factor(g_out, r1, nullptr, kAbsDrop2, kRelDrop);
+    HIP_TRY(launch_update_gram(basis, n, ld, col, b, rinv, b, col, 1, gpart, st));
+    parts = gpart;
+  }
+  np = plan_update_gram(n);
   // second pass: a column that survived the first pass has unit norm, so only exact zeros are dropped
-  factor(gpart, plan_update_gram(n), nullptr, r_out, r1, 0.25, 1e-8);
-  HIP_TRY(launch_apply_rinv(basis, n, ld, col, b, rinv, z, s, st));
+  if (gram_cholesky_takes_parts(np, b)) {
+    HIP_TRY(launch_factor_apply_rinv(basis, n, ld, col, b, {parts, np, nullptr, r_out, r1, 0.25, 1e-8}, z, s, st));
+  } else {
+    factor(nullptr, r_out, r1, 0.25, 1e-8);
+    HIP_TRY(launch_apply_rinv(basis, n, ld, col, b, rinv, z, s, st));
+  }
   tm->end(kFamQr, (ngram > 0 ? 4.0 : 5.0) * blk + (z ? blk : 0.0), 4.0 * (double)n * b * b);
 }
 

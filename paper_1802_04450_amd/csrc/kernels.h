@@ -83,11 +83,23 @@ hipError_t launch_row_gemm(double* basis, int64_t n, int64_t ld, int acol0, int 
 //   If rprev != null: rout = r * rprev (composition of two passes) else rout = r.  Any output may be null.
 hipError_t launch_gram_cholesky(const double* g_in, int b, double* g_out, double* rinv, double* rout,
                                 const double* rprev, double abs_tol2, double rel_tol, hipStream_t st);
-// The same on the sum of npart partial Gram blocks (as launch_project and launch_update_gram leave them), where
-// gram_cholesky_takes_parts says that one launch is the cheaper way.
+// The same on the sum of nparts partial Gram blocks (as launch_project and launch_update_gram leave them), as the first
+// part of the launch that applies rinv, where gram_cholesky_takes_parts says that this is the cheaper way.
+struct GramParts {
+  const double* parts = nullptr;
+  int nparts = 0;
+  double *g_out = nullptr, *r_out = nullptr;  // may be null
+  const double* rprev = nullptr;
+  double abs_tol2 = 0.0, rel_tol = 0.0;
+};
 bool gram_cholesky_takes_parts(int npart, int b);
-hipError_t launch_gram_cholesky_parts(const double* gpart, int npart, int b, double* g_out, double* rinv, double* rout,
-                                      const double* rprev, double abs_tol2, double rel_tol, hipStream_t st);
+// W <- W rinv for W = basis[:, col : col+b]; gpart: the partial Gram matrices of the new block (see launch_update_gram),
+// another buffer than f.parts
+hipError_t launch_factor_update_gram(double* basis, int64_t n, int64_t ld, int col, int b, const GramParts& f, double* gpart,
+                                     hipStream_t st);
+// as launch_apply_rinv
+hipError_t launch_factor_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const GramParts& f, double* z,
+                                    const double* s, hipStream_t st);
 // basis[:, col0 : col0+b] = basis[:, col0 : col0+b] * rinv  (rinv b x b row-major stride kPartialPad);
 // if z != null also z[i*b + t] = s[i] * new value.
 hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const double* rinv, double* z,

@@ -1258,18 +1258,161 @@ __global__ __launch_bounds__(kCholThreads) void gram_cholesky_kernel(const doubl
   }
 }
 
+// Cholesky of the b x b Gram matrix in the registers of one wave: lane t owns column t of G, R and R^-1;
+// values of other columns travel by lane reads.  Same dropping rule as documented in kernels.h.
+// Value of lane `l` (a compile-time constant after unrolling) for the whole wave: a scalar lane read, not a trip
+// through the LDS crossbar.
+__device__ __forceinline__ double bcast_lane(double v, int l) {
+  const long long bits = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)bits, l);
+  const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// sqrt(p) and its inverse, and quotients by it, for the factorizations below: one approximate inverse root (v_rsq_f64),
+// two Newton steps, then root, inverse and quotients each corrected by their own remainder, as a division does.  Half the
+// dependent operations of a square root and a division, and the inverse serves the whole row and the triangular inverse
+// (b = 16: 9.2 -> 7.7 us, b = 8 with the sum of the partial blocks 4.9 -> 4.0 us; b = 32, bound by the fetch of its code,
+// 38.7 -> 36.6 us).  p > 0 and normal: it has passed the drop test.
+__device__ __forceinline__ void root_and_inverse(double p, double* root, double* inv) {
+  double y = __builtin_amdgcn_rsq(p);
+  const double h = 0.5 * p;
+  y = fma(y, fma(-h * y, y, 0.5), y);
+  y = fma(y, fma(-h * y, y, 0.5), y);
+  double r = p * y;
+  r = fma(fma(-r, r, p), 0.5 * y, r);
+  *inv = fma(fma(-r, y, 1.0), y, y);
+  *root = r;
+}
+__device__ __forceinline__ double quotient(double a, double root, double inv) {
+  const double q = a * inv;
+  return fma(fma(-q, root, a), inv, q);
+}
+
+// Cholesky with column drop, inverse and product with the factor before it, by one wave, lane t = column t (see
+// launch_gram_cholesky): b <= 16.  g: b x b, row stride gs.  A finished row of R is taken out of all remaining rows at
+// once, a finished entry of the inverse's column goes into all sums that wait for it, so that the multiply-adds of a step
+// do not wait for one another.
+template <int B>
+__device__ __forceinline__ void chol_wave(const double* g, int gs, double* __restrict__ g_out,
+                                          double* __restrict__ rinv_out, double* __restrict__ r_out,
+                                          const double* __restrict__ rprev, double abs_tol2, double rel_tol) {
+  const int t = threadIdx.x & 63;
+  const bool act = t < B;
+  const int tc = act ? t : 0;
+  double gcol[B], rcol[B], ricol[B], root[B], inv[B];
+  double gdiag = 0.0;  // own diagonal entry of g
+#pragma unroll
+  for (int q = 0; q < B; ++q) {
+    const int lo = q < tc ? q : tc, hi = q < tc ? tc : q;
+    gcol[q] = g[lo * gs + hi];  // upper triangle, mirrored
+    gdiag = q == tc ? gcol[q] : gdiag;
+    ricol[q] = 0.0;
+  }
+  if (g_out && act) {
+#pragma unroll
+    for (int q = 0; q < B; ++q) g_out[q * kPartialPad + t] = gcol[q];
+  }
+#pragma unroll
+  for (int k = 0; k < B; ++k) {
+    const double gkk = bcast_lane(gdiag, k), pk = bcast_lane(gcol[k], k);
+    const bool drop = !(gkk > abs_tol2) || !(pk > rel_tol * gkk);
+    root_and_inverse(drop ? 1.0 : pk, &root[k], &inv[k]);
+    rcol[k] = drop || t < k ? 0.0 : (t == k ? root[k] : quotient(gcol[k], root[k], inv[k]));
+#pragma unroll
+    for (int q = k + 1; q < B; ++q) gcol[q] -= bcast_lane(rcol[k], q) * rcol[k];
+  }
+  double rcc = 0.0;  // own diagonal entry
+#pragma unroll
+  for (int q = 0; q < B; ++q) rcc = (q == t) ? rcol[q] : rcc;
+  // ricol[r] holds the sum over the finished entries x > r of R[r][x] Rinv[x][t] until it is its turn
+#pragma unroll
+  for (int r = B - 1; r >= 0; --r) {
+    const double rrr = bcast_lane(rcol[r], r);
+    double v = 0.0;
+    if (rrr != 0.0 && rcc != 0.0) v = (t == r) ? inv[r] : (t > r ? -quotient(ricol[r], root[r], inv[r]) : 0.0);
+    ricol[r] = v;
+#pragma unroll
+    for (int x = 0; x < r; ++x) ricol[x] += bcast_lane(rcol[x], r) * v;
+  }
+  if (rinv_out && act) {
+#pragma unroll
+    for (int q = 0; q < B; ++q) rinv_out[q * kPartialPad + t] = ricol[q];
+  }
+  if (r_out) {
+    if (rprev) {
+      double v[B];
+#pragma unroll
+      for (int q = 0; q < B; ++q) v[q] = 0.0;
+#pragma unroll
+      for (int x = 0; x < B; ++x) {
+        const double p = rprev[x * kPartialPad + tc];
+#pragma unroll
+        for (int q = 0; q <= x; ++q) v[q] += bcast_lane(rcol[q], x) * p;
+      }
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (act) r_out[q * kPartialPad + t] = v[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < B; ++q)
+        if (act) r_out[q * kPartialPad + t] = rcol[q];
+    }
+  }
+}
+
+// From few partial Gram blocks to the inverse factor, by a workgroup that goes on with it: every workgroup of the consuming
+// launch adds the partial blocks up (in one fixed order) and factorizes for itself, which costs it what a launch of one
+// workgroup for that took, without the launch; workgroup 0 writes what others read.  Up to 32 loads one after the other per
+// thread.  Block QR of 2,000 x 8: 38 -> 31 us, 16,000 x 8: 63 -> 40 us, 4,040 x 16: 59 -> 47 us.  sub: 256 doubles of LDS,
+// rinv: B rows of kPartialPad, there for all on return.
+template <int B>
+__device__ __forceinline__ void chol_of_parts(const GramParts& f, double* sub, double* rinv) {
+  constexpr int SPLIT = kThreads / (B * B);
+  const int e = threadIdx.x % (B * B), r = threadIdx.x / (B * B);
+  const double* p = f.parts + (e / B) * kPartialPad + e % B;
+  double acc = 0.0;
+#pragma unroll 8
+  for (int q = r; q < f.nparts; q += SPLIT) acc += p[(int64_t)q * B * kPartialPad];
+  sub[threadIdx.x] = acc;
+  __syncthreads();
+  if (threadIdx.x < 64) {  // a wave
+#pragma unroll
+    for (int h = 0; h < B * B; h += 64) {
+      double tot = sub[h + threadIdx.x];
+#pragma unroll
+      for (int q = 1; q < SPLIT; ++q) tot += sub[q * B * B + h + threadIdx.x];
+      sub[h + threadIdx.x] = tot;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own LDS operations complete in order
+    __builtin_amdgcn_wave_barrier();
+    const bool writes = blockIdx.x == 0;
+    chol_wave<B>(sub, B, writes ? f.g_out : nullptr, rinv, writes ? f.r_out : nullptr, f.rprev, f.abs_tol2, f.rel_tol);
+  }
+  __syncthreads();
+}
+
 // Row groups per workgroup: the staging of R^-1 is paid once for all of them, but only once the chip has its workgroups
 // (always 16 groups: 12.4 us for 4,040 rows of 8 columns, in eight workgroups, now 3.5; 100,000 x 16: 19 -> 12 us).
 inline int rinv_trips(int64_t n, int b) {
   const int64_t groups = ceil_div64(n, kThreads / b), trips = groups / 1024;
   return (int)(trips < 1 ? 1 : (trips > 16 ? 16 : trips));
 }
+// FACTOR = b: R^-1 is made here, from the partial Gram blocks; 0: it is read from rinv
+template <int FACTOR>
 __global__ __launch_bounds__(kThreads) void apply_rinv_kernel(double* __restrict__ basis, int64_t n, int64_t ld,
                                                               int col0, int b, int trips, const double* __restrict__ rinv,
-                                                              double* __restrict__ z, const double* __restrict__ s) {
+                                                              double* __restrict__ z, const double* __restrict__ s,
+                                                              GramParts f) {
   __shared__ double Ri[kMaxBlock][kMaxBlock + 1];
   __shared__ double Wt[2 * kThreads];  // rows_per_block rows of b + 1 doubles (b >= 1)
-  for (int e = threadIdx.x; e < b * b; e += kThreads) Ri[e / b][e % b] = rinv[(e / b) * kPartialPad + (e % b)];
+  if constexpr (FACTOR > 0) {
+    __shared__ double made[FACTOR * kPartialPad];
+    chol_of_parts<FACTOR>(f, Wt, made);
+    for (int e = threadIdx.x; e < b * b; e += kThreads) Ri[e / b][e % b] = made[(e / b) * kPartialPad + (e % b)];
+  } else {
+    for (int e = threadIdx.x; e < b * b; e += kThreads) Ri[e / b][e % b] = rinv[(e / b) * kPartialPad + (e % b)];
+  }
   const int rows_per_block = kThreads / b;
   const int t = threadIdx.x % b, rl = threadIdx.x / b;
   // the entry of the next trip is requested before this trip's sums, so its latency hides behind them
@@ -1458,12 +1601,13 @@ __global__ __launch_bounds__(kThreads) void cheb_combine_kernel(const double* __
 // Workgroups walk the 128-row tiles with a grid stride, so the number of Gram partials is the grid size.
 // PIPE: the variant for long contractions, see the note at its loop.  It needs more registers (fewer resident waves),
 // which costs more than it gains when the contraction has only a trip or two, so it is a kernel of its own.
-template <int NT, bool PIPE>
+// FACTOR = b <= 16: bmat is the R^-1 that is made here, from the partial Gram blocks (kdim = b then).
+template <int NT, bool PIPE, int FACTOR>
 __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void update_gram_kernel(double* __restrict__ basis, int64_t n, int64_t ld,
                                                                int acol0, int kdim, const double* __restrict__ bmat, int b,
                                                                int ccol0, int vec_ok, int overwrite,
                                                                double* __restrict__ gpart,
-                                                               const int* __restrict__ skip) {
+                                                               const int* __restrict__ skip, GramParts f) {
   if (skip && *skip) return;  // uniform over the grid
   constexpr int MT = 2;
   constexpr int BW = NT * 16;
@@ -1479,7 +1623,14 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void update_gram_kernel(
   auto load_chunk = [&](int k0, int kc, int kc16) {
     stage_coefficients<NT>(lds, bmat, kPartialPad, k0, kc, kc16, 0, b);
   };
-  if (single) {
+  if constexpr (FACTOR > 0) {
+    static_assert(NT == 1 && kThreads == 256, "a thread per entry of a 16 x 16 block");
+    double* made = wt + 256;
+    chol_of_parts<FACTOR>(f, wt, made);
+    const int kk = threadIdx.x >> 4, t = threadIdx.x & 15;  // the order of stage_coefficients
+    lds[(((kk & 3) * 4 + (kk >> 2)) << 4) + t] = kk < FACTOR && t < FACTOR ? made[kk * kPartialPad + t] : 0.0;
+    __syncthreads();
+  } else if (single) {
     load_chunk(0, kdim, (kdim + 15) & ~15);
     __syncthreads();
   }
@@ -1648,109 +1799,6 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void update_gram_kernel(
   }
 }
 
-// Cholesky of the b x b Gram matrix in the registers of one wave: lane t owns column t of G, R and R^-1;
-// values of other columns travel by lane reads.  Same dropping rule as documented in kernels.h.
-// Value of lane `l` (a compile-time constant after unrolling) for the whole wave: a scalar lane read, not a trip
-// through the LDS crossbar.
-__device__ __forceinline__ double bcast_lane(double v, int l) {
-  const long long bits = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)bits, l);
-  const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// sqrt(p) and its inverse, and quotients by it, for the factorizations below: one approximate inverse root (v_rsq_f64),
-// two Newton steps, then root, inverse and quotients each corrected by their own remainder, as a division does.  Half the
-// dependent operations of a square root and a division, and the inverse serves the whole row and the triangular inverse
-// (b = 16: 9.2 -> 7.7 us, b = 8 with the sum of the partial blocks 4.9 -> 4.0 us; b = 32, bound by the fetch of its code,
-// 38.7 -> 36.6 us).  p > 0 and normal: it has passed the drop test.
-__device__ __forceinline__ void root_and_inverse(double p, double* root, double* inv) {
-  double y = __builtin_amdgcn_rsq(p);
-  const double h = 0.5 * p;
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  y = fma(y, fma(-h * y, y, 0.5), y);
-  double r = p * y;
-  r = fma(fma(-r, r, p), 0.5 * y, r);
-  *inv = fma(fma(-r, y, 1.0), y, y);
-  *root = r;
-}
-__device__ __forceinline__ double quotient(double a, double root, double inv) {
-  const double q = a * inv;
-  return fma(fma(-q, root, a), inv, q);
-}
-
-// Cholesky with column drop, inverse and product with the factor before it, by one wave, lane t = column t (see
-// launch_gram_cholesky): b <= 16.  g: b x b, row stride gs.  A finished row of R is taken out of all remaining rows at
-// once, a finished entry of the inverse's column goes into all sums that wait for it, so that the multiply-adds of a step
-// do not wait for one another.
-template <int B>
-__device__ __forceinline__ void chol_wave(const double* g, int gs, double* __restrict__ g_out,
-                                          double* __restrict__ rinv_out, double* __restrict__ r_out,
-                                          const double* __restrict__ rprev, double abs_tol2, double rel_tol) {
-  const int t = threadIdx.x & 63;
-  const bool act = t < B;
-  const int tc = act ? t : 0;
-  double gcol[B], rcol[B], ricol[B], root[B], inv[B];
-  double gdiag = 0.0;  // own diagonal entry of g
-#pragma unroll
-  for (int q = 0; q < B; ++q) {
-    const int lo = q < tc ? q : tc, hi = q < tc ? tc : q;
-    gcol[q] = g[lo * gs + hi];  // upper triangle, mirrored
-    gdiag = q == tc ? gcol[q] : gdiag;
-    ricol[q] = 0.0;
-  }
-  if (g_out && act) {
-#pragma unroll
-    for (int q = 0; q < B; ++q) g_out[q * kPartialPad + t] = gcol[q];
-  }
-#pragma unroll
-  for (int k = 0; k < B; ++k) {
-    const double gkk = bcast_lane(gdiag, k), pk = bcast_lane(gcol[k], k);
-    const bool drop = !(gkk > abs_tol2) || !(pk > rel_tol * gkk);
-    root_and_inverse(drop ? 1.0 : pk, &root[k], &inv[k]);
-    rcol[k] = drop || t < k ? 0.0 : (t == k ? root[k] : quotient(gcol[k], root[k], inv[k]));
-#pragma unroll
-    for (int q = k + 1; q < B; ++q) gcol[q] -= bcast_lane(rcol[k], q) * rcol[k];
-  }
-  double rcc = 0.0;  // own diagonal entry
-#pragma unroll
-  for (int q = 0; q < B; ++q) rcc = (q == t) ? rcol[q] : rcc;
-  // ricol[r] holds the sum over the finished entries x > r of R[r][x] Rinv[x][t] until it is its turn
-#pragma unroll
-  for (int r = B - 1; r >= 0; --r) {
-    const double rrr = bcast_lane(rcol[r], r);
-    double v = 0.0;
-    if (rrr != 0.0 && rcc != 0.0) v = (t == r) ? inv[r] : (t > r ? -quotient(ricol[r], root[r], inv[r]) : 0.0);
-    ricol[r] = v;
-#pragma unroll
-    for (int x = 0; x < r; ++x) ricol[x] += bcast_lane(rcol[x], r) * v;
-  }
-  if (rinv_out && act) {
-#pragma unroll
-    for (int q = 0; q < B; ++q) rinv_out[q * kPartialPad + t] = ricol[q];
-  }
-  if (r_out) {
-    if (rprev) {
-      double v[B];
-#pragma unroll
-      for (int q = 0; q < B; ++q) v[q] = 0.0;
-#pragma unroll
-      for (int x = 0; x < B; ++x) {
-        const double p = rprev[x * kPartialPad + tc];
-#pragma unroll
-        for (int q = 0; q <= x; ++q) v[q] += bcast_lane(rcol[q], x) * p;
-      }
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (act) r_out[q * kPartialPad + t] = v[q];
-    } else {
-#pragma unroll
-      for (int q = 0; q < B; ++q)
-        if (act) r_out[q * kPartialPad + t] = rcol[q];
-    }
-  }
-}
-
 template <int B>
 __global__ __launch_bounds__(64) void chol_wave_kernel(const double* __restrict__ g_in, double* __restrict__ g_out,
                                                        double* __restrict__ rinv_out, double* __restrict__ r_out,
@@ -1829,39 +1877,6 @@ __global__ __launch_bounds__(64) void chol_reg_kernel(const double* __restrict__
       if (act) r_out[q * kPartialPad + t] = v;
     }
   }
-}
-
-
-// From npart partial Gram blocks to the factor in one launch instead of two, where there are few of them: the workgroup
-// adds them up in a fixed order first.
-constexpr int kPartsThreads = 256;
-template <int B>
-__global__ __launch_bounds__(kPartsThreads) void chol_parts_kernel(const double* __restrict__ gpart, int npart,
-                                                                   double* __restrict__ g_out,
-                                                                   double* __restrict__ rinv_out,
-                                                                   double* __restrict__ r_out,
-                                                                   const double* __restrict__ rprev, double abs_tol2,
-                                                                   double rel_tol) {
-  constexpr int SPLIT = kPartsThreads / (B * B);
-  __shared__ double sub[SPLIT][B * B];
-  const int e = threadIdx.x % (B * B), r = threadIdx.x / (B * B);
-  const double* p = gpart + (e / B) * kPartialPad + e % B;
-  double acc = 0.0;
-#pragma unroll 8
-  for (int q = r; q < npart; q += SPLIT) acc += p[(int64_t)q * B * kPartialPad];
-  sub[r][e] = acc;
-  __syncthreads();
-  if (threadIdx.x >= 64) return;  // a wave: the others are done
-#pragma unroll
-  for (int f = 0; f < B * B; f += 64) {
-    double tot = sub[0][f + threadIdx.x];
-#pragma unroll
-    for (int q = 1; q < SPLIT; ++q) tot += sub[q][f + threadIdx.x];
-    sub[0][f + threadIdx.x] = tot;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own LDS operations complete in order
-  __builtin_amdgcn_wave_barrier();
-  chol_wave<B>(sub[0], B, g_out, rinv_out, r_out, rprev, abs_tol2, rel_tol);
 }
 
 
@@ -2243,17 +2258,6 @@ bool gram_cholesky_takes_parts(int npart, int b) {
   return (b == 8 && npart <= 128) || (b == 16 && npart <= 32);
 }
 
-hipError_t launch_gram_cholesky_parts(const double* gpart, int npart, int b, double* g_out, double* rinv, double* rout,
-                                      const double* rprev, double abs_tol2, double rel_tol, hipStream_t st) {
-  if (!gram_cholesky_takes_parts(npart, b)) return hipErrorInvalidValue;
-#define SC_CHOL(BB)                                                                                                   \
-  hipLaunchKernelGGL((chol_parts_kernel<BB>), dim3(1), dim3(kPartsThreads), 0, st, gpart, npart, g_out, rinv, rout, \
-                     rprev, abs_tol2, rel_tol)
-  if (b == 8) SC_CHOL(8); else SC_CHOL(16);
-#undef SC_CHOL
-  return hipGetLastError();
-}
-
 // skip[0] = 1 if a second Gram-Schmidt pass is unnecessary for every column of the block, else 0.  Column t lost
 // removed_t = sum_c h[c][t]^2 of its squared norm to the first pass and kept gram[t][t]; the first pass leaves an
 // orthogonality error of about eps * sqrt(1 + removed / kept), which a second pass is needed for only when
@@ -2342,8 +2346,8 @@ hipError_t launch_update_gram(double* basis, int64_t n, int64_t ld, int acol0, i
   const unsigned grid = (unsigned)plan_update_gram(n);
   const bool pipe = kdim >= 128;  // loads one trip ahead pay from a few trips on
 #define SC_LAUNCH_UG(NTV, PV)                                                                                     \
-  hipLaunchKernelGGL((update_gram_kernel<NTV, PV>), dim3(grid), dim3(kThreads), 0, st, basis, n, ld, acol0, kdim, \
-                     bmat, b, ccol0, vec_ok, overwrite, gpart, skip)
+  hipLaunchKernelGGL((update_gram_kernel<NTV, PV, 0>), dim3(grid), dim3(kThreads), 0, st, basis, n, ld, acol0, kdim, \
+                     bmat, b, ccol0, vec_ok, overwrite, gpart, skip, GramParts{})
   if (b <= 16) {
     if (pipe) SC_LAUNCH_UG(1, true); else SC_LAUNCH_UG(1, false);
   } else {
@@ -2353,11 +2357,36 @@ hipError_t launch_update_gram(double* basis, int64_t n, int64_t ld, int acol0, i
   return hipGetLastError();
 }
 
+hipError_t launch_factor_update_gram(double* basis, int64_t n, int64_t ld, int col, int b, const GramParts& f, double* gpart,
+                                     hipStream_t st) {
+  if (!gram_cholesky_takes_parts(f.nparts, b) || f.parts == gpart) return hipErrorInvalidValue;
+  const int vec_ok = (ld % 4 == 0 && col % 4 == 0 && (reinterpret_cast<uintptr_t>(basis) % 32 == 0)) ? 1 : 0;
+#define SC_FACTOR_UG(BB)                                                                                              \
+  hipLaunchKernelGGL((update_gram_kernel<1, false, BB>), dim3((unsigned)plan_update_gram(n)), dim3(kThreads), 0, st, \
+                     basis, n, ld, col, b, nullptr, b, col, vec_ok, 1, gpart, nullptr, f)
+  if (b == 8) SC_FACTOR_UG(8); else SC_FACTOR_UG(16);
+#undef SC_FACTOR_UG
+  return hipGetLastError();
+}
+
+hipError_t launch_factor_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const GramParts& f, double* z,
+                                    const double* s, hipStream_t st) {
+  if (!gram_cholesky_takes_parts(f.nparts, b)) return hipErrorInvalidValue;
+  const int trips = rinv_trips(n, b);
+  const dim3 grid((unsigned)ceil_div64(n, (int64_t)(kThreads / b) * trips));
+#define SC_FACTOR_RINV(BB)                                                                                          \
+  hipLaunchKernelGGL((apply_rinv_kernel<BB>), grid, dim3(kThreads), 0, st, basis, n, ld, col0, b, trips, nullptr, z, \
+                     s, f)
+  if (b == 8) SC_FACTOR_RINV(8); else SC_FACTOR_RINV(16);
+#undef SC_FACTOR_RINV
+  return hipGetLastError();
+}
+
 hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const double* rinv, double* z,
                              const double* s, hipStream_t st) {
   const int trips = rinv_trips(n, b);
-  hipLaunchKernelGGL(apply_rinv_kernel, dim3((unsigned)ceil_div64(n, (int64_t)(kThreads / b) * trips)), dim3(kThreads), 0,
-                     st, basis, n, ld, col0, b, trips, rinv, z, s);
+  hipLaunchKernelGGL(apply_rinv_kernel<0>, dim3((unsigned)ceil_div64(n, (int64_t)(kThreads / b) * trips)), dim3(kThreads), 0,
+                     st, basis, n, ld, col0, b, trips, rinv, z, s, GramParts{});
   return hipGetLastError();
 }
 
