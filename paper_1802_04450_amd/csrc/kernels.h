@@ -199,7 +199,7 @@ hipError_t long_row_list(const int64_t* rowptr, int64_t n, void* work, size_t wo
 hipError_t launch_iota(int32_t* label, int64_t n, hipStream_t st);
 // one round of minimum-label propagation with pointer jumping; *changed = 1 if a label moved
 hipError_t launch_cc_round(const int64_t* rowptr, const int32_t* col, const double* val, int32_t* label, int64_t n,
-                           int* changed, hipStream_t st);
+                           const int* before, int* changed, hipStream_t st);
 // permuted CSR: row p = input row old_of_new[p], column c renamed new_of_old[c]; rowptr_new precomputed
 hipError_t launch_permute_csr(const int64_t* rowptr, const int32_t* col, const double* val, const int32_t* old_of_new,
                               const int32_t* new_of_old, const int64_t* rowptr_new, int32_t* col_new, double* val_new,

@@ -1890,11 +1890,13 @@ __global__ __launch_bounds__(kThreads) void iota_kernel(int32_t* __restrict__ la
 
 // One round: label[i] <- min over i and its neighbours (entries with weight exactly 0 do not connect), followed
 // by pointer jumping label <- label[label].  Labels only decrease and always name a node of the same component,
-// so concurrent in-place updates are harmless; *changed is set if anything moved.
+// so concurrent in-place updates are harmless; *changed is set if anything moved.  before (may be null): the mark of the
+// round before; if nothing moved in it there is nothing to do, so that the host may ask for several rounds at a time.
 __global__ __launch_bounds__(kThreads) void cc_round_kernel(const int64_t* __restrict__ rowptr,
                                                             const int32_t* __restrict__ col,
                                                             const double* __restrict__ val, int32_t* label, int64_t n,
-                                                            int* __restrict__ changed) {
+                                                            const int* __restrict__ before, int* __restrict__ changed) {
+  if (before && !*before) return;  // uniform over the grid
   const int64_t row = ((int64_t)blockIdx.x * kThreads + threadIdx.x) >> 4;
   const int lane = threadIdx.x & 15;
   if (row >= n) return;  // uniform over the 16-lane group
@@ -2478,9 +2480,9 @@ hipError_t launch_iota(int32_t* label, int64_t n, hipStream_t st) {
 }
 
 hipError_t launch_cc_round(const int64_t* rowptr, const int32_t* col, const double* val, int32_t* label, int64_t n,
-                           int* changed, hipStream_t st) {
+                           const int* before, int* changed, hipStream_t st) {
   hipLaunchKernelGGL(cc_round_kernel, dim3((unsigned)ceil_div64(n * 16, kThreads)), dim3(kThreads), 0, st, rowptr,
-                     col, val, label, n, changed);
+                     col, val, label, n, before, changed);
   return hipGetLastError();
 }
 
