@@ -890,10 +890,10 @@ int reorder_csr(const int64_t* rowptr, const int32_t* col, const double* val, in
   HIP_TRY(order_by_component(rowptr, col, label.p, n, by_length, big_rows, work.p, work_bytes, old_of_new_out, new_of_old_dev,
                              rowptr_out, comp_dev.p, st));
   HIP_TRY(launch_permute_csr(rowptr, col, val, old_of_new_out, new_of_old_dev, rowptr_out, col_out, val_out, n, st));
+  if (comp_of_new) comp_of_new->assign((size_t)n, 0);  // before the first copy is under way: it may throw
   int32_t last_comp = 0;
   HIP_TRY(hipMemcpyAsync(&last_comp, comp_dev.p + (n - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st));
   if (comp_of_new) {
-    comp_of_new->assign((size_t)n, 0);
     HIP_TRY(hipMemcpyAsync(comp_of_new->data(), comp_dev.p, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   }
   HIP_TRY(hipStreamSynchronize(st));
@@ -970,6 +970,9 @@ struct Solver {
   std::vector<int32_t> comp_host;   // component index of each internal row (only after reorder())
   int ncomp = 0;
   PinnedBuf<double> slots_host;
+  // marks of the setup's checks and the number of long rows, as the device hands them back.  Here and not on setup()'s stack:
+  // a setup that fails with such a copy under way leaves it in memory that outlasts it (released only once it is done).
+  PinnedBuf<int32_t> marks;
   // pinned staging for the small coefficient blocks of a rotation (locking b Ritz vectors): the upload then needs no
   // wait on the host.  ystage_busy: an upload from it may still be in flight (cleared by the next wait on the stream).
   PinnedBuf<double> ystage;
@@ -1106,12 +1109,13 @@ struct Solver {
   void setup() {
     const double t0 = now_s();
     flag.alloc(1);
+    marks.alloc(2);
+    int32_t &hflag = marks.p[0], &hcount = marks.p[1];
     HIP_TRY(hipMemsetAsync(flag.p, 0, sizeof(int), st));
     HIP_TRY(hipMemcpyAsync(&nnz, rowptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (nnz < 0) SC_THROW(SC_ECSR);
     HIP_TRY(launch_validate_csr(rowptr, col, n, nnz, flag.p, st));
-    int hflag = 0;
     HIP_TRY(hipMemcpyAsync(&hflag, flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (hflag & 3) SC_THROW(SC_ECSR);
@@ -1151,7 +1155,6 @@ struct Solver {
       lcount.alloc(1);
       longrows.alloc((size_t)n);
       HIP_TRY(long_row_list(rowptr, n, lwork.p, lw, longrows.p, lcount.p, st));
-      int32_t hcount = 0;
       HIP_TRY(hipMemcpyAsync(&hcount, lcount.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
       if (hflag & 4) SC_THROW(SC_EZERODEG);

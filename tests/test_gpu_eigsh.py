@@ -504,3 +504,38 @@ def test_check_phase(B, k, block, no_filter, most):
     assert code == B.SC_OK
     check_against_oracle(g, k, lam, vec, lam0, vec0)
     assert most is None or stats["block_steps"] <= most, stats
+
+
+def test_setup_that_runs_out_of_memory_after_the_degrees(B):
+    """The setup of a wide solve asks for its scaled values while the marks of the degree pass are on their way to the host:
+    without room for them the call is refused, and the next one is not disturbed by it."""
+    n, half = 200_000, 150
+    step = torch.cat([torch.arange(-half, 0, device="cuda:0"), torch.arange(1, half + 1, device="cuda:0")])
+    col = (torch.arange(n, device="cuda:0")[:, None] + step[None, :]) % n
+    col = col.sort(dim=1).values.reshape(-1).to(torch.int32)
+    nnz = col.numel()
+    rowptr = torch.arange(n + 1, dtype=torch.int64, device="cuda:0") * (2 * half)
+    val = torch.ones(nnz, dtype=torch.float64, device="cuda:0")
+    B.sc_release_cache()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    # the renumbering takes 12 bytes an entry and about 60 a row, the scaled values 8 an entry
+    room = 12 * nnz + 60 * n + (200 << 20)
+    assert room < 20 * nnz
+    held = []
+    for _ in range(8):                          # what is reported as free comes down in steps
+        more = torch.cuda.mem_get_info()[0] - room
+        if more < 8 << 20:
+            break
+        held.append(torch.empty(more, dtype=torch.uint8, device="cuda:0"))
+    with pytest.raises(B.ScError) as e:
+        B.sc_laplacian_eigsh(rowptr, col, val, 16, 1e-6, block=16)
+    del held
+    B.sc_release_cache()
+    torch.cuda.empty_cache()
+    assert e.value.code == B.SC_ENOMEM
+    g = wl.disjoint_union(wl.ring(150), wl.random_weighted_connected(400, 900, 2))
+    lam0, vec0 = dense.smallest_eigenpairs(*g[:3], 9)
+    lam, vec, code, _ = solve(B, g, 8, 1e-10, block=16)
+    assert code == B.SC_OK
+    check_against_oracle(g, 8, lam, vec, lam0, vec0)
