@@ -148,9 +148,10 @@ typedef struct sc_stats {
  * locked and active basis vectors, second pass against the active Krylov vectors; a phase's random start
  * block gets both passes against everything), thick restart, locking, and re-injection of a fresh random
  * block after every lock so that multiple eigenvalues are found with their multiplicity; once k pairs
- * are locked one further deflated phase must find nothing better: it ends when a larger eigenvalue would, but for a
- * chance of 1e-20, have shown in its random block, or when its largest Ritz pair has converged (skipped under SC_FLAG_NO_VERIFY, and when
- * the k-th locked theta is already within tol of 1, the largest value the spectrum of S can reach for W >= 0);
+ * are locked one further deflated phase must find nothing better: for W >= 0, whose S has its spectrum in [-1, 1], it ends
+ * when a larger eigenvalue would, but for a chance of 1e-20, have shown in its random block, and for any W when its largest
+ * Ritz pair has converged (skipped under SC_FLAG_NO_VERIFY, and, for W >= 0, when the k-th locked theta is already within
+ * tol of 1);
  * the outputs are the locked Ritz pairs in ascending order of lambda (after a Rayleigh-Ritz step over them when
  * some pair did not meet tol, or under SC_FLAG_FINAL_RR).  Only the projected
  * eigenproblems (size <= m) run on the host.

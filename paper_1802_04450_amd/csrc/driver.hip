@@ -964,6 +964,7 @@ struct Solver {
   DevBuf<double> val_s;  // S_ij = s_i W_ij s_j multiplied out: the operator copy used when b >= 8
   DevBuf<int32_t> longrows;  // rows with more than kLongRow entries (wide products only), ascending
   int nlong = 0;
+  bool below_zero = false;   // W has weights below zero: the spectrum of S need not lie in [-1, 1]
   ResidentPlan resident;     // LDS-resident start-block filter (wide products on a block-diagonal operator)
   const int32_t* rowmap = nullptr;  // device: original row of each internal row, null if not reordered
   const int32_t* rowinv = nullptr;  // device: internal row of each original row, null if not reordered
@@ -1142,6 +1143,7 @@ struct Solver {
     if (b < 8) {  // otherwise the wait below does
       HIP_TRY(hipStreamSynchronize(st));
       if (hflag & 4) SC_THROW(SC_EZERODEG);
+      below_zero = (hflag & kBelowZero) != 0;
     }
     avg_deg = (double)nnz / (double)n;
     if (b >= 8) {
@@ -1158,6 +1160,7 @@ struct Solver {
       HIP_TRY(hipMemcpyAsync(&hcount, lcount.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));
       if (hflag & 4) SC_THROW(SC_EZERODEG);
+      below_zero = (hflag & kBelowZero) != 0;
       nlong = hcount;
       if (!(flags & SC_FLAG_NO_START_FILTER)) plan_resident(rowptr, col, val_s.p, n, nnz, b, st, &resident);
     }
@@ -1455,7 +1458,7 @@ struct Solver {
       if (verifying && (flags & SC_FLAG_NO_VERIFY)) break;
       // W >= 0 makes D^-1 W row-stochastic, so no eigenvalue of S exceeds 1: once the k-th locked theta is within
       // tol of 1 a check phase could not find anything better by more than tol
-      if (verifying && kth_locked_theta() + tol >= 1.0) break;
+      if (verifying && !below_zero && kth_locked_theta() + tol >= 1.0) break;
       if ((int64_t)nl >= n) break;
       const bool last_cycle_phase = cycles >= maxiter;  // out of budget: only build enough Ritz vectors to answer
       if (last_cycle_phase && verifying) {
@@ -1467,10 +1470,11 @@ struct Solver {
       stats.phases += 1;
 
       // ---- start block
-      if (verifying) plan_check_filter();
+      if (verifying && !below_zero) plan_check_filter();
       bool filtered = filt_d > 0;
-      // the check phase's test (check_steps_needed) holds as long as the basis is the Krylov space of a random block
-      bool check_open = verifying && !last_cycle_phase;
+      // the check phase's test (check_steps_needed) holds for a spectrum in [-1, 1] and as long as the basis is the Krylov
+      // space of a random block
+      bool check_open = verifying && !last_cycle_phase && !below_zero;
       const int check_d = filt_d;
       const double check_lo = filt_lo, check_a = filt_a;
       // exponent of the filter this phase starts from (0: none, or not a random block), for the degree feedback
@@ -1702,7 +1706,6 @@ struct Solver {
         }
 
         int check_more = 0;  // block steps that the check phase's test still needs, 0 = unknown or out of reach
-        if (theta[0] < -1.0 - 1e-9 && nreal == ja) check_open = false;  // weights below zero: the test takes [-1, t]
         if (check_open && nreal == ja) {
           const int need = check_steps_needed(theta[ja - 1], kth_locked_theta() + tol, check_d, check_lo, check_a);
           if (debug_on())

@@ -22,7 +22,9 @@ hipError_t launch_validate_csr(const int64_t* rowptr, const int32_t* col, int64_
 // launch_validate_csr has accepted (columns are used as row indices).
 hipError_t launch_validate_symmetry(const int64_t* rowptr, const int32_t* col, const double* val, int64_t n, int* flag,
                                     hipStream_t st);
-// d_i = sum of row i, s_i = d_i^-1/2; flag[0] |= 4 if some d_i is <= 0 or not finite.  d may be null.
+// d_i = sum of row i, s_i = d_i^-1/2; flag[0] |= 4 if some d_i is <= 0 or not finite, |= kBelowZero if some weight is below
+// zero.  d may be null.
+constexpr int kBelowZero = 32;
 hipError_t launch_degree_scaling(const int64_t* rowptr, const double* val, int64_t n, double* d, double* s, int* flag,
                                  hipStream_t st);
 

@@ -88,8 +88,12 @@ __global__ __launch_bounds__(kThreads) void degree_kernel(const int64_t* __restr
   const int lane = threadIdx.x & 15;
   if (row >= n) return;  // uniform over the 16-lane group
   const int64_t e1 = rowptr[row + 1];
-  double acc = 0.0;
-  for (int64_t e = rowptr[row] + lane; e < e1; e += 16) acc += val[e];
+  double acc = 0.0, least = 0.0;
+  for (int64_t e = rowptr[row] + lane; e < e1; e += 16) {
+    acc += val[e];
+    least = fmin(least, val[e]);
+  }
+  if (least < 0.0 && !(*flag & kBelowZero)) atomicOr(flag, kBelowZero);  // once or a few times, not once a weight
 #pragma unroll
   for (int o = 8; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 16);
   if (lane == 0) {

@@ -539,3 +539,30 @@ def test_setup_that_runs_out_of_memory_after_the_degrees(B):
     lam, vec, code, _ = solve(B, g, 8, 1e-10, block=16)
     assert code == B.SC_OK
     check_against_oracle(g, 8, lam, vec, lam0, vec0)
+
+
+@pytest.mark.parametrize("block", [2, 8, 16])
+def test_check_phase_with_weights_below_zero(B, block):
+    """A few weights below zero move the spectrum of the normalized matrix out of [-1, 1], which the check phase's bound takes
+    for granted: it then goes on until the largest pair of the rest has converged."""
+    (rp, c, v, n0), _ = wl.stochastic_block_model(1200, 10, 0.33, 0.002, 3)
+    n, k = n0 + 2, 11
+    w = np.zeros((n, n))
+    for i in range(n0):
+        w[i, c[rp[i]:rp[i + 1]]] = v[rp[i]:rp[i + 1]]
+    w[n0, n0 + 1] = w[n0 + 1, n0] = 50.0         # +-1.001 with the two weights below zero
+    w[n0, 0] = w[0, n0] = w[n0 + 1, 700] = w[700, n0 + 1] = -0.05
+    rows, cols = np.nonzero(w)
+    rp = np.searchsorted(rows, np.arange(n + 1)).astype(np.int64)
+    g = (rp, cols.astype(np.int32), w[rows, cols], n)
+    s = 1.0 / np.sqrt(w.sum(1))
+    lam0 = 1.0 - np.linalg.eigvalsh(s[:, None] * w * s[None, :])[::-1]
+    assert lam0[0] < -1e-4 and lam0[-1] > 2.0 + 1e-4 and lam0[k] - lam0[k - 1] > 0.2
+    lam, vec, code, stats = solve(B, g, k, 1e-10, block=block, m=96)
+    assert code == B.SC_OK
+    assert np.max(np.abs(lam - lam0[:k])) <= 1e-9
+    assert np.max(compare.residual_norms(*g[:3], lam, vec)) <= 1e-8
+    _, _, _, locking = solve(B, g, k, 1e-10, block=block, m=96, flags=B.SC_FLAG_NO_VERIFY)
+    # the rest's spectrum is dense at its upper end: nothing there converges in a few steps
+    steps = stats["block_steps"] - locking["block_steps"]
+    assert steps >= 15, steps
