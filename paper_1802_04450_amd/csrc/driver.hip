@@ -556,10 +556,13 @@ constexpr double kSlicedCopyS = 1.5e-6;
 // Finds the diagonal blocks and their chunk counts on the device, sizes the items on the host.  A block goes, in this
 // order of preference, as items of 32 or 16 columns with its entries in registers (at most two chunks per lane
 // group), or in the sliced form (entries streamed from a sliced copy made here from `val`) with as many of 16, 8 or 4 columns
-// as LDS holds - or as the model prefers: narrower items read the entries more often and fill the chip better.  The
+// as LDS holds - or as the model prefers: narrower items read the entries more often and fill the chip better.  Rows over
+// sliced_piece() entries are cut into pieces where the pieces' sums fit LDS beside the iterate, else they stay whole (100
+// complete graphs of 1,000 nodes, 16 columns: 762 us a step by the general product, 293 us; 200 blocks of 1,200 rows with
+// 300 entries each 573 and 232 us).  The
 // plan is usable when b is 16 or 32, every block fits LDS one way or the other, the sliced copy's padding stays below
 // a half, and the modelled step time beats the general product's: an item with its entries in registers costs the LDS bytes
-// its step reads (entries times 8 bytes per column) at about half a compute unit's LDS rate, a sliced one
+// its step reads (the block's entries times 8 bytes per column) at about half a compute unit's LDS rate, a sliced one
 // sliced_entry_s per entry and kSlicedStepS, the items spread over the 256 compute units, largest first; the general product gathers
 // 8 b bytes per entry from the L2 caches at the 14.5 TB/s measured for it (3.2 M entries, 16 columns: 28 us; 0.73 M: 11.5 us),
 // and a launch takes 3 us more.
@@ -582,26 +585,25 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   HIP_TRY(hipMemcpyAsync(&nblk, count.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (nblk <= 0 || (int64_t)nblk > (int64_t)1 << 22) return;  // the item table stays small
-  extra.alloc((size_t)3 * nblk);
+  extra.alloc((size_t)kBlockCounts * nblk);
   HIP_TRY(launch_block_extra_chunks(rowptr, starts.p, nblk, n, extra.p, st));
-  std::vector<int32_t> hs((size_t)nblk + 1), hx((size_t)3 * nblk);
+  std::vector<int32_t> hs((size_t)nblk + 1), hx((size_t)kBlockCounts * nblk);
   HIP_TRY(hipMemcpyAsync(hs.data(), starts.p, (size_t)nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(hx.data(), extra.p, (size_t)3 * nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipMemcpyAsync(hx.data(), extra.p, (size_t)kBlockCounts * nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   hs[nblk] = (int32_t)n;
   struct Item {
     int32_t row0, nrows, col0, shape, extra;
     double cost;  // seconds per step
   };
-  const double avg_deg = (double)nnz / (double)n;
   // What the blocks make of items, the sliced ones of at most `widest` columns; the large ones (kLargeBlock) may be left to
   // the product-per-step kernel.  False: the large blocks are not the matrix's last rows.
   struct Split {
     std::vector<Item> items;
     std::vector<int32_t> blocks;  // the blocks that go in the sliced form
-    int64_t sliced_rows = 0, rest_row0 = 0, extra = 0, nslots = 0;
+    int64_t rest_row0 = 0, extra = 0, nslots = 0;
     size_t lds = 0, sliced_blocks = 0;
-    double step_s = 0.0;
+    double step_s = 0.0, sliced_entries = 0.0;
   };
   auto split = [&](int widest, bool leave_large, Split* out) -> bool {
     out->rest_row0 = n;
@@ -611,10 +613,12 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
       const bool large = nr > kLargeBlock;
       if (large_seen && !large) return false;
       large_seen = large;
+      const int32_t* counts = &hx[(size_t)kBlockCounts * t];
+      const double entries = counts[3];
       int cl = 0, nx = 0, bs = 0, x = 0;
       size_t lds = 0;
       for (int c = b == 32 ? 4 : 2; c >= 2 && cl == 0; c /= 2) {  // widest lane group first
-        const int chunks = c == 4 ? hx[3 * t] : hx[3 * t + 1];
+        const int chunks = c == 4 ? counts[0] : counts[1];
         if (chunks >= (1 << 26) || nr + chunks > resident_max_chunks(c)) continue;
         lds = resident_item_lds_bytes(nr, c, chunks);
         if (lds > (size_t)lds_limit) continue;
@@ -622,9 +626,16 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
         nx = chunks;
         bs = 8 * c;
       }
-      double cost = (double)nr * avg_deg * 8.0 * bs / 150e9;
-      for (int c = std::min(widest, b); c >= 4 && cl == 0 && !no_sliced && !(large && leave_large); c /= 2) {
-        x = hx[3 * t + 2];
+      double cost = entries * 8.0 * bs / 150e9;
+      // Rows in pieces; without room for that in any width, in whole (not the large blocks: the product takes those).
+      const int last_piece = large ? sliced_piece() : INT32_MAX;
+      for (int piece = sliced_piece(), c = std::min(widest, b); cl == 0 && !no_sliced && !(large && leave_large); c /= 2) {
+        if (c < 4) {
+          if (piece == last_piece) break;
+          piece = last_piece;
+          c = std::min(widest, b);
+        }
+        x = piece == INT32_MAX ? 0 : counts[2];
         lds = resident_sliced_lds_bytes(nr, x, c);
         if (lds > (size_t)lds_limit) continue;
         const int64_t first = out->nslots;
@@ -635,11 +646,11 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
         nx = (int)first;
         bs = c;
         out->nslots += count;
-        out->blocks.insert(out->blocks.end(), {hs[t], nr, (int32_t)out->extra, x, c, (int32_t)first});
+        out->blocks.insert(out->blocks.end(), {hs[t], nr, (int32_t)out->extra, x, c, (int32_t)first, piece});
         out->extra += x;
-        out->sliced_rows += nr;
+        out->sliced_entries += entries;
         out->sliced_blocks += 1;
-        cost = (double)nr * avg_deg * sliced_entry_s(c);
+        cost = entries * sliced_entry_s(c);
       }
       if (cl == 0) {
         // without an item: acceptable only as part of a run of such blocks at the end of the matrix (the solver's
@@ -715,8 +726,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
     int64_t total = 0;
     HIP_TRY(hipMemcpyAsync(&total, plan->slice_base.p + nslots, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));  // also: the host vector above has been read
-    // padding: against the sliced blocks' share of the matrix entries, estimated by their share of the rows
-    const double basis_entries = (double)nnz * (double)best.sliced_rows / (double)n;
+    const double basis_entries = best.sliced_entries;  // the padding comes on top
     if (debug_on())
       std::fprintf(stderr, "[sceig] sliced copy: %d slots, %lld entries for %.0f of the matrix\n", nslots,
                    (long long)total, basis_entries);
@@ -2456,9 +2466,17 @@ int sc_workspace_bytes(int64_t n, int64_t nnz, int32_t k, const sc_options* opt,
   }
   total += up(N * 8);                       // scaling vector
   if (b >= 8) total += up(Z * 8) + up(N * 4) + up(long_row_list_workspace(n)) + 256;  // scaled values, long-row list
-  if (b >= 8 && !(o.flags & SC_FLAG_NO_START_FILTER))  // diagonal-block search and the work items of the resident filter
-    total += up(diagonal_blocks_workspace(n)) + up(N * 4) + 256 + up(N * 8) + up(N * 18) + up(N * 4) +
-             up(Z * 15 + N * 2) + up(Z * 3 + N / 4) + 5 * up(N / 8 + 64) + up(sliced_scan_workspace((int)std::min<int64_t>(n, INT32_MAX)));  // + sliced copy (at most 1.5 x the entries, 10 bytes each) and its tables (56 bytes a slot for a slice; at most one per 16 rows and 16 more per block, of 124 rows and more)
+  if (b >= 8 && !(o.flags & SC_FLAG_NO_START_FILTER)) {  // plan_resident
+    // diagonal-block search, counts of every block, and the work items: one of 20 bytes a block, more only for blocks that
+    // have, rows and sixteenths of their entries together, 100 and more
+    total += up(diagonal_blocks_workspace(n)) + up(N * 4) + 256 + up(N * sizeof(int32_t) * kBlockCounts) + up(N * 22 + Z / 8);
+    // The sliced copy, at most 1.5 x the entries at 10 bytes, and its tables, 56 bytes a slot.  A block has as many slots as
+    // slices of rows (at most one per 16) and of extra rows (one per 1,024 entries), rounded up to the 16 waves, and 16 more
+    // of either kind (sliced_places): 66 on top, for blocks that have, rows and sixteenths of their entries together, 616 and
+    // more (smaller ones keep their entries in registers).
+    total += up(Z * 15) + up(N * 10 + Z / 2) + up(Z / 16) + up(N * 4) + 8 * 256 +
+             up(sliced_scan_workspace((int)std::min<int64_t>(n, INT32_MAX)));
+  }
   total += up(N * ld * 8) + up(N * (size_t)b * 8) + up(N * rot_cols * 8);  // basis, packed block, rotation workspace
   total += up((size_t)kMaxPartials * jmax * kPP * 8) + up((size_t)kGramPartials * kPP * kPP * 8) + 2 * up(jmax * kPP * 8);
   total += up((size_t)(m / b + 4) * kSlotDoubles * 8) + up(jmax * std::max<size_t>(rot_cols, (size_t)k) * 8);

@@ -131,8 +131,10 @@ int resident_max_chunks(int cl);
 size_t diagonal_blocks_workspace(int64_t n);
 hipError_t diagonal_blocks(const int64_t* rowptr, const int32_t* col, int64_t n, void* work, size_t work_bytes,
                            int32_t* starts, int32_t* count, hipStream_t st);
-// extra[3 t], extra[3 t + 1], extra[3 t + 2] (device int32) = extra chunks of block t for chunks of 32 and of 16 entries, and
-// the extra rows of the sliced form
+// extra[4 t], extra[4 t + 1], extra[4 t + 2] (device int32) = extra chunks of block t for chunks of 32 and of 16 entries, and
+// the extra rows of the sliced form in pieces of sliced_piece() entries; extra[4 t + 3] = the block's entries (at most
+// INT32_MAX)
+constexpr int kBlockCounts = 4;
 hipError_t launch_block_extra_chunks(const int64_t* rowptr, const int32_t* starts, int nblk, int64_t n, int32_t* extra,
                                      hipStream_t st);
 // y (n x b, leading dimension ldy >= b) = the recurrence applied to x (packed n x b): u_0 = x, u_1 = alpha_first (A u_0 - shift u_0),
@@ -156,14 +158,16 @@ hipError_t launch_cheb_resident(const int64_t* rowptr, const int32_t* col, const
 // key of random block number `stream_id` under `seed`: entry i * b + t of the block launch_random_block writes is
 // 2 u - 1 with u the top 53 bits of mix(key + i * b + t)
 uint64_t random_block_key(uint64_t seed, uint64_t stream_id);
-// Sliced copy of diagonal blocks for the sliced form.  A block with `extra` extra rows (the third count of
-// launch_block_extra_chunks) has sliced_block_slots slots for slices; blocks: device, for every sliced block (first row, rows,
-// place of its first extra row in a list for all blocks, extra rows, columns of its items, first slot).  sliced_extra_rows
+// Sliced copy of diagonal blocks for the sliced form.  A block whose rows are cut into pieces has `extra` extra rows (the third
+// count of launch_block_extra_chunks for pieces of sliced_piece() entries, 0 for pieces of INT32_MAX) and sliced_block_slots
+// slots for slices; blocks: device, for every sliced block (first row, rows, place of its first extra row in a list for all
+// blocks, extra rows, columns of its items, first slot, entries of a piece).  sliced_extra_rows
 // makes that list and row_extra (int32[n]).  sliced_copy_layout fills, per slot, desc (sliced_desc_bytes of scratch),
 // slice_len, slice_first, slice_entries (int64[nslots + 1]: entries the slice takes in the copy, padding included) and
 // slice_base (int64[nslots + 1]: exclusive prefix sums; the last one is the size of the copy).  sliced_copy_fill writes the
 // copy: scol (8-byte aligned) and sval (16-byte aligned) with room for slice_base[nslots] entries.
-constexpr int kSliceBlockInts = 6;
+constexpr int kSliceBlockInts = 7;
+int sliced_piece();
 int sliced_shape(int cols);
 size_t resident_sliced_lds_bytes(int nrows, int extra, int cols);
 int sliced_block_slots(int nrows, int extra, int cols);

@@ -387,7 +387,8 @@ __device__ __forceinline__ void resident_item(const int64_t* __restrict__ rowptr
 //     load and its values with two 16-byte loads, kSliceAhead groups before they are multiplied.  Columns are stored in units of 32 bytes of the iterate (16 bits).
 //   * A row's entries beyond kSliceLong are extra rows of their own (hubs of several hundred entries beside rows of thirty
 //     would be what a step waits for): extra rows have slices like others, a lane parks its sum in LDS, and the row's owner
-//     adds the sums in order once the step's reads are over.
+//     adds the sums in order once the step's reads are over.  Where LDS has no room for these sums (a block of 1,000 rows with
+//     more than 300 entries each) all rows keep their entries: there they are long throughout.
 //   * The slices are dealt to the sixteen waves one by one, extra rows first, each to the wave with the least to do (a step
 //     lasts as long as its slowest wave); a wave's slices lie one behind the other in the copy, so that it reads its entries as
 //     one stream over slice and step boundaries.
@@ -641,9 +642,9 @@ __global__ __launch_bounds__(kRT) void cheb_resident_kernel(const int64_t* __res
 // ---- sliced copy of diagonal blocks ------------------------------------------------------------------------------------
 // What a slice of the copy holds: `rows` consecutive rows of the matrix from `first` on (none: a place without a slice), or as
 // many extra rows of the list, of a block of blk_rows rows from blk0 on whose extra rows begin at extra0 of the list (extra
-// = 1), for items of `cols` columns.
+// = 1), for items of `cols` columns.  A row's first `piece` entries are its own, `piece` more of them go to each extra row.
 struct SliceDesc {
-  int32_t first, rows, blk0, blk_rows, cols, extra, extra0;
+  int32_t first, rows, blk0, blk_rows, cols, extra, extra0, piece;
 };
 
 // Entries [*from, *from + return value) of row `*row` of the matrix: what place j of the slice holds.
@@ -658,13 +659,13 @@ __device__ __forceinline__ int slice_row(const SliceDesc& sd, int j, const int64
   // the extra row's number within its row
   const int chunk = sd.extra ? sd.first + j - sd.extra0 - (row_extra[r] >> 16) + 1 : 0;
   const int64_t e0 = rowptr[r];
-  const int len = (int)(rowptr[r + 1] - e0) - chunk * kSliceLong;
-  *from = e0 + (int64_t)chunk * kSliceLong;
-  return len < kSliceLong ? len : kSliceLong;
+  const int len = (int)(rowptr[r + 1] - e0) - chunk * sd.piece;
+  *from = e0 + (int64_t)chunk * sd.piece;
+  return len < sd.piece ? len : sd.piece;
 }
 
 // The extra rows of the sliced blocks, blocks[kSliceBlockInts t ..] = (first row, rows, place of its first extra row in the
-// list, extra rows, columns, first slot): list[.] = the row each belongs to, row_extra[r] = place of row r's first one within the block << 16 | their number.  A wave per
+// list, extra rows, columns, first slot, piece): list[.] = the row each belongs to, row_extra[r] = place of row r's first one within the block << 16 | their number.  A wave per
 // block.
 __global__ __launch_bounds__(256) void slice_extra_kernel(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ blocks,
                                                           int nblocks, int32_t* __restrict__ list,
@@ -674,12 +675,12 @@ __global__ __launch_bounds__(256) void slice_extra_kernel(const int64_t* __restr
   if (t >= nblocks) return;
   const int32_t* blk = blocks + (int64_t)kSliceBlockInts * t;
   const int64_t row0 = blk[0];
-  const int rows = blk[1], base = blk[2];
+  const int rows = blk[1], base = blk[2], piece = blk[6];
   int at = 0;
   for (int r0 = 0; r0 < rows; r0 += 64) {
     const int r = r0 + lane;
     const int len = r < rows ? (int)(rowptr[row0 + r + 1] - rowptr[row0 + r]) : 0;
-    const int x = len > kSliceLong ? (len + kSliceLong - 1) / kSliceLong - 1 : 0;
+    const int x = len > piece ? (len - 1) / piece : 0;
     int incl = x;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -706,7 +707,7 @@ __global__ __launch_bounds__(256) void slice_layout_kernel(const int64_t* __rest
   constexpr int MAXN = (kSliceOwn + kSliceExtra) * kSliceWaves;
   __shared__ int length[MAXN], slot_of[MAXN];
   const int32_t* blk = blocks + (int64_t)kSliceBlockInts * blockIdx.x;
-  const int row0 = blk[0], nr = blk[1], extra0 = blk[2], nx = blk[3], cols = blk[4], slot0 = blk[5];
+  const int row0 = blk[0], nr = blk[1], extra0 = blk[2], nx = blk[3], cols = blk[4], slot0 = blk[5], piece = blk[6];
   const int rs = 256 / cols, xs = sliced_slices(nx, cols), rsl = sliced_slices(nr, cols);
   const int xslots = sliced_extra_slots(nx, cols), rslots = sliced_slots(nr, cols), slots = xslots + rslots;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -714,7 +715,7 @@ __global__ __launch_bounds__(256) void slice_layout_kernel(const int64_t* __rest
   auto describe = [&](int q) __attribute__((always_inline)) -> SliceDesc {  // slice q: the extra rows' first
     const bool x = q < xs;
     const int at = rs * (x ? q : q - xs), left = (x ? nx : nr) - at;
-    return SliceDesc{(x ? extra0 : row0) + at, left < rs ? left : rs, row0, nr, cols, x ? 1 : 0, extra0};
+    return SliceDesc{(x ? extra0 : row0) + at, left < rs ? left : rs, row0, nr, cols, x ? 1 : 0, extra0, piece};
   };
   for (int q = wave; q < xs + rsl; q += 4) {
     const SliceDesc sd = describe(q);
@@ -728,7 +729,7 @@ __global__ __launch_bounds__(256) void slice_layout_kernel(const int64_t* __rest
     if (lane == 0) length[q] = len < 1 ? 1 : len;
   }
   for (int q = threadIdx.x; q < slots * kSliceWaves; q += 256) {  // no slice, unless one is dealt
-    desc[slot0 + q] = SliceDesc{0, 0, row0, nr, cols, 0, extra0};
+    desc[slot0 + q] = SliceDesc{0, 0, row0, nr, cols, 0, extra0, piece};
     slice_len[slot0 + q] = 0;
     slice_first[slot0 + q] = 0;
     slice_entries[slot0 + q] = 0;
@@ -866,8 +867,8 @@ __global__ __launch_bounds__(256) void slice_fill_kernel(const int64_t* __restri
   }
 }
 
-// extra[3 t], extra[3 t + 1], extra[3 t + 2] = chunks beyond the first, summed over the rows of diagonal block t, for chunks of
-// 32, 16 and kSliceLong entries.  One wave per block.
+// extra[4 t], extra[4 t + 1], extra[4 t + 2] = chunks beyond the first, summed over the rows of diagonal block t, for chunks of
+// 32, 16 and kSliceLong entries, extra[4 t + 3] = its entries (INT32_MAX if more).  One wave per block.
 __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* __restrict__ rowptr,
                                                                  const int32_t* __restrict__ starts, int nblk, int64_t n,
                                                                  int32_t* __restrict__ extra) {
@@ -889,9 +890,11 @@ __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* 
     xl += __shfl_xor(xl, o, 64);
   }
   if (lane == 0) {
-    extra[3 * t] = x32;
-    extra[3 * t + 1] = x16;
-    extra[3 * t + 2] = xl;
+    const int64_t entries = rowptr[r1] - rowptr[r0];
+    extra[kBlockCounts * t] = x32;
+    extra[kBlockCounts * t + 1] = x16;
+    extra[kBlockCounts * t + 2] = xl;
+    extra[kBlockCounts * t + 3] = entries < INT32_MAX ? (int32_t)entries : INT32_MAX;
   }
 }
 
@@ -929,6 +932,8 @@ size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 size_t resident_item_lds_bytes(int nrows, int cl, int extra) { return resident_lds_bytes(nrows, cl, extra); }
 
 int resident_max_chunks(int cl) { return kRS * (kRT / cl); }
+
+int sliced_piece() { return kSliceLong; }
 
 int sliced_shape(int cols) { return cols == 16 ? kShape16 : cols == 8 ? kShape8 : kShape4; }
 

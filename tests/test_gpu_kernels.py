@@ -565,3 +565,26 @@ def test_chebyshev_filter_sliced_widths(B, widest, ncols, degree, monkeypatch):
     # a row's sum of up to 2,400 products, and `degree` steps of at most twice the growth of the recurrence
     assert np.max(np.abs(got.cpu().numpy() - want)) <= 1e-11 * max(1.0, np.max(np.abs(want)))
     assert torch.equal(got, B.sc_chebyshev_filter(drp, dc, dv, dx, 0.3, degree))
+
+
+# blocks whose rows are too long for their extra rows' sums to fit LDS beside the iterate: complete graphs and dense random ones
+# of up to 1,272 rows, between blocks of the other kinds, and a larger one that stays with the product
+@pytest.mark.parametrize("widest", [16, 8, 4])
+@pytest.mark.parametrize("ncols,degree", [(16, 1), (32, 6)])
+def test_chebyshev_filter_of_blocks_with_long_rows(B, widest, ncols, degree, monkeypatch):
+    from oracle import blockops
+    monkeypatch.setenv("SCEIG_FORCE_RESIDENT", "1")
+    monkeypatch.setenv("SCEIG_SLICED_COLUMNS", str(widest))
+    rp, c, v, n = wl.disjoint_union(wl.complete(620), wl.path(7), wl.random_weighted_connected(257, 9000, 1), wl.complete(700),
+                                    wl.random_weighted_connected(1000, 200_000, 2), wl.ring(900),
+                                    wl.random_weighted_connected(1272, 190_000, 3), wl.complete(1301))
+    x = np.random.default_rng(ncols).standard_normal((n, ncols))
+    want = blockops.chebyshev_filter(rp, c, v, x, 0.3, degree)
+    drp, dc, dv = B.csr_to_device(rp, c, v)
+    dx = torch.from_numpy(x).cuda()
+    before = B.sc_counter(B.SC_COUNTER_RESIDENT_FILTERS)
+    got = B.sc_chebyshev_filter(drp, dc, dv, dx, 0.3, degree)
+    assert B.sc_counter(B.SC_COUNTER_RESIDENT_FILTERS) == before + 1
+    # a row's sum of up to 1,300 products, and `degree` steps of at most twice the growth of the recurrence
+    assert np.max(np.abs(got.cpu().numpy() - want)) <= 1e-11 * max(1.0, np.max(np.abs(want)))
+    assert torch.equal(got, B.sc_chebyshev_filter(drp, dc, dv, dx, 0.3, degree))
