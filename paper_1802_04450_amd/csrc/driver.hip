@@ -553,6 +553,191 @@ constexpr double kSlicedStepS = 1.5e-6;
 // Making the sliced copy takes about 150 us, which a hundred filter steps have to bring in.
 constexpr double kSlicedCopyS = 1.5e-6;
 
+double general_step_seconds(int64_t nnz, int b) { return 3e-6 + (double)nnz * 8.0 * b / 14.5e12; }
+
+struct WorkItem {
+  int32_t row0, nrows, col0, shape, extra;
+  double cost;  // seconds per step
+};
+
+// One way to make items of the blocks: the sliced ones of at most `widest` columns, the large ones (kLargeBlock) left to the
+// product-per-step kernel or not.
+struct ItemSplit {
+  std::vector<WorkItem> sliced;
+  std::vector<int32_t> blocks;  // the blocks that go in the sliced form, kSliceBlockInts each
+  int64_t rest_row0 = 0, extra = 0, nslots = 0;
+  size_t lds = 0;
+  double step_s = 0.0, sliced_entries = 0.0;
+};
+
+// Host side of plan_resident: starts[nblk + 1], counts[kBlockCounts nblk].  What holds for every split, the blocks whose
+// entries fit the registers, is looked at once; a split goes through the others (`open`).  (With all blocks in each of the six
+// splits, 2,000,000 rings of 3 nodes cost 0.5 s of host time before the solve.)
+class ItemPlanner {
+ public:
+  ItemPlanner(const int32_t* starts, const int32_t* counts, int nblk, int b, size_t lds_limit, bool no_sliced)
+      : starts_(starts), counts_(counts), nblk_(nblk), b_(b), lds_limit_(lds_limit), no_sliced_(no_sliced) {
+    form_.resize((size_t)nblk);
+    bool large_seen = false;
+    for (int t = 0; t < nblk; ++t) {
+      const int nr = rows(t), shape = register_form(nr, counts + (size_t)kBlockCounts * t, &fixed_lds_);
+      if (nr > kLargeBlock) large_seen = true;
+      else if (large_seen) large_last_ = false;
+      form_[t] = (uint8_t)shape;
+      if (shape == 0) {
+        open_.push_back(t);
+      } else {
+        last_fixed_ = t;
+        fixed_items_ += b / (8 * shape);
+        fixed_s_ += register_cost(t) * (b / (8 * shape));
+      }
+    }
+  }
+
+  // The split with the shortest modelled step; false: there is none.  forced: the only width to look at, for tests (may be
+  // null).
+  bool best_split(int64_t n, double general_step_s, const char* forced, ItemSplit* best) const {
+    if (!large_last_) return false;  // what may be left out has to be the matrix's last rows
+    bool have = false;
+    for (int widest = 16; widest >= 4; widest /= 2)
+      for (int leave = 0; leave < 2; ++leave) {
+        if (open_.empty() && (widest < 16 || leave)) continue;  // all the same
+        if (!open_.empty() && forced && (std::atoi(forced) != widest || leave)) continue;
+        ItemSplit s;
+        if (!split(n, widest, leave != 0, &s) || (fixed_items_ == 0 && s.sliced.empty())) continue;
+        // the rows without items still take the general product, step by step, after the one launch of the items
+        const double rest_share = (double)(n - s.rest_row0) / (double)n;
+        s.step_s += (!s.blocks.empty() ? kSlicedStepS + kSlicedCopyS : 1e-6) +
+                    (rest_share > 0.0 ? std::max(4e-6, rest_share * general_step_s) : 0.0);
+        if (debug_on())
+          std::fprintf(stderr, "[sceig] resident filter plan: %d blocks (%zu sliced, at most %d columns), %lld items, LDS %zu, "
+                       "rest %.3f, modelled step %.1f us against %.1f us\n", nblk_, s.blocks.size() / kSliceBlockInts, widest,
+                       (long long)(fixed_items_ + (int64_t)s.sliced.size()), s.lds, rest_share, s.step_s * 1e6,
+                       general_step_s * 1e6);
+        if (!have || s.step_s < best->step_s) *best = std::move(s);
+        have = true;
+      }
+    return have;
+  }
+
+  // all items of a split, the longest first, those of a block next to one another
+  std::vector<WorkItem> items(const ItemSplit& s) const {
+    std::vector<WorkItem> all;
+    all.reserve((size_t)fixed_items_ + s.sliced.size());
+    for (int t = 0; t < nblk_; ++t) {
+      const int cl = form_[t];
+      if (cl == 0) continue;
+      const int chunks = counts_[(size_t)kBlockCounts * t + (cl == 4 ? 0 : 1)];
+      for (int c0 = 0; c0 < b_; c0 += 8 * cl) all.push_back(WorkItem{starts_[t], rows(t), c0, cl | (chunks << 4), 0, register_cost(t)});
+    }
+    all.insert(all.end(), s.sliced.begin(), s.sliced.end());
+    auto longer = [](const WorkItem& x, const WorkItem& y) { return x.cost > y.cost; };
+    if (!std::is_sorted(all.begin(), all.end(), longer)) std::stable_sort(all.begin(), all.end(), longer);
+    return all;
+  }
+
+ private:
+  int rows(int t) const { return starts_[t + 1] - starts_[t]; }
+  double register_cost(int t) const { return (double)counts_[(size_t)kBlockCounts * t + 3] * 64.0 * form_[t] / 150e9; }
+
+  // widest lane group whose items take the block: 4, 2 or 0 (none)
+  int register_form(int nr, const int32_t* counts, size_t* lds_most) const {
+    for (int c = b_ == 32 ? 4 : 2; c >= 2; c /= 2) {
+      const int chunks = c == 4 ? counts[0] : counts[1];
+      if (chunks >= (1 << 26) || nr + chunks > resident_max_chunks(c)) continue;
+      const size_t lds = resident_item_lds_bytes(nr, c, chunks);
+      if (lds > lds_limit_) continue;
+      *lds_most = std::max(*lds_most, lds);
+      return c;
+    }
+    return 0;
+  }
+
+  // False: blocks without an item that are not the matrix's last rows.
+  bool split(int64_t n, int widest, bool leave_large, ItemSplit* out) const {
+    out->rest_row0 = n;
+    out->lds = fixed_lds_;
+    double sum = fixed_s_;
+    int first_rest = nblk_;
+    for (const int t : open_) {
+      const int nr = rows(t);
+      const bool large = nr > kLargeBlock;
+      const int32_t* counts = counts_ + (size_t)kBlockCounts * t;
+      const double entries = counts[3];
+      // Rows in pieces; without room for that in any width, in whole (not the large blocks: the product takes those).
+      const int last_piece = large ? sliced_piece() : INT32_MAX;
+      bool taken = false;
+      for (int piece = sliced_piece(), c = std::min(widest, b_); !taken && !no_sliced_ && !(large && leave_large); c /= 2) {
+        if (c < 4) {
+          if (piece == last_piece) break;
+          piece = last_piece;
+          c = std::min(widest, b_);
+        }
+        const int x = piece == INT32_MAX ? 0 : counts[2];
+        const size_t lds = resident_sliced_lds_bytes(nr, x, c);
+        if (lds > lds_limit_) continue;
+        const int64_t first = out->nslots;
+        const int count = sliced_block_slots(nr, x, c);
+        // the item's word has 27 bits for the first slot
+        if (first + count >= ((int64_t)1 << 27) || out->extra + x > INT32_MAX) return false;
+        if (first_rest < nblk_) return false;
+        taken = true;
+        out->nslots += count;
+        out->blocks.insert(out->blocks.end(), {starts_[t], nr, (int32_t)out->extra, x, c, (int32_t)first, piece});
+        out->extra += x;
+        out->sliced_entries += entries;
+        out->lds = std::max(out->lds, lds);
+        const double cost = entries * sliced_entry_s(c);
+        sum += cost * (b_ / c);
+        for (int c0 = 0; c0 < b_; c0 += c)
+          out->sliced.push_back(WorkItem{starts_[t], nr, c0, (int32_t)(sliced_shape(c) | (first << 4)), x, cost});
+      }
+      if (!taken && first_rest == nblk_) {
+        // without an item: acceptable only as part of a run of such blocks at the end of the matrix (the solver's
+        // renumbering puts the large components there), which the product-per-step kernel then takes
+        first_rest = t;
+        out->rest_row0 = starts_[t];
+      }
+    }
+    if (first_rest < nblk_ && last_fixed_ > first_rest) return false;
+    out->step_s = longest_unit(*out, sum);
+    return true;
+  }
+
+  // How long the busiest of the 256 compute units takes when it is given the items, the longest first.  Only the items above a
+  // 64th of a unit's share are dealt one by one (there are at most 64 a unit); the others fill up what these leave.
+  double longest_unit(const ItemSplit& s, double sum) const {
+    const double share = sum / 256.0, least = share / 64.0;
+    std::vector<double> large;
+    for (int t = 0; t < nblk_; ++t)
+      if (form_[t] != 0 && register_cost(t) > least) large.insert(large.end(), (size_t)(b_ / (8 * form_[t])), register_cost(t));
+    for (const WorkItem& it : s.sliced)
+      if (it.cost > least) large.push_back(it.cost);
+    std::sort(large.begin(), large.end(), std::greater<double>());
+    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+    for (int q = 0; q < 256; ++q) busy.push(0.0);
+    double longest = share;
+    for (const double cost : large) {
+      const double at = busy.top() + cost;
+      busy.pop();
+      busy.push(at);
+      longest = std::max(longest, at);
+    }
+    return longest;
+  }
+
+  const int32_t *starts_, *counts_;
+  int nblk_, b_;
+  size_t lds_limit_;
+  bool no_sliced_, large_last_ = true;
+  std::vector<uint8_t> form_;  // lanes of a group, 0: not in registers
+  std::vector<int32_t> open_;  // the blocks without such a form
+  int last_fixed_ = -1;
+  size_t fixed_lds_ = 0;
+  int64_t fixed_items_ = 0;
+  double fixed_s_ = 0.0;
+};
+
 // Finds the diagonal blocks and their chunk counts on the device, sizes the items on the host.  A block goes, in this
 // order of preference, as items of 32 or 16 columns with its entries in registers (at most two chunks per lane
 // group), or in the sliced form (entries streamed from a sliced copy made here from `val`) with as many of 16, 8 or 4 columns
@@ -592,110 +777,10 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   HIP_TRY(hipMemcpyAsync(hx.data(), extra.p, (size_t)kBlockCounts * nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   hs[nblk] = (int32_t)n;
-  struct Item {
-    int32_t row0, nrows, col0, shape, extra;
-    double cost;  // seconds per step
-  };
-  // What the blocks make of items, the sliced ones of at most `widest` columns; the large ones (kLargeBlock) may be left to
-  // the product-per-step kernel.  False: the large blocks are not the matrix's last rows.
-  struct Split {
-    std::vector<Item> items;
-    std::vector<int32_t> blocks;  // the blocks that go in the sliced form
-    int64_t rest_row0 = 0, extra = 0, nslots = 0;
-    size_t lds = 0, sliced_blocks = 0;
-    double step_s = 0.0, sliced_entries = 0.0;
-  };
-  auto split = [&](int widest, bool leave_large, Split* out) -> bool {
-    out->rest_row0 = n;
-    bool large_seen = false;
-    for (int t = 0; t < nblk; ++t) {
-      const int nr = hs[t + 1] - hs[t];
-      const bool large = nr > kLargeBlock;
-      if (large_seen && !large) return false;
-      large_seen = large;
-      const int32_t* counts = &hx[(size_t)kBlockCounts * t];
-      const double entries = counts[3];
-      int cl = 0, nx = 0, bs = 0, x = 0;
-      size_t lds = 0;
-      for (int c = b == 32 ? 4 : 2; c >= 2 && cl == 0; c /= 2) {  // widest lane group first
-        const int chunks = c == 4 ? counts[0] : counts[1];
-        if (chunks >= (1 << 26) || nr + chunks > resident_max_chunks(c)) continue;
-        lds = resident_item_lds_bytes(nr, c, chunks);
-        if (lds > (size_t)lds_limit) continue;
-        cl = c;
-        nx = chunks;
-        bs = 8 * c;
-      }
-      double cost = entries * 8.0 * bs / 150e9;
-      // Rows in pieces; without room for that in any width, in whole (not the large blocks: the product takes those).
-      const int last_piece = large ? sliced_piece() : INT32_MAX;
-      for (int piece = sliced_piece(), c = std::min(widest, b); cl == 0 && !no_sliced && !(large && leave_large); c /= 2) {
-        if (c < 4) {
-          if (piece == last_piece) break;
-          piece = last_piece;
-          c = std::min(widest, b);
-        }
-        x = piece == INT32_MAX ? 0 : counts[2];
-        lds = resident_sliced_lds_bytes(nr, x, c);
-        if (lds > (size_t)lds_limit) continue;
-        const int64_t first = out->nslots;
-        const int count = sliced_block_slots(nr, x, c);
-        // the item's word has 27 bits for the first slot
-        if (first + count >= ((int64_t)1 << 27) || out->extra + x > INT32_MAX) return false;
-        cl = sliced_shape(c);
-        nx = (int)first;
-        bs = c;
-        out->nslots += count;
-        out->blocks.insert(out->blocks.end(), {hs[t], nr, (int32_t)out->extra, x, c, (int32_t)first, piece});
-        out->extra += x;
-        out->sliced_entries += entries;
-        out->sliced_blocks += 1;
-        cost = entries * sliced_entry_s(c);
-      }
-      if (cl == 0) {
-        // without an item: acceptable only as part of a run of such blocks at the end of the matrix (the solver's
-        // renumbering puts the large components there), which the product-per-step kernel then takes
-        if (out->rest_row0 == n) out->rest_row0 = hs[t];
-        continue;
-      }
-      if (out->rest_row0 < n) return false;
-      for (int c0 = 0; c0 < b; c0 += bs) out->items.push_back(Item{hs[t], nr, c0, (int32_t)(cl | (nx << 4)), x, cost});
-      out->lds = std::max(out->lds, lds);
-    }
-    std::stable_sort(out->items.begin(), out->items.end(), [](const Item& x, const Item& y) { return x.cost > y.cost; });
-    // the longest first on 256 compute units
-    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
-    for (int q = 0; q < 256; ++q) busy.push(0.0);
-    for (const Item& it : out->items) {
-      const double at = busy.top() + it.cost;
-      busy.pop();
-      busy.push(at);
-      out->step_s = std::max(out->step_s, at);
-    }
-    return true;
-  };
-  const double general_step_s = 3e-6 + (double)nnz * 8.0 * b / 14.5e12;
-  Split best;
-  bool have = false;
-  const char* forced = std::getenv("SCEIG_SLICED_COLUMNS");  // for tests of every width
-  for (int widest = 16; widest >= 4; widest /= 2)
-    for (int leave = 0; leave < 2; ++leave) {
-      if (forced && (std::atoi(forced) != widest || leave)) continue;
-      Split s;
-      if (!split(widest, leave != 0, &s) || s.items.empty()) continue;
-      // the rows without items still take the general product, step by step, after the one launch of the items
-      const double rest_share = (double)(n - s.rest_row0) / (double)n;
-      s.step_s += (s.sliced_blocks > 0 ? kSlicedStepS + kSlicedCopyS : 1e-6) +
-                  (rest_share > 0.0 ? std::max(4e-6, rest_share * general_step_s) : 0.0);
-      if (debug_on())
-        std::fprintf(stderr, "[sceig] resident filter plan: %d blocks (%zu sliced, at most %d columns), %zu items, LDS %zu, "
-                     "rest %.3f, modelled step %.1f us against %.1f us\n", nblk, s.sliced_blocks, widest, s.items.size(),
-                     s.lds, rest_share, s.step_s * 1e6, general_step_s * 1e6);
-      if (!have || s.step_s < best.step_s) best = std::move(s);
-      have = true;
-    }
-  if (!have) return;
-  std::vector<Item>& items = best.items;
+  const double general_step_s = general_step_seconds(nnz, b);
+  ItemPlanner planner(hs.data(), hx.data(), nblk, b, (size_t)lds_limit, no_sliced);
+  ItemSplit best;
+  if (!planner.best_split(n, general_step_s, std::getenv("SCEIG_SLICED_COLUMNS"), &best)) return;
   const int64_t rest_row0 = best.rest_row0;
   const size_t lds_max = best.lds;
   plan->est_step_s = best.step_s;
@@ -703,6 +788,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   // (100,000 rows in 100 components: 25 us against 28 us by the general product; 30,000 in 20: 18 against 11.5)
   plan->single = best.step_s + 10e-6 < general_step_s;
   if (!(plan->est_step_s < general_step_s) && !std::getenv("SCEIG_FORCE_RESIDENT")) return;
+  std::vector<WorkItem> items = planner.items(best);
   const int nslots = (int)best.nslots;
   if (nslots > 0) {
     DevBuf<int32_t> d_blocks, d_list;
@@ -718,7 +804,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
     plan->slice_first.alloc((size_t)nslots);
     const size_t sw = sliced_scan_workspace(nslots);
     swork.alloc(sw);
-    const int nsliced = (int)best.sliced_blocks;
+    const int nsliced = (int)(best.blocks.size() / kSliceBlockInts);
     HIP_TRY(hipMemcpyAsync(d_blocks.p, best.blocks.data(), best.blocks.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_TRY(sliced_extra_rows(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, st));
     HIP_TRY(sliced_copy_layout(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, nslots, d_desc.p, plan->slice_len.p,
@@ -747,7 +833,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
     // Workgroups go to the eight XCDs in turn (workgroup i to XCD i mod 8), each XCD with an L2 of its own.  The items
     // of one block (its column slices) read the same matrix entries, so they are placed eight apart: they run on the
     // same XCD at about the same time, and what the first fetches the others find in that L2.
-    std::vector<std::vector<Item>> queue(8);
+    std::vector<std::vector<WorkItem>> queue(8);
     size_t q = 0;
     for (size_t i = 0; i < items.size();) {
       size_t j = i;
@@ -756,7 +842,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
       ++q;
       i = j;
     }
-    std::vector<Item> placed;
+    std::vector<WorkItem> placed;
     placed.reserve(items.size());
     for (size_t r = 0; placed.size() < items.size(); ++r)
       for (int x = 0; x < 8; ++x)
@@ -765,7 +851,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   }
   std::vector<int32_t> words;
   words.reserve(items.size() * kItemInts);
-  for (const Item& it : items) words.insert(words.end(), {it.row0, it.nrows, it.col0, it.shape, it.extra});
+  for (const WorkItem& it : items) words.insert(words.end(), {it.row0, it.nrows, it.col0, it.shape, it.extra});
   plan->items.alloc(words.size());
   HIP_TRY(hipMemcpyAsync(plan->items.p, words.data(), words.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
   HIP_TRY(hipStreamSynchronize(st));  // `words` is pageable host memory
@@ -2015,6 +2101,16 @@ int guarded(int (*fn)(void*), void* ctx) {
 bool supported_block(int b) { return b == 1 || b == 2 || b == 4 || b == 8 || b == 16 || b == 32; }
 
 }  // namespace
+
+double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, int64_t lds_limit,
+                            int64_t* nitems) {
+  ItemPlanner planner(starts, counts, nblk, b, (size_t)lds_limit, false);
+  ItemSplit best;
+  if (!planner.best_split(starts[nblk], general_step_seconds(nnz, b), nullptr, &best)) return -1.0;
+  *nitems = (int64_t)planner.items(best).size();
+  return best.step_s;
+}
+
 }  // namespace sceig
 
 using namespace sceig;

@@ -182,6 +182,12 @@ hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const dou
                             const int32_t* list, const int32_t* row_extra, int nslots, const int64_t* slice_base,
                             const int64_t* slice_entries, uint16_t* scol, double* sval, hipStream_t st);
 
+// Host part of the filter's plan alone (driver.hip), for tests: what a step is modelled to take, in seconds, for diagonal blocks of
+// rows starts[t] .. starts[t + 1] with the counts of launch_block_extra_chunks and b = 16 or 32 columns; *nitems = the work
+// items.  Negative: there is no plan.
+double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, int64_t lds_limit,
+                            int64_t* nitems);
+
 // ---- connected components and locality reordering (setup) --------------------------------------
 // Renumbering from the component labels (label[i] = smallest node index of i's component), on the device:
 //   old_of_new[p] = original index of new row p (components contiguous, ordered by their smallest node; inside a

@@ -4,6 +4,7 @@ GPU work come back as error codes."""
 import ctypes
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -218,3 +219,43 @@ def test_label_screen_scratch_is_what_the_header_says():
                 assert need <= 4 * (n + k + 64) * (d + 16) + 12 * n + 2100 * (d + 4) + 2 ** 20, (n, d, k, need)
                 assert need == 0 or n * ldx * k >= 4e8
     assert used > 20
+
+
+def _items_model(starts, counts, b, nnz, lds=162_816):
+    f = binding.lib()._ZN5sceig20resident_items_modelEPKiS1_iillPl
+    f.restype = ctypes.c_double
+    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_int64,
+                  ctypes.POINTER(ctypes.c_int64)]
+    starts, counts, out = np.ascontiguousarray(starts, np.int32), np.ascontiguousarray(counts, np.int32), ctypes.c_int64(0)
+    took = []
+    for _ in range(3):
+        t0 = time.perf_counter()
+        step = f(starts.ctypes.data, counts.ctypes.data, len(starts) - 1, b, nnz, lds, ctypes.byref(out))
+        took.append(time.perf_counter() - t0)
+    return step, out.value, min(took)
+
+
+@pytest.mark.parametrize("sliced", [0, 1, 40])
+def test_items_of_many_blocks_are_planned_once(sliced):
+    """The host's part of the filter plan for 500,000 blocks whose entries fit the registers, alone and beside a few that need
+    another form: it looks at the many once, not once per split and with a place in a queue each (0.3 s; 0.02 s)."""
+    many, big = 500_000, 900
+    rows = np.concatenate([np.full(many, 4), np.full(sliced, big)])
+    starts = np.concatenate([[0], np.cumsum(rows)])
+    # chunks beyond the first of rows of 3 and of 40 entries, extra rows, entries
+    counts = np.concatenate([np.tile([0, 0, 0, 12], (many, 1)), np.tile([big, 2 * big, 0, 40 * big], (sliced, 1)).reshape(-1, 4)])
+    nnz = int(counts[:, 3].sum())
+    step, items, took = _items_model(starts, counts, 16, nnz)
+    share = (many * 12 * 128.0 / 150e9 + sliced * 40 * big * 128.0 / 204e9) / 256
+    assert share <= step <= share + 40 * big * 128.0 / 204e9 * (sliced > 0) + 4e-6
+    assert many + sliced <= items <= many + 4 * sliced
+    assert took < 0.13, took
+
+
+def test_items_of_equal_blocks_share_the_compute_units():
+    """512 equal blocks: two for each of the 256 compute units, in either register form."""
+    for b in (16, 32):
+        starts = np.arange(513) * 100
+        counts = np.tile([0, 0, 0, 1000], (512, 1))
+        step, items, _ = _items_model(starts, counts, b, 512_000)
+        assert items == 512 and step == pytest.approx(2 * 1000 * 8.0 * b / 150e9 + 1e-6, rel=1e-12)
