@@ -486,9 +486,11 @@ int sc_version(void);
  * Process-wide event counters (for tests and tuning: which code path a call took).  HOST ONLY.
  *   SC_COUNTER_RESIDENT_FILTERS  start-block filters (inside sc_laplacian_eigsh or sc_chebyshev_filter) that ran as one
  *                                launch with the iterates resident in LDS, since the library was loaded
+ *   SC_COUNTER_GROUPED_SEARCHES  sc_knn_search calls that passed over the points that cannot hold a neighbour
  * Returns the count, or -1 for an unknown id.
  */
 #define SC_COUNTER_RESIDENT_FILTERS 0
+#define SC_COUNTER_GROUPED_SEARCHES 1
 int64_t sc_counter(int32_t which);
 
 /*

@@ -127,6 +127,7 @@ def lib() -> ctypes.CDLL:
 
 
 SC_COUNTER_RESIDENT_FILTERS = 0
+SC_COUNTER_GROUPED_SEARCHES = 1
 
 
 def sc_counter(which: int) -> int:

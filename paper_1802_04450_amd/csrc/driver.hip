@@ -516,6 +516,7 @@ void enqueue_block_qr(double* basis, int64_t n, int64_t ld, int col, int b, doub
 }
 
 std::atomic<int64_t> resident_launches{0};  // sc_counter(SC_COUNTER_RESIDENT_FILTERS)
+std::atomic<int64_t> grouped_searches{0};   // sc_counter(SC_COUNTER_GROUPED_SEARCHES)
 
 // Plan of the LDS-resident Chebyshev filter (resident.hip) for one matrix and block width: the diagonal blocks of the
 // matrix cut into work items (block rows x column slice) whose two iterates fit the LDS of a compute unit.
@@ -2403,6 +2404,7 @@ int sc_version(void) { return 100; }
 int64_t sc_counter(int32_t which) {
   switch (which) {
     case SC_COUNTER_RESIDENT_FILTERS: return resident_launches.load(std::memory_order_relaxed);
+    case SC_COUNTER_GROUPED_SEARCHES: return grouped_searches.load(std::memory_order_relaxed);
     default: return -1;
   }
 }
@@ -3137,9 +3139,10 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
         double* bound = nullptr;
         const size_t gb = knn_group_workspace(c->n, c->d, c->k);
         DevBuf<char> group;
-        const bool grouped = gb > 0 && group.try_alloc(gb);
+        bool grouped = gb > 0 && !std::getenv("SCEIG_NO_GROUPS") && group.try_alloc(gb);
         HIP_TRY(launch_knn_screen(xp.p, c->n, c->d, c->k, work.p, grouped ? group.p : nullptr, left.p, &tiles, &ntiles,
-                                  &bound, c->idx, c->dist, c->st));
+                                  &bound, &grouped, c->idx, c->dist, c->st));
+        if (grouped) grouped_searches.fetch_add(1, std::memory_order_relaxed);
         HIP_TRY(hipMemcpyAsync(left.p, ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
         if (*left.p > 0) {

@@ -349,11 +349,11 @@ hipError_t launch_knn_pad(const double* x, int64_t ldx, int64_t n, int d, double
 constexpr int kLostSlots = 64, kLostStride = 32, kLostInts = kLostSlots * kLostStride;
 size_t knn_screen_workspace(int64_t n, int d, int k);
 // Scratch of the screen's grouped form, which passes over the tiles of points that cannot hold a neighbour; 0 where it is
-// not used.  group_work may be null: the screen then looks at every pair.
+// not used.  group_work may be null: the screen then looks at every pair.  *grouped_out: whether it took the grouped form.
 size_t knn_group_workspace(int64_t n, int d, int k);
 hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* work, void* group_work, int32_t* host,
-                             int32_t** tiles, int32_t** ntiles, double** bound, int32_t* idx_out, double* dist_out,
-                             hipStream_t st);
+                             int32_t** tiles, int32_t** ntiles, double** bound, bool* grouped_out, int32_t* idx_out,
+                             double* dist_out, hipStream_t st);
 hipError_t launch_knn_search(int64_t n, int d, int k, double* xp, const int32_t* tiles, int64_t ntiles,
                              const double* bound, int32_t* idx_out, double* dist_out, hipStream_t st);
 // The undirected edges {i, j} (j in i's list or i in j's) once each as eu < ev, in row order of the emitting list;

@@ -911,8 +911,11 @@ __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restric
 //     pivot among every 64th, of these among every 16th and every 4th, which keeps the tiles of one query block close.
 //     A point farther from its pivot than kGroupFar times what pivots have to the nearest of every 4th one (in the mean of
 //     the squares) would make its tile's ball useless: such points have kFarCells cells of their own, behind the others.
-//     Where that mean is more than kGroupSpread of the points' own spread there are no clusters to speak of (in more than a
-//     few dimensions), and the plain passes are taken at once.
+//   * Whether it will pay is asked of the pivots first: how many of them one has within four times its distance to the nearest
+//     other one, in the mean over kWithin of them.  This goes with the share of the points that the lists will keep; where it
+//     is above group_within the plain passes are taken at once.  (Finding out by making the lists costs 220 of 980 us for
+//     65,000 points, 290 of 2,000 for 100,000.  Lines for 600 sets of 22,500 to 400,000 points in 2 to 128 dimensions: even
+//     and normal, curves, sheets, clusters tight and overlapping, heavy tails.)
 //   * Reach: the threshold pass over the tiles around the query block alone (kGroupAhead on either side) bounds the distance
 //     to the k-th neighbour of every query; reach_t = the largest one of tile t.
 //   * Lists: a tile has a centre and a radius (fp64 against the rounded centre, rounded up).  A query block keeps the tiles w
@@ -923,7 +926,11 @@ __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restric
 //     look at every tile (the far points') are not what a pass waits for.
 // All bounds are in the centred and scaled coordinates of the screen (largest norm in [1, 2)) with a margin of 2e-5 of the
 // centre distance (sums of up to 128 rounded squares) and 2e-6 + 8 sqrt(DP) 2^-52 A for the rounding of the coordinates.
-// The host reads how much the lists leave (one wait) and takes the plain passes where that is more than kGroupMost.
+// The host reads how much the lists leave (one wait) and takes the plain passes where that is more than group_most: a pair of
+// tiles costs four times as much by a list, twice where its products are longer (plain -> grouped, with the lists, which are
+// made by then; 100,000 points, 10 neighbours, 4 to 6 dimensions: a share of 0.15 1,995 -> 1,583 us, 0.20 2,017 -> 1,885, 0.22
+// 1,941 -> 1,997, 0.26 2,017 -> 2,335, 0.45 2,008 -> 3,526; 32 dimensions: 0.25 3,297 -> 2,629, 0.39 949 -> 1,116 with 45,000,
+// 0.47 3,266 -> 4,141; 64 dimensions: 0.38 6,808 -> 4,680, 0.71 6,833 -> 7,737).
 //
 // What bounded the search before was the number of pairs: 100,000 points of 32 coordinates in 100 clusters took two passes
 // of 1.5 and 2.1 ms over 10^10 of them, 3.7 ms in all; 1.09 ms with the lists (3 % of the tile pairs).  400,000 points in 400
@@ -931,16 +938,19 @@ __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restric
 // before.  The line: 30,000 x 32 in 30 clusters (2.9e10) 0.58 -> 0.54 ms, 45,000 x 32 (6.5e10) 1.01 -> 0.60 ms, and the same
 // without clusters 1.00 -> 0.98 ms.
 constexpr double kGroupMinWork = 6.0e10;  // n^2 (padded coordinates)
-constexpr double kGroupMost = 0.6;        // share of the plain passes' tile pairs
 constexpr int kGroupCell = 64;
 constexpr int kGroupMaxCells = 16384;  // 16 bits in the keys
 constexpr int kGroupAhead = 24;
 constexpr int kFarCells = 64;
-constexpr double kGroupFar = 4.0, kGroupSpread = 0.1;
+constexpr double kGroupFar = 4.0;
+// Share of the pivots within four times the distance to the nearest one up to which the lists are made.
+double group_within(int dpb) { return dpb <= 16 ? 0.105 : 0.25; }
+// share of the plain passes' tile pairs up to which the lists are taken
+double group_most(int dpb) { return dpb <= 16 ? 0.25 : dpb <= 32 ? 0.38 : 0.62; }
 
 struct GroupInfo {  // device
   unsigned long long pairs;  // sum of the lists' lengths over the query blocks
-  double spread;             // mean squared distance of the pivots to the nearest of every 4th, over twice the mean squared norm
+  double within;             // share of the pivots within four times a pivot's distance to its nearest other one
   float far;                 // squared distance to the pivot from which a point is a far one, in the screen's scale
   int32_t tiles;             // tiles of the grouped places
   int32_t nparts;            // parts of the lists
@@ -1042,13 +1052,90 @@ __global__ __launch_bounds__(kT) void group_assign_kernel(const u4* __restrict__
   }
 }
 
+constexpr int kKeyPivots = 4;
+// d2[p] = squared distance of row q[p] to the row y, of `pairs` pairs of coordinates
+__device__ __forceinline__ void pivot_distances(const double2* const (&q)[kKeyPivots], const double2* __restrict__ y, int pairs,
+                                                double (&d2)[kKeyPivots]) {
+#pragma unroll
+  for (int p = 0; p < kKeyPivots; ++p) d2[p] = 0.0;
+  for (int t = 0; t < pairs; ++t) {
+    const double2 b = y[t];
+#pragma unroll
+    for (int p = 0; p < kKeyPivots; ++p) {
+      const double2 a = q[p][t];
+      d2[p] = fma(a.x - b.x, a.x - b.x, d2[p]);
+      d2[p] = fma(a.y - b.y, a.y - b.y, d2[p]);
+    }
+  }
+}
+
+// within[e0 .. e0 + kKeyPivots) = how many pivots are within four times the distance that pivot e cells / kWithin has to its
+// nearest other one, the equal ones among them.  A workgroup.
+constexpr int kWithin = 256;
+__device__ __forceinline__ void count_within(const double2* __restrict__ xp2, int pairs, const int32_t* __restrict__ pivot,
+                                             int cells, int e0, int32_t* __restrict__ within) {
+  constexpr int W = kT / 64;
+  __shared__ double least[kKeyPivots][W];
+  __shared__ int counts[kKeyPivots][W];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const double2* q[kKeyPivots];
+  int from[kKeyPivots], count[kKeyPivots];
+  double other[kKeyPivots], d2[kKeyPivots];
+#pragma unroll
+  for (int p = 0; p < kKeyPivots; ++p) {
+    from[p] = (int)((int64_t)(e0 + p) * cells / kWithin);
+    q[p] = xp2 + (int64_t)pivot[from[p]] * pairs;
+    other[p] = INFINITY;
+    count[p] = 0;
+  }
+  for (int c = threadIdx.x; c < cells; c += kT) {
+    pivot_distances(q, xp2 + (int64_t)pivot[c] * pairs, pairs, d2);
+#pragma unroll
+    for (int p = 0; p < kKeyPivots; ++p)
+      if (c != from[p]) other[p] = fmin(other[p], d2[p]);
+  }
+#pragma unroll
+  for (int p = 0; p < kKeyPivots; ++p) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) other[p] = fmin(other[p], __shfl_xor(other[p], o, 64));
+    if (lane == 0) least[p][wave] = other[p];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < kKeyPivots; ++p)
+#pragma unroll
+    for (int w = 0; w < W; ++w) other[p] = fmin(other[p], least[p][w]);
+  for (int c = threadIdx.x; c < cells; c += kT) {
+    pivot_distances(q, xp2 + (int64_t)pivot[c] * pairs, pairs, d2);
+#pragma unroll
+    for (int p = 0; p < kKeyPivots; ++p) count[p] += c != from[p] && d2[p] <= 16.0 * other[p] ? 1 : 0;
+  }
+#pragma unroll
+  for (int p = 0; p < kKeyPivots; ++p) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) count[p] += __shfl_xor(count[p], o, 64);
+    if (lane == 0) counts[p][wave] = count[p];
+  }
+  __syncthreads();
+  if (threadIdx.x < kKeyPivots) {
+    int all = 0;
+    for (int w = 0; w < W; ++w) all += counts[threadIdx.x][w];
+    within[e0 + threadIdx.x] = all;
+  }
+}
+
 // key[f] = (nearest of every 64th pivot, of every 16th, of every 4th, f) of pivot f, each nearest to the one after it;
 // near2[f] = squared distance to the nearest other one of every 4th.  A wave takes kKeyPivots pivots at a time, so that a row
 // that it reads serves them all.
-constexpr int kKeyPivots = 4;
+// The workgroups from `key_blocks` on count what is within reach of some pivots (count_within).
 __global__ __launch_bounds__(kT) void group_key_kernel(const double* __restrict__ xp, int dp, const int32_t* __restrict__ pivot,
                                                        int cells, unsigned long long* __restrict__ key,
-                                                       double* __restrict__ near2) {
+                                                       double* __restrict__ near2, int key_blocks,
+                                                       int32_t* __restrict__ within) {
+  if ((int)blockIdx.x >= key_blocks) {
+    count_within(reinterpret_cast<const double2*>(xp), dp / 2, pivot, cells, ((int)blockIdx.x - key_blocks) * kKeyPivots, within);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int f0 = ((int)blockIdx.x * (kT / 64) + (threadIdx.x >> 6)) * kKeyPivots;
   if (f0 >= cells) return;
@@ -1059,7 +1146,7 @@ __global__ __launch_bounds__(kT) void group_key_kernel(const double* __restrict_
 #pragma unroll
   for (int level = 0; level < 3; ++level) {
     const int step = level == 0 ? 4 : level == 1 ? 16 : 64;
-    const double2* __restrict__ q[kKeyPivots];
+    const double2* q[kKeyPivots];
     double best[kKeyPivots], other[kKeyPivots];
     int at[kKeyPivots];
 #pragma unroll
@@ -1069,19 +1156,8 @@ __global__ __launch_bounds__(kT) void group_key_kernel(const double* __restrict_
       at[p] = 0;
     }
     for (int c = lane; c * step < cells; c += 64) {
-      const double2* __restrict__ y = xp2 + (int64_t)pivot[c * step] * (dp / 2);
       double d2[kKeyPivots];
-#pragma unroll
-      for (int p = 0; p < kKeyPivots; ++p) d2[p] = 0.0;
-      for (int t = 0; t < dp / 2; ++t) {
-        const double2 b = y[t];
-#pragma unroll
-        for (int p = 0; p < kKeyPivots; ++p) {
-          const double2 a = q[p][t];
-          d2[p] = fma(a.x - b.x, a.x - b.x, d2[p]);
-          d2[p] = fma(a.y - b.y, a.y - b.y, d2[p]);
-        }
-      }
+      pivot_distances(q, xp2 + (int64_t)pivot[c * step] * (dp / 2), dp / 2, d2);
 #pragma unroll
       for (int p = 0; p < kKeyPivots; ++p) {
         if (c * step != from[p]) other[p] = fmin(other[p], d2[p]);
@@ -1116,17 +1192,14 @@ __global__ __launch_bounds__(kT) void group_key_kernel(const double* __restrict_
                     ((unsigned long long)found[0][p] << 16) | (unsigned)(f0 + p);
 }
 
-// info->spread and info->far from the pivots' near2 and norms.  One workgroup.
-__global__ __launch_bounds__(1024) void group_spread_kernel(const double* __restrict__ near2, const double* __restrict__ nrm2,
-                                                            const int32_t* __restrict__ pivot, int cells,
+// info->within and info->far from the pivots' counts and near2.  One workgroup.
+__global__ __launch_bounds__(1024) void group_measure_kernel(const double* __restrict__ near2,
+                                                            const int32_t* __restrict__ within, int cells,
                                                             const ScreenScale* __restrict__ scale,
                                                             GroupInfo* __restrict__ info) {
   __shared__ double sums[2][16];
-  double a = 0.0, b = 0.0;
-  for (int f = threadIdx.x; f < cells; f += 1024) {
-    a += near2[f];
-    b += nrm2[pivot[f]];
-  }
+  double a = 0.0, b = (int)threadIdx.x < kWithin ? (double)within[threadIdx.x] : 0.0;
+  for (int f = threadIdx.x; f < cells; f += 1024) a += near2[f];
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     a += __shfl_xor(a, o, 64);
@@ -1143,7 +1216,7 @@ __global__ __launch_bounds__(1024) void group_spread_kernel(const double* __rest
     b += sums[1][w];
   }
   const double f = screen_factor(*scale);
-  info->spread = a / (2.0 * b);
+  info->within = screen_usable(*scale) ? b / ((double)kWithin * cells) : 1.0;  // no grouping without a scale
   info->far = (float)(kGroupFar * (a / cells) * f * f);
 }
 
@@ -1553,7 +1626,7 @@ struct GroupPlan {
   int64_t blocks = 0;            // query blocks of a round
   int least = 0, slices = 0;     // parts that a list has at least; sets of 16 classes
   size_t off_pb = 0, off_half = 0, off_norm = 0, off_phalf = 0, off_pnorm = 0, off_src = 0, off_pivot = 0, off_size = 0,
-         off_base = 0, off_order = 0, off_key = 0, off_near2 = 0, off_cell = 0, off_seat = 0, off_info = 0, off_centre = 0, off_radius = 0,
+         off_base = 0, off_order = 0, off_key = 0, off_near2 = 0, off_within = 0, off_cell = 0, off_seat = 0, off_info = 0, off_centre = 0, off_radius = 0,
          off_reach = 0, off_idle = 0, off_near = 0, off_near_count = 0, off_parts = 0, off_maxima = 0, off_tau = 0, off_count = 0,
          off_list = 0, bytes = 0;
 };
@@ -1595,6 +1668,7 @@ GroupPlan plan_group(int64_t n, int d, int k) {
   g.off_order = place((size_t)(g.cells + kFarCells) * 4);
   g.off_key = place((size_t)g.cells * 8);
   g.off_near2 = place((size_t)g.cells * 8);
+  g.off_within = place((size_t)kWithin * 4);
   g.off_cell = place((size_t)n * 4);
   g.off_seat = place((size_t)n * 4);
   g.off_info = place(sizeof(GroupInfo));
@@ -1621,8 +1695,8 @@ size_t knn_screen_workspace(int64_t n, int d, int k) { return plan_screen(n, d, 
 size_t knn_group_workspace(int64_t n, int d, int k) { return plan_group(n, d, k).bytes; }
 
 hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* work, void* group_work, int32_t* host,
-                             int32_t** tiles, int32_t** ntiles, double** bound, int32_t* idx_out, double* dist_out,
-                             hipStream_t st) {
+                             int32_t** tiles, int32_t** ntiles, double** bound, bool* grouped_out, int32_t* idx_out,
+                             double* dist_out, hipStream_t st) {
   const ScreenPlan p = plan_screen(n, d, k);
   if (!p.use) return hipErrorInvalidValue;
   const int dp = knn_padded_dim(d), ks = p.dpb / 16;
@@ -1739,17 +1813,19 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
   if (grouped) {
     int32_t* pivot = reinterpret_cast<int32_t*>(gw + g.off_pivot);
     double* near2 = reinterpret_cast<double*>(gw + g.off_near2);
+    int32_t* within = reinterpret_cast<int32_t*>(gw + g.off_within);
     const int per = kKeyPivots * (kT / 64);
     hipLaunchKernelGGL(group_init_kernel, dim3(blocks(g.tiles * 32)), dim3(kT), 0, st, n, g.tiles * 32, g.cells,
                        g.pivot_tiles * 32, reinterpret_cast<int32_t*>(gw + g.off_src), pivot,
                        reinterpret_cast<int32_t*>(gw + g.off_size), reinterpret_cast<int32_t*>(gw + g.off_order), info);
-    hipLaunchKernelGGL(group_key_kernel, dim3((unsigned)((g.cells + per - 1) / per)), dim3(kT), 0, st, xp, dp, pivot, g.cells,
-                       reinterpret_cast<unsigned long long*>(gw + g.off_key), near2);
-    hipLaunchKernelGGL(group_spread_kernel, dim3(1), dim3(1024), 0, st, near2, nrm2, pivot, g.cells, scale, info);
+    const int key_blocks = (g.cells + per - 1) / per;
+    hipLaunchKernelGGL(group_key_kernel, dim3((unsigned)(key_blocks + kWithin / kKeyPivots)), dim3(kT), 0, st, xp, dp, pivot,
+                       g.cells, reinterpret_cast<unsigned long long*>(gw + g.off_key), near2, key_blocks, within);
+    hipLaunchKernelGGL(group_measure_kernel, dim3(1), dim3(1024), 0, st, near2, within, g.cells, scale, info);
     GroupInfo got;
     e = read_info(&got);
     if (e != hipSuccess) return e;
-    grouped = got.spread < kGroupSpread;  // a NaN is no
+    grouped = got.within < group_within(p.dpb);  // a NaN is no
   }
   if (grouped) {
     u4* gxb = reinterpret_cast<u4*>(gw);
@@ -1814,7 +1890,7 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     nparts = got.nparts;
     const int64_t here = got.tiles < g.chunk ? got.tiles : g.chunk;  // query tiles of the first round, whose lists are made
     all_tiles = got.tiles;
-    if (!((double)got.pairs < kGroupMost * (double)p.tiles * (double)((here + qt - 1) / qt))) {  // as they are, then
+    if (!((double)got.pairs < group_most(p.dpb) * (double)p.tiles * (double)((here + qt - 1) / qt))) {  // as they are, then
       all_tiles = p.tiles;
       chunk = p.chunk;
       slices = p.slices;
@@ -1829,6 +1905,7 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     }
   }
   const int64_t places = src ? all_tiles * 32 : n;
+  *grouped_out = src != nullptr;
   for (int64_t t0 = 0; t0 < all_tiles; t0 += chunk) {
     const int64_t nt = all_tiles - t0 < chunk ? all_tiles - t0 : chunk;
     const int64_t q0 = 32 * t0, nq = places - q0 < 32 * nt ? places - q0 : 32 * nt;
