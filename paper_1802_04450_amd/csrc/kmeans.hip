@@ -309,7 +309,7 @@ __global__ __launch_bounds__(kT) void centroid_finish_kernel(const double* __res
 // kScreenFloor (below, what single squares lose to the denormal numbers is no longer negligible), and the lower bound has
 // to exceed the distance kept by 1e-6 of it: more than the fp64 sums are off.  A NaN on the way fails the test and the
 // point is computed; so is every point of data that have no such scale (scale 0: copies of zeros).
-// Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 14.2 us with the copy, which an XCD's L2 keeps
+// Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 12.8 us with the copy, which an XCD's L2 keeps
 // its part of from draw to draw (21 MB in all); what is left is the chain centre, its row, the point's row.  (Leaving points out by the triangle inequality with a kept assignment did
 // not shorten the pass: it saves no load of the first row.)
 constexpr int kSeedPoints = 64;   // points per block
@@ -319,7 +319,13 @@ constexpr int kExactLanes = 16;
 // draws: 1.64 against 1.88 ms; at 140,000 of 128, 128 draws: 2.82 against 2.64 ms).
 constexpr int64_t kDrawBlocks = 1800;
 
-constexpr int64_t kSeedWide = 768;
+// Two blocks a workgroup and a thread's copies requested before the draw, from kSeedWide blocks on and up to kSeedWideDim
+// coordinates.  A draw inside the pass, us with one block / two / four: 80,000 x 100 13.0 / 11.8 / 13.7, 100,000 x 100 14.5 / 12.8 /
+// 13.5, 115,000 x 64 12.1 / 11.2 / 11.4; fewer blocks leave the chip idle (60,000 x 100 11.8 / 11.1 / 13.7, 40,000 x 100 11.2 / 11.5 /
+// 14.3), and with 128 coordinates the registers do (60,000 11.4 / 12.1 / 15.1, 100,000 13.1 / 13.2 / 13.8).  Without a draw inside:
+// 140,000 x 32 13.3 / 12.2 / 13.3, 600,000 x 16 26.2 / 19.7 / 19.4, 200,000 x 100 24.1 / 20.9 / 25.4, of 128 20.9 / 23.7 / 30.1.
+constexpr int64_t kSeedWide = 1024;
+constexpr int kSeedWideDim = 112;
 constexpr float kScreenFloor = 1e-30f;
 
 // xh[i] = the centred and scaled point in bf16, padded with zeros to dpb coordinates (a multiple of 8); err[i] as above,
@@ -1247,13 +1253,10 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
                      st, x, ldx, d, n, xh, dpb, err, u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], \
                      dist2[at] + n)
     if (screened && i > 1) {
-      // four blocks a workgroup: a quarter as many that read all block sums for the draw (15.6 -> 14.2 us a
-      // draw at 100,000 x 100), and fewer launches'
-      // worth of workgroups where there are few coordinates (300,000 x 20, no draw inside: 20.9 -> 17.5 us a pass;
-      // 140,000 x 128: 21.0 against 23.2 us, so not there)
-      if (draw && dpb <= 128 && nb >= kSeedWide) SC_SEED(true, true, 4, true);
+      const bool wide = dpb <= kSeedWideDim && nb >= kSeedWide;
+      if (draw && wide) SC_SEED(true, true, 2, true);
       else if (draw) SC_SEED(true, true, 1, false);
-      else if (dpb <= 64 && nb >= kSeedWide) SC_SEED(true, false, 4, true);
+      else if (wide) SC_SEED(true, false, 2, true);
       else SC_SEED(true, false, 1, false);
     } else {
       if (draw) SC_SEED(false, true, 1, false); else SC_SEED(false, false, 1, false);

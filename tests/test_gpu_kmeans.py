@@ -195,7 +195,11 @@ def test_update_over_its_ranges(B, n, d, k):
 @pytest.mark.parametrize("n,d,k,kind", [(62501, 64, 33, "blobs"), (120003, 34, 40, "blobs"), (45001, 90, 32, "offset"),
                                         (40001, 101, 35, "equal"), (62501, 64, 40, 1e20), (62501, 64, 40, 1e19),
                                         (120003, 34, 40, 1e25), (62501, 64, 40, 3e-23), (62501, 64, 40, 1e-21),
-                                        (62501, 64, 40, 1e-30), (62501, 64, 33, 1e120), (62501, 64, 33, "two scales")])
+                                        (62501, 64, 40, 1e-30), (62501, 64, 33, 1e120), (62501, 64, 33, "two scales"),
+                                        # around the numbers of blocks from which two go to a workgroup and the draw moves
+                                        # out, an odd number of them, a last block of one point; the most coordinates
+                                        (65409, 105, 32, "blobs"), (65473, 112, 33, "blobs"), (65537, 113, 32, "blobs"),
+                                        (115137, 40, 32, "offset"), (115201, 40, 34, "equal"), (65600, 64, 33, 1e20)])
 def test_screened_seeding_equals_plain_distances(B, n, d, k, kind):
     x = _blobs(n, d, 25, seed=n, spread=0.3)
     if kind == "offset":
