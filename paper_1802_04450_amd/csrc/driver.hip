@@ -1421,38 +1421,6 @@ struct Solver {
     filt_rate = rate;
   }
 
-  // The check phase's question is whether S has an eigenvalue above kappa (the k-th locked one plus tol) outside the
-  // locked vectors.  It is answered from below: the phase's basis spans all T(S) F(S) q, F the start filter (Chebyshev of
-  // degree d on [lo, a]), T any polynomial of degree steps - 1, q a random column.  Take T = the Chebyshev polynomial of
-  // [-1, t] for some t between the largest Ritz value theta and kappa.  If such an eigenvalue existed, P = T F would be at
-  // least P(kappa) on it and at most max|F| on the spectrum below t (none lies below -1), and were its share of q larger
-  // than sqrt(M) max|F| / P(kappa), M = (t + 1) / (t - theta) - 1, the Rayleigh quotient of P(S) q alone, hence the
-  // largest Ritz value, would exceed theta.  A share below x has probability at most x sqrt(n) in one random column (the
-  // entries are uniform; a unit combination of them has density at most 1/sqrt(2), Ball 1986) and that to the power b in
-  // all of them.  Returns the block steps after which this probability is below 1e-20, with the best t of a few.
-  // Waiting for the largest Ritz value itself to converge says no more and costs far more: the spectrum is dense there
-  // (4,040 nodes in one component, 10 values: 85 steps against 1).
-  int check_steps_needed(double theta, double kappa, int d, double lo, double a) const {
-    auto lncosh = [](double v) { return v + std::log1p(std::exp(-2.0 * v)) - std::log(2.0); };
-    auto lnf = [&](double y) {  // ln |F(y)| outside the damped interval, 0 inside (where |F| <= 1)
-      const double x = std::fabs((2.0 * y - a - lo) / (a - lo));
-      return d > 0 && x > 1.0 ? lncosh(d * std::acosh(x)) : 0.0;
-    };
-    if (!(kappa > theta)) return 1 << 30;
-    double best = 1e9;
-    for (int i = 1; i <= 9; ++i) {
-      const double t = theta + 0.1 * i * (kappa - theta);
-      if (!(t > theta) || !(t < kappa) || !(t > -1.0)) continue;
-      const double share = 0.5 * std::log(std::max((t + 1.0) / (t - theta) - 1.0, 1e-3));
-      const double need = share + 0.5 * std::log((double)n) + 20.0 * std::log(10.0) / b;
-      const double have = (d > 0 && kappa <= a ? 0.0 : lnf(kappa)) - std::max({0.0, lnf(t), lnf(-1.0)});
-      const double rate = std::acosh((2.0 * kappa - t + 1.0) / (t + 1.0));
-      const double steps = need <= have ? 1.0 : 1.0 + std::ceil((need - have + std::log(2.0)) / std::max(rate, 1e-9));
-      best = std::min(best, steps);
-    }
-    return (int)best;
-  }
-
   // Filter of the check phase's block: the degree that answers the question above with one block step, where the
   // amplification of the locked vectors above kappa (they are projected out before and after) leaves room for it.
   void plan_check_filter() {
@@ -1469,7 +1437,7 @@ struct Solver {
       // the Ritz value of the filtered block will be somewhat above the estimate
       const double seen = theta + 0.05 * (kappa - theta);
       for (int d = 2; d <= dmax && (best == 0 || d < best); ++d) {
-        if (check_steps_needed(seen, kappa, d, -1.0, a) > 1) continue;
+        if (check_steps_needed(seen, kappa, d, -1.0, a, n, b) > 1) continue;
         best = d;
         filt_a = a;
       }
@@ -1804,7 +1772,7 @@ struct Solver {
 
         int check_more = 0;  // block steps that the check phase's test still needs, 0 = unknown or out of reach
         if (check_open && nreal == ja) {
-          const int need = check_steps_needed(theta[ja - 1], kth_locked_theta() + tol, check_d, check_lo, check_a);
+          const int need = check_steps_needed(theta[ja - 1], kth_locked_theta() + tol, check_d, check_lo, check_a, n, b);
           if (debug_on())
             std::fprintf(stderr, "[sceig] check phase: %d of %d steps\n", steps_in_phase, need);
           if (need <= steps_in_phase) {
@@ -2102,6 +2070,38 @@ int guarded(int (*fn)(void*), void* ctx) {
 bool supported_block(int b) { return b == 1 || b == 2 || b == 4 || b == 8 || b == 16 || b == 32; }
 
 }  // namespace
+
+// The check phase's question is whether S has an eigenvalue above kappa (the k-th locked one plus tol) outside the
+// locked vectors.  It is answered from below: the phase's basis spans all T(S) F(S) q, F the start filter (Chebyshev of
+// degree d on [lo, a]), T any polynomial of degree steps - 1, q a random column.  Take T = the Chebyshev polynomial of
+// [-1, t] for some t between the largest Ritz value theta and kappa.  If such an eigenvalue existed, P = T F would be at
+// least P(kappa) on it and at most max|F| on the spectrum below t (none lies below -1), and were its share of q larger
+// than sqrt(M) max|F| / P(kappa), M = (t + 1) / (t - theta) - 1, the Rayleigh quotient of P(S) q alone, hence the
+// largest Ritz value, would exceed theta.  A share below x has probability at most x sqrt(2 n) in one random column (the
+// entries are uniform in [-1, 1]; a unit combination of them has density at most 1/sqrt(2), Ball 1986, and |q| is at most
+// sqrt(n)) and that to the power b in all of them.
+// Waiting for the largest Ritz value itself to converge says no more and costs far more: the spectrum is dense there
+// (4,040 nodes in one component, 10 values: 85 steps against 1).
+int check_steps_needed(double theta, double kappa, int d, double lo, double a, int64_t n, int b) {
+  auto lncosh = [](double v) { return v + std::log1p(std::exp(-2.0 * v)) - std::log(2.0); };
+  auto lnf = [&](double y) {  // ln |F(y)| outside the damped interval, 0 inside (where |F| <= 1)
+    const double x = std::fabs((2.0 * y - a - lo) / (a - lo));
+    return d > 0 && x > 1.0 ? lncosh(d * std::acosh(x)) : 0.0;
+  };
+  if (!(kappa > theta)) return 1 << 30;
+  double best = 1e9;
+  for (int i = 1; i <= 9; ++i) {
+    const double t = theta + 0.1 * i * (kappa - theta);
+    if (!(t > theta) || !(t < kappa) || !(t > -1.0)) continue;
+    const double share = 0.5 * std::log(std::max((t + 1.0) / (t - theta) - 1.0, 1e-3));
+    const double need = share + 0.5 * std::log(2.0 * (double)n) + 20.0 * std::log(10.0) / b;
+    const double have = (d > 0 && kappa <= a ? 0.0 : lnf(kappa)) - std::max({0.0, lnf(t), lnf(-1.0)});
+    const double rate = std::acosh((2.0 * kappa - t + 1.0) / (t + 1.0));
+    const double steps = need <= have ? 1.0 : 1.0 + std::ceil((need - have + std::log(2.0)) / std::max(rate, 1e-9));
+    best = std::min(best, steps);
+  }
+  return (int)best;
+}
 
 double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, int64_t lds_limit,
                             int64_t* nitems) {

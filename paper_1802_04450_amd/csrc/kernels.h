@@ -182,6 +182,11 @@ hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const dou
                             const int32_t* list, const int32_t* row_extra, int nslots, const int64_t* slice_base,
                             const int64_t* slice_entries, uint16_t* scol, double* sval, hipStream_t st);
 
+// Block steps of b random columns after which the check phase of a solve (driver.hip), whose largest Ritz value is theta, has
+// shown but for a chance of 1e-20 that nothing above kappa is left, on n rows and for a spectrum in [-1, 1]; its block went
+// through a filter of degree d on [lo, a] (d = 0: none).  2^30: never.
+int check_steps_needed(double theta, double kappa, int d, double lo, double a, int64_t n, int b);
+
 // Host part of the filter's plan alone (driver.hip), for tests: what a step is modelled to take, in seconds, for diagonal blocks of
 // rows starts[t] .. starts[t + 1] with the counts of launch_block_extra_chunks and b = 16 or 32 columns; *nitems = the work
 // items.  Negative: there is no plan.

@@ -259,3 +259,66 @@ def test_items_of_equal_blocks_share_the_compute_units():
         counts = np.tile([0, 0, 0, 1000], (512, 1))
         step, items, _ = _items_model(starts, counts, b, 512_000)
         assert items == 512 and step == pytest.approx(2 * 1000 * 8.0 * b / 150e9 + 1e-6, rel=1e-12)
+
+
+def _chebyshev(y, degree, lo, hi):
+    x = (2.0 * y - hi - lo) / (hi - lo)
+    inside = np.cos(degree * np.arccos(np.clip(x, -1.0, 1.0)))
+    return np.where(np.abs(x) <= 1.0, inside, np.cosh(degree * np.arccosh(np.maximum(np.abs(x), 1.0))))
+
+
+def _undetected(theta, kappa, d, lo, a, steps, n, b):
+    """log10 of the chance that an eigenvalue from kappa on stays below a largest Ritz value of theta: with P = T F, a share
+    x of it in a column shows once x^2 P(kappa)^2 (kappa - theta) > max P^2 (theta + 1), the most that eigenvalues of
+    [-1, theta] can pull the Rayleigh quotient of P(S) q below theta."""
+    low, high = np.linspace(-1.0, theta, 6001), np.linspace(kappa, 1.0, 2001)
+    f_low = np.abs(_chebyshev(low, d, lo, a)) if d else 1.0
+    f_high = np.abs(_chebyshev(high, d, lo, a)) if d else 1.0
+    best = 0.0
+    for t in np.linspace(theta, kappa, 42)[1:-1]:
+        most = np.max(f_low * np.abs(_chebyshev(low, steps - 1, -1.0, t)))
+        least = np.min(f_high * np.abs(_chebyshev(high, steps - 1, -1.0, t)))
+        share = most / max(least, 1e-300) * np.sqrt((theta + 1.0) / (kappa - theta))
+        best = min(best, b * np.log10(share * np.sqrt(2.0 * n)))
+    return best
+
+
+def _check_steps_needed():
+    f = binding.lib()._ZN5sceig18check_steps_neededEddiddli
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_double, ctypes.c_double, ctypes.c_int, ctypes.c_double, ctypes.c_double, ctypes.c_int64, ctypes.c_int]
+    return f
+
+
+@pytest.mark.parametrize("b", [1, 2, 8, 16, 32])
+@pytest.mark.parametrize("theta,kappa,d,lo,a", [
+    (0.5, 0.6, 0, -1.0, 0.0), (0.9, 0.999, 0, -1.0, 0.0), (-0.2, 0.3, 0, -1.0, 0.0), (0.98, 0.981, 0, -1.0, 0.0),
+    (0.5, 0.6, 12, -1.0, 0.55), (0.5, 0.6, 40, -1.0, 0.53), (0.9, 0.93, 20, -0.4, 0.91), (0.9, 0.93, 6, -0.7, 0.6),
+    (0.3, 0.95, 9, -1.0, 0.4), (0.99, 0.9999, 30, -0.5, 0.992)])
+def test_check_phase_steps_leave_a_chance_of_1e_minus_20(b, theta, kappa, d, lo, a):
+    """The number of block steps after which a solve stops looking for a larger eigenvalue, against the polynomials
+    themselves: enough for what it promises, and not many more than that."""
+    f = _check_steps_needed()
+    for n in (50, 4040, 2_000_000):
+        steps = f(theta, kappa, d, lo, a, n, b)
+        assert 1 <= steps < 10_000
+        assert _undetected(theta, kappa, d, lo, a, steps, n, b) <= -20.0
+        fewer = int(0.8 * steps) - 2
+        assert fewer < 1 or _undetected(theta, kappa, d, lo, a, fewer, n, b) > -20.0
+        assert f(kappa, kappa, d, lo, a, n, b) == f(kappa + 0.001, kappa, d, lo, a, n, b) == 1 << 30
+
+
+@pytest.mark.parametrize("b", [2, 8, 16, 32])
+def test_check_phase_filter_that_makes_one_step_enough(b):
+    """The shortest filters after which one block step is said to be enough: there is no room to spare in them."""
+    f = _check_steps_needed()
+    seen = 0
+    for n in (60, 700, 4040, 100_003):
+        for theta, kappa in ((0.5, 0.6), (0.9, 0.95), (0.97, 0.9999), (0.2, 0.7), (0.7, 0.73)):
+            for part in (0.2, 0.4, 0.6):
+                a = theta + part * (kappa - theta)
+                d = next((q for q in range(2, 121) if f(theta + 0.05 * (kappa - theta), kappa, q, -1.0, a, n, b) == 1), None)
+                if d is not None:
+                    seen += 1
+                    assert _undetected(theta + 0.05 * (kappa - theta), kappa, d, -1.0, a, 1, n, b) <= -20.0, (n, theta, kappa, a, d)
+    assert seen >= 30
