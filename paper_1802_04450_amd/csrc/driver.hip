@@ -2075,7 +2075,7 @@ bool supported_block(int b) { return b == 1 || b == 2 || b == 4 || b == 8 || b =
 // locked vectors.  It is answered from below: the phase's basis spans all T(S) F(S) q, F the start filter (Chebyshev of
 // degree d on [lo, a]), T any polynomial of degree steps - 1, q a random column.  Take T = the Chebyshev polynomial of
 // [-1, t] for some t between the largest Ritz value theta and kappa.  If such an eigenvalue existed, P = T F would be at
-// least P(kappa) on it and at most max|F| on the spectrum below t (none lies below -1), and were its share of q larger
+// least P(kappa) on it (kappa > a) and at most max|F| on the spectrum below t (none lies below -1), and were its share of q larger
 // than sqrt(M) max|F| / P(kappa), M = (t + 1) / (t - theta) - 1, the Rayleigh quotient of P(S) q alone, hence the
 // largest Ritz value, would exceed theta.  A share below x has probability at most x sqrt(2 n) in one random column (the
 // entries are uniform in [-1, 1]; a unit combination of them has density at most 1/sqrt(2), Ball 1986, and |q| is at most
@@ -2089,13 +2089,14 @@ int check_steps_needed(double theta, double kappa, int d, double lo, double a, i
     return d > 0 && x > 1.0 ? lncosh(d * std::acosh(x)) : 0.0;
   };
   if (!(kappa > theta)) return 1 << 30;
+  if (d > 0 && !(kappa > a)) return 1 << 30;  // between kappa and a the filter may have put out what is asked for
   double best = 1e9;
   for (int i = 1; i <= 9; ++i) {
     const double t = theta + 0.1 * i * (kappa - theta);
     if (!(t > theta) || !(t < kappa) || !(t > -1.0)) continue;
     const double share = 0.5 * std::log(std::max((t + 1.0) / (t - theta) - 1.0, 1e-3));
     const double need = share + 0.5 * std::log(2.0 * (double)n) + 20.0 * std::log(10.0) / b;
-    const double have = (d > 0 && kappa <= a ? 0.0 : lnf(kappa)) - std::max({0.0, lnf(t), lnf(-1.0)});
+    const double have = lnf(kappa) - std::max({0.0, lnf(t), lnf(-1.0)});
     const double rate = std::acosh((2.0 * kappa - t + 1.0) / (t + 1.0));
     const double steps = need <= have ? 1.0 : 1.0 + std::ceil((need - have + std::log(2.0)) / std::max(rate, 1e-9));
     best = std::min(best, steps);

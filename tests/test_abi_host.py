@@ -322,3 +322,14 @@ def test_check_phase_filter_that_makes_one_step_enough(b):
                     seen += 1
                     assert _undetected(theta + 0.05 * (kappa - theta), kappa, d, -1.0, a, 1, n, b) <= -20.0, (n, theta, kappa, a, d)
     assert seen >= 30
+
+
+@pytest.mark.parametrize("b", [1, 8, 32])
+@pytest.mark.parametrize("kappa", [0.55, 0.65, 0.7])
+def test_check_phase_does_not_trust_a_filter_that_damps_what_it_asks_for(b, kappa):
+    """A filter whose damped interval reaches past the value that something larger would have (a later phase has locked larger
+    values than an earlier one) has zeros there: no number of steps shows an eigenvalue that it has put out."""
+    f = _check_steps_needed()
+    for d in (1, 2, 17, 30):
+        assert f(0.5, kappa, d, -1.0, 0.7, 4040, b) == f(0.5, kappa, d, -0.4, 0.7, 4040, b) == 1 << 30
+    assert f(0.5, kappa, 0, -1.0, 0.7, 4040, b) < 1000 and f(0.5, 0.701, 30, -1.0, 0.7, 4040, b) < 1000
