@@ -1049,6 +1049,8 @@ struct Solver {
   // SCEIG_FILTER_FP64_TAIL = a number larger than any degree keeps every step in double precision.
   int filter_tail64 = std::getenv("SCEIG_FILTER_FP64_TAIL") ? std::atoi(std::getenv("SCEIG_FILTER_FP64_TAIL")) : 6;
   bool tentative_two_passes = std::getenv("SCEIG_TENTATIVE_TWO_PASSES") != nullptr;
+  // for tests of the check phase: the solve works for one pair more and gives up the unlock-th largest before that phase
+  int unlock = std::getenv("SCEIG_UNLOCK") ? std::atoi(std::getenv("SCEIG_UNLOCK")) : -1;
   double tentative_min_work = std::getenv("SCEIG_TENTATIVE_MIN_WORK") ? std::atof(std::getenv("SCEIG_TENTATIVE_MIN_WORK")) : 2e7;
   size_t ws_limit = 0;         // > 0: size of the caller's workspace, checked against the estimate once nnz is known
   hipStream_t st;
@@ -1504,6 +1506,7 @@ struct Solver {
   int run(double* evals_out, double* evecs_out) {
     const double t_begin = now_s();
     timer.st = st;
+    if (unlock >= 0) k += 1;
     setup();
     int cycles = 0;
     bool not_converged = false;
@@ -1519,6 +1522,14 @@ struct Solver {
     std::vector<char> ghost;
 
     while (!finished) {
+      if (unlock >= 0 && nl >= k) {
+        std::vector<int> order((size_t)nl);
+        std::iota(order.begin(), order.end(), 0);
+        std::sort(order.begin(), order.end(), [&](int x, int y) { return theta_locked[x] > theta_locked[y]; });
+        k -= 1;
+        drop_locked(order[std::min(unlock, k)]);
+        unlock = -1;
+      }
       const bool verifying = nl >= k;
       if (verifying && (flags & SC_FLAG_NO_VERIFY)) break;
       // W >= 0 makes D^-1 W row-stochastic, so no eigenvalue of S exceeds 1: once the k-th locked theta is within

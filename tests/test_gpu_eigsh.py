@@ -506,6 +506,26 @@ def test_check_phase(B, k, block, no_filter, most):
     assert most is None or stats["block_steps"] <= most, stats
 
 
+# k = 10: what is missing stands clear of the rest (the largest, one in the middle, the last); k = 7 and 14: among close values
+@pytest.mark.parametrize("k,block,missing,no_filter", [(10, 1, 0, False), (10, 2, 4, False), (10, 8, 0, False), (10, 8, 9, False),
+                                                       (10, 16, 4, False), (10, 16, 9, False), (10, 8, 9, True),
+                                                       (10, 2, 9, True), (10, 16, 0, True), (7, 8, 6, False), (7, 2, 6, True),
+                                                       (14, 16, 13, False), (14, 1, 12, False)])
+def test_check_phase_finds_what_the_locked_pairs_lack(B, k, block, missing, no_filter, monkeypatch):
+    """One of the k largest is given up for the one after them before the check phase, which has to bring it back."""
+    g, _ = wl.stochastic_block_model(1200, 10, 0.33, 0.002, 3)
+    rp, c, v, n = g
+    lam0, vec0 = dense.smallest_eigenpairs(rp, c, v, k + 1)
+    flags = B.SC_FLAG_NO_START_FILTER if no_filter else 0
+    monkeypatch.setenv("SCEIG_UNLOCK", str(missing))
+    wrong, _, code, _ = solve(B, g, k, 1e-10, block=block, m=128, flags=flags | B.SC_FLAG_NO_VERIFY)
+    assert code == B.SC_OK
+    assert np.max(np.abs(wrong - np.delete(lam0, missing))) <= 1e-9      # it is missing
+    lam, vec, code, _ = solve(B, g, k, 1e-10, block=block, m=128, flags=flags)
+    assert code == B.SC_OK
+    check_against_oracle(g, k, lam, vec, lam0, vec0)
+
+
 def test_setup_that_runs_out_of_memory_after_the_degrees(B):
     """The setup of a wide solve asks for its scaled values while the marks of the degree pass are on their way to the host:
     without room for them the call is refused, and the next one is not disturbed by it."""
