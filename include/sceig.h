@@ -487,10 +487,13 @@ int sc_version(void);
  *   SC_COUNTER_RESIDENT_FILTERS  start-block filters (inside sc_laplacian_eigsh or sc_chebyshev_filter) that ran as one
  *                                launch with the iterates resident in LDS, since the library was loaded
  *   SC_COUNTER_GROUPED_SEARCHES  sc_knn_search calls that passed over the points that cannot hold a neighbour
+ *   SC_COUNTER_SCREENED_LABELLINGS  labelling steps of k-means in which the reduced-precision screen left at most a quarter of
+ *                                the points to the fp64 labelling
  * Returns the count, or -1 for an unknown id.
  */
 #define SC_COUNTER_RESIDENT_FILTERS 0
 #define SC_COUNTER_GROUPED_SEARCHES 1
+#define SC_COUNTER_SCREENED_LABELLINGS 2
 int64_t sc_counter(int32_t which);
 
 /*

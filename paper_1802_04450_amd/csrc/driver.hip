@@ -517,6 +517,7 @@ void enqueue_block_qr(double* basis, int64_t n, int64_t ld, int col, int b, doub
 
 std::atomic<int64_t> resident_launches{0};  // sc_counter(SC_COUNTER_RESIDENT_FILTERS)
 std::atomic<int64_t> grouped_searches{0};   // sc_counter(SC_COUNTER_GROUPED_SEARCHES)
+std::atomic<int64_t> screened_labellings{0};  // sc_counter(SC_COUNTER_SCREENED_LABELLINGS)
 
 // Plan of the LDS-resident Chebyshev filter (resident.hip) for one matrix and block width: the diagonal blocks of the
 // matrix cut into work items (block rows x column slice) whose two iterates fit the LDS of a compute unit.
@@ -2214,7 +2215,7 @@ struct KMeans {
     work.alloc(wb);
     if (lwb) lwork.alloc(lwb);
     // the reduced copy of the points is worth its three launches from the third step on
-    const size_t sb = max_iter >= 3 ? label_screen_workspace(n, ldx, k) : 0;
+    const size_t sb = max_iter >= 3 && !std::getenv("SCEIG_NO_LABEL_SCREEN") ? label_screen_workspace(n, ldx, k) : 0;
     bool screen = sb > 0 && swork.try_alloc(sb);
     if (screen) HIP_TRY(launch_label_copy(x.p, ldx, d, n, k, swork.p, st));
     HIP_TRY(launch_fill_int32(labels, n, -1, 0, st));
@@ -2254,7 +2255,10 @@ struct KMeans {
       last_changes = 0;
       for (int s = 0; s < kChangeSlots; ++s) last_changes += hchanges.p[s * kChangeStride];
       // where the screen leaves much to the fp64 labelling it only comes on top
-      if (screen && hchanges.p[kChangeUndecided] > n / 4) screen = false;
+      if (screen && hchanges.p[kChangeUndecided] > n / 4)
+        screen = false;
+      else if (screen)
+        screened_labellings.fetch_add(1, std::memory_order_relaxed);
       if (last_changes == 0) {
         converged = 1;
         break;
@@ -2417,6 +2421,7 @@ int64_t sc_counter(int32_t which) {
   switch (which) {
     case SC_COUNTER_RESIDENT_FILTERS: return resident_launches.load(std::memory_order_relaxed);
     case SC_COUNTER_GROUPED_SEARCHES: return grouped_searches.load(std::memory_order_relaxed);
+    case SC_COUNTER_SCREENED_LABELLINGS: return screened_labellings.load(std::memory_order_relaxed);
     default: return -1;
   }
 }

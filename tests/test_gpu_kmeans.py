@@ -312,7 +312,7 @@ def test_labelling_in_parts_takes_the_lowest_index_on_ties(B):
                                         (40_010, 100, 100, "split"), (33_333, 128, 101, "blobs"), (30_001, 129, 104, "blobs"),
                                         (13_007, 300, 110, "split"), (200_001, 20, 100, "offset"), (60_000, 70, 96, "equal"),
                                         (60_001, 70, 96, "nan"), (2_100, 130, 1500, "blobs")])
-def test_screened_labelling_is_the_nearest_centre(B, n, d, k, kind):
+def test_screened_labelling_is_the_nearest_centre(B, n, d, k, kind, monkeypatch):
     gen = torch.Generator(device="cuda:0").manual_seed(n + d)
     blobs = k // 4 if kind == "split" else k
     cen = torch.randn((blobs, d), dtype=torch.float64, device="cuda:0", generator=gen)
@@ -327,7 +327,18 @@ def test_screened_labelling_is_the_nearest_centre(B, n, d, k, kind):
     init = x[torch.randperm(n - 100, device="cuda:0", generator=gen)[:k] + 100].clone()
     if kind == "equal":
         init[1] = init[0]
+    seen = B.sc_counter(B.SC_COUNTER_SCREENED_LABELLINGS)
     labels, centres, code, stats = B.sc_kmeans_lloyd(x, init, 3)
+    # no scale with a NaN; half of the points as near to two equal centres: the screen is given up after the first step
+    by_screen = 0 if kind in ("equal", "nan") else stats["iterations"]
+    assert B.sc_counter(B.SC_COUNTER_SCREENED_LABELLINGS) - seen == by_screen
+    # the same labels and centres as by the fp64 labelling alone
+    with monkeypatch.context() as m:
+        m.setenv("SCEIG_NO_LABEL_SCREEN", "1")
+        plain_labels, plain_centres, _, _ = B.sc_kmeans_lloyd(x, init, 3)
+    assert B.sc_counter(B.SC_COUNTER_SCREENED_LABELLINGS) - seen == by_screen
+    assert torch.equal(labels, plain_labels)
+    assert torch.equal(torch.nan_to_num(centres), torch.nan_to_num(plain_centres))
     # the labels are those of the last labelling step: its centres come out of a run one update shorter
     _, before, _, st2 = B.sc_kmeans_lloyd(x, init, 2)
     assert stats["iterations"] == 3 or stats["converged"]
