@@ -552,7 +552,9 @@ constexpr int kLargeBlock = 1272;
 // items of 4 columns, 19.5 in 8 or 16; 500,000 in 500 38 us in 8 and in 16; 212,000 in 234 13.8 us in 8).
 double sliced_entry_s(int cols) { return 8.0 * cols / 204e9; }
 constexpr double kSlicedStepS = 1.5e-6;
-// Making the sliced copy takes about 150 us, which a hundred filter steps have to bring in.
+// A hundred filter steps have to bring in the sliced copy.  Stated for 100,000 rows of 32 entries, where making it takes about 150
+// us; it grows with the entries (0.5 ms for 500,000 rows), but so does what a step gains by the form (100,000 rows 15 us,
+// 500,000 over 70), so that where the choice is close the copy is the small one.
 constexpr double kSlicedCopyS = 1.5e-6;
 
 double general_step_seconds(int64_t nnz, int b) { return 3e-6 + (double)nnz * 8.0 * b / 14.5e12; }

@@ -1276,8 +1276,7 @@ __device__ __forceinline__ double bcast_lane(double v, int l) {
 // sqrt(p) and its inverse, and quotients by it, for the factorizations below: one approximate inverse root (v_rsq_f64),
 // two Newton steps, then root, inverse and quotients each corrected by their own remainder, as a division does.  Half the
 // dependent operations of a square root and a division, and the inverse serves the whole row and the triangular inverse
-// (b = 16: 9.2 -> 7.7 us, b = 8 with the sum of the partial blocks 4.9 -> 4.0 us; b = 32, bound by the fetch of its code,
-// 38.7 -> 36.6 us).  p > 0 and normal: it has passed the drop test.
+// (a launch for b = 16: 9.2 -> 7.7 us; for b = 32, bound by the fetch of its code, 38.7 -> 36.6 us).  p > 0 and normal: it has passed the drop test.
 __device__ __forceinline__ void root_and_inverse(double p, double* root, double* inv) {
   double y = __builtin_amdgcn_rsq(p);
   const double h = 0.5 * p;

@@ -750,15 +750,16 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(2))) void s
   }
 }
 
-// tau[q] = v* - 2 e, v* = the (k+1)-th largest of the query's maxima, found bit by bit; clears the query's list.  A wave
-// per query.  bound[first query + q] = a squared distance that at least k others do not exceed: what the fp64 kernel
-// starts from if it comes to that (first query + q and bound's index: place and point of a grouped set).  tau = +inf (nothing is listed, the query falls back) where the point set has no
-// usable scale or far too many would be listed; the kLostSlots counters at `lost_count` count those between them (one counter for
-// all of 100,000 such queries took 1 ms).
-// filled classes: those of the parts of the query block's list where the points are grouped (see group_parts).
+// tau[q] = v* - 2 e, v* = the (k+1)-th largest maximum of query q0 + q, found bit by bit; clears the query's list.
+// bound[i] = a squared distance that at least k others do not exceed, from the query's point i: what the fp64 kernel starts from
+// if it comes to that.  i = q0 + q, or src[q0 + q] where the points are grouped; there only the classes that the parts of the
+// query block's list fill are looked at (group_parts).
+// A query is lost (tau = +inf: nothing is listed, the fp64 kernel takes it) in a point set without a usable scale and where
+// more than most_classes classes reach the cut, far too many for its list; the kLostSlots counters at `lost_count` count the
+// lost ones between them (one counter for all of 100,000 took 1 ms).
 // What depends on the point set alone is formed once a wave, which then takes `run` queries, up to kThresholdRun where there
-// are enough for every place of a wave on the chip (a wave a query, with the
-// square roots and the logarithm of the estimate in each, took 110 instead of 74 us for 100,000 queries and 208 classes).
+// are enough for every place of a wave on the chip (a wave a query, with the square roots and the logarithm of the estimate in
+// each, took 110 instead of 74 us for 100,000 queries and 208 classes).
 constexpr int kThresholdRun = 8;
 template <int NP>  // keys per lane: groups <= 64 NP
 __global__ __launch_bounds__(kT) void screen_threshold_kernel(const float* __restrict__ maxima, int groups, int k, int dp,

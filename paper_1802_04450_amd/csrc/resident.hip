@@ -621,7 +621,7 @@ __global__ __launch_bounds__(kRT) void cheb_resident_kernel(const int64_t* __res
     resident_item<4>(rowptr, col, val, x, y, ldy, b, d, alpha_first, alpha_rest, shift, row0, nr, col0, nx, smem, d32, rnd_key, use_rnd);
   else if (cl == 2)
     resident_item<2>(rowptr, col, val, x, y, ldy, b, d, alpha_first, alpha_rest, shift, row0, nr, col0, nx, smem, d32, rnd_key, use_rnd);
-  else {  // sliced form: the item's last word carries its first slice instead of a chunk count
+  else {  // sliced form: its first slot takes the chunk count's place, the last word is the block's number of extra rows
 #define SC_SLICED(CV, MAXSV)                                                                                             \
   resident_item_sliced<CV, MAXSV>(scol, sval, slice_base, slice_len, x, y, ldy, b, d, alpha_first, alpha_rest, shift,    \
                                   slice_first, row_extra, row0, nr, col0, nx, it[4], smem, rnd_key, use_rnd)
