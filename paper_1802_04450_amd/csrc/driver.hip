@@ -2087,10 +2087,10 @@ bool supported_block(int b) { return b == 1 || b == 2 || b == 4 || b == 8 || b =
 
 // The check phase's question is whether S has an eigenvalue above kappa (the k-th locked one plus tol) outside the
 // locked vectors.  It is answered from below: the phase's basis spans all T(S) F(S) q, F the start filter (Chebyshev of
-// degree d on [lo, a]), T any polynomial of degree steps - 1, q a random column.  Take T = the Chebyshev polynomial of
-// [-1, t] for some t between the largest Ritz value theta and kappa.  If such an eigenvalue existed, P = T F would be at
-// least P(kappa) on it (kappa > a) and at most max|F| on the spectrum below t (none lies below -1), and were its share of q larger
-// than sqrt(M) max|F| / P(kappa), M = (t + 1) / (t - theta) - 1, the Rayleigh quotient of P(S) q alone, hence the
+// degree d on [lo, a], a < kappa), T any polynomial of degree steps - 1, q a random column.  Take T = the Chebyshev
+// polynomial of [-1, t] for some t between the largest Ritz value theta and kappa.  If such an eigenvalue existed, P = T F
+// would be at least P(kappa) on it and at most max|F| on the spectrum below t (none lies below -1), and were its share of q
+// larger than sqrt(M) max|F| / P(kappa), M = (t + 1) / (t - theta) - 1, the Rayleigh quotient of P(S) q alone, hence the
 // largest Ritz value, would exceed theta.  A share below x has probability at most x sqrt(2 n) in one random column (the
 // entries are uniform in [-1, 1]; a unit combination of them has density at most 1/sqrt(2), Ball 1986, and |q| is at most
 // sqrt(n)) and that to the power b in all of them.
