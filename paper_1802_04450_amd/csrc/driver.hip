@@ -571,8 +571,11 @@ struct ItemSplit {
   std::vector<int32_t> blocks;  // the blocks that go in the sliced form, kSliceBlockInts each
   int64_t rest_row0 = 0, extra = 0, nslots = 0;
   size_t lds = 0;
-  double step_s = 0.0, sliced_entries = 0.0;
+  double step_s = 0.0, sliced_entries = 0.0, padded = 0.0;
 };
+
+// A sliced copy of more than this times its blocks' entries is not taken.
+constexpr double kMostPadding = 1.5;
 
 // Host side of plan_resident: starts[nblk + 1], counts[kBlockCounts nblk].  What holds for every split, the blocks whose
 // entries fit the registers, is looked at once; a split goes through the others (`open`).  (With all blocks in each of the six
@@ -590,25 +593,31 @@ class ItemPlanner {
       form_[t] = (uint8_t)shape;
       if (shape == 0) {
         open_.push_back(t);
+        open_large_ = open_large_ || nr > kLargeBlock;
       } else {
         last_fixed_ = t;
         fixed_items_ += b / (8 * shape);
         fixed_s_ += register_cost(t) * (b / (8 * shape));
+        longest_fixed_ = std::max(longest_fixed_, register_cost(t));
       }
     }
   }
 
   // The split with the shortest modelled step; false: there is none.  forced: the only width to look at, for tests (may be
-  // null).
-  bool best_split(int64_t n, double general_step_s, const char* forced, ItemSplit* best) const {
+  // null).  any: also a split that is not worth it (longer steps than the general product's, too much padding).
+  // What can be told before a split is made or its sliced copy begun is told first: a plan that came to nothing cost a filter
+  // call on 20,000 rows 22 us, on 50,000 rows in no order of length 76 us.
+  bool best_split(int64_t n, double general_step_s, const char* forced, bool any, ItemSplit* best) const {
     if (!large_last_) return false;  // what may be left out has to be the matrix's last rows
+    if (!any && std::max(longest_fixed_, fixed_s_ / 256.0) + 1e-6 >= general_step_s) return false;
     bool have = false;
     for (int widest = 16; widest >= 4; widest /= 2)
       for (int leave = 0; leave < 2; ++leave) {
-        if (open_.empty() && (widest < 16 || leave)) continue;  // all the same
+        if ((open_.empty() && widest < 16) || (!open_large_ && leave)) continue;  // all the same
         if (!open_.empty() && forced && (std::atoi(forced) != widest || leave)) continue;
         ItemSplit s;
         if (!split(n, widest, leave != 0, &s) || (fixed_items_ == 0 && s.sliced.empty())) continue;
+        if (!any && s.padded > kMostPadding * s.sliced_entries) continue;
         // the rows without items still take the general product, step by step, after the one launch of the items
         const double rest_share = (double)(n - s.rest_row0) / (double)n;
         s.step_s += (!s.blocks.empty() ? kSlicedStepS + kSlicedCopyS : 1e-6) +
@@ -690,6 +699,7 @@ class ItemPlanner {
         out->blocks.insert(out->blocks.end(), {starts_[t], nr, (int32_t)out->extra, x, c, (int32_t)first, piece});
         out->extra += x;
         out->sliced_entries += entries;
+        out->padded += counts[4];
         out->lds = std::max(out->lds, lds);
         const double cost = entries * sliced_entry_s(c);
         sum += cost * (b_ / c);
@@ -718,8 +728,8 @@ class ItemPlanner {
     for (const WorkItem& it : s.sliced)
       if (it.cost > least) large.push_back(it.cost);
     std::sort(large.begin(), large.end(), std::greater<double>());
-    std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
-    for (int q = 0; q < 256; ++q) busy.push(0.0);
+    if (large.size() <= 256) return large.empty() ? share : std::max(share, large[0]);  // one each
+    std::priority_queue<double, std::vector<double>, std::greater<double>> busy(std::greater<double>(), std::vector<double>(256, 0.0));
     double longest = share;
     for (const double cost : large) {
       const double at = busy.top() + cost;
@@ -733,13 +743,13 @@ class ItemPlanner {
   const int32_t *starts_, *counts_;
   int nblk_, b_;
   size_t lds_limit_;
-  bool no_sliced_, large_last_ = true;
+  bool no_sliced_, large_last_ = true, open_large_ = false;
   std::vector<uint8_t> form_;  // lanes of a group, 0: not in registers
   std::vector<int32_t> open_;  // the blocks without such a form
   int last_fixed_ = -1;
   size_t fixed_lds_ = 0;
   int64_t fixed_items_ = 0;
-  double fixed_s_ = 0.0;
+  double fixed_s_ = 0.0, longest_fixed_ = 0.0;
 };
 
 // Finds the diagonal blocks and their chunk counts on the device, sizes the items on the host.  A block goes, in this
@@ -784,14 +794,15 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   const double general_step_s = general_step_seconds(nnz, b);
   ItemPlanner planner(hs.data(), hx.data(), nblk, b, (size_t)lds_limit, no_sliced);
   ItemSplit best;
-  if (!planner.best_split(n, general_step_s, std::getenv("SCEIG_SLICED_COLUMNS"), &best)) return;
+  const bool forced = std::getenv("SCEIG_FORCE_RESIDENT") != nullptr;
+  if (!planner.best_split(n, general_step_s, std::getenv("SCEIG_SLICED_COLUMNS"), forced, &best)) return;
   const int64_t rest_row0 = best.rest_row0;
   const size_t lds_max = best.lds;
   plan->est_step_s = best.step_s;
   // loading and storing the iterates takes about ten more microseconds, which d steps share and a single product does not
   // (100,000 rows in 100 components: 25 us against 28 us by the general product; 30,000 in 20: 18 against 11.5)
   plan->single = best.step_s + 10e-6 < general_step_s;
-  if (!(plan->est_step_s < general_step_s) && !std::getenv("SCEIG_FORCE_RESIDENT")) return;
+  if (!(plan->est_step_s < general_step_s) && !forced) return;
   std::vector<WorkItem> items = planner.items(best);
   const int nslots = (int)best.nslots;
   if (nslots > 0) {
@@ -820,7 +831,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
     if (debug_on())
       std::fprintf(stderr, "[sceig] sliced copy: %d slots, %lld entries for %.0f of the matrix\n", nslots,
                    (long long)total, basis_entries);
-    if ((double)total > 1.5 * basis_entries && !std::getenv("SCEIG_FORCE_RESIDENT")) {
+    if ((double)total > kMostPadding * basis_entries && !forced) {
       plan->slice_base.release();
       plan->slice_len.release();
       plan->slice_first.release();
@@ -2122,7 +2133,7 @@ double resident_items_model(const int32_t* starts, const int32_t* counts, int nb
                             int64_t* nitems) {
   ItemPlanner planner(starts, counts, nblk, b, (size_t)lds_limit, false);
   ItemSplit best;
-  if (!planner.best_split(starts[nblk], general_step_seconds(nnz, b), nullptr, &best)) return -1.0;
+  if (!planner.best_split(starts[nblk], general_step_seconds(nnz, b), nullptr, false, &best)) return -1.0;
   *nitems = (int64_t)planner.items(best).size();
   return best.step_s;
 }

@@ -131,10 +131,10 @@ int resident_max_chunks(int cl);
 size_t diagonal_blocks_workspace(int64_t n);
 hipError_t diagonal_blocks(const int64_t* rowptr, const int32_t* col, int64_t n, void* work, size_t work_bytes,
                            int32_t* starts, int32_t* count, hipStream_t st);
-// extra[4 t], extra[4 t + 1], extra[4 t + 2] (device int32) = extra chunks of block t for chunks of 32 and of 16 entries, and
-// the extra rows of the sliced form in pieces of sliced_piece() entries; extra[4 t + 3] = the block's entries (at most
-// INT32_MAX)
-constexpr int kBlockCounts = 4;
+// extra[kBlockCounts t ..] (device int32) = extra chunks of block t for chunks of 32 and of 16 entries, the extra rows of the
+// sliced form in pieces of sliced_piece() entries, the block's entries, and the least that its rows' first pieces take in the
+// sliced form with their padding (both at most INT32_MAX)
+constexpr int kBlockCounts = 5;
 hipError_t launch_block_extra_chunks(const int64_t* rowptr, const int32_t* starts, int nblk, int64_t n, int32_t* extra,
                                      hipStream_t st);
 // y (n x b, leading dimension ldy >= b) = the recurrence applied to x (packed n x b): u_0 = x, u_1 = alpha_first (A u_0 - shift u_0),

@@ -867,8 +867,9 @@ __global__ __launch_bounds__(256) void slice_fill_kernel(const int64_t* __restri
   }
 }
 
-// extra[4 t], extra[4 t + 1], extra[4 t + 2] = chunks beyond the first, summed over the rows of diagonal block t, for chunks of
-// 32, 16 and kSliceLong entries, extra[4 t + 3] = its entries (INT32_MAX if more).  One wave per block.
+// counts of diagonal block t, from extra[kBlockCounts t] on: chunks beyond the first, summed over its rows, for chunks of 32, 16
+// and kSliceLong entries; its entries; what its rows' first kSliceLong entries take in slices of 16 rows, padding included (both
+// INT32_MAX if more).  One wave per block.
 __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* __restrict__ rowptr,
                                                                  const int32_t* __restrict__ starts, int nblk, int64_t n,
                                                                  int32_t* __restrict__ extra) {
@@ -877,8 +878,17 @@ __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* 
   if (t >= nblk) return;
   const int64_t r0 = starts[t], r1 = t + 1 < nblk ? (int64_t)starts[t + 1] : n;
   int x32 = 0, x16 = 0, xl = 0;
-  for (int64_t r = r0 + lane; r < r1; r += 64) {
-    const int len = (int)(rowptr[r + 1] - rowptr[r]);
+  int64_t padded = 0;  // of the lane's slices
+  for (int64_t first = r0; first < r1; first += 64) {  // uniform over the wave
+    const int64_t r = first + lane;
+    const int len = r < r1 ? (int)(rowptr[r + 1] - rowptr[r]) : 0;
+    int longest = len < kSliceLong ? len : kSliceLong;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) {
+      const int other = __shfl_xor(longest, o, 16);
+      longest = other > longest ? other : longest;
+    }
+    if ((lane & 15) == 0) padded += 16 * ((longest + 3) / 4 * 4);
     if (len > 32) x32 += (len + 31) / 32 - 1;
     if (len > 16) x16 += (len + 15) / 16 - 1;
     if (len > kSliceLong) xl += (len + kSliceLong - 1) / kSliceLong - 1;
@@ -888,6 +898,7 @@ __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* 
     x32 += __shfl_xor(x32, o, 64);
     x16 += __shfl_xor(x16, o, 64);
     xl += __shfl_xor(xl, o, 64);
+    padded += __shfl_xor(padded, o, 64);
   }
   if (lane == 0) {
     const int64_t entries = rowptr[r1] - rowptr[r0];
@@ -895,6 +906,7 @@ __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* 
     extra[kBlockCounts * t + 1] = x16;
     extra[kBlockCounts * t + 2] = xl;
     extra[kBlockCounts * t + 3] = entries < INT32_MAX ? (int32_t)entries : INT32_MAX;
+    extra[kBlockCounts * t + 4] = padded < INT32_MAX ? (int32_t)padded : INT32_MAX;
   }
 }
 

@@ -242,8 +242,9 @@ def test_items_of_many_blocks_are_planned_once(sliced):
     many, big = 500_000, 900
     rows = np.concatenate([np.full(many, 4), np.full(sliced, big)])
     starts = np.concatenate([[0], np.cumsum(rows)])
-    # chunks beyond the first of rows of 3 and of 40 entries, extra rows, entries
-    counts = np.concatenate([np.tile([0, 0, 0, 12], (many, 1)), np.tile([big, 2 * big, 0, 40 * big], (sliced, 1)).reshape(-1, 4)])
+    # chunks beyond the first of rows of 3 and of 40 entries, extra rows, entries, these with their padding
+    counts = np.concatenate([np.tile([0, 0, 0, 12, 64], (many, 1)),
+                             np.tile([big, 2 * big, 0, 40 * big, 41 * big], (sliced, 1)).reshape(-1, 5)])
     nnz = int(counts[:, 3].sum())
     step, items, took = _items_model(starts, counts, 16, nnz)
     share = (many * 12 * 128.0 / 150e9 + sliced * 40 * big * 128.0 / 204e9) / 256
@@ -256,9 +257,26 @@ def test_items_of_equal_blocks_share_the_compute_units():
     """512 equal blocks: two for each of the 256 compute units, in either register form."""
     for b in (16, 32):
         starts = np.arange(513) * 100
-        counts = np.tile([0, 0, 0, 1000], (512, 1))
+        counts = np.tile([0, 0, 0, 1000, 1100], (512, 1))
         step, items, _ = _items_model(starts, counts, b, 512_000)
         assert items == 512 and step == pytest.approx(2 * 1000 * 8.0 * b / 150e9 + 1e-6, rel=1e-12)
+
+
+def test_no_plan_is_made_that_will_not_be_taken():
+    """Sliced blocks whose padding is too much even in the narrowest slices, and blocks in registers that take longer than the
+    general product: known from the counts, before anything is laid out."""
+    starts = np.arange(101) * 900
+    counts = np.tile([900, 1800, 0, 40 * 900, 41 * 900], (100, 1))
+    step, items, _ = _items_model(starts, counts, 16, 100 * 40 * 900)
+    assert step > 0 and items >= 100
+    counts[:, 4] = 61 * 900
+    step, _, _ = _items_model(starts, counts, 16, 100 * 40 * 900)
+    assert step == -1.0
+    # five blocks of 600 rows, 15 entries a row: 8 us a step for each, 3.4 by the product
+    starts = np.arange(6) * 600
+    counts = np.tile([0, 0, 0, 9000, 9600], (5, 1))
+    step, _, _ = _items_model(starts, counts, 16, 5 * 9000)
+    assert step == -1.0
 
 
 def _chebyshev(y, degree, lo, hi):
