@@ -353,8 +353,9 @@ int sc_sym_eig_top(const double* a, int32_t n, int32_t count, double* w, double*
  * The library stages its own row-major copy of the points and never keeps a caller's pointer.  Device scratch beside that
  * copy: about 17 n bytes for the seeding, which takes 2 n d bytes more where it can have them; after that about
  * 4 n + 4 n k / 1,024 bytes (12 n and those of a radix sort beyond 1,024 clusters) and 16 k d + 2^22 for the iterations.
- * From n dp k of 4e8, dp = d rounded up to a multiple of four, and three iterations on these take 4 (n + k + 64) (d + 16) + 12 n + 2100 (d + 4) + 2^20 bytes more (a
- * reduced-precision copy that only screens the centres) where they can have them.
+ * From n dp k of 4e8 on, dp = d rounded up to a multiple of four, and where max_iter is large enough to bring in its cost
+ * (three at the least), these take 4 (n + k + 64) (d + 16) + 12 n + 2100 (d + 4) + 2^20 bytes more (a reduced-precision copy
+ * that only screens the centres) where they can have them.
  */
 typedef struct sc_kmeans_stats {
   int32_t iterations;   /* labelling steps done */

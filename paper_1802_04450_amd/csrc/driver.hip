@@ -2227,8 +2227,8 @@ struct KMeans {
     const size_t wb = kmeans_update_workspace(n, ldx, k), lwb = label_workspace(n, ldx, k);
     work.alloc(wb);
     if (lwb) lwork.alloc(lwb);
-    // the reduced copy of the points is worth its three launches from the third step on
-    const size_t sb = max_iter >= 3 && !std::getenv("SCEIG_NO_LABEL_SCREEN") ? label_screen_workspace(n, ldx, k) : 0;
+    const bool many = max_iter >= label_screen_steps(n, ldx, k) || std::getenv("SCEIG_FORCE_LABEL_SCREEN");
+    const size_t sb = many && !std::getenv("SCEIG_NO_LABEL_SCREEN") ? label_screen_workspace(n, ldx, k) : 0;
     bool screen = sb > 0 && swork.try_alloc(sb);
     if (screen) HIP_TRY(launch_label_copy(x.p, ldx, d, n, k, swork.p, st));
     HIP_TRY(launch_fill_int32(labels, n, -1, 0, st));

@@ -291,10 +291,12 @@ hipError_t launch_label(const double* x, int64_t ldx, int64_t n, const double* c
 hipError_t launch_label_listed(const double* x, int64_t ldx, int64_t n, const int32_t* rows, const int* listed,
                                const double* ct, int64_t ldc, int k, const double* cnorm, int32_t* label, int* changes,
                                hipStream_t st);
-// Labelling screened in bf16 (kmeans.hip): the same labels.  0 bytes where it does not pay.  launch_label_copy makes the
+// Labelling screened in bf16 (kmeans.hip): the same labels.  It pays from label_screen_steps labelling steps on (INT32_MAX:
+// never); 0 bytes where it is not made.  launch_label_copy makes the
 // reduced copy of the points, once; launch_label_screened does a labelling step and leaves the number of points that the
 // screen could not decide, which were labelled in fp64, at changes[kChangeUndecided].
 constexpr int kChangeUndecided = 1;
+int label_screen_steps(int64_t n, int64_t ldx, int k);
 size_t label_screen_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, hipStream_t st);
 hipError_t launch_label_screened(const double* x, int64_t ldx, int d, int64_t n, const double* c, const double* ct,

@@ -6,6 +6,8 @@
 // host (a counter-based generator); a draw is one distance pass that also leaves block sums and one single-workgroup
 // kernel that walks the sums level by level to the drawn point.
 #include <hip/hip_runtime.h>
+#include <algorithm>
+#include <cmath>
 #include <cstring>
 
 #include <rocprim/device/device_radix_sort.hpp>
@@ -1274,8 +1276,7 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
 
 namespace {
 
-// Where the fp64 product takes clearly more than the two launches of the screened form (n d k of 4e8: 33 us;
-// 50,000 x 64, 128 centres, 20 steps 2.63 -> 2.50 ms, 100,000 x 100, 100 centres 4.19 -> 3.25 ms).
+// Below, the fp64 product takes no more than the two launches of the screened form (4e8: 33 us).
 bool label_screened(int64_t n, int64_t ldx, int k) { return (double)n * (double)ldx * (double)k >= 4.0e8; }
 
 struct LabelScreen {
@@ -1310,6 +1311,34 @@ LabelScreen plan_label_screen(int64_t n, int64_t ldx, int k) {
 }
 
 }  // namespace
+
+// The reduced copy of the points costs about as much as a fp64 labelling, and a screened step saves a tenth to a half of one,
+// so the number of steps decides.  Fitted to 290 shapes (2,500 to 2,000,000 points of 2 to 2,000 normal coordinates, 16 to
+// 2,000 centres; us a step by the fp64 product, saved by the screen, and the copy): 100,000 x 100, 100 centres 115 / 30 / 90,
+// 500,000 x 100, 128 480 / 257 / 453, 1,000,000 x 8, 64 184 / 47 / 208, 65,000 x 64, 1,000 236 / 105 / 60, 200,000 x 500, 64
+// 541 / 163 / 747.  Never where a wave's chain over few tiles of points is what a step lasts (20,000 x 2,000, 64 centres 394 /
+// -116 / 397, 5,000 x 100, 1,000 60 / -30 / 63, 45,000 x 16, 1,000 88 / -4 / 38) or where there is next to nothing to
+// multiply (200,000 x 2, 512 156 / -11 / 73).  In the mean over the shapes 10 steps take 14 % less than by the product alone
+// (4 % with the screen always), 3 steps 6 % less (14 % more).
+int label_screen_steps(int64_t n, int64_t ldx, int k) {
+  const double w = (double)n * (double)ldx * (double)k, m = (double)n;
+  const double copy = 7.5e-6 * m * (double)((ldx + 15) / 16 * 16) + 1.3e-4 * m + 10.0;
+  double gain = 0.0;
+  if (ldx <= 128) {
+    const bool few = ldx >= 64 ? (n >= 45000 && k >= 128) || (n >= 30000 && k >= 256) || (n >= 20000 && k >= 1000 && ldx >= 100)
+                               : ldx >= 32 && n >= 45000 && k >= 1000;
+    if ((ldx < 8 && n < 500000) || (n < 65000 && !few)) return INT32_MAX;
+    gain = 3.5e-8 * w * std::min(1.0, ((double)ldx + 24.0) / 88.0) * (n < 65000 ? 0.5 : 1.0) - 2.0 +
+           4e-5 * std::max(0.0, m - 200000.0);
+  } else {
+    const bool few = (n >= 45000 && k >= 128) || (n >= 30000 && k >= 500 && ldx <= 512) || (n >= 20000 && k >= 1000 && ldx <= 320);
+    if (n < 65000 && !few) return INT32_MAX;
+    const double fill = std::min(1.0, m / 1e5);
+    gain = 2.3e-8 * w * (ldx <= 320 ? fill : k >= 256 ? fill * std::sqrt(fill) : fill * fill) - 4.0;
+  }
+  if (gain < 4.0) return INT32_MAX;
+  return std::max(3, (int)std::ceil(std::min(1.2 * copy / gain, 1e9)));
+}
 
 size_t label_screen_workspace(int64_t n, int64_t ldx, int k) {
   return label_screened(n, ldx, k) ? plan_label_screen(n, ldx, k).bytes : 0;

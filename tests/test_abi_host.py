@@ -253,6 +253,19 @@ def test_items_of_many_blocks_are_planned_once(sliced):
     assert took < 0.13, took
 
 
+@pytest.mark.parametrize("n,d,k,least,most", [
+    (100_000, 100, 100, 3, 5), (500_000, 100, 128, 3, 4), (65_000, 64, 1000, 3, 3), (1_000_000, 8, 64, 4, 12), (200_000, 20, 100, 6, 25),
+    (142_541, 500, 100, 3, 6), (20_000, 2000, 64, None, None), (5_000, 100, 1000, None, None), (40_000, 100, 100, None, None),
+    (45_000, 16, 1000, None, None), (200_000, 2, 512, None, None), (10_000, 500, 256, None, None)])
+def test_steps_that_bring_in_the_labelling_screen(n, d, k, least, most):
+    """Around the measured numbers of labelling steps after which the reduced copy of the points has paid; never where a step
+    by the screen takes longer than by the product."""
+    f = binding.lib()._ZN5sceig18label_screen_stepsElli
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
+    steps = f(n, (d + 3) // 4 * 4, k)
+    assert steps == 2 ** 31 - 1 if least is None else least <= steps <= most, steps
+
+
 def test_items_of_equal_blocks_share_the_compute_units():
     """512 equal blocks: two for each of the 256 compute units, in either register form."""
     for b in (16, 32):
