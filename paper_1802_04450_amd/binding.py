@@ -129,6 +129,7 @@ def lib() -> ctypes.CDLL:
 SC_COUNTER_RESIDENT_FILTERS = 0
 SC_COUNTER_GROUPED_SEARCHES = 1
 SC_COUNTER_SCREENED_LABELLINGS = 2
+SC_COUNTER_FP64_SEARCHES = 3
 
 
 def sc_counter(which: int) -> int:

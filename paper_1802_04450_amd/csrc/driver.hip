@@ -517,6 +517,7 @@ void enqueue_block_qr(double* basis, int64_t n, int64_t ld, int col, int b, doub
 
 std::atomic<int64_t> resident_launches{0};  // sc_counter(SC_COUNTER_RESIDENT_FILTERS)
 std::atomic<int64_t> grouped_searches{0};   // sc_counter(SC_COUNTER_GROUPED_SEARCHES)
+std::atomic<int64_t> fp64_searches{0};      // sc_counter(SC_COUNTER_FP64_SEARCHES)
 std::atomic<int64_t> screened_labellings{0};  // sc_counter(SC_COUNTER_SCREENED_LABELLINGS)
 
 // Plan of the LDS-resident Chebyshev filter (resident.hip) for one matrix and block width: the diagonal blocks of the
@@ -2434,6 +2435,7 @@ int64_t sc_counter(int32_t which) {
   switch (which) {
     case SC_COUNTER_RESIDENT_FILTERS: return resident_launches.load(std::memory_order_relaxed);
     case SC_COUNTER_GROUPED_SEARCHES: return grouped_searches.load(std::memory_order_relaxed);
+    case SC_COUNTER_FP64_SEARCHES: return fp64_searches.load(std::memory_order_relaxed);
     case SC_COUNTER_SCREENED_LABELLINGS: return screened_labellings.load(std::memory_order_relaxed);
     default: return -1;
   }
@@ -3176,6 +3178,7 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
         HIP_TRY(hipMemcpyAsync(left.p, ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
         if (*left.p > 0) {
+          fp64_searches.fetch_add(1, std::memory_order_relaxed);
           HIP_TRY(launch_knn_search(c->n, c->d, c->k, xp.p, tiles, *left.p, bound, c->idx, c->dist, c->st));
           HIP_TRY(hipStreamSynchronize(c->st));
         }

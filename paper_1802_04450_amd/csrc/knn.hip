@@ -850,12 +850,16 @@ __global__ __launch_bounds__(kT) void screen_threshold_kernel(const float* __res
   }
 }
 
+// grouped points: queries of a round whose lists of candidates did not come out right, for group_exact_kernel
+constexpr int kMostLost = 1024;
+
 // The k nearest of the listed candidates, by (exact squared distance, index).  A wave per query: a lane computes a
 // candidate's distance as the other kernels do, its rank is the number of listed candidates before it.
 __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restrict__ xp, int dp, int64_t q0, int64_t nq,
                                                          const int32_t* __restrict__ src, int k, int cap,
                                                          const int32_t* __restrict__ count,
                                                          const int32_t* __restrict__ list,
+                                                         int32_t* __restrict__ nlost, int32_t* __restrict__ lost,
                                                          int32_t* __restrict__ tile_flag, int32_t* __restrict__ tiles,
                                                          int32_t* __restrict__ ntiles, int32_t* __restrict__ idx_out,
                                                          double* __restrict__ dist_out) {
@@ -869,6 +873,13 @@ __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restric
   if (i < 0) return;
   const int found = count[q];
   if (found > cap || found < k) {
+    if (src && lane == 0) {
+      const int at = atomicAdd(nlost, 1);
+      if (at < kMostLost) {
+        lost[at] = (int32_t)q;
+        return;
+      }
+    }
     if (lane == 0 && atomicExch(&tile_flag[i / kMq], 1) == 0) tiles[atomicAdd(ntiles, 1)] = (int32_t)(i / kMq);
     return;
   }
@@ -955,7 +966,7 @@ struct GroupInfo {  // device
   float far;                 // squared distance to the pivot from which a point is a far one, in the screen's scale
   int32_t tiles;             // tiles of the grouped places
   int32_t nparts;            // parts of the lists
-  int32_t pad;
+  int32_t lost;              // queries that the ranking handed on (may exceed kMostLost: the others went to the fp64 kernel)
 };
 
 // entries of `parts` for the list of query block b, and the block's maxima cleared where parts will share them; by the
@@ -987,6 +998,7 @@ __global__ __launch_bounds__(kT) void group_init_kernel(int64_t n, int64_t place
     info->pairs = 0ull;
     info->tiles = 0;
     info->nparts = 0;
+    info->lost = 0;
   }
 }
 
@@ -1351,6 +1363,71 @@ __global__ __launch_bounds__(64) void group_window_kernel(GroupInfo* __restrict_
 __global__ void group_recount_kernel(GroupInfo* __restrict__ info) {
   info->pairs = 0ull;
   info->nparts = 0;
+  info->lost = 0;
+}
+
+// The queries that the ranking handed on, from the tiles of their block's list in fp64: what is not beyond the bound of the k-th
+// distance, ranked as there.  A workgroup per query.  Where the points are grouped a query's neighbours lie in few tiles and
+// share classes, and now and then one's list of candidates runs over; a handful of such queries through all points, one workgroup
+// per 64 of them, is what a search then lasted (62,000 normal points of 2 coordinates, 50 neighbours, 5.8 ms for 1.3 without
+// groups; 100,000 even ones of 3, 100 neighbours, 17.5 for 4.2).
+constexpr int kExactThreads = 512, kExactRoom = 4096;
+__global__ __launch_bounds__(kExactThreads) void group_exact_kernel(
+    const double* __restrict__ xp, int dp, const int32_t* __restrict__ src, int64_t q0, int qt, const int32_t* __restrict__ near,
+    const int32_t* __restrict__ near_count, int64_t near_stride, const double* __restrict__ bound, int k,
+    const GroupInfo* __restrict__ info, const int32_t* __restrict__ lost, int32_t* __restrict__ tile_flag,
+    int32_t* __restrict__ tiles, int32_t* __restrict__ ntiles, int32_t* __restrict__ idx_out, double* __restrict__ dist_out) {
+  __shared__ double dist[kExactRoom];
+  __shared__ int32_t idx[kExactRoom];
+  __shared__ int32_t kept;
+  const int nlost = info->lost < kMostLost ? info->lost : kMostLost;
+  for (int l = blockIdx.x; l < nlost; l += gridDim.x) {  // uniform over the workgroup
+    const int64_t q = lost[l], i = src[q0 + q], b = q / (32 * qt);
+    const double most = bound[i];
+    const int32_t* __restrict__ mine = near + b * near_stride;
+    const int64_t places = 32 * (int64_t)near_count[b];
+    const double2* __restrict__ xp2 = reinterpret_cast<const double2*>(xp);
+    const double2* __restrict__ qr = xp2 + i * (dp / 2);
+    if (threadIdx.x == 0) kept = 0;
+    __syncthreads();
+    for (int64_t e = threadIdx.x; e < places; e += kExactThreads) {
+      const int32_t j = src[32 * (int64_t)mine[e >> 5] + (e & 31)];
+      if (j < 0 || j == i) continue;
+      const double2* __restrict__ yr = xp2 + (int64_t)j * (dp / 2);
+      double ex = 0.0;
+#pragma unroll 4
+      for (int t = 0; t < dp / 2; ++t) {
+        const double2 qv = qr[t], yv = yr[t];
+        const double d0 = qv.x - yv.x;
+        ex = fma(d0, d0, ex);
+        const double d1 = qv.y - yv.y;
+        ex = fma(d1, d1, ex);
+      }
+      if (!(ex <= most)) continue;
+      const int at = atomicAdd(&kept, 1);
+      if (at < kExactRoom) {
+        dist[at] = ex;
+        idx[at] = j;
+      }
+    }
+    __syncthreads();
+    const int found = kept;
+    if (found > kExactRoom || found < k) {
+      if (threadIdx.x == 0 && atomicExch(&tile_flag[i / kMq], 1) == 0) tiles[atomicAdd(ntiles, 1)] = (int32_t)(i / kMq);
+    } else {
+      for (int c = threadIdx.x; c < found; c += kExactThreads) {
+        const double v = dist[c];
+        const int32_t id = idx[c];
+        int rank = 0;
+        for (int o = 0; o < found; ++o) rank += (dist[o] < v || (dist[o] == v && idx[o] < id)) ? 1 : 0;
+        if (rank < k) {
+          idx_out[i * k + rank] = id;
+          dist_out[i * k + rank] = sqrt(v);
+        }
+      }
+    }
+    __syncthreads();  // before the next query's candidates
+  }
 }
 
 // reach[t] = the largest bound of a k-th distance among the points of tile t, in the screen's scale.  A half-wave per tile.
@@ -1629,7 +1706,7 @@ struct GroupPlan {
   size_t off_pb = 0, off_half = 0, off_norm = 0, off_phalf = 0, off_pnorm = 0, off_src = 0, off_pivot = 0, off_size = 0,
          off_base = 0, off_order = 0, off_key = 0, off_near2 = 0, off_within = 0, off_cell = 0, off_seat = 0, off_info = 0, off_centre = 0, off_radius = 0,
          off_reach = 0, off_idle = 0, off_near = 0, off_near_count = 0, off_parts = 0, off_maxima = 0, off_tau = 0, off_count = 0,
-         off_list = 0, bytes = 0;
+         off_list = 0, off_lost = 0, bytes = 0;
 };
 
 GroupPlan plan_group(int64_t n, int d, int k) {
@@ -1684,6 +1761,7 @@ GroupPlan plan_group(int64_t n, int d, int k) {
   g.off_tau = place((size_t)g.chunk * 32 * 4);
   g.off_count = place((size_t)g.chunk * 32 * 4);
   g.off_list = place((size_t)g.chunk * 32 * p.cap * 4);
+  g.off_lost = place((size_t)kMostLost * 4);
   g.bytes = off;
   g.use = true;
   return g;
@@ -1928,8 +2006,12 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     for (int q = 0; q < kLostSlots; ++q) lost += host[q * kLostStride];
     lost_before += lost;
     if (lost <= nq / 2) screen(true, t0, nt, nparts);
+    int32_t* gone = reinterpret_cast<int32_t*>(gw + g.off_lost);
     hipLaunchKernelGGL(screen_rank_kernel, dim3(blocks(nq * 64)), dim3(kT), rank_lds, st, xp, dp, q0, nq, src, k, p.cap, count,
-                       list, flag, *tiles, *ntiles, idx_out, dist_out);
+                       list, &info->lost, gone, flag, *tiles, *ntiles, idx_out, dist_out);
+    if (src)
+      hipLaunchKernelGGL(group_exact_kernel, dim3(256), dim3(kExactThreads), 0, st, xp, dp, src, q0, qt, near, near_count,
+                         near_stride, *bound, k, info, gone, flag, *tiles, *ntiles, idx_out, dist_out);
   }
   return hipGetLastError();
 }

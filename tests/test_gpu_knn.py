@@ -279,6 +279,26 @@ def test_grouped_search(B, n, d, k, kind, monkeypatch):
     _sampled(x, k, np.concatenate([[0, 99, 100, 600, n - 1], rng.integers(0, n, 120)]), idx, dist)
 
 
+# many neighbours in few tiles: the lists of candidates of some queries run over
+@pytest.mark.parametrize("n,d,k,kind", [(62_001, 2, 50, "normal"), (100_003, 2, 50, "normal"), (100_000, 3, 100, "uniform"),
+                                        (62_000, 10, 100, "tight"), (30_011, 70, 60, "tight"), (62_500, 2, 200, "uniform")])
+def test_grouped_search_whose_lists_run_over(B, n, d, k, kind, monkeypatch):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + d)
+    x = torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    if kind == "uniform":
+        x = torch.rand((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    elif kind == "tight":             # clusters of very different widths
+        at = torch.arange(n, device="cuda:0") % 40
+        x = x * (10.0 ** (-2.0 * torch.rand(40, dtype=torch.float64, device="cuda:0", generator=gen)))[at, None]
+        x += 8.0 * torch.randn((40, d), dtype=torch.float64, device="cuda:0", generator=gen)[at]
+    fp64 = B.sc_counter(B.SC_COUNTER_FP64_SEARCHES)
+    idx, dist = B.sc_knn_search(x, k)
+    assert B.sc_counter(B.SC_COUNTER_FP64_SEARCHES) == fp64
+    monkeypatch.setenv("SCEIG_NO_GROUPS", "1")
+    plain_idx, plain_dist = B.sc_knn_search(x, k)
+    assert torch.equal(idx, plain_idx) and torch.equal(dist, plain_dist)
+
+
 @pytest.mark.parametrize("n,d,kind,grouped", [(90_000, 4, "normal", 0), (66_000, 5, "curve", 0), (66_000, 8, "curve", 0),
                                               (66_000, 6, "uniform", 0), (66_000, 3, "uniform", 1), (66_000, 2, "normal", 1),
                                               (66_000, 10, "blobs", 1), (45_000, 32, "blobs", 1), (45_000, 32, "normal", 0)])
