@@ -606,24 +606,23 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(2))) void s
 
   u4 next[NL];
   float hnext = 0.0f;
-  // the tiles of the chunk after the next one are looked up a chunk ahead
+  // LISTED: the tiles of the chunk after the next one are looked up a chunk ahead (kept in registers without a list, too, they
+  // cost 3 to 6 % of a pass at 128 coordinates)
   int64_t at[NL], hat = 0;
+  auto nth = [&](int64_t chunk, int of) __attribute__((always_inline)) -> int64_t {
+    const int64_t j = chunk * CT + of;
+    return tile_of(j < nj ? j : nj - 1);  // the last tile again: skipped below
+  };
   auto look_up = [&](int64_t chunk) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < NL; ++u) {
-      const int64_t j = chunk * CT + (tid + u * kMt) / PT;
-      at[u] = tile_of(j < nj ? j : nj - 1);  // the last tile again: skipped below
-    }
-    if (tid < CT * 32) {
-      const int64_t j = chunk * CT + tid / 32;
-      hat = tile_of(j < nj ? j : nj - 1);
-    }
+    for (int u = 0; u < NL; ++u) at[u] = nth(chunk, (tid + u * kMt) / PT);
+    if (tid < CT * 32) hat = nth(chunk, tid / 32);
   };
   auto request = [&](int64_t chunk) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < NL; ++u) next[u] = xb[at[u] * PT + (tid + u * kMt) % PT];
-    if (tid < CT * 32) hnext = half[hat * 32 + tid % 32];
-    if (!LISTED || chunk + 1 < nchunk) look_up(chunk + 1);
+    for (int u = 0; u < NL; ++u) next[u] = xb[(LISTED ? at[u] : nth(chunk, (tid + u * kMt) / PT)) * PT + (tid + u * kMt) % PT];
+    if (tid < CT * 32) hnext = half[(LISTED ? hat : nth(chunk, tid / 32)) * 32 + tid % 32];
+    if (LISTED && chunk + 1 < nchunk) look_up(chunk + 1);
   };
   auto park = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
@@ -646,7 +645,7 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(2))) void s
     queued = 0;
   };
 
-  look_up(0);
+  if (LISTED) look_up(0);
   request(0);
   park(0);
   __syncthreads();
@@ -1071,6 +1070,7 @@ __device__ __forceinline__ void pivot_distances(const double2* const (&q)[kKeyPi
                                                 double (&d2)[kKeyPivots]) {
 #pragma unroll
   for (int p = 0; p < kKeyPivots; ++p) d2[p] = 0.0;
+#pragma unroll 4
   for (int t = 0; t < pairs; ++t) {
     const double2 b = y[t];
 #pragma unroll
