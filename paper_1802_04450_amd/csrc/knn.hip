@@ -954,8 +954,15 @@ constexpr int kGroupMaxCells = 16384;  // 16 bits in the keys
 constexpr int kGroupAhead = 24;
 constexpr int kFarCells = 64;
 constexpr double kGroupFar = 4.0;
-// Share of the pivots within four times the distance to the nearest one up to which the lists are made.
-double group_within(int dpb) { return dpb <= 16 ? 0.105 : 0.25; }
+// Share of the pivots within four times the distance to the nearest one up to which the lists are made.  Up to 16 coordinates
+// smaller sets have less to save and more neighbours need more tiles (points without clusters; share, plain -> grouped: 62,000
+// points, 10 neighbours 0.053 948 -> 778 us, 0.076 920 -> 1,096; 80,000 0.051 1,354 -> 1,326; 100,000 0.093 1,957 -> 1,984;
+// 140,000 0.064 3,573 -> 2,838; 50 neighbours, 62,000 0.053 1,265 -> 1,324, 80,000 0.051 1,798 -> 2,087, 100,000 0.047 2,536 ->
+// 2,579, 140,000 0.035 4,442 -> 3,517, 0.064 4,457 -> 4,838).
+double group_within(int64_t n, int dpb, int k) {
+  if (dpb > 16) return 0.25;
+  return 0.095 * std::min(1.0, (double)n / 1e5) * std::min(1.0, std::max(0.5, std::pow(10.0 / k, 0.4)));
+}
 // share of the plain passes' tile pairs up to which the lists are taken
 double group_most(int dpb) { return dpb <= 16 ? 0.25 : dpb <= 32 ? 0.38 : 0.62; }
 
@@ -1904,7 +1911,7 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     GroupInfo got;
     e = read_info(&got);
     if (e != hipSuccess) return e;
-    grouped = got.within < group_within(p.dpb);  // a NaN is no
+    grouped = got.within < group_within(n, p.dpb, k);  // a NaN is no
   }
   if (grouped) {
     u4* gxb = reinterpret_cast<u4*>(gw);

@@ -301,7 +301,7 @@ def test_grouped_search_whose_lists_run_over(B, n, d, k, kind, monkeypatch):
 
 
 @pytest.mark.parametrize("n,d,kind,grouped", [(90_000, 4, "normal", 0), (66_000, 5, "curve", 0), (66_000, 8, "curve", 0),
-                                              (66_000, 6, "uniform", 0), (66_000, 3, "uniform", 1), (66_000, 2, "normal", 1),
+                                              (66_000, 6, "uniform", 0), (62_000, 3, "normal", 0), (66_000, 3, "uniform", 1), (66_000, 2, "normal", 1),
                                               (66_000, 10, "blobs", 1), (45_000, 32, "blobs", 1), (45_000, 32, "normal", 0)])
 def test_points_are_grouped_where_it_pays(B, n, d, kind, grouped):
     """Without clusters in four dimensions and more the lists of the groups keep a third of the pairs and more, at several times
