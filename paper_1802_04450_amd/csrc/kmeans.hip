@@ -512,6 +512,29 @@ __global__ __launch_bounds__(kSelectThreads) void seed_select_kernel(const doubl
   if (threadIdx.x == 0) *chosen = (int32_t)at;
 }
 
+// What lane `lane` of kExactLanes adds to the squared distance of two rows of d doubles: its coordinates in order, E of either row
+// on their way before the first is used.  (One after the other they were what a draw lasted: 100,000 x 100, 100 draws 1,520 ->
+// 1,335 us; rows like those of an embedding, most workgroups with a point to compute, 3,220 -> 2,095.)
+template <int E>
+__device__ __forceinline__ double lane_square(const double* __restrict__ x, const double* __restrict__ y, int d, int lane) {
+  double acc = 0.0;
+  for (int base = lane; base - lane < d; base += E * kExactLanes) {
+    double a[E], b[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int t = base + e * kExactLanes < d ? base + e * kExactLanes : 0;
+      a[e] = x[t];
+      b[e] = y[t];
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const double diff = base + e * kExactLanes < d ? a[e] - b[e] : 0.0;
+      acc += diff * diff;
+    }
+  }
+  return acc;
+}
+
 // The pass for the centre *centre (DRAW false), or for the centre that this draw itself takes from the distances before it
 // (DRAW true; every workgroup finds it for itself from the block sums, workgroup 0 writes it down): dist2 and bsum go from
 // one buffer to the other.
@@ -625,11 +648,11 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
     const int count = ntodo;
     for (int s = group; s < count; s += kT / kExactLanes) {  // uniform over the point's lanes
       const int pt = todo[s];
-      double acc2 = 0.0;
-      for (int t = lane; t < d; t += kExactLanes) {
-        const double diff = x[(i0 + pt) * ldx + t] - x[c * ldx + t];
-        acc2 += diff * diff;
-      }
+      const double *xi = x + (i0 + pt) * ldx, *xc = x + c * ldx;
+      double acc2 = d <= kExactLanes       ? lane_square<1>(xi, xc, d, lane)
+                    : d <= 2 * kExactLanes ? lane_square<2>(xi, xc, d, lane)
+                    : d <= 4 * kExactLanes ? lane_square<4>(xi, xc, d, lane)
+                                           : lane_square<8>(xi, xc, d, lane);
 #pragma unroll
       for (int o = kExactLanes / 2; o > 0; o >>= 1) acc2 += __shfl_xor(acc2, o, kExactLanes);
       if (lane == 0 && acc2 < pts[pt]) pts[pt] = acc2;

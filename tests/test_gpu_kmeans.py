@@ -199,7 +199,10 @@ def test_update_over_its_ranges(B, n, d, k):
                                         # around the numbers of blocks from which two go to a workgroup and the draw moves
                                         # out, an odd number of them, a last block of one point; the most coordinates
                                         (65409, 105, 32, "blobs"), (65473, 112, 33, "blobs"), (65537, 113, 32, "blobs"),
-                                        (115137, 40, 32, "offset"), (115201, 40, 34, "equal"), (65600, 64, 33, 1e20)])
+                                        (115137, 40, 32, "offset"), (115201, 40, 34, "equal"), (65600, 64, 33, 1e20),
+                                        # few and many coordinates: one to several batches of a row's loads
+                                        (270_001, 16, 32, "blobs"), (250_003, 17, 33, "offset"), (130_001, 31, 32, "equal"),
+                                        (31_000, 130, 32, "blobs"), (9_001, 500, 33, "offset")])
 def test_screened_seeding_equals_plain_distances(B, n, d, k, kind):
     x = _blobs(n, d, 25, seed=n, spread=0.3)
     if kind == "offset":
