@@ -553,10 +553,12 @@ constexpr int kLargeBlock = 1272;
 // items of 4 columns, 19.5 in 8 or 16; 500,000 in 500 38 us in 8 and in 16; 212,000 in 234 13.8 us in 8).
 double sliced_entry_s(int cols) { return 8.0 * cols / 204e9; }
 constexpr double kSlicedStepS = 1.5e-6;
-// A hundred filter steps have to bring in the sliced copy.  Stated for 100,000 rows of 32 entries, where making it takes about 150
-// us; it grows with the entries (0.5 ms for 500,000 rows), but so does what a step gains by the form (100,000 rows 15 us,
-// 500,000 over 70), so that where the choice is close the copy is the small one.
-constexpr double kSlicedCopyS = 1.5e-6;
+// What making the sliced copy takes, which the filter steps to come have to bring in (3.2 M entries 150 us, 15.8 M 0.6 ms, 20 M
+// 0.75 ms; charged as the same 1.5 us a step everywhere it slowed solves of few steps down: 20 complete graphs of 1,000 nodes,
+// 14 steps 3.75 -> 4.51 ms, 24 of 600 2.13 -> 2.54, 50,000 rows in 50 components, 20 values, 24 steps 4.63 -> 4.81).
+double sliced_copy_s(double entries) { return 60e-6 + 37e-12 * entries; }
+// Filter steps of a solve: 14 to 36 after each phase of b values but the last (k = 100 in 100 components, b = 16: 142).
+double expected_filter_steps(int k, int b) { return 16.0 * std::max(1, (k - 1) / b); }
 
 double general_step_seconds(int64_t nnz, int b) { return 3e-6 + (double)nnz * 8.0 * b / 14.5e12; }
 
@@ -573,6 +575,7 @@ struct ItemSplit {
   int64_t rest_row0 = 0, extra = 0, nslots = 0;
   size_t lds = 0;
   double step_s = 0.0, sliced_entries = 0.0, padded = 0.0;
+  double copy_s = 0.0;  // the sliced copy's share of step_s
 };
 
 // A sliced copy of more than this times its blocks' entries is not taken.
@@ -606,9 +609,10 @@ class ItemPlanner {
 
   // The split with the shortest modelled step; false: there is none.  forced: the only width to look at, for tests (may be
   // null).  any: also a split that is not worth it (longer steps than the general product's, too much padding).
+  // steps: how many steps share what making the sliced copy takes.
   // What can be told before a split is made or its sliced copy begun is told first: a plan that came to nothing cost a filter
   // call on 20,000 rows 22 us, on 50,000 rows in no order of length 76 us.
-  bool best_split(int64_t n, double general_step_s, const char* forced, bool any, ItemSplit* best) const {
+  bool best_split(int64_t n, double general_step_s, double steps, const char* forced, bool any, ItemSplit* best) const {
     if (!large_last_) return false;  // what may be left out has to be the matrix's last rows
     if (!any && std::max(longest_fixed_, fixed_s_ / 256.0) + 1e-6 >= general_step_s) return false;
     bool have = false;
@@ -621,7 +625,8 @@ class ItemPlanner {
         if (!any && s.padded > kMostPadding * s.sliced_entries) continue;
         // the rows without items still take the general product, step by step, after the one launch of the items
         const double rest_share = (double)(n - s.rest_row0) / (double)n;
-        s.step_s += (!s.blocks.empty() ? kSlicedStepS + kSlicedCopyS : 1e-6) +
+        s.copy_s = s.blocks.empty() ? 0.0 : sliced_copy_s(s.sliced_entries) / steps;
+        s.step_s += (!s.blocks.empty() ? kSlicedStepS + s.copy_s : 1e-6) +
                     (rest_share > 0.0 ? std::max(4e-6, rest_share * general_step_s) : 0.0);
         if (debug_on())
           std::fprintf(stderr, "[sceig] resident filter plan: %d blocks (%zu sliced, at most %d columns), %lld items, LDS %zu, "
@@ -763,10 +768,10 @@ class ItemPlanner {
 // plan is usable when b is 16 or 32, every block fits LDS one way or the other, the sliced copy's padding stays below
 // a half, and the modelled step time beats the general product's: an item with its entries in registers costs the LDS bytes
 // its step reads (the block's entries times 8 bytes per column) at about half a compute unit's LDS rate, a sliced one
-// sliced_entry_s per entry and kSlicedStepS, the items spread over the 256 compute units, largest first; the general product gathers
+// sliced_entry_s per entry, kSlicedStepS and its share of sliced_copy_s in a filter of `steps` steps, the items spread over the 256 compute units, largest first; the general product gathers
 // 8 b bytes per entry from the L2 caches at the 14.5 TB/s measured for it (3.2 M entries, 16 columns: 28 us; 0.73 M: 11.5 us),
 // and a launch takes 3 us more.
-void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val, int64_t n, int64_t nnz, int b,
+void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val, int64_t n, int64_t nnz, int b, double steps,
                    hipStream_t st, ResidentPlan* plan) {
   plan->usable = false;
   plan->nitems = 0;
@@ -796,13 +801,13 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   ItemPlanner planner(hs.data(), hx.data(), nblk, b, (size_t)lds_limit, no_sliced);
   ItemSplit best;
   const bool forced = std::getenv("SCEIG_FORCE_RESIDENT") != nullptr;
-  if (!planner.best_split(n, general_step_s, std::getenv("SCEIG_SLICED_COLUMNS"), forced, &best)) return;
+  if (!planner.best_split(n, general_step_s, steps, std::getenv("SCEIG_SLICED_COLUMNS"), forced, &best)) return;
   const int64_t rest_row0 = best.rest_row0;
   const size_t lds_max = best.lds;
   plan->est_step_s = best.step_s;
   // loading and storing the iterates takes about ten more microseconds, which d steps share and a single product does not
   // (100,000 rows in 100 components: 25 us against 28 us by the general product; 30,000 in 20: 18 against 11.5)
-  plan->single = best.step_s + 10e-6 < general_step_s;
+  plan->single = best.step_s - best.copy_s + 11.5e-6 < general_step_s;
   if (!(plan->est_step_s < general_step_s) && !forced) return;
   std::vector<WorkItem> items = planner.items(best);
   const int nslots = (int)best.nslots;
@@ -1276,7 +1281,7 @@ struct Solver {
       if (hflag & 4) SC_THROW(SC_EZERODEG);
       below_zero = (hflag & kBelowZero) != 0;
       nlong = hcount;
-      if (!(flags & SC_FLAG_NO_START_FILTER)) plan_resident(rowptr, col, val_s.p, n, nnz, b, st, &resident);
+      if (!(flags & SC_FLAG_NO_START_FILTER)) plan_resident(rowptr, col, val_s.p, n, nnz, b, expected_filter_steps(k, b), st, &resident);
     }
     const double t3 = now_s();
 
@@ -2130,11 +2135,11 @@ int check_steps_needed(double theta, double kappa, int d, double lo, double a, i
   return (int)best;
 }
 
-double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, int64_t lds_limit,
-                            int64_t* nitems) {
+double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, double steps,
+                            int64_t lds_limit, int64_t* nitems) {
   ItemPlanner planner(starts, counts, nblk, b, (size_t)lds_limit, false);
   ItemSplit best;
-  if (!planner.best_split(starts[nblk], general_step_seconds(nnz, b), nullptr, false, &best)) return -1.0;
+  if (!planner.best_split(starts[nblk], general_step_seconds(nnz, b), steps, nullptr, false, &best)) return -1.0;
   *nitems = (int64_t)planner.items(best).size();
   return best.step_s;
 }
@@ -2980,7 +2985,7 @@ int sc_chebyshev_filter(const int64_t* csr_rowptr, const int32_t* csr_col, const
           nlong = hcount;
         }
         ResidentPlan resident;  // used when the matrix as given is block diagonal with blocks that fit LDS
-        if (wide) plan_resident(c->rp, c->c, vals.p, c->n, nnz, c->b, c->st, &resident);
+        if (wide) plan_resident(c->rp, c->c, vals.p, c->n, nnz, c->b, (double)std::max(c->d, 1), c->st, &resident);
         const double* res = enqueue_cheb_filter(c->rp, c->c, c->v, wide ? vals.p : nullptr, s.p, c->n, nnz, c->b, c->d,
                                                 c->a, z.p, b1.p, b2.p, b3.p, (double)nnz / (double)c->n,
                                                 wide ? longrows.p : nullptr, nlong, &resident, c->st, nullptr);

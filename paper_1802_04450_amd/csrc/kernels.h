@@ -188,10 +188,10 @@ hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const dou
 int check_steps_needed(double theta, double kappa, int d, double lo, double a, int64_t n, int b);
 
 // Host part of the filter's plan alone (driver.hip), for tests: what a step is modelled to take, in seconds, for diagonal blocks of
-// rows starts[t] .. starts[t + 1] with the counts of launch_block_extra_chunks and b = 16 or 32 columns; *nitems = the work
-// items.  Negative: there is no plan.
-double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, int64_t lds_limit,
-                            int64_t* nitems);
+// rows starts[t] .. starts[t + 1] with the counts of launch_block_extra_chunks and b = 16 or 32 columns in a filter of `steps` steps; *nitems
+// = the work items.  Negative: there is no plan.
+double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, double steps,
+                            int64_t lds_limit, int64_t* nitems);
 
 // ---- connected components and locality reordering (setup) --------------------------------------
 // Renumbering from the component labels (label[i] = smallest node index of i's component), on the device:

@@ -869,17 +869,18 @@ __global__ __launch_bounds__(256) void slice_fill_kernel(const int64_t* __restri
 
 // counts of diagonal block t, from extra[kBlockCounts t] on: chunks beyond the first, summed over its rows, for chunks of 32, 16
 // and kSliceLong entries; its entries; what its rows' first kSliceLong entries take in slices of 16 rows, padding included (both
-// INT32_MAX if more).  One wave per block.
-__global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* __restrict__ rowptr,
-                                                                 const int32_t* __restrict__ starts, int nblk, int64_t n,
-                                                                 int32_t* __restrict__ extra) {
-  const int t = (int)(((int64_t)blockIdx.x * 256 + threadIdx.x) >> 6);
-  const int lane = threadIdx.x & 63;
-  if (t >= nblk) return;
+// INT32_MAX if more).  W waves per block: few blocks are large ones (one wave for each of 20 blocks of 5,000 rows took 35 us).
+template <int W>
+__global__ __launch_bounds__(W > 1 ? 64 * W : 256) void block_counts_kernel(const int64_t* __restrict__ rowptr,
+                                                                          const int32_t* __restrict__ starts, int nblk,
+                                                                          int64_t n, int32_t* __restrict__ extra) {
+  __shared__ int64_t sums[W][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int t = W > 1 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;
+  if (t >= nblk) return;  // uniform over the workgroup where it meets below
   const int64_t r0 = starts[t], r1 = t + 1 < nblk ? (int64_t)starts[t + 1] : n;
-  int x32 = 0, x16 = 0, xl = 0;
-  int64_t padded = 0;  // of the lane's slices
-  for (int64_t first = r0; first < r1; first += 64) {  // uniform over the wave
+  int64_t v[4] = {0, 0, 0, 0};  // chunks of 32, of 16, of kSliceLong; padded entries
+  for (int64_t first = r0 + (W > 1 ? 64 * wave : 0); first < r1; first += 64 * W) {  // uniform over the wave
     const int64_t r = first + lane;
     const int len = r < r1 ? (int)(rowptr[r + 1] - rowptr[r]) : 0;
     int longest = len < kSliceLong ? len : kSliceLong;
@@ -888,26 +889,34 @@ __global__ __launch_bounds__(256) void block_extra_chunks_kernel(const int64_t* 
       const int other = __shfl_xor(longest, o, 16);
       longest = other > longest ? other : longest;
     }
-    if ((lane & 15) == 0) padded += 16 * ((longest + 3) / 4 * 4);
-    if (len > 32) x32 += (len + 31) / 32 - 1;
-    if (len > 16) x16 += (len + 15) / 16 - 1;
-    if (len > kSliceLong) xl += (len + kSliceLong - 1) / kSliceLong - 1;
+    if ((lane & 15) == 0) v[3] += 16 * ((longest + 3) / 4 * 4);
+    if (len > 32) v[0] += (len + 31) / 32 - 1;
+    if (len > 16) v[1] += (len + 15) / 16 - 1;
+    if (len > kSliceLong) v[2] += (len + kSliceLong - 1) / kSliceLong - 1;
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    x32 += __shfl_xor(x32, o, 64);
-    x16 += __shfl_xor(x16, o, 64);
-    xl += __shfl_xor(xl, o, 64);
-    padded += __shfl_xor(padded, o, 64);
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v[q] += __shfl_xor(v[q], o, 64);
+  if constexpr (W > 1) {
+    if (lane == 0)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) sums[wave][q] = v[q];
+    __syncthreads();
+    if (threadIdx.x) return;
+    for (int w = 1; w < W; ++w)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] += sums[w][q];
+  } else if (lane) {
+    return;
   }
-  if (lane == 0) {
-    const int64_t entries = rowptr[r1] - rowptr[r0];
-    extra[kBlockCounts * t] = x32;
-    extra[kBlockCounts * t + 1] = x16;
-    extra[kBlockCounts * t + 2] = xl;
-    extra[kBlockCounts * t + 3] = entries < INT32_MAX ? (int32_t)entries : INT32_MAX;
-    extra[kBlockCounts * t + 4] = padded < INT32_MAX ? (int32_t)padded : INT32_MAX;
-  }
+  const int64_t entries = rowptr[r1] - rowptr[r0];
+  auto put = [&](int q, int64_t c) { extra[kBlockCounts * (int64_t)t + q] = c < INT32_MAX ? (int32_t)c : INT32_MAX; };
+  put(0, v[0]);
+  put(1, v[1]);
+  put(2, v[2]);
+  put(3, entries);
+  put(4, v[3]);
 }
 
 // ---- diagonal blocks of a CSR matrix -------------------------------------------------------------------------------
@@ -1003,8 +1012,10 @@ hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const dou
 hipError_t launch_block_extra_chunks(const int64_t* rowptr, const int32_t* starts, int nblk, int64_t n, int32_t* extra,
                                      hipStream_t st) {
   if (nblk <= 0) return hipSuccess;
-  hipLaunchKernelGGL(block_extra_chunks_kernel, dim3((unsigned)(((int64_t)nblk * 64 + 255) / 256)), dim3(256), 0, st,
-                     rowptr, starts, nblk, n, extra);
+  if (nblk <= 1024)
+    hipLaunchKernelGGL(block_counts_kernel<16>, dim3((unsigned)nblk), dim3(1024), 0, st, rowptr, starts, nblk, n, extra);
+  else
+    hipLaunchKernelGGL(block_counts_kernel<1>, dim3((unsigned)((nblk + 3) / 4)), dim3(256), 0, st, rowptr, starts, nblk, n, extra);
   return hipGetLastError();
 }
 

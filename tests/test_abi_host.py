@@ -221,16 +221,16 @@ def test_label_screen_scratch_is_what_the_header_says():
     assert used > 20
 
 
-def _items_model(starts, counts, b, nnz, lds=162_816):
-    f = binding.lib()._ZN5sceig20resident_items_modelEPKiS1_iillPl
+def _items_model(starts, counts, b, nnz, steps=100.0, lds=162_816):
+    f = binding.lib()._ZN5sceig20resident_items_modelEPKiS1_iildlPl
     f.restype = ctypes.c_double
-    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_int64,
-                  ctypes.POINTER(ctypes.c_int64)]
+    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.c_double,
+                  ctypes.c_int64, ctypes.POINTER(ctypes.c_int64)]
     starts, counts, out = np.ascontiguousarray(starts, np.int32), np.ascontiguousarray(counts, np.int32), ctypes.c_int64(0)
     took = []
     for _ in range(3):
         t0 = time.perf_counter()
-        step = f(starts.ctypes.data, counts.ctypes.data, len(starts) - 1, b, nnz, lds, ctypes.byref(out))
+        step = f(starts.ctypes.data, counts.ctypes.data, len(starts) - 1, b, nnz, steps, lds, ctypes.byref(out))
         took.append(time.perf_counter() - t0)
     return step, out.value, min(took)
 
@@ -273,6 +273,18 @@ def test_items_of_equal_blocks_share_the_compute_units():
         counts = np.tile([0, 0, 0, 1000, 1100], (512, 1))
         step, items, _ = _items_model(starts, counts, b, 512_000)
         assert items == 512 and step == pytest.approx(2 * 1000 * 8.0 * b / 150e9 + 1e-6, rel=1e-12)
+
+
+def test_few_steps_do_not_bring_in_the_sliced_copy():
+    """20 complete graphs of 1,000 nodes: a step by the sliced form takes a tenth less than by the product, and making the
+    sliced copy as long as four of them."""
+    starts = np.arange(21) * 1000
+    counts = np.tile([999 * 31, 999 * 62, 999 * 15, 999_000, 64_000], (20, 1))
+    nnz = 20 * 999_000
+    general = 3e-6 + nnz * 128.0 / 14.5e12
+    few, many = _items_model(starts, counts, 16, nnz, 24.0)[0], _items_model(starts, counts, 16, nnz, 600.0)[0]
+    assert many < 0.95 * general < general < few
+    assert few - many == pytest.approx((60e-6 + 37e-12 * nnz) * (1 / 24.0 - 1 / 600.0), rel=1e-9)
 
 
 def test_no_plan_is_made_that_will_not_be_taken():
