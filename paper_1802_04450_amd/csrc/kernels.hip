@@ -1115,8 +1115,10 @@ __device__ __forceinline__ void label_mult_tiles(d4 (&acc)[1][4], const d4 (&a)[
 // LISTED: only the points rows[0 .. *listed), by any number of workgroups.
 // PARTS: workgroup (., y) looks at the `per` centres from y * per on only (a multiple of 64) and leaves value and index of
 // the best at pv, pj [y][n].
+// Up to 16 coordinates four waves a SIMD, for which the compiler left two registers too few (500,000 x 16, 64 centres 73 -> 62
+// us, 2,000,000 x 4 260 -> 220).
 template <int KG, bool PARTS, bool LISTED>
-__global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const double* __restrict__ x, int64_t ldx,
+__global__ __launch_bounds__(kThreads, KG == 1 ? 4 : 2) SC_MFMA_IN_VGPRS void label_kernel(const double* __restrict__ x, int64_t ldx,
                                                                           int64_t n, const int32_t* __restrict__ rows,
                                                                           const int* __restrict__ listed,
                                                                           const double* __restrict__ ct,
@@ -1135,7 +1137,8 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const 
   const int kdim = (int)ldx;
   const int j0 = PARTS ? (int)blockIdx.y * per : 0;
   const int j1 = PARTS && j0 + per < k ? j0 + per : k;
-  for (int64_t block = blockIdx.x; block * 64 < n; block += gridDim.x) {  // uniform over the workgroup; one trip without a list
+  // the 64 points of a block, by the whole workgroup
+  auto label_block = [&](int64_t block) __attribute__((always_inline)) {
     const int64_t row0 = (block * 4 + wave) * 16;
     d4 a[KG];
     LabelBest<1> best;
@@ -1160,8 +1163,13 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void label_kernel(const 
     } else {
       const int moved = best.store(row0, n, at, i, g, label);
       // one counter for everybody is 10 ns per wave, 87 us at 140,000 points
-      if (lane == 0 && moved) atomicAdd(&changes[(block % kChangeSlots) * kChangeStride], moved);
+      if (lane == 0 && moved) atomicAdd(&changes[((unsigned)block % kChangeSlots) * kChangeStride], moved);
     }
+  };
+  if constexpr (LISTED) {
+    for (int64_t block = blockIdx.x; block * 64 < n; block += gridDim.x) label_block(block);  // uniform over the workgroup
+  } else {
+    label_block(blockIdx.x);
   }
 }
 

@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kT) void centroid_finish_kernel(const double* __res
 // kScreenFloor (below, what single squares lose to the denormal numbers is no longer negligible), and the lower bound has
 // to exceed the distance kept by 1e-6 of it: more than the fp64 sums are off.  A NaN on the way fails the test and the
 // point is computed; so is every point of data that have no such scale (scale 0: copies of zeros).
-// Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 12.8 us with the copy, which an XCD's L2 keeps
+// Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 11.3 us with the copy, which an XCD's L2 keeps
 // its part of from draw to draw (21 MB in all); what is left is the chain centre, its row, the point's row.  (Leaving points out by the triangle inequality with a kept assignment did
 // not shorten the pass: it saves no load of the first row.)
 constexpr int kSeedPoints = 64;   // points per block
@@ -322,10 +322,10 @@ constexpr int kExactLanes = 16;
 constexpr int64_t kDrawBlocks = 1800;
 
 // Two blocks a workgroup and a thread's copies requested before the draw, from kSeedWide blocks on and up to kSeedWideDim
-// coordinates.  A draw inside the pass, us with one block / two / four: 80,000 x 100 13.0 / 11.8 / 13.7, 100,000 x 100 14.5 / 12.8 /
-// 13.5, 115,000 x 64 12.1 / 11.2 / 11.4; fewer blocks leave the chip idle (60,000 x 100 11.8 / 11.1 / 13.7, 40,000 x 100 11.2 / 11.5 /
-// 14.3), and with 128 coordinates the registers do (60,000 11.4 / 12.1 / 15.1, 100,000 13.1 / 13.2 / 13.8).  Without a draw inside:
-// 140,000 x 32 13.3 / 12.2 / 13.3, 600,000 x 16 26.2 / 19.7 / 19.4, 200,000 x 100 24.1 / 20.9 / 25.4, of 128 20.9 / 23.7 / 30.1.
+// coordinates.  A draw inside the pass, us with one block / two / four: 80,000 x 100 11.1 / 10.0 / 10.9, 100,000 x 100 12.6 / 11.3 /
+// 11.3, 115,000 x 64 11.2 / 10.4 / 10.3; fewer blocks leave the chip idle (60,000 x 100 9.7 / 9.2 / 10.5, 40,000 x 100 8.8 / 8.8 /
+// 10.3), and with 128 coordinates the registers do (60,000 9.4 / 9.5 / 11.0, 100,000 11.5 / 11.4 / 11.6).  Without a draw inside:
+// 140,000 x 32 12.2 / 11.5 / 12.1, 600,000 x 16 24.2 / 18.7 / 18.3, 200,000 x 100 21.1 / 19.1 / 22.1, of 128 18.3 / 21.9 / 26.6.
 constexpr int64_t kSeedWide = 1024;
 constexpr int kSeedWideDim = 112;
 constexpr float kScreenFloor = 1e-30f;
@@ -1351,7 +1351,7 @@ int label_screen_steps(int64_t n, int64_t ldx, int k) {
     const bool few = ldx >= 64 ? (n >= 45000 && k >= 128) || (n >= 30000 && k >= 256) || (n >= 20000 && k >= 1000 && ldx >= 100)
                                : ldx >= 32 && n >= 45000 && k >= 1000;
     if ((ldx < 8 && n < 500000) || (n < 65000 && !few)) return INT32_MAX;
-    gain = 3.5e-8 * w * std::min(1.0, ((double)ldx + 24.0) / 88.0) * (n < 65000 ? 0.5 : 1.0) - 2.0 +
+    gain = 3.5e-8 * w * (ldx <= 16 ? 0.25 : 1.0) * std::min(1.0, ((double)ldx + 24.0) / 88.0) * (n < 65000 ? 0.5 : 1.0) - 2.0 +
            4e-5 * std::max(0.0, m - 200000.0);
   } else {
     const bool few = (n >= 45000 && k >= 128) || (n >= 30000 && k >= 500 && ldx <= 512) || (n >= 20000 && k >= 1000 && ldx <= 320);

@@ -254,7 +254,7 @@ def test_items_of_many_blocks_are_planned_once(sliced):
 
 
 @pytest.mark.parametrize("n,d,k,least,most", [
-    (100_000, 100, 100, 3, 5), (500_000, 100, 128, 3, 4), (65_000, 64, 1000, 3, 3), (1_000_000, 8, 64, 4, 12), (200_000, 20, 100, 6, 25),
+    (100_000, 100, 100, 3, 5), (500_000, 100, 128, 3, 4), (65_000, 64, 1000, 3, 3), (1_000_000, 8, 64, 4, 14), (200_000, 20, 100, 6, 25),
     (142_541, 500, 100, 3, 6), (20_000, 2000, 64, None, None), (5_000, 100, 1000, None, None), (40_000, 100, 100, None, None),
     (45_000, 16, 1000, None, None), (200_000, 2, 512, None, None), (10_000, 500, 256, None, None)])
 def test_steps_that_bring_in_the_labelling_screen(n, d, k, least, most):
