@@ -1338,10 +1338,10 @@ LabelScreen plan_label_screen(int64_t n, int64_t ldx, int k) {
 // The reduced copy of the points costs about as much as a fp64 labelling, and a screened step saves a tenth to a half of one,
 // so the number of steps decides.  Fitted to 290 shapes (2,500 to 2,000,000 points of 2 to 2,000 normal coordinates, 16 to
 // 2,000 centres; us a step by the fp64 product, saved by the screen, and the copy): 100,000 x 100, 100 centres 115 / 30 / 90,
-// 500,000 x 100, 128 480 / 257 / 453, 1,000,000 x 8, 64 184 / 47 / 208, 65,000 x 64, 1,000 236 / 105 / 60, 200,000 x 500, 64
+// 500,000 x 100, 128 480 / 257 / 453, 1,000,000 x 8, 64 169 / 31 / 216, 65,000 x 64, 1,000 236 / 105 / 60, 200,000 x 500, 64
 // 541 / 163 / 747.  Never where a wave's chain over few tiles of points is what a step lasts (20,000 x 2,000, 64 centres 394 /
 // -116 / 397, 5,000 x 100, 1,000 60 / -30 / 63, 45,000 x 16, 1,000 88 / -4 / 38) or where there is next to nothing to
-// multiply (200,000 x 2, 512 156 / -11 / 73).  In the mean over the shapes 10 steps take 14 % less than by the product alone
+// multiply (200,000 x 2, 1,000 238 / -28 / 78).  In the mean over the shapes 10 steps take 14 % less than by the product alone
 // (4 % with the screen always), 3 steps 6 % less (14 % more).
 int label_screen_steps(int64_t n, int64_t ldx, int k) {
   const double w = (double)n * (double)ldx * (double)k, m = (double)n;
