@@ -281,12 +281,14 @@ def test_grouped_search(B, n, d, k, kind, monkeypatch):
 
 # many neighbours in few tiles: the lists of candidates of some queries run over
 @pytest.mark.parametrize("n,d,k,kind", [(62_001, 2, 50, "normal"), (100_003, 2, 50, "normal"), (100_000, 3, 100, "uniform"),
-                                        (62_000, 10, 100, "tight"), (30_011, 70, 60, "tight"), (62_500, 2, 200, "uniform")])
+                                        (62_000, 10, 100, "tight"), (30_011, 70, 60, "tight"), (62_500, 2, 200, "uniform"), (62_000, 16, 60, "line")])
 def test_grouped_search_whose_lists_run_over(B, n, d, k, kind, monkeypatch):
     gen = torch.Generator(device="cuda:0").manual_seed(n + d)
     x = torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
     if kind == "uniform":
         x = torch.rand((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    elif kind == "line":              # closer to one another than the screen can tell: nearly all run over
+        x = 0.01 * x + torch.linspace(0, 50, n, dtype=torch.float64, device="cuda:0")[:, None]
     elif kind == "tight":             # clusters of very different widths
         at = torch.arange(n, device="cuda:0") % 40
         x = x * (10.0 ** (-2.0 * torch.rand(40, dtype=torch.float64, device="cuda:0", generator=gen)))[at, None]
@@ -294,7 +296,7 @@ def test_grouped_search_whose_lists_run_over(B, n, d, k, kind, monkeypatch):
     fp64 = B.sc_counter(B.SC_COUNTER_FP64_SEARCHES)
     idx, dist = B.sc_knn_search(x, k)
     # clusters a hundredth as wide as the points are far apart: the screen cannot tell their points apart
-    assert kind == "tight" or B.sc_counter(B.SC_COUNTER_FP64_SEARCHES) == fp64
+    assert kind in ("tight", "line") or B.sc_counter(B.SC_COUNTER_FP64_SEARCHES) == fp64
     monkeypatch.setenv("SCEIG_NO_GROUPS", "1")
     plain_idx, plain_dist = B.sc_knn_search(x, k)
     assert torch.equal(idx, plain_idx) and torch.equal(dist, plain_dist)
