@@ -175,6 +175,66 @@ def test_bucketed_edge_similarity_matches_oracle(B, d, ldx, measure, twist):
     np.testing.assert_allclose(got[ok], ref, rtol=1e-12, atol=4.0 * d * 2.0 ** -53)
 
 
+# where rows begin inside a line: every offset of the first row from a 16- and a 64-byte multiple, strides of every residue,
+# rows of one chunk of loads and of several with every remainder, odd dimensions; pair by pair and in buckets
+@pytest.mark.parametrize("d", [1, 2, 5, 7, 8, 9, 31, 32, 33, 40, 41, 63, 64, 66, 97, 130, 161])
+@pytest.mark.parametrize("more,shift", [(0, 0), (1, 0), (2, 2), (3, 1), (0, 6), (4, 4)])
+def test_edge_similarity_wherever_rows_begin(B, d, more, shift):
+    n, ldx = 600, d + more
+    rng = np.random.default_rng(d + 1000 * more)
+    buf = torch.full((n * ldx + 64,), float("nan"), dtype=torch.float64, device="cuda:0")   # what is read beside the rows shows
+    x = rng.normal(size=(n, d)) + 1.0
+    rows = buf[shift:shift + n * ldx].view(n, ldx)
+    rows[:, :d] = torch.from_numpy(x).cuda()
+    u, v = _edges(n, 4001, 17)
+    u[:4], v[:4] = [0, n - 1, 0, n - 1], [n - 1, 0, 0, n - 1]
+    du, dv = _dev(u, torch.int32), _dev(v, torch.int32)
+    val = torch.empty(u.size, dtype=torch.float64, device="cuda:0")
+    for measure in (1, 2):
+        assert B.lib().sc_edge_similarity(rows.data_ptr(), ldx, n, d, du.data_ptr(), dv.data_ptr(), u.size, measure,
+                                          float(np.sqrt(d)), val.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+        ref = osim.edge_similarity(x, u, v, measure, float(np.sqrt(d)))
+        np.testing.assert_allclose(val.cpu().numpy(), ref, rtol=1e-12, atol=4.0 * d * 2.0 ** -53)
+
+
+@pytest.mark.parametrize("d,more,shift", [(90, 0, 2), (90, 1, 1), (61, 1, 6), (200, 0, 0), (5, 1, 2), (24, 8, 4)])
+def test_bucketed_edge_similarity_wherever_rows_begin(B, d, more, shift):
+    """The same values, to the last bit, as pair by pair: the sums are formed in one order."""
+    n, ldx = 5_000_000 // d + 11, d + more
+    gen = torch.Generator(device="cuda:0").manual_seed(d)
+    buf = torch.full((n * ldx + 64,), float("nan"), dtype=torch.float64, device="cuda:0")
+    rows = buf[shift:shift + n * ldx].view(n, ldx)
+    rows[:, :d] = torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    ne = 8 * n + 3
+    u = torch.randint(0, n, (ne,), device="cuda:0", generator=gen, dtype=torch.int32)
+    v = torch.where(torch.rand(ne, device="cuda:0", generator=gen) < 0.5, (u + 3) % n,
+                    torch.randint(0, n, (ne,), device="cuda:0", generator=gen, dtype=torch.int32))
+
+    def call(a, b, measure):
+        val = torch.empty(a.numel(), dtype=torch.float64, device="cuda:0")
+        assert B.lib().sc_edge_similarity(rows.data_ptr(), ldx, n, d, a.data_ptr(), b.data_ptr(), a.numel(), measure, 9.0,
+                                          val.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+        return val
+
+    for measure in (0, 2):
+        bucketed = call(u, v, measure)
+        few = ne // 4                                    # two pairs a row: pair by pair
+        assert torch.equal(bucketed[:few], call(u[:few].contiguous(), v[:few].contiguous(), measure))
+
+
+# entries listed several times side by side in a row, in every order; more rows than row and column have 32 bits for
+@pytest.mark.parametrize("n,ne,cols", [(40, 8000, 40), (500, 30_000, 7), (5000, 200_000, 3000), (5_000_000, 700_000, 5_000_000)])
+@pytest.mark.parametrize("symmetrize", [False, True])
+def test_coo_to_csr_keeps_the_order_of_repeated_entries(B, n, ne, cols, symmetrize):
+    rng = np.random.default_rng(n)
+    r, c = rng.integers(0, n, size=ne), rng.integers(0, cols, size=ne)
+    r[ne // 2:], c[ne // 2:] = r[:ne - ne // 2][::-1], c[:ne - ne // 2][::-1]
+    w = np.arange(ne, dtype=np.float64)
+    got = B.sc_coo_to_csr(_dev(r, torch.int32), _dev(c, torch.int32), _dev(w, torch.float64), n, symmetrize)
+    for a, b in zip(got, _csr_by_sorting(r, c, w, n, symmetrize)):
+        np.testing.assert_array_equal(a.cpu().numpy(), b)
+
+
 def test_coo_to_csr_edge_cases(B):
     z32 = torch.empty(0, dtype=torch.int32, device="cuda:0")
     z64 = torch.empty(0, dtype=torch.float64, device="cuda:0")
