@@ -854,7 +854,8 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (d4){0.0, 0.0, 0.0, 0.0};
-  d4 a0[2][MT], a1[2][MT];  // operand registers of the pipelined path: a0 carries over from chunk to chunk
+  constexpr int H = MT > 2 ? 1 : 2;  // groups of 16 indices a trip: what the registers hold
+  d4 a0[H][MT], a1[H][MT];  // operand registers of the pipelined path: a0 carries over from chunk to chunk
 
   for (int k0 = 0; k0 < kdim; k0 += KC) {
     const int kc = (kdim - k0) < KC ? (kdim - k0) : KC;
@@ -871,9 +872,9 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
       // The request that follows a chunk's last trip is the first trip of the NEXT chunk (columns are clamped to the
       // contraction's end, not to the chunk's): it is in flight while the workgroup restages the coefficient chunk
       // behind two barriers, so the stream of operand loads no longer drains at every chunk boundary.
-      auto fetch = [&](d4 (&av)[2][MT], int kb) __attribute__((always_inline)) {
+      auto fetch = [&](d4 (&av)[H][MT], int kb) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < H; ++h) {
           int kcol = k0 + kb + 16 * h + 4 * g;
           kcol = kcol + 3 < kdim ? kcol : kdim - 4;
 #pragma unroll
@@ -882,9 +883,9 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
         }
       };
       const int tiles = (n1 - n0 + 15) / 16;  // of a group of columns fewer than NT may hold any
-      auto mult = [&](const d4 (&av)[2][MT], int kb) __attribute__((always_inline)) {
+      auto mult = [&](const d4 (&av)[H][MT], int kb) __attribute__((always_inline)) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < H; ++h) {
           if (kb + 16 * h < kc16) {  // uniform; the LDS slots beyond kc16 were not filled
             const int kt = (kb >> 4) + h;
 #pragma unroll
@@ -903,20 +904,20 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
         }
       };
       if (k0 == 0) fetch(a0, 0);  // later chunks find their first trip requested by the chunk before
-      for (int kb = 0; kb < kc16; kb += 64) {
-        fetch(a1, kb + 32);
+      for (int kb = 0; kb < kc16; kb += 32 * H) {
+        fetch(a1, kb + 16 * H);
         mult(a0, kb);
-        if (kb + 32 >= kc16) break;
-        fetch(a0, kb + 64);
-        mult(a1, kb + 32);
+        if (kb + 16 * H >= kc16) break;
+        fetch(a0, kb + 32 * H);
+        mult(a1, kb + 16 * H);
       }
       kk0 = kc16;
     }
-    // two 16-index groups per trip: their loads are issued together, ahead of the MFMAs that use them
-    for (int kk = kk0; kk < kc16; kk += 32) {
-      double a[2][MT][4];
+    // H 16-index groups per trip: their loads are issued together, ahead of the MFMAs that use them
+    for (int kk = kk0; kk < kc16; kk += 16 * H) {
+      double a[H][MT][4];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < H; ++h) {
         const int kcol = k0 + kk + 16 * h + 4 * g;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void row_gemm_kernel(dou
         }
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < H; ++h) {
         if (kk + 16 * h < kc16) {  // uniform; the LDS slots beyond kc16 were not filled
           const int kt = (kk >> 4) + h;
 #pragma unroll
@@ -2153,21 +2154,28 @@ hipError_t launch_row_gemm(double* basis, int64_t n, int64_t ld, int acol0, int 
                            hipStream_t st, const int* skip) {
   if (kdim <= 0 || ncols <= 0) return hipSuccess;
   const int vec_ok = (ld % 4 == 0 && acol0 % 4 == 0 && (reinterpret_cast<uintptr_t>(basis) % 32 == 0)) ? 1 : 0;
-  constexpr int MT = 2;
-  const unsigned gx = (unsigned)ceil_div64(n, 4 * 16 * MT);
   const bool pipe = kdim >= 128;  // loads one trip ahead pay from a few trips on
-#define SC_LAUNCH_RG(NTV, PV, GRID)                                                                                \
-  hipLaunchKernelGGL((row_gemm_kernel<NTV, MT, PV>), dim3(GRID), dim3(kThreads), 0, st, basis, n, ld, acol0,       \
-                     kdim, bmat, ldb, ncols, mode, ccol0, out, ldo, vec_ok, rowmap, skip)
+  const int64_t gx = ceil_div64(n, 4 * 16 * 2);
+#define SC_LAUNCH_RG(NTV, MT, PV, GRID)                                                                            \
+  hipLaunchKernelGGL((row_gemm_kernel<NTV, MT, PV>), dim3((unsigned)(GRID)), dim3(kThreads), 0, st, basis, n, ld,  \
+                     acol0, kdim, bmat, ldb, ncols, mode, ccol0, out, ldo, vec_ok, rowmap, skip)
   if (ncols <= 16) {
-    if (pipe) SC_LAUNCH_RG(1, true, gx); else SC_LAUNCH_RG(1, false, gx);
+    if (pipe) SC_LAUNCH_RG(1, 2, true, gx); else SC_LAUNCH_RG(1, 2, false, gx);
   } else if (ncols <= 32) {
-    if (pipe) SC_LAUNCH_RG(2, true, gx); else SC_LAUNCH_RG(2, false, gx);
+    if (pipe) SC_LAUNCH_RG(2, 2, true, gx); else SC_LAUNCH_RG(2, 2, false, gx);
   } else {
     if (mode == 0 || (mode == 3 && ncols > 64)) return hipErrorInvalidValue;
-    const int64_t grid = ceil_div64(gx, 8) * 8 * ((ncols + 63) / 64);
+    const int64_t groups = (ncols + 63) / 64, grid = ceil_div64(gx, 8) * 8 * groups;
+    // 64 rows a wave instead of 32: half the chunks of coefficients that the matrix instructions wait for, half the
+    // coefficients read from LDS.  Where there are four rounds of workgroups and more (two a compute unit); fewer of them
+    // leave the last round emptier than that gains.  300,007 rows, 400 x 200: 1,062 -> 970 us (a round and a half less of
+    // 9.2), 300,000 x 192 927 -> 873, 500,000 rows, 1,000 x 500 8.63 -> 7.98 ms = 64 TFLOP/s; 300,007 x 64 (2.3 rounds)
+    // 402 and 403 us, 100,000 rows, 200 x 100 154 and 160, 5,000 rows, 300 x 200 54 and 74.
+    const int64_t grid4 = ceil_div64(ceil_div64(n, 4 * 16 * 4), 8) * 8 * groups;
     if (grid > INT32_MAX) return hipErrorInvalidValue;
-    if (pipe) SC_LAUNCH_RG(4, true, (unsigned)grid); else SC_LAUNCH_RG(4, false, (unsigned)grid);
+    if (pipe && vec_ok && kdim % 4 == 0 && grid4 >= 2048) SC_LAUNCH_RG(4, 4, true, grid4);
+    else if (pipe) SC_LAUNCH_RG(4, 2, true, grid);
+    else SC_LAUNCH_RG(4, 2, false, grid);
   }
 #undef SC_LAUNCH_RG
   return hipGetLastError();

@@ -336,6 +336,24 @@ def test_rotate(B, n, j0, ja, l, colmajor):
     assert np.max(np.abs(out - ref)) <= 1e-12 * np.abs(ref).max()
 
 
+# four rounds of workgroups and more of 256 rows: panels with a ragged last wave, last groups of one to four tiles, contractions
+# that end inside a chunk and inside 16 indices
+@pytest.mark.parametrize("n,j0,ja,l,colmajor", [(65_537, 4, 132, 512, False), (74_909, 0, 128, 449, True), (131_200, 8, 260, 250, False),
+                                                (524_321, 0, 140, 40, False)])
+def test_rotate_of_many_rows(B, n, j0, ja, l, colmajor):
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    basis = torch.randn((n, (j0 + ja + 7) // 4 * 4), dtype=torch.float64, device="cuda:0", generator=gen)
+    y = torch.randn((ja, l), dtype=torch.float64, device="cuda:0", generator=gen)
+    out = B.sc_rotate(basis, j0, ja, y, out_colmajor=colmajor)
+    if colmajor:
+        out = out.T
+    for r0 in range(0, n, 1 << 16):
+        a = basis[r0:r0 + (1 << 16), j0:j0 + ja]
+        # sums of ja products in another order: ja 2^-53 of the sum of their absolute values
+        err = (out[r0:r0 + (1 << 16)] - a @ y).abs() / (a.abs() @ y.abs())
+        assert float(err.max()) <= 2.0 * ja * 2.0 ** -53
+
+
 def test_reorder_csr_is_a_permutation_similarity(B):
     from oracle import components
     parts = [wl.ring(30), wl.path(41), wl.random_weighted_connected(200, 500, 3), wl.hypercube(5)]
