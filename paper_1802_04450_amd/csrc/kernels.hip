@@ -2106,9 +2106,11 @@ ProjectPlan plan_project(int64_t n, int ja, int max_partials) {
   p.nwc = ja <= 64 ? 1 : (ja <= 128 ? 2 : 4);
   const int nwr = 4 / p.nwc;
   const int coltiles = (ja + 64 * p.nwc - 1) / (64 * p.nwc);
-  // about 768 workgroups in total (three per compute unit), at least 16 rows per wave slice, and no
-  // more partial blocks (one per workgroup and column tile group) than the reduction is meant to sum
-  int64_t panels = 768 / coltiles;
+  // 512 workgroups in total, the two per compute unit that the registers allow (768 leave a second round half empty: both
+  // passes against 992 columns of 500,000 rows, 32 at a time, 3,462 -> 3,397 us, of 300,000 rows 2,208 -> 2,099; against 500
+  // columns 2,087 -> 1,979; 1,024 and more were slower still), at least 16 rows per wave slice, and no more partial blocks
+  // (one per workgroup and column tile group) than the reduction is meant to sum
+  int64_t panels = 512 / coltiles;
   if (panels < 16) panels = 16;
   if (panels > max_partials) panels = max_partials;
   int64_t rows = ceil_div64(n, panels);
