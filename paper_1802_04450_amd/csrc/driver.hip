@@ -1122,6 +1122,10 @@ struct Solver {
   // costs block steps, never correctness: the phases converge by their own residual tests.
   double spec_lo = -1.0;
   bool spec_lo_set = false;
+  // the degree feedback's last first residual, the degrees that it added, and whether such degrees have met the floor (see run())
+  double rw_before = 0.0;
+  int more_degrees = 0;
+  bool at_floor = false;
   bool late_off = false;    // projecting the locked vectors out after the filter has stopped paying (see run())
   int filt_extra = 0;       // degrees added to (or taken from) the planned degree: feedback from the phases' first steps
   sc_stats stats{};
@@ -1782,13 +1786,43 @@ struct Solver {
           for (int t = 0; t < std::min(want, nsel); ++t) rw = std::max(rw, rho[t]);
           if (rw > 0.0) {
             const double target = (late_projection && tight_target ? 0.01 : 0.125) * tol;
-            const double need = std::log(rw / target) / phase_rate;
-            if (late_projection && rw > 0.5 * tol)
+            double need = std::log(rw / target) / phase_rate;
+            // What the next phase will see at the same degree: its residuals are relative to what the block holds along the
+            // `left_then` directions of the multiple eigenvalue that remain, at least a random left_then x b matrix's smallest
+            // singular value, sqrt(left_then) - sqrt(b) about; with b directions left or fewer 30 times more than before was seen
+            // (so with 2 to 16 left).  The floor is relative to it, too, and grows with the root of the locked vectors' number.
+            // Where that takes the residual near tol, the next phase is planned for it.
+            const int left = ncomp - nl, left_then = left - want;
+            double ahead_of = 1.0;
+            if (k <= ncomp && left > b && left_then >= 1 && nl + want < k) {
+              ahead_of = 30.0;
+              if (left_then > b)
+                ahead_of = std::min(ahead_of, (std::sqrt((double)left) - std::sqrt((double)b)) /
+                                                  (std::sqrt((double)left_then) - std::sqrt((double)b)));
+              if (late_projection) ahead_of *= std::sqrt((double)(nl + want) / nl);
+            }
+            if (!late_projection && rw * ahead_of > 0.5 * tol) need = std::log(rw * ahead_of / target) / phase_rate;
+            // Degrees that the phase before asked for and that have not brought half of what they are worth have met the
+            // floor, too: what is kept of them takes the polynomial's part of the residual below it, and no more are asked for.
+            if (late_projection && more_degrees > 0 && rw > 2.0 * rw_before * std::exp(-phase_rate * more_degrees)) {
+              const int kept = std::max(0, (int)std::ceil(std::log(rw_before / rw) / phase_rate + 0.7));
+              filt_extra -= std::max(0, more_degrees - kept);
+              at_floor = true;
+            }
+            const int extra = filt_extra;
+            if (late_projection && rw * ahead_of > 0.5 * tol) {
               late_off = true;  // the floor, not the polynomial: more degrees would not help
-            else if (need > (late_projection && tight_target ? 1.0 : 0.5))  // see above
-              filt_extra = std::min(filt_extra + (int)std::ceil(need), 6);
-            else if (need < -1.5)
+              at_floor = false;
+            } else if (need > (late_projection && tight_target ? 1.0 : 0.5)) {  // see above
+              if (!(late_projection && at_floor)) filt_extra = std::min(filt_extra + (int)std::ceil(need), 6);
+            } else if (need < -1.5) {
               filt_extra = std::max(filt_extra - 1, -4);
+            }
+            more_degrees = filt_extra - extra;
+            rw_before = rw;
+            if (debug_on())
+              std::fprintf(stderr, "[sceig] first residual %.2e, aim %.2e: degrees %+d%s\n", rw, target, filt_extra,
+                           at_floor ? ", at the floor" : "");
           }
           phase_rate = 0.0;  // once per phase
         }
