@@ -130,6 +130,7 @@ SC_COUNTER_RESIDENT_FILTERS = 0
 SC_COUNTER_GROUPED_SEARCHES = 1
 SC_COUNTER_SCREENED_LABELLINGS = 2
 SC_COUNTER_FP64_SEARCHES = 3
+SC_COUNTER_START_PAIRS = 4
 
 
 def sc_counter(which: int) -> int:

@@ -429,6 +429,8 @@ int enqueue_cgs2(double* basis, int64_t n, int64_t ld, int j, int wcol, int b, i
   return ngram;
 }
 
+constexpr double kSecondPassRatio2 = 1e6;  // squared norm removed to squared norm kept: more, and a second pass follows
+
 // Gram-Schmidt of basis[:, wcol : wcol+b] against basis[:, 0 : j] with the second pass decided on the device ("twice
 // is enough", and once is when nothing is lost to cancellation): after the first pass a one-workgroup kernel compares,
 // per column, the squared norm the pass removed with the squared norm it kept; if no column lost more than a factor
@@ -465,7 +467,7 @@ int enqueue_cgs_adaptive(double* basis, int64_t n, int64_t ld, int j, int wcol, 
     tm->end(kFamUpdate, counted * 8.0 * rows * (j + 2 * b), counted * 2.0 * rows * j * b);
     if (pass == 0) {
       HIP_TRY(launch_reduce_partials(gpart, ngram, b, b, gram_tmp, nullptr, 0, nullptr, 0, st));
-      HIP_TRY(launch_second_pass_test(h1, j, b, gram_tmp, 1e6, skip, st));
+      HIP_TRY(launch_second_pass_test({h1, j}, {}, b, gram_tmp, kSecondPassRatio2, skip, st));
     }
   }
   return ngram;
@@ -518,6 +520,7 @@ void enqueue_block_qr(double* basis, int64_t n, int64_t ld, int col, int b, doub
 std::atomic<int64_t> resident_launches{0};  // sc_counter(SC_COUNTER_RESIDENT_FILTERS)
 std::atomic<int64_t> grouped_searches{0};   // sc_counter(SC_COUNTER_GROUPED_SEARCHES)
 std::atomic<int64_t> fp64_searches{0};      // sc_counter(SC_COUNTER_FP64_SEARCHES)
+std::atomic<int64_t> start_pairs{0};        // sc_counter(SC_COUNTER_START_PAIRS)
 std::atomic<int64_t> screened_labellings{0};  // sc_counter(SC_COUNTER_SCREENED_LABELLINGS)
 
 // Plan of the LDS-resident Chebyshev filter (resident.hip) for one matrix and block width: the diagonal blocks of the
@@ -893,7 +896,10 @@ double* enqueue_cheb_filter(const int64_t* rowptr, const int32_t* col, const dou
                             const double* s, int64_t n, int64_t nnz, int b, int d, double a, double* z, double* buf1,
                             double* buf2, double* buf3, double avg_deg, const int32_t* longrows, int nlong,
                             const ResidentPlan* resident, hipStream_t st, KTimer* tm, double* direct = nullptr,
-                            int64_t direct_ld = 0, double lo = -1.0, int d32 = 0, uint64_t rnd_key = 0, int use_rnd = 0) {
+                            int64_t direct_ld = 0, double lo = -1.0, int d32 = 0, uint64_t rnd_key = 0, int use_rnd = 0,
+                            int copies = 1, uint64_t rnd_key2 = 0) {
+  // copies = 2 (use_rnd, the one-launch form with an item for every row, direct): random block rnd_key2 too, into the b
+  // columns behind
   // lo: lower end of the damped interval; -1 always holds (||S||_2 = 1), the solver passes its estimate of the
   // bottom of the spectrum when it has one
   KTimer none;
@@ -911,7 +917,7 @@ double* enqueue_cheb_filter(const int64_t* rowptr, const int32_t* col, const dou
     HIP_TRY(launch_cheb_resident(rowptr, col, val_scaled, z, out, ldo, b, d, 1.0 / e, 2.0 / e, c, resident->items.p,
                                  resident->nitems, resident->lds_bytes, resident->scol.p, resident->sval.p,
                                  resident->slice_base.p, resident->slice_len.p, resident->slice_first.p,
-                                 resident->row_extra.p, st, d32, rnd_key, use_rnd));
+                                 resident->row_extra.p, st, d32, rnd_key, use_rnd, copies, rnd_key2));
     const int64_t r0 = resident->rest_row0;
     if (r0 < n) {
       // the blocks without an item: the recurrence step by step on their rows alone (their iterates rotate through the
@@ -930,7 +936,7 @@ double* enqueue_cheb_filter(const int64_t* rowptr, const int32_t* col, const dou
       if (cur != out)
         HIP_TRY(launch_copy_cols(cur + r0 * b, b, 0, out + r0 * ldo, ldo, 0, b, n - r0, st));
     }
-    tm->end(kFamSpmm, d * bytes + (d - 1) * 8.0 * (double)n * b, d * 2.0 * (double)nnz * b, d);
+    tm->end(kFamSpmm, copies * (d * bytes + (d - 1) * 8.0 * (double)n * b), copies * d * 2.0 * (double)nnz * b, d);
     return direct ? nullptr : buf1;
   }
   if (val_scaled) {
@@ -1068,6 +1074,8 @@ struct Solver {
   // the form): the later steps damp what the rounding of the earlier ones adds along the unwanted directions.
   // SCEIG_FILTER_FP64_TAIL = a number larger than any degree keeps every step in double precision.
   int filter_tail64 = std::getenv("SCEIG_FILTER_FP64_TAIL") ? std::atoi(std::getenv("SCEIG_FILTER_FP64_TAIL")) : 6;
+  double pair_min_work = std::getenv("SCEIG_PAIR_MIN_WORK") ? std::atof(std::getenv("SCEIG_PAIR_MIN_WORK")) : 2e7;
+  bool no_start_pairs = std::getenv("SCEIG_NO_START_PAIRS") != nullptr;
   bool tentative_two_passes = std::getenv("SCEIG_TENTATIVE_TWO_PASSES") != nullptr;
   // for tests of the check phase: the solve works for one pair more and gives up the unlock-th largest before that phase
   int unlock = std::getenv("SCEIG_UNLOCK") ? std::atoi(std::getenv("SCEIG_UNLOCK")) : -1;
@@ -1075,7 +1083,7 @@ struct Solver {
   size_t ws_limit = 0;         // > 0: size of the caller's workspace, checked against the estimate once nnz is known
   hipStream_t st;
   // device
-  DevBuf<double> basis, s, z, part, gpart, h1, hsum, small, slots, yd, rot;
+  DevBuf<double> basis, s, z, part, gpart, h1, hsum, hpair, small, slots, yd, rot;
   DevBuf<int> flag;
   DevBuf<int64_t> rowptr_p;
   DevBuf<int32_t> col_p, old_of_new_d, new_of_old_d, comp_d, perm_d;
@@ -1122,8 +1130,16 @@ struct Solver {
   // costs block steps, never correctness: the phases converge by their own residual tests.
   double spec_lo = -1.0;
   bool spec_lo_set = false;
+  // The start block of the next phase, where it went through the filter together with this phase's and out of the locked
+  // vectors in the same pass over them (see run()).
+  struct Ahead {
+    bool ready = false;
+    int from = 0;        // locked vectors it has been projected against
+    int extra = 0;       // filt_extra of its filter
+    double rate = 0.0;   // filt_rate of its filter
+  } ahead;
   // the degree feedback's last first residual, the degrees that it added, and whether such degrees have met the floor (see run())
-  double rw_before = 0.0;
+  double rw_before = 0.0, rw_next = 0.0;  // rw_next: what the next phase is expected to see
   int more_degrees = 0;
   bool at_floor = false;
   bool late_off = false;    // projecting the locked vectors out after the filter has stopped paying (see run())
@@ -1131,6 +1147,9 @@ struct Solver {
   sc_stats stats{};
   KTimer timer;
 
+  // the last b columns of the rotation workspace, which only a rotation of more vectors than b less than it holds takes (a restart)
+  double* ahead_block() { return rot.p + (size_t)n * (rot_cols - b); }
+  int pair_pad() const { return 2 * b > kMaxBlock ? kPairPad : kPP; }
   double* rinv() { return small.p; }
   double* r1() { return small.p + kPP * kPP; }
   double* gram() { return small.p + 2 * kPP * kPP; }
@@ -1297,6 +1316,7 @@ struct Solver {
     gpart.alloc((size_t)kGramPartials * kPP * kPP);
     h1.alloc((size_t)jmax * kPP);
     hsum.alloc((size_t)jmax * kPP);
+    hpair.alloc((size_t)jmax * pair_pad());
     small.alloc(3 * kPP * kPP);
     max_slots = m / b + 4;
     slots.alloc((size_t)max_slots * kSlotDoubles);
@@ -1367,7 +1387,9 @@ struct Solver {
   // recurrence: no reorthogonalization.  The caller orthogonalizes and orthonormalizes the result again.
   // rnd_key / use_rnd: the block to filter is random block rnd_key, which the one-launch form makes in its prologue
   // (the caller has checked that this form takes every row); z is then not read
-  void apply_start_filter(int d, double a, uint64_t rnd_key = 0, int use_rnd = 0) {
+  // pair: two random blocks at once, into columns [nl, nl + 2b): rnd_key and rnd_key2 (use_rnd), or, without the one-launch form,
+  // the 2b columns of random block rnd_key by the products of blocks twice as wide
+  void apply_start_filter(int d, double a, uint64_t rnd_key = 0, int use_rnd = 0, bool pair = false, uint64_t rnd_key2 = 0) {
     double* buf1 = rot.p;
     double* buf2 = rot.p + (size_t)n * b;
     double* buf3 = rot.p + 2 * (size_t)n * b;
@@ -1386,12 +1408,80 @@ struct Solver {
       if (growth > 0.0) d32 = std::min(d32, (int)std::floor(69.0 / growth));  // e^69 = 1e30
       if (d32 < 1) d32 = 0;
     }
-    const double* res = enqueue_cheb_filter(rowptr, col, val, val_s.p, s.p, n, nnz, b, d, a, z.p, buf1, buf2, buf3,
-                                            avg_deg, longrows.p, nlong, &resident, st, &timer, basis.p + nl, ld, filt_lo,
-                                            d32, rnd_key, use_rnd);
-    stats.spmv_cols += (int64_t)d * b;
-    stats.filter_steps += d;
-    if (res) HIP_TRY(launch_copy_cols(res, b, 0, basis.p, ld, nl, b, n, st));
+    const int w = pair ? 2 * b : b;
+    const double* res;
+    if (pair && !use_rnd) {
+      const size_t block = (size_t)n * w;
+      HIP_TRY(launch_random_block(rot.p, n, w, 0, w, seed, rnd_key, st));
+      res = enqueue_cheb_filter(rowptr, col, val, val_s.p, s.p, n, nnz, w, d, a, rot.p, rot.p + block, rot.p + 2 * block, nullptr,
+                                avg_deg, longrows.p, nlong, nullptr, st, &timer, nullptr, 0, filt_lo);
+    } else {
+      res = enqueue_cheb_filter(rowptr, col, val, val_s.p, s.p, n, nnz, b, d, a, z.p, buf1, buf2, buf3, avg_deg, longrows.p,
+                                nlong, &resident, st, &timer, basis.p + nl, ld, filt_lo, d32, rnd_key, use_rnd, pair ? 2 : 1,
+                                rnd_key2);
+    }
+    stats.spmv_cols += (int64_t)d * w;
+    stats.filter_steps += pair ? 2 * d : d;
+    if (res) HIP_TRY(launch_copy_cols(res, w, 0, basis.p, ld, nl, w, n, st));
+  }
+
+  // The first Gram-Schmidt pass of two start blocks side by side against all locked vectors, which are read once for both; the
+  // second one then waits in ahead_block().  Returns the number of Gram partials of the first one, which is finished.
+  int project_pair() {
+    const int w = 2 * b, pad = pair_pad();
+    const ProjectPlan plan = plan_project(n, nl, kMaxPartials, w);
+    timer.begin(kFamProject);
+    HIP_TRY(launch_project(basis.p, n, ld, 0, nl, nl, w, plan, part.p, st));
+    timer.end(kFamProject, 8.0 * (double)n * (nl + w), 2.0 * (double)n * nl * w);
+    timer.begin(kFamOther);
+    HIP_TRY(launch_reduce_partials(part.p, plan.npart, nl, w, hpair.p, nullptr, 0, nullptr, 0, st));
+    timer.end(kFamOther, 8.0 * plan.npart * (double)nl * w, 0.0);
+    timer.begin(kFamUpdate);
+    HIP_TRY(launch_row_gemm(basis.p, n, ld, 0, nl, hpair.p, pad, w, 0, nl, nullptr, 0, nullptr, st));
+    HIP_TRY(launch_copy_cols(basis.p, ld, nl + b, ahead_block(), b, 0, b, n, st));
+    timer.end(kFamUpdate, 8.0 * (double)n * (nl + 2 * w + 2 * b), 2.0 * (double)n * nl * w);
+    const ProjectPlan gplan = plan_project(n, b, kMaxPartials);
+    HIP_TRY(launch_project(basis.p, n, ld, nl, b, nl, b, gplan, gpart.p, st));
+    return finish_start_block({hpair.p, nl, pad}, {}, gplan.npart, true);
+  }
+
+  // The block that project_pair() left in ahead_block(), now in columns [nl, nl + b): what has been locked since is projected out.
+  int project_rest() {
+    const int c0 = ahead.from, jc = nl - c0;
+    if (jc <= 0) {
+      const ProjectPlan gplan = plan_project(n, b, kMaxPartials);
+      HIP_TRY(launch_project(basis.p, n, ld, nl, b, nl, b, gplan, gpart.p, st));
+      return finish_start_block({hpair.p + b, c0, pair_pad()}, {}, gplan.npart, true);
+    }
+    const ProjectPlan plan = plan_project(n, jc, kMaxPartials);
+    timer.begin(kFamProject);
+    HIP_TRY(launch_project(basis.p, n, ld, c0, jc, nl, b, plan, part.p, st));
+    timer.end(kFamProject, 8.0 * (double)n * (jc + b), 2.0 * (double)n * jc * b);
+    timer.begin(kFamOther);
+    HIP_TRY(launch_reduce_partials(part.p, plan.npart, jc, b, h1.p, nullptr, 0, nullptr, 0, st));
+    timer.end(kFamOther, 8.0 * plan.npart * (double)jc * b, 0.0);
+    timer.begin(kFamUpdate);
+    HIP_TRY(launch_update_gram(basis.p, n, ld, c0, jc, h1.p, b, nl, 0, gpart.p, st));
+    timer.end(kFamUpdate, 8.0 * (double)n * (jc + 2 * b), 2.0 * (double)n * jc * b);
+    return finish_start_block({hpair.p + b, c0, pair_pad()}, {h1.p, jc, kPP}, plan_update_gram(n), false);
+  }
+
+  // The second pass over all locked vectors, which the device leaves out where the passes before it have removed little (as in
+  // enqueue_cgs_adaptive).  ngram Gram partials are in gpart, by a projection of the block on itself or by the fused update.
+  int finish_start_block(Removed h, Removed h2, int ngram, bool by_project) {
+    HIP_TRY(launch_reduce_partials(gpart.p, ngram, b, b, gram(), nullptr, 0, nullptr, 0, st));
+    HIP_TRY(launch_second_pass_test(h, h2, b, gram(), kSecondPassRatio2, flag.p, st));
+    const ProjectPlan plan = plan_project(n, nl, kMaxPartials);
+    HIP_TRY(launch_project(basis.p, n, ld, 0, nl, nl, b, plan, part.p, st, flag.p));
+    HIP_TRY(launch_reduce_partials(part.p, plan.npart, nl, b, h1.p, nullptr, 0, nullptr, 0, st, flag.p));
+    if (by_project) {
+      HIP_TRY(launch_row_gemm(basis.p, n, ld, 0, nl, h1.p, kPP, b, 0, nl, nullptr, 0, nullptr, st, flag.p));
+      const ProjectPlan gplan = plan_project(n, b, kMaxPartials);
+      HIP_TRY(launch_project(basis.p, n, ld, nl, b, nl, b, gplan, gpart.p, st, flag.p));
+    } else {
+      HIP_TRY(launch_update_gram(basis.p, n, ld, 0, nl, h1.p, b, nl, 0, gpart.p, st, flag.p));
+    }
+    return ngram;
   }
 
   // Decide the filter of the next start block from the Ritz values theta (ascending, ghosts at the bottom).
@@ -1599,12 +1689,33 @@ struct Solver {
       // the random block; when it goes into the filter as it is (the wide blocks' operand is a plain packed copy) it is
       // drawn into the packed buffer directly: same numbers, one pass less
       const bool use_v0 = v0 && stats.phases == 1;
+      // A block that waits from the phase before, unless that phase has shown that its filter was too weak.
+      const bool from_ahead = ahead.ready && filtered && late_projection && prev_filtered_steps == 1;
+      ahead.ready = false;
+      if (from_ahead) {
+        phase_rate = filt_extra == ahead.extra ? ahead.rate : 0.0;
+        start_pairs.fetch_add(1, std::memory_order_relaxed);
+      }
       const bool random_packed = filtered && late_projection && val_s.p && !use_v0;
       // ... and where the one-launch filter takes every row it makes those numbers itself: no pass to write them
       const bool random_inside = random_packed && resident.usable && resident.rest_row0 >= n && !no_random_inside;
-      uint64_t rnd_key = 0;
-      if (random_inside) {
+      // Two start blocks at once, this phase's and the next one's, where the locked vectors are what a phase costs to read: one
+      // pass over them takes both through the first Gram-Schmidt pass (500,000 rows, 64 columns instead of 32: the passes of the
+      // 2,000-component solve 118 -> 95 ms), and the filter has twice the work items, which evens out its last round.  The second
+      // one is projected against what this phase locks when its turn comes.  Not while the filter's degree is still being
+      // found, nor where the phase after this one may have to project before the filter: the second block would be made for nothing.
+      const bool pair = random_packed && !from_ahead && !no_start_pairs && !verifying && !last_cycle_phase && k - nl > b && nl > 0 &&
+                        (double)n * nl >= pair_min_work && prev_filtered_steps == 1 && more_degrees <= 0 && rw_next <= 0.25 * tol &&
+                        (random_inside ? rot_cols >= (size_t)4 * b
+                                       : !resident.usable && 2 * b <= kMaxBlock && rot_cols >= (size_t)7 * b);
+      uint64_t rnd_key = 0, rnd_key2 = 0;
+      if (from_ahead) {
+        HIP_TRY(launch_copy_cols(ahead_block(), b, 0, basis.p, ld, nl, b, n, st));
+      } else if (random_inside) {
         rnd_key = random_block_key(seed, stream_id++);
+        if (pair) rnd_key2 = random_block_key(seed, stream_id++);
+      } else if (pair) {
+        rnd_key = stream_id++;
       } else if (random_packed) {
         HIP_TRY(launch_random_block(z.p, n, b, 0, b, seed, stream_id++, st));
       } else {
@@ -1612,26 +1723,36 @@ struct Solver {
         if (use_v0)  // the caller's start vector leads the first block, the other columns stay random
           HIP_TRY(launch_set_column(basis.p, n, ld, nl, v0, rowmap, st));
       }
-      if (filtered) {
+      if (from_ahead) {
+        filt_d = 0;
+      } else if (filtered) {
         if (debug_on())
-          std::fprintf(stderr, "[sceig] t=%.4fs phase %d start block filtered: degree %d, damped interval [%.4f, %.6f]%s\n",
+          std::fprintf(stderr, "[sceig] t=%.4fs phase %d start block filtered: degree %d, damped interval [%.4f, %.6f]%s%s\n",
                        now_s() - t_begin, stats.phases, filt_d, filt_lo, filt_a,
-                       late_projection ? ", locked vectors projected out afterwards" : "");
+                       late_projection ? ", locked vectors projected out afterwards" : "", pair ? ", with the next one's" : "");
         if (!late_projection)
           (void)enqueue_cgs2(basis.p, n, ld, nl, nl, b, nl, part.p, h1.p, hsum.p, nullptr, 0, nullptr, st, &timer);
         if (!random_packed) HIP_TRY(launch_pack_scaled(basis.p + nl, ld, zs(), n, b, z.p, st));
-        apply_start_filter(filt_d, filt_a, rnd_key, random_inside ? 1 : 0);
+        apply_start_filter(filt_d, filt_a, rnd_key, random_inside ? 1 : 0, pair, rnd_key2);
         filt_d = 0;
       }
       // a block that went into the filter orthogonal to the locked vectors picked up along them since only what is of
       // the order of their residuals relative to the block, so one projection removes it without cancellation
       const int ngram0 =
-          late_projection
+          pair ? project_pair()
+          : from_ahead ? project_rest()
+          : late_projection
               ? enqueue_cgs_adaptive(basis.p, n, ld, nl, nl, b, part.p, h1.p, hsum.p, gpart.p, gram(), flag.p, st, &timer)
               : enqueue_cgs2(basis.p, n, ld, nl, nl, b, filtered ? nl : 0, part.p, h1.p, hsum.p, nullptr, 0, gpart.p, st,
                              &timer);
       enqueue_block_qr(basis.p, n, ld, nl, b, part.p, gpart.p, ngram0, gram(), rinv(), r1(), slot(0) + kPP * kPP,
                        slot(0) + 2 * kPP * kPP, z.p, zs(), st, &timer);
+      if (pair) {
+        ahead.ready = true;
+        ahead.from = nl;
+        ahead.extra = filt_extra;
+        ahead.rate = phase_rate;
+      }
       int ja = b;            // active columns whose coupling is (or will be) assembled
       int assembled = 0;     // active columns of T that are final (their block has been multiplied by S)
       int next_slot = 1;     // slot 0 = start block QR
@@ -1820,6 +1941,7 @@ struct Solver {
             }
             more_degrees = filt_extra - extra;
             rw_before = rw;
+            rw_next = rw * ahead_of;
             if (debug_on())
               std::fprintf(stderr, "[sceig] first residual %.2e, aim %.2e: degrees %+d%s\n", rw, target, filt_extra,
                            at_floor ? ", at the floor" : "");
@@ -1967,6 +2089,7 @@ struct Solver {
         if (full) {
           // ---- thick restart: keep the leading Ritz vectors and the residual block
           cycles += 1;
+          ahead.ready = false;  // the rotation takes the workspace it waits in
           stats.restarts += 1;
           check_open = false;
           const int l = l_restart;
@@ -2475,6 +2598,7 @@ int64_t sc_counter(int32_t which) {
     case SC_COUNTER_RESIDENT_FILTERS: return resident_launches.load(std::memory_order_relaxed);
     case SC_COUNTER_GROUPED_SEARCHES: return grouped_searches.load(std::memory_order_relaxed);
     case SC_COUNTER_FP64_SEARCHES: return fp64_searches.load(std::memory_order_relaxed);
+    case SC_COUNTER_START_PAIRS: return start_pairs.load(std::memory_order_relaxed);
     case SC_COUNTER_SCREENED_LABELLINGS: return screened_labellings.load(std::memory_order_relaxed);
     default: return -1;
   }
@@ -2647,7 +2771,8 @@ int sc_workspace_bytes(int64_t n, int64_t nnz, int32_t k, const sc_options* opt,
              up(sliced_scan_workspace((int)std::min<int64_t>(n, INT32_MAX)));
   }
   total += up(N * ld * 8) + up(N * (size_t)b * 8) + up(N * rot_cols * 8);  // basis, packed block, rotation workspace
-  total += up((size_t)kMaxPartials * jmax * kPP * 8) + up((size_t)kGramPartials * kPP * kPP * 8) + 2 * up(jmax * kPP * 8);
+  total += up((size_t)kMaxPartials * jmax * kPP * 8) + up((size_t)kGramPartials * kPP * kPP * 8) + 2 * up(jmax * kPP * 8) +
+           up(jmax * kPairPad * 8);
   total += up((size_t)(m / b + 4) * kSlotDoubles * 8) + up(jmax * std::max<size_t>(rot_cols, (size_t)k) * 8);
   if (o.flags & SC_FLAG_COMPONENT_NULLSPACE) total += up(N * 8) + up(N * 4) + up(N * 8);
   total += up((size_t)3 * kPP * kPP * 8) + up((size_t)k * 4);  // small matrices, the output permutation

@@ -12,6 +12,7 @@ namespace sceig {
 constexpr int kMaxBlock = 32;      // largest Lanczos block size
 constexpr int kLongRow = 128;      // rows with more entries than this are "long" for the wide sparse products
 constexpr int kPartialPad = 32;    // column stride of partial / coefficient blocks (>= kMaxBlock)
+constexpr int kPairPad = 64;       // the same for two blocks side by side of more than kMaxBlock columns together
 
 // ---- setup ---------------------------------------------------------------------------------
 // flag[0] |= 1 if rowptr is not monotone / rowptr[0] != 0, |= 2 if a column is out of range.
@@ -50,9 +51,11 @@ struct ProjectPlan {
   int npart;           // number of partial blocks produced = row panels (one per workgroup: waves that share a
                        // column tile add their sums inside the workgroup)
 };
-ProjectPlan plan_project(int64_t n, int ja, int max_partials);
+// max_partials: partial blocks of kPartialPad columns that there is room for.
+ProjectPlan plan_project(int64_t n, int ja, int max_partials, int b = 1);
 // part[p][c][t] (c < ja, t < kPartialPad) = sum over the rows of partial p of A[i, acol0 + c] * B[i, bcol0 + t]
-// with A and B both columns of `basis` (row-major n x ld); t >= b entries are written as 0.
+// with A and B both columns of `basis` (row-major n x ld); t >= b entries are written as 0.  b <= 2 kMaxBlock, with the plan
+// for that b; kPairPad takes the place of kPartialPad, here and in launch_reduce_partials, where b > kMaxBlock.
 // skip (here and below; may be null): device int; if *skip != 0 when the kernel starts, the launch does nothing.
 hipError_t launch_project(const double* basis, int64_t n, int64_t ld, int acol0, int ja, int bcol0, int b,
                           const ProjectPlan& plan, double* part, hipStream_t st, const int* skip = nullptr);
@@ -63,13 +66,17 @@ hipError_t launch_reduce_partials(const double* part, int npart, int ja, int b, 
                                   int accumulate, double* slot, int slot_row0, hipStream_t st,
                                   const int* skip = nullptr);
 // skip[0] = 1 when no column of the block needs a second Gram-Schmidt pass: for every column t < b the squared norm
-// the first pass removed, sum_c h[c*kPartialPad + t]^2 over c < ja, is at most ratio2 times the squared norm it kept,
-// gram[t*kPartialPad + t]; else skip[0] = 0.
-hipError_t launch_second_pass_test(const double* h, int ja, int b, const double* gram, double ratio2, int* skip,
+// the first pass removed, the sum of the squares of the t-th column of h (rows x b, row stride pad) and of h2, is at most ratio2
+// times the squared norm it kept, gram[t*kPartialPad + t]; else skip[0] = 0.
+struct Removed {
+  const double* h = nullptr;
+  int rows = 0, pad = kPartialPad;
+};
+hipError_t launch_second_pass_test(Removed h, Removed h2, int b, const double* gram, double ratio2, int* skip,
                                    hipStream_t st);
 
 // C = A * B row GEMM:  A = basis[:, acol0 : acol0+kdim] (n x kdim), B = bmat (kdim x ncols, row-major, ldb).
-// mode 0: basis[:, ccol0 + t] -= C[:, t]          (in place update, ncols <= 32, out unused)
+// mode 0: basis[:, ccol0 + t] -= C[:, t]          (in place update, ncols <= 64, out unused)
 // mode 1: out[i*ldo + t]  = C[i, t]                (row-major)
 // mode 2: out[t*ldo + r(i)] = C[i, t]             (column-major; r(i) = rowmap[i] if rowmap != null, else i)
 // mode 3: basis[:, ccol0 + t] = C[:, t]           (ncols <= 64, out unused; the columns written may be among the
@@ -150,11 +157,13 @@ hipError_t launch_block_extra_chunks(const int64_t* rowptr, const int32_t* start
 // rounded to float), the rest in double; sliced items take all steps in double.  0 gives the recurrence in double.
 // use_rnd != 0: x is not read; the operand is the random block of key rnd_key (random_block_key), entry by entry as
 // launch_random_block would have written it into a packed n x b buffer.
+// copies = 2 (use_rnd only): the same for the random block of key rnd_key2, whose result goes to the b columns behind y's.
 hipError_t launch_cheb_resident(const int64_t* rowptr, const int32_t* col, const double* val, const double* x, double* y,
                                 int64_t ldy, int b, int d, double alpha_first, double alpha_rest, double shift, const int32_t* items,
                                 int nitems, size_t lds_bytes, const uint16_t* scol, const double* sval,
                                 const int64_t* slice_base, const int32_t* slice_len, const int32_t* slice_first,
-                                const int32_t* row_extra, hipStream_t st, int d32 = 0, uint64_t rnd_key = 0, int use_rnd = 0);
+                                const int32_t* row_extra, hipStream_t st, int d32 = 0, uint64_t rnd_key = 0, int use_rnd = 0,
+                                int copies = 1, uint64_t rnd_key2 = 0);
 // key of random block number `stream_id` under `seed`: entry i * b + t of the block launch_random_block writes is
 // 2 u - 1 with u the top 53 bits of mix(key + i * b + t)
 uint64_t random_block_key(uint64_t seed, uint64_t stream_id);

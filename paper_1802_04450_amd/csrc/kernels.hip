@@ -607,7 +607,7 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void project_kernel(cons
   const int cbase = c0 + 4 * i;
   const bool full = vec_ok && (cbase + 3 < ja);
   // four row-quads (16 rows) per trip: all their loads are issued before the first MFMA needs them
-  constexpr int U = 4;
+  constexpr int U = NT == 4 ? 2 : 4;  // NT = 4: two row-quads, what the registers hold
   int64_t rstart = r0;
   // With all 16 NT block columns present and vector loads allowed, a wave runs the whole trips of its row slice
   // without a branch round any load: the operands of the next trip are requested before the MFMAs of
@@ -710,7 +710,8 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void project_kernel(cons
           for (int rr = 0; rr < 4; ++rr) acc[nt][q][rr] += theirs[((nt * 4 + q) * 4 + rr) * 64];
     }
   }
-  double* out = part + (int64_t)pidx * ja * kPartialPad;
+  constexpr int PAD = NT == 4 ? kPairPad : kPartialPad;
+  double* out = part + (int64_t)pidx * ja * PAD;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -718,7 +719,7 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void project_kernel(cons
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) {
         const int c = c0 + 4 * (4 * rr + g) + q;
-        if (c < ja) out[(int64_t)c * kPartialPad + i + 16 * nt] = acc[nt][q][rr];
+        if (c < ja) out[(int64_t)c * PAD + i + 16 * nt] = acc[nt][q][rr];
       }
 }
 
@@ -729,7 +730,7 @@ constexpr int kRedSplit = 32;
 constexpr int kRedElems = kThreads / kRedSplit;  // 32 output elements per workgroup
 __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const double* __restrict__ part, int npart, int ja,
                                                                    int ncol, double* __restrict__ h,
-                                                                   double* __restrict__ hsum, int accumulate,
+                                                                   double* __restrict__ hsum, int accumulate, int pad,
                                                                    double* __restrict__ slot, int slot_row0,
                                                                    const int* __restrict__ skip) {
   __shared__ double sub[kRedSplit][kRedElems + 1];
@@ -744,8 +745,8 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const double*
     const int p0 = r * chunk;
     int p1 = p0 + chunk;
     if (p1 > npart) p1 = npart;
-    const int64_t stride = (int64_t)ja * kPartialPad;
-    const double* p = part + (int64_t)c * kPartialPad + t;
+    const int64_t stride = (int64_t)ja * pad;
+    const double* p = part + (int64_t)c * pad + t;
     int q = p0;
     for (; q + 8 <= p1; q += 8) {  // eight independent loads in flight, added in index order
       double v[8];
@@ -762,13 +763,13 @@ __global__ __launch_bounds__(kThreads) void reduce_partials_kernel(const double*
     double tot = sub[0][el];
 #pragma unroll
     for (int q = 1; q < kRedSplit; ++q) tot += sub[q][el];
-    const int idx = c * kPartialPad + t;
+    const int idx = c * pad + t;
     if (h) h[idx] = tot;
     if (hsum) {
       if (accumulate) tot += hsum[idx];
       hsum[idx] = tot;
     }
-    if (slot && c >= slot_row0) slot[(c - slot_row0) * kPartialPad + t] = tot;
+    if (slot && c >= slot_row0) slot[(c - slot_row0) * pad + t] = tot;
   }
 }
 
@@ -2101,9 +2102,9 @@ hipError_t launch_spmm_vals_cheb(const int64_t* rowptr, const int32_t* col, cons
                                longrows, nlong, st, row_begin);
 }
 
-ProjectPlan plan_project(int64_t n, int ja, int max_partials) {
+ProjectPlan plan_project(int64_t n, int ja, int max_partials, int b) {
   ProjectPlan p;
-  p.nwc = ja <= 64 ? 1 : (ja <= 128 ? 2 : 4);
+  p.nwc = ja <= 64 && b <= kMaxBlock ? 1 : (ja <= 128 && b <= kMaxBlock ? 2 : 4);  // two blocks: no sums through LDS
   const int nwr = 4 / p.nwc;
   const int coltiles = (ja + 64 * p.nwc - 1) / (64 * p.nwc);
   // 512 workgroups in total, the two per compute unit that the registers allow (768 leave a second round half empty: both
@@ -2112,6 +2113,7 @@ ProjectPlan plan_project(int64_t n, int ja, int max_partials) {
   // (one per workgroup and column tile group) than the reduction is meant to sum
   int64_t panels = 512 / coltiles;
   if (panels < 16) panels = 16;
+  if (b > kMaxBlock) max_partials = max_partials * kPartialPad / kPairPad;
   if (panels > max_partials) panels = max_partials;
   int64_t rows = ceil_div64(n, panels);
   rows = ceil_div64(rows, 16 * nwr) * 16 * nwr;
@@ -2130,6 +2132,12 @@ hipError_t launch_project(const double* basis, int64_t n, int64_t ld, int acol0,
   // barrier needs every wave of such a workgroup to have a tile, which one tile group (ja <= 64 * nwc) guarantees
   const int nwr = 4 / plan.nwc;
   if (nwr > 1 && ja > 64 * plan.nwc) return hipErrorInvalidValue;
+  if (b > kMaxBlock) {
+    if (b > 2 * kMaxBlock || nwr > 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((project_kernel<4>), grid, dim3(kThreads), 0, st, basis, n, ld, acol0, ja, bcol0, b,
+                       plan.rows_per_panel, plan.nwc, vec_ok, part, skip);
+    return hipGetLastError();
+  }
   const int nt = b <= 16 ? 1 : 2;
   const size_t lds = nwr > 1 ? (size_t)(nwr - 1) * plan.nwc * 16 * nt * 64 * sizeof(double) : 0;
   if (b <= 16) {
@@ -2147,7 +2155,7 @@ hipError_t launch_reduce_partials(const double* part, int npart, int ja, int b, 
   if (ja <= 0) return hipSuccess;
   const int total = ja * b;
   hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((total + kRedElems - 1) / kRedElems)), dim3(kThreads), 0,
-                     st, part, npart, ja, b, h, hsum, accumulate, slot, slot_row0, skip);
+                     st, part, npart, ja, b, h, hsum, accumulate, b > kMaxBlock ? kPairPad : kPartialPad, slot, slot_row0, skip);
   return hipGetLastError();
 }
 
@@ -2166,7 +2174,7 @@ hipError_t launch_row_gemm(double* basis, int64_t n, int64_t ld, int acol0, int 
   } else if (ncols <= 32) {
     if (pipe) SC_LAUNCH_RG(2, 2, true, gx); else SC_LAUNCH_RG(2, 2, false, gx);
   } else {
-    if (mode == 0 || (mode == 3 && ncols > 64)) return hipErrorInvalidValue;
+    if ((mode == 0 || mode == 3) && ncols > 64) return hipErrorInvalidValue;
     const int64_t groups = (ncols + 63) / 64, grid = ceil_div64(gx, 8) * 8 * groups;
     // 64 rows a wave instead of 32: half the chunks of coefficients that the matrix instructions wait for, half the
     // coefficients read from LDS.  Where there are four rounds of workgroups and more (two a compute unit); fewer of them
@@ -2286,7 +2294,7 @@ bool gram_cholesky_takes_parts(int npart, int b) {
 // orthogonality error of about eps * sqrt(1 + removed / kept), which a second pass is needed for only when
 // removed > ratio2 * kept.  One workgroup; fixed summation order.
 constexpr int kTestThreads = 1024;  // 32 row classes per column: the coefficient block has up to m rows
-__global__ __launch_bounds__(kTestThreads) void second_pass_test_kernel(const double* __restrict__ h, int ja, int b,
+__global__ __launch_bounds__(kTestThreads) void second_pass_test_kernel(Removed h, Removed h2, int b,
                                                                         const double* __restrict__ gram, double ratio2,
                                                                         int* __restrict__ skip) {
   __shared__ double sub[kTestThreads];
@@ -2295,9 +2303,12 @@ __global__ __launch_bounds__(kTestThreads) void second_pass_test_kernel(const do
   const int t = threadIdx.x % kPartialPad, r = threadIdx.x / kPartialPad;
   double acc = 0.0;
   if (t < b)
-    for (int c = r; c < ja; c += kTestThreads / kPartialPad) {
-      const double v = h[(int64_t)c * kPartialPad + t];
-      acc += v * v;
+    for (int q = 0; q < 2; ++q) {
+      const Removed& x = q ? h2 : h;
+      for (int c = r; c < x.rows; c += kTestThreads / kPartialPad) {
+        const double v = x.h[(int64_t)c * x.pad + t];
+        acc += v * v;
+      }
     }
   sub[threadIdx.x] = acc;
   __syncthreads();
@@ -2352,9 +2363,9 @@ hipError_t launch_mfma_rate(double* sink, int shape, int workgroups, int iters, 
   return hipGetLastError();
 }
 
-hipError_t launch_second_pass_test(const double* h, int ja, int b, const double* gram, double ratio2, int* skip,
+hipError_t launch_second_pass_test(Removed h, Removed h2, int b, const double* gram, double ratio2, int* skip,
                                    hipStream_t st) {
-  hipLaunchKernelGGL(second_pass_test_kernel, dim3(1), dim3(kTestThreads), 0, st, h, ja, b, gram, ratio2, skip);
+  hipLaunchKernelGGL(second_pass_test_kernel, dim3(1), dim3(kTestThreads), 0, st, h, h2, b, gram, ratio2, skip);
   return hipGetLastError();
 }
 

@@ -613,9 +613,20 @@ __global__ __launch_bounds__(kRT) void cheb_resident_kernel(const int64_t* __res
                                                             const int32_t* __restrict__ slice_len,
                                                             const int32_t* __restrict__ slice_first,
                                                             const int32_t* __restrict__ row_extra, int d32,
-                                                            uint64_t rnd_key, int use_rnd) {
+                                                            uint64_t rnd_key, int use_rnd, int nitems, int copies,
+                                                            uint64_t rnd_key2) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int32_t* it = items + kItemInts * (int64_t)blockIdx.x;
+  int item = (int)blockIdx.x;
+  if (copies == 2) {
+    // an item of the one block and of the other on one XCD, one after the other: the sliced form's entries meet in its L2
+    item = (int)(blockIdx.x / 16 * 8 + blockIdx.x % 8);
+    if (item >= nitems) return;  // uniform
+    if (blockIdx.x / 8 % 2) {
+      y += b;
+      rnd_key = rnd_key2;
+    }
+  }
+  const int32_t* it = items + kItemInts * (int64_t)item;
   const int row0 = it[0], nr = it[1], col0 = it[2], cl = it[3] & 15, nx = it[3] >> 4;  // uniform over the workgroup
   if (cl == 4)
     resident_item<4>(rowptr, col, val, x, y, ldy, b, d, alpha_first, alpha_rest, shift, row0, nr, col0, nx, smem, d32, rnd_key, use_rnd);
@@ -1049,14 +1060,18 @@ hipError_t launch_cheb_resident(const int64_t* rowptr, const int32_t* col, const
                                 int64_t ldy, int b, int d, double alpha_first, double alpha_rest, double shift, const int32_t* items,
                                 int nitems, size_t lds_bytes, const uint16_t* scol, const double* sval,
                                 const int64_t* slice_base, const int32_t* slice_len, const int32_t* slice_first,
-                                const int32_t* row_extra, hipStream_t st, int d32, uint64_t rnd_key, int use_rnd) {
+                                const int32_t* row_extra, hipStream_t st, int d32, uint64_t rnd_key, int use_rnd,
+                                int copies, uint64_t rnd_key2) {
   if (nitems <= 0 || d <= 0) return hipSuccess;
+  if (copies < 1 || copies > 2 || (copies == 2 && (!use_rnd || ldy < 2 * b))) return hipErrorInvalidValue;
   if (d32 < 0 || d32 >= d) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&cheb_resident_kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cheb_resident_kernel, dim3((unsigned)nitems), dim3(kRT), lds_bytes, st, rowptr, col, val, x, y, ldy, b, d,
-                     alpha_first, alpha_rest, shift, items, scol, sval, slice_base, slice_len, slice_first, row_extra, d32, rnd_key, use_rnd);
+  const unsigned grid = copies == 2 ? (unsigned)((nitems + 7) / 8 * 16) : (unsigned)nitems;
+  hipLaunchKernelGGL(cheb_resident_kernel, dim3(grid), dim3(kRT), lds_bytes, st, rowptr, col, val, x, y, ldy, b, d,
+                     alpha_first, alpha_rest, shift, items, scol, sval, slice_base, slice_len, slice_first, row_extra, d32, rnd_key, use_rnd, nitems,
+                     copies, rnd_key2);
   return hipGetLastError();
 }
 

@@ -364,6 +364,36 @@ def test_filter_interval_with_a_wrong_spectrum_bottom(B, monkeypatch):
         assert compare.orthonormality_defect(vec) <= 1e-10
 
 
+# the one-launch filter with 32 and 16 columns, the products of a block twice as wide with 16 and 8; blocks of 4 make no pairs
+@pytest.mark.parametrize("config,n,comps,block,tol,resident", [(2, 40_000, 200, 32, 1e-8, True), (2, 60_001, 300, 32, 1e-7, True),
+                                                               (5, 100_000, 400, 16, 1e-7, True), (2, 20_000, 120, 16, 1e-8, False),
+                                                               (2, 12_003, 60, 8, 1e-7, False), (2, 30_000, 20, 4, 1e-8, False)])
+def test_two_start_blocks_at_once(B, monkeypatch, config, n, comps, block, tol, resident):
+    """Start blocks made in pairs: as many phases as one by one, and the null space as well resolved."""
+    cfg = wl.reduced(wl.CONFIGS[config], n=n, components=comps)
+    g, label, sigma = wl.build_config_graph(cfg, device="cuda")
+    rp, c, v, n = g
+    assert components.component_labels(rp, c, v)[0] == comps
+    basis = components.null_space(rp, c, v)
+    monkeypatch.setenv("SCEIG_PAIR_MIN_WORK", "1")
+    runs = []
+    for alone in ("", "1"):
+        if alone:
+            monkeypatch.setenv("SCEIG_NO_START_PAIRS", alone)
+        before = [B.sc_counter(x) for x in (B.SC_COUNTER_START_PAIRS, B.SC_COUNTER_RESIDENT_FILTERS)]
+        lam, vec, code, stats = solve(B, g, comps, tol, block=block, m=comps + 8 * block + 40)
+        after = [B.sc_counter(x) for x in (B.SC_COUNTER_START_PAIRS, B.SC_COUNTER_RESIDENT_FILTERS)]
+        assert code == B.SC_OK, stats
+        assert (after[0] > before[0]) == (not alone and block >= 8), stats
+        assert (after[1] > before[1]) == resident, stats
+        assert np.max(np.abs(lam)) <= tol
+        assert compare.residual_norms(rp, c, v, lam, vec).max() <= 10 * tol
+        assert np.max(compare.containment_defect(vec, basis)) <= 100 * tol
+        assert compare.orthonormality_defect(vec) <= 1e-10
+        runs.append(stats)
+    assert runs[0]["phases"] <= runs[1]["phases"] + 1, runs
+
+
 def test_release_cache_between_calls(B):
     """Workspace blocks are kept between calls; giving them back must not change any later result."""
     g = wl.disjoint_union(*[wl.ring(20 + 3 * t) for t in range(6)])
