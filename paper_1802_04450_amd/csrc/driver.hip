@@ -366,6 +366,8 @@ constexpr int kSlotDoubles = 3 * kPP * kPP;  // A, R, G
 constexpr int kMaxPartials = 512;
 constexpr double kAbsDrop2 = 1e-24;  // squared norm below which a residual column counts as zero
 constexpr double kRelDrop = 1e-12;   // squared sine below which a column counts as dependent
+// in the second factorization: a column that survived the first one has unit norm, so only exact zeros are dropped
+constexpr double kAbsDrop2Again = 0.25, kRelDropAgain = 1e-8;
 
 int pow2_floor(int x) {
   int p = 1;
@@ -507,11 +509,10 @@ void enqueue_block_qr(double* basis, int64_t n, int64_t ld, int col, int b, doub
     parts = gpart;
   }
   np = plan_update_gram(n);
-  // second pass: a column that survived the first pass has unit norm, so only exact zeros are dropped
   if (gram_cholesky_takes_parts(np, b)) {
-    HIP_TRY(launch_factor_apply_rinv(basis, n, ld, col, b, {parts, np, nullptr, r_out, r1, 0.25, 1e-8}, z, s, st));
+    HIP_TRY(launch_factor_apply_rinv(basis, n, ld, col, b, {parts, np, nullptr, r_out, r1, kAbsDrop2Again, kRelDropAgain}, z, s, st));
   } else {
-    factor(nullptr, r_out, r1, 0.25, 1e-8);
+    factor(nullptr, r_out, r1, kAbsDrop2Again, kRelDropAgain);
     HIP_TRY(launch_apply_rinv(basis, n, ld, col, b, rinv, z, s, st));
   }
   tm->end(kFamQr, (ngram > 0 ? 4.0 : 5.0) * blk + (z ? blk : 0.0), 4.0 * (double)n * b * b);
@@ -521,6 +522,7 @@ std::atomic<int64_t> resident_launches{0};  // sc_counter(SC_COUNTER_RESIDENT_FI
 std::atomic<int64_t> grouped_searches{0};   // sc_counter(SC_COUNTER_GROUPED_SEARCHES)
 std::atomic<int64_t> fp64_searches{0};      // sc_counter(SC_COUNTER_FP64_SEARCHES)
 std::atomic<int64_t> start_pairs{0};        // sc_counter(SC_COUNTER_START_PAIRS)
+std::atomic<int64_t> small_steps{0};        // sc_counter(SC_COUNTER_SMALL_STEPS)
 std::atomic<int64_t> screened_labellings{0};  // sc_counter(SC_COUNTER_SCREENED_LABELLINGS)
 
 // Plan of the LDS-resident Chebyshev filter (resident.hip) for one matrix and block width: the diagonal blocks of the
@@ -1076,6 +1078,9 @@ struct Solver {
   int filter_tail64 = std::getenv("SCEIG_FILTER_FP64_TAIL") ? std::atoi(std::getenv("SCEIG_FILTER_FP64_TAIL")) : 6;
   double pair_min_work = std::getenv("SCEIG_PAIR_MIN_WORK") ? std::atof(std::getenv("SCEIG_PAIR_MIN_WORK")) : 2e7;
   bool no_start_pairs = std::getenv("SCEIG_NO_START_PAIRS") != nullptr;
+  bool no_small_steps = std::getenv("SCEIG_NO_SMALL_STEPS") != nullptr;
+  // looks of a workgroup of a one-launch step for the others, each about 0.6 us; 0, for tests: none is ever found there
+  uint32_t step_polls = std::getenv("SCEIG_STEP_POLLS") ? (uint32_t)std::atoi(std::getenv("SCEIG_STEP_POLLS")) : 8192;
   bool tentative_two_passes = std::getenv("SCEIG_TENTATIVE_TWO_PASSES") != nullptr;
   // for tests of the check phase: the solve works for one pair more and gives up the unlock-th largest before that phase
   int unlock = std::getenv("SCEIG_UNLOCK") ? std::atoi(std::getenv("SCEIG_UNLOCK")) : -1;
@@ -1146,6 +1151,23 @@ struct Solver {
   int filt_extra = 0;       // degrees added to (or taken from) the planned degree: feedback from the phases' first steps
   sc_stats stats{};
   KTimer timer;
+
+  // Steps enqueued since slots were last fetched; groups: workgroups of the one launch that took it, 0: it was the ordinary ones.
+  struct Pending {
+    int ja, si;
+    bool tentative;
+    int groups;
+  };
+  std::vector<Pending> pending_steps;
+  uint32_t met = 0;  // workgroups x meetings of the one-launch steps so far
+  size_t lds_limit = 0;
+  // words 0 (validation, second-pass test), kSyncCount and kSyncAbort (one-launch steps) of one zeroed block
+  uint32_t* sync_words() { return reinterpret_cast<uint32_t*>(flag.p); }
+  // the entry of slot i that a one-launch step counts its finished workgroups in: past the columns that the slot's rows use
+  static_assert(kSmallStepBlock < kPP, "a slot's rows leave room");
+  static_assert(kSmallStepGroups <= kMaxPartials && 2 * kSmallStepGroups * kSmallStepBlock * kSmallStepBlock <= kGramPartials * kPP * kPP,
+                "a one-launch step's partial sums fit where the ordinary launches' do");
+  int* done_word(double* slot) { return reinterpret_cast<int*>(slot + kPP - 1); }
 
   // the last b columns of the rotation workspace, which only a rotation of more vectors than b less than it holds takes (a restart)
   double* ahead_block() { return rot.p + (size_t)n * (rot_cols - b); }
@@ -1251,10 +1273,10 @@ struct Solver {
 
   void setup() {
     const double t0 = now_s();
-    flag.alloc(1);
+    flag.alloc(kSyncWords);
     marks.alloc(2);
     int32_t &hflag = marks.p[0], &hcount = marks.p[1];
-    HIP_TRY(hipMemsetAsync(flag.p, 0, sizeof(int), st));
+    HIP_TRY(hipMemsetAsync(flag.p, 0, kSyncWords * sizeof(int), st));
     HIP_TRY(hipMemcpyAsync(&nnz, rowptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (nnz < 0) SC_THROW(SC_ECSR);
@@ -1346,6 +1368,54 @@ struct Solver {
   // vectors, the most expensive thing a step does once many are locked, is never made for them; if the test fails
   // the step is taken again in full.
   void enqueue_step(int ja, int si, bool tentative = false) {
+    stats.block_steps += 1;
+    stats.spmv_cols += b;
+    pending_steps.push_back({ja, si, tentative, tentative ? 0 : enqueue_small_step(ja, si)});
+    if (!pending_steps.back().groups) enqueue_step_launches(ja, si, tentative);
+  }
+
+  // The step as one launch, where it is for that kernel; returns the number of its workgroups, else 0.
+  int enqueue_small_step(int ja, int si) {
+    const int jt = nl + ja;
+    if (no_small_steps || b != kSmallStepBlock || !val_s.p || nlong > 0) return 0;
+    if (!lds_limit) lds_limit = (size_t)device_lds_limit();
+    SmallStep a;
+    a.rows = small_step_rows(n, jt, lds_limit);
+    if (!a.rows) return 0;
+    const int groups = small_step_groups(n, a.rows);
+    double* sl = slot(si);
+    a.rowptr = rowptr;
+    a.col = col;
+    a.val = val_s.p;
+    a.basis = basis.p;
+    a.z = z.p;
+    a.n = n;
+    a.ld = ld;
+    a.j = jt;
+    a.from1 = 0;
+    a.from2 = nl;
+    a.part = part.p;
+    a.gpart = gpart.p;
+    a.h = h1.p;
+    a.slot_a = sl;
+    a.slot_r = sl + kPP * kPP;
+    a.slot_g = sl + 2 * kPP * kPP;
+    a.done = done_word(sl);
+    a.sync = sync_words();
+    a.base = met;
+    a.polls = step_polls;
+    a.abs_tol2[0] = kAbsDrop2;
+    a.rel_tol[0] = kRelDrop;
+    a.abs_tol2[1] = kAbsDrop2Again;
+    a.rel_tol[1] = kRelDropAgain;
+    met += (uint32_t)groups * small_step_meetings(jt, a.from1, a.from2);
+    timer.begin(kFamOther);
+    HIP_TRY(launch_small_step(a, lds_limit, st));
+    timer.end(kFamOther, spmm_bytes() + 8.0 * (double)n * (jt + 2 * b), 2.0 * (double)nnz * b + 4.0 * (double)n * (2 * jt - nl + b) * b);
+    return groups;
+  }
+
+  void enqueue_step_launches(int ja, int si, bool tentative) {
     const int jt = nl + ja;
     timer.begin(kFamSpmm);
     spmm_from_z(basis.p + jt, ld);
@@ -1369,8 +1439,6 @@ struct Solver {
       enqueue_block_qr(basis.p, n, ld, jt, b, part.p, gpart.p, ngram, gram(), rinv(), r1(), sl + kPP * kPP,
                        sl + 2 * kPP * kPP, z.p, zs(), st, &timer);
     }
-    stats.block_steps += 1;
-    stats.spmv_cols += b;
   }
 
   void fetch_slots(int first, int count) {
@@ -1379,6 +1447,25 @@ struct Solver {
                            (size_t)count * kSlotDoubles * sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     ystage_busy = false;
+    for (size_t q = 0; q < pending_steps.size(); ++q) {
+      const Pending& p = pending_steps[q];
+      if (!p.groups) continue;
+      if (*done_word(slots_host.p + (size_t)p.si * kSlotDoubles) == p.groups) {
+        small_steps.fetch_add(1, std::memory_order_relaxed);
+        continue;
+      }
+      // Its workgroups did not all come to run: the step and those behind it are taken again by the ordinary launches, from the
+      // basis block that it started from.  No further step is tried that way in this solve.
+      if (debug_on()) std::fprintf(stderr, "[sceig] a step's workgroups did not meet: ordinary launches from here on\n");
+      no_small_steps = true;
+      std::vector<Pending> again(pending_steps.begin() + q, pending_steps.end());
+      pending_steps.clear();
+      HIP_TRY(launch_pack_scaled(basis.p + nl + again[0].ja - b, ld, zs(), n, b, z.p, st));
+      for (const Pending& r : again) enqueue_step_launches(r.ja, r.si, r.tentative);
+      fetch_slots(first, count);
+      return;
+    }
+    pending_steps.clear();
   }
 
   // Start-block filter.  The block at columns [nl, nl+b) (orthonormal, its s-scaled packed copy in z) is replaced
@@ -2599,6 +2686,7 @@ int64_t sc_counter(int32_t which) {
     case SC_COUNTER_GROUPED_SEARCHES: return grouped_searches.load(std::memory_order_relaxed);
     case SC_COUNTER_FP64_SEARCHES: return fp64_searches.load(std::memory_order_relaxed);
     case SC_COUNTER_START_PAIRS: return start_pairs.load(std::memory_order_relaxed);
+    case SC_COUNTER_SMALL_STEPS: return small_steps.load(std::memory_order_relaxed);
     case SC_COUNTER_SCREENED_LABELLINGS: return screened_labellings.load(std::memory_order_relaxed);
     default: return -1;
   }

@@ -114,6 +114,44 @@ hipError_t launch_factor_apply_rinv(double* basis, int64_t n, int64_t ld, int co
 hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const double* rinv, double* z,
                              const double* s, hipStream_t st);
 
+// One block step, or the start block's Gram-Schmidt and QR, as one launch whose workgroups meet five to seven times: for few
+// rows, where the launches of a step are each as long as a launch takes at least.  Columns [j, j + kSmallStepBlock) of the
+// basis become the product of the operator (rowptr, col, val) with z, or stay as they are where val is null; then they are
+// orthogonalized against columns [from1, j) and once more against [from2, j) (from >= j: not), made orthonormal by two
+// Cholesky QRs as launch_gram_cholesky does, and z becomes a packed copy of them.  slot_a (may be null): the sum of both passes'
+// coefficients of columns [j - kSmallStepBlock, j); slot_g: the Gram matrix before the first factorization; slot_r: the factor
+// of both; rows of kPartialPad.
+// The workgroups wait for one another, `polls` looks each time.  If one is then still missing (other work holds the compute
+// units), sync[kSyncAbort] is raised and this launch and all further ones with this sync leave without a result: the caller
+// finds that out by *done, the number of workgroups that have finished, and takes the step by other launches.  base: what
+// sync[kSyncCount] has counted before, workgroups x meetings of all launches since both words were zero.
+constexpr int kSmallStepBlock = 8;
+constexpr int kSmallStepGroups = 128;   // workgroups at most: two such launches fit on the chip's 256 compute units side by side
+constexpr int kSmallStepColumns = 256;  // j at most
+constexpr int kSyncCount = 16, kSyncAbort = 48, kSyncWords = 64;  // words on cache lines of their own
+struct SmallStep {
+  const int64_t* rowptr = nullptr;
+  const int32_t* col = nullptr;
+  const double* val = nullptr;
+  double *basis = nullptr, *z = nullptr;
+  int64_t n = 0, ld = 0;
+  int j = 0, from1 = 0, from2 = 0;
+  int rows = 0;             // rows a workgroup (small_step_rows)
+  double* part = nullptr;   // workgroups x j x kSmallStepBlock
+  double* gpart = nullptr;  // 2 x workgroups x kSmallStepBlock^2
+  double* h = nullptr;      // j x kSmallStepBlock
+  double *slot_a = nullptr, *slot_g = nullptr, *slot_r = nullptr;
+  int* done = nullptr;
+  uint32_t* sync = nullptr;
+  uint32_t base = 0, polls = 0;
+  double abs_tol2[2] = {0.0, 0.0}, rel_tol[2] = {0.0, 0.0};
+};
+// Rows a workgroup takes; 0: the step is not for this kernel (too many rows, or columns for a workgroup's LDS).
+int small_step_rows(int64_t n, int j, size_t lds_limit);
+inline int small_step_groups(int64_t n, int rows) { return (int)((n + rows - 1) / rows); }
+inline uint32_t small_step_meetings(int j, int from1, int from2) { return 2 + (from1 < j ? 2 : 0) + (from2 < j ? 2 : 0); }
+hipError_t launch_small_step(const SmallStep& a, size_t lds_limit, hipStream_t st);
+
 // Fused variant used inside the block step (same arithmetic as the separate kernels):
 //   update_gram: basis[:, ccol0 : ccol0+b] -= basis[:, acol0 : acol0+kdim] * bmat (bmat kdim x b, row stride
 //                kPartialPad) and

@@ -616,3 +616,37 @@ def test_check_phase_with_weights_below_zero(B, block):
     # the rest's spectrum is dense at its upper end: nothing there converges in a few steps
     steps = stats["block_steps"] - locking["block_steps"]
     assert steps >= 15, steps
+
+
+# rows on either side of a workgroup's share and of the most that 128 workgroups take; with m = 300 and no filter a basis that
+# outgrows the workgroups' LDS (128 columns of 128 rows), so that both forms take turns
+@pytest.mark.parametrize("n,k,m,way", [(60, 3, 0, "one"), (65, 4, 0, "one"), (129, 6, 0, "one"), (2000, 9, 0, "one"),
+                                       (4033, 10, 0, "one"), (8192, 12, 0, "one"), (8193, 12, 300, "both"),
+                                       (16384, 8, 0, "one"), (16385, 8, 0, "none"), (2000, 9, 0, "hub")])
+def test_block_step_as_one_launch(B, monkeypatch, n, k, m, way):
+    """Steps whose workgroups meet inside one launch, the ordinary launches, and a solve whose first step finds its workgroups
+    missing (none is ever seen to arrive): the same pairs."""
+    rp, c, v, n = wl.random_weighted_connected(n, 4 * n, 5 + n)
+    if way == "hub":  # a row too long for a lane group: node 0 is tied to 200 others
+        rp, c, v, n = wl.disjoint_union((rp, c, v, n), wl.complete_bipartite(1, 200))
+    g = (rp, c, v, n)
+    flags = B.SC_FLAG_NO_START_FILTER if way == "both" else 0
+    runs = []
+    for env in ({}, {"SCEIG_NO_SMALL_STEPS": "1"}, {"SCEIG_STEP_POLLS": "0"}):
+        for name, value in env.items():
+            monkeypatch.setenv(name, value)
+        before = B.sc_counter(B.SC_COUNTER_SMALL_STEPS)
+        lam, vec, code, stats = solve(B, g, k, 1e-9, block=8, m=m, flags=flags)
+        taken = B.sc_counter(B.SC_COUNTER_SMALL_STEPS) - before
+        for name in env:
+            monkeypatch.delenv(name)
+        assert code == B.SC_OK, stats
+        if env or way in ("none", "hub"):
+            assert taken == 0, (env, taken)
+        else:
+            assert 0 < taken <= stats["block_steps"] and (way == "both" or taken == stats["block_steps"]), (taken, stats)
+            assert way != "both" or taken < stats["block_steps"], (taken, stats)
+        assert compare.residual_norms(rp, c, v, lam, vec).max() <= 1e-8
+        assert compare.orthonormality_defect(vec) <= 1e-12
+        runs.append(lam)
+    assert np.max(np.abs(runs[0] - runs[1])) <= 1e-11 and np.max(np.abs(runs[2] - runs[1])) <= 1e-11
