@@ -491,7 +491,8 @@ int sc_version(void);
  *   SC_COUNTER_SCREENED_LABELLINGS  labelling steps of k-means in which the reduced-precision screen left at most a quarter of
  *                                the points to the fp64 labelling
  *   SC_COUNTER_START_PAIRS       phases of sc_laplacian_eigsh whose start block was made together with the phase's before
- *   SC_COUNTER_SMALL_STEPS       block steps of sc_laplacian_eigsh that ran as one launch
+ *   SC_COUNTER_FUSED_STEPS       block steps of sc_laplacian_eigsh that ran as one launch
+ *   SC_COUNTER_FUSED_QRS         block QRs of sc_laplacian_eigsh, other than those steps', that ran as one launch
  *   SC_COUNTER_FP64_SEARCHES     sc_knn_search calls whose screen left queries to the fp64 search through all points
  * Returns the count, or -1 for an unknown id.
  */
@@ -500,7 +501,8 @@ int sc_version(void);
 #define SC_COUNTER_SCREENED_LABELLINGS 2
 #define SC_COUNTER_FP64_SEARCHES 3
 #define SC_COUNTER_START_PAIRS 4
-#define SC_COUNTER_SMALL_STEPS 5
+#define SC_COUNTER_FUSED_STEPS 5
+#define SC_COUNTER_FUSED_QRS 6
 int64_t sc_counter(int32_t which);
 
 /*

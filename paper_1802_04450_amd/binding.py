@@ -131,7 +131,8 @@ SC_COUNTER_GROUPED_SEARCHES = 1
 SC_COUNTER_SCREENED_LABELLINGS = 2
 SC_COUNTER_FP64_SEARCHES = 3
 SC_COUNTER_START_PAIRS = 4
-SC_COUNTER_SMALL_STEPS = 5
+SC_COUNTER_FUSED_STEPS = 5
+SC_COUNTER_FUSED_QRS = 6
 
 
 def sc_counter(which: int) -> int:

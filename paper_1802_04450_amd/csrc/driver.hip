@@ -369,6 +369,19 @@ constexpr double kRelDrop = 1e-12;   // squared sine below which a column counts
 // in the second factorization: a column that survived the first one has unit norm, so only exact zeros are dropped
 constexpr double kAbsDrop2Again = 0.25, kRelDropAgain = 1e-8;
 
+constexpr size_t kFusedLds = 160 * 1024;  // a workgroup of the fused launches takes at most
+
+// An area for the sums under way in one fused launch of a solve (launch_fused_step, launch_fused_qr); 0: it has none.
+size_t fused_exchange_doubles(int64_t n, int m, int b) {
+  int64_t len = 0;
+  const int qr = fused_qr_rows(n, b, kFusedLds);
+  if (qr) len = fused_exchange(fused_groups(n, qr), 0, 0, b);
+  const int jmax = std::min(m, kFusedColumns);
+  const int rows = b == kFusedStepBlock ? fused_step_rows(n, kFusedStepBlock, kFusedLds) : 0;
+  if (rows) len = std::max(len, fused_exchange(fused_groups(n, rows), jmax, jmax, b));
+  return (size_t)len;
+}
+
 int pow2_floor(int x) {
   int p = 1;
   while (p * 2 <= x) p *= 2;
@@ -522,7 +535,8 @@ std::atomic<int64_t> resident_launches{0};  // sc_counter(SC_COUNTER_RESIDENT_FI
 std::atomic<int64_t> grouped_searches{0};   // sc_counter(SC_COUNTER_GROUPED_SEARCHES)
 std::atomic<int64_t> fp64_searches{0};      // sc_counter(SC_COUNTER_FP64_SEARCHES)
 std::atomic<int64_t> start_pairs{0};        // sc_counter(SC_COUNTER_START_PAIRS)
-std::atomic<int64_t> small_steps{0};        // sc_counter(SC_COUNTER_SMALL_STEPS)
+std::atomic<int64_t> fused_steps{0};        // sc_counter(SC_COUNTER_FUSED_STEPS)
+std::atomic<int64_t> fused_qrs{0};          // sc_counter(SC_COUNTER_FUSED_QRS)
 std::atomic<int64_t> screened_labellings{0};  // sc_counter(SC_COUNTER_SCREENED_LABELLINGS)
 
 // Plan of the LDS-resident Chebyshev filter (resident.hip) for one matrix and block width: the diagonal blocks of the
@@ -1078,9 +1092,9 @@ struct Solver {
   int filter_tail64 = std::getenv("SCEIG_FILTER_FP64_TAIL") ? std::atoi(std::getenv("SCEIG_FILTER_FP64_TAIL")) : 6;
   double pair_min_work = std::getenv("SCEIG_PAIR_MIN_WORK") ? std::atof(std::getenv("SCEIG_PAIR_MIN_WORK")) : 2e7;
   bool no_start_pairs = std::getenv("SCEIG_NO_START_PAIRS") != nullptr;
-  bool no_small_steps = std::getenv("SCEIG_NO_SMALL_STEPS") != nullptr;
-  // looks of a workgroup of a one-launch step for the others, each about 0.6 us; 0, for tests: none is ever found there
-  uint32_t step_polls = std::getenv("SCEIG_STEP_POLLS") ? (uint32_t)std::atoi(std::getenv("SCEIG_STEP_POLLS")) : 8192;
+  bool no_fused = std::getenv("SCEIG_NO_FUSED") != nullptr;
+  // looks of a fused launch's workgroup for the others' start, each about 0.6 us; -1, for tests: the word is stopped beforehand
+  int fused_polls = std::getenv("SCEIG_FUSED_POLLS") ? std::atoi(std::getenv("SCEIG_FUSED_POLLS")) : 2048;
   bool tentative_two_passes = std::getenv("SCEIG_TENTATIVE_TWO_PASSES") != nullptr;
   // for tests of the check phase: the solve works for one pair more and gives up the unlock-th largest before that phase
   int unlock = std::getenv("SCEIG_UNLOCK") ? std::atoi(std::getenv("SCEIG_UNLOCK")) : -1;
@@ -1152,21 +1166,25 @@ struct Solver {
   sc_stats stats{};
   KTimer timer;
 
-  // Steps enqueued since slots were last fetched; groups: workgroups of the one launch that took it, 0: it was the ordinary ones.
+  // Steps (si > 0), and the start block's QR (si = 0), enqueued since slots were last fetched.  groups: workgroups of the one
+  // launch (launch_fused_step, launch_fused_qr) that they or their QR went through; 0: there was none.
   struct Pending {
     int ja, si;
     bool tentative;
     int groups;
+    bool whole;  // it was the whole step
   };
   std::vector<Pending> pending_steps;
-  uint32_t met = 0;  // workgroups x meetings of the one-launch steps so far
+  // What those launches share: the word that counts their workgroups, behind the validation flag in one zeroed block, and two
+  // areas for the sums under way, which take turns.
+  uint32_t arrivals = 0;  // workgroups so far
+  DevBuf<double> exchange;
+  size_t exchange_len = 0;  // doubles of an area
+  int64_t exchange_used = 0;  // by the last launch
+  int exchange_turn = 0;
   size_t lds_limit = 0;
-  // words 0 (validation, second-pass test), kSyncCount and kSyncAbort (one-launch steps) of one zeroed block
-  uint32_t* sync_words() { return reinterpret_cast<uint32_t*>(flag.p); }
-  // the entry of slot i that a one-launch step counts its finished workgroups in: past the columns that the slot's rows use
-  static_assert(kSmallStepBlock < kPP, "a slot's rows leave room");
-  static_assert(kSmallStepGroups <= kMaxPartials && 2 * kSmallStepGroups * kSmallStepBlock * kSmallStepBlock <= kGramPartials * kPP * kPP,
-                "a one-launch step's partial sums fit where the ordinary launches' do");
+  // the entry of slot i that a fused launch counts its finished workgroups in: past the columns that the slot's rows use
+  static_assert(16 < kPP, "a slot's rows leave room");
   int* done_word(double* slot) { return reinterpret_cast<int*>(slot + kPP - 1); }
 
   // the last b columns of the rotation workspace, which only a rotation of more vectors than b less than it holds takes (a restart)
@@ -1339,6 +1357,13 @@ struct Solver {
     h1.alloc((size_t)jmax * kPP);
     hsum.alloc((size_t)jmax * kPP);
     hpair.alloc((size_t)jmax * pair_pad());
+    exchange_len = no_fused ? 0 : fused_exchange_doubles(n, (int)m, b);
+    if (exchange_len) {
+      lds_limit = std::min((size_t)device_lds_limit(), kFusedLds);
+      exchange.alloc(2 * exchange_len);
+      HIP_TRY(hipMemsetAsync(exchange.p, 0xff, 2 * exchange_len * sizeof(double), st));
+      if (fused_polls < 0) HIP_TRY(hipMemsetAsync(flag.p + kSyncWord, 0x80, sizeof(int), st));
+    }
     small.alloc(3 * kPP * kPP);
     max_slots = m / b + 4;
     slots.alloc((size_t)max_slots * kSlotDoubles);
@@ -1370,52 +1395,78 @@ struct Solver {
   void enqueue_step(int ja, int si, bool tentative = false) {
     stats.block_steps += 1;
     stats.spmv_cols += b;
-    pending_steps.push_back({ja, si, tentative, tentative ? 0 : enqueue_small_step(ja, si)});
-    if (!pending_steps.back().groups) enqueue_step_launches(ja, si, tentative);
+    const int groups = tentative ? 0 : enqueue_fused_step(ja, si);
+    pending_steps.push_back({ja, si, tentative, groups ? groups : enqueue_step_launches(ja, si, tentative), groups > 0});
   }
 
-  // The step as one launch, where it is for that kernel; returns the number of its workgroups, else 0.
-  int enqueue_small_step(int ja, int si) {
-    const int jt = nl + ja;
-    if (no_small_steps || b != kSmallStepBlock || !val_s.p || nlong > 0) return 0;
-    if (!lds_limit) lds_limit = (size_t)device_lds_limit();
-    SmallStep a;
-    a.rows = small_step_rows(n, jt, lds_limit);
-    if (!a.rows) return 0;
-    const int groups = small_step_groups(n, a.rows);
+  // A fused launch's arguments, but for its product and Gram-Schmidt.
+  FusedStep fused(int col, int rows, int si, int64_t exchanged) {
     double* sl = slot(si);
-    a.rowptr = rowptr;
-    a.col = col;
-    a.val = val_s.p;
+    FusedStep a;
     a.basis = basis.p;
     a.z = z.p;
     a.n = n;
     a.ld = ld;
-    a.j = jt;
-    a.from1 = 0;
-    a.from2 = nl;
-    a.part = part.p;
-    a.gpart = gpart.p;
-    a.h = h1.p;
+    a.j = col;
+    a.rows = rows;
     a.slot_a = sl;
     a.slot_r = sl + kPP * kPP;
     a.slot_g = sl + 2 * kPP * kPP;
     a.done = done_word(sl);
-    a.sync = sync_words();
-    a.base = met;
-    a.polls = step_polls;
+    a.sync = reinterpret_cast<uint32_t*>(flag.p) + kSyncWord;
+    a.base = arrivals;
+    a.polls = fused_polls;
+    a.exchange = exchange.p + exchange_turn * exchange_len;
+    a.used = exchange.p + (1 - exchange_turn) * exchange_len;
+    a.clear = exchange_used;
     a.abs_tol2[0] = kAbsDrop2;
     a.rel_tol[0] = kRelDrop;
     a.abs_tol2[1] = kAbsDrop2Again;
     a.rel_tol[1] = kRelDropAgain;
-    met += (uint32_t)groups * small_step_meetings(jt, a.from1, a.from2);
+    arrivals += (uint32_t)fused_groups(n, rows);
+    exchange_used = exchanged;
+    exchange_turn ^= 1;
+    return a;
+  }
+  bool may_fuse() const { return !no_fused && exchange_len > 0 && arrivals < (1u << 30); }
+
+  // The step as one launch, where it is for that kernel; returns the number of its workgroups, else 0.
+  int enqueue_fused_step(int ja, int si) {
+    const int jt = nl + ja;
+    const int rows = may_fuse() && b == kFusedStepBlock && nlong == 0 ? fused_step_rows(n, jt, lds_limit) : 0;
+    if (!rows) return 0;
+    const int groups = fused_groups(n, rows);
+    FusedStep a = fused(jt, rows, si, fused_exchange(groups, jt, jt - nl, b));
+    a.rowptr = rowptr;
+    a.col = col;
+    a.val = val_s.p;
+    a.from1 = 0;
+    a.from2 = nl;
     timer.begin(kFamOther);
-    HIP_TRY(launch_small_step(a, lds_limit, st));
+    HIP_TRY(launch_fused_step(a, lds_limit, st));
     timer.end(kFamOther, spmm_bytes() + 8.0 * (double)n * (jt + 2 * b), 2.0 * (double)nnz * b + 4.0 * (double)n * (2 * jt - nl + b) * b);
     return groups;
   }
 
-  void enqueue_step_launches(int ja, int si, bool tentative) {
+  // Block QR of columns [col, col + b) into slot si, as one launch where there is one; returns the number of its workgroups, else 0.
+  // ngram as for enqueue_block_qr.
+  int fused_qr_rows_now() const { return may_fuse() ? fused_qr_rows(n, b, lds_limit) : 0; }
+  int enqueue_qr(int col, int ngram, int si) {
+    const int rows = fused_qr_rows_now();
+    if (!rows) {
+      enqueue_block_qr(basis.p, n, ld, col, b, part.p, gpart.p, ngram, gram(), rinv(), r1(), slot(si) + kPP * kPP,
+                       slot(si) + 2 * kPP * kPP, z.p, zs(), st, &timer);
+      return 0;
+    }
+    const int groups = fused_groups(n, rows);
+    timer.begin(kFamQr);
+    HIP_TRY(launch_fused_qr(fused(col, rows, si, fused_exchange(groups, 0, 0, b)), b, lds_limit, st));
+    timer.end(kFamQr, 24.0 * (double)n * b, 4.0 * (double)n * b * b);
+    return groups;
+  }
+  void enqueue_start_qr(int ngram) { pending_steps.push_back({b, 0, false, enqueue_qr(nl, ngram, 0), false}); }
+
+  int enqueue_step_launches(int ja, int si, bool tentative) {
     const int jt = nl + ja;
     timer.begin(kFamSpmm);
     spmm_from_z(basis.p + jt, ld);
@@ -1425,8 +1476,9 @@ struct Solver {
     // second pass would restore is not needed, and the residual block W - V (V^T W) itself comes out of one pass to
     // rounding relative to W (1e-16 of a block of norm one, against residuals of the size of tol).
     const bool one_pass = tentative && !tentative_two_passes;
-    const int ngram = enqueue_cgs2(basis.p, n, ld, jt, jt, b, one_pass ? jt : nl, part.p, h1.p, hsum.p, sl, jt - b, gpart.p,
-                                   st, &timer, tentative ? nl : 0, one_pass && b < kWideUpdate);
+    const bool own_gram = tentative || !fused_qr_rows_now();  // the one-launch QR makes its Gram matrix itself
+    const int ngram = enqueue_cgs2(basis.p, n, ld, jt, jt, b, one_pass ? jt : nl, part.p, h1.p, hsum.p, sl, jt - b,
+                                   own_gram ? gpart.p : nullptr, st, &timer, tentative ? nl : 0, one_pass && b < kWideUpdate);
     if (tentative && ngram > 0) {
       // Only the Gram matrix of the residual block is looked at (residual estimates; a block that vanished): the
       // block is not orthonormalized, since it either is dropped with the phase or built again.  The slot of the QR
@@ -1436,9 +1488,9 @@ struct Solver {
       HIP_TRY(launch_reduce_partials(gpart.p, ngram, b, b, sl + kPP * kPP, nullptr, 0, nullptr, 0, st));
       timer.end(kFamQr, 0.0, 0.0);
     } else {
-      enqueue_block_qr(basis.p, n, ld, jt, b, part.p, gpart.p, ngram, gram(), rinv(), r1(), sl + kPP * kPP,
-                       sl + 2 * kPP * kPP, z.p, zs(), st, &timer);
+      return enqueue_qr(jt, ngram, si);
     }
+    return 0;
   }
 
   void fetch_slots(int first, int count) {
@@ -1450,18 +1502,24 @@ struct Solver {
     for (size_t q = 0; q < pending_steps.size(); ++q) {
       const Pending& p = pending_steps[q];
       if (!p.groups) continue;
-      if (*done_word(slots_host.p + (size_t)p.si * kSlotDoubles) == p.groups) {
-        small_steps.fetch_add(1, std::memory_order_relaxed);
+      const int done = *done_word(slots_host.p + (size_t)p.si * kSlotDoubles);
+      if (done == p.groups) {
+        (p.whole ? fused_steps : fused_qrs).fetch_add(1, std::memory_order_relaxed);
         continue;
       }
-      // Its workgroups did not all come to run: the step and those behind it are taken again by the ordinary launches, from the
-      // basis block that it started from.  No further step is tried that way in this solve.
-      if (debug_on()) std::fprintf(stderr, "[sceig] a step's workgroups did not meet: ordinary launches from here on\n");
-      no_small_steps = true;
-      std::vector<Pending> again(pending_steps.begin() + q, pending_steps.end());
+      if (done != 0) SC_THROW(SC_EHIP);  // workgroups that had all started did not come to an end
+      // Its workgroups did not all come to run, and it has done nothing, nor have the fused launches behind it: block and packed
+      // operand are as they were.  It and all behind it are taken again by the ordinary launches, and no further one is tried.
+      if (debug_on()) std::fprintf(stderr, "[sceig] a fused launch's workgroups did not all start: ordinary launches from here on\n");
+      no_fused = true;
+      const std::vector<Pending> again(pending_steps.begin() + q, pending_steps.end());
       pending_steps.clear();
-      HIP_TRY(launch_pack_scaled(basis.p + nl + again[0].ja - b, ld, zs(), n, b, z.p, st));
-      for (const Pending& r : again) enqueue_step_launches(r.ja, r.si, r.tentative);
+      for (const Pending& r : again) {
+        if (r.si == 0)
+          (void)enqueue_qr(nl, 0, 0);
+        else
+          (void)enqueue_step_launches(r.ja, r.si, r.tentative);
+      }
       fetch_slots(first, count);
       return;
     }
@@ -1830,10 +1888,9 @@ struct Solver {
           : from_ahead ? project_rest()
           : late_projection
               ? enqueue_cgs_adaptive(basis.p, n, ld, nl, nl, b, part.p, h1.p, hsum.p, gpart.p, gram(), flag.p, st, &timer)
-              : enqueue_cgs2(basis.p, n, ld, nl, nl, b, filtered ? nl : 0, part.p, h1.p, hsum.p, nullptr, 0, gpart.p, st,
-                             &timer);
-      enqueue_block_qr(basis.p, n, ld, nl, b, part.p, gpart.p, ngram0, gram(), rinv(), r1(), slot(0) + kPP * kPP,
-                       slot(0) + 2 * kPP * kPP, z.p, zs(), st, &timer);
+              : enqueue_cgs2(basis.p, n, ld, nl, nl, b, filtered ? nl : 0, part.p, h1.p, hsum.p, nullptr, 0,
+                             fused_qr_rows_now() ? nullptr : gpart.p, st, &timer);
+      enqueue_start_qr(ngram0);
       if (pair) {
         ahead.ready = true;
         ahead.from = nl;
@@ -2105,9 +2162,9 @@ struct Solver {
             rotate_into(ja, Y, ycols, sel, nl);
             HIP_TRY(launch_pack_scaled(basis.p + nl, ld, zs(), n, b, z.p, st));
             apply_start_filter(filt_d, filt_a);
-            const int ngram1 = enqueue_cgs2(basis.p, n, ld, nl, nl, b, nl, part.p, h1.p, hsum.p, nullptr, 0, gpart.p, st, &timer);
-            enqueue_block_qr(basis.p, n, ld, nl, b, part.p, gpart.p, ngram1, gram(), rinv(), r1(), slot(0) + kPP * kPP,
-                             slot(0) + 2 * kPP * kPP, z.p, zs(), st, &timer);
+            const int ngram1 = enqueue_cgs2(basis.p, n, ld, nl, nl, b, nl, part.p, h1.p, hsum.p, nullptr, 0,
+                                            fused_qr_rows_now() ? nullptr : gpart.p, st, &timer);
+            enqueue_start_qr(ngram1);
             filt_d = 0;
             filtered = true;
             ja = b;
@@ -2686,7 +2743,8 @@ int64_t sc_counter(int32_t which) {
     case SC_COUNTER_GROUPED_SEARCHES: return grouped_searches.load(std::memory_order_relaxed);
     case SC_COUNTER_FP64_SEARCHES: return fp64_searches.load(std::memory_order_relaxed);
     case SC_COUNTER_START_PAIRS: return start_pairs.load(std::memory_order_relaxed);
-    case SC_COUNTER_SMALL_STEPS: return small_steps.load(std::memory_order_relaxed);
+    case SC_COUNTER_FUSED_STEPS: return fused_steps.load(std::memory_order_relaxed);
+    case SC_COUNTER_FUSED_QRS: return fused_qrs.load(std::memory_order_relaxed);
     case SC_COUNTER_SCREENED_LABELLINGS: return screened_labellings.load(std::memory_order_relaxed);
     default: return -1;
   }
@@ -2860,7 +2918,7 @@ int sc_workspace_bytes(int64_t n, int64_t nnz, int32_t k, const sc_options* opt,
   }
   total += up(N * ld * 8) + up(N * (size_t)b * 8) + up(N * rot_cols * 8);  // basis, packed block, rotation workspace
   total += up((size_t)kMaxPartials * jmax * kPP * 8) + up((size_t)kGramPartials * kPP * kPP * 8) + 2 * up(jmax * kPP * 8) +
-           up(jmax * kPairPad * 8);
+           up(jmax * kPairPad * 8) + up(2 * fused_exchange_doubles(n, (int)m, b) * 8);
   total += up((size_t)(m / b + 4) * kSlotDoubles * 8) + up(jmax * std::max<size_t>(rot_cols, (size_t)k) * 8);
   if (o.flags & SC_FLAG_COMPONENT_NULLSPACE) total += up(N * 8) + up(N * 4) + up(N * 8);
   total += up((size_t)3 * kPP * kPP * 8) + up((size_t)k * 4);  // small matrices, the output permutation

@@ -114,43 +114,48 @@ hipError_t launch_factor_apply_rinv(double* basis, int64_t n, int64_t ld, int co
 hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int b, const double* rinv, double* z,
                              const double* s, hipStream_t st);
 
-// One block step, or the start block's Gram-Schmidt and QR, as one launch whose workgroups meet five to seven times: for few
-// rows, where the launches of a step are each as long as a launch takes at least.  Columns [j, j + kSmallStepBlock) of the
-// basis become the product of the operator (rowptr, col, val) with z, or stay as they are where val is null; then they are
-// orthogonalized against columns [from1, j) and once more against [from2, j) (from >= j: not), made orthonormal by two
-// Cholesky QRs as launch_gram_cholesky does, and z becomes a packed copy of them.  slot_a (may be null): the sum of both passes'
-// coefficients of columns [j - kSmallStepBlock, j); slot_g: the Gram matrix before the first factorization; slot_r: the factor
-// of both; rows of kPartialPad.
-// The workgroups wait for one another, `polls` looks each time.  If one is then still missing (other work holds the compute
-// units), sync[kSyncAbort] is raised and this launch and all further ones with this sync leave without a result: the caller
-// finds that out by *done, the number of workgroups that have finished, and takes the step by other launches.  base: what
-// sync[kSyncCount] has counted before, workgroups x meetings of all launches since both words were zero.
-constexpr int kSmallStepBlock = 8;
-constexpr int kSmallStepGroups = 128;   // workgroups at most: two such launches fit on the chip's 256 compute units side by side
-constexpr int kSmallStepColumns = 256;  // j at most
-constexpr int kSyncCount = 16, kSyncAbort = 48, kSyncWords = 64;  // words on cache lines of their own
-struct SmallStep {
+// One block step, or the QR of a block, as one launch whose workgroups exchange partial sums while it runs: for few rows,
+// where the launches of a step are each as long as a launch takes at least.
+//   launch_fused_step: columns [j, j + kFusedStepBlock) of the basis become the product of the operator (rowptr, col, val) with
+//     z, orthogonalized against columns [from1, j) and once more against [from2, j) (from >= j: not), and then as below.  slot_a:
+//     the sum of both passes' coefficients of columns [j - kFusedStepBlock, j).
+//   launch_fused_qr: columns [j, j + b) are made orthonormal by two Cholesky QRs as launch_gram_cholesky does, and z becomes a
+//     packed copy of them.  slot_g: the Gram matrix before the first factorization; slot_r: the factor of both.
+// Rows of the slots are kPartialPad long.
+// The workgroups wait for one another.  If, after `polls` looks, one has not started yet (other work holds the compute units), the
+// launch leaves without having done anything, and so do all further ones with this sync: *done is then 0, else the number of
+// workgroups, and the caller takes the step by other launches.  base: the workgroups of all launches with this sync so far.
+// exchange: fused_exchange() doubles of all ones, which the launch writes; the first `clear` doubles of used, those of the launch
+// before, become all ones again (two such areas take turns).
+constexpr int kFusedStepBlock = 8;
+constexpr int kFusedGroups = 256;   // workgroups at most
+constexpr int kFusedColumns = 256;  // j of launch_fused_step at most
+constexpr int kSyncWord = 16, kSyncWords = 64;  // the word that counts, on a cache line of its own
+struct FusedStep {
   const int64_t* rowptr = nullptr;
   const int32_t* col = nullptr;
   const double* val = nullptr;
   double *basis = nullptr, *z = nullptr;
   int64_t n = 0, ld = 0;
   int j = 0, from1 = 0, from2 = 0;
-  int rows = 0;             // rows a workgroup (small_step_rows)
-  double* part = nullptr;   // workgroups x j x kSmallStepBlock
-  double* gpart = nullptr;  // 2 x workgroups x kSmallStepBlock^2
-  double* h = nullptr;      // j x kSmallStepBlock
+  int rows = 0;  // rows a workgroup: fused_step_rows, fused_qr_rows
   double *slot_a = nullptr, *slot_g = nullptr, *slot_r = nullptr;
   int* done = nullptr;
   uint32_t* sync = nullptr;
-  uint32_t base = 0, polls = 0;
+  uint32_t base = 0;
+  int polls = 0;
+  double *exchange = nullptr, *used = nullptr;
+  int64_t clear = 0;
   double abs_tol2[2] = {0.0, 0.0}, rel_tol[2] = {0.0, 0.0};
 };
-// Rows a workgroup takes; 0: the step is not for this kernel (too many rows, or columns for a workgroup's LDS).
-int small_step_rows(int64_t n, int j, size_t lds_limit);
-inline int small_step_groups(int64_t n, int rows) { return (int)((n + rows - 1) / rows); }
-inline uint32_t small_step_meetings(int j, int from1, int from2) { return 2 + (from1 < j ? 2 : 0) + (from2 < j ? 2 : 0); }
-hipError_t launch_small_step(const SmallStep& a, size_t lds_limit, hipStream_t st);
+// Rows that a workgroup takes; 0: the call is not for this kernel (too many rows, or columns, for the workgroups' LDS).
+int fused_step_rows(int64_t n, int j, size_t lds_limit);
+int fused_qr_rows(int64_t n, int b, size_t lds_limit);
+inline int fused_groups(int64_t n, int rows) { return (int)((n + rows - 1) / rows); }
+// Sums of j1 and j2 x b coefficients and two Gram matrices, with the workgroups' shares of them.
+inline int64_t fused_exchange(int groups, int j1, int j2, int b) { return (int64_t)(groups + 1) * b * (j1 + j2 + 2 * b); }
+hipError_t launch_fused_step(const FusedStep& a, size_t lds_limit, hipStream_t st);
+hipError_t launch_fused_qr(const FusedStep& a, int b, size_t lds_limit, hipStream_t st);
 
 // Fused variant used inside the block step (same arithmetic as the separate kernels):
 //   update_gram: basis[:, ccol0 : ccol0+b] -= basis[:, acol0 : acol0+kdim] * bmat (bmat kdim x b, row stride

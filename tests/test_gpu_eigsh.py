@@ -618,34 +618,37 @@ def test_check_phase_with_weights_below_zero(B, block):
     assert steps >= 15, steps
 
 
-# rows on either side of a workgroup's share and of the most that 128 workgroups take; with m = 300 and no filter a basis that
-# outgrows the workgroups' LDS (128 columns of 128 rows), so that both forms take turns
-@pytest.mark.parametrize("n,k,m,way", [(60, 3, 0, "one"), (65, 4, 0, "one"), (129, 6, 0, "one"), (2000, 9, 0, "one"),
-                                       (4033, 10, 0, "one"), (8192, 12, 0, "one"), (8193, 12, 300, "both"),
-                                       (16384, 8, 0, "one"), (16385, 8, 0, "none"), (2000, 9, 0, "hub")])
-def test_block_step_as_one_launch(B, monkeypatch, n, k, m, way):
-    """Steps whose workgroups meet inside one launch, the ordinary launches, and a solve whose first step finds its workgroups
-    missing (none is ever seen to arrive): the same pairs."""
+# Steps and block QRs as one launch.  Rows on either side of a workgroup's share and of the most that 128 workgroups take; with
+# m = 300 and no filter a basis that outgrows the workgroups' LDS (128 columns of 128 rows); a row too long for a lane group (whose
+# QRs are taken that way all the same); blocks of 16, whose QRs alone are, up to the rows that 256 workgroups hold.
+@pytest.mark.parametrize("n,k,m,block,way", [(60, 3, 0, 8, "all"), (65, 4, 0, 8, "all"), (129, 6, 0, 8, "all"), (2000, 9, 0, 8, "all"),
+                                             (4033, 10, 0, 8, "all"), (8192, 12, 0, 8, "all"), (8193, 12, 300, 8, "some"),
+                                             (16384, 8, 0, 8, "all"), (16385, 8, 0, 8, "qr"), (2000, 9, 0, 8, "hub"),
+                                             (100, 5, 0, 16, "qr"), (16385, 20, 0, 16, "qr"), (100_003, 20, 0, 16, "qr"),
+                                             (240_000, 4, 0, 16, "qr"), (300_000, 4, 0, 16, "none"), (2000, 9, 0, 4, "none")])
+def test_block_step_as_one_launch(B, monkeypatch, n, k, m, block, way):
+    """Launches whose workgroups exchange sums, the ordinary launches, and a solve whose first such launch finds that its workgroups
+    cannot all have started: the same pairs."""
     rp, c, v, n = wl.random_weighted_connected(n, 4 * n, 5 + n)
-    if way == "hub":  # a row too long for a lane group: node 0 is tied to 200 others
+    if way == "hub":  # node 0 is tied to 200 others
         rp, c, v, n = wl.disjoint_union((rp, c, v, n), wl.complete_bipartite(1, 200))
     g = (rp, c, v, n)
-    flags = B.SC_FLAG_NO_START_FILTER if way == "both" else 0
+    flags = B.SC_FLAG_NO_START_FILTER if way == "some" else 0
     runs = []
-    for env in ({}, {"SCEIG_NO_SMALL_STEPS": "1"}, {"SCEIG_STEP_POLLS": "0"}):
+    for env in ({}, {"SCEIG_NO_FUSED": "1"}, {"SCEIG_FUSED_POLLS": "-1"}):
         for name, value in env.items():
             monkeypatch.setenv(name, value)
-        before = B.sc_counter(B.SC_COUNTER_SMALL_STEPS)
-        lam, vec, code, stats = solve(B, g, k, 1e-9, block=8, m=m, flags=flags)
-        taken = B.sc_counter(B.SC_COUNTER_SMALL_STEPS) - before
+        before = [B.sc_counter(x) for x in (B.SC_COUNTER_FUSED_STEPS, B.SC_COUNTER_FUSED_QRS)]
+        lam, vec, code, stats = solve(B, g, k, 1e-9, block=block, m=m, flags=flags)
+        steps, qrs = [B.sc_counter(x) - y for x, y in zip((B.SC_COUNTER_FUSED_STEPS, B.SC_COUNTER_FUSED_QRS), before)]
         for name in env:
             monkeypatch.delenv(name)
         assert code == B.SC_OK, stats
-        if env or way in ("none", "hub"):
-            assert taken == 0, (env, taken)
+        if env or way == "none":
+            assert steps == 0 and qrs == 0, (env, steps, qrs)
         else:
-            assert 0 < taken <= stats["block_steps"] and (way == "both" or taken == stats["block_steps"]), (taken, stats)
-            assert way != "both" or taken < stats["block_steps"], (taken, stats)
+            assert qrs > 0
+            assert {"all": steps == stats["block_steps"], "some": 0 < steps < stats["block_steps"]}.get(way, steps == 0), (steps, stats)
         assert compare.residual_norms(rp, c, v, lam, vec).max() <= 1e-8
         assert compare.orthonormality_defect(vec) <= 1e-12
         runs.append(lam)
