@@ -101,7 +101,7 @@ template <int B>
 constexpr int kRed = kWaves * B * B > kThreads ? kWaves * B * B : kThreads;  // partial sums of the waves
 template <int B, bool STEP>
 size_t fused_lds_bytes(int j, int rows) {
-  size_t d = (size_t)rows * (B + 1) + kRed<B> + 2 * B * kPartialPad + 2;
+  size_t d = (size_t)rows * (B + 1) + kRed<B> + 2 * B * kCholPitch<B> + 2;
   if (STEP) d += (size_t)(rows + B + 1) * basis_pitch(j);
   return d * sizeof(double);
 }
@@ -117,12 +117,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int pitch = STEP ? basis_pitch(j) : 0, j16 = pitch - 1;
   double* const w = lds;
   double* const red = w + rows * WP;
-  double* const rinv = red;  // and the Gram matrix: there between sums
-  double* const gram = red + B * kPartialPad;
-  static_assert(B * (B + kPartialPad) <= kRed<B>, "both fit");
-  double* const factor = red + kRed<B>;  // of either pass
-  int* const flag = reinterpret_cast<int*>(factor + 2 * B * kPartialPad);  // [0] all there, [1] a wait that should have ended did not
-  double* const q = factor + 2 * B * kPartialPad + 2;
+  double* const gram = red;  // there between sums
+  double* const factor = red + kRed<B>;  // chol_rows' results of either pass
+  int* const flag = reinterpret_cast<int*>(factor + 2 * B * kCholPitch<B>);  // [0] all there, [1] a wait that should have ended did not
+  double* const q = factor + 2 * B * kCholPitch<B> + 2;
   double* const h = q + (size_t)rows * pitch;
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i = lane & 15, g = lane >> 4;
@@ -308,14 +306,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     }
     __syncthreads();
     if (flag[1]) return;
-    if (wave == 0) chol_wave<B>(gram, B, nullptr, rinv, factor + pass * B * kPartialPad, nullptr, a.abs_tol2[pass], a.rel_tol[pass]);
+    const double* const made = factor + pass * B * kCholPitch<B>;
+    if (wave == 0) chol_rows<B>(gram, B, factor + pass * B * kCholPitch<B>, a.abs_tol2[pass], a.rel_tol[pass]);
     __syncthreads();
     for (int t = wave; t < rows / 16; t += kWaves) {
       d4 out = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int k = 0; k < B; k += 4) {
         const double x = w[(16 * t + i) * WP + k + g];
-        const double y = i < B ? rinv[(k + g) * kPartialPad + i] : 0.0;
+        const double y = i < B ? made[i * kCholPitch<B> + B + k + g] : 0.0;
         out = MFMA_F64(x, y, out);
       }
       // the wave alone reads these rows, and has
@@ -337,7 +336,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     const int r = tid / B, t = tid % B;
     double sum = 0.0;
 #pragma unroll
-    for (int x = 0; x < B; ++x) sum += factor[(B + r) * kPartialPad + x] * factor[x * kPartialPad + t];
+    for (int x = 0; x < B; ++x) sum += factor[(B + r) * kCholPitch<B> + x] * factor[x * kCholPitch<B> + t];
     a.slot_r[r * kPartialPad + t] = sum;
   }
   // the places that the launch before this one has written are for the next one

@@ -1277,9 +1277,9 @@ __global__ __launch_bounds__(kCholThreads) void gram_cholesky_kernel(const doubl
 // launch adds the partial blocks up (in one fixed order) and factorizes for itself, which costs it what a launch of one
 // workgroup for that took, without the launch; workgroup 0 writes what others read.  Up to 32 loads one after the other per
 // thread.  Block QR of 2,000 x 8: 38 -> 31 us, 16,000 x 8: 63 -> 40 us, 4,040 x 16: 59 -> 47 us.  sub: 256 doubles of LDS,
-// rinv: B rows of kPartialPad, there for all on return.
+// rows: B x kCholPitch, rinv: B rows of kPartialPad, there for all on return.
 template <int B>
-__device__ __forceinline__ void chol_of_parts(const GramParts& f, double* sub, double* rinv) {
+__device__ __forceinline__ void chol_of_parts(const GramParts& f, double* sub, double* rows, double* rinv) {
   constexpr int SPLIT = kThreads / (B * B);
   const int e = threadIdx.x % (B * B), r = threadIdx.x / (B * B);
   const double* p = f.parts + (e / B) * kPartialPad + e % B;
@@ -1299,7 +1299,7 @@ __device__ __forceinline__ void chol_of_parts(const GramParts& f, double* sub, d
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own LDS operations complete in order
     __builtin_amdgcn_wave_barrier();
     const bool writes = blockIdx.x == 0;
-    chol_wave<B>(sub, B, writes ? f.g_out : nullptr, rinv, writes ? f.r_out : nullptr, f.rprev, f.abs_tol2, f.rel_tol);
+    chol_wave<B>(sub, B, rows, writes ? f.g_out : nullptr, rinv, writes ? f.r_out : nullptr, f.rprev, f.abs_tol2, f.rel_tol);
   }
   __syncthreads();
 }
@@ -1320,7 +1320,8 @@ __global__ __launch_bounds__(kThreads) void apply_rinv_kernel(double* __restrict
   __shared__ double Wt[2 * kThreads];  // rows_per_block rows of b + 1 doubles (b >= 1)
   if constexpr (FACTOR > 0) {
     __shared__ double made[FACTOR * kPartialPad];
-    chol_of_parts<FACTOR>(f, Wt, made);
+    __shared__ double rows[FACTOR * kCholPitch<FACTOR>];
+    chol_of_parts<FACTOR>(f, Wt, rows, made);
     for (int e = threadIdx.x; e < b * b; e += kThreads) Ri[e / b][e % b] = made[(e / b) * kPartialPad + (e % b)];
   } else {
     for (int e = threadIdx.x; e < b * b; e += kThreads) Ri[e / b][e % b] = rinv[(e / b) * kPartialPad + (e % b)];
@@ -1538,7 +1539,8 @@ __global__ __launch_bounds__(kThreads) SC_MFMA_IN_VGPRS void update_gram_kernel(
   if constexpr (FACTOR > 0) {
     static_assert(NT == 1 && kThreads == 256, "a thread per entry of a 16 x 16 block");
     double* made = wt + 256;
-    chol_of_parts<FACTOR>(f, wt, made);
+    static_assert(256 + FACTOR * (kPartialPad + kCholPitch<FACTOR>) <= 128 * WP, "all of it fits the tile");
+    chol_of_parts<FACTOR>(f, wt, made + FACTOR * kPartialPad, made);
     const int kk = threadIdx.x >> 4, t = threadIdx.x & 15;  // the order of stage_coefficients
     lds[(((kk & 3) * 4 + (kk >> 2)) << 4) + t] = kk < FACTOR && t < FACTOR ? made[kk * kPartialPad + t] : 0.0;
     __syncthreads();
@@ -1715,82 +1717,9 @@ template <int B>
 __global__ __launch_bounds__(64) void chol_wave_kernel(const double* __restrict__ g_in, double* __restrict__ g_out,
                                                        double* __restrict__ rinv_out, double* __restrict__ r_out,
                                                        const double* __restrict__ rprev, double abs_tol2, double rel_tol) {
-  chol_wave<B>(g_in, kPartialPad, g_out, rinv_out, r_out, rprev, abs_tol2, rel_tol);
+  __shared__ double rows[B * kCholPitch<B>];
+  chol_wave<B>(g_in, kPartialPad, rows, g_out, rinv_out, r_out, rprev, abs_tol2, rel_tol);
 }
-
-// The same for b = 32 with every entry as one chain of multiply-adds: 38.6 us, where the form above takes 54 (its code is
-// longer, and what bounds straight-line code of 40 KB that runs once is the instruction fetch), and rolled loops over LDS
-// by a workgroup 45 (two barriers a step).
-template <int B>
-__global__ __launch_bounds__(64) void chol_reg_kernel(const double* __restrict__ g_in, double* __restrict__ g_out,
-                                                      double* __restrict__ rinv_out, double* __restrict__ r_out,
-                                                      const double* __restrict__ rprev, double abs_tol2,
-                                                      double rel_tol) {
-  const int t = threadIdx.x;
-  const bool act = t < B;
-  const int tc = act ? t : 0;
-  double gcol[B], rcol[B], ricol[B], inv[B];
-#pragma unroll
-  for (int q = 0; q < B; ++q) {
-    const int lo = q < tc ? q : tc, hi = q < tc ? tc : q;
-    gcol[q] = g_in[lo * kPartialPad + hi];  // upper triangle, mirrored
-    rcol[q] = 0.0;
-    ricol[q] = 0.0;
-  }
-  if (g_out && act) {
-#pragma unroll
-    for (int q = 0; q < B; ++q) g_out[q * kPartialPad + t] = gcol[q];
-  }
-#pragma unroll
-  for (int k = 0; k < B; ++k) {
-    double v = gcol[k];
-#pragma unroll
-    for (int q = 0; q < k; ++q) v -= bcast_lane(rcol[q], k) * rcol[q];
-    const double gkk = bcast_lane(gcol[k], k), pk = bcast_lane(v, k);
-    const bool drop = !(gkk > abs_tol2) || !(pk > rel_tol * gkk);
-    double root;
-    root_and_inverse(drop ? 1.0 : pk, &root, &inv[k]);
-    rcol[k] = drop || t < k ? 0.0 : (t == k ? root : quotient(v, root, inv[k]));
-  }
-  double rcc = 0.0;  // own diagonal entry
-#pragma unroll
-  for (int q = 0; q < B; ++q) rcc = (q == t) ? rcol[q] : rcc;
-#pragma unroll
-  for (int r = B - 1; r >= 0; --r) {
-    const double rrr = bcast_lane(rcol[r], r);
-    double sum = 0.0;
-#pragma unroll
-    for (int x = r + 1; x < B; ++x) {
-      const double rrx = bcast_lane(rcol[r], x);
-      sum += (x <= t) ? rrx * ricol[x] : 0.0;
-    }
-    double v = 0.0;
-    if (rrr != 0.0 && rcc != 0.0) v = (t == r) ? inv[r] : (t > r ? -quotient(sum, rrr, inv[r]) : 0.0);
-    ricol[r] = v;
-  }
-  if (rinv_out && act) {
-#pragma unroll
-    for (int q = 0; q < B; ++q) rinv_out[q * kPartialPad + t] = ricol[q];
-  }
-  if (r_out) {
-    double pcol[B];
-    if (rprev) {
-#pragma unroll
-      for (int x = 0; x < B; ++x) pcol[x] = rprev[x * kPartialPad + tc];
-    }
-#pragma unroll
-    for (int q = 0; q < B; ++q) {
-      double v = rcol[q];
-      if (rprev) {
-        v = 0.0;
-#pragma unroll
-        for (int x = q; x < B; ++x) v += bcast_lane(rcol[q], x) * pcol[x];
-      }
-      if (act) r_out[q * kPartialPad + t] = v;
-    }
-  }
-}
-
 
 // --------------------------------------------------------------------------------------------
 // connected components by minimum-label propagation, and the row/column permutation of the CSR
@@ -2172,9 +2101,7 @@ hipError_t launch_gram_cholesky(const double* g_in, int b, double* g_out, double
     case 4: SC_CHOL(4); break;
     case 8: SC_CHOL(8); break;
     case 16: SC_CHOL(16); break;
-    case 32:
-      hipLaunchKernelGGL((chol_reg_kernel<32>), dim3(1), dim3(64), 0, st, g_in, g_out, rinv, rout, rprev, abs_tol2, rel_tol);
-      break;
+    case 32: SC_CHOL(32); break;
     default:
       hipLaunchKernelGGL(gram_cholesky_kernel, dim3(1), dim3(kCholThreads), 0, st, g_in, b, g_out, rinv, rout, rprev,
                          abs_tol2, rel_tol);
