@@ -351,7 +351,7 @@ int sc_sym_eig_top(const double* a, int32_t n, int32_t count, double* w, double*
  * colmajor == 0: points[i*ld + t], ld >= d.  Centres: device fp64[k*d], row-major k x d.  Labels: device int32[n].
  * 1 <= k <= n <= 2^27, d >= 1 (else SC_EDOMAIN).  All work is enqueued on `stream`; the calls return after it is done.
  * The library stages its own row-major copy of the points and never keeps a caller's pointer.  Device scratch beside that
- * copy: about 17 n bytes for the seeding, which takes 2 n d bytes more where it can have them; after that about
+ * copy: about 17 n + 2^17 bytes for the seeding, which takes 2 n d bytes more where it can have them; after that about
  * 4 n + 4 n k / 1,024 bytes (12 n and those of a radix sort beyond 1,024 clusters) and 16 k d + 2^22 for the iterations.
  * From n dp k of 4e8 on, dp = d rounded up to a multiple of four, and where max_iter is large enough to bring in its cost
  * (three at the least), these take 4 (n + k + 64) (d + 16) + 12 n + 2100 (d + 4) + 2^20 bytes more (a reduced-precision copy
@@ -493,6 +493,7 @@ int sc_version(void);
  *   SC_COUNTER_START_PAIRS       phases of sc_laplacian_eigsh whose start block was made together with the phase's before
  *   SC_COUNTER_FUSED_STEPS       block steps of sc_laplacian_eigsh that ran as one launch
  *   SC_COUNTER_FUSED_QRS         block QRs of sc_laplacian_eigsh, other than those steps', that ran as one launch
+ *   SC_COUNTER_FUSED_SEEDINGS    seedings of k-means whose draws, but for the last, ran as one launch
  *   SC_COUNTER_FP64_SEARCHES     sc_knn_search calls whose screen left queries to the fp64 search through all points
  * Returns the count, or -1 for an unknown id.
  */
@@ -503,6 +504,7 @@ int sc_version(void);
 #define SC_COUNTER_START_PAIRS 4
 #define SC_COUNTER_FUSED_STEPS 5
 #define SC_COUNTER_FUSED_QRS 6
+#define SC_COUNTER_FUSED_SEEDINGS 7
 int64_t sc_counter(int32_t which);
 
 /*

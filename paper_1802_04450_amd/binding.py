@@ -133,6 +133,7 @@ SC_COUNTER_FP64_SEARCHES = 3
 SC_COUNTER_START_PAIRS = 4
 SC_COUNTER_FUSED_STEPS = 5
 SC_COUNTER_FUSED_QRS = 6
+SC_COUNTER_FUSED_SEEDINGS = 7
 
 
 def sc_counter(which: int) -> int:

@@ -369,6 +369,8 @@ constexpr double kRelDrop = 1e-12;   // squared sine below which a column counts
 // in the second factorization: a column that survived the first one has unit norm, so only exact zeros are dropped
 constexpr double kAbsDrop2Again = 0.25, kRelDropAgain = 1e-8;
 
+// looks of a fused launch's workgroup for the others' start, each about 0.6 us; -1, for tests: the word is stopped beforehand
+int fused_polls() { return std::getenv("SCEIG_FUSED_POLLS") ? std::atoi(std::getenv("SCEIG_FUSED_POLLS")) : 2048; }
 constexpr size_t kFusedLds = 160 * 1024;  // a workgroup of the fused launches takes at most
 
 // An area for the sums under way in one fused launch of a solve (launch_fused_step, launch_fused_qr); 0: it has none.
@@ -536,6 +538,7 @@ std::atomic<int64_t> grouped_searches{0};   // sc_counter(SC_COUNTER_GROUPED_SEA
 std::atomic<int64_t> fp64_searches{0};      // sc_counter(SC_COUNTER_FP64_SEARCHES)
 std::atomic<int64_t> start_pairs{0};        // sc_counter(SC_COUNTER_START_PAIRS)
 std::atomic<int64_t> fused_steps{0};        // sc_counter(SC_COUNTER_FUSED_STEPS)
+std::atomic<int64_t> fused_seedings{0};     // sc_counter(SC_COUNTER_FUSED_SEEDINGS)
 std::atomic<int64_t> fused_qrs{0};          // sc_counter(SC_COUNTER_FUSED_QRS)
 std::atomic<int64_t> screened_labellings{0};  // sc_counter(SC_COUNTER_SCREENED_LABELLINGS)
 
@@ -1092,9 +1095,8 @@ struct Solver {
   int filter_tail64 = std::getenv("SCEIG_FILTER_FP64_TAIL") ? std::atoi(std::getenv("SCEIG_FILTER_FP64_TAIL")) : 6;
   double pair_min_work = std::getenv("SCEIG_PAIR_MIN_WORK") ? std::atof(std::getenv("SCEIG_PAIR_MIN_WORK")) : 2e7;
   bool no_start_pairs = std::getenv("SCEIG_NO_START_PAIRS") != nullptr;
+  int polls = fused_polls();
   bool no_fused = std::getenv("SCEIG_NO_FUSED") != nullptr;
-  // looks of a fused launch's workgroup for the others' start, each about 0.6 us; -1, for tests: the word is stopped beforehand
-  int fused_polls = std::getenv("SCEIG_FUSED_POLLS") ? std::atoi(std::getenv("SCEIG_FUSED_POLLS")) : 2048;
   bool tentative_two_passes = std::getenv("SCEIG_TENTATIVE_TWO_PASSES") != nullptr;
   // for tests of the check phase: the solve works for one pair more and gives up the unlock-th largest before that phase
   int unlock = std::getenv("SCEIG_UNLOCK") ? std::atoi(std::getenv("SCEIG_UNLOCK")) : -1;
@@ -1362,7 +1364,7 @@ struct Solver {
       lds_limit = std::min((size_t)device_lds_limit(), kFusedLds);
       exchange.alloc(2 * exchange_len);
       HIP_TRY(hipMemsetAsync(exchange.p, 0xff, 2 * exchange_len * sizeof(double), st));
-      if (fused_polls < 0) HIP_TRY(hipMemsetAsync(flag.p + kSyncWord, 0x80, sizeof(int), st));
+      if (polls < 0) HIP_TRY(hipMemsetAsync(flag.p + kSyncWord, 0x80, sizeof(int), st));
     }
     small.alloc(3 * kPP * kPP);
     max_slots = m / b + 4;
@@ -1415,7 +1417,7 @@ struct Solver {
     a.done = done_word(sl);
     a.sync = reinterpret_cast<uint32_t*>(flag.p) + kSyncWord;
     a.base = arrivals;
-    a.polls = fused_polls;
+    a.polls = polls;
     a.exchange = exchange.p + exchange_turn * exchange_len;
     a.used = exchange.p + (1 - exchange_turn) * exchange_len;
     a.clear = exchange_used;
@@ -2474,17 +2476,6 @@ int resolve_basis(int64_t n, int32_t k, const sc_options& o, int64_t* m_out, int
 // ---- k-means on the embedding (Section II Step 4, Section IV-C, Algorithms 4 and 5) ------------------------------
 namespace {
 
-// Counter-based uniform numbers in [0, 1) for the seeding draws: top 53 bits of mix(mix(seed) + index).
-uint64_t km_mix64(uint64_t x) {
-  x += 0x9E3779B97F4A7C15ull;
-  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
-  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
-  return x ^ (x >> 31);
-}
-double km_uniform01(uint64_t seed, uint64_t index) {
-  return (double)(km_mix64(km_mix64(seed) + index) >> 11) * (1.0 / 9007199254740992.0);
-}
-
 struct KMeans {
   const double* points;
   int64_t ld;
@@ -2503,8 +2494,6 @@ struct KMeans {
 
   // Algorithm 5: chosen (device int32[k]) and the chosen points as centres (device k x ldx)
   void seed(uint64_t seed_value, int32_t* chosen, double* c) {
-    std::vector<double> u((size_t)k);
-    for (int i = 0; i < k; ++i) u[i] = km_uniform01(seed_value, (uint64_t)i);
     int screen = 1;
     size_t wb = kmeans_seed_workspace(n, ldx, d, k, screen);
     DevBuf<char> work;
@@ -2513,9 +2502,26 @@ struct KMeans {
       wb = kmeans_seed_workspace(n, ldx, d, k, screen);
       work.alloc(wb);
     }
-    HIP_TRY(launch_kmeanspp(x.p, ldx, d, n, k, u.data(), screen, work.p, wb, chosen, st));
-    HIP_TRY(launch_gather_rows(x.p, ldx, chosen, k, c, st));
-    HIP_TRY(hipStreamSynchronize(st));  // u and work are released on return
+    PinnedBuf<int> done;
+    SeedFused f;
+    if (!std::getenv("SCEIG_NO_FUSED")) {
+      done.alloc(1);
+      f.lds_limit = std::min((size_t)device_lds_limit(), kFusedLds);
+      f.polls = fused_polls();
+    }
+    for (;;) {
+      HIP_TRY(launch_kmeanspp(x.p, ldx, d, n, k, seed_key(seed_value), screen, work.p, wb, chosen, f, st));
+      HIP_TRY(launch_gather_rows(x.p, ldx, chosen, k, c, st));
+      if (f.groups) HIP_TRY(hipMemcpyAsync(done.p, f.done, sizeof(int), hipMemcpyDeviceToHost, st));
+      HIP_TRY(hipStreamSynchronize(st));  // work is released on return
+      if (!f.groups) return;
+      if (*done.p == f.groups) {
+        fused_seedings.fetch_add(1, std::memory_order_relaxed);
+        return;
+      }
+      if (*done.p != 0) SC_THROW(SC_EHIP);  // workgroups that had all started did not come to an end
+      f.polls = kNeverFused;  // they did not all come to run
+    }
   }
 
   // Algorithm 4 step 3 from the centres in c (device k x ldx, updated in place)
@@ -2745,6 +2751,7 @@ int64_t sc_counter(int32_t which) {
     case SC_COUNTER_START_PAIRS: return start_pairs.load(std::memory_order_relaxed);
     case SC_COUNTER_FUSED_STEPS: return fused_steps.load(std::memory_order_relaxed);
     case SC_COUNTER_FUSED_QRS: return fused_qrs.load(std::memory_order_relaxed);
+    case SC_COUNTER_FUSED_SEEDINGS: return fused_seedings.load(std::memory_order_relaxed);
     case SC_COUNTER_SCREENED_LABELLINGS: return screened_labellings.load(std::memory_order_relaxed);
     default: return -1;
   }

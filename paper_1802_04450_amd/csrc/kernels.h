@@ -365,8 +365,26 @@ hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n
 // Algorithm 5 with the uniform numbers u[0..k-1] supplied by the host; chosen: device int32[k].  screen = 0: without the
 // reduced copy of the points, which makes the draws faster and takes a quarter of their bytes
 size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen);
-hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, int screen, void* work,
-                           size_t work_bytes, int32_t* chosen, hipStream_t st);
+// Uniform number `index` in [0, 1) of the seeding draws: top 53 bits of mix(key + index), key = seed_key(seed).
+__host__ __device__ inline uint64_t seed_mix(uint64_t x) {
+  x += 0x9E3779B97F4A7C15ull;
+  x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+  x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+  return x ^ (x >> 31);
+}
+inline uint64_t seed_key(uint64_t seed) { return seed_mix(seed); }
+__host__ __device__ inline double seed_uniform(uint64_t key, uint64_t index) {
+  return (double)(seed_mix(key + index) >> 11) * (1.0 / 9007199254740992.0);
+}
+constexpr int kNeverFused = -2;
+struct SeedFused {
+  size_t lds_limit = 0;
+  int polls = kNeverFused;  // as for launch_fused_step
+  int groups = 0;           // out: workgroups of the one launch, 0: there is none
+  int* done = nullptr;      // out: device, in work
+};
+hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, uint64_t key, int screen, void* work,
+                           size_t work_bytes, int32_t* chosen, SeedFused& f, hipStream_t st);
 hipError_t launch_gather_rows(const double* x, int64_t ldx, const int32_t* index, int k, double* c, hipStream_t st);
 // part[p], p < kmeans_objective_parts(): partial sums of |x_i - c_label(i)|^2 (add them in order on the host); NaN for a
 // point whose label is not in [0, k)

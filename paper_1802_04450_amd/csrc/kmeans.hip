@@ -18,6 +18,7 @@
 
 #include <cstdint>
 
+#include "exchange.h"
 #include "kernels.h"
 
 namespace sceig {
@@ -421,12 +422,13 @@ __device__ __forceinline__ double wave_inclusive(double v, int lane) {
   return v;
 }
 
-// The first position p in [0, count) with base + (v[0] + ... + v[p]) > r, searched by one wave in pieces of 64; *base
+// The first position p in [0, count) with base + (v(0) + ... + v(p)) > r, searched by one wave in pieces of 64; *base
 // receives the sum before that position.  -1 if there is none (then *base = base + the whole sum).
-__device__ int wave_first_exceeding(const double* __restrict__ v, int64_t count, double r, double* base, int lane) {
+template <class Values>
+__device__ int wave_first_exceeding(Values v, int64_t count, double r, double* base, int lane) {
   double acc = *base;
   for (int64_t p0 = 0; p0 < count; p0 += 64) {
-    const double mine = p0 + lane < count ? v[p0 + lane] : 0.0;
+    const double mine = p0 + lane < count ? v(p0 + lane) : 0.0;
     const double incl = wave_inclusive(mine, lane) + acc;
     const bool hit = p0 + lane < count && incl > r;
     const uint64_t mask = __ballot(hit);
@@ -486,7 +488,7 @@ __device__ int64_t draw_point(const double* __restrict__ bsum, int64_t nb, const
       b1 = b1 < nb ? b1 : nb;
       double base = excl[tr];
       bool missed = false;
-      int jb = wave_first_exceeding(bsum + b0, b1 - b0, r, &base, lane);
+      int jb = wave_first_exceeding([&](int64_t p) { return bsum[b0 + p]; }, b1 - b0, r, &base, lane);
       if (jb < 0) {  // the run's own sum exceeded r but its block sums, added up one by one, do not: take its last block
         jb = (int)(b1 - b0) - 1;
         missed = true;
@@ -494,7 +496,7 @@ __device__ int64_t draw_point(const double* __restrict__ bsum, int64_t nb, const
       const int64_t p0 = (b0 + jb) * kSeedPoints;
       int64_t p1 = p0 + kSeedPoints;
       p1 = p1 < n ? p1 : n;
-      int jp = missed ? -1 : wave_first_exceeding(dist2 + p0, p1 - p0, r, &base, lane);
+      int jp = missed ? -1 : wave_first_exceeding([&](int64_t p) { return dist2[p0 + p]; }, p1 - p0, r, &base, lane);
       if (jp < 0) jp = (int)(p1 - p0) - 1;
       at = (int32_t)(p0 + jp);
     }
@@ -532,6 +534,23 @@ __device__ __forceinline__ double lane_square(const double* __restrict__ x, cons
       acc += diff * diff;
     }
   }
+  return acc;
+}
+
+// Whether the distance kept stands, by the screen's squared distance of the copies.
+__device__ __forceinline__ bool distance_stands(float acc, int d, float2 own_err, double centre_err, double kept) {
+  const double low = sqrt((double)acc) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)own_err.x - centre_err;
+  const double l = ldexp(low, -(int)own_err.y);
+  return acc >= kScreenFloor && low > 0.0 && l * l >= kept * (1.0 + 1e-6);
+}
+// The squared distance of two rows by kExactLanes lanes (each gets it).
+__device__ __forceinline__ double row_square(const double* __restrict__ xi, const double* __restrict__ xc, int d, int lane) {
+  double acc = d <= kExactLanes       ? lane_square<1>(xi, xc, d, lane)
+               : d <= 2 * kExactLanes ? lane_square<2>(xi, xc, d, lane)
+               : d <= 4 * kExactLanes ? lane_square<4>(xi, xc, d, lane)
+                                      : lane_square<8>(xi, xc, d, lane);
+#pragma unroll
+  for (int o = kExactLanes / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kExactLanes);
   return acc;
 }
 
@@ -638,23 +657,14 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
       for (int o = SL / 2; o > 0; o >>= 1) acc[r] += __shfl_xor(acc[r], o, SL);
       if (sl == 0 && p < here) {
         const float2 mine = own_err[r];
-        const double low = sqrt((double)acc[r]) * (1.0 - (d + 8) * 1.1920928955078125e-07) - (double)mine.x - centre_err;
-        const double l = ldexp(low, -(int)mine.y);
-        const bool stands = acc[r] >= kScreenFloor && low > 0.0 && l * l >= pts[p] * (1.0 + 1e-6);
-        if (!stands) todo[atomicAdd(&ntodo, 1)] = p;
+        if (!distance_stands(acc[r], d, mine, centre_err, pts[p])) todo[atomicAdd(&ntodo, 1)] = p;
       }
     }
     __syncthreads();
     const int count = ntodo;
     for (int s = group; s < count; s += kT / kExactLanes) {  // uniform over the point's lanes
       const int pt = todo[s];
-      const double *xi = x + (i0 + pt) * ldx, *xc = x + c * ldx;
-      double acc2 = d <= kExactLanes       ? lane_square<1>(xi, xc, d, lane)
-                    : d <= 2 * kExactLanes ? lane_square<2>(xi, xc, d, lane)
-                    : d <= 4 * kExactLanes ? lane_square<4>(xi, xc, d, lane)
-                                           : lane_square<8>(xi, xc, d, lane);
-#pragma unroll
-      for (int o = kExactLanes / 2; o > 0; o >>= 1) acc2 += __shfl_xor(acc2, o, kExactLanes);
+      const double acc2 = row_square(x + (i0 + pt) * ldx, x + c * ldx, d, lane);
       if (lane == 0 && acc2 < pts[pt]) pts[pt] = acc2;
     }
   } else {  // the lanes take their four points together
@@ -687,6 +697,279 @@ __global__ __launch_bounds__(kT) void seed_distance_kernel(const double* __restr
     const int64_t block = (int64_t)blockIdx.x * SUB + (threadIdx.x >> 6);
     if ((threadIdx.x & 63) == 0 && block < nb) bsum[block] = tot;
   }
+}
+
+// ---- all draws in one launch -----------------------------------------------------------------------------------------
+// A draw's pass is short once the points are where the compute units read them fastest, and then the launch, the loads at its
+// start and the wait for its last workgroup are most of it.  Here the workgroups keep their blocks of points in LDS from the
+// first draw to the last (the bf16 copy with the screen, else the points), with the distances.  A workgroup's blocks are what a
+// thread of draw_point adds up, so that one sum a workgroup is all that the others need to find the run of blocks that the point
+// lies in: every workgroup finds it for itself, with the sums in draw_point's order, and the one that holds the run finds the point
+// and tells the others (which reading the run's distances would take longer: 256 workgroups at the same lines).  Three areas of
+// sums take turns: once all sums of a draw are there, all workgroups are through with those of the draw before.
+// The screen takes the distance of the copies from a product, |x|^2 + |c|^2 - 2 x.c, half an instruction a coordinate instead of
+// three and a half.  That is off by (d + 12) 2^-23 (|x|^2 + |c|^2) for the sums of squares and as much for the product; twice
+// as much is allowed for (kScreenFloor as above).
+// What is left of a draw (100,000 x 100) is the exchange, the search for the point and the loads of its row and of the rows to
+// compute, each waiting for the one before.
+struct SeedDraws {
+  const double* x;
+  int64_t ldx, n, nb;
+  int d, dpb, k, per;  // per: blocks a workgroup
+  const __bf16* xh;
+  const float2* err;
+  uint64_t key;
+  double *dist2, *bsum;  // distances to the first centre, their block sums; in the end, to all centres but the last
+  double* ring;          // 3 x kRunCopies x workgroups, all ones
+  uint64_t* points;      // kDrawTold x 16, no draw's
+  int32_t* chosen;
+  uint32_t* word;  // 0 before the launch
+  int* done;       // workgroups that have finished; 0: not all of them started, and nothing has been done
+  int polls;
+};
+constexpr int kDrawThreads = 512;
+constexpr int kRunCopies = 8;  // of every sum: fewer workgroups that look at the same lines (all at one: 4.4 us, at eight: 2.4)
+constexpr int kDrawTold = 16;  // places that a point is told at, on lines of their own
+constexpr int kDrawGroups = kT;  // workgroups: draw_point's threads
+constexpr int kDrawPer = (int)((kDrawBlocks + kDrawGroups - 1) / kDrawGroups);
+static_assert(kDrawPer <= kDrawThreads / 64, "a wave per block sum, a thread per distance");
+
+constexpr int kDrawPlaces = 3 * kRunCopies * kDrawGroups + kDrawTold * 16;  // ring and points
+constexpr size_t kDrawShared = kDrawPlaces * 8 + 256;                      // ... arrivals and finished workgroups
+inline size_t seed_draws_lds(int per, int d, int dpb, bool screen) {
+  const size_t points = (size_t)per * kSeedPoints;
+  return points * (8 + 4) + (screen ? points * (12 + 2 * (size_t)dpb) : points * (size_t)d * 8);
+}
+
+// draw_point from the sums of the runs (thread t: that of run t, 0 from `runs` on); block sums and distances of the own run in
+// LDS.  Draw number m.
+__device__ __forceinline__ int64_t draw_from_runs(double run, int runs, int own, int per, const double* block_sum, int blocks_here,
+                                                  const double* pts, int64_t n, double u, uint32_t m, uint64_t* told, int* bad) {
+  __shared__ double wave_tot[kT / 64];
+  __shared__ double excl[kT];
+  __shared__ int first_run;
+  __shared__ int32_t drawn;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const double incl_w = wave_inclusive(run, lane);
+  if (lane == 63 && t < kT) wave_tot[wave] = incl_w;
+  if (t == 0) first_run = kT;
+  __syncthreads();
+  double offset = 0.0, total = 0.0;
+#pragma unroll
+  for (int w = 0; w < kT / 64; ++w) {
+    if (w < wave) offset += wave_tot[w];
+    total += wave_tot[w];
+  }
+  const double incl = incl_w + offset;
+  if (t < kT) excl[t] = incl - run;
+  const double r = u * total;
+  if (t < runs && incl > r) atomicMin(&first_run, t);
+  __syncthreads();
+  const int tr = first_run;
+  if (wave == 0) {
+    if (tr == own) {
+      double base = excl[tr];
+      bool missed = false;
+      int jb = wave_first_exceeding([&](int64_t p) { return block_sum[p]; }, blocks_here, r, &base, lane);
+      if (jb < 0) {
+        jb = blocks_here - 1;
+        missed = true;
+      }
+      const int64_t p0 = ((int64_t)own * per + jb) * kSeedPoints;
+      const int here = n - p0 < kSeedPoints ? (int)(n - p0) : kSeedPoints;
+      int jp = missed ? -1 : wave_first_exceeding([&](int64_t p) { return pts[jb * kSeedPoints + p]; }, here, r, &base, lane);
+      if (jp < 0) jp = here - 1;
+      if (lane < kDrawTold)
+        __hip_atomic_store(told + lane * 16, (uint64_t)m << 32 | (uint64_t)(p0 + jp), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (lane == 0) drawn = (int32_t)(p0 + jp);
+    } else if (tr < runs) {
+      if (lane == 0) {
+        uint64_t seen = 0;
+        int looks = 0;
+        do
+          seen = __hip_atomic_load(told + own % kDrawTold * 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while (seen >> 32 != m && ++looks < kLooks);
+        if (seen >> 32 != m) *bad = 1;
+        drawn = seen >> 32 == m ? (int32_t)(seen & 0xffffffffu) : 0;
+      }
+    } else if (lane == 0) {
+      drawn = (int32_t)(n - 1);  // nothing exceeds r: all distances are zero (or u * total rounded up to the total)
+    }
+  }
+  __syncthreads();
+  return drawn;
+}
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+union Bf16Piece {
+  bf16x2 pair[4];
+  uint4 v;
+};
+__device__ __forceinline__ float piece_product(const Bf16Piece& a, const Bf16Piece& b, float acc) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_fdot2_f32_bf16(a.pair[q], b.pair[q], acc, false);
+  return acc;
+}
+
+// The first centre's index, and the places that seed_draws_kernel's workgroups share.
+__global__ __launch_bounds__(kT) void seed_start_kernel(int32_t* __restrict__ chosen, int32_t first, long long* __restrict__ shared,
+                                                        int count, uint32_t* __restrict__ word, uint32_t value) {
+  const int t = blockIdx.x * kT + threadIdx.x;
+  if (t == 0) {
+    *chosen = first;
+    if (word) *word = value;
+  }
+  for (int e = t; e < count; e += gridDim.x * kT) shared[e] = -1;
+}
+
+template <bool SCREEN>
+__global__ __launch_bounds__(kDrawThreads) void seed_draws_kernel(SeedDraws a) {
+  extern __shared__ uint4 draw_lds[];
+  __shared__ int ntodo, there, bad;
+  __shared__ double block_sum[kDrawThreads / 64];
+  const int d = a.d, dpb = a.dpb, tid = threadIdx.x, wave = tid >> 6, wl = tid & 63;
+  const int64_t nb = a.nb;
+  const int points = a.per * kSeedPoints, runs = gridDim.x;
+  __bf16* const rows_h = reinterpret_cast<__bf16*>(draw_lds);  // 16 bytes apiece
+  double* const rows = reinterpret_cast<double*>(draw_lds);
+  double* const pts = SCREEN ? reinterpret_cast<double*>(rows_h + (size_t)points * dpb) : rows + (size_t)points * d;
+  float2* const errs = reinterpret_cast<float2*>(pts + points);
+  float* const norms = reinterpret_cast<float*>(errs + points);
+  int* const todo = SCREEN ? reinterpret_cast<int*>(norms + points) : reinterpret_cast<int*>(errs);
+  const int64_t block0 = (int64_t)blockIdx.x * a.per, i0 = block0 * kSeedPoints;
+  const int here = a.n - i0 < points ? (int)(a.n - i0) : points;
+  const int blocks_here = nb - block0 < a.per ? (int)(nb - block0) : a.per;
+  if (tid == 0) {
+    if (blockIdx.x == 0) {
+      __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // before anyone counts up
+    }
+    arrive(a.word);
+    bad = 0;
+    ntodo = 0;
+  }
+  constexpr int SL = 4;  // lanes per point of the screen
+  const int sl = tid % SL;
+  if constexpr (SCREEN) {
+    const uint4* __restrict__ from = reinterpret_cast<const uint4*>(a.xh + i0 * dpb);
+#pragma unroll 8
+    for (int e = tid; e < here * (dpb / 8); e += kDrawThreads) draw_lds[e] = from[e];
+  } else {
+    for (int p = tid / 16; p < here; p += kDrawThreads / 16)
+#pragma unroll 4
+      for (int t = tid % 16; t < d; t += 16) rows[(size_t)p * d + t] = a.x[(i0 + p) * a.ldx + t];
+  }
+  for (int p = tid; p < points; p += kDrawThreads) {
+    pts[p] = p < here ? a.dist2[i0 + p] : 0.0;
+    if constexpr (SCREEN) errs[p] = p < here ? a.err[i0 + p] : make_float2(0.0f, 0.0f);
+  }
+  double run = 0.0;
+  if (tid < runs) {
+    const int64_t j0 = (int64_t)tid * a.per, j1 = j0 + a.per < nb ? j0 + a.per : nb;
+    for (int64_t j = j0; j < j1; ++j) run += a.bsum[j];
+  }
+  if (tid < blocks_here) block_sum[tid] = a.bsum[block0 + tid];
+  if (tid == 0) there = all_arrived(a.word, gridDim.x, a.polls);
+  __syncthreads();
+  if (!there) return;
+  if constexpr (SCREEN) {
+    for (int p = tid / SL; p < here; p += kDrawThreads / SL) {
+      float acc = 0.0f;
+      for (int t = sl * 8; t < dpb; t += SL * 8) {
+        Bf16Piece own;
+        own.v = *reinterpret_cast<const uint4*>(rows_h + (size_t)p * dpb + t);
+        acc = piece_product(own, own, acc);
+      }
+#pragma unroll
+      for (int o = SL / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, SL);
+      if (sl == 0) norms[p] = acc;
+    }
+  }
+
+  const int lane = tid % kExactLanes, group = tid / kExactLanes;
+  for (int m = 1; m + 1 < a.k; ++m) {  // centre m
+    if (m > 1 && tid < runs) {
+      double v[1];
+      if (!get(a.ring + ((m - 1) % 3 * kRunCopies + (int)blockIdx.x % kRunCopies) * runs + tid, 0, 1, v)) bad = 1;
+      run = v[0];
+    }
+    const int64_t c = draw_from_runs(run, runs, (int)blockIdx.x, a.per, block_sum, blocks_here, pts, a.n,
+                                     seed_uniform(a.key, (uint64_t)m), (uint32_t)m, a.points, &bad);
+    if (bad) return;
+    if (tid < kRunCopies) {
+      if (m > 2)  // everyone is through with these
+        __hip_atomic_store(reinterpret_cast<long long*>(a.ring + ((m - 2) % 3 * kRunCopies + tid) * runs + blockIdx.x), -1ll,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (blockIdx.x == 0 && tid == 0) a.chosen[m] = (int32_t)c;
+    }
+    const double* __restrict__ xc = a.x + c * a.ldx;
+    if constexpr (SCREEN) {
+      const float centre_err = a.err[c].x;
+      const __bf16* __restrict__ hc = a.xh + c * dpb;
+      const float slack = (float)(4 * d + 48) * 1.1920928955078125e-07f;
+      for (int p0 = tid / SL; p0 - tid / SL < here; p0 += 4 * (kDrawThreads / SL)) {  // four points a lane
+        float acc[4] = {}, own_norm = 0.0f;
+#pragma unroll 4
+        for (int t = sl * 8; t < dpb; t += SL * 8) {
+          Bf16Piece own, b;
+          b.v = *reinterpret_cast<const uint4*>(hc + t);
+          own_norm = piece_product(b, b, own_norm);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int p = p0 + u * (kDrawThreads / SL);
+            own.v = *reinterpret_cast<const uint4*>(rows_h + (size_t)(p < here ? p : 0) * dpb + t);
+            acc[u] = piece_product(own, b, acc[u]);
+          }
+        }
+#pragma unroll
+        for (int o = SL / 2; o > 0; o >>= 1) {
+          own_norm += __shfl_xor(own_norm, o, SL);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[u] += __shfl_xor(acc[u], o, SL);
+        }
+        // a lane per point: the four have the same sums
+        float mine = acc[0];
+#pragma unroll
+        for (int u = 1; u < 4; ++u) mine = sl == u ? acc[u] : mine;
+        const int p = p0 + sl * (kDrawThreads / SL);
+        if (p < here) {
+          const float both = norms[p] + own_norm;
+          const float low2 = (both - 2.0f * mine) - slack * both;
+          if (!(both >= kScreenFloor) || !distance_stands(low2, d, errs[p], (double)centre_err, pts[p])) todo[atomicAdd(&ntodo, 1)] = p;
+        }
+      }
+      __syncthreads();
+      const int count = ntodo;
+      for (int s = group; s < count; s += kDrawThreads / kExactLanes) {  // uniform over the point's lanes
+        const int p = todo[s];
+        const double acc = row_square(a.x + (i0 + p) * a.ldx, xc, d, lane);
+        if (lane == 0 && acc < pts[p]) pts[p] = acc;
+      }
+    } else {
+      for (int p = group; p < here; p += kDrawThreads / kExactLanes) {
+        const double acc = row_square(rows + (size_t)p * d, xc, d, lane);
+        if (lane == 0 && acc < pts[p]) pts[p] = acc;
+      }
+    }
+    __syncthreads();
+    if (tid == 0) ntodo = 0;
+    if (wave < blocks_here) {  // a wave per block
+      double tot = pts[tid];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
+      if (wl == 0) block_sum[wave] = tot;
+    }
+    __syncthreads();
+    if (tid < kRunCopies && m + 2 < a.k) {
+      double sum = 0.0;
+      for (int b = 0; b < blocks_here; ++b) sum += block_sum[b];
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the place that is free again is so before that
+      put(a.ring + (m % 3 * kRunCopies + tid) * runs + blockIdx.x, sum);
+    }
+  }
+  if (tid < here) a.dist2[i0 + tid] = pts[tid];
+  if (tid < blocks_here) a.bsum[block0 + tid] = block_sum[tid];
+  if (tid == 0) __hip_atomic_fetch_add(a.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // ---- labelling, screened -------------------------------------------------------------------------------------------
@@ -1229,6 +1512,11 @@ namespace {
 // the L2s and there are draws to spread that over: 100,000 x 100, 100 draws 2.04 -> 1.64 ms, 142,541 x 500, 500 draws
 // 60 -> 27 ms; 140,000 x 8, 100 draws 1.47 -> 1.44 ms, 50,000 x 64, 16 draws 0.19 -> 0.23 ms.
 bool seed_screened(int64_t n, int d, int k) { return n * (int64_t)d >= 4000000 && k >= 32; }
+// Draws in one launch: as many blocks as seed_distance_kernel draws from; with the screen always (100,000 x 100, 100 draws 1,350 ->
+// 1,110 us, 110,000 x 128, 128 draws 1,790 -> 1,380, 90,000 x 112, 33 draws 511 -> 479), else where workgroups, and with them the
+// exchange, are few, and draws make up for the launch's own costs (2,000 x 128, 40 draws 359 -> 260, 2,000 x 2, 16 draws 134 -> 123,
+// 10,000 x 2, 20 draws 171 -> 166; 20,000 x 64, 16 draws 165 -> 170, 40,900 x 30, 24 draws 230 -> 246).
+bool seed_fused(int64_t nb, int k, bool screened) { return nb <= kDrawBlocks && (screened || (nb <= 256 && k >= 16)); }
 inline int seed_dpb(int d) { return (d + 7) / 8 * 8; }
 
 }  // namespace
@@ -1238,14 +1526,18 @@ size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen) {
   // mean[ldx] | sums[kSeedParts][ldx] | tops[kSeedParts] | scale | err[n] | xh[n][dpb]
   const size_t nb = (size_t)((n + kSeedPoints - 1) / kSeedPoints);
   size_t bytes = 2 * ((size_t)n + nb) * 8 + 1024;
+  if (seed_fused((int64_t)nb, k, screen && seed_screened(n, d, k))) bytes += kDrawShared;
   if (screen && seed_screened(n, d, k)) bytes += (size_t)(ldx + 1) * 8 * (kSeedParts + 1) + (size_t)n * (8 + 2 * (size_t)seed_dpb(d)) + 1024;
   return bytes;
 }
 
-// Algorithm 5.  u[0 .. k-1]: host array of uniform numbers in [0, 1).  chosen: device int32[k], the indices of the
-// chosen points in the order they were drawn.  One or two launches per draw.
-hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, const double* u, int screen, void* work,
-                           size_t work_bytes, int32_t* chosen, hipStream_t st) {
+// Algorithm 5 with the uniform numbers seed_uniform(key, 0 .. k-1).  chosen: device int32[k], the indices of the chosen points
+// in the order they were drawn.  One or two launches per draw, or (f.groups > 0, the number of its workgroups) one for all but the
+// last; whether that has come to run *f.done says once the stream is idle: f.groups, else 0, and the call has to be made again
+// without (f.polls = kNeverFused).
+hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, uint64_t key, int screen, void* work,
+                           size_t work_bytes, int32_t* chosen, SeedFused& f, hipStream_t st) {
+  f.groups = 0;
   if (n <= 0 || n > INT32_MAX || k < 1) return hipErrorInvalidValue;
   const int64_t nb = (n + kSeedPoints - 1) / kSeedPoints;
   if (work_bytes < kmeans_seed_workspace(n, ldx, d, k, screen)) return hipErrorInvalidValue;
@@ -1258,9 +1550,15 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
   __bf16* xh = reinterpret_cast<__bf16*>(((uintptr_t)(err + n) + 15) / 16 * 16);
   const int dpb = seed_dpb(d);
   const bool screened = screen && seed_screened(n, d, k), draws = nb <= kDrawBlocks;
-  int64_t first = (int64_t)(u[0] * (double)n);
+  int64_t first = (int64_t)(seed_uniform(key, 0) * (double)n);
   first = first < n - 1 ? first : n - 1;
-  hipLaunchKernelGGL(iota_fill_kernel, dim3(1), dim3(kT), 0, st, chosen, 1, (int32_t)first, 0);
+  const int per = (int)((nb + kDrawGroups - 1) / kDrawGroups);
+  const size_t lds = seed_draws_lds(per, d, dpb, screened);
+  const bool fused = f.polls != kNeverFused && seed_fused(nb, k, screened) && lds + 4096 <= f.lds_limit;  // beside what the draw takes
+  double* const ring = fused ? reinterpret_cast<double*>(static_cast<char*>(work) + (work_bytes - kDrawShared) / 16 * 16) : nullptr;
+  uint32_t* const words = fused ? reinterpret_cast<uint32_t*>(ring + kDrawPlaces) : nullptr;
+  hipLaunchKernelGGL(seed_start_kernel, dim3(fused ? 8 : 1), dim3(kT), 0, st, chosen, (int32_t)first, reinterpret_cast<long long*>(ring),
+                     fused ? kDrawPlaces : 0, words, f.polls < 0 ? kStopped : 0u);
   if (screened) {
     hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums, tops);
     hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, tops, kSeedParts, ldx, n, mean,
@@ -1275,7 +1573,7 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
     if (i > 1) at ^= 1;
 #define SC_SEED(SCR, DRW, SUBV, AHD)                                                                                     \
   hipLaunchKernelGGL((seed_distance_kernel<SCR, DRW, SUBV, AHD>), dim3((unsigned)((nb + SUBV - 1) / SUBV)), dim3(kT), 0, \
-                     st, x, ldx, d, n, xh, dpb, err, u[i - 1], chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], \
+                     st, x, ldx, d, n, xh, dpb, err, seed_uniform(key, (uint64_t)i - 1), chosen + (i - 1), i == 1 ? 1 : 0, bin, nb, din, dist2[at], \
                      dist2[at] + n)
     if (screened && i > 1) {
       const bool wide = dpb <= kSeedWideDim && nb >= kSeedWide;
@@ -1288,11 +1586,28 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
     }
 #undef SC_SEED
   };
+  if (fused) {
+    pass(1);
+    const void* kernel = screened ? reinterpret_cast<const void*>(seed_draws_kernel<true>) : reinterpret_cast<const void*>(seed_draws_kernel<false>);
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    f.done = reinterpret_cast<int*>(words + 32);
+    f.groups = (int)((nb + per - 1) / per);
+    SeedDraws a{x, ldx, n, nb, d, dpb, k, per, xh, err, key, dist2[0], dist2[0] + n, ring,
+                reinterpret_cast<uint64_t*>(ring + 3 * kRunCopies * kDrawGroups), chosen, words, f.done, f.polls};
+    if (screened)
+      hipLaunchKernelGGL(seed_draws_kernel<true>, dim3((unsigned)f.groups), dim3(kDrawThreads), lds, st, a);
+    else
+      hipLaunchKernelGGL(seed_draws_kernel<false>, dim3((unsigned)f.groups), dim3(kDrawThreads), lds, st, a);
+    hipLaunchKernelGGL(seed_select_kernel, dim3(1), dim3(kSelectThreads), 0, st, dist2[0] + n, nb, dist2[0], n,
+                       seed_uniform(key, (uint64_t)k - 1), chosen + k - 1);
+    return hipGetLastError();
+  }
   for (int i = 1; i < k; ++i) {
     pass(i);
     if (!draws || i == k - 1)
-      hipLaunchKernelGGL(seed_select_kernel, dim3(1), dim3(kSelectThreads), 0, st, dist2[at] + n, nb, dist2[at], n, u[i],
-                         chosen + i);
+      hipLaunchKernelGGL(seed_select_kernel, dim3(1), dim3(kSelectThreads), 0, st, dist2[at] + n, nb, dist2[at], n,
+                         seed_uniform(key, (uint64_t)i), chosen + i);
   }
   return hipGetLastError();
 }

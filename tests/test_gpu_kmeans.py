@@ -357,3 +357,40 @@ def test_screened_labelling_is_the_nearest_centre(B, n, d, k, kind, monkeypatch)
         size = (xr.norm(dim=1) + cen_used.norm(dim=1).max()) ** 2
         assert bool((got - v.min(1)[0] <= (4 * d + 16) * 1.2e-16 * size)[fine].all()), r0
         assert bool(((lab >= 0) & (lab < k))[fine].all())
+
+
+# Draws in one launch.  Without the screen: 16 draws and blocks of points from one to the 256 that it is taken for; with it: one and
+# several blocks a workgroup, the last ones ragged, up to the blocks that it takes (1,800) and the LDS (128 coordinates there)
+@pytest.mark.parametrize("n,d,k,data,one", [(16, 3, 16, "blobs", True), (65, 1, 16, "blobs", True), (4097, 17, 31, "blobs", True),
+                                            (16384, 5, 16, "blobs", True), (16385, 5, 16, "blobs", False), (500, 7, 15, "blobs", False),
+                                            (2000, 130, 20, "blobs", True), (3000, 9, 40, "few", True), (700, 4, 20, "nan", True),
+                                            (40_000, 100, 33, "blobs", True), (115_200, 35, 40, "blobs", True),
+                                            (115_201, 35, 40, "blobs", False), (115_200, 128, 34, "blobs", True),
+                                            (100_003, 99, 32, "blobs", True), (60_000, 67, 32, "embedding", True),
+                                            (50_000, 80, 32, "few", True), (50_000, 80, 32, "huge", True), (50_000, 80, 32, "nan", True)])
+def test_draws_in_one_launch(B, monkeypatch, n, d, k, data, one):
+    """The points drawn by one launch, by a launch a draw, and when the one launch finds that its workgroups cannot all have
+    started: the same, also where there are fewer different points than draws, no scale for the screen, or no number."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + d)
+    cen = torch.randn((k, d), dtype=torch.float64, generator=g, device="cuda")
+    lab = torch.randint(0, k, (n,), generator=g, device="cuda")
+    spread = {"embedding": 1e-6, "few": 0.0}.get(data, 0.15)
+    x = (cen[lab[:]] if data != "few" else cen[lab % 7]) + spread * torch.randn((n, d), dtype=torch.float64, generator=g, device="cuda")
+    if data == "huge":
+        x *= 1e140
+    if data == "nan":
+        x[n // 2, d // 2] = float("nan")
+    picked = []
+    for env in ({}, {"SCEIG_NO_FUSED": "1"}, {"SCEIG_FUSED_POLLS": "-1"}):
+        for name, value in env.items():
+            monkeypatch.setenv(name, value)
+        before = B.sc_counter(B.SC_COUNTER_FUSED_SEEDINGS)
+        chosen, out = B.sc_kmeanspp(x, k, 5)
+        assert B.sc_counter(B.SC_COUNTER_FUSED_SEEDINGS) - before == (1 if one and not env else 0)
+        for name in env:
+            monkeypatch.delenv(name)
+        picked.append(chosen)
+        same = out == x[chosen.long()]
+        assert bool((same | (out.isnan() & x[chosen.long()].isnan())).all())
+    assert torch.equal(picked[0], picked[1]) and torch.equal(picked[2], picked[1])
