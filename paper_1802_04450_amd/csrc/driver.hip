@@ -12,7 +12,7 @@
 //   -> Cholesky QR twice (Gram by MFMA, b x b factorisation in one workgroup) -> next block + its
 //   scaled packed copy for the next SpMM.
 // Per step the b x b diagonal block, the QR factor R and the Gram matrix of the residual block are
-// kept in device "slots" and fetched only when the host inspects convergence.
+// kept in "slots" in host memory that the kernels write to, and looked at only when the host inspects convergence.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -105,7 +105,7 @@ class BlockCache {
         }
       }
     }
-    return pinned_ ? hipHostMalloc(p, bytes, hipHostMallocDefault) : hipMalloc(p, bytes);
+    return pinned_ ? hipHostMalloc(p, bytes, hipHostMallocCoherent) : hipMalloc(p, bytes);
   }
   void put(void* p, size_t bytes) {
     int dev = 0;
@@ -1104,7 +1104,7 @@ struct Solver {
   size_t ws_limit = 0;         // > 0: size of the caller's workspace, checked against the estimate once nnz is known
   hipStream_t st;
   // device
-  DevBuf<double> basis, s, z, part, gpart, h1, hsum, hpair, small, slots, yd, rot;
+  DevBuf<double> basis, s, z, part, gpart, h1, hsum, hpair, small, yd, rot;
   DevBuf<int> flag;
   DevBuf<int64_t> rowptr_p;
   DevBuf<int32_t> col_p, old_of_new_d, new_of_old_d, comp_d, perm_d;
@@ -1118,7 +1118,7 @@ struct Solver {
   const int32_t* rowinv = nullptr;  // device: internal row of each original row, null if not reordered
   std::vector<int32_t> comp_host;   // component index of each internal row (only after reorder())
   int ncomp = 0;
-  PinnedBuf<double> slots_host;
+  PinnedBuf<double> slots;  // kernels write to it, none reads it
   // marks of the setup's checks and the number of long rows, as the device hands them back.  Here and not on setup()'s stack:
   // a setup that fails with such a copy under way leaves it in memory that outlasts it (released only once it is done).
   PinnedBuf<int32_t> marks;
@@ -1185,7 +1185,7 @@ struct Solver {
   int64_t exchange_used = 0;  // by the last launch
   int exchange_turn = 0;
   size_t lds_limit = 0;
-  // the entry of slot i that a fused launch counts its finished workgroups in: past the columns that the slot's rows use
+  // the entry of a slot that a fused launch leaves its number of workgroups in, at its end: past the columns that the slot's rows use
   static_assert(16 < kPP, "a slot's rows leave room");
   int* done_word(double* slot) { return reinterpret_cast<int*>(slot + kPP - 1); }
 
@@ -1217,7 +1217,7 @@ struct Solver {
       HIP_TRY(launch_spmm(rowptr, col, val, s.p, n, z.p, b, y, ldy, avg_deg, st));
     }
   }
-  const double* hslot(int i) const { return slots_host.p + (size_t)i * kSlotDoubles; }
+  const double* hslot(int i) const { return slots.p + (size_t)i * kSlotDoubles; }
 
   void reorder() {
     rowptr_p.alloc((size_t)n + 1);
@@ -1369,7 +1369,6 @@ struct Solver {
     small.alloc(3 * kPP * kPP);
     max_slots = m / b + 4;
     slots.alloc((size_t)max_slots * kSlotDoubles);
-    slots_host.alloc((size_t)max_slots * kSlotDoubles);
     ystage.alloc(kYStageDoubles);
     rot_cols = (size_t)std::min(m, std::max(m / 2 + b, 2 * b));
     rot.alloc((size_t)n * rot_cols);
@@ -1415,7 +1414,8 @@ struct Solver {
     a.slot_r = sl + kPP * kPP;
     a.slot_g = sl + 2 * kPP * kPP;
     a.done = done_word(sl);
-    a.sync = reinterpret_cast<uint32_t*>(flag.p) + kSyncWord;
+    *a.done = 0;  // what used the slot before has been looked at
+    a.sync = reinterpret_cast<uint32_t*>(flag.p);
     a.base = arrivals;
     a.polls = polls;
     a.exchange = exchange.p + exchange_turn * exchange_len;
@@ -1495,16 +1495,29 @@ struct Solver {
     return 0;
   }
 
-  void fetch_slots(int first, int count) {
-    if (count <= 0) return;
-    HIP_TRY(hipMemcpyAsync(slots_host.p + (size_t)first * kSlotDoubles, slots.p + (size_t)first * kSlotDoubles,
-                           (size_t)count * kSlotDoubles * sizeof(double), hipMemcpyDeviceToHost, st));
+  // Waits for everything enqueued.  Behind a fused launch by the word that it writes at its end (6 us earlier than the stream is
+  // found idle), for as long as such a launch can be expected to last.
+  void wait_for_slots() {
+    if (!pending_steps.empty() && pending_steps.back().groups) {
+      const volatile int* done = done_word(slot(pending_steps.back().si));
+      const double until = now_s() + 1e-3;
+      do {
+        for (int i = 0; i < 64; ++i)
+          if (*done == pending_steps.back().groups) {
+            std::atomic_thread_fence(std::memory_order_acquire);
+            return;
+          }
+      } while (now_s() < until);
+    }
     HIP_TRY(hipStreamSynchronize(st));
+  }
+  void fetch_slots() {
+    wait_for_slots();
     ystage_busy = false;
     for (size_t q = 0; q < pending_steps.size(); ++q) {
       const Pending& p = pending_steps[q];
       if (!p.groups) continue;
-      const int done = *done_word(slots_host.p + (size_t)p.si * kSlotDoubles);
+      const int done = *done_word(slot(p.si));
       if (done == p.groups) {
         (p.whole ? fused_steps : fused_qrs).fetch_add(1, std::memory_order_relaxed);
         continue;
@@ -1522,7 +1535,7 @@ struct Solver {
         else
           (void)enqueue_step_launches(r.ja, r.si, r.tentative);
       }
-      fetch_slots(first, count);
+      fetch_slots();
       return;
     }
     pending_steps.clear();
@@ -1902,7 +1915,6 @@ struct Solver {
       int ja = b;            // active columns whose coupling is (or will be) assembled
       int assembled = 0;     // active columns of T that are final (their block has been multiplied by S)
       int next_slot = 1;     // slot 0 = start block QR
-      int fetched = 0;       // slots already on the host
       int steps_in_phase = 0;
       T.clear();
       ghost.assign((size_t)cap + b, 0);
@@ -1959,8 +1971,7 @@ struct Solver {
         }
         // ---- inspect: bring the slots over and assemble T
         T.touch(ja + b);
-        fetch_slots(fetched, next_slot - fetched);
-        fetched = next_slot;
+        fetch_slots();
         if (!start_block_seen) {
           const double* r0 = hslot(0) + kPP * kPP;
           for (int x = 0; x < b; ++x) ghost[x] = (r0[x * kPP + x] == 0.0);
@@ -2122,8 +2133,7 @@ struct Solver {
           tentative_allowed = false;
           ja = b;
           assembled = 0;
-          next_slot = 1;
-          fetched = 1;  // slot 0 (the start block's QR) is on the host already
+          next_slot = 1;  // slot 0 (the start block's QR) is on the host already
           pending = 0;
           steps_in_phase = 0;
           T.clear();
@@ -2172,7 +2182,6 @@ struct Solver {
             ja = b;
             assembled = 0;
             next_slot = 1;
-            fetched = 0;
             steps_in_phase = 0;
             T.clear();
             std::fill(ghost.begin(), ghost.end(), 0);
@@ -2262,7 +2271,6 @@ struct Solver {
           ja = l + b;
           assembled = l;
           next_slot = 1;
-          fetched = 1;
           // The residual of the last wanted pair keeps decaying across restarts: when the rate observed so far says
           // that convergence is further away than the basis has room for, the next inspection worth its projected
           // eigenproblem is the one at the next restart.
@@ -2926,7 +2934,7 @@ int sc_workspace_bytes(int64_t n, int64_t nnz, int32_t k, const sc_options* opt,
   total += up(N * ld * 8) + up(N * (size_t)b * 8) + up(N * rot_cols * 8);  // basis, packed block, rotation workspace
   total += up((size_t)kMaxPartials * jmax * kPP * 8) + up((size_t)kGramPartials * kPP * kPP * 8) + 2 * up(jmax * kPP * 8) +
            up(jmax * kPairPad * 8) + up(2 * fused_exchange_doubles(n, (int)m, b) * 8);
-  total += up((size_t)(m / b + 4) * kSlotDoubles * 8) + up(jmax * std::max<size_t>(rot_cols, (size_t)k) * 8);
+  total += up(jmax * std::max<size_t>(rot_cols, (size_t)k) * 8);
   if (o.flags & SC_FLAG_COMPONENT_NULLSPACE) total += up(N * 8) + up(N * 4) + up(N * 8);
   total += up((size_t)3 * kPP * kPP * 8) + up((size_t)k * 4);  // small matrices, the output permutation
   total += 16 * 256;                        // flags and counters, alignment of the caller's workspace

@@ -77,11 +77,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   const int nwg = gridDim.x, wg = blockIdx.x;
   const int64_t row0 = (int64_t)wg * rows;
   if (tid == 0) {
-    if (wg == 0) {
-      __hip_atomic_store(a.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // before anyone counts up
-    }
-    arrive(a.sync);
+    arrive(a.sync + kSyncWord);
     flag[1] = 0;
   }
 
@@ -152,7 +148,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
   }
-  if (tid == 0) flag[0] = all_arrived(a.sync, a.base + nwg, a.polls);
+  if (tid == 0) flag[0] = all_arrived(a.sync + kSyncWord, a.base + nwg, a.polls);
   __syncthreads();
   if (!flag[0]) return;  // nothing has been written
 
@@ -292,7 +288,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   // the places that the launch before this one has written are for the next one
   for (int64_t e = (int64_t)wg * kThreads + tid; e < a.clear; e += (int64_t)nwg * kThreads)
     reinterpret_cast<long long*>(a.used)[e] = -1;
-  if (tid == 0) __hip_atomic_fetch_add(a.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (wg == 0) {  // the slot, in host memory, before the word that says so
+    __threadfence_system();
+    __syncthreads();
+  }
+  if (tid == 0 && __hip_atomic_fetch_add(a.sync + kSyncDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == a.base + nwg)
+    __hip_atomic_store(a.done, nwg, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 template <int B, bool STEP>

@@ -123,14 +123,15 @@ hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int
 //     packed copy of them.  slot_g: the Gram matrix before the first factorization; slot_r: the factor of both.
 // Rows of the slots are kPartialPad long.
 // The workgroups wait for one another.  If, after `polls` looks, one has not started yet (other work holds the compute units), the
-// launch leaves without having done anything, and so do all further ones with this sync: *done is then 0, else the number of
-// workgroups, and the caller takes the step by other launches.  base: the workgroups of all launches with this sync so far.
+// launch leaves without having done anything, and so do all further ones with this sync, and the caller takes the step by other
+// launches.  Slots and *done are in coherent host memory: *done becomes the number of workgroups when all of them are through and
+// the slots are written; it is not touched else.  base: the workgroups of all launches with this sync so far.
 // exchange: fused_exchange() doubles of all ones, which the launch writes; the first `clear` doubles of used, those of the launch
 // before, become all ones again (two such areas take turns).
 constexpr int kFusedStepBlock = 8;
 constexpr int kFusedGroups = 256;   // workgroups at most
 constexpr int kFusedColumns = 256;  // j of launch_fused_step at most
-constexpr int kSyncWord = 16, kSyncWords = 64;  // the word that counts, on a cache line of its own
+constexpr int kSyncWord = 16, kSyncDone = 48, kSyncWords = 64;  // the words that count, on cache lines of their own, from 0 on
 struct FusedStep {
   const int64_t* rowptr = nullptr;
   const int32_t* col = nullptr;
