@@ -362,7 +362,7 @@ struct KTimer {
 };
 
 constexpr int kPP = kPartialPad;
-constexpr int kSlotDoubles = 3 * kPP * kPP;  // A, R, G
+constexpr int kSlotDoubles = 3 * kPP * kPP + 8;  // A, R, G, the word that a fused launch writes at its end
 constexpr int kMaxPartials = 512;
 constexpr double kAbsDrop2 = 1e-24;  // squared norm below which a residual column counts as zero
 constexpr double kRelDrop = 1e-12;   // squared sine below which a column counts as dependent
@@ -1185,9 +1185,7 @@ struct Solver {
   int64_t exchange_used = 0;  // by the last launch
   int exchange_turn = 0;
   size_t lds_limit = 0;
-  // the entry of a slot that a fused launch leaves its number of workgroups in, at its end: past the columns that the slot's rows use
-  static_assert(16 < kPP, "a slot's rows leave room");
-  int* done_word(double* slot) { return reinterpret_cast<int*>(slot + kPP - 1); }
+  int* done_word(double* slot) { return reinterpret_cast<int*>(slot + 3 * kPP * kPP); }
 
   // the last b columns of the rotation workspace, which only a rotation of more vectors than b less than it holds takes (a restart)
   double* ahead_block() { return rot.p + (size_t)n * (rot_cols - b); }
@@ -1296,7 +1294,7 @@ struct Solver {
     flag.alloc(kSyncWords);
     marks.alloc(2);
     int32_t &hflag = marks.p[0], &hcount = marks.p[1];
-    HIP_TRY(hipMemsetAsync(flag.p, 0, kSyncWords * sizeof(int), st));
+    HIP_TRY(hipMemsetAsync(flag.p, 0, sizeof(int), st));
     HIP_TRY(hipMemcpyAsync(&nnz, rowptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (nnz < 0) SC_THROW(SC_ECSR);
@@ -1363,8 +1361,7 @@ struct Solver {
     if (exchange_len) {
       lds_limit = std::min((size_t)device_lds_limit(), kFusedLds);
       exchange.alloc(2 * exchange_len);
-      HIP_TRY(hipMemsetAsync(exchange.p, 0xff, 2 * exchange_len * sizeof(double), st));
-      if (polls < 0) HIP_TRY(hipMemsetAsync(flag.p + kSyncWord, 0x80, sizeof(int), st));
+      HIP_TRY(launch_fused_prepare(exchange.p, 2 * exchange_len, reinterpret_cast<uint32_t*>(flag.p), polls < 0, st));
     }
     small.alloc(3 * kPP * kPP);
     max_slots = m / b + 4;
@@ -2688,8 +2685,50 @@ namespace {
 // Block QR on caller-visible scratch: part (kMaxPartials * b * kPP doubles), gpart (kGramPartials * kPP * kPP) and
 // small (5 * kPP * kPP).  Every entry of the scratch is written by a kernel before a kernel reads it, so its contents
 // on entry do not matter.
+// done: where the fused launch's word goes, host memory or (read_back) device memory.  r_out and g_out come from the fused launch
+// directly; the rest of its scratch is exchange (fused_exchange(...) doubles, among part and gpart) and sync.
+struct QrFused {
+  double* exchange = nullptr;
+  uint32_t* sync = nullptr;
+  int* done = nullptr;
+  bool read_back = false;
+};
 void run_block_qr(double* basis, int64_t n, int64_t ld, int j, int b, double* r_out, double* g_out, double* part,
-                  double* gpart, double* small, hipStream_t st) {
+                  double* gpart, double* small, const QrFused& fused, hipStream_t st) {
+  const size_t lds_limit = std::min((size_t)device_lds_limit(), kFusedLds);
+  const int rows = std::getenv("SCEIG_NO_FUSED") ? 0 : fused_qr_rows(n, b, lds_limit);
+  if (rows) {
+    const int groups = fused_groups(n, rows), polls = fused_polls();
+    FusedStep a;
+    a.basis = basis;
+    a.n = n;
+    a.ld = ld;
+    a.j = j;
+    a.rows = rows;
+    a.slot_g = g_out;
+    a.slot_r = r_out;
+    a.slot_ld = b;
+    a.done = fused.done;
+    a.sync = fused.sync;
+    a.polls = polls;
+    a.exchange = a.used = fused.exchange;
+    a.abs_tol2[0] = kAbsDrop2;
+    a.rel_tol[0] = kRelDrop;
+    a.abs_tol2[1] = kAbsDrop2Again;
+    a.rel_tol[1] = kRelDropAgain;
+    int done = 0;
+    if (!fused.read_back) *fused.done = 0;
+    HIP_TRY(launch_fused_prepare(fused.exchange, fused_exchange(groups, 0, 0, b), fused.sync, polls < 0, st));
+    HIP_TRY(launch_fused_qr(a, b, lds_limit, st));
+    if (fused.read_back) HIP_TRY(hipMemcpyAsync(&done, fused.done, sizeof(int), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (!fused.read_back) done = *static_cast<volatile int*>(fused.done);
+    if (done == groups) {
+      fused_qrs.fetch_add(1, std::memory_order_relaxed);
+      return;
+    }
+    if (done != 0) SC_THROW(SC_EHIP);
+  }
   double* rinv = small;
   double* r1 = small + kPP * kPP;
   double* rr = small + 2 * kPP * kPP;
@@ -2718,6 +2757,7 @@ struct BlockQrCall {
 constexpr size_t kQrPartDoubles = (size_t)kMaxPartials * kMaxBlock * kPP;
 constexpr size_t kQrGpartDoubles = (size_t)kGramPartials * kPP * kPP;
 constexpr size_t kQrSmallDoubles = (size_t)5 * kPP * kPP;
+static_assert((kFusedGroups + 1) * 2 * kMaxBlock * kMaxBlock <= (int)kQrGpartDoubles, "a fused launch's exchange fits where the partial Gram blocks do");
 constexpr size_t kQrScratchDoubles = kQrPartDoubles + kQrGpartDoubles + kQrSmallDoubles;
 
 }  // namespace
@@ -3186,7 +3226,11 @@ int sc_block_qr(double* basis, int64_t n, int64_t ld, int32_t j, int32_t b, doub
         part.alloc((size_t)kMaxPartials * c->b * kPP);
         gpart.alloc(kQrGpartDoubles);
         small.alloc(kQrSmallDoubles);
-        run_block_qr(c->basis, c->n, c->ld, c->j, c->b, c->r, c->g, part.p, gpart.p, small.p, c->st);
+        DevBuf<uint32_t> sync;
+        PinnedBuf<int> done;
+        sync.alloc(kSyncWords);
+        done.alloc(1);
+        run_block_qr(c->basis, c->n, c->ld, c->j, c->b, c->r, c->g, part.p, gpart.p, small.p, {gpart.p, sync.p, done.p, false}, c->st);
         return SC_OK;
       },
       &ctx);
@@ -3204,7 +3248,8 @@ int sc_block_qr_noalloc(double* basis, int64_t n, int64_t ld, int32_t j, int32_t
         BlockQrCall* c = static_cast<BlockQrCall*>(p);
         double* sp = scratch_on_current_device();
         run_block_qr(c->basis, c->n, c->ld, c->j, c->b, c->r, c->g, sp, sp + kQrPartDoubles,
-                     sp + kQrPartDoubles + kQrGpartDoubles, c->st);
+                     sp + kQrPartDoubles + kQrGpartDoubles,
+                     {sp + kQrPartDoubles, reinterpret_cast<uint32_t*>(sp), reinterpret_cast<int*>(sp) + kSyncWord + 16, true}, c->st);
         return SC_OK;
       },
       &ctx);

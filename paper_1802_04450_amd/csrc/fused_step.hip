@@ -48,7 +48,9 @@ __device__ __forceinline__ void add_up(const double* part, double* sums, int tot
 // ---- the launch --------------------------------------------------------------------------------------------------------
 __host__ __device__ inline int basis_pitch(int j) { return (j + 15) / 16 * 16 + 1; }  // odd: no bank conflicts along rows or columns
 template <int B>
-constexpr int kRed = kWaves * B * B > kThreads ? kWaves * B * B : kThreads;  // partial sums of the waves
+constexpr int kGramParts = B > 16 ? kWaves / 2 : kWaves;  // Gram matrices of waves, or of pairs of them
+template <int B>
+constexpr int kRed = kGramParts<B> * B * B > kThreads ? kGramParts<B> * B * B : kThreads;  // partial sums of the waves
 template <int B, bool STEP>
 size_t fused_lds_bytes(int j, int rows) {
   size_t d = (size_t)rows * (B + 1) + kRed<B> + 2 * B * kCholPitch<B> + 2;
@@ -63,6 +65,8 @@ template <int B, bool STEP>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) void fused_step_kernel(FusedStep a) {
   extern __shared__ double lds[];
   constexpr int WP = B + 1;  // row pitch of the block and of the coefficients
+  constexpr int NT = B > 16 ? 2 : 1;
+  static_assert(!STEP || B == kFusedStepBlock, "a tile holds the block");
   const int rows = a.rows, j = a.j;
   const int pitch = STEP ? basis_pitch(j) : 0, j16 = pitch - 1;
   double* const w = lds;
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       if (flag[1]) return;
       if (wg == 0 && tid < B * B) {
         slot_sum += h[(j - B + tid / B) * WP + tid % B];
-        a.slot_a[tid / B * kPartialPad + tid % B] = slot_sum;
+        a.slot_a[tid / B * a.slot_ld + tid % B] = slot_sum;
       }
       for (int t = wave; t < rows / 16; t += kWaves) {
         d4 acc = {0.0, 0.0, 0.0, 0.0};
@@ -225,30 +229,50 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     double* const part = at;
     double* const sums = part + (int64_t)nwg * B * B;
     at = sums + B * B;
-    d4 acc = {0.0, 0.0, 0.0, 0.0};
+    d4 acc[NT][NT];
+#pragma unroll
+    for (int x = 0; x < NT; ++x)
+#pragma unroll
+      for (int y = 0; y < NT; ++y) acc[x][y] = (d4){0.0, 0.0, 0.0, 0.0};
     for (int k0 = 16 * wave; k0 < rows; k0 += 16 * kWaves)
 #pragma unroll
       for (int k = k0 + g; k < k0 + 16 + g; k += 4) {
-        const double x = i < B ? w[k * WP + i] : 0.0;
-        acc = MFMA_F64(x, x, acc);
+        double v[NT];
+#pragma unroll
+        for (int x = 0; x < NT; ++x) v[x] = i < B ? w[k * WP + 16 * x + i] : 0.0;
+#pragma unroll
+        for (int x = 0; x < NT; ++x)
+#pragma unroll
+          for (int y = 0; y < NT; ++y) acc[x][y] = MFMA_F64(v[x], v[y], acc[x][y]);
       }
-    if (i < B)
 #pragma unroll
-      for (int rr = 0; rr < B / 4; ++rr) red[wave * B * B + (4 * rr + g) * B + i] = acc[rr];  // rows from B on vanish
+    for (int turn = 0; turn < kWaves / kGramParts<B>; ++turn) {  // the second wave of a pair adds to what the first has left
+      if (turn > 0) __syncthreads();
+      if (i < B && wave / kGramParts<B> == turn)
+#pragma unroll
+        for (int x = 0; x < NT; ++x)
+#pragma unroll
+          for (int y = 0; y < NT; ++y)
+#pragma unroll
+            for (int rr = 0; rr < (B < 16 ? B / 4 : 4); ++rr) {  // rows from B on vanish
+              double* const to = red + wave % kGramParts<B> * B * B + (16 * x + 4 * rr + g) * B + 16 * y + i;
+              *to = (turn > 0 ? *to : 0.0) + acc[x][y][rr];
+            }
+    }
     __syncthreads();
-    if (tid < B * B) {
-      double sum = red[tid];
+    for (int e = tid; e < B * B; e += kThreads) {
+      double sum = red[e];
 #pragma unroll
-      for (int x = 1; x < kWaves; ++x) sum += red[x * B * B + tid];
-      put(part + wg * B * B + tid, sum);
+      for (int x = 1; x < kGramParts<B>; ++x) sum += red[x * B * B + e];
+      put(part + (int64_t)wg * B * B + e, sum);
     }
     __syncthreads();
     add_up(part, sums, B * B, wg, nwg, red, flag + 1);
-    if (tid < B * B) {
+    for (int e = tid; e < B * B; e += kThreads) {
       double one[1];
-      if (!get(sums + tid, 0, 1, one)) flag[1] = 1;
-      gram[tid] = one[0];
-      if (pass == 0 && wg == 0) a.slot_g[tid / B * kPartialPad + tid % B] = one[0];
+      if (!get(sums + e, 0, 1, one)) flag[1] = 1;
+      gram[e] = one[0];
+      if (pass == 0 && wg == 0 && a.slot_g) a.slot_g[e / B * a.slot_ld + e % B] = one[0];
     }
     __syncthreads();
     if (flag[1]) return;
@@ -256,17 +280,22 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     if (wave == 0) chol_rows<B>(gram, B, factor + pass * B * kCholPitch<B>, a.abs_tol2[pass], a.rel_tol[pass]);
     __syncthreads();
     for (int t = wave; t < rows / 16; t += kWaves) {
-      d4 out = {0.0, 0.0, 0.0, 0.0};
+      d4 out[NT];
+#pragma unroll
+      for (int y = 0; y < NT; ++y) out[y] = (d4){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int k = 0; k < B; k += 4) {
         const double x = w[(16 * t + i) * WP + k + g];
-        const double y = i < B ? made[i * kCholPitch<B> + B + k + g] : 0.0;
-        out = MFMA_F64(x, y, out);
+#pragma unroll
+        for (int y = 0; y < NT; ++y)
+          out[y] = MFMA_F64(x, i < B ? made[(16 * y + i) * kCholPitch<B> + B + k + g] : 0.0, out[y]);
       }
       // the wave alone reads these rows, and has
       if (i < B)
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) w[(16 * t + 4 * rr + g) * WP + i] = out[rr];
+        for (int y = 0; y < NT; ++y)
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) w[(16 * t + 4 * rr + g) * WP + 16 * y + i] = out[y][rr];
     }
     __syncthreads();
   }
@@ -275,15 +304,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     if (row < a.n) {
       const double v = w[e / B * WP + e % B];
       a.basis[row * a.ld + j + e % B] = v;
-      a.z[row * B + e % B] = v;
+      if (a.z) a.z[row * B + e % B] = v;
     }
   }
-  if (wg == 0 && tid < B * B) {  // the product of both factors
-    const int r = tid / B, t = tid % B;
-    double sum = 0.0;
+  if (wg == 0 && a.slot_r) {  // the product of both factors
+    for (int e = tid; e < B * B; e += kThreads) {
+      const int r = e / B, t = e % B;
+      double sum = 0.0;
 #pragma unroll
-    for (int x = 0; x < B; ++x) sum += factor[(B + r) * kCholPitch<B> + x] * factor[x * kCholPitch<B> + t];
-    a.slot_r[r * kPartialPad + t] = sum;
+      for (int x = 0; x < B; ++x) sum += factor[(B + r) * kCholPitch<B> + x] * factor[x * kCholPitch<B> + t];
+      a.slot_r[r * a.slot_ld + t] = sum;
+    }
   }
   // the places that the launch before this one has written are for the next one
   for (int64_t e = (int64_t)wg * kThreads + tid; e < a.clear; e += (int64_t)nwg * kThreads)
@@ -294,6 +325,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
   }
   if (tid == 0 && __hip_atomic_fetch_add(a.sync + kSyncDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == a.base + nwg)
     __hip_atomic_store(a.done, nwg, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// What a first launch finds: nothing exchanged, nobody arrived.
+__global__ __launch_bounds__(kThreads) void fused_prepare_kernel(long long* __restrict__ exchange, int64_t len,
+                                                                 uint32_t* __restrict__ sync, uint32_t word) {
+  if (blockIdx.x == 0 && threadIdx.x >= kSyncWord && threadIdx.x < kSyncWords) sync[threadIdx.x] = threadIdx.x == kSyncWord ? word : 0;
+  for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < len; e += (int64_t)gridDim.x * kThreads) exchange[e] = -1;
 }
 
 template <int B, bool STEP>
@@ -308,6 +346,13 @@ hipError_t launch(const FusedStep& a, hipStream_t st) {
 
 }  // namespace
 
+hipError_t launch_fused_prepare(double* exchange, int64_t len, uint32_t* sync, bool stopped, hipStream_t st) {
+  const int64_t groups = std::min<int64_t>((len + 4 * kThreads - 1) / (4 * kThreads), 1024);
+  hipLaunchKernelGGL(fused_prepare_kernel, dim3((unsigned)std::max<int64_t>(groups, 1)), dim3(kThreads), 0, st,
+                     reinterpret_cast<long long*>(exchange), len, sync, stopped ? kStopped : 0u);
+  return hipGetLastError();
+}
+
 int fused_step_rows(int64_t n, int j, size_t lds_limit) {
   for (int rows : {64, 128})
     if (n <= (int64_t)rows * 128) return j <= kFusedColumns && fused_lds_bytes<kFusedStepBlock, true>(j, rows) <= lds_limit ? rows : 0;
@@ -316,8 +361,10 @@ int fused_step_rows(int64_t n, int j, size_t lds_limit) {
 
 int fused_qr_rows(int64_t n, int b, size_t lds_limit) {
   const int64_t rows = std::max<int64_t>(64, (n + 16 * kFusedGroups - 1) / (16 * kFusedGroups) * 16);
-  if ((b != 8 && b != 16) || rows > 4096) return 0;
-  const size_t lds = b == 8 ? fused_lds_bytes<8, false>(0, (int)rows) : fused_lds_bytes<16, false>(0, (int)rows);
+  if ((b != 8 && b != 16 && b != 32) || rows > 4096) return 0;
+  const size_t lds = b == 8    ? fused_lds_bytes<8, false>(0, (int)rows)
+                     : b == 16 ? fused_lds_bytes<16, false>(0, (int)rows)
+                               : fused_lds_bytes<32, false>(0, (int)rows);
   return lds <= lds_limit ? (int)rows : 0;
 }
 
@@ -329,7 +376,7 @@ hipError_t launch_fused_step(const FusedStep& a, size_t lds_limit, hipStream_t s
 
 hipError_t launch_fused_qr(const FusedStep& a, int b, size_t lds_limit, hipStream_t st) {
   if (a.rows <= 0 || a.rows != fused_qr_rows(a.n, b, lds_limit) || a.j < 0) return hipErrorInvalidValue;
-  return b == 8 ? launch<8, false>(a, st) : launch<16, false>(a, st);
+  return b == 8 ? launch<8, false>(a, st) : b == 16 ? launch<16, false>(a, st) : launch<32, false>(a, st);
 }
 
 }  // namespace sceig

@@ -121,17 +121,17 @@ hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int
 //     the sum of both passes' coefficients of columns [j - kFusedStepBlock, j).
 //   launch_fused_qr: columns [j, j + b) are made orthonormal by two Cholesky QRs as launch_gram_cholesky does, and z becomes a
 //     packed copy of them.  slot_g: the Gram matrix before the first factorization; slot_r: the factor of both.
-// Rows of the slots are kPartialPad long.
+// Rows of the slots are slot_ld long; z and, but for launch_fused_step, the slots may be null.
 // The workgroups wait for one another.  If, after `polls` looks, one has not started yet (other work holds the compute units), the
 // launch leaves without having done anything, and so do all further ones with this sync, and the caller takes the step by other
-// launches.  Slots and *done are in coherent host memory: *done becomes the number of workgroups when all of them are through and
+// launches.  Slots and *done may be in coherent host memory: *done becomes the number of workgroups when all of them are through and
 // the slots are written; it is not touched else.  base: the workgroups of all launches with this sync so far.
 // exchange: fused_exchange() doubles of all ones, which the launch writes; the first `clear` doubles of used, those of the launch
 // before, become all ones again (two such areas take turns).
 constexpr int kFusedStepBlock = 8;
 constexpr int kFusedGroups = 256;   // workgroups at most
 constexpr int kFusedColumns = 256;  // j of launch_fused_step at most
-constexpr int kSyncWord = 16, kSyncDone = 48, kSyncWords = 64;  // the words that count, on cache lines of their own, from 0 on
+constexpr int kSyncWord = 16, kSyncDone = 48, kSyncWords = 64;  // the words that count, on cache lines of their own; 0 .. 15 are the caller's
 struct FusedStep {
   const int64_t* rowptr = nullptr;
   const int32_t* col = nullptr;
@@ -141,6 +141,7 @@ struct FusedStep {
   int j = 0, from1 = 0, from2 = 0;
   int rows = 0;  // rows a workgroup: fused_step_rows, fused_qr_rows
   double *slot_a = nullptr, *slot_g = nullptr, *slot_r = nullptr;
+  int slot_ld = kPartialPad;
   int* done = nullptr;
   uint32_t* sync = nullptr;
   uint32_t base = 0;
@@ -155,6 +156,8 @@ int fused_qr_rows(int64_t n, int b, size_t lds_limit);
 inline int fused_groups(int64_t n, int rows) { return (int)((n + rows - 1) / rows); }
 // Sums of j1 and j2 x b coefficients and two Gram matrices, with the workgroups' shares of them.
 inline int64_t fused_exchange(int groups, int j1, int j2, int b) { return (int64_t)(groups + 1) * b * (j1 + j2 + 2 * b); }
+// Before the first launch with this sync (kSyncWords) and these areas; stopped: as after a launch that has left.
+hipError_t launch_fused_prepare(double* exchange, int64_t len, uint32_t* sync, bool stopped, hipStream_t st);
 hipError_t launch_fused_step(const FusedStep& a, size_t lds_limit, hipStream_t st);
 hipError_t launch_fused_qr(const FusedStep& a, int b, size_t lds_limit, hipStream_t st);
 

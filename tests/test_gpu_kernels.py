@@ -302,6 +302,49 @@ def test_block_qr_over_its_rules(B, n, b):
     assert np.max(np.abs(g - w.T @ w)) <= 1e-12 * np.abs(w.T @ w).max()
 
 
+# the QR as one launch: from one row to the most that 256 workgroups hold in LDS (557,056, 258,048 and 94,208 rows), and one more;
+# odd offsets and leading dimensions; a zero and a dependent column
+@pytest.mark.parametrize("n,j,b,one", [(1, 0, 8, True), (63, 1, 16, True), (65, 3, 32, True), (16_385, 5, 8, True), (557_056, 0, 8, True),
+                                       (557_057, 0, 8, False), (100_003, 2, 16, True), (258_048, 1, 16, True), (258_049, 1, 16, False),
+                                       (20_001, 7, 32, True), (94_208, 0, 32, True), (94_209, 0, 32, False), (3000, 2, 4, False)])
+def test_block_qr_in_one_launch(B, monkeypatch, n, j, b, one):
+    """One launch, the ordinary ones, and one that finds that its workgroups cannot all have started: the same block and factor."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + b)
+    start = torch.randn((n, j + b + 3), dtype=torch.float64, generator=gen, device="cuda")
+    gone = []
+    if n > 3 * b:
+        start[:, j + 2] = 0.0
+        start[:, j + b - 1] = 2.0 * start[:, j] - start[:, j + 1]
+        gone = [2, b - 1]
+    rank = min(n, b) - len(gone)
+    runs = []
+    for env in ({}, {"SCEIG_NO_FUSED": "1"}, {"SCEIG_FUSED_POLLS": "-1"}):
+        for name, value in env.items():
+            monkeypatch.setenv(name, value)
+        before = B.sc_counter(B.SC_COUNTER_FUSED_QRS)
+        basis = start.clone()
+        r, g = B.sc_block_qr(basis, j, b)
+        assert B.sc_counter(B.SC_COUNTER_FUSED_QRS) - before == (1 if one and not env else 0)
+        for name in env:
+            monkeypatch.delenv(name)
+        w, q = start[:, j:j + b], basis[:, j:j + b]
+        assert torch.equal(basis[:, :j], start[:, :j]) and torch.equal(basis[:, j + b:], start[:, j + b:])
+        gram = w.T.contiguous() @ w.contiguous()
+        assert (g - gram).abs().max() <= 1e-12 * gram.abs().max()
+        keep = [x for x in range(min(n, b)) if x not in gone]
+        eye = torch.zeros((b, b), dtype=torch.float64, device="cuda")
+        eye[keep, keep] = 1.0
+        assert (q.T.contiguous() @ q.contiguous() - eye).abs().max() <= 1e-13 and len(keep) == rank
+        assert bool((q[:, gone] == 0.0).all()) and bool((r[gone, :] == 0.0).all())
+        wide = keep + gone
+        assert (q @ r[:, wide] - w[:, wide]).abs().max() <= 1e-11 * w.abs().max()
+        runs.append((basis, r))
+    for basis, r in runs[:1] + runs[2:]:
+        assert (r - runs[1][1])[:, keep].abs().max() <= 1e-10 * r.abs().max()
+        assert (basis - runs[1][0]).abs().max() <= 1e-10
+
+
 def test_block_qr_drops_dependent_and_zero_columns(B):
     n, b = 3000, 8
     rng = np.random.default_rng(5)
