@@ -2536,12 +2536,13 @@ struct KMeans {
     DevBuf<int32_t> start;
     DevBuf<int> changes;
     DevBuf<char> work, lwork, swork;
-    PinnedBuf<int> hchanges;
+    PinnedBuf<int> counts;  // of a labelling: labels changed, points undecided, its number
     ct.alloc((size_t)ldx * ldc);
     cnorm.alloc((size_t)k);
     start.alloc((size_t)k + 1);
     changes.alloc(kChangeInts);
-    hchanges.alloc(kChangeInts);
+    counts.alloc(3);
+    counts.p[2] = 0;
     const size_t wb = kmeans_update_workspace(n, ldx, k), lwb = label_workspace(n, ldx, k);
     work.alloc(wb);
     if (lwb) lwork.alloc(lwb);
@@ -2580,13 +2581,21 @@ struct KMeans {
       if (timing) HIP_TRY(hipEventRecord(events.v.back().b, st));
       dist_bytes += 8.0 * ((double)n * d + (double)k * d) + 8.0 * (double)n;
       dist_flops += 2.0 * (double)n * k * d;
-      HIP_TRY(hipMemcpyAsync(hchanges.p, changes.p, sizeof(int) * kChangeInts, hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipStreamSynchronize(st));
+      // The centres are moved before it is known whether any label has changed: the host learns that while they are (it used to
+      // wait for a copy with nothing under way, 15 us an iteration), and centres of the labels that they come from stay as they are.
+      HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, work.p, wb, start.p, c, ct.p, ldc, cnorm.p, changes.p,
+                                     {counts.p, it + 1}, st));
+      const volatile int* number = counts.p + 2;
+      const double until = now_s() + 2e-3;
+      while (*number != it + 1 && now_s() < until)
+        for (int i = 0; i < 64 && *number != it + 1; ++i) {
+        }
+      if (*number != it + 1) HIP_TRY(hipStreamSynchronize(st));
+      std::atomic_thread_fence(std::memory_order_acquire);
       ++iters;
-      last_changes = 0;
-      for (int s = 0; s < kChangeSlots; ++s) last_changes += hchanges.p[s * kChangeStride];
+      last_changes = counts.p[0];
       // where the screen leaves much to the fp64 labelling it only comes on top
-      if (screen && hchanges.p[kChangeUndecided] > n / 4)
+      if (screen && counts.p[1] > n / 4)
         screen = false;
       else if (screen)
         screened_labellings.fetch_add(1, std::memory_order_relaxed);
@@ -2594,7 +2603,6 @@ struct KMeans {
         converged = 1;
         break;
       }
-      HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, work.p, wb, start.p, c, ct.p, ldc, cnorm.p, changes.p, st));
     }
     if (stats) {
       // objective of the final labelling against the centres it was computed from (after a converged run these are

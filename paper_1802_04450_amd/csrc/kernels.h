@@ -351,7 +351,7 @@ hipError_t launch_label_listed(const double* x, int64_t ldx, int64_t n, const in
 // never); 0 bytes where it is not made.  launch_label_copy makes the
 // reduced copy of the points, once; launch_label_screened does a labelling step and leaves the number of points that the
 // screen could not decide, which were labelled in fp64, at changes[kChangeUndecided].
-constexpr int kChangeUndecided = 1;
+constexpr int kChangeUndecided = 1, kChangeSum = 2;
 int label_screen_steps(int64_t n, int64_t ldx, int k);
 size_t label_screen_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, hipStream_t st);
@@ -361,11 +361,17 @@ hipError_t launch_label_screened(const double* x, int64_t ldx, int d, int64_t n,
 hipError_t launch_fill_int32(int32_t* a, int64_t n, int32_t value, int use_iota, hipStream_t st);
 // centres = means of their points (grouped by label, fixed summation order); empty clusters keep their centre.  ct, cnorm
 // and changes as launch_centroid_operand would then make them.  work: kmeans_update_workspace(n, ldx, k) bytes; start:
-// device int32[k+1] (first grouped position of every cluster)
+// device int32[k+1] (first grouped position of every cluster).  The labelling's counts, which the caller decides by whether to
+// go on, are in report.host (coherent host memory) once report.host[2] = report.number, long before the update is done: [0] labels
+// changed, [1] points that the screen could not decide.  If no label has changed the centres come out as they are.
+struct LabelReport {
+  int* host;
+  int number;
+};
 size_t kmeans_update_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, void* work,
                                   size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
-                                  int* changes, hipStream_t st);
+                                  int* changes, const LabelReport& report, hipStream_t st);
 // Algorithm 5 with the uniform numbers u[0..k-1] supplied by the host; chosen: device int32[k].  screen = 0: without the
 // reduced copy of the points, which makes the draws faster and takes a quarter of their bytes
 size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen);

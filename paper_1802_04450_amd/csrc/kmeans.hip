@@ -96,9 +96,30 @@ __global__ __launch_bounds__(kT) void iota_fill_kernel(int32_t* __restrict__ a, 
 constexpr int kMaxBins = 1024;
 constexpr int kSortBlock = 4 * kT;
 
+// The labelling's counts to the host's memory, by one wave (see launch_centroid_update).
+// changes[kChangeSum], for the launches behind it: the labels changed; if none has, they leave everything as it is.
+__device__ __forceinline__ void report_labelling(int* __restrict__ changes, const LabelReport& report) {
+  int sum = changes[(threadIdx.x & 63) * kChangeStride];
+  static_assert(kChangeSlots == 64, "a lane per slot");
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if ((threadIdx.x & 63) == 0) {
+    changes[kChangeSum] = sum;
+    report.host[0] = sum;
+    report.host[1] = changes[kChangeUndecided];
+    __threadfence_system();
+    __hip_atomic_store(report.host + 2, report.number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+__global__ __launch_bounds__(64) void label_report_kernel(int* __restrict__ changes, LabelReport report) {
+  report_labelling(changes, report);
+}
+
 __global__ __launch_bounds__(kT) void label_count_kernel(const int32_t* __restrict__ label, int64_t n, int k, int nb,
-                                                         int32_t* __restrict__ count) {
+                                                         int32_t* __restrict__ count, int* __restrict__ changes,
+                                                         LabelReport report) {
   __shared__ int bin[kMaxBins];
+  if (blockIdx.x == 0 && threadIdx.x < 64) report_labelling(changes, report);
   for (int c = threadIdx.x; c < k; c += kT) bin[c] = 0;
   __syncthreads();
 #pragma unroll
@@ -112,7 +133,8 @@ __global__ __launch_bounds__(kT) void label_count_kernel(const int32_t* __restri
 
 // count[c][.] becomes its exclusive prefix sum, total[c] the sum.  A wave per cluster.
 __global__ __launch_bounds__(kT) void label_offset_kernel(int32_t* __restrict__ count, int k, int nb,
-                                                          int32_t* __restrict__ total) {
+                                                          int32_t* __restrict__ total, const int* __restrict__ changed) {
+  if (*changed == 0) return;
   const int lane = threadIdx.x & 63;
   const int c = blockIdx.x * (kT / 64) + (threadIdx.x >> 6);
   if (c >= k) return;
@@ -137,7 +159,9 @@ __global__ __launch_bounds__(kT) void label_offset_kernel(int32_t* __restrict__ 
 __global__ __launch_bounds__(kT) void label_scatter_kernel(const int32_t* __restrict__ label, int64_t n, int k, int bits,
                                                            int nb, const int32_t* __restrict__ count,
                                                            const int32_t* __restrict__ total,
-                                                           int32_t* __restrict__ start, int32_t* __restrict__ member) {
+                                                           int32_t* __restrict__ start, int32_t* __restrict__ member,
+                                                           const int* __restrict__ changed) {
+  if (*changed == 0) return;
   __shared__ int base[kT / 64][kMaxBins];
   __shared__ int wave_sum[kT / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -236,7 +260,8 @@ template <int DL>
 __global__ __launch_bounds__(kT) void cluster_sum_kernel(const double* __restrict__ x, int64_t ldx,
                                                          const int32_t* __restrict__ member,
                                                          const int32_t* __restrict__ start, int parts,
-                                                         double* __restrict__ part) {
+                                                         double* __restrict__ part, const int* __restrict__ changed) {
+  if (*changed == 0) return;
   constexpr int S = kT / DL;
   __shared__ double2 red[kT];
   const int j = blockIdx.x, q = blockIdx.y;
@@ -282,6 +307,7 @@ __global__ __launch_bounds__(kT) void centroid_finish_kernel(const double* __res
                                                              const int32_t* __restrict__ start, int d, int64_t ldx,
                                                              double* __restrict__ c, double* __restrict__ ct, int64_t ldc,
                                                              double* __restrict__ cnorm, int* __restrict__ changes) {
+  if (changes[kChangeSum] == 0) return;  // then the slots are zero
   const int j = blockIdx.x;
   if (j == 0 && threadIdx.x < kChangeSlots) changes[threadIdx.x * kChangeStride] = 0;
   const int len = start[j + 1] - start[j];
@@ -1463,7 +1489,7 @@ size_t kmeans_update_workspace(int64_t n, int64_t ldx, int k) {
 
 hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, void* work,
                                   size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
-                                  int* changes, hipStream_t st) {
+                                  int* changes, const LabelReport& report, hipStream_t st) {
   if (n <= 0 || n > INT32_MAX || work_bytes < kmeans_update_workspace(n, ldx, k)) return hipErrorInvalidValue;
   const int parts = update_parts(n, ldx, k);
   char* base = static_cast<char*>(work);
@@ -1475,15 +1501,17 @@ hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n
     const int nb = (int)((n + kSortBlock - 1) / kSortBlock);
     int32_t* count = reinterpret_cast<int32_t*>(base);
     int32_t* total = count + (size_t)k * nb;
-    hipLaunchKernelGGL(label_count_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, nb, count);
-    hipLaunchKernelGGL(label_offset_kernel, dim3((unsigned)((k + 3) / 4)), dim3(kT), 0, st, count, k, nb, total);
+    hipLaunchKernelGGL(label_count_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, nb, count, changes,
+                       report);
+    hipLaunchKernelGGL(label_offset_kernel, dim3((unsigned)((k + 3) / 4)), dim3(kT), 0, st, count, k, nb, total, changes + kChangeSum);
     hipLaunchKernelGGL(label_scatter_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, bits_for(k), nb, count, total,
-                       start, member);
+                       start, member, changes + kChangeSum);
   } else {
     int32_t* sorted_label = reinterpret_cast<int32_t*>(base);
     int32_t* ident = sorted_label + n;
     char* temp = reinterpret_cast<char*>(((uintptr_t)(ident + n) + 255) / 256 * 256);
     size_t sb = label_sort_bytes(n);
+    hipLaunchKernelGGL(label_report_kernel, dim3(1), dim3(64), 0, st, changes, report);
     hipLaunchKernelGGL(iota_fill_kernel, dim3(blocks(n)), dim3(kT), 0, st, ident, n, 0, 1);
     // one value more than there are clusters: a label outside [0, k), all ones in these bits, comes after them all
     const hipError_t e = rocprim::radix_sort_pairs(temp, sb, label, sorted_label, ident, member, (size_t)n, 0u,
@@ -1493,7 +1521,7 @@ hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n
   }
 #define SC_SUM(DLV)                                                                                                     \
   hipLaunchKernelGGL((cluster_sum_kernel<DLV>), dim3((unsigned)k, (unsigned)parts, (unsigned)((ldx + 2 * DLV - 1) / (2 * DLV))), \
-                     dim3(kT), 0, st, x, ldx, member, start, parts, sums)
+                     dim3(kT), 0, st, x, ldx, member, start, parts, sums, changes + kChangeSum)
   if (ldx <= 4) SC_SUM(2);
   else if (ldx <= 8) SC_SUM(4);
   else if (ldx <= 16) SC_SUM(8);
