@@ -1175,11 +1175,17 @@ struct Solver {
     bool tentative;
     int groups;
     bool whole;  // it was the whole step
+    int number;  // of the launch
   };
   std::vector<Pending> pending_steps;
+  // The step behind the one that is being inspected, enqueued before it is known whether it will be asked for: the device would
+  // have nothing to do meanwhile.  If it is not, its block and its slot are written over.
+  Pending ahead_step;
+  bool step_ahead = false;
   // What those launches share: the word that counts their workgroups, behind the validation flag in one zeroed block, and two
   // areas for the sums under way, which take turns.
   uint32_t arrivals = 0;  // workgroups so far
+  int fused_number = 0;   // launches so far
   DevBuf<double> exchange;
   size_t exchange_len = 0;  // doubles of an area
   int64_t exchange_used = 0;  // by the last launch
@@ -1366,6 +1372,7 @@ struct Solver {
     small.alloc(3 * kPP * kPP);
     max_slots = m / b + 4;
     slots.alloc((size_t)max_slots * kSlotDoubles);
+    for (int i = 0; i < max_slots; ++i) *done_word(slot(i)) = 0;  // a launch of another solve may have had the same number
     ystage.alloc(kYStageDoubles);
     rot_cols = (size_t)std::min(m, std::max(m / 2 + b, 2 * b));
     rot.alloc((size_t)n * rot_cols);
@@ -1394,7 +1401,7 @@ struct Solver {
     stats.block_steps += 1;
     stats.spmv_cols += b;
     const int groups = tentative ? 0 : enqueue_fused_step(ja, si);
-    pending_steps.push_back({ja, si, tentative, groups ? groups : enqueue_step_launches(ja, si, tentative), groups > 0});
+    pending_steps.push_back({ja, si, tentative, groups ? groups : enqueue_step_launches(ja, si, tentative), groups > 0, fused_number});
   }
 
   // A fused launch's arguments, but for its product and Gram-Schmidt.
@@ -1411,7 +1418,7 @@ struct Solver {
     a.slot_r = sl + kPP * kPP;
     a.slot_g = sl + 2 * kPP * kPP;
     a.done = done_word(sl);
-    *a.done = 0;  // what used the slot before has been looked at
+    a.number = ++fused_number;
     a.sync = reinterpret_cast<uint32_t*>(flag.p);
     a.base = arrivals;
     a.polls = polls;
@@ -1463,7 +1470,10 @@ struct Solver {
     timer.end(kFamQr, 24.0 * (double)n * b, 4.0 * (double)n * b * b);
     return groups;
   }
-  void enqueue_start_qr(int ngram) { pending_steps.push_back({b, 0, false, enqueue_qr(nl, ngram, 0), false}); }
+  void enqueue_start_qr(int ngram) {
+    const int groups = enqueue_qr(nl, ngram, 0);
+    pending_steps.push_back({b, 0, false, groups, false, fused_number});
+  }
 
   int enqueue_step_launches(int ja, int si, bool tentative) {
     const int jt = nl + ja;
@@ -1500,7 +1510,7 @@ struct Solver {
       const double until = now_s() + 1e-3;
       do {
         for (int i = 0; i < 64; ++i)
-          if (*done == pending_steps.back().groups) {
+          if (*done == pending_steps.back().number) {
             std::atomic_thread_fence(std::memory_order_acquire);
             return;
           }
@@ -1515,15 +1525,16 @@ struct Solver {
       const Pending& p = pending_steps[q];
       if (!p.groups) continue;
       const int done = *done_word(slot(p.si));
-      if (done == p.groups) {
+      if (done == p.number) {
         (p.whole ? fused_steps : fused_qrs).fetch_add(1, std::memory_order_relaxed);
         continue;
       }
-      if (done != 0) SC_THROW(SC_EHIP);  // workgroups that had all started did not come to an end
+      if (done == -p.number) SC_THROW(SC_EHIP);  // workgroups that had all started did not come to an end
       // Its workgroups did not all come to run, and it has done nothing, nor have the fused launches behind it: block and packed
       // operand are as they were.  It and all behind it are taken again by the ordinary launches, and no further one is tried.
       if (debug_on()) std::fprintf(stderr, "[sceig] a fused launch's workgroups did not all start: ordinary launches from here on\n");
       no_fused = true;
+      step_ahead = false;
       const std::vector<Pending> again(pending_steps.begin() + q, pending_steps.end());
       pending_steps.clear();
       for (const Pending& r : again) {
@@ -1951,11 +1962,19 @@ struct Solver {
           tentative_allowed && ncomp > 0 && (double)(k - b) > 4.0 * std::max(ncomp - (k - b), 1);
       if (check_open && filtered) next_check = 1;
       if (tentative_allowed) next_check = 1;  // a look after the cheap first step costs far less than a full second step
+      bool goes_on = false;  // the last inspection has asked for the step behind the one it looked at
       while (!phase_over) {
         if (next_slot >= max_slots) SC_THROW(SC_EDOMAIN);  // cannot happen: a cycle has at most m/b steps
         // the phase's first step, inspected right after it, with room for its block in the basis
         const bool tentative = tentative_allowed && steps_in_phase == 0 && ja == b && next_check <= 1 && ja + b <= cap;
-        enqueue_step(ja, next_slot, tentative);
+        if (step_ahead && goes_on) {
+          stats.block_steps += 1;
+          stats.spmv_cols += b;
+          pending_steps.push_back(ahead_step);
+        } else {
+          enqueue_step(ja, next_slot, tentative);
+        }
+        step_ahead = goes_on = false;
         ++next_slot;
         ++pending;
         ++steps_in_phase;
@@ -1968,6 +1987,11 @@ struct Solver {
         }
         // ---- inspect: bring the slots over and assemble T
         T.touch(ja + b);
+        if (!full && !tentative && pending_steps.back().whole && next_slot < max_slots) {
+          const int groups = enqueue_fused_step(ja + b, next_slot);
+          ahead_step = {ja + b, next_slot, false, groups, true, fused_number};
+          step_ahead = groups > 0;
+        }
         fetch_slots();
         if (!start_block_seen) {
           const double* r0 = hslot(0) + kPP * kPP;
@@ -2288,6 +2312,7 @@ struct Solver {
           ja += b;
           next_check = schedule_check(rho[std::min({want, nreal, nsel}) - 1], (cap - ja) / b + 1);
           if (check_more > 0) next_check = check_more;
+          goes_on = true;
         }
         (void)assembled;
       }
@@ -2731,11 +2756,11 @@ void run_block_qr(double* basis, int64_t n, int64_t ld, int j, int b, double* r_
     if (fused.read_back) HIP_TRY(hipMemcpyAsync(&done, fused.done, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (!fused.read_back) done = *static_cast<volatile int*>(fused.done);
-    if (done == groups) {
+    if (done == a.number) {
       fused_qrs.fetch_add(1, std::memory_order_relaxed);
       return;
     }
-    if (done != 0) SC_THROW(SC_EHIP);
+    if (done == -a.number) SC_THROW(SC_EHIP);
   }
   double* rinv = small;
   double* r1 = small + kPP * kPP;

@@ -58,6 +58,11 @@ size_t fused_lds_bytes(int j, int rows) {
   return d * sizeof(double);
 }
 
+// A wait that should have ended did not.
+__device__ __forceinline__ void failed(const FusedStep& a) {
+  if (threadIdx.x == 0) __hip_atomic_store(a.done, -a.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Workgroup w holds rows [w rows, w rows + rows) of the block in LDS throughout, and with STEP those of the basis.  What the
 // others need of it are its partial sums of the coefficients and of the Gram matrices; each is added up in two goes: every
 // workgroup adds its share of the entries over all workgroups, then all read the sums.
@@ -202,7 +207,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
         }
       }
       __syncthreads();
-      if (flag[1]) return;
+      if (flag[1]) return failed(a);
       if (wg == 0 && tid < B * B) {
         slot_sum += h[(j - B + tid / B) * WP + tid % B];
         a.slot_a[tid / B * a.slot_ld + tid % B] = slot_sum;
@@ -275,7 +280,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       if (pass == 0 && wg == 0 && a.slot_g) a.slot_g[e / B * a.slot_ld + e % B] = one[0];
     }
     __syncthreads();
-    if (flag[1]) return;
+    if (flag[1]) return failed(a);
     const double* const made = factor + pass * B * kCholPitch<B>;
     if (wave == 0) chol_rows<B>(gram, B, factor + pass * B * kCholPitch<B>, a.abs_tol2[pass], a.rel_tol[pass]);
     __syncthreads();
@@ -324,7 +329,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
     __syncthreads();
   }
   if (tid == 0 && __hip_atomic_fetch_add(a.sync + kSyncDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == a.base + nwg)
-    __hip_atomic_store(a.done, nwg, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(a.done, a.number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // What a first launch finds: nothing exchanged, nobody arrived.

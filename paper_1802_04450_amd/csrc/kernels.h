@@ -124,8 +124,8 @@ hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int
 // Rows of the slots are slot_ld long; z and, but for launch_fused_step, the slots may be null.
 // The workgroups wait for one another.  If, after `polls` looks, one has not started yet (other work holds the compute units), the
 // launch leaves without having done anything, and so do all further ones with this sync, and the caller takes the step by other
-// launches.  Slots and *done may be in coherent host memory: *done becomes the number of workgroups when all of them are through and
-// the slots are written; it is not touched else.  base: the workgroups of all launches with this sync so far.
+// launches.  Slots and *done may be in coherent host memory: *done becomes `number` when all workgroups are through and the slots
+// are written (-number: they had all started, but did not come to an end); it is not touched else.  base: the workgroups of all launches with this sync so far.
 // exchange: fused_exchange() doubles of all ones, which the launch writes; the first `clear` doubles of used, those of the launch
 // before, become all ones again (two such areas take turns).
 constexpr int kFusedStepBlock = 8;
@@ -143,6 +143,7 @@ struct FusedStep {
   double *slot_a = nullptr, *slot_g = nullptr, *slot_r = nullptr;
   int slot_ld = kPartialPad;
   int* done = nullptr;
+  int number = 1;
   uint32_t* sync = nullptr;
   uint32_t base = 0;
   int polls = 0;
