@@ -2607,9 +2607,14 @@ struct KMeans {
       dist_bytes += 8.0 * ((double)n * d + (double)k * d) + 8.0 * (double)n;
       dist_flops += 2.0 * (double)n * k * d;
       // The centres are moved before it is known whether any label has changed: the host learns that while they are (it used to
-      // wait for a copy with nothing under way, 15 us an iteration), and centres of the labels that they come from stay as they are.
-      HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, work.p, wb, start.p, c, ct.p, ldc, cnorm.p, changes.p,
-                                     {counts.p, it + 1}, st));
+      // wait for a copy with nothing under way, 15 us an iteration), and centres of the labels that they come from stay as they
+      // are.  Not after the second labelling, the last one where clusters lie well apart: the launches would come to nothing.
+      auto update = [&](int which) {
+        HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, work.p, wb, start.p, c, ct.p, ldc, cnorm.p, changes.p,
+                                       {counts.p, it + 1}, which, st));
+      };
+      const bool wait = it == 1;
+      update(wait ? kUpdateReport : kUpdateReport | kUpdateCentres);
       const volatile int* number = counts.p + 2;
       const double until = now_s() + 2e-3;
       while (*number != it + 1 && now_s() < until)
@@ -2628,6 +2633,7 @@ struct KMeans {
         converged = 1;
         break;
       }
+      if (wait) update(kUpdateCentres);
     }
     if (stats) {
       // objective of the final labelling against the centres it was computed from (after a converged run these are

@@ -58,5 +58,12 @@ __device__ __forceinline__ bool all_arrived(uint32_t* word, uint32_t target, int
   return seen == target;
 }
 
+// Stores to coherent host memory, and the wait that orders them: a release fence would write the whole L2 back first (5 to 10 us).
+template <class T>
+__device__ __forceinline__ void put_host(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void host_written() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 }  // namespace
 }  // namespace sceig

@@ -60,7 +60,7 @@ size_t fused_lds_bytes(int j, int rows) {
 
 // A wait that should have ended did not.
 __device__ __forceinline__ void failed(const FusedStep& a) {
-  if (threadIdx.x == 0) __hip_atomic_store(a.done, -a.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (threadIdx.x == 0) put_host(a.done, -a.number);
 }
 
 // Workgroup w holds rows [w rows, w rows + rows) of the block in LDS throughout, and with STEP those of the basis.  What the
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       if (flag[1]) return failed(a);
       if (wg == 0 && tid < B * B) {
         slot_sum += h[(j - B + tid / B) * WP + tid % B];
-        a.slot_a[tid / B * a.slot_ld + tid % B] = slot_sum;
+        put_host(a.slot_a + tid / B * a.slot_ld + tid % B, slot_sum);
       }
       for (int t = wave; t < rows / 16; t += kWaves) {
         d4 acc = {0.0, 0.0, 0.0, 0.0};
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       double one[1];
       if (!get(sums + e, 0, 1, one)) flag[1] = 1;
       gram[e] = one[0];
-      if (pass == 0 && wg == 0 && a.slot_g) a.slot_g[e / B * a.slot_ld + e % B] = one[0];
+      if (pass == 0 && wg == 0 && a.slot_g) put_host(a.slot_g + e / B * a.slot_ld + e % B, one[0]);
     }
     __syncthreads();
     if (flag[1]) return failed(a);
@@ -318,18 +318,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) v
       double sum = 0.0;
 #pragma unroll
       for (int x = 0; x < B; ++x) sum += factor[(B + r) * kCholPitch<B> + x] * factor[x * kCholPitch<B> + t];
-      a.slot_r[r * a.slot_ld + t] = sum;
+      put_host(a.slot_r + r * a.slot_ld + t, sum);
     }
   }
   // the places that the launch before this one has written are for the next one
   for (int64_t e = (int64_t)wg * kThreads + tid; e < a.clear; e += (int64_t)nwg * kThreads)
     reinterpret_cast<long long*>(a.used)[e] = -1;
   if (wg == 0) {  // the slot, in host memory, before the word that says so
-    __threadfence_system();
+    host_written();
     __syncthreads();
   }
   if (tid == 0 && __hip_atomic_fetch_add(a.sync + kSyncDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == a.base + nwg)
-    __hip_atomic_store(a.done, a.number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    put_host(a.done, a.number);
 }
 
 // What a first launch finds: nothing exchanged, nobody arrived.

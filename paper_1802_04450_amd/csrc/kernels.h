@@ -365,6 +365,8 @@ hipError_t launch_fill_int32(int32_t* a, int64_t n, int32_t value, int use_iota,
 // device int32[k+1] (first grouped position of every cluster).  The labelling's counts, which the caller decides by whether to
 // go on, are in report.host (coherent host memory) once report.host[2] = report.number, long before the update is done: [0] labels
 // changed, [1] points that the screen could not decide.  If no label has changed the centres come out as they are.
+// which: the launch that reports, the ones behind it, or both.
+constexpr int kUpdateReport = 1, kUpdateCentres = 2;
 struct LabelReport {
   int* host;
   int number;
@@ -372,7 +374,7 @@ struct LabelReport {
 size_t kmeans_update_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, void* work,
                                   size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
-                                  int* changes, const LabelReport& report, hipStream_t st);
+                                  int* changes, const LabelReport& report, int which, hipStream_t st);
 // Algorithm 5 with the uniform numbers u[0..k-1] supplied by the host; chosen: device int32[k].  screen = 0: without the
 // reduced copy of the points, which makes the draws faster and takes a quarter of their bytes
 size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen);

@@ -105,10 +105,10 @@ __device__ __forceinline__ void report_labelling(int* __restrict__ changes, cons
   for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
   if ((threadIdx.x & 63) == 0) {
     changes[kChangeSum] = sum;
-    report.host[0] = sum;
-    report.host[1] = changes[kChangeUndecided];
-    __threadfence_system();
-    __hip_atomic_store(report.host + 2, report.number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    put_host(report.host, sum);
+    put_host(report.host + 1, changes[kChangeUndecided]);
+    host_written();
+    put_host(report.host + 2, report.number);
   }
 }
 __global__ __launch_bounds__(64) void label_report_kernel(int* __restrict__ changes, LabelReport report) {
@@ -1489,7 +1489,7 @@ size_t kmeans_update_workspace(int64_t n, int64_t ldx, int k) {
 
 hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, void* work,
                                   size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
-                                  int* changes, const LabelReport& report, hipStream_t st) {
+                                  int* changes, const LabelReport& report, int which, hipStream_t st) {
   if (n <= 0 || n > INT32_MAX || work_bytes < kmeans_update_workspace(n, ldx, k)) return hipErrorInvalidValue;
   const int parts = update_parts(n, ldx, k);
   char* base = static_cast<char*>(work);
@@ -1501,8 +1501,9 @@ hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n
     const int nb = (int)((n + kSortBlock - 1) / kSortBlock);
     int32_t* count = reinterpret_cast<int32_t*>(base);
     int32_t* total = count + (size_t)k * nb;
-    hipLaunchKernelGGL(label_count_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, nb, count, changes,
-                       report);
+    if (which & kUpdateReport)
+      hipLaunchKernelGGL(label_count_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, nb, count, changes, report);
+    if (!(which & kUpdateCentres)) return hipGetLastError();
     hipLaunchKernelGGL(label_offset_kernel, dim3((unsigned)((k + 3) / 4)), dim3(kT), 0, st, count, k, nb, total, changes + kChangeSum);
     hipLaunchKernelGGL(label_scatter_kernel, dim3((unsigned)nb), dim3(kT), 0, st, label, n, k, bits_for(k), nb, count, total,
                        start, member, changes + kChangeSum);
@@ -1511,7 +1512,8 @@ hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n
     int32_t* ident = sorted_label + n;
     char* temp = reinterpret_cast<char*>(((uintptr_t)(ident + n) + 255) / 256 * 256);
     size_t sb = label_sort_bytes(n);
-    hipLaunchKernelGGL(label_report_kernel, dim3(1), dim3(64), 0, st, changes, report);
+    if (which & kUpdateReport) hipLaunchKernelGGL(label_report_kernel, dim3(1), dim3(64), 0, st, changes, report);
+    if (!(which & kUpdateCentres)) return hipGetLastError();
     hipLaunchKernelGGL(iota_fill_kernel, dim3(blocks(n)), dim3(kT), 0, st, ident, n, 0, 1);
     // one value more than there are clusters: a label outside [0, k), all ones in these bits, comes after them all
     const hipError_t e = rocprim::radix_sort_pairs(temp, sb, label, sorted_label, ident, member, (size_t)n, 0u,
