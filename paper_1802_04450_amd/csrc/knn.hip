@@ -854,6 +854,17 @@ constexpr int kMostLost = 1024;  // more of them in a round go to the fp64 kerne
 
 // The k nearest of the listed candidates, by (exact squared distance, index).  A wave per query: a lane computes a
 // candidate's distance as the other kernels do, its rank is the number of listed candidates before it.
+// Eight coordinates of 64 rows at a time go through LDS, four lanes a row: a lane that read its own row asked for a line of its
+// own in every load, 64 a load, and that was what the launch lasted.  Ranks come from the upper words of the distances, of which
+// no two are alike in most queries; where some are, the ranks do not add up to what they then do, and the distances and indices
+// themselves are compared.  100,000 queries of 32 coordinates, 20 neighbours: 212 -> 152 us (32
+// coordinates of all rows at once: 162); what is left is rows from the L2s, 17 TB/s if all lists are full.
+constexpr int kRankPitch = 5;                       // double2s a row: four and one for the banks
+constexpr int kRankStage = 64 * kRankPitch + 16;    // ... and the query's
+// waves a workgroup: four, or one where lists are so long (171 neighbours) that four take more than 64 KB of LDS
+inline int rank_threads(int cap) { return cap <= 576 ? kT : 64; }
+inline size_t rank_lds_bytes(int cap) { return (size_t)(rank_threads(cap) / 64) * (kRankStage * 16 + ((size_t)cap + 3) / 4 * 4 * 16); }
+typedef double v2d __attribute__((ext_vector_type(2)));
 __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restrict__ xp, int dp, int64_t q0, int64_t nq,
                                                          const int32_t* __restrict__ src, int k, int cap,
                                                          const int32_t* __restrict__ count,
@@ -862,14 +873,19 @@ __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restric
                                                          int32_t* __restrict__ tile_flag, int32_t* __restrict__ tiles,
                                                          int32_t* __restrict__ ntiles, int32_t* __restrict__ idx_out,
                                                          double* __restrict__ dist_out) {
-  extern __shared__ double lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  double* dist = lds + (size_t)wave * cap;
-  int32_t* idx = reinterpret_cast<int32_t*>(lds + (size_t)(kT / 64) * cap) + (size_t)wave * cap;
-  const int64_t q = (int64_t)blockIdx.x * (kT / 64) + wave;
+  extern __shared__ v2d rank_lds[];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  const int cap4 = (cap + 3) / 4 * 4;
+  v2d* const stage = rank_lds + (size_t)wave * kRankStage;
+  v2d* const query = stage + 64 * kRankPitch;
+  double* const dist = reinterpret_cast<double*>(rank_lds + (size_t)waves * kRankStage) + (size_t)wave * cap4;
+  int32_t* const idx = reinterpret_cast<int32_t*>(dist + (size_t)(waves - wave) * cap4) + (size_t)wave * cap4;
+  uint32_t* const upper = reinterpret_cast<uint32_t*>(idx + (size_t)waves * cap4);
+  const int64_t q = (int64_t)blockIdx.x * waves + wave;
   if (q >= nq) return;
   const int64_t i = src ? (int64_t)src[q0 + q] : q0 + q;
   if (i < 0) return;
+  const int32_t first = list[q * cap + (lane < cap ? lane : 0)];  // before it is known how many there are
   const int found = count[q];
   if (found > cap || found < k) {
     // no further count once there are too many: one counter for 100,000 queries is 1 ms
@@ -883,34 +899,81 @@ __global__ __launch_bounds__(kT) void screen_rank_kernel(const double* __restric
     if (lane == 0 && atomicExch(&tile_flag[i / kMq], 1) == 0) tiles[atomicAdd(ntiles, 1)] = (int32_t)(i / kMq);
     return;
   }
-  const double2* __restrict__ xp2 = reinterpret_cast<const double2*>(xp);
-  const double2* __restrict__ qr = xp2 + i * (dp / 2);
-  for (int c = lane; c < found; c += 64) {
-    const int32_t j = list[q * cap + c];
-    const double2* __restrict__ yr = xp2 + (int64_t)j * (dp / 2);
+  const v2d* __restrict__ qr = reinterpret_cast<const v2d*>(xp + i * dp);
+  for (int c0 = 0; c0 < found; c0 += 64) {
+    const int here = found - c0 < 64 ? found - c0 : 64;
+    const int32_t j = c0 == 0 ? first : list[q * cap + c0 + (lane < here ? lane : 0)];
+    int32_t row[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) row[u] = __shfl(j, 16 * u + lane / 4 < here ? 16 * u + lane / 4 : 0, 64);
     double ex = 0.0;
-#pragma unroll 8
-    for (int t = 0; t < dp / 2; ++t) {
-      const double2 qv = qr[t], yv = yr[t];
-      const double d0 = qv.x - yv.x;
-      ex = fma(d0, d0, ex);
-      const double d1 = qv.y - yv.y;
-      ex = fma(d1, d1, ex);
+    for (int t0 = 0; t0 < dp; t0 += 16) {  // 16 coordinates of all rows under way at once
+      v2d v[2][4], own = {0.0, 0.0};
+      if (lane < 8 && t0 + 2 * lane < dp) own = qr[t0 / 2 + lane];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int t = t0 + 8 * h + 2 * (lane & 3);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          v[h][u] = *reinterpret_cast<const v2d*>(xp + (int64_t)row[u] * dp + (t < dp ? t : 0));
+      }
+      if (lane < 8) query[lane] = own;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) stage[(16 * u + lane / 4) * kRankPitch + (lane & 3)] = v[h][u];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's own LDS operations complete in order
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const v2d yv = stage[lane * kRankPitch + p], qv = query[4 * h + p];
+          const bool in = t0 + 8 * h + 2 * p < dp;  // uniform; both rows' padding is even
+          const double d0 = in ? qv.x - yv.x : 0.0, d1 = in ? qv.y - yv.y : 0.0;
+          ex = fma(d0, d0, ex);
+          ex = fma(d1, d1, ex);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
     }
-    dist[c] = ex;
-    idx[c] = j;
+    if (lane < here) {
+      dist[c0 + lane] = ex;
+      idx[c0 + lane] = j;
+      upper[c0 + lane] = (uint32_t)__double2hiint(ex);
+    }
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // the wave's own LDS operations complete in order
+  if (lane < 3 && found + lane < cap4) upper[found + lane] = 0xffffffffu;  // no distance: up to a whole piece of four
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+  auto place = [&](int c, int rank) __attribute__((always_inline)) {
+    if (rank < k) {
+      idx_out[i * k + rank] = idx[c];
+      dist_out[i * k + rank] = sqrt(dist[c]);
+    }
+  };
+  if (found <= 128) {
+    const uint32_t own0 = lane < found ? upper[lane] : 0u, own1 = 64 + lane < found ? upper[64 + lane] : 0u;
+    int rank0 = 0, rank1 = 0;
+    for (int o = 0; o < found; o += 4) {
+      const uint4 h = *reinterpret_cast<const uint4*>(upper + o);
+      rank0 += (h.x < own0) + (h.y < own0) + (h.z < own0) + (h.w < own0);
+      if (found > 64) rank1 += (h.x < own1) + (h.y < own1) + (h.z < own1) + (h.w < own1);
+    }
+    int sum = rank0 + rank1;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (sum == found * (found - 1) / 2) {  // uniform; less where two are alike
+      if (lane < found) place(lane, rank0);
+      if (64 + lane < found) place(64 + lane, rank1);
+      return;
+    }
+  }
   for (int c = lane; c < found; c += 64) {
-    const double v = dist[c];
+    const double own = dist[c];
     const int32_t id = idx[c];
     int rank = 0;
-    for (int o = 0; o < found; ++o) rank += (dist[o] < v || (dist[o] == v && idx[o] < id)) ? 1 : 0;
-    if (rank < k) {
-      idx_out[i * k + rank] = id;
-      dist_out[i * k + rank] = sqrt(v);
-    }
+    for (int o = 0; o < found; ++o) rank += (dist[o] < own || (dist[o] == own && idx[o] < id)) ? 1 : 0;
+    place(c, rank);
   }
 }
 
@@ -1812,7 +1875,8 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
   int32_t* lost_count = *ntiles + 1;
   *bound = reinterpret_cast<double*>(w + p.off_bound);
   int64_t lost_before = 0;
-  const size_t rank_lds = (size_t)(kT / 64) * p.cap * 12;
+  const size_t rank_lds = rank_lds_bytes(p.cap);
+  const int rank_t = rank_threads(p.cap);
   const int qt = 4 * p.nq;
   hipError_t e = launch_fill_int32(flag, (n + kMq - 1) / kMq + 1 + kLostInts, 0, 0, st);  // the flags and the counts behind
   if (e != hipSuccess) return e;
@@ -2022,7 +2086,7 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     lost_before += lost;
     if (lost <= nq / 2) screen(true, t0, nt, nparts);
     int32_t* gone = reinterpret_cast<int32_t*>(gw + g.off_lost);
-    hipLaunchKernelGGL(screen_rank_kernel, dim3(blocks(nq * 64)), dim3(kT), rank_lds, st, xp, dp, q0, nq, src, k, p.cap, count,
+    hipLaunchKernelGGL(screen_rank_kernel, dim3((unsigned)((nq * 64 + rank_t - 1) / rank_t)), dim3(rank_t), rank_lds, st, xp, dp, q0, nq, src, k, p.cap, count,
                        list, &info->lost, gone, flag, *tiles, *ntiles, idx_out, dist_out);
     if (src)
       hipLaunchKernelGGL(group_exact_kernel, dim3(256), dim3(kExactThreads), 0, st, xp, dp, src, q0, qt, near, near_count,

@@ -85,6 +85,22 @@ def test_screened_search_matches_oracle(B, n, d, k, kind):
     assert np.all(idx != np.arange(n)[:, None])
 
 
+# whole coordinates: distances are exact and many are equal, in their upper words or altogether.  Lists of one and of several waves'
+# lengths, on both sides of where a workgroup has one wave (170 neighbours); coordinates that fill no piece of 8, 16 or 32
+@pytest.mark.parametrize("n,d,k,most", [(4000, 2, 10, 60), (4000, 2, 64, 60), (4003, 5, 33, 12), (4000, 18, 170, 9), (4000, 18, 171, 9),
+                                        (4100, 36, 20, 400), (4001, 128, 40, 3), (6000, 3, 200, 25), (3000, 40, 1, 100_000)])
+def test_screened_search_ranks_equal_distances_by_index(B, n, d, k, most):
+    rng = np.random.default_rng(n + d + k)
+    x = rng.integers(0, most, size=(n, d)).astype(np.float64)
+    sq = (x * x).sum(axis=1)
+    d2 = sq[:, None] + sq[None, :] - 2.0 * (x @ x.T)    # whole numbers below 2^53: exact
+    np.fill_diagonal(d2, np.inf)
+    near = np.argsort(d2, axis=1, kind="stable")[:, :k]
+    idx, dist = B.sc_knn_search(_dev(x, torch.float64), k)
+    np.testing.assert_array_equal(idx.cpu().numpy(), near)
+    np.testing.assert_array_equal(dist.cpu().numpy(), np.sqrt(np.take_along_axis(d2, near, axis=1)))
+
+
 def test_search_orders_equal_distances_by_index(B):
     # integer points on a line and on a small grid: many exactly equal distances, all sums exact in fp64
     x = np.arange(37, dtype=np.float64)[:, None]
