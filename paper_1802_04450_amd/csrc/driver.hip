@@ -989,6 +989,17 @@ double* enqueue_cheb_filter(const int64_t* rowptr, const int32_t* col, const dou
 
 constexpr int kGramPartials = 1024;
 
+// Waits for launch_report's word, or for the stream if that takes long.
+void wait_for_report(const int64_t* host, hipStream_t st) {
+  const volatile int64_t* there = host + 3;
+  const double until = now_s() + 2e-3;
+  while (*there == 0 && now_s() < until)
+    for (int i = 0; i < 64 && *there == 0; ++i) {
+    }
+  if (*there == 0) HIP_TRY(hipStreamSynchronize(st));
+  std::atomic_thread_fence(std::memory_order_acquire);
+}
+
 // Connected components by label propagation on the device, then rows and columns are renumbered so that every
 // component is contiguous (stable inside a component).  The sparse products then gather from a few hundred KB at
 // a time instead of from all over the vector; mathematically the result is a permutation similarity of the input.
@@ -1006,18 +1017,27 @@ int reorder_csr(const int64_t* rowptr, const int32_t* col, const double* val, in
   // nothing to do 2 us, or 8 where the grid is large (2,000 nodes, the renumbering: 256 us with two rounds a look, 184 now).
   const int batch = n <= 200000 ? 8 : 4;
   flag.alloc((size_t)batch);
+  PinnedBuf<int64_t> report;
+  report.alloc(4);
   HIP_TRY(launch_iota(label.p, n, st));
-  for (int looks = 0; looks < 100000; ++looks) {
-    int h = 0;
+  auto rounds = [&]() {
     HIP_TRY(hipMemsetAsync(flag.p, 0, (size_t)batch * sizeof(int), st));
     for (int q = 0; q < batch; ++q)
       HIP_TRY(launch_cc_round(rowptr, col, val, label.p, n, q ? flag.p + q - 1 : nullptr, flag.p + q, st));
-    HIP_TRY(hipMemcpyAsync(&h, flag.p + batch - 1, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    if (debug_on() && (looks % 50 == 49)) std::fprintf(stderr, "[sceig] component pass: %d rounds\n", batch * (looks + 1));
-    if (!h) break;
-    if (looks + 1 == 100000) SC_THROW(SC_EINTERNAL);  // labels still changing: they do not name the components yet
-  }
+  };
+  auto settle = [&]() {
+    for (int looks = 0; looks < 100000; ++looks) {
+      rounds();
+      HIP_TRY(launch_report(nullptr, flag.p + batch - 1, nullptr, report.p, st));
+      wait_for_report(report.p, st);
+      if (debug_on() && (looks % 50 == 49)) std::fprintf(stderr, "[sceig] component pass: %d rounds\n", batch * (looks + 1));
+      if (!report.p[1]) return;
+    }
+    SC_THROW(SC_EINTERNAL);  // labels still changing: they do not name the components yet
+  };
+  // Where eight rounds all but always do, the numbering goes on without a look, and is made again in the other case.
+  const bool unseen = batch == 8;
+  if (unseen) rounds(); else settle();
   // numbering, permuted row pointers and component index of every new row, all on the device
   int32_t* new_of_old_dev = new_of_old_out;
   if (!new_of_old_dev) {
@@ -1029,17 +1049,21 @@ int reorder_csr(const int64_t* rowptr, const int32_t* col, const double* val, in
   const size_t work_bytes = order_by_component_workspace(n);
   work.alloc(work_bytes);
   comp_dev.alloc((size_t)n);
-  HIP_TRY(order_by_component(rowptr, col, label.p, n, by_length, big_rows, work.p, work_bytes, old_of_new_out, new_of_old_dev,
-                             rowptr_out, comp_dev.p, st));
-  HIP_TRY(launch_permute_csr(rowptr, col, val, old_of_new_out, new_of_old_dev, rowptr_out, col_out, val_out, n, st));
-  if (comp_of_new) comp_of_new->assign((size_t)n, 0);  // before the first copy is under way: it may throw
-  int32_t last_comp = 0;
-  HIP_TRY(hipMemcpyAsync(&last_comp, comp_dev.p + (n - 1), sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  if (comp_of_new) {
-    HIP_TRY(hipMemcpyAsync(comp_of_new->data(), comp_dev.p, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  for (bool again = unseen;; again = false) {
+    HIP_TRY(order_by_component(rowptr, col, label.p, n, by_length, big_rows, work.p, work_bytes, old_of_new_out, new_of_old_dev,
+                               rowptr_out, comp_dev.p, st));
+    HIP_TRY(launch_permute_csr(rowptr, col, val, old_of_new_out, new_of_old_dev, rowptr_out, col_out, val_out, n, st));
+    HIP_TRY(launch_report(nullptr, flag.p + batch - 1, comp_dev.p + (n - 1), report.p, st));
+    wait_for_report(report.p, st);
+    if (!again || !report.p[1]) break;
+    settle();
   }
-  HIP_TRY(hipStreamSynchronize(st));
-  const int ncomp = (int)last_comp + 1;
+  const int ncomp = (int)report.p[2] + 1;
+  if (comp_of_new) {
+    comp_of_new->assign((size_t)n, 0);
+    HIP_TRY(hipMemcpyAsync(comp_of_new->data(), comp_dev.p, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+  }
   (void)nnz;
   return ncomp;
 }
@@ -1118,6 +1142,7 @@ struct Solver {
   const int32_t* rowinv = nullptr;  // device: internal row of each original row, null if not reordered
   std::vector<int32_t> comp_host;   // component index of each internal row (only after reorder())
   int ncomp = 0;
+  PinnedBuf<int64_t> report;  // launch_report
   PinnedBuf<double> slots;  // kernels write to it, none reads it
   // marks of the setup's checks and the number of long rows, as the device hands them back.  Here and not on setup()'s stack:
   // a setup that fails with such a copy under way leaves it in memory that outlasts it (released only once it is done).
@@ -1298,15 +1323,16 @@ struct Solver {
   void setup() {
     const double t0 = now_s();
     flag.alloc(kSyncWords);
-    marks.alloc(2);
-    int32_t &hflag = marks.p[0], &hcount = marks.p[1];
+    marks.alloc(1);
+    report.alloc(4);
+    int32_t& hflag = marks.p[0];
     HIP_TRY(hipMemsetAsync(flag.p, 0, sizeof(int), st));
-    HIP_TRY(hipMemcpyAsync(&nnz, rowptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    HIP_TRY(launch_validate_csr(rowptr, col, n, -1, flag.p, st));
+    HIP_TRY(launch_report(rowptr + n, flag.p, nullptr, report.p, st));
+    wait_for_report(report.p, st);
+    nnz = report.p[0];
+    hflag = (int32_t)report.p[1];
     if (nnz < 0) SC_THROW(SC_ECSR);
-    HIP_TRY(launch_validate_csr(rowptr, col, n, nnz, flag.p, st));
-    HIP_TRY(hipMemcpyAsync(&hflag, flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
     if (hflag & 3) SC_THROW(SC_ECSR);
     if (ws_limit > 0) {  // a workspace that cannot hold the solve is refused before anything is computed
       sc_options o{};
@@ -1327,9 +1353,10 @@ struct Solver {
     const double t2 = now_s();
     s.alloc((size_t)n);
     HIP_TRY(launch_degree_scaling(rowptr, val, n, nullptr, s.p, flag.p, st));
-    HIP_TRY(hipMemcpyAsync(&hflag, flag.p, sizeof(int), hipMemcpyDeviceToHost, st));
     if (b < 8) {  // otherwise the wait below does
-      HIP_TRY(hipStreamSynchronize(st));
+      HIP_TRY(launch_report(nullptr, flag.p, nullptr, report.p, st));
+      wait_for_report(report.p, st);
+      hflag = (int32_t)report.p[1];
       if (hflag & 4) SC_THROW(SC_EZERODEG);
       below_zero = (hflag & kBelowZero) != 0;
     }
@@ -1345,11 +1372,12 @@ struct Solver {
       lcount.alloc(1);
       longrows.alloc((size_t)n);
       HIP_TRY(long_row_list(rowptr, n, lwork.p, lw, longrows.p, lcount.p, st));
-      HIP_TRY(hipMemcpyAsync(&hcount, lcount.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-      HIP_TRY(hipStreamSynchronize(st));
+      HIP_TRY(launch_report(nullptr, flag.p, lcount.p, report.p, st));
+      wait_for_report(report.p, st);
+      hflag = (int32_t)report.p[1];
       if (hflag & 4) SC_THROW(SC_EZERODEG);
       below_zero = (hflag & kBelowZero) != 0;
-      nlong = hcount;
+      nlong = (int)report.p[2];
       if (!(flags & SC_FLAG_NO_START_FILTER)) plan_resident(rowptr, col, val_s.p, n, nnz, b, expected_filter_steps(k, b), st, &resident);
     }
     const double t3 = now_s();
@@ -3106,6 +3134,7 @@ int sc_reorder_csr(const int64_t* csr_rowptr, const int32_t* csr_col, const doub
         HIP_TRY(hipMemcpyAsync(&nnz, c->rp + c->n, sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
         const int ncomp = reorder_csr(c->rp, c->c, c->v, c->n, nnz, c->rpo, c->co, c->vo, c->oon, nullptr, nullptr, 0, c->st);
+        HIP_TRY(hipStreamSynchronize(c->st));
         if (c->nc) *c->nc = ncomp;
         return SC_OK;
       },

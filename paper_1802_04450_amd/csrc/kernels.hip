@@ -6,6 +6,7 @@
 //   D (16 x 16): lane l, register r (0..3) holds D[4*r + l / 16][l % 16]
 #include <type_traits>
 
+#include "exchange.h"
 #include "kernels.h"
 #include "wave_chol.h"
 
@@ -34,14 +35,20 @@ __global__ __launch_bounds__(kThreads) void validate_rowptr_kernel(const int64_t
                                                                    int64_t nnz, int* __restrict__ flag) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= n) return;
+  if (nnz < 0) nnz = rowptr[n];
   const int64_t a = rowptr[i], b = rowptr[i + 1];
   bool bad = a > b || a < 0 || b > nnz;
   if (i == 0 && a != 0) bad = true;
   if (bad) atomicOr(flag, 1);
 }
 
-__global__ __launch_bounds__(kThreads) void validate_col_kernel(const int32_t* __restrict__ col, int64_t nnz, int64_t n,
-                                                                int* __restrict__ flag) {
+// rowptr (may be null): nnz is there, and flag tells whether it can be believed
+__global__ __launch_bounds__(kThreads) void validate_col_kernel(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                                                int64_t nnz, int64_t n, int* __restrict__ flag) {
+  if (rowptr) {
+    if (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1) return;
+    nnz = rowptr[n];
+  }
   int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   bool bad = false;
@@ -1805,14 +1812,33 @@ __global__ __launch_bounds__(kThreads) void nullspace_fill_kernel(double* __rest
 // ============================================================================================
 // launch wrappers
 // ============================================================================================
+__global__ __launch_bounds__(64) void report_kernel(const int64_t* __restrict__ wide, const int32_t* __restrict__ a,
+                                                    const int32_t* __restrict__ b, int64_t* __restrict__ host) {
+  if (threadIdx.x != 0) return;
+  if (wide) put_host(host, *wide);
+  if (a) put_host(host + 1, (int64_t)*a);
+  if (b) put_host(host + 2, (int64_t)*b);
+  host_written();
+  put_host(host + 3, (int64_t)1);
+}
+
+hipError_t launch_report(const int64_t* wide, const int32_t* a, const int32_t* b, int64_t* host, hipStream_t st) {
+  host[3] = 0;
+  hipLaunchKernelGGL(report_kernel, dim3(1), dim3(64), 0, st, wide, a, b, host);
+  return hipGetLastError();
+}
+
 hipError_t launch_validate_csr(const int64_t* rowptr, const int32_t* col, int64_t n, int64_t nnz, int* flag,
                                hipStream_t st) {
   hipLaunchKernelGGL(validate_rowptr_kernel, dim3((unsigned)ceil_div64(n, kThreads)), dim3(kThreads), 0, st, rowptr,
                      n, nnz, flag);
-  if (nnz > 0) {
+  if (nnz < 0) {
+    hipLaunchKernelGGL(validate_col_kernel, dim3((unsigned)std::min<int64_t>(ceil_div64(4 * n, kThreads), 8192)), dim3(kThreads), 0, st,
+                       rowptr, col, nnz, n, flag);
+  } else if (nnz > 0) {
     int64_t blocks = ceil_div64(nnz, kThreads);
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(validate_col_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, col, nnz, n, flag);
+    hipLaunchKernelGGL(validate_col_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, st, nullptr, col, nnz, n, flag);
   }
   return hipGetLastError();
 }

@@ -653,3 +653,38 @@ def test_block_step_as_one_launch(B, monkeypatch, n, k, m, block, way):
         assert compare.orthonormality_defect(vec) <= 1e-12
         runs.append(lam)
     assert np.max(np.abs(runs[0] - runs[1])) <= 1e-11 and np.max(np.abs(runs[2] - runs[1])) <= 1e-11
+
+
+# more components among the nodes that a workgroup counts than its table has places, beside some too large for most work items
+@pytest.mark.parametrize("tiny,large", [(9000, (1500, 2000)), (700, (1273,)), (3000, ())])
+def test_component_sizes_of_many_components(B, tiny, large):
+    g = wl.disjoint_union(*[wl.random_weighted_connected(m, 4 * m, 3) for m in large], *[wl.complete(3)] * tiny)
+    perm = np.random.default_rng(tiny).permutation(g[3])
+    g = wl.relabel(g, perm)
+    rp, c, v, n = g
+    lam, vec, code, stats = solve(B, g, 20, 1e-9, block=16)
+    assert code == B.SC_OK and stats["components"] == tiny + len(large)
+    assert np.max(np.abs(lam)) <= 1e-9
+    assert compare.residual_norms(rp, c, v, lam, vec).max() <= 1e-8
+    assert compare.orthonormality_defect(vec) <= 1e-10
+
+
+# labels that need more rounds than are made before the numbering goes on unseen (a path in random order), and more nodes than that
+# is done for
+@pytest.mark.parametrize("n", [3000, 60_000, 200_000, 200_001])
+def test_renumbering_of_components_that_settle_late(B, n):
+    parts = [wl.path(n // 2), wl.ring(n // 3), wl.path(n - n // 2 - n // 3)]
+    g = wl.relabel(wl.disjoint_union(*parts), np.random.default_rng(n).permutation(n))
+    rp, c, v, n = g
+    comp = components.component_labels(rp, c, v)[1]
+    drp, dc, dv = B.csr_to_device(rp, c, v)
+    rpo, co, vo, old, count = B.sc_reorder_csr(drp, dc, dv, n)
+    assert count == 3
+    old = old.cpu().numpy()
+    assert np.array_equal(np.sort(old), np.arange(n)) and np.count_nonzero(np.diff(comp[old])) == 2
+    inverse = np.empty(n, dtype=np.int64)
+    inverse[old] = np.arange(n)
+    rpo, co = rpo.cpu().numpy(), co.cpu().numpy()
+    row = np.repeat(np.arange(n), np.diff(rp))
+    want = np.sort(inverse[row] * n + inverse[np.asarray(c)])
+    assert np.array_equal(np.sort(np.repeat(np.arange(n), np.diff(rpo)) * np.int64(n) + co), want)
