@@ -362,6 +362,16 @@ struct KTimer {
 };
 
 constexpr int kPP = kPartialPad;
+
+void wait_for_report(const int64_t* host, hipStream_t st) { HIP_TRY(wait_for_word(host + 3, 1, st)); }
+// the entry count of a CSR
+int64_t entry_count(const int64_t* rowptr, int64_t n, hipStream_t st) {
+  PinnedBuf<int64_t> report;
+  report.alloc(4);
+  HIP_TRY(launch_report(rowptr + n, nullptr, nullptr, report.p, st));
+  wait_for_report(report.p, st);
+  return report.p[0];
+}
 constexpr int kSlotDoubles = 3 * kPP * kPP + 8;  // A, R, G, the word that a fused launch writes at its end
 constexpr int kMaxPartials = 512;
 constexpr double kAbsDrop2 = 1e-24;  // squared norm below which a residual column counts as zero
@@ -557,6 +567,7 @@ struct ResidentPlan {
   DevBuf<double> sval;
   DevBuf<int64_t> slice_base;
   DevBuf<int32_t> slice_len, slice_first, row_extra;
+  PinnedBuf<int32_t> words;  // the items, until they are copied
 };
 
 int device_lds_limit() {
@@ -808,19 +819,23 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   starts.alloc((size_t)n);
   count.alloc(1);
   HIP_TRY(diagonal_blocks(rowptr, col, n, work.p, wb, starts.p, count.p, st));
-  int32_t nblk = 0;
-  HIP_TRY(hipMemcpyAsync(&nblk, count.p, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipStreamSynchronize(st));
+  PinnedBuf<int64_t> report;
+  report.alloc(4);
+  HIP_TRY(launch_report(nullptr, count.p, nullptr, report.p, st));
+  wait_for_report(report.p, st);
+  const int32_t nblk = (int32_t)report.p[1];
   if (nblk <= 0 || (int64_t)nblk > (int64_t)1 << 22) return;  // the item table stays small
   extra.alloc((size_t)kBlockCounts * nblk);
   HIP_TRY(launch_block_extra_chunks(rowptr, starts.p, nblk, n, extra.p, st));
-  std::vector<int32_t> hs((size_t)nblk + 1), hx((size_t)kBlockCounts * nblk);
-  HIP_TRY(hipMemcpyAsync(hs.data(), starts.p, (size_t)nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(hx.data(), extra.p, (size_t)kBlockCounts * nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  PinnedBuf<int32_t> hs, hx;
+  hs.alloc((size_t)nblk + 1);
+  hx.alloc((size_t)kBlockCounts * nblk);
+  HIP_TRY(hipMemcpyAsync(hs.p, starts.p, (size_t)nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+  HIP_TRY(hipMemcpyAsync(hx.p, extra.p, (size_t)kBlockCounts * nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
-  hs[nblk] = (int32_t)n;
+  hs.p[nblk] = (int32_t)n;
   const double general_step_s = general_step_seconds(nnz, b);
-  ItemPlanner planner(hs.data(), hx.data(), nblk, b, (size_t)lds_limit, no_sliced);
+  ItemPlanner planner(hs.p, hx.p, nblk, b, (size_t)lds_limit, no_sliced);
   ItemSplit best;
   const bool forced = std::getenv("SCEIG_FORCE_RESIDENT") != nullptr;
   if (!planner.best_split(n, general_step_s, steps, std::getenv("SCEIG_SLICED_COLUMNS"), forced, &best)) return;
@@ -848,13 +863,16 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
     const size_t sw = sliced_scan_workspace(nslots);
     swork.alloc(sw);
     const int nsliced = (int)(best.blocks.size() / kSliceBlockInts);
-    HIP_TRY(hipMemcpyAsync(d_blocks.p, best.blocks.data(), best.blocks.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    PinnedBuf<int32_t> blocks;
+    blocks.alloc(best.blocks.size());
+    std::copy(best.blocks.begin(), best.blocks.end(), blocks.p);
+    HIP_TRY(hipMemcpyAsync(d_blocks.p, blocks.p, best.blocks.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_TRY(sliced_extra_rows(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, st));
     HIP_TRY(sliced_copy_layout(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, nslots, d_desc.p, plan->slice_len.p,
                                plan->slice_first.p, d_entries.p, plan->slice_base.p, swork.p, sw, st));
-    int64_t total = 0;
-    HIP_TRY(hipMemcpyAsync(&total, plan->slice_base.p + nslots, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));  // also: the host vector above has been read
+    HIP_TRY(launch_report(plan->slice_base.p + nslots, nullptr, nullptr, report.p, st));
+    wait_for_report(report.p, st);
+    const int64_t total = report.p[0];
     const double basis_entries = best.sliced_entries;  // the padding comes on top
     if (debug_on())
       std::fprintf(stderr, "[sceig] sliced copy: %d slots, %lld entries for %.0f of the matrix\n", nslots,
@@ -870,7 +888,8 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
     plan->sval.alloc((size_t)total);
     HIP_TRY(sliced_copy_fill(rowptr, col, val, d_desc.p, d_list.p, plan->row_extra.p, nslots, plan->slice_base.p, d_entries.p, plan->scol.p, plan->sval.p,
                              st));
-    HIP_TRY(hipStreamSynchronize(st));  // the temporaries above are released on return
+    HIP_TRY(launch_report(nullptr, nullptr, nullptr, report.p, st));
+    wait_for_report(report.p, st);  // the temporaries above are released on return
   }
   {
     // Workgroups go to the eight XCDs in turn (workgroup i to XCD i mod 8), each XCD with an L2 of its own.  The items
@@ -896,8 +915,9 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   words.reserve(items.size() * kItemInts);
   for (const WorkItem& it : items) words.insert(words.end(), {it.row0, it.nrows, it.col0, it.shape, it.extra});
   plan->items.alloc(words.size());
-  HIP_TRY(hipMemcpyAsync(plan->items.p, words.data(), words.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipStreamSynchronize(st));  // `words` is pageable host memory
+  plan->words.alloc(words.size());  // the copy reads them when its turn comes
+  std::copy(words.begin(), words.end(), plan->words.p);
+  HIP_TRY(hipMemcpyAsync(plan->items.p, plan->words.p, words.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
   plan->nitems = (int)items.size();
   plan->lds_bytes = lds_max;
   plan->rest_row0 = rest_row0;
@@ -988,17 +1008,6 @@ double* enqueue_cheb_filter(const int64_t* rowptr, const int32_t* col, const dou
 }
 
 constexpr int kGramPartials = 1024;
-
-// Waits for launch_report's word, or for the stream if that takes long.
-void wait_for_report(const int64_t* host, hipStream_t st) {
-  const volatile int64_t* there = host + 3;
-  const double until = now_s() + 2e-3;
-  while (*there == 0 && now_s() < until)
-    for (int i = 0; i < 64 && *there == 0; ++i) {
-    }
-  if (*there == 0) HIP_TRY(hipStreamSynchronize(st));
-  std::atomic_thread_fence(std::memory_order_acquire);
-}
 
 // Connected components by label propagation on the device, then rows and columns are renumbered so that every
 // component is contiguous (stable inside a component).  The sparse products then gather from a few hundred KB at
@@ -1143,6 +1152,8 @@ struct Solver {
   std::vector<int32_t> comp_host;   // component index of each internal row (only after reorder())
   int ncomp = 0;
   PinnedBuf<int64_t> report;  // launch_report
+  PinnedBuf<int32_t> outpos_host;
+  PinnedBuf<double> evals_pinned;
   PinnedBuf<double> slots;  // kernels write to it, none reads it
   // marks of the setup's checks and the number of long rows, as the device hands them back.  Here and not on setup()'s stack:
   // a setup that fails with such a copy under way leaves it in memory that outlasts it (released only once it is done).
@@ -2370,14 +2381,15 @@ struct Solver {
       for (int t = 0; t < nfound; ++t) evals_host[t] = 1.0 - theta_locked[order[t]];
       std::vector<int32_t> outpos((size_t)nx, -1);  // output column of every locked basis column
       for (int t = 0; t < nfound; ++t) outpos[order[t]] = t;
-      HIP_TRY(hipMemcpyAsync(perm_d.p, outpos.data(), (size_t)nx * sizeof(int32_t), hipMemcpyHostToDevice, st));
+      outpos_host.alloc((size_t)nx);
+      std::copy(outpos.begin(), outpos.end(), outpos_host.p);
+      HIP_TRY(hipMemcpyAsync(perm_d.p, outpos_host.p, (size_t)nx * sizeof(int32_t), hipMemcpyHostToDevice, st));
       // rows of unit length are made on the way out (the packed block is free: it takes the factors), unless the rows
       // are to be scaled by D^-1/2 first
       const bool unit_rows = (flags & SC_FLAG_ROW_NORMALIZE) && !(flags & SC_FLAG_RANDOM_WALK_VECTORS);
       if (unit_rows) HIP_TRY(launch_row_factor(basis.p, n, ld, perm_d.p, nx, z.p, st));
       HIP_TRY(launch_gather_cols_colmajor(basis.p, n, ld, perm_d.p, nx, evecs_out, rowinv, unit_rows ? z.p : nullptr, st));
       rows_done = unit_rows;
-      HIP_TRY(hipStreamSynchronize(st));  // `outpos` is pageable host memory
     } else if (nx > 0) {
       std::vector<double> G((size_t)nx * nx, 0.0), hbuf((size_t)nx * kPP);
       const ProjectPlan plan = plan_project(n, nx, kMaxPartials);
@@ -2419,7 +2431,9 @@ struct Solver {
     // the embedding handed to k-means (Section II Step 4) with every point on the unit sphere
     if ((flags & SC_FLAG_ROW_NORMALIZE) && !rows_done && nfound > 0)
       HIP_TRY(launch_normalize_rows_colmajor(evecs_out, n, nfound, st));
-    HIP_TRY(hipMemcpyAsync(evals_out, evals_host.data(), (size_t)k_out * sizeof(double), hipMemcpyHostToDevice, st));
+    evals_pinned.alloc((size_t)k_out);
+    std::copy(evals_host.begin(), evals_host.end(), evals_pinned.p);
+    HIP_TRY(hipMemcpyAsync(evals_out, evals_pinned.p, (size_t)k_out * sizeof(double), hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (debug_on()) std::fprintf(stderr, "[sceig] t=%.4fs outputs written\n", now_s() - t_begin);
 
@@ -2668,13 +2682,14 @@ struct KMeans {
       // also the means of their clusters)
       const int np = kmeans_objective_parts();
       part.alloc((size_t)np);
-      std::vector<double> hp((size_t)np);
+      PinnedBuf<double> hp;
+      hp.alloc((size_t)np);
       if (converged || max_iter == 0 || iters == 0) {
         HIP_TRY(launch_objective(x.p, ldx, d, n, labels, k, c, part.p, st));
-        HIP_TRY(hipMemcpyAsync(hp.data(), part.p, sizeof(double) * np, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(hp.p, part.p, sizeof(double) * np, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         double tot = 0.0;
-        for (int p = 0; p < np; ++p) tot += hp[p];
+        for (int p = 0; p < np; ++p) tot += hp.p[p];
         stats->objective = tot;
       } else {
         stats->objective = -1.0;  // the centres moved after the last labelling
@@ -3181,9 +3196,7 @@ int sc_spmm_normalized(const int64_t* csr_rowptr, const int32_t* csr_col, const 
         static thread_local const double* last_val = nullptr;
         static thread_local int64_t last_n = -1, last_nnz = 0;
         if (last_rp != c->rp || last_col != c->c || last_val != c->v || last_n != c->n) {
-          int64_t nnz = 0;
-          HIP_TRY(hipMemcpyAsync(&nnz, c->rp + c->n, sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
-          HIP_TRY(hipStreamSynchronize(c->st));
+          const int64_t nnz = entry_count(c->rp, c->n, c->st);
           last_rp = c->rp;
           last_col = c->c;
           last_val = c->v;
@@ -3375,9 +3388,7 @@ int sc_chebyshev_filter(const int64_t* csr_rowptr, const int32_t* csr_col, const
   return guarded(
       [](void* p) {
         Ctx* c = static_cast<Ctx*>(p);
-        int64_t nnz = 0;
-        HIP_TRY(hipMemcpyAsync(&nnz, c->rp + c->n, sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
-        HIP_TRY(hipStreamSynchronize(c->st));
+        const int64_t nnz = entry_count(c->rp, c->n, c->st);
         if (nnz < 0) SC_THROW(SC_ECSR);
         DevBuf<double> s, vals, z, b1, b2, b3;
         DevBuf<int> flag;
@@ -3385,10 +3396,11 @@ int sc_chebyshev_filter(const int64_t* csr_rowptr, const int32_t* csr_col, const
         HIP_TRY(hipMemsetAsync(flag.p, 0, sizeof(int), c->st));
         s.alloc((size_t)c->n);
         HIP_TRY(launch_degree_scaling(c->rp, c->v, c->n, nullptr, s.p, flag.p, c->st));
-        int hflag = 0;
-        HIP_TRY(hipMemcpyAsync(&hflag, flag.p, sizeof(int), hipMemcpyDeviceToHost, c->st));
-        HIP_TRY(hipStreamSynchronize(c->st));
-        if (hflag & 4) SC_THROW(SC_EZERODEG);
+        PinnedBuf<int64_t> report;
+        report.alloc(4);
+        HIP_TRY(launch_report(nullptr, flag.p, nullptr, report.p, c->st));
+        wait_for_report(report.p, c->st);
+        if (report.p[1] & 4) SC_THROW(SC_EZERODEG);
         const size_t blk = (size_t)c->n * c->b;
         z.alloc(blk);
         b1.alloc(blk);
@@ -3412,10 +3424,9 @@ int sc_chebyshev_filter(const int64_t* csr_rowptr, const int32_t* csr_col, const
           lcount.alloc(1);
           longrows.alloc((size_t)c->n);
           HIP_TRY(long_row_list(c->rp, c->n, lwork.p, lw, longrows.p, lcount.p, c->st));
-          int32_t hcount = 0;
-          HIP_TRY(hipMemcpyAsync(&hcount, lcount.p, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
-          HIP_TRY(hipStreamSynchronize(c->st));
-          nlong = hcount;
+          HIP_TRY(launch_report(nullptr, lcount.p, nullptr, report.p, c->st));
+          wait_for_report(report.p, c->st);
+          nlong = (int)report.p[1];
         }
         ResidentPlan resident;  // used when the matrix as given is block diagonal with blocks that fit LDS
         if (wide) plan_resident(c->rp, c->c, vals.p, c->n, nnz, c->b, (double)std::max(c->d, 1), c->st, &resident);
@@ -3493,9 +3504,9 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
         DevBuf<double> mean, norm;
         DevBuf<char> work;
         DevBuf<int> bad;
-        PinnedBuf<int> hbad;
+        PinnedBuf<int64_t> report;
         bad.alloc(2);
-        hbad.alloc(1);
+        report.alloc(4);
         HIP_TRY(launch_fill_int32(bad.p, 2, 0, 0, c->st));
         if (c->measure != 2) {
           mean.alloc((size_t)c->n);
@@ -3510,9 +3521,9 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
           HIP_TRY(launch_edge_similarity(c->x, c->ldx, c->d, c->u, c->v, c->ne, c->measure, c->sigma, mean.p, norm.p,
                                          c->n, bad.p, c->val, c->st));
         }
-        HIP_TRY(hipMemcpyAsync(hbad.p, bad.p, sizeof(int), hipMemcpyDeviceToHost, c->st));
+        HIP_TRY(launch_report(nullptr, bad.p, nullptr, report.p, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
-        return *hbad.p ? SC_ECSR : SC_OK;
+        return report.p[1] ? SC_ECSR : SC_OK;
       },
       &ctx);
 }
@@ -3549,7 +3560,7 @@ int sc_coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int
         DevBuf<int> bad;
         PinnedBuf<int64_t> host;  // rowptr[n], then the two flags
         bad.alloc(2);
-        host.alloc(2);
+        host.alloc(4);
         for (int radix = 0; radix < 2; ++radix) {
           size_t wb = coo_to_csr_workspace(total, c->n, radix);
           if (radix == 0 && !work.try_alloc(wb)) {  // no room for the buckets: the sort needs less
@@ -3560,13 +3571,10 @@ int sc_coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int
           HIP_TRY(launch_fill_int32(bad.p, 2, 0, 0, c->st));
           HIP_TRY(coo_to_csr(c->row, c->col, c->val, c->nnz, c->n, c->sym, radix, work.p, wb, c->rp, c->co, c->vo, bad.p,
                              c->st));
-          HIP_TRY(hipMemcpyAsync(host.p, c->rp + c->n, sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
-          HIP_TRY(hipMemcpyAsync(host.p + 1, bad.p, 2 * sizeof(int), hipMemcpyDeviceToHost, c->st));
+          HIP_TRY(launch_report(c->rp + c->n, bad.p, bad.p + 1, host.p, c->st));
           HIP_TRY(hipStreamSynchronize(c->st));
-          int flags[2];
-          std::memcpy(flags, host.p + 1, sizeof flags);
-          if (flags[0]) return SC_ECSR;
-          if (!flags[1]) break;  // else a bucket overflowed: the radix sort
+          if (host.p[1]) return SC_ECSR;
+          if (!host.p[2]) break;  // else a bucket overflowed: the radix sort
         }
         if (c->nnz_out) *c->nnz_out = host.p[0];
         return SC_OK;
@@ -3613,11 +3621,13 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
         HIP_TRY(launch_knn_screen(xp.p, c->n, c->d, c->k, work.p, grouped ? group.p : nullptr, left.p, &tiles, &ntiles,
                                   &bound, &grouped, c->idx, c->dist, c->st));
         if (grouped) grouped_searches.fetch_add(1, std::memory_order_relaxed);
-        HIP_TRY(hipMemcpyAsync(left.p, ntiles, sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
+        PinnedBuf<int64_t> report;
+        report.alloc(4);
+        HIP_TRY(launch_report(nullptr, ntiles, nullptr, report.p, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
-        if (*left.p > 0) {
+        if (report.p[1] > 0) {
           fp64_searches.fetch_add(1, std::memory_order_relaxed);
-          HIP_TRY(launch_knn_search(c->n, c->d, c->k, xp.p, tiles, *left.p, bound, c->idx, c->dist, c->st));
+          HIP_TRY(launch_knn_search(c->n, c->d, c->k, xp.p, tiles, (int32_t)report.p[1], bound, c->idx, c->dist, c->st));
           HIP_TRY(hipStreamSynchronize(c->st));
         }
         return SC_OK;
@@ -3648,16 +3658,13 @@ int sc_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int32_
         Ctx* c = static_cast<Ctx*>(p);
         const size_t wb = knn_pairs_workspace(c->n, c->k);
         DevBuf<char> work;
-        DevBuf<int32_t> two;
-        PinnedBuf<int32_t> host;
+        PinnedBuf<int64_t> host;
         work.alloc(wb);
-        two.alloc(2);
-        host.alloc(2);
-        HIP_TRY(launch_knn_union_pairs(c->idx, c->dist, c->n, c->k, c->sigma, work.p, wb, c->eu, c->ev, c->val, two.p,
+        host.alloc(4);
+        HIP_TRY(launch_knn_union_pairs(c->idx, c->dist, c->n, c->k, c->sigma, work.p, wb, c->eu, c->ev, c->val, host.p,
                                        c->st));
-        HIP_TRY(hipMemcpyAsync(host.p, two.p, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
-        *c->np = (int64_t)host.p[0] + (int64_t)host.p[1];
+        *c->np = host.p[1] + host.p[2];
         return SC_OK;
       },
       &ctx);

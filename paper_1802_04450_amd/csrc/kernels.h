@@ -18,6 +18,8 @@ constexpr int kPairPad = 64;       // the same for two blocks side by side of mo
 // host[0] = *wide, host[1] = *a, host[2] = *b (what is null is left out), and then host[3] = 1, in coherent host memory: what the
 // host waits for comes without a copy and without waiting for the stream (a word to the host 12 us sooner).
 hipError_t launch_report(const int64_t* wide, const int32_t* a, const int32_t* b, int64_t* host, hipStream_t st);
+// Host: until *word = value, which a kernel on st writes to coherent host memory, or, if that takes long, the stream is idle.
+hipError_t wait_for_word(const int64_t* word, int64_t value, hipStream_t st);
 // nnz < 0: it is read from rowptr[n].
 // flag[0] |= 1 if rowptr is not monotone / rowptr[0] != 0, |= 2 if a column is out of range.
 hipError_t launch_validate_csr(const int64_t* rowptr, const int32_t* col, int64_t n, int64_t nnz, int* flag,
@@ -452,10 +454,10 @@ hipError_t launch_knn_search(int64_t n, int d, int k, double* xp, const int32_t*
                              const double* bound, int32_t* idx_out, double* dist_out, hipStream_t st);
 // The undirected edges {i, j} (j in i's list or i in j's) once each as eu < ev, in row order of the emitting list;
 // val = the listed distance, or exp(-dist^2 / (2 sigma^2)) if sigma > 0.  eu, ev, val have room for n * k entries;
-// last_two (device int32[2]) receives two numbers whose sum is the pair count.  work: knn_pairs_workspace(n, k) bytes.
+// host (4 words of coherent host memory): host[1] + host[2] is the pair count once st is idle.  work: knn_pairs_workspace(n, k) bytes.
 size_t knn_pairs_workspace(int64_t n, int k);
 hipError_t launch_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int k, double sigma, void* work,
-                                  size_t work_bytes, int32_t* eu, int32_t* ev, double* val, int32_t* last_two,
+                                  size_t work_bytes, int32_t* eu, int32_t* ev, double* val, int64_t* host,
                                   hipStream_t st);
 size_t coo_to_csr_workspace(int64_t total, int64_t n, int radix);
 hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int64_t nnz_in, int64_t n,

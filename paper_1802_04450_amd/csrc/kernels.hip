@@ -4,6 +4,8 @@
 //   A (16 x 4):  lane l holds A[l % 16][l / 16]
 //   B (4 x 16):  lane l holds B[l / 16][l % 16]
 //   D (16 x 16): lane l, register r (0..3) holds D[4*r + l / 16][l % 16]
+#include <atomic>
+#include <chrono>
 #include <type_traits>
 
 #include "exchange.h"
@@ -1820,6 +1822,20 @@ __global__ __launch_bounds__(64) void report_kernel(const int64_t* __restrict__ 
   if (b) put_host(host + 2, (int64_t)*b);
   host_written();
   put_host(host + 3, (int64_t)1);
+}
+
+hipError_t wait_for_word(const int64_t* word, int64_t value, hipStream_t st) {
+  const volatile int64_t* there = word;
+  const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+  while (*there != value && std::chrono::steady_clock::now() < until)
+    for (int i = 0; i < 64 && *there != value; ++i) {
+    }
+  if (*there != value) {
+    const hipError_t e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return e;
+  }
+  std::atomic_thread_fence(std::memory_order_acquire);
+  return hipSuccess;
 }
 
 hipError_t launch_report(const int64_t* wide, const int32_t* a, const int32_t* b, int64_t* host, hipStream_t st) {

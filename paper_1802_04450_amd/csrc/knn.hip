@@ -24,6 +24,7 @@
 
 #include <cstdint>
 
+#include "exchange.h"
 #include "kernels.h"
 
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -1700,6 +1701,23 @@ hipError_t launch_knn_mfma(const double* xp, const double* xn, int64_t n, int k,
   return hipGetLastError();
 }
 
+// What the host decides by, to its memory; the word behind it last.
+__global__ __launch_bounds__(64) void info_report_kernel(const int64_t* __restrict__ info, int count, int64_t* __restrict__ host) {
+  if ((int)threadIdx.x < count) put_host(host + threadIdx.x, info[threadIdx.x]);
+  host_written();
+  if (threadIdx.x == 0) put_host(host + count, (int64_t)1);
+}
+static_assert(kLostSlots == 64, "a lane per slot");
+__global__ __launch_bounds__(64) void lost_report_kernel(const int32_t* __restrict__ lost_count, int64_t* __restrict__ host) {
+  int sum = lost_count[threadIdx.x * kLostStride];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  if (threadIdx.x != 0) return;
+  put_host(host, (int64_t)sum);
+  host_written();
+  put_host(host + 1, (int64_t)1);
+}
+
 // How the bf16 screen goes about n points of d coordinates and k neighbours.
 struct ScreenPlan {
   bool use = false;
@@ -1960,9 +1978,14 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     else SC_GROUP_LIST(128, 8);
 #undef SC_GROUP_LIST
   };
+  static_assert(sizeof(GroupInfo) % 8 == 0 && sizeof(GroupInfo) + 8 <= kLostInts * 4, "whole words, and one behind them");
+  int64_t* const words = reinterpret_cast<int64_t*>(host);
+  constexpr int kInfoWords = sizeof(GroupInfo) / 8;
   auto read_info = [&](GroupInfo* to) -> hipError_t {
-    hipError_t r = hipMemcpyAsync(host, info, sizeof(GroupInfo), hipMemcpyDeviceToHost, st);
-    if (r == hipSuccess) r = hipStreamSynchronize(st);
+    words[kInfoWords] = 0;
+    hipLaunchKernelGGL(info_report_kernel, dim3(1), dim3(64), 0, st, reinterpret_cast<const int64_t*>(info), kInfoWords, words);
+    hipError_t r = hipGetLastError();
+    if (r == hipSuccess) r = wait_for_word(words + kInfoWords, 1, st);
     if (r == hipSuccess) std::memcpy(to, host, sizeof(*to));
     return r;
   };
@@ -2077,12 +2100,13 @@ hipError_t launch_knn_screen(const double* xp, int64_t n, int d, int k, void* wo
     screen(false, t0, nt, nparts);
     threshold(q0, nq, lost_count);
     // most queries lost: the second pass would be for nothing, an empty list sends them all to the fp64 kernel
-    e = hipMemcpyAsync(host, lost_count, sizeof(int32_t) * kLostInts, hipMemcpyDeviceToHost, st);
+    words[1] = 0;
+    hipLaunchKernelGGL(lost_report_kernel, dim3(1), dim3(kLostSlots), 0, st, lost_count, words);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = hipStreamSynchronize(st);
+    e = wait_for_word(words + 1, 1, st);
     if (e != hipSuccess) return e;
-    int64_t lost = -lost_before;
-    for (int q = 0; q < kLostSlots; ++q) lost += host[q * kLostStride];
+    const int64_t lost = words[0] - lost_before;
     lost_before += lost;
     if (lost <= nq / 2) screen(true, t0, nt, nparts);
     int32_t* gone = reinterpret_cast<int32_t*>(gw + g.off_lost);
@@ -2138,7 +2162,7 @@ size_t knn_pairs_workspace(int64_t n, int k) {
 }
 
 hipError_t launch_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int k, double sigma, void* work,
-                                  size_t work_bytes, int32_t* eu, int32_t* ev, double* val, int32_t* last_two,
+                                  size_t work_bytes, int32_t* eu, int32_t* ev, double* val, int64_t* host,
                                   hipStream_t st) {
   if (n < 1 || k < 1 || n > INT32_MAX || n * k > INT32_MAX) return hipErrorInvalidValue;
   const int64_t words = (n * k + 63) / 64;
@@ -2159,11 +2183,7 @@ hipError_t launch_knn_union_pairs(const int32_t* idx, const double* dist, int64_
   hipLaunchKernelGGL(pair_emit_kernel, dim3(blocks(n * k)), dim3(kT), 0, st, idx, dist, n, k, mask, off,
                      sigma > 0.0 ? 1.0 / (2.0 * sigma * sigma) : 0.0, eu, ev, val);
   // the pair count = the last offset + the last count: both handed back for the host to add
-  e = hipMemcpyAsync(last_two, off + (words - 1), sizeof(int32_t), hipMemcpyDeviceToDevice, st);
-  if (e != hipSuccess) return e;
-  e = hipMemcpyAsync(last_two + 1, cnt + (words - 1), sizeof(int32_t), hipMemcpyDeviceToDevice, st);
-  if (e != hipSuccess) return e;
-  return hipGetLastError();
+  return launch_report(nullptr, off + (words - 1), cnt + (words - 1), host, st);
 }
 
 }  // namespace sceig

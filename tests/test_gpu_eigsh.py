@@ -678,7 +678,7 @@ def test_renumbering_of_components_that_settle_late(B, n):
     rp, c, v, n = g
     comp = components.component_labels(rp, c, v)[1]
     drp, dc, dv = B.csr_to_device(rp, c, v)
-    rpo, co, vo, old, count = B.sc_reorder_csr(drp, dc, dv, n)
+    rpo, co, vo, old, count = B.sc_reorder_csr(drp, dc, dv)
     assert count == 3
     old = old.cpu().numpy()
     assert np.array_equal(np.sort(old), np.arange(n)) and np.count_nonzero(np.diff(comp[old])) == 2
