@@ -1155,8 +1155,8 @@ struct Solver {
   PinnedBuf<int32_t> outpos_host;
   PinnedBuf<double> evals_pinned;
   PinnedBuf<double> slots;  // kernels write to it, none reads it
-  // marks of the setup's checks and the number of long rows, as the device hands them back.  Here and not on setup()'s stack:
-  // a setup that fails with such a copy under way leaves it in memory that outlasts it (released only once it is done).
+  // The mark of the symmetry check, which comes by a copy.  Here and not on setup()'s stack: a setup that fails with the copy
+  // under way leaves it in memory that outlasts it (released only once it is done).
   PinnedBuf<int32_t> marks;
   // pinned staging for the small coefficient blocks of a rotation (locking b Ritz vectors): the upload then needs no
   // wait on the host.  ystage_busy: an upload from it may still be in flight (cleared by the next wait on the stream).

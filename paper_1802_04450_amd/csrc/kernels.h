@@ -381,10 +381,11 @@ size_t kmeans_update_workspace(int64_t n, int64_t ldx, int k);
 hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n, const int32_t* label, int k, void* work,
                                   size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
                                   int* changes, const LabelReport& report, int which, hipStream_t st);
-// Algorithm 5 with the uniform numbers u[0..k-1] supplied by the host; chosen: device int32[k].  screen = 0: without the
-// reduced copy of the points, which makes the draws faster and takes a quarter of their bytes
+// Algorithm 5, launch_kmeanspp below; chosen: device int32[k].  screen = 0: without the reduced copy of the points, which
+// makes the draws faster and takes a quarter of their bytes
 size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen);
-// Uniform number `index` in [0, 1) of the seeding draws: top 53 bits of mix(key + index), key = seed_key(seed).
+// Uniform number `index` in [0, 1) of the seeding draws, made where it is used: top 53 bits of mix(key + index),
+// key = seed_key(seed).
 __host__ __device__ inline uint64_t seed_mix(uint64_t x) {
   x += 0x9E3779B97F4A7C15ull;
   x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
@@ -440,8 +441,8 @@ hipError_t launch_knn_pad(const double* x, int64_t ldx, int64_t n, int d, double
 // The bf16 screen: bytes of scratch it needs, 0 where it is not used.  It leaves device pointers to a list of tiles of
 // 64 queries that it could not settle, to their number and to an upper bound of every query's k-th squared distance;
 // launch_knn_search does those (tiles, ntiles, bound), or every query when tiles is null (all that there is to do without
-// the screen; bound may be null then).  host: kLostInts pinned ints; the call waits for the stream (once per round of
-// queries, and up to twice more, once a round, where the points are grouped).
+// the screen; bound may be null then).  host: kLostInts pinned ints that launches write to; the call waits for their words
+// (once per round of queries, and up to twice more, once a round, where the points are grouped).
 constexpr int kLostSlots = 64, kLostStride = 32, kLostInts = kLostSlots * kLostStride;
 size_t knn_screen_workspace(int64_t n, int d, int k);
 // Scratch of the screen's grouped form, which passes over the tiles of points that cannot hold a neighbour; 0 where it is

@@ -2,9 +2,10 @@
 // kernels.  The distance step is the paper's expanded form S = |v|^2 + |c|^2 - 2 V C^T with the product on the fp64
 // matrix cores and the arg-min in the same launch (label_kernel, kernels.hip); |v|^2 does not change the arg-min and is left out.  The centre update
 // is sort based as in the paper (points ordered by label, every cluster a contiguous run), with a fixed summation
-// order so that results are reproducible.  The seeding follows Algorithm 5 with the uniform numbers supplied by the
-// host (a counter-based generator); a draw is one distance pass that also leaves block sums and one single-workgroup
-// kernel that walks the sums level by level to the drawn point.
+// order so that results are reproducible.  The seeding follows Algorithm 5 with uniform numbers from a counter-based
+// generator; a draw is one distance pass that also leaves block sums and a walk over the sums, level by level, to the
+// drawn point: all draws in one launch where its workgroups are all on the chip (seed_draws_kernel), else a launch or two
+// a draw.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <cmath>
