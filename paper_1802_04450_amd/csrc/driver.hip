@@ -2556,11 +2556,13 @@ struct KMeans {
   int d, k;
   hipStream_t st;
   int64_t ldx = 0;
-  DevBuf<double> x;
+  DevBuf<double> x, centring;  // centring: mean and scale of the points, for the seeding's and the labelling's reduced copies
+  bool centred = false;
 
   void stage() {  // row-major, zero padded, 32-byte aligned rows: the left operand of the distance product
     ldx = ((int64_t)d + 3) / 4 * 4;
     x.alloc((size_t)n * ldx);
+    centring.alloc((size_t)ldx + 1);
     HIP_TRY(launch_points_to_rowmajor(points, ld, colmajor, n, d, x.p, ldx, st));
   }
 
@@ -2582,7 +2584,7 @@ struct KMeans {
       f.polls = fused_polls();
     }
     for (;;) {
-      HIP_TRY(launch_kmeanspp(x.p, ldx, d, n, k, seed_key(seed_value), screen, work.p, wb, chosen, f, st));
+      HIP_TRY(launch_kmeanspp(x.p, ldx, d, n, k, seed_key(seed_value), screen, work.p, wb, chosen, centring.p, &centred, f, st));
       HIP_TRY(launch_gather_rows(x.p, ldx, chosen, k, c, st));
       if (f.groups) HIP_TRY(hipMemcpyAsync(done.p, f.done, sizeof(int), hipMemcpyDeviceToHost, st));
       HIP_TRY(hipStreamSynchronize(st));  // work is released on return
@@ -2616,7 +2618,7 @@ struct KMeans {
     const bool many = max_iter >= label_screen_steps(n, ldx, k) || std::getenv("SCEIG_FORCE_LABEL_SCREEN");
     const size_t sb = many && !std::getenv("SCEIG_NO_LABEL_SCREEN") ? label_screen_workspace(n, ldx, k) : 0;
     bool screen = sb > 0 && swork.try_alloc(sb);
-    if (screen) HIP_TRY(launch_label_copy(x.p, ldx, d, n, k, swork.p, st));
+    if (screen) HIP_TRY(launch_label_copy(x.p, ldx, d, n, k, swork.p, centring.p, centred, st));
     HIP_TRY(launch_fill_int32(labels, n, -1, 0, st));
     int iters = 0, converged = 0, last_changes = 0;
     const bool timing = stats && stats->timing;
@@ -2642,7 +2644,7 @@ struct KMeans {
         HIP_TRY(hipEventRecord(events.v.back().a, st));
       }
       if (screen)
-        HIP_TRY(launch_label_screened(x.p, ldx, d, n, c, ct.p, ldc, k, cnorm.p, swork.p, labels, changes.p, st));
+        HIP_TRY(launch_label_screened(x.p, ldx, d, n, c, ct.p, ldc, k, cnorm.p, swork.p, centring.p, labels, changes.p, st));
       else
         HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, lwork.p, lwb, labels, changes.p, st));
       if (timing) HIP_TRY(hipEventRecord(events.v.back().b, st));

@@ -356,14 +356,16 @@ hipError_t launch_label_listed(const double* x, int64_t ldx, int64_t n, const in
                                hipStream_t st);
 // Labelling screened in bf16 (kmeans.hip): the same labels.  It pays from label_screen_steps labelling steps on (INT32_MAX:
 // never); 0 bytes where it is not made.  launch_label_copy makes the
-// reduced copy of the points, once; launch_label_screened does a labelling step and leaves the number of points that the
+// reduced copy of the points, once (centring: ldx + 1 doubles, the points' mean and scale; centred: launch_kmeanspp has left them
+// there for the same points, else they are made: 100,000 x 100 43 us); launch_label_screened does a labelling step and leaves the number of points that the
 // screen could not decide, which were labelled in fp64, at changes[kChangeUndecided].
 constexpr int kChangeUndecided = 1, kChangeSum = 2;
 int label_screen_steps(int64_t n, int64_t ldx, int k);
 size_t label_screen_workspace(int64_t n, int64_t ldx, int k);
-hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, hipStream_t st);
+hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, double* centring, bool centred,
+                             hipStream_t st);
 hipError_t launch_label_screened(const double* x, int64_t ldx, int d, int64_t n, const double* c, const double* ct,
-                                 int64_t ldc, int k, const double* cnorm, void* work, int32_t* label, int* changes,
+                                 int64_t ldc, int k, const double* cnorm, void* work, const double* centring, int32_t* label, int* changes,
                                  hipStream_t st);
 hipError_t launch_fill_int32(int32_t* a, int64_t n, int32_t value, int use_iota, hipStream_t st);
 // centres = means of their points (grouped by label, fixed summation order); empty clusters keep their centre.  ct, cnorm
@@ -382,7 +384,8 @@ hipError_t launch_centroid_update(const double* x, int64_t ldx, int d, int64_t n
                                   size_t work_bytes, int32_t* start, double* c, double* ct, int64_t ldc, double* cnorm,
                                   int* changes, const LabelReport& report, int which, hipStream_t st);
 // Algorithm 5, launch_kmeanspp below; chosen: device int32[k].  screen = 0: without the reduced copy of the points, which
-// makes the draws faster and takes a quarter of their bytes
+// makes the draws faster and takes a quarter of their bytes.  centring: ldx + 1 doubles; *centred: whether the reduced copy has left
+// there what launch_label_copy takes
 size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen);
 // Uniform number `index` in [0, 1) of the seeding draws, made where it is used: top 53 bits of mix(key + index),
 // key = seed_key(seed).
@@ -404,7 +407,7 @@ struct SeedFused {
   int* done = nullptr;      // out: device, in work
 };
 hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, uint64_t key, int screen, void* work,
-                           size_t work_bytes, int32_t* chosen, SeedFused& f, hipStream_t st);
+                           size_t work_bytes, int32_t* chosen, double* centring, bool* centred, SeedFused& f, hipStream_t st);
 hipError_t launch_gather_rows(const double* x, int64_t ldx, const int32_t* index, int k, double* c, hipStream_t st);
 // part[p], p < kmeans_objective_parts(): partial sums of |x_i - c_label(i)|^2 (add them in order on the host); NaN for a
 // point whose label is not in [0, k)

@@ -1554,7 +1554,7 @@ inline int seed_dpb(int d) { return (d + 7) / 8 * 8; }
 
 size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen) {
   // two of (dist2[n] | bsum[ceil(n / 64)])  and, with the screen,
-  // mean[ldx] | sums[kSeedParts][ldx] | tops[kSeedParts] | scale | err[n] | xh[n][dpb]
+  // sums[kSeedParts][ldx] | tops[kSeedParts] | err[n] | xh[n][dpb]
   const size_t nb = (size_t)((n + kSeedPoints - 1) / kSeedPoints);
   size_t bytes = 2 * ((size_t)n + nb) * 8 + 1024;
   if (seed_fused((int64_t)nb, k, screen && seed_screened(n, d, k))) bytes += kDrawShared;
@@ -1567,20 +1567,20 @@ size_t kmeans_seed_workspace(int64_t n, int64_t ldx, int d, int k, int screen) {
 // last; whether that has come to run *f.done says once the stream is idle: f.groups, else 0, and the call has to be made again
 // without (f.polls = kNeverFused).
 hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k, uint64_t key, int screen, void* work,
-                           size_t work_bytes, int32_t* chosen, SeedFused& f, hipStream_t st) {
+                           size_t work_bytes, int32_t* chosen, double* centring, bool* centred, SeedFused& f, hipStream_t st) {
   f.groups = 0;
   if (n <= 0 || n > INT32_MAX || k < 1) return hipErrorInvalidValue;
   const int64_t nb = (n + kSeedPoints - 1) / kSeedPoints;
   if (work_bytes < kmeans_seed_workspace(n, ldx, d, k, screen)) return hipErrorInvalidValue;
   double* dist2[2] = {static_cast<double*>(work), static_cast<double*>(work) + n + nb};
-  double* mean = dist2[1] + n + nb;
-  double* sums = mean + ldx;
+  double *mean = centring, *scale = centring + ldx;
+  double* sums = dist2[1] + n + nb;
   uint32_t* tops = reinterpret_cast<uint32_t*>(sums + (size_t)kSeedParts * ldx);
-  double* scale = reinterpret_cast<double*>(tops + kSeedParts);
-  float2* err = reinterpret_cast<float2*>(scale + 1);
+  float2* err = reinterpret_cast<float2*>(tops + kSeedParts);
   __bf16* xh = reinterpret_cast<__bf16*>(((uintptr_t)(err + n) + 15) / 16 * 16);
   const int dpb = seed_dpb(d);
   const bool screened = screen && seed_screened(n, d, k), draws = nb <= kDrawBlocks;
+  *centred = screened;
   int64_t first = (int64_t)(seed_uniform(key, 0) * (double)n);
   first = first < n - 1 ? first : n - 1;
   const int per = (int)((nb + kDrawGroups - 1) / kDrawGroups);
@@ -1651,8 +1651,7 @@ bool label_screened(int64_t n, int64_t ldx, int k) { return (double)n * (double)
 struct LabelScreen {
   int ks = 0, ctiles = 0;
   int64_t tiles = 0;
-  size_t off_cb = 0, off_bound = 0, off_half = 0, off_most = 0, off_mean = 0, off_sums = 0, off_tops = 0, off_scale = 0,
-         off_rows = 0, bytes = 0;
+  size_t off_cb = 0, off_bound = 0, off_half = 0, off_most = 0, off_sums = 0, off_tops = 0, off_rows = 0, bytes = 0;
 };
 
 LabelScreen plan_label_screen(int64_t n, int64_t ldx, int k) {
@@ -1670,10 +1669,8 @@ LabelScreen plan_label_screen(int64_t n, int64_t ldx, int k) {
   p.off_bound = place((size_t)n * sizeof(float2));
   p.off_half = place((size_t)p.ctiles * 32 * 4);
   p.off_most = place((size_t)p.ctiles * sizeof(CentreBound));
-  p.off_mean = place((size_t)ldx * 8);
   p.off_sums = place((size_t)kSeedParts * ldx * 8);
   p.off_tops = place((size_t)kSeedParts * 4);
-  p.off_scale = place(8);
   p.off_rows = place((size_t)n * 4);
   p.bytes = off;
   return p;
@@ -1713,15 +1710,17 @@ size_t label_screen_workspace(int64_t n, int64_t ldx, int k) {
   return label_screened(n, ldx, k) ? plan_label_screen(n, ldx, k).bytes : 0;
 }
 
-hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, hipStream_t st) {
+hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int k, void* work, double* centring, bool centred,
+                             hipStream_t st) {
   const LabelScreen p = plan_label_screen(n, ldx, k);
   char* w = static_cast<char*>(work);
-  double* mean = reinterpret_cast<double*>(w + p.off_mean);
+  double *mean = centring, *scale = centring + ldx;
   double* sums = reinterpret_cast<double*>(w + p.off_sums);
   uint32_t* tops = reinterpret_cast<uint32_t*>(w + p.off_tops);
-  double* scale = reinterpret_cast<double*>(w + p.off_scale);
-  hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums, tops);
-  hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, tops, kSeedParts, ldx, n, mean, scale);
+  if (!centred) {
+    hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums, tops);
+    hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, tops, kSeedParts, ldx, n, mean, scale);
+  }
   hipLaunchKernelGGL(label_copy_kernel<false>, dim3((unsigned)((p.tiles + kT / 64 - 1) / (kT / 64))), dim3(kT), 0, st, x, ldx,
                      d, n, p.tiles, p.ks, mean, scale, reinterpret_cast<uint4*>(w),
                      reinterpret_cast<float2*>(w + p.off_bound), nullptr, nullptr, nullptr);
@@ -1729,12 +1728,11 @@ hipError_t launch_label_copy(const double* x, int64_t ldx, int d, int64_t n, int
 }
 
 hipError_t launch_label_screened(const double* x, int64_t ldx, int d, int64_t n, const double* c, const double* ct,
-                                 int64_t ldc, int k, const double* cnorm, void* work, int32_t* label, int* changes,
+                                 int64_t ldc, int k, const double* cnorm, void* work, const double* centring, int32_t* label, int* changes,
                                  hipStream_t st) {
   const LabelScreen p = plan_label_screen(n, ldx, k);
   char* w = static_cast<char*>(work);
-  const double* mean = reinterpret_cast<const double*>(w + p.off_mean);
-  const double* scale = reinterpret_cast<const double*>(w + p.off_scale);
+  const double *mean = centring, *scale = centring + ldx;
   float* half = reinterpret_cast<float*>(w + p.off_half);
   CentreBound* most = reinterpret_cast<CentreBound*>(w + p.off_most);
   int32_t* rows = reinterpret_cast<int32_t*>(w + p.off_rows);

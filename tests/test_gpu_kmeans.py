@@ -359,6 +359,24 @@ def test_screened_labelling_is_the_nearest_centre(B, n, d, k, kind, monkeypatch)
         assert bool(((lab >= 0) & (lab < k))[fine].all())
 
 
+# the seeding and the labelling both by their reduced copies, which share the points' mean and scale: the same as without the
+# labelling's, and as steps of their own from the chosen points, which make them again
+@pytest.mark.parametrize("n,d,k,kind", [(40_003, 100, 101, "normal"), (125_003, 33, 97, "offset"), (125_000, 32, 100, "small")])
+def test_mean_and_scale_shared_by_seeding_and_labelling(B, n, d, k, kind, monkeypatch):
+    gen = torch.Generator(device="cuda:0").manual_seed(n + k)
+    x = torch.randn((n, d), dtype=torch.float64, device="cuda:0", generator=gen)
+    x = 300.0 + x if kind == "offset" else 1e-9 * x if kind == "small" else x
+    monkeypatch.setenv("SCEIG_FORCE_LABEL_SCREEN", "1")
+    seen = B.sc_counter(B.SC_COUNTER_SCREENED_LABELLINGS)
+    labels, centres = B.sc_kmeans(x, k, 5, max_iter=4)[:2]
+    assert B.sc_counter(B.SC_COUNTER_SCREENED_LABELLINGS) > seen
+    alone_labels, alone_centres = B.sc_kmeans_lloyd(x, B.sc_kmeanspp(x, k, 5)[1], 4)[:2]
+    assert torch.equal(labels, alone_labels) and torch.equal(centres, alone_centres)
+    monkeypatch.setenv("SCEIG_NO_LABEL_SCREEN", "1")
+    plain_labels, plain_centres = B.sc_kmeans(x, k, 5, max_iter=4)[:2]
+    assert torch.equal(labels, plain_labels) and torch.equal(centres, plain_centres)
+
+
 # Draws in one launch.  Without the screen: 16 draws and blocks of points from one to the 256 that it is taken for; with it: one and
 # several blocks a workgroup, the last ones ragged, up to the blocks that it takes (1,800) and the LDS (128 coordinates there)
 @pytest.mark.parametrize("n,d,k,data,one", [(16, 3, 16, "blobs", True), (65, 1, 16, "blobs", True), (4097, 17, 31, "blobs", True),
