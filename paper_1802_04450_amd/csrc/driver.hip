@@ -2558,6 +2558,13 @@ struct KMeans {
   int64_t ldx = 0;
   DevBuf<double> x, centring;  // centring: mean and scale of the points, for the seeding's and the labelling's reduced copies
   bool centred = false;
+  // Of the iterations.  Here and not on lloyd()'s stack: launches that use them are under way when it returns, and a block
+  // may only go back to the cache once they are done (run_kmeans waits for the stream).
+  DevBuf<double> ct, cnorm;
+  DevBuf<int32_t> start;
+  DevBuf<int> changes;
+  DevBuf<char> update_work, label_work, screen_work;
+  PinnedBuf<int> counts;  // of a labelling: labels changed, points undecided, its number
 
   void stage() {  // row-major, zero padded, 32-byte aligned rows: the left operand of the distance product
     ldx = ((int64_t)d + 3) / 4 * 4;
@@ -2598,14 +2605,9 @@ struct KMeans {
     }
   }
 
-  // Algorithm 4 step 3 from the centres in c (device k x ldx, updated in place)
+  // Algorithm 4 step 3 from the centres in c (device k x ldx, updated in place).  Returns with launches under way.
   int lloyd(double* c, int max_iter, int32_t* labels, sc_kmeans_stats* stats) {
     const int64_t ldc = ((int64_t)k + 15) / 16 * 16;
-    DevBuf<double> ct, cnorm, part;
-    DevBuf<int32_t> start;
-    DevBuf<int> changes;
-    DevBuf<char> work, lwork, swork;
-    PinnedBuf<int> counts;  // of a labelling: labels changed, points undecided, its number
     ct.alloc((size_t)ldx * ldc);
     cnorm.alloc((size_t)k);
     start.alloc((size_t)k + 1);
@@ -2613,12 +2615,12 @@ struct KMeans {
     counts.alloc(3);
     counts.p[2] = 0;
     const size_t wb = kmeans_update_workspace(n, ldx, k), lwb = label_workspace(n, ldx, k);
-    work.alloc(wb);
-    if (lwb) lwork.alloc(lwb);
+    update_work.alloc(wb);
+    if (lwb) label_work.alloc(lwb);
     const bool many = max_iter >= label_screen_steps(n, ldx, k) || std::getenv("SCEIG_FORCE_LABEL_SCREEN");
     const size_t sb = many && !std::getenv("SCEIG_NO_LABEL_SCREEN") ? label_screen_workspace(n, ldx, k) : 0;
-    bool screen = sb > 0 && swork.try_alloc(sb);
-    if (screen) HIP_TRY(launch_label_copy(x.p, ldx, d, n, k, swork.p, centring.p, centred, st));
+    bool screen = sb > 0 && screen_work.try_alloc(sb);
+    if (screen) HIP_TRY(launch_label_copy(x.p, ldx, d, n, k, screen_work.p, centring.p, centred, st));
     HIP_TRY(launch_fill_int32(labels, n, -1, 0, st));
     int iters = 0, converged = 0, last_changes = 0;
     const bool timing = stats && stats->timing;
@@ -2644,9 +2646,10 @@ struct KMeans {
         HIP_TRY(hipEventRecord(events.v.back().a, st));
       }
       if (screen)
-        HIP_TRY(launch_label_screened(x.p, ldx, d, n, c, ct.p, ldc, k, cnorm.p, swork.p, centring.p, labels, changes.p, st));
+        HIP_TRY(launch_label_screened(x.p, ldx, d, n, c, ct.p, ldc, k, cnorm.p, screen_work.p, centring.p, labels,
+                                      changes.p, st));
       else
-        HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, lwork.p, lwb, labels, changes.p, st));
+        HIP_TRY(launch_label(x.p, ldx, n, ct.p, ldc, k, cnorm.p, label_work.p, lwb, labels, changes.p, st));
       if (timing) HIP_TRY(hipEventRecord(events.v.back().b, st));
       dist_bytes += 8.0 * ((double)n * d + (double)k * d) + 8.0 * (double)n;
       dist_flops += 2.0 * (double)n * k * d;
@@ -2654,8 +2657,8 @@ struct KMeans {
       // wait for a copy with nothing under way, 15 us an iteration), and centres of the labels that they come from stay as they
       // are.  Not after the second labelling, the last one where clusters lie well apart: the launches would come to nothing.
       auto update = [&](int which) {
-        HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, work.p, wb, start.p, c, ct.p, ldc, cnorm.p, changes.p,
-                                       {counts.p, it + 1}, which, st));
+        HIP_TRY(launch_centroid_update(x.p, ldx, d, n, labels, k, update_work.p, wb, start.p, c, ct.p, ldc, cnorm.p,
+                                       changes.p, {counts.p, it + 1}, which, st));
       };
       const bool wait = it == 1;
       update(wait ? kUpdateReport : kUpdateReport | kUpdateCentres);
@@ -2683,6 +2686,7 @@ struct KMeans {
       // objective of the final labelling against the centres it was computed from (after a converged run these are
       // also the means of their clusters)
       const int np = kmeans_objective_parts();
+      DevBuf<double> part;
       part.alloc((size_t)np);
       PinnedBuf<double> hp;
       hp.alloc((size_t)np);
@@ -2714,7 +2718,12 @@ struct KMeans {
 };
 
 struct KMeansCall {
-  KMeans km;
+  const double* points;
+  int64_t ld;
+  int colmajor;
+  int64_t n;
+  int d, k;
+  hipStream_t st;
   uint64_t seed;
   int max_iter;
   int mode;  // 0 = seeding only, 1 = Lloyd from given centres, 2 = both
@@ -2726,7 +2735,7 @@ struct KMeansCall {
 
 int run_kmeans(void* p) {
   KMeansCall* c = static_cast<KMeansCall*>(p);
-  KMeans& km = c->km;
+  KMeans km{c->points, c->ld, c->colmajor, c->n, c->d, c->k, c->st};  // here: an error unwinds it, and its blocks wait
   const auto t0 = std::chrono::steady_clock::now();
   km.stage();
   DevBuf<double> cen;
@@ -3447,7 +3456,7 @@ int sc_kmeanspp(const double* points, int64_t ld, int32_t colmajor, int64_t n, i
   if (!centroids_out) return SC_EINVAL;
   const int a = kmeans_args_ok(points, ld, colmajor, n, d, k);
   if (a != SC_OK) return a;
-  KMeansCall call{{points, ld, colmajor, n, d, k, reinterpret_cast<hipStream_t>(stream)}, seed, 0, 0, chosen_out, nullptr,
+  KMeansCall call{points, ld, colmajor, n, d, k, reinterpret_cast<hipStream_t>(stream), seed, 0, 0, chosen_out, nullptr,
                   centroids_out, nullptr};
   return guarded(run_kmeans, &call);
 }
@@ -3463,7 +3472,7 @@ int sc_kmeans_lloyd(const double* points, int64_t ld, int32_t colmajor, int64_t 
     *stats = sc_kmeans_stats{};
     stats->timing = timing;
   }
-  KMeansCall call{{points, ld, colmajor, n, d, k, reinterpret_cast<hipStream_t>(stream)}, 0, max_iter, 1, nullptr,
+  KMeansCall call{points, ld, colmajor, n, d, k, reinterpret_cast<hipStream_t>(stream), 0, max_iter, 1, nullptr,
                   labels_out, centroids, stats};
   return guarded(run_kmeans, &call);
 }
@@ -3479,7 +3488,7 @@ int sc_kmeans(const double* points, int64_t ld, int32_t colmajor, int64_t n, int
     *stats = sc_kmeans_stats{};
     stats->timing = timing;
   }
-  KMeansCall call{{points, ld, colmajor, n, d, k, reinterpret_cast<hipStream_t>(stream)}, seed, max_iter, 2, nullptr,
+  KMeansCall call{points, ld, colmajor, n, d, k, reinterpret_cast<hipStream_t>(stream), seed, max_iter, 2, nullptr,
                   labels_out, centroids_out, stats};
   return guarded(run_kmeans, &call);
 }

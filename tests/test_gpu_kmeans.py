@@ -412,3 +412,39 @@ def test_draws_in_one_launch(B, monkeypatch, n, d, k, data, one):
         same = out == x[chosen.long()]
         assert bool((same | (out.isnan() & x[chosen.long()].isnan())).all())
     assert torch.equal(picked[0], picked[1]) and torch.equal(picked[2], picked[1])
+
+
+# two callers with streams of their own, and nothing that makes a call wait before its end (no statistics): the iterations' blocks
+# of the one are free for the other only once its launches are done.  Up to 1,024 clusters and more of them (radix sort); calls
+# that converge, after two labellings and after many, and calls that end at max_iter
+@pytest.mark.parametrize("n,d,k,max_iter,spread", [(3000, 4, 8, 50, 0.02), (20_000, 8, 64, 60, 0.6), (20_000, 8, 64, 3, 0.6),
+                                                   (12_000, 4, 1100, 40, 0.3), (12_000, 4, 1100, 2, 0.3)])
+def test_two_callers_at_once_without_statistics(B, n, d, k, max_iter, spread):
+    import threading
+    sets = [_dev(wl.gaussian_blobs(n, d, min(k, 40), seed, spread)) for seed in (1, 2)]
+    alone = []
+    for x in sets:
+        labels, centres, code, _ = B.sc_kmeans(x, k, 9, max_iter=max_iter)
+        assert code in (B.SC_OK, B.SC_NOT_CONVERGED)
+        alone.append((labels, centres, code))
+    rounds = 12
+    labels = [[torch.full((n,), -7, dtype=torch.int32, device="cuda:0") for _ in range(rounds)] for _ in sets]
+    centres = [[torch.zeros((k, d), dtype=torch.float64, device="cuda:0") for _ in range(rounds)] for _ in sets]
+    codes = [[], []]
+    torch.cuda.synchronize()
+
+    def call(t):
+        stream = torch.cuda.Stream()
+        for r in range(rounds):
+            codes[t].append(B.lib().sc_kmeans(sets[t].data_ptr(), d, 0, n, d, k, 9, max_iter, labels[t][r].data_ptr(),
+                                              centres[t][r].data_ptr(), None, stream.cuda_stream))
+
+    callers = [threading.Thread(target=call, args=(t,)) for t in range(2)]
+    for c in callers:
+        c.start()
+    for c in callers:
+        c.join()
+    for t in range(2):
+        for r in range(rounds):
+            assert codes[t][r] == alone[t][2], (t, r)
+            assert torch.equal(labels[t][r], alone[t][0]) and torch.equal(centres[t][r], alone[t][1]), (t, r)
