@@ -838,14 +838,15 @@ __device__ __forceinline__ float piece_product(const Bf16Piece& a, const Bf16Pie
   return acc;
 }
 
-// The first centre's index, and the places that seed_draws_kernel's workgroups share.
-__global__ __launch_bounds__(kT) void seed_start_kernel(int32_t* __restrict__ chosen, int32_t first, long long* __restrict__ shared,
-                                                        int count, uint32_t* __restrict__ word, uint32_t value) {
+// The first centre's index, and the places that seed_draws_kernel's workgroups share.  It stands for the centres up to `filled`
+// until they are drawn: a launch behind seed_draws_kernel that reads the points chosen finds points also where that kernel's
+// workgroups have not all started, which the host only learns later.
+__global__ __launch_bounds__(kT) void seed_start_kernel(int32_t* __restrict__ chosen, int32_t first, int filled,
+                                                        long long* __restrict__ shared, int count, uint32_t* __restrict__ word,
+                                                        uint32_t value) {
   const int t = blockIdx.x * kT + threadIdx.x;
-  if (t == 0) {
-    *chosen = first;
-    if (word) *word = value;
-  }
+  if (t == 0 && word) *word = value;
+  for (int e = t; e < filled; e += gridDim.x * kT) chosen[e] = first;
   for (int e = t; e < count; e += gridDim.x * kT) shared[e] = -1;
 }
 
@@ -1588,8 +1589,8 @@ hipError_t launch_kmeanspp(const double* x, int64_t ldx, int d, int64_t n, int k
   const bool fused = f.polls != kNeverFused && seed_fused(nb, k, screened) && lds + 4096 <= f.lds_limit;  // beside what the draw takes
   double* const ring = fused ? reinterpret_cast<double*>(static_cast<char*>(work) + (work_bytes - kDrawShared) / 16 * 16) : nullptr;
   uint32_t* const words = fused ? reinterpret_cast<uint32_t*>(ring + kDrawPlaces) : nullptr;
-  hipLaunchKernelGGL(seed_start_kernel, dim3(fused ? 8 : 1), dim3(kT), 0, st, chosen, (int32_t)first, reinterpret_cast<long long*>(ring),
-                     fused ? kDrawPlaces : 0, words, f.polls < 0 ? kStopped : 0u);
+  hipLaunchKernelGGL(seed_start_kernel, dim3(fused ? 8 : 1), dim3(kT), 0, st, chosen, (int32_t)first, fused ? k : 1,
+                     reinterpret_cast<long long*>(ring), fused ? kDrawPlaces : 0, words, f.polls < 0 ? kStopped : 0u);
   if (screened) {
     hipLaunchKernelGGL(seed_sum_kernel, dim3(kSeedParts), dim3(kT), 0, st, x, ldx, n, sums, tops);
     hipLaunchKernelGGL(seed_mean_kernel, dim3(blocks(ldx)), dim3(kT), 0, st, sums, tops, kSeedParts, ldx, n, mean,

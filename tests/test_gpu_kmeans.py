@@ -414,6 +414,23 @@ def test_draws_in_one_launch(B, monkeypatch, n, d, k, data, one):
     assert torch.equal(picked[0], picked[1]) and torch.equal(picked[2], picked[1])
 
 
+# What is enqueued behind the one launch before the host knows whether its workgroups have all started: the rows of the points
+# chosen.  The places of the points not drawn hold what was in the caller's memory, here numbers that are no point's.
+@pytest.mark.parametrize("n,d,k", [(2000, 16, 32), (16, 3, 16), (45_000, 100, 40), (115_200, 128, 34)])
+def test_draws_that_do_not_start_leave_points_chosen(B, monkeypatch, n, d, k):
+    x = _dev(wl.gaussian_blobs(n, d, min(k, 10), 3, 0.3))
+    chosen, centres = B.sc_kmeanspp(x, k, 5)
+    torch.cuda.synchronize()
+    monkeypatch.setenv("SCEIG_FUSED_POLLS", "-1")
+    again = torch.full((k,), 0x7ffffff0, dtype=torch.int32, device="cuda:0")
+    rows = torch.zeros((k, d), dtype=torch.float64, device="cuda:0")
+    before = B.sc_counter(B.SC_COUNTER_FUSED_SEEDINGS)
+    torch.cuda.synchronize()
+    assert B.lib().sc_kmeanspp(x.data_ptr(), d, 0, n, d, k, 5, again.data_ptr(), rows.data_ptr(), 0) == B.SC_OK
+    assert B.sc_counter(B.SC_COUNTER_FUSED_SEEDINGS) == before
+    assert torch.equal(again, chosen) and torch.equal(rows, centres)
+
+
 # two callers with streams of their own, and nothing that makes a call wait before its end (no statistics): the iterations' blocks
 # of the one are free for the other only once its launches are done.  Up to 1,024 clusters and more of them (radix sort); calls
 # that converge, after two labellings and after many, and calls that end at max_iter
