@@ -2662,13 +2662,7 @@ struct KMeans {
       };
       const bool wait = it == 1;
       update(wait ? kUpdateReport : kUpdateReport | kUpdateCentres);
-      const volatile int* number = counts.p + 2;
-      const double until = now_s() + 2e-3;
-      while (*number != it + 1 && now_s() < until)
-        for (int i = 0; i < 64 && *number != it + 1; ++i) {
-        }
-      if (*number != it + 1) HIP_TRY(hipStreamSynchronize(st));
-      std::atomic_thread_fence(std::memory_order_acquire);
+      HIP_TRY(wait_for_word(counts.p + 2, it + 1, st));
       ++iters;
       last_changes = counts.p[0];
       // where the screen leaves much to the fp64 labelling it only comes on top
@@ -3534,6 +3528,7 @@ int sc_edge_similarity(const double* x, int64_t ldx, int64_t n, int32_t d, const
         }
         HIP_TRY(launch_report(nullptr, bad.p, nullptr, report.p, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
+        wait_for_report(report.p, c->st);
         return report.p[1] ? SC_ECSR : SC_OK;
       },
       &ctx);
@@ -3584,6 +3579,7 @@ int sc_coo_to_csr(const int32_t* row, const int32_t* col, const double* val, int
                              c->st));
           HIP_TRY(launch_report(c->rp + c->n, bad.p, bad.p + 1, host.p, c->st));
           HIP_TRY(hipStreamSynchronize(c->st));
+          wait_for_report(host.p, c->st);
           if (host.p[1]) return SC_ECSR;
           if (!host.p[2]) break;  // else a bucket overflowed: the radix sort
         }
@@ -3636,6 +3632,7 @@ int sc_knn_search(const double* x, int64_t ldx, int64_t n, int32_t d, int32_t k_
         report.alloc(4);
         HIP_TRY(launch_report(nullptr, ntiles, nullptr, report.p, c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
+        wait_for_report(report.p, c->st);
         if (report.p[1] > 0) {
           fp64_searches.fetch_add(1, std::memory_order_relaxed);
           HIP_TRY(launch_knn_search(c->n, c->d, c->k, xp.p, tiles, (int32_t)report.p[1], bound, c->idx, c->dist, c->st));
@@ -3675,6 +3672,7 @@ int sc_knn_union_pairs(const int32_t* idx, const double* dist, int64_t n, int32_
         HIP_TRY(launch_knn_union_pairs(c->idx, c->dist, c->n, c->k, c->sigma, work.p, wb, c->eu, c->ev, c->val, host.p,
                                        c->st));
         HIP_TRY(hipStreamSynchronize(c->st));
+        wait_for_report(host.p, c->st);
         *c->np = host.p[1] + host.p[2];
         return SC_OK;
       },

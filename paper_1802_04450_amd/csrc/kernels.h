@@ -18,8 +18,10 @@ constexpr int kPairPad = 64;       // the same for two blocks side by side of mo
 // host[0] = *wide, host[1] = *a, host[2] = *b (what is null is left out), and then host[3] = 1, in coherent host memory: what the
 // host waits for comes without a copy and without waiting for the stream (a word to the host 12 us sooner).
 hipError_t launch_report(const int64_t* wide, const int32_t* a, const int32_t* b, int64_t* host, hipStream_t st);
-// Host: until *word = value, which a kernel on st writes to coherent host memory, or, if that takes long, the stream is idle.
+// Host: until *word = value, which a kernel on st writes to coherent host memory.  An error where the stream has come to its end
+// without that: what the word stands for is then whatever the memory held.
 hipError_t wait_for_word(const int64_t* word, int64_t value, hipStream_t st);
+hipError_t wait_for_word(const int32_t* word, int32_t value, hipStream_t st);
 // nnz < 0: it is read from rowptr[n].
 // flag[0] |= 1 if rowptr is not monotone / rowptr[0] != 0, |= 2 if a column is out of range.
 hipError_t launch_validate_csr(const int64_t* rowptr, const int32_t* col, int64_t n, int64_t nnz, int* flag,

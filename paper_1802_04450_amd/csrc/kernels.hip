@@ -1824,8 +1824,10 @@ __global__ __launch_bounds__(64) void report_kernel(const int64_t* __restrict__ 
   put_host(host + 3, (int64_t)1);
 }
 
-hipError_t wait_for_word(const int64_t* word, int64_t value, hipStream_t st) {
-  const volatile int64_t* there = word;
+namespace {
+template <class T>
+hipError_t wait_for(const T* word, T value, hipStream_t st) {
+  const volatile T* there = word;
   const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
   while (*there != value && std::chrono::steady_clock::now() < until)
     for (int i = 0; i < 64 && *there != value; ++i) {
@@ -1833,10 +1835,15 @@ hipError_t wait_for_word(const int64_t* word, int64_t value, hipStream_t st) {
   if (*there != value) {
     const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
+    if (*there != value) return hipErrorUnknown;
   }
   std::atomic_thread_fence(std::memory_order_acquire);
   return hipSuccess;
 }
+}  // namespace
+
+hipError_t wait_for_word(const int64_t* word, int64_t value, hipStream_t st) { return wait_for(word, value, st); }
+hipError_t wait_for_word(const int32_t* word, int32_t value, hipStream_t st) { return wait_for(word, value, st); }
 
 hipError_t launch_report(const int64_t* wide, const int32_t* a, const int32_t* b, int64_t* host, hipStream_t st) {
   host[3] = 0;

@@ -178,3 +178,19 @@ def test_symmetry_validation_flag(B):
             with pytest.raises(B.ScError) as e:
                 B.sc_laplacian_eigsh(drp, dc, dv, 3, 1e-9, flags=B.SC_FLAG_VALIDATE_SYMMETRY)
             assert e.value.code == B.SC_ECSR, name
+
+
+@pytest.mark.parametrize("dtype,name", [(torch.int64, "_ZN5sceig13wait_for_wordEPKllP12ihipStream_t"),
+                                        (torch.int32, "_ZN5sceig13wait_for_wordEPKiiP12ihipStream_t")])
+def test_a_word_that_does_not_come_is_an_error(B, dtype, name):
+    """What the device reports lies in recycled host memory: a wait whose word has not been written when the stream is at its
+    end must not let the caller read on."""
+    import ctypes
+    integer = ctypes.c_int64 if dtype == torch.int64 else ctypes.c_int32
+    wait = getattr(B.lib(), name)
+    wait.restype, wait.argtypes = ctypes.c_int, [ctypes.c_void_p, integer, ctypes.c_void_p]
+    word = torch.zeros(4, dtype=dtype, pin_memory=True)
+    stream = torch.cuda.Stream()
+    assert wait(word.data_ptr(), 1, stream.cuda_stream) != 0
+    word[0] = 1
+    assert wait(word.data_ptr(), 1, stream.cuda_stream) == 0
