@@ -309,6 +309,33 @@ struct PinnedBuf {
   ~PinnedBuf() { release(); }
 };
 
+// Words that are copied to or from the device, as many as the problem has of something: pinned where they are few.  Pinned memory
+// of a size that no call has asked for before costs more than copies of pageable memory do (solves of about 100,000 components,
+// their number another in every call: 13.8 ms with pinned words for them, 12.2 with pageable ones; of 300,000 81.7 and 78.8).
+struct HostInts {
+  static constexpr size_t kPinned = 65536;
+  PinnedBuf<int32_t> pinned;
+  std::vector<int32_t> pageable;
+  int32_t* p = nullptr;
+  void alloc(size_t count) {
+    if (count <= kPinned) pinned.alloc(count);
+    else pageable.resize(count);
+    p = count <= kPinned ? pinned.p : pageable.data();
+  }
+  // true: pinned, so that a copy may go on after the call that enqueues it; else the stream has to be waited for
+  bool take(std::vector<int32_t>&& v) {
+    if (v.size() > kPinned) {
+      pageable = std::move(v);
+      p = pageable.data();
+      return false;
+    }
+    pinned.alloc(v.size());
+    std::copy(v.begin(), v.end(), pinned.p);
+    p = pinned.p;
+    return true;
+  }
+};
+
 // Optional per-launch timing of selected kernel families with HIP events on the solver's stream.
 enum Family { kFamSpmm = 0, kFamProject = 1, kFamUpdate = 2, kFamRotate = 3, kFamQr = 4, kFamOther = 5 };
 struct KTimer {
@@ -567,7 +594,7 @@ struct ResidentPlan {
   DevBuf<double> sval;
   DevBuf<int64_t> slice_base;
   DevBuf<int32_t> slice_len, slice_first, row_extra;
-  PinnedBuf<int32_t> words;  // the items, until they are copied
+  HostInts words;  // the items, until they are copied
 };
 
 int device_lds_limit() {
@@ -827,7 +854,7 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   if (nblk <= 0 || (int64_t)nblk > (int64_t)1 << 22) return;  // the item table stays small
   extra.alloc((size_t)kBlockCounts * nblk);
   HIP_TRY(launch_block_extra_chunks(rowptr, starts.p, nblk, n, extra.p, st));
-  PinnedBuf<int32_t> hs, hx;
+  HostInts hs, hx;
   hs.alloc((size_t)nblk + 1);
   hx.alloc((size_t)kBlockCounts * nblk);
   HIP_TRY(hipMemcpyAsync(hs.p, starts.p, (size_t)nblk * sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -863,10 +890,10 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
     const size_t sw = sliced_scan_workspace(nslots);
     swork.alloc(sw);
     const int nsliced = (int)(best.blocks.size() / kSliceBlockInts);
-    PinnedBuf<int32_t> blocks;
-    blocks.alloc(best.blocks.size());
-    std::copy(best.blocks.begin(), best.blocks.end(), blocks.p);
-    HIP_TRY(hipMemcpyAsync(d_blocks.p, blocks.p, best.blocks.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    HostInts blocks;
+    const size_t nwords = best.blocks.size();
+    (void)blocks.take(std::move(best.blocks));  // the wait for `total` below is behind the copy
+    HIP_TRY(hipMemcpyAsync(d_blocks.p, blocks.p, nwords * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_TRY(sliced_extra_rows(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, st));
     HIP_TRY(sliced_copy_layout(rowptr, d_blocks.p, nsliced, d_list.p, plan->row_extra.p, nslots, d_desc.p, plan->slice_len.p,
                                plan->slice_first.p, d_entries.p, plan->slice_base.p, swork.p, sw, st));
@@ -915,9 +942,10 @@ void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val,
   words.reserve(items.size() * kItemInts);
   for (const WorkItem& it : items) words.insert(words.end(), {it.row0, it.nrows, it.col0, it.shape, it.extra});
   plan->items.alloc(words.size());
-  plan->words.alloc(words.size());  // the copy reads them when its turn comes
-  std::copy(words.begin(), words.end(), plan->words.p);
-  HIP_TRY(hipMemcpyAsync(plan->items.p, plan->words.p, words.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+  const size_t nwords = words.size();
+  const bool apart = plan->words.take(std::move(words));  // the copy reads them when its turn comes
+  HIP_TRY(hipMemcpyAsync(plan->items.p, plan->words.p, nwords * sizeof(int32_t), hipMemcpyHostToDevice, st));
+  if (!apart) HIP_TRY(hipStreamSynchronize(st));
   plan->nitems = (int)items.size();
   plan->lds_bytes = lds_max;
   plan->rest_row0 = rest_row0;

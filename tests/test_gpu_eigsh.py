@@ -669,6 +669,23 @@ def test_component_sizes_of_many_components(B, tiny, large):
     assert compare.orthonormality_defect(vec) <= 1e-10
 
 
+# the filter's items as pinned words and, beyond 65,536 of them, as pageable ones (five an item, an item or more a block)
+@pytest.mark.parametrize("blocks", [3000, 13_107, 13_108, 70_000])
+def test_filter_items_of_many_blocks(B, blocks):
+    n = 3 * blocks
+    rp = np.arange(0, 6 * blocks + 1, 2, dtype=np.int64)
+    row = np.repeat(np.arange(n), 2).reshape(n, 2)
+    c = (row // 3 * 3 + (row + [[1, 2]] - row // 3 * 3) % 3).astype(np.int32)
+    c.sort(axis=1)
+    before = B.sc_counter(B.SC_COUNTER_RESIDENT_FILTERS)
+    lam, vec, code, stats = solve(B, (rp, c.reshape(-1), np.ones(6 * blocks), n), 40, 1e-9, block=16)
+    assert code == B.SC_OK and stats["components"] == blocks
+    assert B.sc_counter(B.SC_COUNTER_RESIDENT_FILTERS) > before
+    assert np.max(np.abs(lam)) <= 1e-9
+    assert compare.residual_norms(rp, c.reshape(-1), np.ones(6 * blocks), lam, vec).max() <= 1e-8
+    assert compare.orthonormality_defect(vec) <= 1e-10
+
+
 # labels that need more rounds than are made before the numbering goes on unseen (a path in random order), and more nodes than that
 # is done for
 @pytest.mark.parametrize("n", [3000, 60_000, 200_000, 200_001])
