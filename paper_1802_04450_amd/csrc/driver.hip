@@ -1158,6 +1158,9 @@ struct Solver {
   bool no_start_pairs = std::getenv("SCEIG_NO_START_PAIRS") != nullptr;
   int polls = fused_polls();
   bool no_fused = std::getenv("SCEIG_NO_FUSED") != nullptr;
+  // for tests of the way back: the word that counts the workgroups is stopped before this launch, as other work that holds the
+  // compute units would have it
+  int fused_stop = std::getenv("SCEIG_FUSED_STOP") ? std::atoi(std::getenv("SCEIG_FUSED_STOP")) : -1;
   bool tentative_two_passes = std::getenv("SCEIG_TENTATIVE_TWO_PASSES") != nullptr;
   // for tests of the check phase: the solve works for one pair more and gives up the unlock-th largest before that phase
   int unlock = std::getenv("SCEIG_UNLOCK") ? std::atoi(std::getenv("SCEIG_UNLOCK")) : -1;
@@ -1487,6 +1490,7 @@ struct Solver {
     a.done = done_word(sl);
     a.number = ++fused_number;
     a.sync = reinterpret_cast<uint32_t*>(flag.p);
+    if (a.number == fused_stop) HIP_TRY(launch_fused_stop(a.sync, st));
     a.base = arrivals;
     a.polls = polls;
     a.exchange = exchange.p + exchange_turn * exchange_len;

@@ -339,6 +339,8 @@ __global__ __launch_bounds__(kThreads) void fused_prepare_kernel(long long* __re
   for (int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x; e < len; e += (int64_t)gridDim.x * kThreads) exchange[e] = -1;
 }
 
+__global__ void fused_stop_kernel(uint32_t* __restrict__ sync) { atomicOr(sync + kSyncWord, kStopped); }
+
 template <int B, bool STEP>
 hipError_t launch(const FusedStep& a, hipStream_t st) {
   const size_t lds = fused_lds_bytes<B, STEP>(a.j, a.rows);
@@ -355,6 +357,11 @@ hipError_t launch_fused_prepare(double* exchange, int64_t len, uint32_t* sync, b
   const int64_t groups = std::min<int64_t>((len + 4 * kThreads - 1) / (4 * kThreads), 1024);
   hipLaunchKernelGGL(fused_prepare_kernel, dim3((unsigned)std::max<int64_t>(groups, 1)), dim3(kThreads), 0, st,
                      reinterpret_cast<long long*>(exchange), len, sync, stopped ? kStopped : 0u);
+  return hipGetLastError();
+}
+
+hipError_t launch_fused_stop(uint32_t* sync, hipStream_t st) {
+  hipLaunchKernelGGL(fused_stop_kernel, dim3(1), dim3(1), 0, st, sync);
   return hipGetLastError();
 }
 

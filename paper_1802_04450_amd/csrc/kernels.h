@@ -167,6 +167,8 @@ inline int fused_groups(int64_t n, int rows) { return (int)((n + rows - 1) / row
 inline int64_t fused_exchange(int groups, int j1, int j2, int b) { return (int64_t)(groups + 1) * b * (j1 + j2 + 2 * b); }
 // Before the first launch with this sync (kSyncWords) and these areas; stopped: as after a launch that has left.
 hipError_t launch_fused_prepare(double* exchange, int64_t len, uint32_t* sync, bool stopped, hipStream_t st);
+// For tests: from here on as after a launch that has left.
+hipError_t launch_fused_stop(uint32_t* sync, hipStream_t st);
 hipError_t launch_fused_step(const FusedStep& a, size_t lds_limit, hipStream_t st);
 hipError_t launch_fused_qr(const FusedStep& a, int b, size_t lds_limit, hipStream_t st);
 

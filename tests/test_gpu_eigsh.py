@@ -655,6 +655,89 @@ def test_block_step_as_one_launch(B, monkeypatch, n, k, m, block, way):
     assert np.max(np.abs(runs[0] - runs[1])) <= 1e-11 and np.max(np.abs(runs[2] - runs[1])) <= 1e-11
 
 
+# The way back in the middle of a solve: the workgroups of launch number `stop` (the start block's QR is the first) find that they
+# cannot all start, and with them those of all further ones.  A step, one that had the next one enqueued behind it, and that one;
+# QRs behind ordinary launches (blocks of 16); bases that outgrow the workgroups' LDS, with restarts; blocks of several phases.
+@pytest.mark.parametrize("graph,k,m,block,flags,stops", [("random", 9, 0, 8, 0, (2, 3, 4, 5, 8, 13, 21, 40)),
+                                                         ("wide", 12, 300, 8, "nofilter", (2, 7, 12, 17, 18, 30)),
+                                                         ("narrow", 9, 40, 8, "nofilter", (3, 6, 9, 11, 20, 60)),
+                                                         ("comps", 30, 0, 8, 0, (2, 3, 6, 7, 10, 12)),
+                                                         ("random16", 20, 0, 16, 0, (2, 3, 5, 9)),
+                                                         ("comps16", 40, 0, 16, 0, (2, 3, 4, 5))])
+def test_fused_launches_that_stop_in_the_middle(B, monkeypatch, graph, k, m, block, flags, stops):
+    if graph.startswith("comps"):
+        rp, c, v, n = wl.disjoint_union(*[wl.random_weighted_connected(60 + 7 * t, 200, t) for t in range(k)])
+    else:
+        n = {"random": 2000, "wide": 8193, "narrow": 3000, "random16": 16385}[graph]
+        rp, c, v, n = wl.random_weighted_connected(n, 4 * n, 5 + n)
+    g = (rp, c, v, n)
+    flags = B.SC_FLAG_NO_START_FILTER if flags == "nofilter" else 0
+
+    def run(**env):
+        for name, value in env.items():
+            monkeypatch.setenv(name, value)
+        before = [B.sc_counter(x) for x in (B.SC_COUNTER_FUSED_STEPS, B.SC_COUNTER_FUSED_QRS)]
+        lam, vec, code, stats = solve(B, g, k, 1e-9, block=block, m=m, flags=flags)
+        ran = sum(B.sc_counter(x) - y for x, y in zip((B.SC_COUNTER_FUSED_STEPS, B.SC_COUNTER_FUSED_QRS), before))
+        for name in env:
+            monkeypatch.delenv(name)
+        assert code == B.SC_OK, (env, stats)
+        assert compare.residual_norms(rp, c, v, lam, vec).max() <= 1e-8, env
+        assert compare.orthonormality_defect(vec) <= 1e-12, env
+        return lam, ran
+
+    plain, ran = run(SCEIG_NO_FUSED="1")
+    assert ran == 0
+    lam, whole = run()
+    assert np.max(np.abs(lam - plain)) <= 1e-11
+    stopped = 0
+    for stop in stops:
+        lam, ran = run(SCEIG_FUSED_STOP=str(stop))
+        assert ran <= stop - 1 and (ran > 0 or stop == 1), (stop, ran, whole)  # a step that was not asked for is none of them
+        stopped += ran < whole
+        assert np.max(np.abs(lam - plain)) <= 1e-11, stop
+    assert stopped >= 2, whole
+
+
+# Two callers at once, whose one-launch forms take the compute units from one another (a workgroup of these QRs fills the LDS), so
+# that which of them start is settled on the device: the same results, but for the last bits.
+@pytest.mark.parametrize("n,b,nodes,k,block", [(557_056, 8, 2000, 9, 8), (94_208, 32, 4033, 10, 8), (258_048, 16, 16385, 20, 16)])
+def test_fused_launches_of_two_callers(B, n, b, nodes, k, block):
+    import threading
+    rp, c, v, _ = wl.random_weighted_connected(nodes, 4 * nodes, 5 + nodes)
+    dev = B.csr_to_device(rp, c, v)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n)
+    start = torch.randn((n, b), dtype=torch.float64, generator=gen, device="cuda")
+    alone = start.clone()
+    B.sc_block_qr(alone, 0, b)
+    lam0 = B.sc_laplacian_eigsh(*dev, k, 1e-9, block=block)[0]
+    torch.cuda.synchronize()
+    eye = torch.eye(b, dtype=torch.float64, device="cuda")
+    wrong = []
+
+    def call(first):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for r in range(12):
+                if (r + first) % 3 != 2:
+                    basis = start.clone()
+                    B.sc_block_qr(basis, 0, b)
+                    if (basis.T.contiguous() @ basis - eye).abs().max() > 1e-13 or (basis - alone).abs().max() > 1e-10:
+                        wrong.append(("qr", first, r))
+                else:
+                    lam, _, code, _ = B.sc_laplacian_eigsh(*dev, k, 1e-9, block=block)
+                    if code != B.SC_OK or (lam - lam0).abs().max() > 1e-11:
+                        wrong.append(("solve", first, r))
+        wrong.append(first)
+
+    callers = [threading.Thread(target=call, args=(t,)) for t in range(2)]
+    for t in callers:
+        t.start()
+    for t in callers:
+        t.join()
+    assert sorted(wrong, key=str) == [0, 1], wrong
+
+
 # more components among the nodes that a workgroup counts than its table has places, beside some too large for most work items
 @pytest.mark.parametrize("tiny,large", [(9000, (1500, 2000)), (700, (1273,)), (3000, ())])
 def test_component_sizes_of_many_components(B, tiny, large):
