@@ -103,8 +103,10 @@ typedef struct sc_options {
 #define SC_FAM_PROJECT 1 /* block projection H = Q^T W of the reorthogonalization (fp64 MFMA) */
 #define SC_FAM_UPDATE 2  /* block update W -= Q H of the reorthogonalization (fp64 MFMA) */
 #define SC_FAM_ROTATE 3  /* restart rotation / Ritz vectors V Y (fp64 MFMA) */
-#define SC_FAM_QR 4      /* Cholesky QR of the new block (Gram, factorisation, scaling), per block step */
-#define SC_FAM_OTHER 5   /* reductions of partial results */
+#define SC_FAM_QR 4      /* Cholesky QR of the new block (Gram, factorisation, scaling), per block step or start block */
+#define SC_FAM_OTHER 5   /* reductions of partial results, and block steps that run as one launch (few rows: product,
+                            reorthogonalization and QR are then counted here, bytes and operations too, and in none of the
+                            families above) */
 #define SC_NUM_FAMILIES 6
 
 typedef struct sc_stats {
@@ -295,16 +297,20 @@ int sc_cgs2(double* basis, int64_t n, int64_t ld, int32_t j, int32_t b, double* 
  * zero columns of Q and zero rows of R.
  *   r_out  device fp64[b*b] row-major upper triangular R (may be NULL)
  *   g_out  device fp64[b*b] Gram matrix W^T W of the block before orthonormalization (may be NULL)
+ * Up to 557,056 rows of 8 columns, 258,048 of 16 or 94,208 of 32 the whole is one launch whose workgroups wait for
+ * one another.  Where other work on the GPU holds the compute units, so that they do not all start within about a
+ * millisecond, the ordinary launches take its place.  These add up in another order: the last bits of a result can differ
+ * between a GPU that the call has for itself and one that it shares (of sc_laplacian_eigsh, too).
  */
 int sc_block_qr(double* basis, int64_t n, int64_t ld, int32_t j, int32_t b, double* r_out, double* g_out,
                 void* stream);
 
 /*
- * sc_block_qr for callers that cannot allocate: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same arguments, same arithmetic and same results as sc_block_qr, but the call allocates nothing
- * (no hipMalloc / hipFree, no block cache): its partial Gram blocks and small matrices live in a fixed device array of
- * 12.6 MB inside the library (about 1.58 million doubles), which every GPU the library runs on holds from the first such
- * call on it until the process ends.
+ * sc_block_qr for callers that cannot allocate: tight serving loops, harnesses that forbid hipMalloc.  (It waits for its
+ * stream, so it cannot be captured into a HIP graph.)  Same arguments, same arithmetic as sc_block_qr and, but for the last
+ * bits as said there, the same results, but the call allocates nothing (no hipMalloc / hipFree, no block cache): its partial
+ * Gram blocks and small matrices live in a fixed device array of 12.6 MB inside the library (about 1.58 million doubles),
+ * which every GPU the library runs on holds from the first such call on it until the process ends.
  *   Limits: b in {1,2,4,8,16,32} (the array is sized for 32 columns; the number of partial blocks does not grow with
  *   n), n <= 2^31 - 1; anything else is SC_EDOMAIN and nothing is written.
  *   All calls on one GPU share that one array: calls that overlap in time on the same GPU (from several threads or
@@ -492,7 +498,8 @@ int sc_version(void);
  *                                the points to the fp64 labelling
  *   SC_COUNTER_START_PAIRS       phases of sc_laplacian_eigsh whose start block was made together with the phase's before
  *   SC_COUNTER_FUSED_STEPS       block steps of sc_laplacian_eigsh that ran as one launch
- *   SC_COUNTER_FUSED_QRS         block QRs of sc_laplacian_eigsh, other than those steps', that ran as one launch
+ *   SC_COUNTER_FUSED_QRS         block QRs of sc_laplacian_eigsh, other than those steps', and calls of sc_block_qr and
+ *                                sc_block_qr_noalloc that ran as one launch
  *   SC_COUNTER_FUSED_SEEDINGS    seedings of k-means whose draws, but for the last, ran as one launch
  *   SC_COUNTER_FP64_SEARCHES     sc_knn_search calls whose screen left queries to the fp64 search through all points
  * Returns the count, or -1 for an unknown id.

@@ -364,11 +364,14 @@ struct KTimer {
     recs.push_back(Rec{fam, cur, e, bytes, flops, launches});
     cur = nullptr;
   }
+  // the last record: to be taken back if what it timed turns out not to have been asked for
+  size_t last() const { return recs.size() - 1; }
+  void forget(size_t rec) { recs[rec].launches = 0; }
   // after the stream has been synchronised
   void collect(sc_stats* out) {
     for (Rec& r : recs) {
       float ms = 0.f;
-      if (hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
+      if (r.launches > 0 && hipEventElapsedTime(&ms, r.a, r.b) == hipSuccess) {
         out->fam_time_s[r.fam] += (double)ms * 1e-3;
         out->fam_launches[r.fam] += r.launches;
         out->fam_bytes[r.fam] += r.bytes;
@@ -1249,6 +1252,11 @@ struct Solver {
   // have nothing to do meanwhile.  If it is not, its block and its slot are written over.
   Pending ahead_step;
   bool step_ahead = false;
+  size_t ahead_rec = 0;  // its times
+  void drop_step_ahead() {
+    if (step_ahead && timer.on(kFamOther)) timer.forget(ahead_rec);
+    step_ahead = false;
+  }
   // What those launches share: the word that counts their workgroups, behind the validation flag in one zeroed block, and two
   // areas for the sums under way, which take turns.
   uint32_t arrivals = 0;  // workgroups so far
@@ -1605,7 +1613,7 @@ struct Solver {
       // operand are as they were.  It and all behind it are taken again by the ordinary launches, and no further one is tried.
       if (debug_on()) std::fprintf(stderr, "[sceig] a fused launch's workgroups did not all start: ordinary launches from here on\n");
       no_fused = true;
-      step_ahead = false;
+      drop_step_ahead();
       const std::vector<Pending> again(pending_steps.begin() + q, pending_steps.end());
       pending_steps.clear();
       for (const Pending& r : again) {
@@ -1678,9 +1686,9 @@ struct Solver {
     timer.begin(kFamUpdate);
     HIP_TRY(launch_row_gemm(basis.p, n, ld, 0, nl, hpair.p, pad, w, 0, nl, nullptr, 0, nullptr, st));
     HIP_TRY(launch_copy_cols(basis.p, ld, nl + b, ahead_block(), b, 0, b, n, st));
-    timer.end(kFamUpdate, 8.0 * (double)n * (nl + 2 * w + 2 * b), 2.0 * (double)n * nl * w);
     const ProjectPlan gplan = plan_project(n, b, kMaxPartials);
     HIP_TRY(launch_project(basis.p, n, ld, nl, b, nl, b, gplan, gpart.p, st));
+    timer.end(kFamUpdate, 8.0 * (double)n * (nl + 2 * w + 3 * b), 2.0 * (double)n * (nl * w + b * b));
     return finish_start_block({hpair.p, nl, pad}, {}, gplan.npart, true);
   }
 
@@ -1689,7 +1697,9 @@ struct Solver {
     const int c0 = ahead.from, jc = nl - c0;
     if (jc <= 0) {
       const ProjectPlan gplan = plan_project(n, b, kMaxPartials);
+      timer.begin(kFamUpdate);
       HIP_TRY(launch_project(basis.p, n, ld, nl, b, nl, b, gplan, gpart.p, st));
+      timer.end(kFamUpdate, 8.0 * (double)n * b, 2.0 * (double)n * b * b);
       return finish_start_block({hpair.p + b, c0, pair_pad()}, {}, gplan.npart, true);
     }
     const ProjectPlan plan = plan_project(n, jc, kMaxPartials);
@@ -1706,13 +1716,18 @@ struct Solver {
   }
 
   // The second pass over all locked vectors, which the device leaves out where the passes before it have removed little (as in
-  // enqueue_cgs_adaptive).  ngram Gram partials are in gpart, by a projection of the block on itself or by the fused update.
+  // enqueue_cgs_adaptive; nor is its traffic counted).  ngram Gram partials are in gpart, by a projection of the block on itself or by the fused update.
   int finish_start_block(Removed h, Removed h2, int ngram, bool by_project) {
     HIP_TRY(launch_reduce_partials(gpart.p, ngram, b, b, gram(), nullptr, 0, nullptr, 0, st));
     HIP_TRY(launch_second_pass_test(h, h2, b, gram(), kSecondPassRatio2, flag.p, st));
     const ProjectPlan plan = plan_project(n, nl, kMaxPartials);
+    timer.begin(kFamProject);
     HIP_TRY(launch_project(basis.p, n, ld, 0, nl, nl, b, plan, part.p, st, flag.p));
+    timer.end(kFamProject, 0.0, 0.0);
+    timer.begin(kFamOther);
     HIP_TRY(launch_reduce_partials(part.p, plan.npart, nl, b, h1.p, nullptr, 0, nullptr, 0, st, flag.p));
+    timer.end(kFamOther, 0.0, 0.0);
+    timer.begin(kFamUpdate);
     if (by_project) {
       HIP_TRY(launch_row_gemm(basis.p, n, ld, 0, nl, h1.p, kPP, b, 0, nl, nullptr, 0, nullptr, st, flag.p));
       const ProjectPlan gplan = plan_project(n, b, kMaxPartials);
@@ -1720,6 +1735,7 @@ struct Solver {
     } else {
       HIP_TRY(launch_update_gram(basis.p, n, ld, 0, nl, h1.p, b, nl, 0, gpart.p, st, flag.p));
     }
+    timer.end(kFamUpdate, 0.0, 0.0);
     return ngram;
   }
 
@@ -2042,10 +2058,12 @@ struct Solver {
           stats.block_steps += 1;
           stats.spmv_cols += b;
           pending_steps.push_back(ahead_step);
+          step_ahead = false;
         } else {
+          drop_step_ahead();
           enqueue_step(ja, next_slot, tentative);
         }
-        step_ahead = goes_on = false;
+        goes_on = false;
         ++next_slot;
         ++pending;
         ++steps_in_phase;
@@ -2062,6 +2080,7 @@ struct Solver {
           const int groups = enqueue_fused_step(ja + b, next_slot);
           ahead_step = {ja + b, next_slot, false, groups, true, fused_number};
           step_ahead = groups > 0;
+          if (step_ahead && timer.on(kFamOther)) ahead_rec = timer.last();
         }
         fetch_slots();
         if (!start_block_seen) {
@@ -2485,6 +2504,7 @@ struct Solver {
     stats.max_residual_est = maxr;
     stats.block = b;
     stats.m = m;
+    drop_step_ahead();
     timer.collect(&stats);
     stats.t_total = now_s() - t_begin;
     if (nfound < k_out) not_converged = true;

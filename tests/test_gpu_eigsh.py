@@ -699,6 +699,18 @@ def test_fused_launches_that_stop_in_the_middle(B, monkeypatch, graph, k, m, blo
     assert stopped >= 2, whole
 
 
+def test_steps_that_were_not_asked_for_are_not_timed(B):
+    """One-launch steps are timed with the reductions, of which a phase without locked vectors has none; the one that a solve has
+    enqueued ahead of its last inspection belongs to no step."""
+    rp, c, v, n = wl.random_weighted_connected(2000, 8000, 11)
+    before = B.sc_counter(B.SC_COUNTER_FUSED_STEPS)
+    _, _, code, stats = solve(B, (rp, c, v, n), 4, 1e-9, block=8, flags=B.SC_FLAG_NO_VERIFY, timing_mask=63)
+    assert code == B.SC_OK and stats["phases"] == 1
+    assert B.sc_counter(B.SC_COUNTER_FUSED_STEPS) - before == stats["block_steps"] > 0
+    assert stats["fam_launches"][5] == stats["block_steps"], stats
+    assert stats["fam_time_s"][5] > 0.0 and stats["fam_flops"][5] > 0.0
+
+
 # Two callers at once, whose one-launch forms take the compute units from one another (a workgroup of these QRs fills the LDS), so
 # that which of them start is settled on the device: the same results, but for the last bits.
 @pytest.mark.parametrize("n,b,nodes,k,block", [(557_056, 8, 2000, 9, 8), (94_208, 32, 4033, 10, 8), (258_048, 16, 16385, 20, 16)])
