@@ -531,8 +531,8 @@ int sc_probe_fp64_matrix_rate(int32_t shape, int32_t workgroups, int32_t iterati
  * returns and handed to later calls that ask for a block of exactly the same size on the same device (a repeated
  * solve of one problem shape then allocates nothing).  At most 4 GiB of device memory (and as much pinned memory)
  * are held this way, where room runs out in the place of blocks that the last few calls have not used; the environment
- * variable SCEIG_CACHE_LIMIT_MB, read once, sets another limit, 0 switches the caching off.  sc_release_cache() gives everything held back to the HIP runtime; call it only while no other call
- * into the library is running.  Returns SC_OK.
+ * variable SCEIG_CACHE_LIMIT_MB, read once, sets another limit, 0 switches the caching off.  sc_release_cache() gives everything
+ * held back to the HIP runtime; call it only while no other call into the library is running.  Returns SC_OK.
  */
 int sc_release_cache(void);
 

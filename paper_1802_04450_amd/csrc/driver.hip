@@ -409,7 +409,14 @@ constexpr double kRelDrop = 1e-12;   // squared sine below which a column counts
 // in the second factorization: a column that survived the first one has unit norm, so only exact zeros are dropped
 constexpr double kAbsDrop2Again = 0.25, kRelDropAgain = 1e-8;
 
-// looks of a fused launch's workgroup for the others' start, each about 0.6 us; -1, for tests: the word is stopped beforehand
+// Looks of a fused launch's workgroup for the others' start, each about 0.6 us; -1, for tests: the word is stopped beforehand.
+// On a GPU that nothing else uses all have started by the time one has loaded its rows.  Beside other work the wait mostly ends
+// in a start, and is shorter than what ordinary launches take there, each of which waits for its turn as well.  Mean times with
+// 2,048 looks, 64, and ordinary launches: beside products of 8,192 x 8,192 a QR of 2,000 x 8 0.18, 1.5 and 2.3 ms, of 94,208 x 32
+// 1.4, 2.6 and 3.6, a seeding of 100,000 x 100 3.6, 3.6 and 24.6, a solve of 2,000 rows 470, 612 and 622; beside solves of 500,000
+// rows, whose filter fills the LDS, a QR of 100,003 x 16 175, 219 and 267 us, of 557,056 x 8 222, 309 and 346, a seeding of 100,000 x
+// 100 1.5, 1.8 and 2.2 ms, solves of 2,000 rows 26, 73 and 82 ms, of 100,000 rows 24, 38 and 20; beside solves of 100,000 rows these
+// 7.7, 8.6 and 7.9.
 int fused_polls() { return std::getenv("SCEIG_FUSED_POLLS") ? std::atoi(std::getenv("SCEIG_FUSED_POLLS")) : 2048; }
 constexpr size_t kFusedLds = 160 * 1024;  // a workgroup of the fused launches takes at most
 
@@ -831,9 +838,9 @@ class ItemPlanner {
 // plan is usable when b is 16 or 32, every block fits LDS one way or the other, the sliced copy's padding stays below
 // a half, and the modelled step time beats the general product's: an item with its entries in registers costs the LDS bytes
 // its step reads (the block's entries times 8 bytes per column) at about half a compute unit's LDS rate, a sliced one
-// sliced_entry_s per entry, kSlicedStepS and its share of sliced_copy_s in a filter of `steps` steps, the items spread over the 256 compute units, largest first; the general product gathers
-// 8 b bytes per entry from the L2 caches at the 14.5 TB/s measured for it (3.2 M entries, 16 columns: 28 us; 0.73 M: 11.5 us),
-// and a launch takes 3 us more.
+// sliced_entry_s per entry, kSlicedStepS and its share of sliced_copy_s in a filter of `steps` steps, the items spread over the
+// 256 compute units, largest first; the general product gathers 8 b bytes per entry from the L2 caches at the 14.5 TB/s measured
+// for it (3.2 M entries, 16 columns: 28 us; 0.73 M: 11.5 us), and a launch takes 3 us more.
 void plan_resident(const int64_t* rowptr, const int32_t* col, const double* val, int64_t n, int64_t nnz, int b, double steps,
                    hipStream_t st, ResidentPlan* plan) {
   plan->usable = false;
@@ -1716,7 +1723,8 @@ struct Solver {
   }
 
   // The second pass over all locked vectors, which the device leaves out where the passes before it have removed little (as in
-  // enqueue_cgs_adaptive; nor is its traffic counted).  ngram Gram partials are in gpart, by a projection of the block on itself or by the fused update.
+  // enqueue_cgs_adaptive; nor is its traffic counted).  ngram Gram partials are in gpart, by a projection of the block on itself
+  // or by the fused update.
   int finish_start_block(Removed h, Removed h2, int ngram, bool by_project) {
     HIP_TRY(launch_reduce_partials(gpart.p, ngram, b, b, gram(), nullptr, 0, nullptr, 0, st));
     HIP_TRY(launch_second_pass_test(h, h2, b, gram(), kSecondPassRatio2, flag.p, st));

@@ -133,9 +133,9 @@ hipError_t launch_apply_rinv(double* basis, int64_t n, int64_t ld, int col0, int
 // The workgroups wait for one another.  If, after `polls` looks, one has not started yet (other work holds the compute units), the
 // launch leaves without having done anything, and so do all further ones with this sync, and the caller takes the step by other
 // launches.  Slots and *done may be in coherent host memory: *done becomes `number` when all workgroups are through and the slots
-// are written (-number: they had all started, but did not come to an end); it is not touched else.  base: the workgroups of all launches with this sync so far.
-// exchange: fused_exchange() doubles of all ones, which the launch writes; the first `clear` doubles of used, those of the launch
-// before, become all ones again (two such areas take turns).
+// are written (-number: they had all started, but did not come to an end); it is not touched else.  base: the workgroups of all
+// launches with this sync so far. exchange: fused_exchange() doubles of all ones, which the launch writes; the first `clear`
+// doubles of used, those of the launch before, become all ones again (two such areas take turns).
 constexpr int kFusedStepBlock = 8;
 constexpr int kFusedGroups = 256;   // workgroups at most
 constexpr int kFusedColumns = 256;  // j of launch_fused_step at most
@@ -208,8 +208,8 @@ hipError_t launch_block_extra_chunks(const int64_t* rowptr, const int32_t* start
 // workgroup, covering columns [col0, col0 + 8 cl); every (block, column) pair must be covered exactly once, extra must
 // be the block's extra-chunk count for chunks of 8 cl entries and nrows + extra <= resident_max_chunks(cl).
 // lds_bytes = the largest resident_item_lds_bytes over the items.  y must not alias x.
-// A sliced item (cl = sliced_shape(cols); the word's upper bits carry the item's first slot, the last word the block's extra rows) covers `cols`
-// = 16, 8 or 4 columns of a block for which resident_sliced_lds_bytes is within the limit, and reads its entries from the
+// A sliced item (cl = sliced_shape(cols); the word's upper bits carry the item's first slot, the last word the block's extra rows)
+// covers `cols` = 16, 8 or 4 columns of a block for which resident_sliced_lds_bytes is within the limit, and reads its entries from the
 // sliced copy (scol, sval, slice_base, slice_len, slice_first, row_extra; null when no item is sliced) made for that many columns.
 // d32 (0 <= d32 < d): the first d32 steps of the items with cl = 2 or 4 run in single precision (iterates and entries
 // rounded to float), the rest in double; sliced items take all steps in double.  0 gives the recurrence in double.
@@ -255,8 +255,8 @@ hipError_t sliced_copy_fill(const int64_t* rowptr, const int32_t* col, const dou
 int check_steps_needed(double theta, double kappa, int d, double lo, double a, int64_t n, int b);
 
 // Host part of the filter's plan alone (driver.hip), for tests: what a step is modelled to take, in seconds, for diagonal blocks of
-// rows starts[t] .. starts[t + 1] with the counts of launch_block_extra_chunks and b = 16 or 32 columns in a filter of `steps` steps; *nitems
-// = the work items.  Negative: there is no plan.
+// rows starts[t] .. starts[t + 1] with the counts of launch_block_extra_chunks and b = 16 or 32 columns in a filter of `steps`
+// steps; *nitems = the work items.  Negative: there is no plan.
 double resident_items_model(const int32_t* starts, const int32_t* counts, int nblk, int b, int64_t nnz, double steps,
                             int64_t lds_limit, int64_t* nitems);
 
@@ -361,8 +361,8 @@ hipError_t launch_label_listed(const double* x, int64_t ldx, int64_t n, const in
 // Labelling screened in bf16 (kmeans.hip): the same labels.  It pays from label_screen_steps labelling steps on (INT32_MAX:
 // never); 0 bytes where it is not made.  launch_label_copy makes the
 // reduced copy of the points, once (centring: ldx + 1 doubles, the points' mean and scale; centred: launch_kmeanspp has left them
-// there for the same points, else they are made: 100,000 x 100 43 us); launch_label_screened does a labelling step and leaves the number of points that the
-// screen could not decide, which were labelled in fp64, at changes[kChangeUndecided].
+// there for the same points, else they are made: 100,000 x 100 43 us); launch_label_screened does a labelling step and leaves the
+// number of points that the screen could not decide, which were labelled in fp64, at changes[kChangeUndecided].
 constexpr int kChangeUndecided = 1, kChangeSum = 2;
 int label_screen_steps(int64_t n, int64_t ldx, int k);
 size_t label_screen_workspace(int64_t n, int64_t ldx, int k);

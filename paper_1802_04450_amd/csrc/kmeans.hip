@@ -1,7 +1,7 @@
 // k-means on the rows of the eigenvector matrix (paper Section II Step 4, Section IV-C, Algorithms 4 and 5): device
 // kernels.  The distance step is the paper's expanded form S = |v|^2 + |c|^2 - 2 V C^T with the product on the fp64
-// matrix cores and the arg-min in the same launch (label_kernel, kernels.hip); |v|^2 does not change the arg-min and is left out.  The centre update
-// is sort based as in the paper (points ordered by label, every cluster a contiguous run), with a fixed summation
+// matrix cores and the arg-min in the same launch (label_kernel, kernels.hip); |v|^2 does not change the arg-min and is left out.
+// The centre update is sort based as in the paper (points ordered by label, every cluster a contiguous run), with a fixed summation
 // order so that results are reproducible.  The seeding follows Algorithm 5 with uniform numbers from a counter-based
 // generator; a draw is one distance pass that also leaves block sums and a walk over the sums, level by level, to the
 // drawn point: all draws in one launch where its workgroups are all on the chip (seed_draws_kernel), else a launch or two
@@ -340,8 +340,8 @@ __global__ __launch_bounds__(kT) void centroid_finish_kernel(const double* __res
 // to exceed the distance kept by 1e-6 of it: more than the fp64 sums are off.  A NaN on the way fails the test and the
 // point is computed; so is every point of data that have no such scale (scale 0: copies of zeros).
 // Per draw at 100,000 points of 100 coordinates: 18.7 us reading 80 MB, 11.3 us with the copy, which an XCD's L2 keeps
-// its part of from draw to draw (21 MB in all); what is left is the chain centre, its row, the point's row.  (Leaving points out by the triangle inequality with a kept assignment did
-// not shorten the pass: it saves no load of the first row.)
+// its part of from draw to draw (21 MB in all); what is left is the chain centre, its row, the point's row.  (Leaving points out
+// by the triangle inequality with a kept assignment did not shorten the pass: it saves no load of the first row.)
 constexpr int kSeedPoints = 64;   // points per block
 constexpr int kExactLanes = 16;
 // Up to this many blocks a pass finds its centre by itself: every workgroup reads all block sums once more, which then

@@ -396,8 +396,8 @@ __global__ __launch_bounds__(kMt) __attribute__((amdgpu_waves_per_eu(DP <= 32 ? 
 // 100,000 points of 32 coordinates, k = 20: 28.2 ms for the fp64 screen alone (22.7 TFLOP/s), 3.75 ms with
 // this one (two passes of 1.5 and 2.1 ms; 64 coordinates, k = 32: 61 -> 7.2 ms).  Data that it cannot settle pay for what
 // it did before that showed: 28.0 -> 29.1 ms for tight clusters far apart, 48.5 -> 53.2 ms with every 20th point the same
-// one, which leaves each tile of 64 queries to the fp64 kernel.  Bound by the matrix cores and, up to 32 coordinates, the vector work on the 16 results that a lane gets from
-// each tile (subtract, running maximum).
+// one, which leaves each tile of 64 queries to the fp64 kernel.  Bound by the matrix cores and, up to 32 coordinates, the vector
+// work on the 16 results that a lane gets from each tile (subtract, running maximum).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -1029,8 +1029,12 @@ double group_within(int64_t n, int dpb, int k) {
   return 0.095 * std::min(1.0, (double)n / 1e5) * std::min(1.0, std::max(0.5, std::pow(10.0 / k, 0.4)));
 }
 // Share of the plain passes' tile pairs up to which the lists are taken.  A cell's points come in the order of its counter's
-// additions, so the share of the same points differs from call to call (62,003 points of 2 coordinates, outliers among them, 300
-// calls: 0.240 to 0.256, 46 of them above 0.25 when the line was there).
+// additions, so the share of the same points differs a little from call to call (62,003 points of 2 coordinates, outliers among
+// them, 300 calls: 0.240 to 0.256), and calls close to the line may go either way.  They take the same time there: up to 16
+// coordinates the lists are the faster way below a share of about 0.2 and the slower one above 0.3, and in between it depends
+// on the points (grouped to plain once the lists are made: 0.215 0.87, 0.22 1.03, 0.24 0.87 and 1.12, 0.248 0.94, 0.251 0.92,
+// 0.253 1.08, 0.254 1.04, 0.255 0.91, 0.263 1.02, 0.268 1.05, 0.274 1.02, 0.275 0.98, 0.28 0.95, 0.284 1.07, 0.30 1.13, 0.31 1.17;
+// 62,003 to 250,000 points of 2 to 16 coordinates, 5 to 50 neighbours).
 double group_most(int dpb) { return dpb <= 16 ? 0.265 : dpb <= 32 ? 0.38 : 0.62; }
 
 struct GroupInfo {  // device
@@ -1359,8 +1363,8 @@ __device__ __forceinline__ float group_margin(const ScreenScale& s, int dp) {
   return (float)(2e-6 + 8.0 * sqrt((double)dp) * 2.3e-16 * s.max_abs * screen_factor(s));
 }
 
-// centre and radius of every tile; the centre's coordinates 4 c .. 4 c + 3 at centre[c stride + tile].  A wave per tile: 64 / dp rows at a time, a lane per
-// coordinate (two at 128).
+// centre and radius of every tile; the centre's coordinates 4 c .. 4 c + 3 at centre[c stride + tile].  A wave per tile: 64 / dp
+// rows at a time, a lane per coordinate (two at 128).
 template <int DP>
 __global__ __launch_bounds__(kT) void group_ball_kernel(const double* __restrict__ xp, const double* __restrict__ mean,
                                                         const ScreenScale* __restrict__ scale, const int32_t* __restrict__ src,

@@ -384,7 +384,8 @@ __device__ __forceinline__ void resident_item(const int64_t* __restrict__ rowptr
 // own row's recurrence reads it), and the entries read again in every step from a copy of the block made for that:
 //   * The block's rows in slices of RS = 64 / LPR rows, LPR = C / 4 lanes per row, four columns a lane; rows padded to the
 //     slice's longest with zero entries, in groups of four rounds: a lane gets a group's four column numbers with one 8-byte
-//     load and its values with two 16-byte loads, kSliceAhead groups before they are multiplied.  Columns are stored in units of 32 bytes of the iterate (16 bits).
+//     load and its values with two 16-byte loads, kSliceAhead groups before they are multiplied.  Columns are stored in units of
+//     32 bytes of the iterate (16 bits).
 //   * A row's entries beyond kSliceLong are extra rows of their own (hubs of several hundred entries beside rows of thirty
 //     would be what a step waits for): extra rows have slices like others, a lane parks its sum in LDS, and the row's owner
 //     adds the sums in order once the step's reads are over.  Where LDS has no room for these sums (a block of 1,000 rows with
@@ -676,8 +677,8 @@ __device__ __forceinline__ int slice_row(const SliceDesc& sd, int j, const int64
 }
 
 // The extra rows of the sliced blocks, blocks[kSliceBlockInts t ..] = (first row, rows, place of its first extra row in the
-// list, extra rows, columns, first slot, piece): list[.] = the row each belongs to, row_extra[r] = place of row r's first one within the block << 16 | their number.  A wave per
-// block.
+// list, extra rows, columns, first slot, piece): list[.] = the row each belongs to, row_extra[r] = place of row r's first one
+// within the block << 16 | their number.  A wave per block.
 __global__ __launch_bounds__(256) void slice_extra_kernel(const int64_t* __restrict__ rowptr, const int32_t* __restrict__ blocks,
                                                           int nblocks, int32_t* __restrict__ list,
                                                           int32_t* __restrict__ row_extra) {

@@ -3,10 +3,10 @@
 //
 // Algorithm 1 centres the data in place and gives one thread a row / an edge.  Here the data are read only: a first
 // kernel stores the mean and the norm of every row (of the centred row for the cross correlation), and the edge
-// kernel forms sum_t (x_it - m_i)(x_jt - m_j) directly, 4 or 16 lanes per edge with 16-byte loads.  Larger data are read bucket by bucket of rows, so that a row comes out of
-// memory a few times instead of once per pair.  The conversion puts the entries into buckets of rows and sorts each in
-// LDS; matrices that this does not suit go through rocPRIM's radix sort of (row, col) keys (a library primitive, the
-// counterpart of the paper's library call) with row pointers by binary search.
+// kernel forms sum_t (x_it - m_i)(x_jt - m_j) directly, 4 or 16 lanes per edge with 16-byte loads.  Larger data are read bucket by
+// bucket of rows, so that a row comes out of memory a few times instead of once per pair.  The conversion puts the entries into
+// buckets of rows and sorts each in LDS; matrices that this does not suit go through rocPRIM's radix sort of (row, col) keys (a
+// library primitive, the counterpart of the paper's library call) with row pointers by binary search.
 #include <hip/hip_runtime.h>
 #include <cstring>
 
@@ -644,7 +644,8 @@ __global__ __launch_bounds__(kET, 6) void edge_bucket_kernel(const double* __res
                                                           double inv_two_sigma2, const double* __restrict__ mean,
                                                           const double* __restrict__ norm, int64_t n,
                                                           double* __restrict__ val) {
-  // rows (group << shift) x dl less their means, their norms, the pairs' sums, the ordered pairs (second row, place of the value, bins, first row)
+  // rows (group << shift) x dl less their means, their norms, the pairs' sums, the ordered pairs (second row, place of the value,
+  // bins, first row)
   extern __shared__ __attribute__((aligned(16))) double rows[];
   __shared__ int32_t wave_sum[kET / 64], before[kMaxGroup + 1];
   __shared__ int32_t vmin, vmax;
@@ -1017,9 +1018,9 @@ hipError_t coo_to_csr(const int32_t* row, const int32_t* col, const double* val,
 
 namespace {
 
-// Rows of a bucket: a power of two that fits kEdgeRowBytes, about half a bucket's room of pairs.  Used where the data exceed what the L2s hold between them and a row occurs in several pairs:
-// 142,541 x 90 with 27 pairs a row 726 -> 478 us, 60,000 x 90 with 26 322 -> 226 us, 142,541 x 128 with 38 1,382 -> 535 us (now 215,
-// 121 and 355);
+// Rows of a bucket: a power of two that fits kEdgeRowBytes, about half a bucket's room of pairs.  Used where the data exceed what
+// the L2s hold between them and a row occurs in several pairs: 142,541 x 90 with 27 pairs a row 726 -> 478 us, 60,000 x 90 with 26
+// 322 -> 226 us, 142,541 x 128 with 38 1,382 -> 535 us (now 215, 121 and 355);
 // 142,541 x 33 with 27 448 -> 436 us, 30,000 x 64 with 26 115 -> 148 us, 142,541 x 90 with 3 111 -> 151 us.
 // Where that would be more buckets than a workgroup of the partition counts, they get up to twice the bytes: 142,541 x 200 with 27
 // pairs a row 1,660 -> 410 us, 1,000,000 x 64 with 27 4,030 -> 1,240, 300,000 x 128 with 10 random pairs a row 1,085 -> 705.

@@ -8,10 +8,7 @@
 namespace sceig {
 namespace {
 
-// Cholesky of the b x b Gram matrix in the registers of one wave: lane t owns column t of G, R and R^-1;
-// values of other columns travel by lane reads.  Same dropping rule as documented in kernels.h.
-// Value of lane `l` (a compile-time constant after unrolling) for the whole wave: a scalar lane read, not a trip
-// through the LDS crossbar.
+// Value of lane `l` (the same for the whole wave) for all lanes: a scalar lane read, not a trip through the LDS crossbar.
 __device__ __forceinline__ double bcast_lane(double v, int l) {
   const long long bits = __double_as_longlong(v);
   const int lo = __builtin_amdgcn_readlane((int)bits, l);
@@ -19,10 +16,11 @@ __device__ __forceinline__ double bcast_lane(double v, int l) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-// sqrt(p) and its inverse, and quotients by it, for the factorizations below: one approximate inverse root (v_rsq_f64),
+// sqrt(p) and its inverse, and quotients by it, for the factorization below: one approximate inverse root (v_rsq_f64),
 // two Newton steps, then root, inverse and quotients each corrected by their own remainder, as a division does.  Half the
-// dependent operations of a square root and a division, and the inverse serves the whole row and the triangular inverse
-// (a launch for b = 16: 9.2 -> 7.7 us; for b = 32, bound by the fetch of its code, 38.7 -> 36.6 us).  p > 0 and normal: it has passed the drop test.
+// dependent operations of a square root and a division, and the inverse serves the whole row of R and of the inverse (in
+// a factorization whose rows were straight-line code, a launch for b = 16: 9.2 -> 7.7 us).  p > 0 and normal: it has
+// passed the drop test.
 __device__ __forceinline__ void root_and_inverse(double p, double* root, double* inv) {
   double y = __builtin_amdgcn_rsq(p);
   const double h = 0.5 * p;
@@ -38,11 +36,11 @@ __device__ __forceinline__ double quotient(double a, double root, double inv) {
   return fma(fma(-q, root, a), inv, q);
 }
 
-// Cholesky with column drop and inverse by one wave (see launch_gram_cholesky): b <= 32.  g: b x b, row stride gs.  Lane t < b
-// holds column t of what is left of G, lane b + c column c of what elimination makes of the identity: the same operations
-// leave R and, row by row, the inverse of its transpose, so that the inverse takes no chain of its own.  Row k of both goes to
-// LDS, rows[k][0 .. b) = R[k], rows[k][b + c] = R^-1[c][k], from where all lanes read the entries of R[k] that they multiply by.
-// The columns move up by one a step, so that the loop is not unrolled: with a step per row in registers, entries by lane
+// Cholesky with column drop (the rule stands at launch_gram_cholesky in kernels.h) and inverse by one wave: b <= 32.  g: b x b,
+// row stride gs.  Lane t < b holds column t of what is left of G, lane b + c column c of what elimination makes of the identity:
+// the same operations leave R and, row by row, the inverse of its transpose, so that the inverse takes no chain of its own.  Row k
+// of both goes to LDS, rows[k][0 .. b) = R[k], rows[k][b + c] = R^-1[c][k], from where all lanes read the entries of R[k] that
+// they multiply by. The columns move up by one a step, so that the loop is not unrolled: with a step per row in registers, entries by lane
 // reads, the code (40 KB for b = 32) ran once and took as long as its fetch, and the inverse took as many steps again.
 // A launch for b = 32: 34 us, now 17; b = 16: 7.5, now 5.8; inside the one-launch QR, b = 16: 4.6, now 2.9.
 template <int B>
